@@ -1146,12 +1146,12 @@ int pgcm_describe_schedule(size_t n, const uint64_t* len, uint32_t unit_bytes, u
     return PGCM_OK;
 }
 
-size_t pgcm_key_tables_bytes(void) { return sizeof(KeyTables); }
+size_t pgcm_key_tables_bytes(void) { return kPublicTablesBytes; }
 
 int pgcm_copy_key_tables(pgcm_key_t* key, void* out, size_t bytes) {
     if (key == nullptr || key->tables == nullptr || (out == nullptr && bytes != 0))
         return PGCM_ERR_ARG;
-    if (bytes > sizeof(KeyTables)) bytes = sizeof(KeyTables);
+    if (bytes > kPublicTablesBytes) bytes = kPublicTablesBytes;
     PGCM_HIP(hipDeviceSynchronize());
     if (bytes != 0) PGCM_HIP(hipMemcpy(out, key->tables, bytes, hipMemcpyDeviceToHost));
     return PGCM_OK;

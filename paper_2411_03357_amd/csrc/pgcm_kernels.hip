@@ -186,6 +186,7 @@ __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict_
                                                           uint32_t nk) {
     __shared__ Gf powers[kNumPowers];
     __shared__ Gf lane_powers[kNumLanePowers];
+    __shared__ Gf row_powers[kHashImages];
     const uint32_t tid = threadIdx.x;
 
     // round tables: te[0][x] = (2s, s, s, 3s) in bytes 0..3, te[r] = te[0] rotated left by 8r bits
@@ -234,6 +235,8 @@ __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict_
         lane_powers[0] = gf_mul_bits(powers[1], powers[0]);  // H^3
         lane_powers[1] = gf_mul_bits(powers[3], powers[2]);  // H^12
         lane_powers[2] = gf_mul_bits(powers[5], powers[4]);  // H^48
+        row_powers[0] = powers[kRowPower];
+        row_powers[1] = gf_mul_bits(powers[kRowPower], powers[kRowPower - 1]);  // H^96
     }
     __syncthreads();
     for (uint32_t e = tid; e < kNumPowers * kNibbleTableEntries; e += blockDim.x) {
@@ -255,16 +258,18 @@ __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict_
         kt->ghash_lane[k][idx] = gf_to_block(gf_mul_bits(gf_from_block(x), lane_powers[k]));
     }
 
-    // Multiplication by H^64 as a 128 x 128 matrix over GF(2), laid out as operands of the
-    // 4-bit floating-point matrix instruction (see GhashRowMatrix): cols[b] = x^b * H^64 for the
-    // block whose only set bit is bit b % 32 of word b / 32.
-    __shared__ Block cols[128];
-    if (tid < 128) {
+    // Multiplications as 128 x 128 matrices over GF(2): cols[m][b] = x^b * H^64 (m = 0) or H^96
+    // (m = 1) for the block whose only set bit is bit b % 32 of word b / 32.
+    __shared__ Block cols[kHashImages][128];
+    if (tid < kHashImages * 128) {
+        const uint32_t m = tid / 128, bit = tid % 128;
         Block x{{0, 0, 0, 0}};
-        x.w[tid / 32] = 1u << (tid % 32);
-        cols[tid] = gf_to_block(gf_mul_bits(gf_from_block(x), powers[kRowPower]));
+        x.w[bit / 32] = 1u << (bit % 32);
+        cols[m][bit] = gf_to_block(gf_mul_bits(gf_from_block(x), row_powers[m]));
     }
     __syncthreads();
+    // H^64 with the bits of every operand quarter in a register of its own lane half (part of the
+    // published tables)
     for (uint32_t e = tid; e < kRowMatrixWords; e += blockDim.x) {
         const uint32_t r = e % 4, lane = (e / 4) % 64, ks = (e / 256) % 2, mt = e / 512;
         // the operand row this lane holds, the product bit it makes, the operand quarter
@@ -273,9 +278,24 @@ __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict_
         uint32_t v = 0;
         for (uint32_t j = 0; j < 8; ++j) {
             const uint32_t in = 32 * r + 4 * j + 2 * ks + h;
-            if ((cols[in].w[word] >> bit) & 1u) v |= 0x2u << (4 * j);  // 1.0 in e2m1
+            if ((cols[0][in].w[word] >> bit) & 1u) v |= 0x2u << (4 * j);  // 1.0 in e2m1
         }
         kt->row_matrix[e] = v;
+    }
+    // ... and both in the operand order of the unit kernel (see GhashRowMatrix)
+    for (uint32_t e = tid; e < kHashImages * kRowMatrixWords; e += blockDim.x) {
+        const uint32_t quarter = e % 4, lane = (e / 4) % 64, ks = (e / 256) % 2, mt = (e / 512) % 4,
+                       m = e / kRowMatrixWords;
+        const uint32_t ml = lane % 32, reg = 4 * (ml / 8) + ml % 4;
+        const uint32_t word = 2 * (mt / 2) + (ml / 4) % 2, bit = 16 * (reg / 8) + 8 * (mt % 2) + reg % 8;
+        // 2.0, 1.0, 0.5, 0.5 in e2m1 where the other operand has 0.5, 1.0, 2.0, 2.0
+        const uint32_t one = quarter == 0 ? 4u : quarter == 1 ? 2u : 1u;
+        uint32_t v = 0;
+        for (uint32_t j = 0; j < 8; ++j) {
+            const uint32_t in = 32 * (2 * ks + lane / 32) + 4 * j + quarter;
+            if ((cols[m][in].w[word] >> bit) & 1u) v |= one << (4 * j);
+        }
+        kt->hash_image[m][e % kRowMatrixWords] = v;
     }
 }
 
@@ -342,29 +362,36 @@ __global__ __launch_bounds__(64) void j0_kernel(const KeyTables* __restrict__ kt
 
 // ------------------------------------------------------------------------------------------
 // The bulk kernel.  LDS map (byte addresses; the object below is the kernel's only LDS):
-//   [0, 8 KiB)           nibble table of H^64 (entry offsets fit the 16-bit DS offset field)
-//   [8 KiB, 72 KiB)      row x (256 B): te[0][x] in dwords 0..31, te[1][x] in dwords 32..63
-//   [72 KiB, 136 KiB)    the same for te[2], te[3]
+//   [0, 16 KiB)          operands of the row hash: the matrix images of H^64 and H^96, or the nibble
+//                        table of H^64 (entry offsets fit the 16-bit DS offset field)
+//   [16 KiB, 80 KiB)     row x (256 B): te[0][x] in dwords 0..31, te[1][x] in dwords 32..63
+//   [80 KiB, 144 KiB)    the same for te[2], te[3]
+//   [144 KiB, 146 KiB)   every wavefront's second-round constants (see ctr_consts)
 // A round-table lookup address is  pair << 16 | x << 8 | 4 * (lane % 32)  plus a constant DS
 // offset, so lane l always reads bank l % 32: lookups never collide, whatever the data.
 namespace {
 
 constexpr uint32_t kLdsGhBytes = kNibbleTableEntries * 16;
-constexpr uint32_t kLdsTeBase = kLdsGhBytes;
+constexpr uint32_t kLdsTeBase = kHashImages * kLdsGhBytes;
 constexpr uint32_t kLdsTeBytes = 4 * 256 * 32 * 4;
-constexpr uint32_t kLdsBytes = kLdsGhBytes + kLdsTeBytes;
+// counter values that differ above their lowest byte and occur in one segment of a unit
+constexpr uint32_t kCtrEntries = 8;
+constexpr uint32_t kLdsCtrBase = kLdsTeBase + kLdsTeBytes;
+constexpr uint32_t kLdsBytes = kLdsCtrBase + kWavesPerGroup * kCtrEntries * 16;
 
 struct alignas(16) BulkLds {
-    Block gh[kNibbleTableEntries];
+    Block gh[kHashImages * kNibbleTableEntries];
     uint32_t te[kLdsTeBytes / 4];
+    Block ctr[kWavesPerGroup * kCtrEntries];
 };
 static_assert(sizeof(BulkLds) == kLdsBytes && offsetof(BulkLds, gh) == 0 &&
-                  offsetof(BulkLds, te) == kLdsTeBase,
+                  offsetof(BulkLds, te) == kLdsTeBase && offsetof(BulkLds, ctr) == kLdsCtrBase,
               "LDS map");
 
 typedef __attribute__((address_space(3))) const uint32_t* lds_u32_ptr;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) const u32x4* lds_u128_ptr;
+typedef __attribute__((address_space(3))) u32x4* lds_u128_wptr;
 typedef __attribute__((address_space(1))) const u32x4* global_u128_cptr;
 typedef __attribute__((address_space(1))) u32x4* global_u128_ptr;
 
@@ -436,6 +463,10 @@ __device__ __forceinline__ u32x4 lds_read128(uint32_t addr) {
     return *reinterpret_cast<lds_u128_ptr>(addr);
 }
 
+__device__ __forceinline__ void lds_write128(uint32_t addr, u32x4 v) {
+    *reinterpret_cast<lds_u128_wptr>(addr) = v;
+}
+
 // Round-table reads.  `a` already is pair << 16 | x << 8 | lane byte; T selects the table of the
 // pair through the constant part of the address, which also carries `base`, the LDS address of
 // the kernel's BulkLds object (a link-time constant, 0 when it is the kernel's only LDS object,
@@ -497,25 +528,72 @@ __device__ __forceinline__ void aes_addr_init(AesAddr& A, uint32_t lane,
     }
 }
 
-// The first three words of every counter block of a chunk are its IV, so in round 1 three of the
-// four lookups of each column do not depend on the block: their sums are formed once per unit.
+// What the first two rounds of a unit's counter blocks have in common.  The blocks differ in the
+// counter word only, and within a segment of at most kSegmentRows rows the counter takes few values
+// above its lowest byte.  The lowest byte reaches, in round 1, column 0 alone, whose other three
+// lookups depend on the IV only: k0 is their sum.  In round 2 that column feeds one lookup of every
+// column; the other three depend on the IV and the counter's upper bytes: their sums, four words,
+// are kept in LDS for every upper value the segment meets (lane i of the wavefront forms the one
+// i above the first).  So a block takes one lookup in round 1 and four in round 2 instead of
+// sixteen each, for 27 lookups per segment and one 16-byte read per row.  The kernel is bound by
+// LDS accesses and by the board's power together, and both go down: per row of 64 blocks 555 -> 532
+// LDS cycles and 448 -> 432 vector instructions, 1.424 -> 1.389 ms for 4096 chunks of 320 KiB
+// (AES-256, alternating on one box), against keeping only round 1's constant sums.
+constexpr uint32_t kSegmentRows = kUnitBlocks / kRowBlocks;
+static_assert(255 + (kSegmentRows + 1) * kRowBlocks <= 256 * kCtrEntries,
+              "upper counter values of a segment of kSegmentRows rows, or one more in unit 0");
 struct CtrConsts {
-    uint32_t k[4];
+    uint32_t k0;
+    uint32_t q_addr;  // LDS address of the wavefront's entries
+    // of the row at hand: this lane's block number in the segment plus the lowest byte of the
+    // segment's first counter, so that its lowest byte is the counter's and rel >> 8 the number
+    // of the upper counter value
+    uint32_t rel;
 };
 
+// The counter block of a row that stands alone (a unit of one row): no constants are formed, and
+// round 1 makes its sixteen lookups like any other.
+struct CtrBlock {
+    uint32_t iv0, iv1, iv2, ctr;
+};
+
+// first_ctr: the counter of the segment's first block (the same in every lane)
 __device__ __forceinline__ CtrConsts ctr_consts(const uint32_t* __restrict__ rk, uint32_t lane,
-                                                uint32_t iv0, uint32_t iv1, uint32_t iv2,
-                                                uint32_t base) {
+                                                uint32_t wave, uint32_t iv0, uint32_t iv1,
+                                                uint32_t iv2, uint32_t first_ctr, uint32_t base) {
     const uint32_t lo = (lane & 31) * 4, hi = lo | 0x10000u;
-    const uint32_t s0 = iv0 ^ rk[0], s1 = iv1 ^ rk[1], s2 = iv2 ^ rk[2];
     auto at = [&](uint32_t w, int k, uint32_t lane_bytes) {
         return (((w >> (8 * k)) & 0xFFu) << 8) | lane_bytes;
     };
+    const uint32_t upper = ((first_ctr >> 8) + lane) << 8;
+    const uint32_t s0 = iv0 ^ rk[0], s1 = iv1 ^ rk[1], s2 = iv2 ^ rk[2],
+                   s3 = bswap32(upper) ^ rk[3];
     CtrConsts c;
-    c.k[0] = te_read<0>(at(s0, 0, lo), base) ^ te_read<1>(at(s1, 1, lo), base) ^ te_read<2>(at(s2, 2, hi), base);
-    c.k[1] = te_read<0>(at(s1, 0, lo), base) ^ te_read<1>(at(s2, 1, lo), base) ^ te_read<3>(at(s0, 3, hi), base);
-    c.k[2] = te_read<0>(at(s2, 0, lo), base) ^ te_read<2>(at(s0, 2, hi), base) ^ te_read<3>(at(s1, 3, hi), base);
-    c.k[3] = te_read<1>(at(s0, 1, lo), base) ^ te_read<2>(at(s1, 2, hi), base) ^ te_read<3>(at(s2, 3, hi), base);
+    c.k0 = xor3(te_read<0>(at(s0, 0, lo), base), te_read<1>(at(s1, 1, lo), base),
+                te_read<2>(at(s2, 2, hi), base));
+    const uint32_t u1 = xor3(te_read<0>(at(s1, 0, lo), base), te_read<1>(at(s2, 1, lo), base),
+                             te_read<2>(at(s3, 2, hi), base)) ^
+                        te_read<3>(at(s0, 3, hi), base) ^ rk[5];
+    const uint32_t u2 = xor3(te_read<0>(at(s2, 0, lo), base), te_read<1>(at(s3, 1, lo), base),
+                             te_read<2>(at(s0, 2, hi), base)) ^
+                        te_read<3>(at(s1, 3, hi), base) ^ rk[6];
+    const uint32_t u3 = xor3(te_read<0>(at(s3, 0, lo), base), te_read<1>(at(s0, 1, lo), base),
+                             te_read<2>(at(s1, 2, hi), base)) ^
+                        te_read<3>(at(s2, 3, hi), base) ^ rk[7];
+    u32x4 q;
+    q.x = xor3(te_read<1>(at(u1, 1, lo), base), te_read<2>(at(u2, 2, hi), base),
+               te_read<3>(at(u3, 3, hi), base));
+    q.y = xor3(te_read<0>(at(u1, 0, lo), base), te_read<1>(at(u2, 1, lo), base),
+               te_read<2>(at(u3, 2, hi), base));
+    q.z = xor3(te_read<0>(at(u2, 0, lo), base), te_read<1>(at(u3, 1, lo), base),
+               te_read<3>(at(u1, 3, hi), base));
+    q.w = xor3(te_read<0>(at(u3, 0, lo), base), te_read<2>(at(u1, 2, hi), base),
+               te_read<3>(at(u2, 3, hi), base));
+    c.q_addr = base + kLdsCtrBase + wave * (kCtrEntries * 16);
+    if (lane < kCtrEntries) lds_write128(c.q_addr + lane * 16, q);
+    // the wavefront's own later reads come after this write: LDS serves a wavefront in order
+    asm volatile("" ::: "memory");
+    c.rel = (first_ctr & 0xFFu) + lane;
     return c;
 }
 
@@ -542,17 +620,37 @@ __device__ __forceinline__ uint32_t nibble_offset(uint32_t v, uint32_t mask_f0) 
     return r;
 }
 
-// Y * H^64 from the nibble table in LDS, cut into sixteen byte steps (two 16-byte lookups and
-// eight XORs each) so that the steps can be spread over the AES rounds of the same row: the
-// hash arithmetic then fills the time the wavefront would wait for round-table lookups.
+// The row hash.  An engine keeps a unit's hash state in four registers per lane, in a form of its
+// own, from row to row: start() clears it, begin() prepares a row's multiplication, its parts
+// ride along with the row's AES rounds, absorb() adds the row's ciphertext, home() leaves the
+// unit's 64 lane sums as blocks.
+
+// A unit of one row: its sums are its blocks, and nothing is multiplied.
+struct GhashNone {
+    static constexpr bool kMatrix = false, kTable = false;
+    uint32_t w[4];
+    __device__ __forceinline__ void begin() {}
+    __device__ __forceinline__ void absorb(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3) {
+        w[0] = c0, w[1] = c1, w[2] = c2, w[3] = c3;
+    }
+};
+
+// Y * H^64 in every lane, from the nibble table in LDS, cut into sixteen byte steps (two 16-byte
+// lookups and eight XORs each) so that the steps can be spread over the AES rounds of the same
+// row: the hash arithmetic then fills the time the wavefront would wait for round-table lookups.
 struct GhashRowMul {
-    static constexpr bool kMatrix = false;
+    static constexpr bool kMatrix = false, kTable = true;
     uint32_t table; // LDS address of the nibble table of H^64
-    uint32_t w[4];  // the multiplicand
+    uint32_t w[4];  // the state, and the multiplicand
     uint32_t t;     // current word << 4: its byte k carries the low nibble of byte k
-    uint32_t z0 = 0, z1 = 0, z2 = 0, z3 = 0;
+    uint32_t z0, z1, z2, z3;
     u32x4 ra, rb;
 
+    __device__ __forceinline__ void start(uint32_t lds_table, uint32_t) {
+        table = lds_table;
+        w[0] = w[1] = w[2] = w[3] = 0;
+    }
+    __device__ __forceinline__ void begin() { z0 = z1 = z2 = z3 = 0; }
     template <int S>
     __device__ __forceinline__ void issue() {
         constexpr int i = S / 4, k = S % 4;
@@ -576,186 +674,189 @@ struct GhashRowMul {
         issue<S>();
         consume();
     }
+    __device__ __forceinline__ void absorb(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3) {
+        w[0] = z0 ^ c0, w[1] = z1 ^ c1, w[2] = z2 ^ c2, w[3] = z3 ^ c3;
+    }
+    __device__ __forceinline__ void home(uint32_t y[4]) const {
+        y[0] = w[0], y[1] = w[1], y[2] = w[2], y[3] = w[3];
+    }
 };
 
-// Y * H^64 on the matrix cores.  Multiplication by a constant is linear over GF(2): product bit
-// m is the parity of the number of bits k with M[m][k] = Y[k] = 1, and the matrix instruction
-// counts those for 32 product bits of 32 lanes at once when every bit is spread out to a 4-bit
-// floating-point number (0 or 1.0).  Per row of 64 lanes: 4 product tiles x 2 column groups (lanes
-// 0..31, lanes 32..63) x 2 instructions of depth 64.  Products are scaled down into the denormal
-// range, where a float's pattern is the integer it counts in units of 2^-149 (the matrix
+// The same on the matrix cores, with the two halves of a row folded together.  The state is, lane
+// by lane, Z; a row turns it into
+//     Z'[0..31] = C[0..31],     Z'[32..63] = C[32..63] + Z[32..63] * H^64 + Z[0..31] * H^96,
+// which stands for the same sum of C(r, lane) * H^(64 * rows after r + 64 - lane) as a
+// multiplication of all 64 lanes by H^64 would: lane l's blocks are moved one row and 32
+// blocks on, to lane l + 32.  Only 32 products are left to be made per row, each a sum of two.
+// Multiplication by a constant is linear over GF(2): product bit m is the parity of the number of
+// bits k with M[m][k] = Z[k] = 1, and the matrix instruction counts those for 32 product bits of
+// 32 columns at once when every bit is spread out to a 4-bit floating-point number.  Per row: 4
+// product tiles x 2 factors x 2 instructions of depth 64.  Products are scaled down into the
+// denormal range, where a float's pattern is the integer it counts in units of 2^-149 (the matrix
 // pipeline keeps denormals, in its results and in the sum it continues from), and rows are
 // scaled apart: result register i of a lane counts in units of 2^(i % 8), and the second tile of
 // a pair shares the first one's registers, another 2^8 up.  So one register holds two counts
-// (each at most 128) whose lowest bits, the parities, sit at bits i % 8 and 8 + i % 8: one
-// masked OR per register collects them, eight registers to a half word.
-// No table lookups: the 8 KiB matrix image is read from LDS, 16 bytes per lane and instruction.
+// whose lowest bits, the parities, sit at bits i % 8 and 8 + i % 8: one masked OR per register
+// collects them, eight registers to a half word.  The two counts stay apart because neither
+// reaches 256: a row of M that is all ones belongs to one constant only (bit m of x * h as a
+// function of x is another one for every h), so both factors' rows could only be all ones
+// with H^64 = H^96, that is H = 1 (or 0), whose matrix has single ones.
+// No table lookups: the matrix images (16 KiB) are read from LDS, 16 bytes per lane and
+// instruction.  Per row that leaves 467 LDS cycles of the 532 the nibble table needs and 3 % fewer
+// cycles in all, but the matrix pipeline draws so much more power that the chip, at its limit
+// of 1400 W under either engine, clocks at 2.15 instead of 2.23 GHz: 1.40 ms against 1.38 ms for
+// 4096 chunks of 320 KiB.  So the table is the default.
 //
 // Operand layout of v_mfma_scale_f32_32x32x64_f8f6f4 with 4-bit operands: lane l holds row (or
 // column) l % 32, depth elements 32 (l / 32) .. + 31, eight to a register, lowest nibble first;
 // one scale (a power of two, biased by 127, in byte 0) per lane.  Result register i of lane l is
 // row 8 (i / 4) + 4 (l / 32) + i % 4 of column l % 32.
-// Depth element <-> bit of Y: quarter c = 0..3 of the depth holds bits 4 j + c of the four words,
-// left where they are inside their nibble (worth 0.5, 1.0, 2.0; bit 3 would be the sign and is
-// moved down one place), the lane's scale making up for it.  A column's quarters 0, 2 belong in
-// lanes 0..31 and 1, 3 in lanes 32..63: one swap of lane halves per register serves both groups.
-// Product bit <-> row: lanes 0..31 make words 0 and 1 of both groups' columns, lanes 32..63
-// words 2 and 3; tile pair p makes word 2 (l / 32) + p, register i of tile 2 p + f its bit
-// 16 (i / 8) + 8 f + i % 8 (KeyTables::row_matrix is laid out to match).
+// Depth element <-> bit of Z: slice s of the depth is words 2 s (lanes 0..31) and 2 s + 1 (lanes
+// 32..63); register c of it holds bits 4 j + c, left where they are inside their nibble (worth 0.5,
+// 1.0, 2.0; bit 3 would be the sign and is moved down one place), which the matrix entries make
+// up for (2.0, 1.0, 0.5, 0.5).
+// Product bit <-> row: tile pair p makes word 2 p in lanes 0..31 and word 2 p + 1 in lanes 32..63,
+// register i of tile 2 p + f its bit 16 (i / 8) + 8 f + i % 8 (KeyTables::hash_image is laid out to
+// match).  So a result comes in the very lanes in which the next row needs it as operand, and the
+// state is kept like that: lo[s], hi[s] are words 2 s (lanes 0..31) and 2 s + 1 (lanes 32..63) of
+// lanes 0..31 and of lanes 32..63; two swaps of lane halves bring a row's ciphertext there.
 typedef int v8i32 __attribute__((ext_vector_type(8)));
 typedef float v16f32 __attribute__((ext_vector_type(16)));
 
 struct GhashRowMatrix {
-    static constexpr bool kMatrix = true;
-    uint32_t image;    // LDS address of this lane's first piece of the matrix image
-    uint32_t scale_b;  // scale of this lane's quarter of the first depth slice
+    static constexpr bool kMatrix = true, kTable = false;
+    uint32_t image;    // LDS address of this lane's first piece of the matrix images
     uint32_t scale_a;  // scale of this lane's matrix row in the first tile of a pair
     uint32_t scale_a2; // ... in the second
-    uint32_t q[4][4];  // operand quarters; after begin(): q[g], q[2 + g] are group g's operands
-    uint32_t out[2][2];
+    uint32_t lo[2], hi[2];
+    uint32_t q[2][2][4];  // [factor: hi with H^64, lo with H^96][slice][bits 4 j + c]
+    uint32_t out[2];
     u32x4 a0, a1;
     v16f32 acc;
-    uint32_t z0, z1, z2, z3;
 
-    // matrix entries (1.0) are scaled to 2^-127 and up, the other operand's to 2^-22
-    static constexpr int kScaleHalf = 127 - 23;  // quarters 2 and 3 hold 2.0
+    // matrix rows are scaled to 2^-127 and up, the other operand to 2^-22
+    static constexpr int kScaleB = 127 - 22;
 
-    __device__ __forceinline__ void init(uint32_t lds_table, uint32_t lane) {
+    __device__ __forceinline__ void start(uint32_t lds_table, uint32_t lane) {
         image = lds_table + lane * 16;
-        scale_b = lane < 32 ? 127u - 21u : 127u - 22u;  // quarter 0 holds 0.5, quarter 1 1.0
         const uint32_t row = lane & 31, reg = 4 * (row / 8) + row % 4;
         scale_a = reg % 8;  // 2^(reg % 8 - 127)
         scale_a2 = scale_a + 8;
+        lo[0] = lo[1] = hi[0] = hi[1] = 0;
     }
-    __device__ __forceinline__ void begin(const uint32_t w[4]) {
+    __device__ __forceinline__ void begin() {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            q[0][i] = w[i] & 0x11111111u;
-            q[1][i] = w[i] & 0x22222222u;
-            q[2][i] = w[i] & 0x44444444u;
-            q[3][i] = (w[i] >> 1) & 0x44444444u;
-        }
+        for (int m = 0; m < 2; ++m)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            // lanes 32..63 of the first operand change places with lanes 0..31 of the second
-            auto a = __builtin_amdgcn_permlane32_swap(q[0][i], q[1][i], false, false);
-            q[0][i] = a[0], q[1][i] = a[1];
-            auto b = __builtin_amdgcn_permlane32_swap(q[2][i], q[3][i], false, false);
-            q[2][i] = b[0], q[3][i] = b[1];
-        }
+            for (int s = 0; s < 2; ++s) {
+                const uint32_t w = m == 0 ? hi[s] : lo[s];
+                q[m][s][0] = w & 0x11111111u;
+                q[m][s][1] = w & 0x22222222u;
+                q[m][s][2] = w & 0x44444444u;
+                q[m][s][3] = (w >> 1) & 0x44444444u;
+            }
     }
-    // Chain C = 2 * pair + group is four instructions into one set of sums, in two halves F
-    // (the pair's tiles), each in three steps that the caller spreads over an AES round: the
-    // tile's two matrix pieces are fetched, the first instruction starts or continues the sums,
-    // the second (which has to wait for the first) follows.
-    template <int C, int F>
+    // Step I = 0 .. 7: chain I / 4 (a tile pair: eight instructions into one set of sums), tile
+    // (I / 2) % 2 of it, factor I % 2; each in three parts that the caller spreads over an AES
+    // round: the two matrix pieces are fetched, the first instruction starts or continues the
+    // sums, the second (which has to wait for the first) follows.
+    template <int I>
     __device__ __forceinline__ void load() {
-        constexpr int mt = 2 * (C / 2) + F;
-        a0 = lds_read128(image + (mt * 2 + 0) * 1024);
-        a1 = lds_read128(image + (mt * 2 + 1) * 1024);
+        constexpr int piece = ((I % 2) * 4 + 2 * (I / 4) + (I / 2) % 2) * 2;
+        a0 = lds_read128(image + piece * 1024);
+        a1 = lds_read128(image + (piece + 1) * 1024);
     }
-    template <int C, int F>
-    __device__ __forceinline__ void first() {
-        constexpr int g = C % 2;
-        const v8i32 A0 = {(int)a0.x, (int)a0.y, (int)a0.z, (int)a0.w, 0, 0, 0, 0};
-        const v8i32 B0 = {(int)q[g][0], (int)q[g][1], (int)q[g][2], (int)q[g][3], 0, 0, 0, 0};
-        if constexpr (F == 0) {
+    template <int I, int S>
+    __device__ __forceinline__ void product() {
+        constexpr int m = I % 2, f = (I / 2) % 2;
+        const u32x4 a = S == 0 ? a0 : a1;
+        const v8i32 A = {(int)a.x, (int)a.y, (int)a.z, (int)a.w, 0, 0, 0, 0};
+        const v8i32 B = {(int)q[m][S][0], (int)q[m][S][1], (int)q[m][S][2], (int)q[m][S][3],
+                         0, 0, 0, 0};
+        if constexpr (I % 4 == 0 && S == 0) {
             const v16f32 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f,
                                  0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-            acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A0, B0, zero, 4, 4, 0,
-                                                                   (int)scale_a, 0, (int)scale_b);
+            acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                A, B, zero, 4, 4, 0, (int)(f == 0 ? scale_a : scale_a2), 0, kScaleB);
         } else {
-            acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A0, B0, acc, 4, 4, 0,
-                                                                   (int)scale_a2, 0, (int)scale_b);
+            acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                A, B, acc, 4, 4, 0, (int)(f == 0 ? scale_a : scale_a2), 0, kScaleB);
         }
-    }
-    template <int C, int F>
-    __device__ __forceinline__ void second() {
-        constexpr int g = C % 2;
-        const v8i32 A1 = {(int)a1.x, (int)a1.y, (int)a1.z, (int)a1.w, 0, 0, 0, 0};
-        const v8i32 B1 = {(int)q[2 + g][0], (int)q[2 + g][1], (int)q[2 + g][2], (int)q[2 + g][3],
-                          0, 0, 0, 0};
-        acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-            A1, B1, acc, 4, 4, 0, (int)(F == 0 ? scale_a : scale_a2), 0, kScaleHalf);
     }
     // the chain's thirty-two parities: registers 0..7 give the low half word, 8..15 the high
     template <int C>
     __device__ __forceinline__ void consume() {
-        uint32_t lo = __float_as_uint(acc[0]) & 0x0101u, hi = __float_as_uint(acc[8]) & 0x0101u;
+        uint32_t l = __float_as_uint(acc[0]) & 0x0101u, h = __float_as_uint(acc[8]) & 0x0101u;
 #pragma unroll
         for (int i = 1; i < 8; ++i) {
             // (sum & mask) | collected, in one instruction (truth table 0xEA)
             const uint32_t mask = 0x0101u << i;
-            lo = __builtin_amdgcn_bitop3_b32(__float_as_uint(acc[i]), mask, lo, 0xEA);
-            hi = __builtin_amdgcn_bitop3_b32(__float_as_uint(acc[8 + i]), mask, hi, 0xEA);
+            l = __builtin_amdgcn_bitop3_b32(__float_as_uint(acc[i]), mask, l, 0xEA);
+            h = __builtin_amdgcn_bitop3_b32(__float_as_uint(acc[8 + i]), mask, h, 0xEA);
         }
-        out[C % 2][C / 2] = (hi << 16) | lo;
+        out[C] = (h << 16) | l;
+        // pinned here: otherwise the optimizer moves the whole chain to where its result is used
+        asm volatile("" : "+v"(out[C]));
     }
-    // lanes 0..31 made words 0, 1 of both groups' columns, lanes 32..63 words 2, 3: the halves
-    // of every column come home
-    __device__ __forceinline__ void finish() {
-        auto r0 = __builtin_amdgcn_permlane32_swap(out[0][0], out[1][0], false, false);
-        auto r1 = __builtin_amdgcn_permlane32_swap(out[0][1], out[1][1], false, false);
-        z0 = r0[0], z1 = r1[0], z2 = r0[1], z3 = r1[1];
+    __device__ __forceinline__ void absorb(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3) {
+        // lanes 32..63 of the first word change places with lanes 0..31 of the second
+        const auto r0 = __builtin_amdgcn_permlane32_swap(c0, c1, false, false);
+        const auto r1 = __builtin_amdgcn_permlane32_swap(c2, c3, false, false);
+        lo[0] = r0[0], hi[0] = r0[1] ^ out[0];
+        lo[1] = r1[0], hi[1] = r1[1] ^ out[1];
+    }
+    __device__ __forceinline__ void home(uint32_t y[4]) const {
+        const auto r0 = __builtin_amdgcn_permlane32_swap(lo[0], hi[0], false, false);
+        const auto r1 = __builtin_amdgcn_permlane32_swap(lo[1], hi[1], false, false);
+        y[0] = r0[0], y[1] = r0[1], y[2] = r1[0], y[3] = r1[1];
     }
 };
 
-// E_K(J0[0..95] || be32(ctr)) for this lane's counter, with the row's GHASH multiplication G
-// riding along; rk is wave-uniform (scalar registers).  Between rounds the state is carried
-// without its round key: the key bytes are added while the next round's addresses are formed.
-// The sixteen byte steps of G: three in round 1, the other thirteen spread evenly over rounds
-// 2 .. kRounds (one each for AES-256, one or two each for the shorter keys).
-// On the matrix cores the multiplication is four chains of four instructions instead: chain c is
-// issued in rounds 2 c + 2 and 2 c + 3 (two matrix pieces fetched ahead of each round's lookups,
+// Rounds kFirst .. kRounds of AES with the row's GHASH multiplication G riding along; rk is
+// wave-uniform (scalar registers).  Between rounds the state u0 .. u3 is carried without its round
+// key: the key bytes are added while the next round's addresses are formed.  With kFirst = 1 the
+// addresses of round 1 are in A already.
+// The byte steps of a table hash from step 4 on are spread evenly over rounds 3 .. kRounds (one
+// each for AES-256, one or two each for the shorter keys).
+// On the matrix cores the multiplication is two chains of eight instructions instead: chain c is
+// issued in rounds 4 c + 3 .. 4 c + 6 (two matrix pieces fetched ahead of each round's lookups,
 // two instructions, one before and one after the round's sums) and its result packed in the
-// middle of round 2 c + 4, so that neither the fetch nor the matrix pipeline is waited for.
-template <int kRounds, class Hash>
-__device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, AesAddr& A,
-                                               const CtrConsts& C, uint32_t ctr, Hash& G,
-                                               uint32_t base, uint32_t& o0, uint32_t& o1,
+// middle of the round after, so that neither the fetch nor the matrix pipeline is waited for.
+template <int kFirst, int kRounds, class Hash>
+__device__ __forceinline__ void aes_rounds_lds(const uint32_t* __restrict__ rk, AesAddr& A,
+                                               uint32_t u0, uint32_t u1, uint32_t u2, uint32_t u3,
+                                               Hash& G, uint32_t base, uint32_t& o0, uint32_t& o1,
                                                uint32_t& o2, uint32_t& o3) {
-    static_assert(kRounds >= 10, "eight chains and their packing need rounds 2 .. 10");
-    // round 1: the counter is the last word, big endian: state byte k is counter byte 3 - k
-    key_xor_into_addr<3, 0>(A.a[3][3], rk[3], ctr);
-    key_xor_into_addr<2, 1>(A.a[3][2], rk[3], ctr);
-    key_xor_into_addr<1, 2>(A.a[3][1], rk[3], ctr);
-    key_xor_into_addr<0, 3>(A.a[3][0], rk[3], ctr);
-    uint32_t l0 = te_read<3>(A.a[3][3], base), l1 = te_read<2>(A.a[3][2], base), l2 = te_read<1>(A.a[3][1], base),
-             l3 = te_read<0>(A.a[3][0], base);
-    if constexpr (!Hash::kMatrix) G.template issue<0>();
-    uint32_t u0 = C.k[0] ^ l0, u1 = C.k[1] ^ l1, u2 = C.k[2] ^ l2, u3 = C.k[3] ^ l3;
-    if constexpr (!Hash::kMatrix) {
-        G.consume();
-        G.template step<1>();
-        G.template step<2>();
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    static_for<2, kRounds + 1>([&](auto round) __attribute__((always_inline)) {
+    static_assert(kRounds >= 10, "eight pairs of matrix instructions in rounds 3 .. 10");
+    static_for<kFirst, kRounds + 1>([&](auto round) __attribute__((always_inline)) {
         constexpr int r = decltype(round)::value;
-        constexpr int step_begin = 3 + (13 * (r - 2)) / (kRounds - 1),
-                      step_end = 3 + (13 * (r - 1)) / (kRounds - 1);
-        static_assert(step_end - step_begin == 1 || step_end - step_begin == 2, "hash steps");
+        constexpr int step_begin = 4 + (12 * (r - 3)) / (kRounds - 2),
+                      step_end = 4 + (12 * (r - 2)) / (kRounds - 2);
+        static_assert(!Hash::kTable || step_end - step_begin == 1 || step_end - step_begin == 2,
+                      "hash steps");
         const uint32_t* k = rk + 4 * (r - 1);
         if constexpr (Hash::kMatrix) {
-            if constexpr (r <= 9) G.template load<(r - 2) / 2, (r - 2) % 2>();
+            if constexpr (r <= 10) G.template load<r - 3>();
             __builtin_amdgcn_sched_barrier(0);
         }
-        key_xor_into_addr<0, 0>(A.a[0][0], k[0], u0);
-        key_xor_into_addr<1, 1>(A.a[0][1], k[0], u0);
-        key_xor_into_addr<2, 2>(A.a[0][2], k[0], u0);
-        key_xor_into_addr<3, 3>(A.a[0][3], k[0], u0);
-        key_xor_into_addr<0, 0>(A.a[1][0], k[1], u1);
-        key_xor_into_addr<1, 1>(A.a[1][1], k[1], u1);
-        key_xor_into_addr<2, 2>(A.a[1][2], k[1], u1);
-        key_xor_into_addr<3, 3>(A.a[1][3], k[1], u1);
-        key_xor_into_addr<0, 0>(A.a[2][0], k[2], u2);
-        key_xor_into_addr<1, 1>(A.a[2][1], k[2], u2);
-        key_xor_into_addr<2, 2>(A.a[2][2], k[2], u2);
-        key_xor_into_addr<3, 3>(A.a[2][3], k[2], u2);
-        key_xor_into_addr<0, 0>(A.a[3][0], k[3], u3);
-        key_xor_into_addr<1, 1>(A.a[3][1], k[3], u3);
-        key_xor_into_addr<2, 2>(A.a[3][2], k[3], u3);
-        key_xor_into_addr<3, 3>(A.a[3][3], k[3], u3);
+        if constexpr (r > 1) {
+            key_xor_into_addr<0, 0>(A.a[0][0], k[0], u0);
+            key_xor_into_addr<1, 1>(A.a[0][1], k[0], u0);
+            key_xor_into_addr<2, 2>(A.a[0][2], k[0], u0);
+            key_xor_into_addr<3, 3>(A.a[0][3], k[0], u0);
+            key_xor_into_addr<0, 0>(A.a[1][0], k[1], u1);
+            key_xor_into_addr<1, 1>(A.a[1][1], k[1], u1);
+            key_xor_into_addr<2, 2>(A.a[1][2], k[1], u1);
+            key_xor_into_addr<3, 3>(A.a[1][3], k[1], u1);
+            key_xor_into_addr<0, 0>(A.a[2][0], k[2], u2);
+            key_xor_into_addr<1, 1>(A.a[2][1], k[2], u2);
+            key_xor_into_addr<2, 2>(A.a[2][2], k[2], u2);
+            key_xor_into_addr<3, 3>(A.a[2][3], k[2], u2);
+            key_xor_into_addr<0, 0>(A.a[3][0], k[3], u3);
+            key_xor_into_addr<1, 1>(A.a[3][1], k[3], u3);
+            key_xor_into_addr<2, 2>(A.a[3][2], k[3], u3);
+            key_xor_into_addr<3, 3>(A.a[3][3], k[3], u3);
+        }
         uint32_t t00 = te_read<0>(A.a[0][0], base), t11 = te_read<1>(A.a[1][1], base),
                  t22 = te_read<2>(A.a[2][2], base), t33 = te_read<3>(A.a[3][3], base);
         uint32_t t10 = te_read<0>(A.a[1][0], base), t21 = te_read<1>(A.a[2][1], base),
@@ -766,12 +867,12 @@ __device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, Aes
                  t12 = te_read<2>(A.a[1][2], base), t23 = te_read<3>(A.a[2][3], base);
         if constexpr (Hash::kMatrix) {
             __builtin_amdgcn_sched_barrier(0);
-            if constexpr (r >= 4 && r <= 10 && r % 2 == 0) G.template consume<(r - 4) / 2>();
-            if constexpr (r <= 9) G.template first<(r - 2) / 2, (r - 2) % 2>();
+            if constexpr (r == 7) G.template consume<0>();
+            if constexpr (r == 11) G.template consume<1>();
+            if constexpr (r <= 10) G.template product<r - 3, 0>();
             __builtin_amdgcn_sched_barrier(0);
-        } else {
-            G.template issue<step_begin>();
         }
+        if constexpr (Hash::kTable) G.template issue<step_begin>();
         if constexpr (r < kRounds) {
             u0 = xor3(t00, t11, t22) ^ t33;
             u1 = xor3(t10, t21, t32) ^ t03;
@@ -791,11 +892,12 @@ __device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, Aes
             o3 = last(t30, t01, t12, t23, A.last_key[3]);
         }
         if constexpr (Hash::kMatrix) {
-            if constexpr (r <= 9) {
+            if constexpr (r <= 10) {
                 __builtin_amdgcn_sched_barrier(0);  // after the round's sums, not before
-                G.template second<(r - 2) / 2, (r - 2) % 2>();
+                G.template product<r - 3, 1>();
             }
-        } else {
+        }
+        if constexpr (Hash::kTable) {
             G.consume();
             if constexpr (step_end - step_begin == 2) G.template step<step_begin + 1>();
         }
@@ -803,6 +905,64 @@ __device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, Aes
         // hash XORs to the end of the block and spills the table entries they wait for
         __builtin_amdgcn_sched_barrier(0);
     });
+    if constexpr (Hash::kMatrix && kRounds == 10) G.template consume<1>();
+}
+
+// E_K(J0[0..95] || be32(ctr)) for this lane's counter, in a row of a unit of several: rounds 1 and
+// 2 from the unit's constants, with two byte steps of a table hash each.
+template <int kRounds, class Hash>
+__device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, AesAddr& A,
+                                            const CtrConsts& C, Hash& G, uint32_t base,
+                                            uint32_t& o0, uint32_t& o1, uint32_t& o2,
+                                            uint32_t& o3) {
+    const u32x4 q = lds_read128(C.q_addr + ((C.rel >> 4) & (16 * (kCtrEntries - 1))));
+    // round 1: the counter is the last word, big endian: its lowest byte is state byte 3
+    key_xor_into_addr<3, 0>(A.a[3][3], rk[3], C.rel);
+    uint32_t u0 = te_read<3>(A.a[3][3], base) ^ C.k0;
+    if constexpr (Hash::kTable) {
+        G.template step<0>();
+        G.template step<1>();
+    }
+    // round 2: column 0 alone depends on the lowest counter byte
+    key_xor_into_addr<0, 0>(A.a[0][0], rk[4], u0);
+    key_xor_into_addr<1, 1>(A.a[0][1], rk[4], u0);
+    key_xor_into_addr<2, 2>(A.a[0][2], rk[4], u0);
+    key_xor_into_addr<3, 3>(A.a[0][3], rk[4], u0);
+    u0 = te_read<0>(A.a[0][0], base) ^ q.x;
+    const uint32_t u3 = te_read<1>(A.a[0][1], base) ^ q.w, u2 = te_read<2>(A.a[0][2], base) ^ q.z,
+                   u1 = te_read<3>(A.a[0][3], base) ^ q.y;
+    if constexpr (Hash::kTable) {
+        G.template step<2>();
+        G.template step<3>();
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    aes_rounds_lds<3, kRounds>(rk, A, u0, u1, u2, u3, G, base, o0, o1, o2, o3);
+}
+
+// ... and in a row that stands alone
+template <int kRounds>
+__device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, AesAddr& A,
+                                            const CtrBlock& C, GhashNone& G, uint32_t base,
+                                            uint32_t& o0, uint32_t& o1, uint32_t& o2,
+                                            uint32_t& o3) {
+    key_xor_into_addr<0, 0>(A.a[0][0], rk[0], C.iv0);
+    key_xor_into_addr<1, 1>(A.a[0][1], rk[0], C.iv0);
+    key_xor_into_addr<2, 2>(A.a[0][2], rk[0], C.iv0);
+    key_xor_into_addr<3, 3>(A.a[0][3], rk[0], C.iv0);
+    key_xor_into_addr<0, 0>(A.a[1][0], rk[1], C.iv1);
+    key_xor_into_addr<1, 1>(A.a[1][1], rk[1], C.iv1);
+    key_xor_into_addr<2, 2>(A.a[1][2], rk[1], C.iv1);
+    key_xor_into_addr<3, 3>(A.a[1][3], rk[1], C.iv1);
+    key_xor_into_addr<0, 0>(A.a[2][0], rk[2], C.iv2);
+    key_xor_into_addr<1, 1>(A.a[2][1], rk[2], C.iv2);
+    key_xor_into_addr<2, 2>(A.a[2][2], rk[2], C.iv2);
+    key_xor_into_addr<3, 3>(A.a[2][3], rk[2], C.iv2);
+    // the counter word is big endian: state byte k is counter byte 3 - k
+    key_xor_into_addr<0, 3>(A.a[3][0], rk[3], C.ctr);
+    key_xor_into_addr<1, 2>(A.a[3][1], rk[3], C.ctr);
+    key_xor_into_addr<2, 1>(A.a[3][2], rk[3], C.ctr);
+    key_xor_into_addr<3, 0>(A.a[3][3], rk[3], C.ctr);
+    aes_rounds_lds<1, kRounds>(rk, A, 0, 0, 0, 0, G, base, o0, o1, o2, o3);
 }
 
 // Y * C from C's nibble table at LDS address `base`, on its own (not riding along with AES):
@@ -839,16 +999,15 @@ __device__ __forceinline__ void ghash_mul_lds(uint32_t base, uint32_t y[4]) {
 // the AAD state; idle lanes run the cipher on a dummy counter, touch no payload and keep a zero
 // hash state.
 // kThrough: the payload is written through to memory (see global_write128_through).
-// kMatrixHash: the hash multiplication runs on the matrix cores; the first 8 KiB of the LDS
-// object then hold the matrix image instead of the nibble table.
+// G: the row hash engine, on the matrix cores or from a table.
 // `edge` is the same in every lane and held in a scalar register (walk_unit sees to that), so
 // the rows that are no edge rows branch past all of the checks.
-template <bool kDecrypt, int kRounds, bool kThrough = false, bool kMatrixHash = false>
+template <bool kDecrypt, int kRounds, bool kThrough, class Ctr, class Hash>
 __device__ __forceinline__ void bulk_row(const uint32_t* __restrict__ rk, AesAddr& A,
-                                         const CtrConsts& C, uint32_t ctr1, const uint8_t* src,
+                                         const Ctr& C, const uint8_t* src,
                                          uint8_t* dst, uint64_t len, int64_t blk, bool edge,
                                          const Block& aad_y, Block* __restrict__ ekj0_out,
-                                         uint32_t lds_base, uint32_t y[4]) {
+                                         uint32_t lds_base, Hash& G) {
     bool active = true;
     uint32_t tail = 0;  // bytes in a ragged block, 0 = whole block
     bool whole = true;
@@ -881,20 +1040,10 @@ __device__ __forceinline__ void bulk_row(const uint32_t* __restrict__ rk, AesAdd
         }
     }
 
-    // counter block inc32^(blk + 1)(J0): the first 96 bits of J0, then its counter field plus
-    // blk + 1 modulo 2^32 (SP 800-38D 6.2, 7.1 step 3; ctr1 is that field plus 1, 2 for a 96-bit
-    // IV) ... while the hash state moves one row along: Y <- Y * H^64
-    std::conditional_t<kMatrixHash, GhashRowMatrix, GhashRowMul> G;
-    if constexpr (kMatrixHash) {
-        G.init(lds_base, __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)));
-        G.begin(y);
-    } else {
-        G.table = lds_base;  // the nibble table is the first member of BulkLds
-        G.w[0] = y[0], G.w[1] = y[1], G.w[2] = y[2], G.w[3] = y[3];
-    }
+    // the keystream block ... while the hash state moves one row along
+    G.begin();
     uint32_t s0, s1, s2, s3;
-    aes_ctr_lds<kRounds>(rk, A, C, (uint32_t)blk + ctr1, G, lds_base, s0, s1, s2, s3);
-    if constexpr (kMatrixHash) G.finish();
+    aes_ctr_lds<kRounds>(rk, A, C, G, lds_base, s0, s1, s2, s3);
     uint32_t o0 = x0 ^ s0, o1 = x1 ^ s1, o2 = x2 ^ s2, o3 = x3 ^ s3;
 
     auto store_block = [&]() __attribute__((always_inline)) {
@@ -945,7 +1094,7 @@ __device__ __forceinline__ void bulk_row(const uint32_t* __restrict__ rk, AesAdd
         }
         if (!active) c0 = c1 = c2 = c3 = 0;  // idle lanes only occur before a chunk's start: Y = 0
     }
-    y[0] = G.z0 ^ c0, y[1] = G.z1 ^ c1, y[2] = G.z2 ^ c2, y[3] = G.z3 ^ c3;
+    G.absorb(c0, c1, c2, c3);
 }
 
 }  // namespace
@@ -957,7 +1106,7 @@ namespace {
 // sixteen 16-byte pieces, eight per table of its pair; every thread fetches the eight entries
 // its pieces need at once (independent loads) and writes each four times over in one store, and
 // a wavefront's store covers four whole rows, so the stores run at the full LDS width.
-template <bool kMatrixHash = false>
+template <bool kMatrixHash>
 __device__ __forceinline__ void fill_bulk_lds(BulkLds& lds, const KeyTables* __restrict__ kt,
                                               uint32_t tid) {
     constexpr uint32_t kPieces = kLdsTeBytes / 16;
@@ -976,21 +1125,22 @@ __device__ __forceinline__ void fill_bulk_lds(BulkLds& lds, const KeyTables* __r
         const u32x4 q = {v[k], v[k], v[k], v[k]};
         te4[k * kGroupThreads + tid] = q;
     }
-    for (uint32_t i = tid; i < kNibbleTableEntries; i += kGroupThreads) {
-        if constexpr (kMatrixHash)
-            lds.gh[i] = reinterpret_cast<const Block*>(kt->row_matrix)[i];
-        else
-            lds.gh[i] = kt->ghash[kRowPower][i];
-    }
+    const Block* from = kMatrixHash ? reinterpret_cast<const Block*>(kt->hash_image) : kt->ghash[kRowPower];
+    constexpr uint32_t kEntries = (kMatrixHash ? kHashImages : 1) * kNibbleTableEntries;
+    for (uint32_t i = tid; i < kEntries; i += kGroupThreads) lds.gh[i] = from[i];
 }
 
 // One unit of one chunk, walked by one wavefront in rows of 64 blocks: keystream, XOR, and the
 // lane's GHASH sum over the unit's rows, sum over rows r of C(r, lane) * (H^64)^(rows after r),
 // left in y.  unit 0 also takes "block -1", whose counter block is J0, and stores E_K(J0).
-template <bool kDecrypt, int kRounds, bool kThrough = false, bool kMatrixHash = false>
+// kSingleRows: units of one row (unit_power = kRowPower) take the row body without unit constants
+// and without a hash multiplication, for the launches whose latency counts: forming the constants
+// is two rounds of dependent lookups, 0.3 us before a lone row of 2.6 us.
+template <bool kDecrypt, int kRounds, bool kThrough, bool kMatrixHash, bool kSingleRows>
 __device__ __forceinline__ void walk_unit(const KeyTables* __restrict__ kt,
                                           const uint32_t* __restrict__ rk, AesAddr& A,
-                                          uint32_t lane, uint32_t lds_base, const uint8_t* src,
+                                          uint32_t lane, uint32_t wave, uint32_t lds_base,
+                                          const uint8_t* src,
                                           uint8_t* dst, uint64_t len, const uint8_t* aad,
                                           uint32_t aad_len, uint32_t unit, uint32_t nunits,
                                           uint32_t first_blocks, uint32_t unit_power,
@@ -1023,22 +1173,46 @@ __device__ __forceinline__ void walk_unit(const KeyTables* __restrict__ kt,
     const int64_t b1 = unit == 0 ? (int64_t)first_blocks : b0 + ((int64_t)1 << unit_power);
     const uint32_t nrows = (uint32_t)((b1 - b0 + kRowBlocks - 1) / kRowBlocks);
 
-    const CtrConsts C = ctr_consts(rk, lane, j.w[0], j.w[1], j.w[2], lds_base);
-    const uint32_t ctr1 = bswap32(j.w[3]) + 1u;
+    // a row's counter blocks: inc32^(blk + 1)(J0), the first 96 bits of J0, then its counter field
+    // plus blk + 1 modulo 2^32 (SP 800-38D 6.2, 7.1 step 3; ctr1 is that field plus 1, 2 for a
+    // 96-bit IV)
+    const uint32_t ctr1 = __builtin_amdgcn_readfirstlane(bswap32(j.w[3])) + 1u;
 
     Block aad_y{{0, 0, 0, 0}};
     if (unit == 0 && aad_len != 0) aad_y = aad_hash(kt, aad, aad_len);
 
-    y[0] = y[1] = y[2] = y[3] = 0;
     // rows are aligned to the unit's end; only rows at the chunk's start can have idle lanes
     // (block index below 0) or block 0, only its very last row can hold a ragged block
     int64_t row_blk = b1 - (int64_t)nrows * kRowBlocks;
-    for (uint32_t r = 0; r < nrows; ++r, row_blk += kRowBlocks) {
-        const bool edge = row_blk <= 0 || (unit + 1 == nunits && r + 1 == nrows);
-        bulk_row<kDecrypt, kRounds, kThrough, kMatrixHash>(rk, A, C, ctr1, src, dst, len,
-                                                           row_blk + lane, edge, aad_y, ekj0_out,
-                                                           lds_base, y);
+    if constexpr (kSingleRows) {
+        if (unit_power == kRowPower) {
+            GhashNone G;
+            // unit 0 may have a row of its own for "block -1" first, which leaves a sum of zero
+            for (uint32_t r = 0; r < nrows; ++r, row_blk += kRowBlocks) {
+                const bool edge = row_blk <= 0 || (unit + 1 == nunits && r + 1 == nrows);
+                const CtrBlock C{j.w[0], j.w[1], j.w[2], (uint32_t)row_blk + lane + ctr1};
+                bulk_row<kDecrypt, kRounds, kThrough>(rk, A, C, src, dst, len, row_blk + lane,
+                                                      edge, aad_y, ekj0_out, lds_base, G);
+            }
+            for (int k = 0; k < 4; ++k) y[k] = G.w[k];
+            return;
+        }
     }
+    std::conditional_t<kMatrixHash, GhashRowMatrix, GhashRowMul> G;
+    G.start(lds_base, lane);
+    for (uint32_t r = 0; r < nrows;) {
+        // a segment: kSegmentRows rows, or all seventeen of a unit 0 that has that many
+        const uint32_t first_ctr = (uint32_t)row_blk + ctr1;
+        CtrConsts C = ctr_consts(rk, lane, wave, j.w[0], j.w[1], j.w[2], first_ctr, lds_base);
+        const uint32_t left = nrows - r;
+        const uint32_t end = left <= kSegmentRows + 1 ? nrows : r + kSegmentRows;
+        for (; r < end; ++r, row_blk += kRowBlocks, C.rel += kRowBlocks) {
+            const bool edge = row_blk <= 0 || (unit + 1 == nunits && r + 1 == nrows);
+            bulk_row<kDecrypt, kRounds, kThrough>(rk, A, C, src, dst, len, row_blk + lane, edge,
+                                                  aad_y, ekj0_out, lds_base, G);
+        }
+    }
+    G.home(y);
 }
 
 }  // namespace
@@ -1052,7 +1226,7 @@ __device__ __forceinline__ void walk_unit(const KeyTables* __restrict__ kt,
 // chunks); coarse_map[i >> kCoarseShift] is a chunk at or before the right one.
 // sets[i * 64 + lane] receives lane's GHASH sum over the unit's rows.
 // ivs: 96-bit IVs (a chunk's at its `index`), read when j0 is null; otherwise j0[c] is chunk c's J0.
-// kMatrixHash: see bulk_row.
+// kMatrixHash: which engine the row hash runs on.
 template <bool kDecrypt, int kRounds, bool kMatrixHash>
 __global__ __launch_bounds__(kGroupThreads) void bulk_kernel(
     const KeyTables* __restrict__ kt, const ChunkDesc* __restrict__ chunks,
@@ -1089,8 +1263,8 @@ __global__ __launch_bounds__(kGroupThreads) void bulk_kernel(
         const ChunkDesc* __restrict__ cd = chunks + chunk;
         const Block j = chunk_j0(kt, ivs, j0, chunk, cd->index);
         uint32_t y[4];
-        walk_unit<kDecrypt, kRounds, false, kMatrixHash>(
-            kt, rk, A, lane, lds_base, cd->src, cd->dst, cd->len, cd->aad, cd->aad_len,
+        walk_unit<kDecrypt, kRounds, false, kMatrixHash, false>(
+            kt, rk, A, lane, tid >> 6, lds_base, cd->src, cd->dst, cd->len, cd->aad, cd->aad_len,
             item - cd->unit_base, cd->nunits, cd->first_blocks, unit_power, j, ekj0 + chunk, y);
         sets[(uint64_t)item * 64 + lane] = Block{{y[0], y[1], y[2], y[3]}};
         if (one_each) break;
@@ -1501,7 +1675,7 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
     __shared__ uint32_t last_flag;
     const uint32_t lds_base = lds_offset(&lds);
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    fill_bulk_lds(lds, kt, tid);
+    fill_bulk_lds<false>(lds, kt, tid);
 
     // this workgroup's chunk: the one whose workgroups include blockIdx.x (host: the grid is the
     // sum of the chunks' ngroups, so the scan ends inside the array)
@@ -1526,7 +1700,7 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
         // When decrypting, the workgroup that finishes the chunk may have to wipe plaintext that
         // other workgroups (on other XCDs) wrote: their stores go through to memory, and must be
         // there before the arrival is counted.  So must E_K(J0), which unit 0's wavefront stores.
-        walk_unit<kDecrypt, kRounds, kDecrypt>(kt, rk, A, lane, lds_base, cd.src, cd.dst, cd.len,
+        walk_unit<kDecrypt, kRounds, kDecrypt, false, true>(kt, rk, A, lane, wave, lds_base, cd.src, cd.dst, cd.len,
                                                cd.aad, cd.aad_len, (uint32_t)unit, cd.nunits,
                                                cd.first_blocks, unit_power, j, ekj0 + chunk, y);
         if (kDecrypt || unit == 0) wait_for_own_global_accesses();

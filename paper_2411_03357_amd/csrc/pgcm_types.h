@@ -47,6 +47,10 @@ constexpr uint32_t kNumPowers = kUnitPower + kFanPower * kMaxLevels + 1;  // H^(
 constexpr uint32_t kRowMatrixWords = 128 * 128 / 8;
 static_assert(kRowMatrixWords * 4 == kNibbleTableEntries * 16, "same room as a nibble table");
 
+// The row hash on the matrix cores multiplies by H^64 and by H^96 at once (GhashRowMatrix): two such
+// images, in the operand order of that engine.
+constexpr uint32_t kHashImages = 2;
+
 // The lane tree of the kernels that finish large chunks folds the 64 lanes in groups of four,
 // three multiplications deep; beside H^(2^k) it needs the nibble tables of H^3, H^12 and H^48.
 constexpr uint32_t kNumLanePowers = 3;
@@ -65,7 +69,11 @@ struct alignas(16) KeyTables {
     Block ghash[kNumPowers][kNibbleTableEntries];
     uint32_t row_matrix[kRowMatrixWords];  // multiplication by H^64 as matrix-core operands
     Block ghash_lane[kNumLanePowers][kNibbleTableEntries];  // nibble tables of H^3, H^12, H^48
+    // ---- up to here the tables are part of what pgcm_copy_key_tables returns ----
+    // multiplications by H^64 and by H^96 as the unit kernel's matrix operands
+    uint32_t hash_image[kHashImages][kRowMatrixWords];
 };
+constexpr size_t kPublicTablesBytes = offsetof(KeyTables, hash_image);
 
 struct alignas(16) ChunkDesc {
     const uint8_t* src;
