@@ -366,12 +366,12 @@ void launch_bulk(int rounds, bool matrix_hash, dim3 grid, hipStream_t stream, Ar
 
 // the kernel of a batch that takes one launch: `done` marks its end
 template <bool kDecrypt, class... Args>
-void launch_swap(int rounds, dim3 grid, hipStream_t stream, bool capturing, hipEvent_t done,
+void launch_swap(int rounds, dim3 grid, dim3 block, hipStream_t stream, bool capturing, hipEvent_t done,
                  Args... args) {
     auto* kernel = rounds == 10   ? swap_kernel<kDecrypt, 10>
                    : rounds == 12 ? swap_kernel<kDecrypt, 12>
                                   : swap_kernel<kDecrypt, 14>;
-    launch_last(kernel, grid, dim3(kGroupThreads), stream, capturing, done, args...);
+    launch_last(kernel, grid, block, stream, capturing, done, args...);
 }
 
 // wide: a workgroup of eight wavefronts per chunk; otherwise a wavefront per chunk
@@ -455,7 +455,6 @@ struct BatchPlan {
     bool all_one_row;     // ... and its one-wavefront-per-chunk kernel
     uint32_t unit_power;  // log2 of the blocks per unit
     uint32_t nunits;
-    uint32_t max_units;   // the most units any one chunk has
     uint32_t nslots;      // partial sets: one per unit and one per fold output
     uint32_t fold_count[kMaxLevels], fold_first[kMaxLevels], nfold;
     uint32_t ncoarse;
@@ -468,7 +467,6 @@ int plan_batch(uint32_t forced_unit_power, uint32_t wave_slots, const BatchArgs&
                                          : choose_unit_power(a.n, a.order, a.len, wave_slots);
     plan->all_small = plan->all_one_row = true;
     uint64_t nunits = 0, nslots = 0;
-    plan->max_units = 0;
     uint64_t fold_items[kMaxLevels] = {0, 0, 0, 0};
     for (size_t k = 0; k < a.n; ++k) {
         const size_t i = a.at(k);
@@ -485,7 +483,6 @@ int plan_batch(uint32_t forced_unit_power, uint32_t wave_slots, const BatchArgs&
             return PGCM_ERR_LEN;
         nunits += nu;
         nslots += nu;
-        if (nu > plan->max_units) plan->max_units = nu;
         for (uint32_t l = 0; l < levels; ++l) {
             fold_items[l] += outs[l];
             nslots += outs[l];
@@ -651,58 +648,79 @@ int run_small_batch(pgcm_key* key, Context* ctx, const BatchArgs& a, bool wide) 
     return rc_end;
 }
 
-// Workspace of the one-launch path: arrival words, tag masks, one set per workgroup.
-constexpr size_t kSwapArriveBytes = 256, kSwapMaskBytes = sizeof(Block) * kArgChunks;
-constexpr size_t kSwapSetsAt = 1024;
-static_assert(kSwapArriveBytes + kSwapMaskBytes <= kSwapSetsAt && 4 * kArgChunks <= kSwapArriveBytes,
-              "one-launch workspace");
+// Workspace of the one-launch path: arrival words, one result per workgroup.
+constexpr size_t kSwapArriveBytes = round_up(sizeof(uint32_t) * kSwapArriveWords, 256);
+constexpr size_t kSwapWorkBytes = kSwapArriveBytes + sizeof(Block) * kSwapMaxGroups;
 
-// does the batch take the one-launch path?
-// (A chunk of more than 128 workgroups is left to the other kernels: the workgroup that finishes
-// it would fold runs of sixteen sets per wavefront, a longer chain of dependent multiplications
-// than the fold kernels' trees; measured on one 8 MiB chunk, 45 against 43 us.)
-inline bool fits_one_launch(const pgcm_key* key, const BatchArgs& a, const BatchPlan& p) {
-    return key->one_launch && a.iv_len == 12 && a.n <= kArgChunks && p.unit_power <= kUnitPower &&
-           p.nunits <= key->wave_slots && p.max_units <= 128 * kWavesPerGroup;
+// How a batch is cut for the one-launch path, if it takes it.
+struct SwapShape {
+    uint32_t unit_power, wave_power, groups;
+};
+
+inline uint32_t swap_groups(const BatchArgs& a, size_t i, uint32_t unit_power, uint32_t wave_power) {
+    const uint64_t blocks = (a.len[i] + 15) / 16 + lead_blocks(a.aad_len ? a.aad_len[i] : 0);
+    const uint64_t units = (blocks + ((uint64_t)1 << unit_power) - 1) >> unit_power;
+    return (uint32_t)((units + ((uint64_t)1 << wave_power) - 1) >> wave_power);
+}
+
+// The smallest unit with which the batch fits the launch's workgroups (a compute unit each) at
+// sixteen wavefronts, then the fewest wavefronts a workgroup with which it still does.
+bool swap_shape(const pgcm_key* key, const BatchArgs& a, SwapShape* shape) {
+    if (!key->one_launch || a.iv_len != 12 || a.n > kArgChunks) return false;
+    const uint32_t most = (uint32_t)key->num_cu < kSwapMaxGroups ? (uint32_t)key->num_cu : kSwapMaxGroups;
+    uint64_t bytes = 0;
+    for (size_t k = 0; k < a.n; ++k) bytes += a.len[a.at(k)];
+    if (bytes > (uint64_t)most * kWavesPerGroup * kUnitBytes) return false;
+    auto groups = [&](uint32_t unit_power, uint32_t wave_power) {
+        uint32_t sum = 0;
+        for (size_t k = 0; k < a.n; ++k) sum += swap_groups(a, a.at(k), unit_power, wave_power);
+        return sum;
+    };
+    const uint32_t forced = key->forced_unit_power;
+    uint32_t up = forced ? forced : kMinUnitPower;
+    if (up > kUnitPower) return false;
+    while (groups(up, 4) > most) {
+        if (forced || up == kUnitPower) return false;
+        ++up;
+    }
+    uint32_t wp = 4;
+    while (wp > 2 && groups(up, wp - 1) <= most) --wp;
+    *shape = SwapShape{up, wp, groups(up, wp)};
+    return true;
 }
 
 // A batch of few chunks that does not fill the chip: one kernel, descriptors as its arguments,
 // nothing staged and nothing uploaded.
-int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const BatchPlan& p) {
+int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapShape& shape) {
     ArgBatch batch;
-    memset(&batch, 0, sizeof(batch));
     batch.nchunks = (uint32_t)a.n;
-    batch.unit_power = p.unit_power;
+    batch.unit_power = shape.unit_power;
+    batch.wave_power = shape.wave_power;
     uint32_t groups = 0;
     for (size_t k = 0; k < a.n; ++k) {
         const size_t i = a.at(k);
-        const UnitPlan up = plan_chunk(a.len[i], p.unit_power);
         ArgChunk& c = batch.c[k];
         c.src = (const uint8_t*)a.src[i];
         c.dst = (uint8_t*)a.dst[i];
         c.len = a.len[i];
         c.aad_len = a.aad_len ? a.aad_len[i] : 0;
         c.aad = c.aad_len ? (const uint8_t*)a.aad[i] : nullptr;
-        c.nunits = up.nunits;
-        c.first_blocks = up.first_blocks;
         c.index = (uint32_t)i;
-        c.group_base = groups;
-        c.ngroups = up.nunits == 0 ? 1 : (up.nunits + kWavesPerGroup - 1) / kWavesPerGroup;
-        groups += c.ngroups;
+        batch.group_base[k] = groups;
+        groups += swap_groups(a, i, shape.unit_power, shape.wave_power);
     }
-    const size_t bytes = kSwapSetsAt + sizeof(Block) * 64 * (size_t)groups;
-    int rc = ensure_work(ctx, bytes, a.stream);
+    batch.group_base[a.n] = groups;
+    int rc = ensure_work(ctx, kSwapWorkBytes, a.stream);
     if (rc != PGCM_OK) return rc;
     uint32_t* d_arrive = reinterpret_cast<uint32_t*>(ctx->work);
-    Block* d_ekj0 = reinterpret_cast<Block*>(ctx->work + kSwapArriveBytes);
-    Block* d_sets = reinterpret_cast<Block*>(ctx->work + kSwapSetsAt);
+    Block* d_slots = reinterpret_cast<Block*>(ctx->work + kSwapArriveBytes);
     // the arrival words are left at zero by every batch of this kind; they need clearing when
     // the workspace is new, was used by a batch of the other kind, or is shared between keys
     if (!ctx->arrive_clean || !ctx->growable)
-        hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(64), 0, a.stream, d_arrive,
-                           (uint32_t)kArgChunks);
+        hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(1024), 0, a.stream, d_arrive,
+                           kSwapArriveWords);
     ctx->arrive_clean = false;
-    ctx->counter_at = nullptr;  // the unit counter of the other kind of batch may lie under the sets
+    ctx->counter_at = nullptr;  // the unit counter of the other kind of batch may lie under this
     // No staging buffer is used, but the context's workspace is: the batch's end is marked on
     // the event of the stage whose turn it is, without taking the turn.  (If that event still
     // guards an earlier batch's staging buffer, that batch ends before this one on the same
@@ -710,12 +728,14 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const BatchP
     const int s = ctx->next_stage;
     const hipEvent_t done = ctx->stage_done[s];
     int rc_timing = record_timing_start(key, a.stream);
+    const dim3 grid(groups), block(64u << shape.wave_power);
     if (a.decrypt)
-        launch_swap<true>(key->rounds, dim3(groups), a.stream, a.capturing, done, (const KeyTables*)key->tables, batch,
-                          a.ivs, d_ekj0, d_sets, d_arrive, a.tags, a.ok);
+        launch_swap<true>(key->rounds, grid, block, a.stream, a.capturing, done,
+                          (const KeyTables*)key->tables, batch, a.ivs, d_slots, d_arrive, a.tags, a.ok);
     else
-        launch_swap<false>(key->rounds, dim3(groups), a.stream, a.capturing, done, (const KeyTables*)key->tables,
-                           batch, a.ivs, d_ekj0, d_sets, d_arrive, a.tags, (uint8_t*)nullptr);
+        launch_swap<false>(key->rounds, grid, block, a.stream, a.capturing, done,
+                           (const KeyTables*)key->tables, batch, a.ivs, d_slots, d_arrive, a.tags,
+                           (uint8_t*)nullptr);
     if (rc_timing == PGCM_OK) rc_timing = record_timing_stop(key, a.stream);
     if (a.capturing) PGCM_HIP(hipEventRecord(done, a.stream));
     ctx->last_stage = s;
@@ -839,12 +859,13 @@ int run_batch(pgcm_key* key, BatchArgs a) {
         rc = acquire_context(key, a.stream, &ctx);
         if (rc != PGCM_OK) return rc;
     }
+    SwapShape shape{};
     if (p.all_one_row)
         rc = run_small_batch(key, ctx, a, false);
     else if (p.all_small && a.n <= kSmallWideMaxChunks)
         rc = run_small_batch(key, ctx, a, true);
-    else if (fits_one_launch(key, a, p))
-        rc = run_one_launch(key, ctx, a, p);
+    else if (swap_shape(key, a, &shape))
+        rc = run_one_launch(key, ctx, a, shape);
     else
         rc = run_unit_batch(key, ctx, a, p);
     release_context(key, ctx);
@@ -1019,6 +1040,7 @@ int pgcm_reserve(pgcm_key_t* key, void* hip_stream, size_t n_max, uint64_t paylo
     int rc = acquire_context(key, stream, &ctx);
     if (rc != PGCM_OK) return rc;
     for (int s = 0; s < kStages && rc == PGCM_OK; ++s) rc = ensure_stage(ctx, s, stage_bytes);
+    if (work_bytes < kSwapWorkBytes) work_bytes = kSwapWorkBytes;
     if (rc == PGCM_OK) rc = ensure_work(ctx, work_bytes, stream);
     if (rc == PGCM_OK) {
         // the context now belongs to this stream, so that the stream's batches find it

@@ -74,43 +74,7 @@ static_assert(make_sbox().v[0x00] == 0x63 && make_sbox().v[0x53] == 0xED, "S-box
 
 // ------------------------------------------------------------------------------------------
 // GF(2^128) in GCM's bit order (SP 800-38D 6.3): bit 0 of a block is the top bit of byte 0.
-// For shifting, a block is held as two big-endian 64-bit halves.
-struct Gf {
-    uint64_t hi, lo;
-};
-
 __device__ __forceinline__ uint32_t bswap32(uint32_t v) { return __builtin_bswap32(v); }
-
-__device__ __forceinline__ Gf gf_from_block(const Block& b) {
-    Gf g;
-    g.hi = ((uint64_t)bswap32(b.w[0]) << 32) | bswap32(b.w[1]);
-    g.lo = ((uint64_t)bswap32(b.w[2]) << 32) | bswap32(b.w[3]);
-    return g;
-}
-
-__device__ __forceinline__ Block gf_to_block(const Gf& g) {
-    Block b;
-    b.w[0] = bswap32((uint32_t)(g.hi >> 32));
-    b.w[1] = bswap32((uint32_t)g.hi);
-    b.w[2] = bswap32((uint32_t)(g.lo >> 32));
-    b.w[3] = bswap32((uint32_t)g.lo);
-    return b;
-}
-
-// bit-serial product (SP 800-38D algorithm 1); used for set-up only
-__device__ Gf gf_mul_bits(const Gf& x, const Gf& y) {
-    Gf z{0, 0}, v = y;
-    for (int i = 0; i < 128; ++i) {
-        uint64_t bit = (i < 64) ? (x.hi >> (63 - i)) & 1 : (x.lo >> (127 - i)) & 1;
-        uint64_t m = 0 - bit;
-        z.hi ^= v.hi & m;
-        z.lo ^= v.lo & m;
-        uint64_t carry = 0 - (v.lo & 1);
-        v.lo = (v.lo >> 1) | (v.hi << 63);
-        v.hi = (v.hi >> 1) ^ (carry & 0xE100000000000000ull);
-    }
-    return z;
-}
 
 // a ^ b ^ c in one instruction (gfx950's three-input bitwise op, truth table 0x96)
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
@@ -170,23 +134,103 @@ __device__ void aes_block_global(const KeyTables* __restrict__ kt, uint32_t s[4]
     s[3] = last(a3, a0, a1, a2) ^ rk[4 * nr + 3];
 }
 
-__device__ __forceinline__ uint32_t sub_word(uint32_t w) {
-    const uint8_t* S = kSbox.v;
-    return (uint32_t)S[w & 0xFF] | ((uint32_t)S[(w >> 8) & 0xFF] << 8) |
-           ((uint32_t)S[(w >> 16) & 0xFF] << 16) | ((uint32_t)S[w >> 24] << 24);
+}  // namespace
+
+// ------------------------------------------------------------------------------------------
+// Arithmetic on field elements held as words of coefficients (GfWords): x^0 is the top bit of the
+// first word, so multiplying by x is a shift to the right.
+namespace {
+
+// x^128 = 1 + x + x^2 + x^7: folds `over`, coefficients x^128 .. x^159, back in; at most the first
+// 25 of them may be set
+__device__ __forceinline__ void gfw_fold_word(GfWords& v, uint32_t over) {
+    v.a[0] ^= over ^ (over >> 1) ^ (over >> 2) ^ (over >> 7);
+}
+
+__device__ __forceinline__ void gfw_mul_x(GfWords& v) {
+    const uint32_t over = 0u - (v.a[3] & 1u);
+    v.a[3] = (v.a[3] >> 1) | (v.a[2] << 31);
+    v.a[2] = (v.a[2] >> 1) | (v.a[1] << 31);
+    v.a[1] = (v.a[1] >> 1) | (v.a[0] << 31);
+    v.a[0] = (v.a[0] >> 1) ^ (over & 0xE1000000u);
+}
+
+// times x^8
+__device__ __forceinline__ void gfw_mul_x8(GfWords& v) {
+    const uint32_t over = v.a[3] << 24;
+    v.a[3] = (v.a[3] >> 8) | (v.a[2] << 24);
+    v.a[2] = (v.a[2] >> 8) | (v.a[1] << 24);
+    v.a[1] = (v.a[1] >> 8) | (v.a[0] << 24);
+    v.a[0] >>= 8;
+    gfw_fold_word(v, over);
+}
+
+__device__ __forceinline__ Block gfw_to_block(const GfWords& v) {
+    return Block{{bswap32(v.a[0]), bswap32(v.a[1]), bswap32(v.a[2]), bswap32(v.a[3])}};
+}
+__device__ __forceinline__ GfWords gfw_from_block(const Block& b) {
+    return GfWords{{bswap32(b.w[0]), bswap32(b.w[1]), bswap32(b.w[2]), bswap32(b.w[3])}};
+}
+
+// bit by bit (SP 800-38D algorithm 1); used for set-up only
+__device__ GfWords gfw_mul(const GfWords& x, GfWords y) {
+    GfWords z{{0, 0, 0, 0}};
+    for (int i = 0; i < 4; ++i) {
+        for (int j = 31; j >= 0; --j) {
+            const uint32_t m = 0u - ((x.a[i] >> j) & 1u);
+            for (int k = 0; k < 4; ++k) z.a[k] ^= y.a[k] & m;
+            gfw_mul_x(y);
+        }
+    }
+    return z;
+}
+
+// coefficient x^i to x^(2 i), then reduced
+__device__ GfWords gfw_square(const GfWords& x) {
+    auto spread = [](uint32_t v) {  // sixteen coefficients to every other place of a word
+        v &= 0xFFFFu;
+        v = (v | (v << 8)) & 0x00FF00FFu;
+        v = (v | (v << 4)) & 0x0F0F0F0Fu;
+        v = (v | (v << 2)) & 0x33333333u;
+        v = (v | (v << 1)) & 0x55555555u;
+        return v << 1;
+    };
+    uint32_t r[8];
+    for (int i = 0; i < 4; ++i) {
+        r[2 * i] = spread(x.a[i] >> 16);
+        r[2 * i + 1] = spread(x.a[i]);
+    }
+    const uint32_t* u = r + 4;  // coefficients from x^128 on, times 1 + x + x^2 + x^7
+    GfWords z;
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t before = i == 0 ? 0u : u[i - 1];
+        z.a[i] = r[i] ^ u[i] ^ ((u[i] >> 1) | (before << 31)) ^ ((u[i] >> 2) | (before << 30)) ^
+                 ((u[i] >> 7) | (before << 25));
+    }
+    gfw_fold_word(z, (u[3] << 31) ^ (u[3] << 30) ^ (u[3] << 25));
+    return z;
 }
 
 }  // namespace
 
 // ------------------------------------------------------------------------------------------
-// Key set-up: key schedule (FIPS-197 5.2), round tables, H and the nibble tables of H^(2^k).
+// Key set-up: key schedule (FIPS-197 5.2), round tables, H and everything made of its powers.
 // One workgroup; `key_words` are the key bytes as nk = 4, 6 or 8 little-endian words.
+// The serial part is one thread's (key schedule, E_K(0), thirty squarings) and runs from LDS; a
+// nibble table is linear in the nibble, so only its 128 products with single coefficients are
+// made, by shifting, and its 512 entries are sums of up to four of them.
 __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict__ kt,
                                                           const uint32_t* __restrict__ key_words,
                                                           uint32_t nk) {
-    __shared__ Gf powers[kNumPowers];
-    __shared__ Gf lane_powers[kNumLanePowers];
-    __shared__ Gf row_powers[kHashImages];
+    // constants with a nibble table: H^(2^k), then H^3, H^12, H^48; then H^96 without one
+    constexpr uint32_t kConstants = kNumPowers + kNumLanePowers + 1, kAt96 = kConstants - 1;
+    constexpr uint32_t kLevels = 6;  // nibble tables of H^1 .. H^32 kept in LDS as well
+    __shared__ GfWords constants[kConstants];
+    __shared__ Block basis[kConstants][128];  // x^b * constant, b = bit b % 32 of word b / 32
+    __shared__ Block nibbles[kLevels][kNibbleTableEntries];
+    __shared__ GfWords h_power[65];
+    __shared__ uint32_t te[4][256], rk[60];
+    __shared__ uint8_t sbox[256];
     const uint32_t tid = threadIdx.x;
 
     // round tables: te[0][x] = (2s, s, s, 3s) in bytes 0..3, te[r] = te[0] rotated left by 8r bits
@@ -194,82 +238,92 @@ __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict_
         uint32_t s = kSbox.v[x];
         uint32_t s2 = xtime((uint8_t)s), s3 = s2 ^ s;
         uint32_t t0 = s2 | (s << 8) | (s << 16) | (s3 << 24);
-        kt->te[0][x] = t0;
-        kt->te[1][x] = (t0 << 8) | (t0 >> 24);
-        kt->te[2][x] = (t0 << 16) | (t0 >> 16);
-        kt->te[3][x] = (t0 << 24) | (t0 >> 8);
+        sbox[x] = (uint8_t)s;
+        te[0][x] = t0;
+        te[1][x] = (t0 << 8) | (t0 >> 24);
+        te[2][x] = (t0 << 16) | (t0 >> 16);
+        te[3][x] = (t0 << 24) | (t0 >> 8);
+        for (int r = 0; r < 4; ++r) kt->te[r][x] = te[r][x];
     }
+    if (tid < 60) rk[tid] = tid < nk ? key_words[tid] : 0;
+    __syncthreads();
+    const uint32_t nr = nk + 6;
     if (tid == 0) {
-        const uint32_t nr = nk + 6, nwords = 4 * (nr + 1);
-        uint32_t w[60];
-        for (uint32_t i = 0; i < 60; ++i) w[i] = 0;
-        for (uint32_t i = 0; i < nk; ++i) w[i] = key_words[i];
-        uint32_t rcon = 1;
-        for (uint32_t i = nk; i < nwords; ++i) {
-            uint32_t t = w[i - 1];
+        auto sub_word = [&](uint32_t w) {
+            return (uint32_t)sbox[w & 0xFF] | ((uint32_t)sbox[(w >> 8) & 0xFF] << 8) |
+                   ((uint32_t)sbox[(w >> 16) & 0xFF] << 16) | ((uint32_t)sbox[w >> 24] << 24);
+        };
+        uint32_t rcon = 1, t = rk[nk - 1];
+        for (uint32_t i = nk; i < 4 * (nr + 1); ++i) {
             if (i % nk == 0) {
                 t = sub_word((t >> 8) | (t << 24)) ^ rcon;  // RotWord on little-endian bytes
                 rcon = xtime((uint8_t)rcon);
             } else if (nk > 6 && i % nk == 4) {
                 t = sub_word(t);
             }
-            w[i] = w[i - nk] ^ t;
+            t ^= rk[i - nk];
+            rk[i] = t;
         }
-        for (uint32_t i = 0; i < 60; ++i) kt->rk[i] = w[i];
+        // H = E_K(0)
+        uint32_t a[4] = {rk[0], rk[1], rk[2], rk[3]};
+        for (uint32_t r = 1; r <= nr; ++r) {
+            uint32_t n[4];
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t x0 = byte_of(a[c], 0), x1 = byte_of(a[(c + 1) & 3], 1),
+                               x2 = byte_of(a[(c + 2) & 3], 2), x3 = byte_of(a[(c + 3) & 3], 3);
+                n[c] = r < nr ? te[0][x0] ^ te[1][x1] ^ te[2][x2] ^ te[3][x3]
+                              : (uint32_t)sbox[x0] | ((uint32_t)sbox[x1] << 8) |
+                                    ((uint32_t)sbox[x2] << 16) | ((uint32_t)sbox[x3] << 24);
+                n[c] ^= rk[4 * r + c];
+            }
+            for (int c = 0; c < 4; ++c) a[c] = n[c];
+        }
+        const Block h{{a[0], a[1], a[2], a[3]}};
+        kt->h = h;
+        GfWords p = gfw_from_block(h);
+        constants[0] = p;
+        for (uint32_t k = 1; k < kNumPowers; ++k) {
+            p = gfw_square(p);
+            constants[k] = p;
+        }
         kt->rounds = nr;
         for (int i = 0; i < 3; ++i) kt->pad_[i] = 0;
     }
-    __threadfence();
     __syncthreads();
-    if (tid == 0) {
-        uint32_t z[4] = {0, 0, 0, 0};
-        aes_block_global(kt, z);
-        Block h{{z[0], z[1], z[2], z[3]}};
-        kt->h = h;
-        Gf p = gf_from_block(h);
-        powers[0] = p;
-        for (uint32_t k = 1; k < kNumPowers; ++k) {
-            p = gf_mul_bits(p, p);
-            powers[k] = p;
+    if (tid < 60) kt->rk[tid] = rk[tid];
+    // H^3, H^12, H^48, H^96 = products of two neighbouring squares
+    if (tid <= kNumLanePowers)
+        constants[kNumPowers + tid] =
+            gfw_mul(constants[tid < 3 ? 2 * tid : 5], constants[tid < 3 ? 2 * tid + 1 : 6]);
+    __syncthreads();
+
+    // sixteen threads per constant, eight neighbouring coefficients each
+    for (uint32_t e = tid; e < kConstants * 16; e += blockDim.x) {
+        const uint32_t c = e / 16, byte = e % 16;
+        GfWords p = constants[c];
+        for (uint32_t i = 0; i < byte; ++i) gfw_mul_x8(p);
+        for (int bit = 7; bit >= 0; --bit) {  // coefficient x^(8 byte + 7 - bit)
+            basis[c][8 * byte + bit] = gfw_to_block(p);
+            gfw_mul_x(p);
         }
-        lane_powers[0] = gf_mul_bits(powers[1], powers[0]);  // H^3
-        lane_powers[1] = gf_mul_bits(powers[3], powers[2]);  // H^12
-        lane_powers[2] = gf_mul_bits(powers[5], powers[4]);  // H^48
-        row_powers[0] = powers[kRowPower];
-        row_powers[1] = gf_mul_bits(powers[kRowPower], powers[kRowPower - 1]);  // H^96
     }
     __syncthreads();
-    for (uint32_t e = tid; e < kNumPowers * kNibbleTableEntries; e += blockDim.x) {
-        uint32_t k = e / kNibbleTableEntries, idx = e % kNibbleTableEntries;
-        uint32_t pos = idx / 16, val = idx % 16;
-        uint32_t byte = pos / 2;
-        uint32_t bits = (pos & 1) ? val : (val << 4);
-        Block x{{0, 0, 0, 0}};
-        x.w[byte / 4] = bits << (8 * (byte % 4));
-        kt->ghash[k][idx] = gf_to_block(gf_mul_bits(gf_from_block(x), powers[k]));
-    }
-    for (uint32_t e = tid; e < kNumLanePowers * kNibbleTableEntries; e += blockDim.x) {
-        uint32_t k = e / kNibbleTableEntries, idx = e % kNibbleTableEntries;
-        uint32_t pos = idx / 16, val = idx % 16;
-        uint32_t byte = pos / 2;
-        uint32_t bits = (pos & 1) ? val : (val << 4);
-        Block x{{0, 0, 0, 0}};
-        x.w[byte / 4] = bits << (8 * (byte % 4));
-        kt->ghash_lane[k][idx] = gf_to_block(gf_mul_bits(gf_from_block(x), lane_powers[k]));
+    for (uint32_t e = tid; e < (kNumPowers + kNumLanePowers) * kNibbleTableEntries; e += blockDim.x) {
+        const uint32_t c = e / kNibbleTableEntries, idx = e % kNibbleTableEntries;
+        const uint32_t pos = idx / 16, val = idx % 16;
+        const Block* from = &basis[c][8 * (pos / 2) + ((pos & 1) ? 0 : 4)];
+        Block z{{0, 0, 0, 0}};
+        for (int i = 0; i < 4; ++i)
+            if (val & (1u << i)) block_xor(z, from[i]);
+        if (c < kNumPowers)
+            kt->ghash[c][idx] = z;
+        else
+            kt->ghash_lane[c - kNumPowers][idx] = z;
+        if (c < kLevels) nibbles[c][idx] = z;
     }
 
-    // Multiplications as 128 x 128 matrices over GF(2): cols[m][b] = x^b * H^64 (m = 0) or H^96
-    // (m = 1) for the block whose only set bit is bit b % 32 of word b / 32.
-    __shared__ Block cols[kHashImages][128];
-    if (tid < kHashImages * 128) {
-        const uint32_t m = tid / 128, bit = tid % 128;
-        Block x{{0, 0, 0, 0}};
-        x.w[bit / 32] = 1u << (bit % 32);
-        cols[m][bit] = gf_to_block(gf_mul_bits(gf_from_block(x), row_powers[m]));
-    }
-    __syncthreads();
-    // H^64 with the bits of every operand quarter in a register of its own lane half (part of the
-    // published tables)
+    // Multiplication by H^64 with the bits of every operand quarter in a register of its own lane
+    // half (part of the published tables)
     for (uint32_t e = tid; e < kRowMatrixWords; e += blockDim.x) {
         const uint32_t r = e % 4, lane = (e / 4) % 64, ks = (e / 256) % 2, mt = e / 512;
         // the operand row this lane holds, the product bit it makes, the operand quarter
@@ -278,11 +332,11 @@ __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict_
         uint32_t v = 0;
         for (uint32_t j = 0; j < 8; ++j) {
             const uint32_t in = 32 * r + 4 * j + 2 * ks + h;
-            if ((cols[0][in].w[word] >> bit) & 1u) v |= 0x2u << (4 * j);  // 1.0 in e2m1
+            if ((basis[kRowPower][in].w[word] >> bit) & 1u) v |= 0x2u << (4 * j);  // 1.0 in e2m1
         }
         kt->row_matrix[e] = v;
     }
-    // ... and both in the operand order of the unit kernel (see GhashRowMatrix)
+    // ... and those by H^64 and H^96 in the operand order of the unit kernel (see GhashRowMatrix)
     for (uint32_t e = tid; e < kHashImages * kRowMatrixWords; e += blockDim.x) {
         const uint32_t quarter = e % 4, lane = (e / 4) % 64, ks = (e / 256) % 2, mt = (e / 512) % 4,
                        m = e / kRowMatrixWords;
@@ -293,9 +347,36 @@ __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict_
         uint32_t v = 0;
         for (uint32_t j = 0; j < 8; ++j) {
             const uint32_t in = 32 * (2 * ks + lane / 32) + 4 * j + quarter;
-            if ((cols[m][in].w[word] >> bit) & 1u) v |= one << (4 * j);
+            if ((basis[m == 0 ? kRowPower : kAt96][in].w[word] >> bit) & 1u) v |= one << (4 * j);
         }
         kt->hash_image[m][e % kRowMatrixWords] = v;
+    }
+
+    // H^1 .. H^64, doubling: H^(2^j + i) = H^i * H^(2^j)
+    if (tid == 0) h_power[1] = constants[0];
+    __syncthreads();
+    for (uint32_t j = 0; j < kLevels; ++j) {
+        if (tid >= 1 && tid <= (1u << j)) {
+            const Block b = gf_mul_table(nibbles[j], gfw_to_block(h_power[tid]));
+            h_power[(1u << j) + tid] = gfw_from_block(b);
+        }
+        __syncthreads();
+    }
+    for (uint32_t e = tid; e < 64 * kDotSlices; e += blockDim.x) {
+        const uint32_t l = e / kDotSlices, t = e % kDotSlices;
+        GfWords p = h_power[64 - l];
+        for (uint32_t i = 0; i < t; ++i) gfw_mul_x8(p);
+        kt->dot[l][t] = p;
+    }
+    // hop[d][k] likewise: k = 2^j + i from i with H^(2^(8 + d + j)), from its nibble table
+    if (tid < kHopPowers) kt->hop[tid][0] = constants[0];
+    for (uint32_t j = 0; (1u << j) < kHopEntries; ++j) {
+        __syncthreads();
+        for (uint32_t e = tid; e < kHopPowers << j; e += blockDim.x) {
+            const uint32_t d = e >> j, i = e & ((1u << j) - 1);
+            const Block b = gf_mul_table(kt->ghash[kHopMinPower + d + j], gfw_to_block(kt->hop[d][i]));
+            kt->hop[d][(1u << j) + i] = gfw_from_block(b);
+        }
     }
 }
 
@@ -326,9 +407,7 @@ __device__ Block j0_from_iv(const KeyTables* __restrict__ kt, const uint8_t* __r
                             uint32_t iv_len) {
     if (iv_len == 12) {
         Block j;
-        for (int w = 0; w < 3; ++w)
-            j.w[w] = (uint32_t)iv[4 * w] | ((uint32_t)iv[4 * w + 1] << 8) |
-                     ((uint32_t)iv[4 * w + 2] << 16) | ((uint32_t)iv[4 * w + 3] << 24);
+        __builtin_memcpy(j.w, iv, 12);  // at any alignment
         j.w[3] = 0x01000000u;  // be32(1)
         return j;
     }
@@ -412,6 +491,77 @@ __device__ __forceinline__ uint8_t global_read8(const uint8_t* p) {
 }
 __device__ __forceinline__ void global_write8(uint8_t* p, uint8_t v) {
     *reinterpret_cast<global_u8_ptr>(reinterpret_cast<uintptr_t>(p)) = v;
+}
+
+// 16 bytes at any alignment
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+typedef __attribute__((address_space(1))) const u32x4_any* global_u128_any_cptr;
+typedef __attribute__((address_space(1))) u32x4_any* global_u128_any_ptr;
+__device__ __forceinline__ Block global_read_block_any(const uint8_t* p) {
+    const u32x4_any v = *reinterpret_cast<global_u128_any_cptr>(reinterpret_cast<uintptr_t>(p));
+    return Block{{v.x, v.y, v.z, v.w}};
+}
+__device__ __forceinline__ void global_write_block_any(uint8_t* p, const Block& b) {
+    const u32x4_any v = {b.w[0], b.w[1], b.w[2], b.w[3]};
+    *reinterpret_cast<global_u128_any_ptr>(reinterpret_cast<uintptr_t>(p)) = v;
+}
+
+// block i of a byte string, zero-padded (SP 800-38D 6.4)
+__device__ __forceinline__ Block padded_block(const uint8_t* p, uint32_t bytes, uint32_t i) {
+    const uint32_t off = 16 * i, m = bytes - off;
+    if (m >= 16) return global_read_block_any(p + off);
+    Block b{{0, 0, 0, 0}};
+#pragma unroll
+    for (uint32_t k = 0; k < 15; ++k)
+        if (k < m) b.w[k / 4] |= (uint32_t)global_read8(p + off + k) << (8 * (k % 4));
+    return b;
+}
+
+// The AAD comes right before the ciphertext in what is hashed, so its blocks are given the numbers
+// -n .. -1 and are hashed by the lanes that lie before the chunk's start: no multiplications of
+// their own, where hashing 64 bytes ahead of block 0 from the table in memory takes some 5 us.
+// AAD of more than kAadLaneBlocks blocks is meant to be rare: all but its last block is hashed
+// serially first, and the sum with that block stands in for "block -1".
+constexpr uint32_t kAadLaneBlocks = 64;
+__device__ __forceinline__ Block serial_hash(const Block* __restrict__ h_table, const uint8_t* p,
+                                             uint32_t bytes, uint32_t blocks) {
+    Block y{{0, 0, 0, 0}};
+    for (uint32_t i = 0; i < blocks; ++i) {
+        const Block b = padded_block(p, bytes, i);
+        block_xor(y, b);
+        y = gf_mul_table(h_table, y);
+    }
+    return y;
+}
+
+struct AadBlocks {
+    const uint8_t* bytes = nullptr;
+    uint32_t len = 0, blocks = 0;
+    Block stand_in{{0, 0, 0, 0}};  // of a long AAD, at block -1
+
+    __device__ __forceinline__ Block at(int64_t blk) const {
+        Block b{{0, 0, 0, 0}};
+        if (blocks > kAadLaneBlocks) {
+            if (blk == -1) b = stand_in;
+        } else if (blk >= -(int64_t)blocks) {
+            b = padded_block(bytes, len, blocks + (uint32_t)(int32_t)blk);
+        }
+        return b;
+    }
+    // to be called by the wavefront that walks the blocks before block 0
+    __device__ __forceinline__ void prepare(const Block* __restrict__ h_table) {
+        if (blocks > kAadLaneBlocks) {
+            stand_in = serial_hash(h_table, bytes, len, blocks - 1);
+            const Block b = padded_block(bytes, len, blocks - 1);
+            block_xor(stand_in, b);
+        }
+    }
+};
+
+__device__ __forceinline__ AadBlocks aad_blocks(const uint8_t* p, uint32_t len) {
+    AadBlocks a;
+    a.bytes = p, a.len = len, a.blocks = (uint32_t)(((uint64_t)len + 15) / 16);
+    return a;
 }
 
 // A block written so that a wavefront on another XCD can read it while this kernel still runs:
@@ -993,53 +1143,62 @@ __device__ __forceinline__ void ghash_mul_lds(uint32_t base, uint32_t y[4]) {
     y[0] = z0, y[1] = z1, y[2] = z2, y[3] = z3;
 }
 
-// One row of a unit: block `blk` of the chunk in this lane.  On `edge` rows (the first and the
-// last row of a chunk; a wave-uniform flag) some lanes may lie before the chunk's start and stay
-// idle, the last lane may hold the chunk's ragged last block, and the lane of block 0 folds in
-// the AAD state; idle lanes run the cipher on a dummy counter, touch no payload and keep a zero
-// hash state.
-// kThrough: the payload is written through to memory (see global_write128_through).
-// G: the row hash engine, on the matrix cores or from a table.
-// `edge` is the same in every lane and held in a scalar register (walk_unit sees to that), so
-// the rows that are no edge rows branch past all of the checks.
-template <bool kDecrypt, int kRounds, bool kThrough, class Ctr, class Hash>
-__device__ __forceinline__ void bulk_row(const uint32_t* __restrict__ rk, AesAddr& A,
-                                         const Ctr& C, const uint8_t* src,
-                                         uint8_t* dst, uint64_t len, int64_t blk, bool edge,
-                                         const Block& aad_y, Block* __restrict__ ekj0_out,
-                                         uint32_t lds_base, Hash& G) {
-    bool active = true;
-    uint32_t tail = 0;  // bytes in a ragged block, 0 = whole block
-    bool whole = true;
+// One row's payload in this lane: block `blk` of the chunk.  On `edge` rows (the first and the last
+// row of a chunk; a wave-uniform flag) some lanes may lie before the chunk's start and stay idle,
+// and the last lane may hold the chunk's ragged last block.
+struct RowPayload {
     uint32_t x0, x1, x2, x3;
+    uint32_t tail;  // bytes in a ragged block, 0 = whole block or none
+    bool whole;
+};
+
+__device__ __forceinline__ RowPayload load_row(const uint8_t* src, uint64_t len, int64_t blk,
+                                               bool edge) {
+    RowPayload r{0, 0, 0, 0, 0, true};
     const uint8_t* sp = src + blk * 16;
-    uint8_t* dp = dst + blk * 16;
     if (!edge) {
         const u32x4 v = global_read128(sp);
-        x0 = v.x, x1 = v.y, x2 = v.z, x3 = v.w;
+        r.x0 = v.x, r.x1 = v.y, r.x2 = v.z, r.x3 = v.w;
     } else {
-        active = blk >= 0;
-        if (active && (uint64_t)blk * 16 + 16 > len) tail = (uint32_t)(len & 15);
-        whole = active && tail == 0;
-        x0 = x1 = x2 = x3 = 0;
-        if (whole) {
+        const bool active = blk >= 0;
+        if (active && (uint64_t)blk * 16 + 16 > len) r.tail = (uint32_t)(len & 15);
+        r.whole = active && r.tail == 0;
+        if (r.whole) {
             const u32x4 v = global_read128(sp);
-            x0 = v.x, x1 = v.y, x2 = v.z, x3 = v.w;
+            r.x0 = v.x, r.x1 = v.y, r.x2 = v.z, r.x3 = v.w;
         }
-        if (tail) {
+        if (r.tail) {
 #pragma unroll
             for (uint32_t b = 0; b < 15; ++b) {
-                if (b < tail) {
+                if (b < r.tail) {
                     const uint32_t v = (uint32_t)global_read8(sp + b) << (8 * (b % 4));
-                    if (b / 4 == 0) x0 |= v;
-                    if (b / 4 == 1) x1 |= v;
-                    if (b / 4 == 2) x2 |= v;
-                    if (b / 4 == 3) x3 |= v;
+                    if (b / 4 == 0) r.x0 |= v;
+                    if (b / 4 == 1) r.x1 |= v;
+                    if (b / 4 == 2) r.x2 |= v;
+                    if (b / 4 == 3) r.x3 |= v;
                 }
             }
         }
     }
+    return r;
+}
 
+// One row of a unit: the payload loaded by load_row is encrypted or decrypted, stored and hashed.
+// On edge rows lanes before the chunk's start touch no payload; they hash the AAD's blocks, which
+// come right before block 0, or a zero block.  The counter block of "block -1" is J0, so the idle
+// lane there computes E_K(J0), the mask of the chunk's tag (SP 800-38D 7.1 steps 2 and 6), which
+// is handed to store_mask.
+// kThrough: the payload is written through to memory (see global_write128_through).
+// G: the row hash engine, on the matrix cores or from a table.
+// `edge` is the same in every lane and held in a scalar register (walk_unit sees to that), so
+// the rows that are no edge rows branch past all of the checks.
+template <bool kDecrypt, int kRounds, bool kThrough, class Ctr, class Hash, class StoreMask>
+__device__ __forceinline__ void bulk_row(const uint32_t* __restrict__ rk, AesAddr& A,
+                                         const Ctr& C, const RowPayload& r, uint8_t* dst,
+                                         int64_t blk, bool edge, const AadBlocks& aad,
+                                         StoreMask&& store_mask, uint32_t lds_base, Hash& G) {
+    uint8_t* dp = dst + blk * 16;
+    const uint32_t x0 = r.x0, x1 = r.x1, x2 = r.x2, x3 = r.x3, tail = r.tail;
     // the keystream block ... while the hash state moves one row along
     G.begin();
     uint32_t s0, s1, s2, s3;
@@ -1055,7 +1214,7 @@ __device__ __forceinline__ void bulk_row(const uint32_t* __restrict__ rk, AesAdd
     };
     if (!edge) {
         store_block();
-    } else if (whole) {
+    } else if (r.whole) {
         store_block();
     }
     if (edge && tail) {
@@ -1081,18 +1240,10 @@ __device__ __forceinline__ void bulk_row(const uint32_t* __restrict__ rk, AesAdd
     // the ciphertext is what gets hashed: the output when encrypting, the input when decrypting
     uint32_t c0 = kDecrypt ? x0 : o0, c1 = kDecrypt ? x1 : o1, c2 = kDecrypt ? x2 : o2,
              c3 = kDecrypt ? x3 : o3;
-    if (edge) {
-        if (blk == 0) {
-            // GHASH continues from the state the AAD left: same as adding it to the first block
-            c0 ^= aad_y.w[0], c1 ^= aad_y.w[1], c2 ^= aad_y.w[2], c3 ^= aad_y.w[3];
-        }
-        if (blk == -1) {
-            // the counter block of "block -1" is J0 itself: this idle lane has just computed
-            // E_K(J0), the mask of the chunk's tag (SP 800-38D 7.1 steps 2 and 6)
-            // (read by another kernel, or by another workgroup of this one: device scope)
-            store_block_device_scope(ekj0_out, s0, s1, s2, s3);
-        }
-        if (!active) c0 = c1 = c2 = c3 = 0;  // idle lanes only occur before a chunk's start: Y = 0
+    if (edge && blk < 0) {
+        if (blk == -1) store_mask(s0, s1, s2, s3);
+        const Block a = aad.at(blk);
+        c0 = a.w[0], c1 = a.w[1], c2 = a.w[2], c3 = a.w[3];
     }
     G.absorb(c0, c1, c2, c3);
 }
@@ -1101,105 +1252,59 @@ __device__ __forceinline__ void bulk_row(const uint32_t* __restrict__ rk, AesAdd
 
 namespace {
 
-// Brings the bulk kernels' tables into LDS; every thread of the 1024 calls it, and a barrier
-// must follow.  Round tables: 32 copies of every entry, lane-interleaved.  A row of the map is
-// sixteen 16-byte pieces, eight per table of its pair; every thread fetches the eight entries
+// Brings the bulk kernels' tables into LDS; every one of the kThreads threads calls it, and a
+// barrier must follow.  Round tables: 32 copies of every entry, lane-interleaved.  A row of the map
+// is sixteen 16-byte pieces, eight per table of its pair; every thread fetches eight of the entries
 // its pieces need at once (independent loads) and writes each four times over in one store, and
 // a wavefront's store covers four whole rows, so the stores run at the full LDS width.
-template <bool kMatrixHash>
+// kHash: the operands of the row hash, none, the nibble table or the matrix images.
+enum class FillHash { kNone, kTable, kMatrix };
+template <FillHash kHash, uint32_t kThreads>
 __device__ __forceinline__ void fill_bulk_lds(BulkLds& lds, const KeyTables* __restrict__ kt,
                                               uint32_t tid) {
     constexpr uint32_t kPieces = kLdsTeBytes / 16;
-    static_assert(kPieces % kGroupThreads == 0, "pieces per thread");
-    constexpr uint32_t kPerThread = kPieces / kGroupThreads;
-    uint32_t v[kPerThread];
-#pragma unroll
-    for (uint32_t k = 0; k < kPerThread; ++k) {
-        const uint32_t g = k * kGroupThreads + tid;  // piece number
-        const uint32_t pair = g >> 12, row = (g >> 4) & 255, t = 2 * pair + ((g >> 3) & 1);
-        v[k] = kt->te[t][row];
-    }
+    static_assert(kPieces % (8 * kThreads) == 0, "pieces per thread");
     u32x4* te4 = reinterpret_cast<u32x4*>(lds.te);
+    for (uint32_t first = tid; first < kPieces; first += 8 * kThreads) {
+        uint32_t v[8];
 #pragma unroll
-    for (uint32_t k = 0; k < kPerThread; ++k) {
-        const u32x4 q = {v[k], v[k], v[k], v[k]};
-        te4[k * kGroupThreads + tid] = q;
+        for (uint32_t k = 0; k < 8; ++k) {
+            const uint32_t g = first + k * kThreads;  // piece number
+            const uint32_t pair = g >> 12, row = (g >> 4) & 255, t = 2 * pair + ((g >> 3) & 1);
+            v[k] = kt->te[t][row];
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < 8; ++k) {
+            const u32x4 q = {v[k], v[k], v[k], v[k]};
+            te4[first + k * kThreads] = q;
+        }
     }
-    const Block* from = kMatrixHash ? reinterpret_cast<const Block*>(kt->hash_image) : kt->ghash[kRowPower];
-    constexpr uint32_t kEntries = (kMatrixHash ? kHashImages : 1) * kNibbleTableEntries;
-    for (uint32_t i = tid; i < kEntries; i += kGroupThreads) lds.gh[i] = from[i];
+    if constexpr (kHash != FillHash::kNone) {
+        constexpr bool kMatrix = kHash == FillHash::kMatrix;
+        const Block* from = kMatrix ? reinterpret_cast<const Block*>(kt->hash_image) : kt->ghash[kRowPower];
+        constexpr uint32_t kEntries = (kMatrix ? kHashImages : 1) * kNibbleTableEntries;
+        for (uint32_t i = tid; i < kEntries; i += kThreads) lds.gh[i] = from[i];
+    }
 }
 
-// One unit of one chunk, walked by one wavefront in rows of 64 blocks: keystream, XOR, and the
-// lane's GHASH sum over the unit's rows, sum over rows r of C(r, lane) * (H^64)^(rows after r),
-// left in y.  unit 0 also takes "block -1", whose counter block is J0, and stores E_K(J0).
-// kSingleRows: units of one row (unit_power = kRowPower) take the row body without unit constants
-// and without a hash multiplication, for the launches whose latency counts: forming the constants
-// is two rounds of dependent lookups, 0.3 us before a lone row of 2.6 us.
-template <bool kDecrypt, int kRounds, bool kThrough, bool kMatrixHash, bool kSingleRows>
-__device__ __forceinline__ void walk_unit(const KeyTables* __restrict__ kt,
-                                          const uint32_t* __restrict__ rk, AesAddr& A,
+// The blocks [b0, b1) of one chunk, walked by one wavefront in rows of 64 that end at b1: keystream,
+// XOR, and the lane's GHASH sum over the rows, sum over rows r of C(r, lane) * (H^64)^(rows after
+// r), left in y.  Negative block numbers are those of the AAD and "block -1" (see bulk_row).
+// last: b1 is the chunk's end.
+template <bool kDecrypt, int kRounds, bool kThrough, bool kMatrixHash, class StoreMask>
+__device__ __forceinline__ void walk_unit(const uint32_t* __restrict__ rk, AesAddr& A,
                                           uint32_t lane, uint32_t wave, uint32_t lds_base,
-                                          const uint8_t* src,
-                                          uint8_t* dst, uint64_t len, const uint8_t* aad,
-                                          uint32_t aad_len, uint32_t unit, uint32_t nunits,
-                                          uint32_t first_blocks, uint32_t unit_power,
-                                          const Block& j, Block* __restrict__ ekj0_out,
-                                          uint32_t y[4]) {
-    // What describes the unit is the same in every lane, and was fetched from memory just now:
-    // moved to scalar registers here, (1) the wait for it comes before the row loop (placed at
-    // the first use inside the loop, that wait would make every row wait for the previous row's
-    // store as well), (2) which rows are edge rows is decided by a scalar branch, and (3) the
-    // payload addresses are a scalar base plus the lane's offset.  (The length, which only edge
-    // rows look at, stays where it is: scalar registers are short, and one that is spilled
-    // costs a vector instruction per use.)
-    // (the builtin returns a signed int: without the casts to uint32_t a low half with its top
-    // bit set would be sign-extended over the high half)
-    auto same_in_all_lanes = [](uint64_t v) __attribute__((always_inline)) {
-        const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-        return (uint64_t)lo | ((uint64_t)hi << 32);
-    };
-    src = reinterpret_cast<const uint8_t*>(same_in_all_lanes(reinterpret_cast<uint64_t>(src)));
-    dst = reinterpret_cast<uint8_t*>(same_in_all_lanes(reinterpret_cast<uint64_t>(dst)));
-    unit = __builtin_amdgcn_readfirstlane(unit);
-    nunits = __builtin_amdgcn_readfirstlane(nunits);
-    first_blocks = __builtin_amdgcn_readfirstlane(first_blocks);
-    unit_power = __builtin_amdgcn_readfirstlane(unit_power);
-
-    // the unit's blocks [b0, b1) of the chunk
-    const int64_t b0 =
-        unit == 0 ? -1 : (int64_t)first_blocks + ((int64_t)(unit - 1) << unit_power);
-    const int64_t b1 = unit == 0 ? (int64_t)first_blocks : b0 + ((int64_t)1 << unit_power);
+                                          const uint8_t* src, uint8_t* dst, uint64_t len,
+                                          int64_t b0, int64_t b1, bool last, const AadBlocks& aad,
+                                          const Block& j, StoreMask&& store_mask, uint32_t y[4]) {
     const uint32_t nrows = (uint32_t)((b1 - b0 + kRowBlocks - 1) / kRowBlocks);
-
     // a row's counter blocks: inc32^(blk + 1)(J0), the first 96 bits of J0, then its counter field
     // plus blk + 1 modulo 2^32 (SP 800-38D 6.2, 7.1 step 3; ctr1 is that field plus 1, 2 for a
     // 96-bit IV)
     const uint32_t ctr1 = __builtin_amdgcn_readfirstlane(bswap32(j.w[3])) + 1u;
-
-    Block aad_y{{0, 0, 0, 0}};
-    if (unit == 0 && aad_len != 0) aad_y = aad_hash(kt, aad, aad_len);
-
-    // rows are aligned to the unit's end; only rows at the chunk's start can have idle lanes
-    // (block index below 0) or block 0, only its very last row can hold a ragged block
-    int64_t row_blk = b1 - (int64_t)nrows * kRowBlocks;
-    if constexpr (kSingleRows) {
-        if (unit_power == kRowPower) {
-            GhashNone G;
-            // unit 0 may have a row of its own for "block -1" first, which leaves a sum of zero
-            for (uint32_t r = 0; r < nrows; ++r, row_blk += kRowBlocks) {
-                const bool edge = row_blk <= 0 || (unit + 1 == nunits && r + 1 == nrows);
-                const CtrBlock C{j.w[0], j.w[1], j.w[2], (uint32_t)row_blk + lane + ctr1};
-                bulk_row<kDecrypt, kRounds, kThrough>(rk, A, C, src, dst, len, row_blk + lane,
-                                                      edge, aad_y, ekj0_out, lds_base, G);
-            }
-            for (int k = 0; k < 4; ++k) y[k] = G.w[k];
-            return;
-        }
-    }
     std::conditional_t<kMatrixHash, GhashRowMatrix, GhashRowMul> G;
     G.start(lds_base, lane);
+    int64_t row_blk = b1 - (int64_t)nrows * kRowBlocks;
     for (uint32_t r = 0; r < nrows;) {
         // a segment: kSegmentRows rows, or all seventeen of a unit 0 that has that many
         const uint32_t first_ctr = (uint32_t)row_blk + ctr1;
@@ -1207,12 +1312,21 @@ __device__ __forceinline__ void walk_unit(const KeyTables* __restrict__ kt,
         const uint32_t left = nrows - r;
         const uint32_t end = left <= kSegmentRows + 1 ? nrows : r + kSegmentRows;
         for (; r < end; ++r, row_blk += kRowBlocks, C.rel += kRowBlocks) {
-            const bool edge = row_blk <= 0 || (unit + 1 == nunits && r + 1 == nrows);
-            bulk_row<kDecrypt, kRounds, kThrough>(rk, A, C, src, dst, len, row_blk + lane, edge,
-                                                  aad_y, ekj0_out, lds_base, G);
+            const bool edge = row_blk < 0 || (last && r + 1 == nrows);
+            const RowPayload p = load_row(src, len, row_blk + lane, edge);
+            bulk_row<kDecrypt, kRounds, kThrough>(rk, A, C, p, dst, row_blk + lane, edge, aad,
+                                                  store_mask, lds_base, G);
         }
     }
     G.home(y);
+}
+
+// (the builtin returns a signed int: without the casts to uint32_t a low half with its top
+// bit set would be sign-extended over the high half)
+__device__ __forceinline__ uint64_t same_in_all_lanes(uint64_t v) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return (uint64_t)lo | ((uint64_t)hi << 32);
 }
 
 }  // namespace
@@ -1240,7 +1354,7 @@ __global__ __launch_bounds__(kGroupThreads) void bulk_kernel(
     const uint32_t lds_base = lds_offset(&lds);
 
     const uint32_t tid = threadIdx.x;
-    fill_bulk_lds<kMatrixHash>(lds, kt, tid);
+    fill_bulk_lds<kMatrixHash ? FillHash::kMatrix : FillHash::kTable, kGroupThreads>(lds, kt, tid);
     __syncthreads();
 
     const uint32_t lane = tid & 63;
@@ -1262,10 +1376,38 @@ __global__ __launch_bounds__(kGroupThreads) void bulk_kernel(
         while (unit_base[chunk + 1] <= item) ++chunk;  // ends: unit_base[nchunks] > item
         const ChunkDesc* __restrict__ cd = chunks + chunk;
         const Block j = chunk_j0(kt, ivs, j0, chunk, cd->index);
+        // What describes the unit is the same in every lane, and was fetched from memory just now:
+        // moved to scalar registers here, (1) the wait for it comes before the row loop (placed at
+        // the first use inside the loop, that wait would make every row wait for the previous
+        // row's store as well), (2) which rows are edge rows is decided by a scalar branch, and
+        // (3) the payload addresses are a scalar base plus the lane's offset.  (The length and the
+        // AAD, which only edge rows look at, stay where they are: scalar registers are short, and
+        // one that is spilled costs a vector instruction per use.)
+        const uint8_t* src = reinterpret_cast<const uint8_t*>(
+            same_in_all_lanes(reinterpret_cast<uint64_t>(cd->src)));
+        uint8_t* dst = reinterpret_cast<uint8_t*>(
+            same_in_all_lanes(reinterpret_cast<uint64_t>(cd->dst)));
+        const uint32_t unit = __builtin_amdgcn_readfirstlane(item - cd->unit_base);
+        const uint32_t nunits = __builtin_amdgcn_readfirstlane(cd->nunits);
+        const uint32_t first_blocks = __builtin_amdgcn_readfirstlane(cd->first_blocks);
+        AadBlocks aad = aad_blocks(cd->aad, cd->aad_len);
+        uint64_t len = cd->len;
+        asm volatile("" : "+v"(len), "+v"(aad.bytes), "+v"(aad.len), "+v"(aad.blocks));  // (1) for these
+        // unit 0 also takes the blocks before block 0
+        const int64_t b1 = (int64_t)first_blocks + ((int64_t)unit << unit_power);
+        int64_t b0 = b1 - ((int64_t)1 << unit_power);
+        if (unit == 0) {
+            b0 = -(int64_t)__builtin_amdgcn_readfirstlane(lead_blocks(cd->aad_len));
+            aad.prepare(kt->ghash[0]);
+        }
+        Block* mask_out = ekj0 + chunk;
         uint32_t y[4];
-        walk_unit<kDecrypt, kRounds, false, kMatrixHash, false>(
-            kt, rk, A, lane, tid >> 6, lds_base, cd->src, cd->dst, cd->len, cd->aad, cd->aad_len,
-            item - cd->unit_base, cd->nunits, cd->first_blocks, unit_power, j, ekj0 + chunk, y);
+        walk_unit<kDecrypt, kRounds, false, kMatrixHash>(
+            rk, A, lane, tid >> 6, lds_base, src, dst, len, b0, b1, unit + 1 == nunits, aad, j,
+            [&](uint32_t s0, uint32_t s1, uint32_t s2, uint32_t s3) __attribute__((always_inline)) {
+                *mask_out = Block{{s0, s1, s2, s3}};
+            },
+            y);
         sets[(uint64_t)item * 64 + lane] = Block{{y[0], y[1], y[2], y[3]}};
         if (one_each) break;
         if (lane == 0)
@@ -1458,15 +1600,44 @@ __device__ __forceinline__ void fold_lanes_by_four(uint32_t lane_tables, uint32_
     }
 }
 
+// Writes the tag, or compares it with the one received and writes the verdict (SP 800-38D 7.2),
+// wiping the output of a rejected chunk.  tag, and when decrypting `received`, are the same in
+// every lane.
+template <bool kDecrypt>
+__device__ __forceinline__ void write_or_compare_tag(const Block& tag, uint8_t* __restrict__ tag_out,
+                                                     const Block& received,
+                                                     uint8_t* __restrict__ ok, uint8_t* dst,
+                                                     uint64_t len, uint32_t lane) {
+    if (!kDecrypt) {
+        if (lane == 0) global_write_block_any(tag_out, tag);
+        return;
+    }
+    // all 16 bytes, no data-dependent exit
+    uint32_t diff = 0;
+    for (int k = 0; k < 4; ++k) diff |= received.w[k] ^ tag.w[k];
+    diff = __builtin_amdgcn_readfirstlane(diff);
+    if (lane == 0) *ok = diff == 0 ? 1 : 0;
+    if (diff != 0) {
+        // rejected: unauthenticated plaintext must not stay behind; the wavefront zero-fills
+        // exactly len bytes
+        const uint64_t whole = len / 16;
+        uint4* d = reinterpret_cast<uint4*>(dst);
+        for (uint64_t b = lane; b < whole; b += 64) d[b] = make_uint4(0, 0, 0, 0);
+        for (uint64_t b = whole * 16 + lane; b < len; b += 64) dst[b] = 0;
+    }
+}
+
 // From the GHASH state over A and C (the same in every lane) to the end of the invocation:
-// length block, one more H, mask with E_K(J0) (SP 800-38D 7.1 steps 5-6); then write the tag, or
-// compare it and write the verdict (7.2), wiping the output of a rejected chunk.
+// length block, one more H, mask with E_K(J0) (SP 800-38D 7.1 steps 5-6), tag or verdict.
 // h_table: LDS address of the nibble table of H.
 template <bool kDecrypt>
 __device__ __forceinline__ void finish_chunk(uint32_t h_table, uint32_t y[4],
                                              const uint32_t mask[4], const ChunkDesc& cd,
                                              uint8_t* __restrict__ tags, uint8_t* __restrict__ ok,
                                              uint32_t lane) {
+    uint8_t* const tag_at = tags + (uint64_t)cd.index * 16;
+    Block received{{0, 0, 0, 0}};
+    if (kDecrypt) received = global_read_block_any(tag_at);
     // [8 |A|]_64 || [8 |C|]_64, big endian
     const uint64_t abits = (uint64_t)cd.aad_len * 8, cbits = cd.len * 8;
     y[0] ^= bswap32((uint32_t)(abits >> 32));
@@ -1474,27 +1645,8 @@ __device__ __forceinline__ void finish_chunk(uint32_t h_table, uint32_t y[4],
     y[2] ^= bswap32((uint32_t)(cbits >> 32));
     y[3] ^= bswap32((uint32_t)cbits);
     ghash_mul_lds(h_table, y);
-    const uint32_t t[4] = {y[0] ^ mask[0], y[1] ^ mask[1], y[2] ^ mask[2], y[3] ^ mask[3]};
-
-    uint8_t* tp = tags + (uint64_t)cd.index * 16;
-    if (!kDecrypt) {
-        if (lane == 0)
-            for (int b = 0; b < 16; ++b) tp[b] = (uint8_t)(t[b / 4] >> (8 * (b % 4)));
-    } else {
-        // all 16 bytes, no data-dependent exit (every lane holds the same values)
-        uint32_t diff = 0;
-        for (int b = 0; b < 16; ++b) diff |= (uint32_t)tp[b] ^ ((t[b / 4] >> (8 * (b % 4))) & 0xFF);
-        diff = __builtin_amdgcn_readfirstlane(diff);
-        if (lane == 0) ok[cd.index] = diff == 0 ? 1 : 0;
-        if (diff != 0) {
-            // rejected: unauthenticated plaintext must not stay behind; the wavefront zero-fills
-            // exactly len bytes
-            const uint64_t whole = cd.len / 16;
-            uint4* d = reinterpret_cast<uint4*>(cd.dst);
-            for (uint64_t b = lane; b < whole; b += 64) d[b] = make_uint4(0, 0, 0, 0);
-            for (uint64_t b = whole * 16 + lane; b < cd.len; b += 64) cd.dst[b] = 0;
-        }
-    }
+    const Block t{{y[0] ^ mask[0], y[1] ^ mask[1], y[2] ^ mask[2], y[3] ^ mask[3]}};
+    write_or_compare_tag<kDecrypt>(t, tag_at, received, ok + cd.index, cd.dst, cd.len, lane);
 }
 
 }  // namespace
@@ -1620,48 +1772,96 @@ template __global__ void final_kernel<true>(const KeyTables*, const ChunkDesc*, 
                                             uint32_t*, uint32_t);
 
 // ------------------------------------------------------------------------------------------
-// A few chunks in ONE launch (the paper's swaps come a few chunks at a time, section 5.1).
-// Descriptors are kernel arguments.  Every wavefront walks one unit as in bulk_kernel; then the
-// workgroup, whose sixteen units belong to one chunk, folds their sets as a tree in LDS (the round
-// tables are no longer needed: their space takes the GHASH tables of the fold).  A chunk of one
-// workgroup is finished there and then.  Otherwise the workgroup writes its set through to memory
-// (device-scope stores, no cache-wide fence), waits for the stores to complete and counts itself
-// in on the chunk's arrival word; the workgroup that arrives last reads the workgroups' sets
-// (device-scope loads) and folds them, each wavefront a run of them and then a tree across the
-// wavefronts, folds the lanes and writes the tag or the verdict.  Nobody waits for anybody: every
-// workgroup runs to its end whatever the others do.
-//
-// LDS after the round tables are done with, in tables of 8 KiB:
-//   0..8   lane tree (see fold_lanes_by_four); the first is H's, for the length block
-//   9..12  H^(2^(p + j)), j = 0 .. 3: tree over the workgroup's sixteen units (p = unit_power);
-//          later, in the workgroup that arrives last,
-//          H^(2^(p + 4 + l + j)), j = 0 .. 3: tree over the sixteen wavefronts' runs of 2^l sets
-//   13     H^(2^(p + 4)): from one workgroup's set to the next
-//   15..16 sixteen sets, one per wavefront
+// A few chunks in ONE launch (the paper's swaps come a few chunks at a time, section 5.1): here
+// the length of the chain of dependent steps counts, not the work.  Descriptors are kernel
+// arguments.  Every wavefront walks one unit; units are of one row as long as the chip has a
+// wavefront for each, and workgroups of four wavefronts as long as there is a compute unit for
+// each (a row takes a lone wavefront 2.6 us, sixteen on one compute unit 4.3 us).  Then
+//   1. the workgroup folds its units' sets into one as a tree in LDS (two to four multiplications
+//      from nibble tables, which take the round tables' place);
+//   2. all its threads form the 64 products of the set's lanes with H^64 .. H^1, bit by bit from
+//      the powers themselves (KeyTables::dot), eight to thirty-two bits of a lane each, and add
+//      them up: no further tables, and one step where a tree over the lanes takes six;
+//   3. one wavefront multiplies the sum by the power of H that takes it to the chunk's end
+//      (KeyTables::hop).  The workgroup with "block -1" adds the length block and E_K(J0), so
+//      that a chunk's tag is plainly the sum of its workgroups' results;
+//   4. a chunk of one workgroup is finished there and then.  Otherwise the result is written
+//      through to memory (device-scope stores, no cache-wide fence), waited for, and the
+//      workgroup counts itself in on the chunk's arrival word; the one that arrives last adds the
+//      results up (device-scope loads) and writes the tag or the verdict.  Nobody waits for
+//      anybody: every workgroup runs to its end whatever the others do.  An arrival word serves
+//      about one workgroup per 11 ns, so those of a chunk of more than 64 are counted in
+//      sixteens first.
+// What a step needs from memory is fetched before the row (tree tables, powers) or by wavefronts
+// that the tree leaves idle.
+// LDS after the round tables are done with, in tables of 8 KiB: 0..3 H^(2^(p + j)), the tree over the
+// workgroup's units (p = unit_power); 4..5 and 6 its sets.
+// Measured against the kernel this replaces (a tree over lanes and workgroups by tables, an extra
+// row for E_K(J0)), per call back to back: one 320 KiB chunk 19.8 -> 14.1 us, one of 2 MiB decrypted
+// 27.9 -> 15.7 us.
 namespace {
 
-constexpr uint32_t kSwapLaneTables = 0, kSwapUnitTables = kLaneTables, kSwapRunTable = 13,
-                   kSwapWaveTables = kLaneTables, kSwapPartial = 15;
-static_assert(kSwapUnitTables + 4 <= kSwapRunTable && kSwapRunTable < kSwapPartial, "table slots");
-static_assert((kSwapPartial + 2) * kLdsGhBytes <= kLdsBytes, "tables and sets fit the LDS object");
+// XOR of the sixteen lanes of a row, left in all of them (DPP: pairs, quads, halves, row)
+__device__ __forceinline__ uint32_t row_summed(uint32_t v) {
+    v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);   // quad_perm 1 0 3 2
+    v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);   // quad_perm 2 3 0 1
+    v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);  // row_half_mirror
+    v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true);  // row_mirror
+    return v;
+}
 
-// sixteen sets (one per wavefront, in y) -> one in wavefront 0, leaves counted back from the
-// last: rounds j = 0 .. 3 with H^(2^(first_power + j)) at tables[first_table + j]
-__device__ __forceinline__ void fold_waves(Block (*tables)[kNibbleTableEntries], Block (*partial)[64],
-                                           uint32_t first_table, uint32_t wave, uint32_t lane,
-                                           uint32_t y[4]) {
-    // every wavefront passes every barrier; only the shrinking front half has work to do
-    for (uint32_t j = 0; j < 4; ++j) {
-        partial[wave][lane] = Block{{y[0], y[1], y[2], y[3]}};
-        __syncthreads();
-        if (wave < (kWavesPerGroup >> (j + 1))) {
-            const Block a = partial[2 * wave][lane], b = partial[2 * wave + 1][lane];
-            y[0] = a.w[0], y[1] = a.w[1], y[2] = a.w[2], y[3] = a.w[3];
-            ghash_mul_lds(lds_offset(tables[first_table + j]), y);
-            y[0] ^= b.w[0], y[1] ^= b.w[1], y[2] ^= b.w[2], y[3] ^= b.w[3];
+// acc * x + (top bit first: bit 7 - i of `byte` at step i ? q : 0), for all eight bits
+template <int kSlices>
+__device__ __forceinline__ GfWords bits_times(const uint32_t byte[kSlices], const GfWords q[kSlices]) {
+    GfWords acc{{0, 0, 0, 0}};
+#pragma unroll
+    for (int bit = 0; bit < 8; ++bit) {  // the byte's lowest bit is its highest coefficient
+        if (bit != 0) gfw_mul_x(acc);
+#pragma unroll
+        for (int s = 0; s < kSlices; ++s) {
+            const uint32_t m = (uint32_t)((int32_t)(byte[s] << (31 - bit)) >> 31);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc.a[k] ^= q[s].a[k] & m;
         }
-        __syncthreads();
     }
+    return acc;
+}
+
+// times x^32: the word that leaves at the end comes back in at the front
+__device__ __forceinline__ void gfw_mul_x32(GfWords& v) {
+    const uint32_t over = v.a[3];
+    v.a[3] = v.a[2];
+    v.a[2] = v.a[1];
+    v.a[1] = v.a[0] ^ (over << 31) ^ (over << 30) ^ (over << 25);
+    v.a[0] = 0;
+    gfw_fold_word(v, over);
+}
+
+// steps 2 and 3 of the kernel, per wavefront: this wavefront's share of the 64 products, summed
+// over its lanes.  Wavefront w of 16 / kSlices takes bytes kSlices * w .. of every lane's sum.
+template <int kSlices>
+__device__ __forceinline__ GfWords dot_share(const Block& y, uint32_t wave, const GfWords q[kSlices]) {
+    const uint32_t first = kSlices * wave, w = first / 4;
+    const uint32_t word = w == 0 ? y.w[0] : w == 1 ? y.w[1] : w == 2 ? y.w[2] : y.w[3];
+    uint32_t byte[kSlices];
+#pragma unroll
+    for (int s = 0; s < kSlices; ++s) byte[s] = word >> (8 * (first % 4 + s));
+    GfWords acc = bits_times<kSlices>(byte, q);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc.a[k] = rows_summed(row_summed(acc.a[k]));
+    return acc;
+}
+
+// this lane's share of (the length block) * H, to be summed over the lanes, from H's nibble table in
+// memory: lane p < 32 looks up nibble p
+__device__ __forceinline__ Block length_block_entry(const Block* __restrict__ h_table,
+                                                    uint64_t aad_len, uint64_t len, uint32_t lane) {
+    const uint64_t abits = aad_len * 8, cbits = len * 8;
+    const uint32_t w = (lane / 8) % 4;
+    const uint32_t be = w == 0 ? (uint32_t)(abits >> 32) : w == 1 ? (uint32_t)abits
+                        : w == 2 ? (uint32_t)(cbits >> 32) : (uint32_t)cbits;
+    const uint32_t nibble = (be >> (28 - 4 * (lane % 8))) & 15;
+    return lane < 32 ? h_table[lane * 16 + nibble] : Block{{0, 0, 0, 0}};
 }
 
 }  // namespace
@@ -1669,138 +1869,224 @@ __device__ __forceinline__ void fold_waves(Block (*tables)[kNibbleTableEntries],
 template <bool kDecrypt, int kRounds>
 __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
     const KeyTables* __restrict__ kt, const ArgBatch batch, const uint8_t* __restrict__ ivs,
-    Block* __restrict__ ekj0, Block* __restrict__ sets, uint32_t* __restrict__ arrive,
-    uint8_t* __restrict__ tags, uint8_t* __restrict__ ok) {
+    Block* __restrict__ slots, uint32_t* __restrict__ arrive, uint8_t* __restrict__ tags,
+    uint8_t* __restrict__ ok) {
     __shared__ BulkLds lds;
-    __shared__ uint32_t last_flag;
+    __shared__ Block mask;                       // E_K(J0), in the workgroup with "block -1"
+    __shared__ GfWords shares[kWavesPerGroup];
     const uint32_t lds_base = lds_offset(&lds);
-    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    fill_bulk_lds<false>(lds, kt, tid);
+    const uint32_t tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t wave_power = batch.wave_power, nwaves = 1u << wave_power;
+    const uint32_t p = batch.unit_power;
 
-    // this workgroup's chunk: the one whose workgroups include blockIdx.x (host: the grid is the
-    // sum of the chunks' ngroups, so the scan ends inside the array)
-    uint32_t chunk = 0;
-    while (chunk + 1 < batch.nchunks && batch.c[chunk + 1].group_base <= blockIdx.x) ++chunk;
+    // this workgroup's chunk: the last one whose first workgroup is not behind it
+    const uint32_t first = lane < batch.nchunks ? batch.group_base[lane] : ~0u;
+    const uint32_t chunk = __builtin_amdgcn_readfirstlane(
+        (uint32_t)__popcll(__ballot(first <= blockIdx.x)) - 1u);
     const ArgChunk cd = batch.c[chunk];
-    const uint32_t unit_power = batch.unit_power;
-    // units are dealt to the chunk's workgroups counted back from its end: workgroup g of G takes
-    // units nunits - 16 (G - g) + wave; a negative number is a wavefront without a unit
-    const uint32_t g = blockIdx.x - cd.group_base;
-    const int32_t unit = (int32_t)cd.nunits - (int32_t)(kWavesPerGroup * (cd.ngroups - g)) + (int32_t)wave;
-    __syncthreads();
+    const uint32_t ngroups = batch.group_base[chunk + 1] - batch.group_base[chunk];
+    const uint32_t g = blockIdx.x - batch.group_base[chunk];
+    // its units, counted back from the chunk's end; a negative number is a wavefront without one
+    const int64_t nblk = (int64_t)((cd.len + 15) / 16);
+    const int64_t lead = lead_blocks(cd.aad_len);
+    const int32_t nunits = (int32_t)((nblk + lead + ((int64_t)1 << p) - 1) >> p);
+    const int32_t unit = nunits - (int32_t)((ngroups - g) << wave_power) + (int32_t)wave;
+    const int64_t b1 = nblk - ((int64_t)(nunits - 1 - unit) << p);
+    const int64_t b0 = unit == 0 ? -lead : b1 - ((int64_t)1 << p);
+    // is "block -1" in this workgroup?
+    const int64_t end = nblk - ((int64_t)(ngroups - 1 - g) << (p + wave_power));
+    const bool has_mask = end >= 0 && end - ((int64_t)1 << (p + wave_power)) < 0;
 
-    uint32_t y[4] = {0, 0, 0, 0};
-    if (unit >= 0) {
-        uint32_t rk[4 * (kRounds + 1)];
+    uint32_t rk[4 * (kRounds + 1)];
 #pragma unroll
-        for (int i = 0; i < 4 * (kRounds + 1); ++i) rk[i] = kt->rk[i];
-        AesAddr A;
-        aes_addr_init(A, lane, rk + 4 * kRounds);
-        const Block j = j0_from_iv(kt, ivs + (uint64_t)cd.index * 12, 12);
-        // When decrypting, the workgroup that finishes the chunk may have to wipe plaintext that
-        // other workgroups (on other XCDs) wrote: their stores go through to memory, and must be
-        // there before the arrival is counted.  So must E_K(J0), which unit 0's wavefront stores.
-        walk_unit<kDecrypt, kRounds, kDecrypt, false, true>(kt, rk, A, lane, wave, lds_base, cd.src, cd.dst, cd.len,
-                                               cd.aad, cd.aad_len, (uint32_t)unit, cd.nunits,
-                                               cd.first_blocks, unit_power, j, ekj0 + chunk, y);
-        if (kDecrypt || unit == 0) wait_for_own_global_accesses();
+    for (int i = 0; i < 4 * (kRounds + 1); ++i) rk[i] = kt->rk[i];
+    const Block j = j0_from_iv(kt, ivs + (uint64_t)cd.index * 12, 12);
+    const bool single = p == kRowPower;
+    if (wave_power == 2) fill_bulk_lds<FillHash::kNone, 256>(lds, kt, tid);
+    else if (wave_power == 3) fill_bulk_lds<FillHash::kNone, 512>(lds, kt, tid);
+    else fill_bulk_lds<FillHash::kNone, 1024>(lds, kt, tid);
+    if (!single)
+        for (uint32_t i = tid; i < kNibbleTableEntries; i += 64u << wave_power)
+            lds.gh[i] = kt->ghash[kRowPower][i];
+
+    // tree tables and powers of H: entry k * threads + tid of the 512 * wave_power, slices
+    // 16 / nwaves * wave .. of lane's
+    u32x4 tree[4];
+    GfWords q[4];
+    // the last wavefront, idle in the tree, finishes the chunk
+    const bool finisher = wave == nwaves - 1;
+    uint8_t* const tag_at = tags + (uint64_t)cd.index * 16;
+    Block extra{{0, 0, 0, 0}};     // what the workgroup with "block -1" adds to the tag
+    GfWords hop{{0, 0, 0, 0}};     // the power of H to the chunk's end, then times x^(8 (lane % 16))
+    Block received{{0, 0, 0, 0}};  // the tag to compare with
+    auto fetch_ahead = [&]() __attribute__((always_inline)) {
+        const u32x4* from = reinterpret_cast<const u32x4*>(kt->ghash[p]);
+        const uint32_t per_thread = (8 * wave_power) >> wave_power;  // 4, 3, 2
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k)
+            if (k < per_thread) tree[k] = from[(k << (6 + wave_power)) + tid];
+        const uint32_t slices = kDotSlices >> wave_power;            // 4, 2, 1
+#pragma unroll
+        for (uint32_t s = 0; s < 4; ++s)
+            if (s < slices) q[s] = kt->dot[lane][slices * wave + s];
+        if (finisher) {
+            hop = kt->hop[p + wave_power - kHopMinPower][ngroups - 1 - g];
+            if (has_mask) extra = length_block_entry(kt->ghash[0], cd.aad_len, cd.len, lane);
+            if (kDecrypt) received = global_read_block_any(tag_at);
+        }
+    };
+
+    AadBlocks aad = aad_blocks(cd.aad, cd.aad_len);
+    auto keep_mask = [&](uint32_t s0, uint32_t s1, uint32_t s2, uint32_t s3)
+        __attribute__((always_inline)) { mask = Block{{s0, s1, s2, s3}}; };
+    uint32_t y[4] = {0, 0, 0, 0};
+    if (single) {
+        // one row of 64 blocks up to b1
+        const int64_t blk = b1 - kRowBlocks + lane;
+        const bool edge = b1 < kRowBlocks || b1 == nblk;
+        RowPayload row{0, 0, 0, 0, 0, false};
+        if (unit >= 0) row = load_row(cd.src, cd.len, blk, edge);
+        fetch_ahead();
+        __syncthreads();  // the tables are in place
+        if (unit >= 0) {
+            if (unit == 0) aad.prepare(kt->ghash[0]);
+            AesAddr A;
+            aes_addr_init(A, lane, rk + 4 * kRounds);
+            GhashNone G;
+            const CtrBlock C{j.w[0], j.w[1], j.w[2], (uint32_t)blk + bswap32(j.w[3]) + 1u};
+            bulk_row<kDecrypt, kRounds, kDecrypt>(rk, A, C, row, cd.dst, blk, edge, aad, keep_mask,
+                                                  lds_base, G);
+            for (int k = 0; k < 4; ++k) y[k] = G.w[k];
+        }
+    } else {
+        __syncthreads();
+        if (unit >= 0) {
+            if (unit == 0) aad.prepare(kt->ghash[0]);
+            AesAddr A;
+            aes_addr_init(A, lane, rk + 4 * kRounds);
+            walk_unit<kDecrypt, kRounds, kDecrypt, false>(rk, A, lane, wave, lds_base, cd.src,
+                                                          cd.dst, cd.len, b0, b1, b1 == nblk, aad,
+                                                          j, keep_mask, y);
+        }
+        fetch_ahead();
     }
-    __syncthreads();  // the round tables are done with: their LDS now takes GHASH tables
+    __syncthreads();  // the round tables are done with: their LDS now takes the tree's
 
     Block(*tables)[kNibbleTableEntries] = reinterpret_cast<Block(*)[kNibbleTableEntries]>(&lds);
-    Block(*partial)[64] = reinterpret_cast<Block(*)[64]>(tables[kSwapPartial]);
-    const bool alone = cd.ngroups == 1;
-    if (cd.nunits > 1)
-        for (uint32_t j = 0; j < 4; ++j)
-            copy_power_table(tables[kSwapUnitTables + j], kt, unit_power + j, tid, kGroupThreads);
-    if (alone) copy_lane_tables(tables + kSwapLaneTables, kt, tid, kGroupThreads);
+    Block(*sets[2])[64] = {reinterpret_cast<Block(*)[64]>(tables[4]),
+                           reinterpret_cast<Block(*)[64]>(tables[6])};
+    {
+        u32x4* to = reinterpret_cast<u32x4*>(tables);
+        const uint32_t per_thread = (8 * wave_power) >> wave_power;
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k)
+            if (k < per_thread) to[(k << (6 + wave_power)) + tid] = tree[k];
+    }
+    sets[0][wave][lane] = Block{{y[0], y[1], y[2], y[3]}};
     __syncthreads();
-    if (cd.nunits > 1) fold_waves(tables, partial, kSwapUnitTables, wave, lane, y);
-    else if (wave == kWavesPerGroup - 1) {
-        // a single unit sits in the last wavefront: hand its set to wavefront 0
-        partial[0][lane] = Block{{y[0], y[1], y[2], y[3]}};
+
+    if (finisher) {
+        if (has_mask) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) extra.w[k] = rows_summed(row_summed(extra.w[k]));
+            block_xor(extra, mask);
+        }
+        GfWords t = hop;
+        gfw_mul_x8(t);
+        if (lane & 1) hop = t;
+        t = hop;
+        gfw_mul_x8(t), gfw_mul_x8(t);
+        if (lane & 2) hop = t;
+        t = hop;
+        gfw_mul_x32(t);
+        if (lane & 4) hop = t;
+        t = hop;
+        gfw_mul_x32(t), gfw_mul_x32(t);
+        if (lane & 8) hop = t;
     }
-    if (cd.nunits <= 1) {
-        __syncthreads();
-        if (wave == 0) {
-            const Block a = partial[0][lane];
+    // 1. every wavefront passes every barrier; only the shrinking front half has work to do
+    for (uint32_t level = 0; level < wave_power; ++level) {
+        if (wave < (nwaves >> (level + 1))) {
+            const Block a = sets[level & 1][2 * wave][lane], b = sets[level & 1][2 * wave + 1][lane];
             y[0] = a.w[0], y[1] = a.w[1], y[2] = a.w[2], y[3] = a.w[3];
-        }
-    }
-
-    if (!alone) {
-        // hand this workgroup's set over and count it in; the last one to arrive goes on
-        if (wave == 0) {
-            store_block_device_scope(sets + (uint64_t)blockIdx.x * 64 + lane, y[0], y[1], y[2], y[3]);
-            // the set (and E_K(J0), waited for before the last barrier) must have reached memory
-            // before the arrival is counted: both are device-scope stores, so waiting for them
-            // to complete is enough, and no cache needs writing back
-            wait_for_own_global_accesses();
-            if (lane == 0) {
-                const uint32_t before = __hip_atomic_fetch_add(arrive + chunk, 1u, __ATOMIC_RELAXED,
-                                                               __HIP_MEMORY_SCOPE_AGENT);
-                last_flag = before + 1 == cd.ngroups;
-                if (before + 1 == cd.ngroups)
-                    __hip_atomic_store(arrive + chunk, 0u, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);  // left zero for the next batch
-            }
+            ghash_mul_lds(lds_offset(tables[level]), y);
+            sets[1 - (level & 1)][wave][lane] =
+                Block{{y[0] ^ b.w[0], y[1] ^ b.w[1], y[2] ^ b.w[2], y[3] ^ b.w[3]}};
         }
         __syncthreads();
-        if (!last_flag) return;  // uniform over the workgroup
-        // the others' sets are read with device-scope loads, issued after the arrival count
-        // was seen: they come from memory, not from this XCD's caches
-
-        // runs of 2^l sets per wavefront, the smallest l with 16 * 2^l >= ngroups; leaves are
-        // counted back from the last set, missing ones at the front count as zero
-        uint32_t l = 0;
-        while ((kWavesPerGroup << l) < cd.ngroups) ++l;
-        copy_lane_tables(tables + kSwapLaneTables, kt, tid, kGroupThreads);
-        copy_power_table(tables[kSwapRunTable], kt, unit_power + 4, tid, kGroupThreads);
-        for (uint32_t j = 0; j < 4; ++j)
-            copy_power_table(tables[kSwapWaveTables + j], kt, unit_power + 4 + l + j, tid,
-                             kGroupThreads);
-        const uint32_t run = 1u << l, pad = (kWavesPerGroup << l) - cd.ngroups;
-        const Block* __restrict__ in = sets + (uint64_t)cd.group_base * 64 + lane;
-        y[0] = y[1] = y[2] = y[3] = 0;
-        const uint32_t first_leaf = wave * run;
-        __syncthreads();
-        bool started = false;  // uniform over the wavefront, like everything in this loop
-        for (uint32_t k = 0; k < run; ++k) {
-            const uint32_t leaf = first_leaf + k;
-            if (leaf < pad) continue;
-            if (started) ghash_mul_lds(lds_offset(tables[kSwapRunTable]), y);
-            started = true;
-            const Block b = load_block_device_scope(in + (uint64_t)(leaf - pad) * 64);
-            y[0] ^= b.w[0], y[1] ^= b.w[1], y[2] ^= b.w[2], y[3] ^= b.w[3];
+    }
+    // 2.
+    {
+        const Block set = sets[wave_power & 1][0][lane];
+        const GfWords share = wave_power == 2   ? dot_share<4>(set, wave, q)
+                              : wave_power == 3 ? dot_share<2>(set, wave, q)
+                                                : dot_share<1>(set, wave, q);
+        if (lane == 0) shares[wave] = share;
+    }
+    // When decrypting, the wavefront that finishes the chunk may have to wipe plaintext that
+    // others (on other XCDs) wrote: their stores go through to memory, and must be there before
+    // the arrival is counted.
+    if (kDecrypt) wait_for_own_global_accesses();
+    __syncthreads();
+    if (!finisher) return;
+    // 3.
+    GfWords sum{{0, 0, 0, 0}};
+    if (lane < nwaves) sum = shares[lane];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sum.a[k] = __builtin_amdgcn_readfirstlane(row_summed(sum.a[k]));
+    {
+        const uint32_t w = (lane / 4) % 4;
+        const uint32_t word = w == 0 ? sum.a[0] : w == 1 ? sum.a[1] : w == 2 ? sum.a[2] : sum.a[3];
+        const uint32_t byte[1] = {word >> (24 - 8 * (lane % 4))};
+        sum = bits_times<1>(byte, &hop);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) sum.a[k] = row_summed(sum.a[k]);
+    }
+    Block tag = gfw_to_block(sum);
+    block_xor(tag, extra);
+    // 4.
+    if (ngroups > 1) {
+        if (lane == 0) store_block_device_scope(slots + blockIdx.x, tag.w[0], tag.w[1], tag.w[2], tag.w[3]);
+        // the result must have reached memory before the arrival is counted: it is a device-scope
+        // store, so waiting for it to complete is enough, and no cache needs writing back
+        wait_for_own_global_accesses();
+        // counts one arrival of `of`; true in every lane if it was the last, and the word is left
+        // zero for the next batch
+        auto last_of = [&](uint32_t* word, uint32_t of) __attribute__((always_inline)) {
+            uint32_t before = 0;
+            if (lane == 0)
+                before = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const bool last = __builtin_amdgcn_readfirstlane(before) + 1 == of;
+            if (last && lane == 0)
+                __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return last;
+        };
+        uint32_t* const main_word = arrive + chunk * kArriveStride;
+        if (ngroups <= 64) {
+            if (!last_of(main_word, ngroups)) return;
+        } else {
+            const uint32_t sixteen = g / 16, base = batch.group_base[chunk] + 16 * sixteen;
+            const uint32_t in_it = ngroups - 16 * sixteen < 16 ? ngroups - 16 * sixteen : 16;
+            if (!last_of(arrive + (64 + base) * kArriveStride, in_it)) return;
+            if (!last_of(main_word, (ngroups + 15) / 16)) return;
         }
-        fold_waves(tables, partial, kSwapWaveTables, wave, lane, y);
+        // the others' results are read with device-scope loads, issued after the arrival count was
+        // seen: they come from memory, not from this XCD's caches
+        tag = Block{{0, 0, 0, 0}};
+        for (uint32_t i = lane; i < ngroups; i += 64) {
+            const Block b = load_block_device_scope(slots + batch.group_base[chunk] + i);
+            block_xor(tag, b);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) tag.w[k] = rows_summed(row_summed(tag.w[k]));
     }
-    if (wave != 0) return;
-
-    // wavefront 0 holds the chunk's 64 lane sums (nothing at all for an empty chunk)
-    Block mask;
-    if (cd.nunits == 0) {
-        const Block a = aad_hash(kt, cd.aad, cd.aad_len);
-        y[0] = a.w[0], y[1] = a.w[1], y[2] = a.w[2], y[3] = a.w[3];
-        const Block j = j0_from_iv(kt, ivs + (uint64_t)cd.index * 12, 12);
-        uint32_t e[4] = {j.w[0], j.w[1], j.w[2], j.w[3]};
-        aes_block_global(kt, e);
-        mask = Block{{e[0], e[1], e[2], e[3]}};
-    } else {
-        fold_lanes_by_four(lds_offset(tables[kSwapLaneTables]), y, lane);
-        mask = load_block_device_scope(ekj0 + chunk);
-    }
-    ChunkDesc d{};
-    d.dst = cd.dst;
-    d.len = cd.len;
-    d.aad_len = cd.aad_len;
-    d.index = cd.index;
-    finish_chunk<kDecrypt>(lds_offset(tables[kSwapLaneTables]), y, mask.w, d, tags, ok, lane);
+    write_or_compare_tag<kDecrypt>(tag, tag_at, received, ok + cd.index, cd.dst, cd.len, lane);
 }
 
 #define PGCM_INSTANTIATE_SWAP(D, R)                                                          \
     template __global__ void swap_kernel<D, R>(const KeyTables*, ArgBatch, const uint8_t*, Block*, \
-                                               Block*, uint32_t*, uint8_t*, uint8_t*)
+                                               uint32_t*, uint8_t*, uint8_t*)
 PGCM_INSTANTIATE_SWAP(false, 10);
 PGCM_INSTANTIATE_SWAP(false, 12);
 PGCM_INSTANTIATE_SWAP(false, 14);
@@ -1809,7 +2095,7 @@ PGCM_INSTANTIATE_SWAP(true, 12);
 PGCM_INSTANTIATE_SWAP(true, 14);
 #undef PGCM_INSTANTIATE_SWAP
 
-__global__ __launch_bounds__(64) void clear_words_kernel(uint32_t* __restrict__ words, uint32_t n) {
+__global__ __launch_bounds__(1024) void clear_words_kernel(uint32_t* __restrict__ words, uint32_t n) {
     for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) words[i] = 0;
 }
 

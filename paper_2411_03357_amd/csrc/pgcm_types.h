@@ -55,6 +55,19 @@ constexpr uint32_t kHashImages = 2;
 // three multiplications deep; beside H^(2^k) it needs the nibble tables of H^3, H^12 and H^48.
 constexpr uint32_t kNumLanePowers = 3;
 
+// The latency path sums a set's 64 lanes as 64 products of a sum with a known power of H, all
+// at once and bit by bit, and moves a workgroup's result to its place with one more such product:
+// it needs powers of H as plain values, held as four words with coefficient x^0 in the top bit of
+// the first (GfWords).  dot[l][t] = H^(64 - l) * x^(8 t);  hop[d][k] = H^(k 2^(8 + d) + 1).
+constexpr uint32_t kDotSlices = 16;
+constexpr uint32_t kHopMinPower = 8;    // the shortest stretch of a workgroup: 4 units of 64 blocks
+constexpr uint32_t kHopPowers = 7;      // ... and the longest: 16 units of 1024 blocks
+constexpr uint32_t kHopEntries = 256;   // workgroups of a chunk
+
+struct alignas(16) GfWords {
+    uint32_t a[4];
+};
+
 struct alignas(16) Block {
     uint32_t w[4];  // bytes 4i..4i+3 of the block, loaded little-endian into w[i]
 };
@@ -72,6 +85,8 @@ struct alignas(16) KeyTables {
     // ---- up to here the tables are part of what pgcm_copy_key_tables returns ----
     // multiplications by H^64 and by H^96 as the unit kernel's matrix operands
     uint32_t hash_image[kHashImages][kRowMatrixWords];
+    GfWords dot[64][kDotSlices];
+    GfWords hop[kHopPowers][kHopEntries];
 };
 constexpr size_t kPublicTablesBytes = offsetof(KeyTables, hash_image);
 
@@ -99,32 +114,46 @@ struct alignas(16) FoldItem {
     uint32_t pad_;
 };
 
+// The blocks before a chunk's block 0 that a kernel walks along with it: "block -1", whose keystream
+// is the tag's mask, and the AAD's blocks, numbered -n .. -1, unless there are more of them than a
+// row holds.
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+constexpr uint32_t lead_blocks(uint32_t aad_len) {
+    return aad_len <= 16 || aad_len > 64 * 16 ? 1 : (aad_len + 15) / 16;
+}
+
 // A batch of few chunks that does not fill the chip (every unit gets a wavefront of its own) is
 // done by ONE kernel, its descriptors travelling as kernel arguments: the paper's swaps arrive a
 // few chunks at a time between synchronisations (section 5.1), and for them the time of a call
-// counts, not the rate.  Every chunk gets workgroups of its own, sixteen units each, counted back
-// from the chunk's end so that only its first workgroup can be short.
-constexpr uint32_t kArgChunks = 24;
-struct alignas(16) ArgChunk {
+// counts, not the rate.  Every chunk gets workgroups of its own, as many units each as a workgroup
+// has wavefronts, counted back from the chunk's end so that only its first workgroup can be short.
+// A chunk's units cover the blocks before its block 0 as well.
+constexpr uint32_t kArgChunks = 60;
+struct ArgChunk {
     const uint8_t* src;
     uint8_t* dst;
     const uint8_t* aad;
     uint64_t len;
     uint32_t aad_len;
-    uint32_t nunits;        // 0 for an empty chunk
-    uint32_t first_blocks;  // blocks in unit 0; every later unit has 2^unit_power
     uint32_t index;         // the chunk's place in the caller's ivs, tags and ok arrays
-    uint32_t group_base;    // first workgroup of the chunk = its first set slot
-    uint32_t ngroups;       // max(1, ceil(nunits / 16))
-    uint32_t pad_[2];
 };
-static_assert(sizeof(ArgChunk) == 64, "argument layout");
-struct alignas(16) ArgBatch {
+static_assert(sizeof(ArgChunk) == 40, "argument layout");
+struct ArgBatch {
     uint32_t nchunks;
     uint32_t unit_power;
-    uint32_t pad_[2];
+    uint32_t wave_power;                  // log2 of the wavefronts per workgroup: 2, 3, 4
+    uint32_t group_base[kArgChunks + 1];  // first workgroup of every chunk; their number
     ArgChunk c[kArgChunks];
 };
+// Workgroups of a launch, and so of a chunk (KeyTables::hop has their distances).
+constexpr uint32_t kSwapMaxGroups = kHopEntries;
+// Arrival words, 64 bytes apart: one per chunk, and one per workgroup for the sixteens that the
+// workgroups of a chunk of many are counted in.
+constexpr uint32_t kArriveStride = 16;
+constexpr uint32_t kSwapArriveWords = (64 + kSwapMaxGroups) * kArriveStride;
+static_assert(kArgChunks <= 64, "arrival words of the chunks");
 
 // A batch whose chunks are all at most this long takes the small-transfer path: one kernel (the
 // paper's non-swap transfers are usually < 8 KB, section 4.2): eight rows of 64 blocks.
