@@ -1,11 +1,14 @@
-"""Builds libpgcm.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Builds libpgcm.so (HIP kernels + C ABI) for gfx950 with hipcc, and the Python binding's native
+marshalling with the host compiler, in-tree."""
 import os
 import shutil
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpgcm.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 SOURCES = ["pgcm_kernels.hip", "pgcm_bitsliced.hip", "pgcm_host.hip", "pgcm_bounce.hip", "pgcm_pipe.hip",
            "pgcm_seq.cpp"]
 HEADERS = ["pgcm_kernels.h", "pgcm_types.h", "pgcm_bitsliced_gen.h", os.path.join("..", "..", "include", "pgcm.h"),
@@ -29,11 +32,26 @@ def hipcc() -> str:
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(MARSHAL):
         return True
-    t = os.path.getmtime(LIB)
-    deps = [os.path.join(CSRC, s) for s in SOURCES + HEADERS] + [os.path.abspath(__file__)]
+    t = min(os.path.getmtime(LIB), os.path.getmtime(MARSHAL))
+    deps = [os.path.join(CSRC, s) for s in SOURCES + HEADERS + ["marshal.cpp"]] + \
+        [os.path.abspath(__file__)]
     return any(os.path.getmtime(d) > t for d in deps)
+
+
+def build_marshal() -> None:
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if cxx is None:
+        raise RuntimeError("no host C++ compiler")
+    tmp = MARSHAL + ".tmp%d" % os.getpid()
+    proc = subprocess.run([cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+                           "-Wall", "-I" + sysconfig.get_paths()["include"],
+                           os.path.join(CSRC, "marshal.cpp"), "-o", tmp],
+                          stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if proc.returncode != 0:
+        raise RuntimeError("compiling marshal.cpp failed:\n" + proc.stdout)
+    os.replace(tmp, MARSHAL)
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
@@ -50,6 +68,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
     if verbose and out.strip():
         print(out)
     os.replace(tmp, LIB)
+    build_marshal()
     return LIB
 
 
