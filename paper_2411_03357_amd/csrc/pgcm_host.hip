@@ -364,28 +364,20 @@ void launch_bulk(int rounds, bool matrix_hash, dim3 grid, hipStream_t stream, Ar
         launch_bulk_rounds<kDecrypt, false>(rounds, grid, stream, args...);
 }
 
-// the kernel of a batch that takes one launch: `done` marks its end
-template <bool kDecrypt, class... Args>
-void launch_swap(int rounds, dim3 grid, dim3 block, hipStream_t stream, bool capturing, hipEvent_t done,
-                 Args... args) {
-    auto* kernel = rounds == 10   ? swap_kernel<kDecrypt, 10>
-                   : rounds == 12 ? swap_kernel<kDecrypt, 12>
-                                  : swap_kernel<kDecrypt, 14>;
-    launch_last(kernel, grid, block, stream, capturing, done, args...);
+// the kernel of a batch that takes one launch: `done`, if not null, marks its end
+template <bool kDecrypt, SwapKind kKind, class... Args>
+void launch_swap(int rounds, dim3 grid, dim3 block, hipStream_t stream, bool capturing,
+                 hipEvent_t done, Args... args) {
+    auto* kernel = rounds == 10   ? swap_kernel<kDecrypt, 10, kKind>
+                   : rounds == 12 ? swap_kernel<kDecrypt, 12, kKind>
+                                  : swap_kernel<kDecrypt, 14, kKind>;
+    launch_last(kernel, grid, block, stream, capturing || done == nullptr, done, args...);
 }
 
-// wide: a workgroup of eight wavefronts per chunk; otherwise a wavefront per chunk
+// many chunks of one row: a wavefront per chunk
 template <bool kDecrypt, class... Args>
-void launch_small(int rounds, bool wide, uint32_t nchunks, hipStream_t stream, bool capturing,
-                  hipEvent_t done, Args... args) {
-    if (wide) {
-        auto* kernel = rounds == 10   ? small_wide_kernel<kDecrypt, 10>
-                       : rounds == 12 ? small_wide_kernel<kDecrypt, 12>
-                                      : small_wide_kernel<kDecrypt, 14>;
-        launch_last(kernel, dim3(nchunks), dim3(kSmallWideWaves * 64), stream, capturing, done,
-                    args...);
-        return;
-    }
+void launch_small(int rounds, uint32_t nchunks, hipStream_t stream, bool capturing, hipEvent_t done,
+                  Args... args) {
     auto* kernel = rounds == 10   ? small_kernel<kDecrypt, 10>
                    : rounds == 12 ? small_kernel<kDecrypt, 12>
                                   : small_kernel<kDecrypt, 14>;
@@ -544,7 +536,9 @@ bool worst_case_sizes(uint32_t forced_unit_power, uint32_t wave_slots, size_t n,
     p.nfold = (uint32_t)folds;
     p.ncoarse = (p.nunits >> kCoarseShift) + 1;
     const WorkLayout w = lay_out(a, p);
-    const size_t small = sizeof(ChunkDesc) * n;  // the small-transfer path stages descriptors only
+    // the other paths stage descriptors only, of chunks or of workgroups
+    const size_t small = sizeof(ChunkDesc) * n > sizeof(GroupDesc) * kSwapMaxGroups
+                             ? sizeof(ChunkDesc) * n : sizeof(GroupDesc) * kSwapMaxGroups;
     *stage_bytes = w.upload_bytes > small ? w.upload_bytes : small;
     *work_bytes = w.bytes;
     return true;
@@ -621,9 +615,9 @@ int record_timing_stop(pgcm_key* key, hipStream_t stream) {
     return PGCM_OK;
 }
 
-// Small-transfer path: one kernel, descriptors read straight from the pinned staging buffer, no
+// Many chunks of one row: one kernel, descriptors read straight from the pinned staging buffer, no
 // device workspace.
-int run_small_batch(pgcm_key* key, Context* ctx, const BatchArgs& a, bool wide) {
+int run_small_batch(pgcm_key* key, Context* ctx, const BatchArgs& a) {
     const uint32_t nchunks = (uint32_t)a.n;
     const int s = ctx->next_stage;
     int rc = ensure_stage(ctx, s, sizeof(ChunkDesc) * a.n);
@@ -634,10 +628,10 @@ int run_small_batch(pgcm_key* key, Context* ctx, const BatchArgs& a, bool wide) 
     rc = record_timing_start(key, a.stream);
     if (rc != PGCM_OK) return rc;
     if (a.decrypt)
-        launch_small<true>(key->rounds, wide, nchunks, a.stream, a.capturing, ctx->stage_done[s], kt, (const ChunkDesc*)h_desc,
+        launch_small<true>(key->rounds, nchunks, a.stream, a.capturing, ctx->stage_done[s], kt, (const ChunkDesc*)h_desc,
                            nchunks, a.ivs, a.iv_len, a.tags, a.ok);
     else
-        launch_small<false>(key->rounds, wide, nchunks, a.stream, a.capturing, ctx->stage_done[s], kt, (const ChunkDesc*)h_desc,
+        launch_small<false>(key->rounds, nchunks, a.stream, a.capturing, ctx->stage_done[s], kt, (const ChunkDesc*)h_desc,
                             nchunks, a.ivs, a.iv_len, a.tags, (uint8_t*)nullptr);
     // from here on the stream will read the staging buffer: mark its end even if a later call
     // fails, so that the buffer is not rewritten under a running kernel
@@ -654,96 +648,161 @@ constexpr size_t kSwapWorkBytes = kSwapArriveBytes + sizeof(Block) * kSwapMaxGro
 
 // How a batch is cut for the one-launch path, if it takes it.
 struct SwapShape {
+    bool narrow;                              // only short chunks: the kernel with small tables
+    bool alone;                               // every chunk has one workgroup
     uint32_t unit_power, wave_power, groups;
 };
 
 inline uint32_t swap_groups(const BatchArgs& a, size_t i, uint32_t unit_power, uint32_t wave_power) {
-    const uint64_t blocks = (a.len[i] + 15) / 16 + lead_blocks(a.aad_len ? a.aad_len[i] : 0);
+    const uint32_t lead = swap_lead_blocks(a.aad_len ? a.aad_len[i] : 0, wave_power < 4);
+    const uint64_t blocks = (a.len[i] + 15) / 16 + lead;
     const uint64_t units = (blocks + ((uint64_t)1 << unit_power) - 1) >> unit_power;
-    return (uint32_t)((units + ((uint64_t)1 << wave_power) - 1) >> wave_power);
+    const uint64_t groups = (units + ((uint64_t)1 << wave_power) - 1) >> wave_power;
+    return groups == 0 ? 1 : (uint32_t)groups;
 }
 
-// The smallest unit with which the batch fits the launch's workgroups (a compute unit each) at
+// Batches of short chunks: units of one row.  As long as there is a compute unit for every chunk a
+// workgroup takes a whole chunk; of more chunks, several workgroups of four wavefronts share a
+// compute unit, and the longer chunks take two or three.
+// Others: the smallest unit with which the batch fits the compute units, a workgroup each, at
 // sixteen wavefronts, then the fewest wavefronts a workgroup with which it still does.
-bool swap_shape(const pgcm_key* key, const BatchArgs& a, SwapShape* shape) {
-    if (!key->one_launch || a.iv_len != 12 || a.n > kArgChunks) return false;
-    const uint32_t most = (uint32_t)key->num_cu < kSwapMaxGroups ? (uint32_t)key->num_cu : kSwapMaxGroups;
-    uint64_t bytes = 0;
-    for (size_t k = 0; k < a.n; ++k) bytes += a.len[a.at(k)];
-    if (bytes > (uint64_t)most * kWavesPerGroup * kUnitBytes) return false;
-    auto groups = [&](uint32_t unit_power, uint32_t wave_power) {
-        uint32_t sum = 0;
-        for (size_t k = 0; k < a.n; ++k) sum += swap_groups(a, a.at(k), unit_power, wave_power);
+bool swap_shape(const pgcm_key* key, const BatchArgs& a, bool all_small, SwapShape* shape) {
+    if (a.n > kSmallMaxChunks || (!all_small && !key->one_launch)) return false;
+    const uint32_t num_cu = (uint32_t)key->num_cu;
+    auto groups = [&](uint32_t unit_power, uint32_t wave_power, uint32_t* most_of_one) {
+        uint64_t sum = 0;
+        *most_of_one = 0;
+        for (size_t k = 0; k < a.n; ++k) {
+            const uint32_t g = swap_groups(a, a.at(k), unit_power, wave_power);
+            if (g > *most_of_one) *most_of_one = g;
+            sum += g;
+        }
         return sum;
     };
-    const uint32_t forced = key->forced_unit_power;
-    uint32_t up = forced ? forced : kMinUnitPower;
-    if (up > kUnitPower) return false;
-    while (groups(up, 4) > most) {
-        if (forced || up == kUnitPower) return false;
-        ++up;
+    uint32_t up = kMinUnitPower, wp = 2, longest = 0;
+    uint64_t total = 0;
+    if (all_small) {
+        total = groups(up, wp, &longest);
+        if (a.n <= num_cu || total > kSwapMaxGroups)
+            while (longest > 1 && wp < 4) total = groups(up, ++wp, &longest);
+        if (total > kSwapMaxGroups) return false;
+    } else {
+        const uint32_t most = num_cu < kSwapChunkGroups ? num_cu : kSwapChunkGroups;
+        if (a.n > most) return false;
+        uint64_t bytes = 0;
+        for (size_t k = 0; k < a.n; ++k) bytes += a.len[a.at(k)];
+        if (bytes > (uint64_t)most * kWavesPerGroup * kUnitBytes) return false;
+        const uint32_t forced = key->forced_unit_power;
+        if (forced) up = forced;
+        if (up > kUnitPower) return false;
+        wp = 4;
+        while ((total = groups(up, wp, &longest)) > most) {
+            if (forced || up == kUnitPower) return false;
+            ++up;
+        }
+        while (wp > 2) {
+            uint32_t l = 0;
+            const uint64_t t = groups(up, wp - 1, &l);
+            if (t > most) break;
+            --wp, total = t, longest = l;
+        }
     }
-    uint32_t wp = 4;
-    while (wp > 2 && groups(up, wp - 1) <= most) --wp;
-    *shape = SwapShape{up, wp, groups(up, wp)};
+    *shape = SwapShape{all_small, longest <= 1, up, wp, (uint32_t)total};
     return true;
 }
 
-// A batch of few chunks that does not fill the chip: one kernel, descriptors as its arguments,
-// nothing staged and nothing uploaded.
+template <SwapKind kKind>
+void launch_swap_batch(const pgcm_key* key, const BatchArgs& a, const SwapShape& shape,
+                       hipEvent_t done, const ArgBatch& batch, const GroupDesc* staged,
+                       Block* slots, uint32_t* arrive) {
+    const dim3 grid(shape.groups), block(64u * ((1u << shape.wave_power) + (shape.wave_power < 4)));
+    const KeyTables* kt = key->tables;
+    if (a.decrypt)
+        launch_swap<true, kKind>(key->rounds, grid, block, a.stream, a.capturing, done, kt, batch,
+                                   staged, a.ivs, a.iv_len, slots, arrive, a.tags, a.ok);
+    else
+        launch_swap<false, kKind>(key->rounds, grid, block, a.stream, a.capturing, done, kt,
+                                    batch, staged, a.ivs, a.iv_len, slots, arrive, a.tags, a.ok);
+}
+
+// A batch of few chunks that does not fill the chip: one kernel.  Up to kArgChunks chunks travel as
+// its arguments, nothing staged; when moreover every chunk has one workgroup, which needs no
+// workspace, the call needs no context at all (ctx is null).
 int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapShape& shape) {
     ArgBatch batch;
     batch.nchunks = (uint32_t)a.n;
     batch.unit_power = shape.unit_power;
     batch.wave_power = shape.wave_power;
+    const bool in_args = a.n <= kArgChunks;
+    GroupDesc* h_groups = nullptr;
+    int s = 0;
+    if (ctx != nullptr) s = ctx->next_stage;
+    if (!in_args) {
+        const int rc = ensure_stage(ctx, s, sizeof(GroupDesc) * shape.groups);
+        if (rc != PGCM_OK) return rc;
+        h_groups = reinterpret_cast<GroupDesc*>(ctx->stage[s]);
+    }
     uint32_t groups = 0;
     for (size_t k = 0; k < a.n; ++k) {
         const size_t i = a.at(k);
-        ArgChunk& c = batch.c[k];
+        ArgChunk c;
         c.src = (const uint8_t*)a.src[i];
         c.dst = (uint8_t*)a.dst[i];
         c.len = a.len[i];
         c.aad_len = a.aad_len ? a.aad_len[i] : 0;
         c.aad = c.aad_len ? (const uint8_t*)a.aad[i] : nullptr;
         c.index = (uint32_t)i;
-        batch.group_base[k] = groups;
-        groups += swap_groups(a, i, shape.unit_power, shape.wave_power);
+        const uint32_t of_chunk = swap_groups(a, i, shape.unit_power, shape.wave_power);
+        if (in_args) {
+            batch.c[k] = c;
+            batch.group_base[k] = groups;
+        } else {
+            for (uint32_t g = 0; g < of_chunk; ++g)
+                h_groups[groups + g] = GroupDesc{c, groups, of_chunk};
+        }
+        groups += of_chunk;
     }
-    batch.group_base[a.n] = groups;
-    int rc = ensure_work(ctx, kSwapWorkBytes, a.stream);
-    if (rc != PGCM_OK) return rc;
-    uint32_t* d_arrive = reinterpret_cast<uint32_t*>(ctx->work);
-    Block* d_slots = reinterpret_cast<Block*>(ctx->work + kSwapArriveBytes);
-    // the arrival words are left at zero by every batch of this kind; they need clearing when
-    // the workspace is new, was used by a batch of the other kind, or is shared between keys
-    if (!ctx->arrive_clean || !ctx->growable)
-        hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(1024), 0, a.stream, d_arrive,
-                           kSwapArriveWords);
-    ctx->arrive_clean = false;
-    ctx->counter_at = nullptr;  // the unit counter of the other kind of batch may lie under this
-    // No staging buffer is used, but the context's workspace is: the batch's end is marked on
-    // the event of the stage whose turn it is, without taking the turn.  (If that event still
-    // guards an earlier batch's staging buffer, that batch ends before this one on the same
-    // stream, so using it again only moves the guard later.)
-    const int s = ctx->next_stage;
-    const hipEvent_t done = ctx->stage_done[s];
+    if (in_args) batch.group_base[a.n] = groups;
+    uint32_t* d_arrive = nullptr;
+    Block* d_slots = nullptr;
+    if (!shape.alone) {
+        const int rc = ensure_work(ctx, kSwapWorkBytes, a.stream);
+        if (rc != PGCM_OK) return rc;
+        d_arrive = reinterpret_cast<uint32_t*>(ctx->work);
+        d_slots = reinterpret_cast<Block*>(ctx->work + kSwapArriveBytes);
+        // the arrival words are left at zero by every batch of this kind; they need clearing when
+        // the workspace is new, was used by a batch of the other kind, or is shared between keys
+        if (!ctx->arrive_clean || !ctx->growable)
+            hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(1024), 0, a.stream, d_arrive,
+                               kSwapArriveWords);
+        ctx->arrive_clean = false;
+        ctx->counter_at = nullptr;  // the unit counter of other batches may lie under this
+    }
     int rc_timing = record_timing_start(key, a.stream);
-    const dim3 grid(groups), block(64u << shape.wave_power);
-    if (a.decrypt)
-        launch_swap<true>(key->rounds, grid, block, a.stream, a.capturing, done,
-                          (const KeyTables*)key->tables, batch, a.ivs, d_slots, d_arrive, a.tags, a.ok);
+    // Where no staging buffer is used but the workspace is, the batch's end is marked on the event
+    // of the stage whose turn it is, without taking the turn.  (If that event still guards an
+    // earlier batch's staging buffer, that batch ends before this one on the same stream, so
+    // using it again only moves the guard later.)
+    const hipEvent_t done = ctx != nullptr ? ctx->stage_done[s] : nullptr;
+    if (shape.narrow)
+        launch_swap_batch<SwapKind::kNarrow>(key, a, shape, done, batch, h_groups, d_slots, d_arrive);
+    else if (shape.unit_power == kRowPower)
+        launch_swap_batch<SwapKind::kRows>(key, a, shape, done, batch, h_groups, d_slots, d_arrive);
     else
-        launch_swap<false>(key->rounds, grid, block, a.stream, a.capturing, done,
-                           (const KeyTables*)key->tables, batch, a.ivs, d_slots, d_arrive, a.tags,
-                           (uint8_t*)nullptr);
+        launch_swap_batch<SwapKind::kUnits>(key, a, shape, done, batch, h_groups, d_slots, d_arrive);
     if (rc_timing == PGCM_OK) rc_timing = record_timing_stop(key, a.stream);
-    if (a.capturing) PGCM_HIP(hipEventRecord(done, a.stream));
-    ctx->last_stage = s;
-    ctx->bound = true;
+    int rc_end = PGCM_OK;
+    if (!in_args) {
+        rc_end = end_of_batch(ctx, s, a.stream, a.capturing);
+    } else if (ctx != nullptr) {
+        if (a.capturing) PGCM_HIP(hipEventRecord(done, a.stream));
+        ctx->last_stage = s;
+        ctx->bound = true;
+    }
     if (rc_timing != PGCM_OK) return rc_timing;
     PGCM_HIP(hipGetLastError());
-    ctx->arrive_clean = true;
-    return PGCM_OK;
+    if (!shape.alone) ctx->arrive_clean = true;
+    return rc_end;
 }
 
 // The kernels of one batch that goes through the unit schedule, enqueued with context `ctx`.
@@ -850,22 +909,22 @@ int run_batch(pgcm_key* key, BatchArgs a) {
         PGCM_HIP(hipStreamIsCapturing(a.stream, &status));
         a.capturing = status == hipStreamCaptureStatusActive;
     }
+    if (a.fixed && a.n > kFixedMaxChunks) return PGCM_ERR_CAPACITY;
+    SwapShape shape{};
+    const bool one_launch = swap_shape(key, a, p.all_small, &shape);
+    if (one_launch && shape.alone && a.n <= kArgChunks) return run_one_launch(key, nullptr, a, shape);
     Context* ctx = nullptr;
     if (a.fixed) {
-        if (a.n > kFixedMaxChunks) return PGCM_ERR_CAPACITY;
         ctx = &key->fixed;
         key->fixed_used = true;
     } else {
         rc = acquire_context(key, a.stream, &ctx);
         if (rc != PGCM_OK) return rc;
     }
-    SwapShape shape{};
-    if (p.all_one_row)
-        rc = run_small_batch(key, ctx, a, false);
-    else if (p.all_small && a.n <= kSmallWideMaxChunks)
-        rc = run_small_batch(key, ctx, a, true);
-    else if (swap_shape(key, a, &shape))
+    if (one_launch)
         rc = run_one_launch(key, ctx, a, shape);
+    else if (p.all_one_row)
+        rc = run_small_batch(key, ctx, a);
     else
         rc = run_unit_batch(key, ctx, a, p);
     release_context(key, ctx);
@@ -1172,7 +1231,7 @@ int pgcm_describe_schedule(size_t n, const uint64_t* len, uint32_t unit_bytes, u
         info->fold_count[l] = p.fold_count[l];
         info->fold_first[l] = p.fold_first[l];
     }
-    info->path = n == 0 ? 0 : p.all_one_row ? 1 : (p.all_small && n <= kSmallWideMaxChunks) ? 2 : 0;
+    info->path = n == 0 ? 0 : p.all_one_row ? 1 : (p.all_small && n <= kSmallMaxChunks) ? 2 : 0;
     if (image != nullptr) {
         if (image_capacity < w.upload_bytes) return PGCM_ERR_CAPACITY;
         memset(image, 0, w.upload_bytes);

@@ -19,12 +19,17 @@ __global__ void bulk_kernel(const KeyTables* kt, const ChunkDesc* chunks,
                             uint32_t nunits_total, uint32_t unit_power, uint32_t* counter,
                             const uint8_t* ivs, const Block* j0, Block* ekj0, Block* sets);
 
-// The whole invocation of a few chunks in one launch of 2^batch.wave_power wavefronts a workgroup
-// (at least four), group_base[nchunks] workgroups.  slots: one block per workgroup; arrive:
-// kSwapArriveWords words, zero on entry and left zero.
-template <bool kDecrypt, int kRounds>
-__global__ void swap_kernel(const KeyTables* kt, ArgBatch batch, const uint8_t* ivs, Block* slots,
-                            uint32_t* arrive, uint8_t* tags, uint8_t* ok);
+// The whole invocation of a few chunks in one launch, 2^wave_power wavefronts of units a workgroup (at
+// least four) and, below sixteen, one more.  The chunks come as arguments, or, when `staged` is not
+// null, with a descriptor per workgroup there (batch then only has unit_power and wave_power).
+// slots: one block per workgroup; arrive: kSwapArriveWords words, zero on entry and left zero;
+// neither is touched if no chunk has more than one workgroup.  kRows: units of one row; kNarrow: likewise, and
+// the round tables take half the room; kUnits: units of two to sixteen rows.
+enum class SwapKind { kNarrow, kRows, kUnits };
+template <bool kDecrypt, int kRounds, SwapKind kKind>
+__global__ void swap_kernel(const KeyTables* kt, ArgBatch batch, const GroupDesc* staged,
+                            const uint8_t* ivs, uint32_t iv_len, Block* slots, uint32_t* arrive,
+                            uint8_t* tags, uint8_t* ok);
 
 __global__ void clear_words_kernel(uint32_t* words, uint32_t n);
 
@@ -48,13 +53,6 @@ constexpr uint32_t kSmallChunksPerGroup = 4;
 template <bool kDecrypt, int kRounds>
 __global__ void small_kernel(const KeyTables* kt, const ChunkDesc* chunks_host, uint32_t nchunks,
                              const uint8_t* ivs, uint32_t iv_len, uint8_t* tags, uint8_t* ok);
-
-// chunks of at most kSmallChunkBytes each, one workgroup per chunk
-constexpr uint32_t kSmallWideWaves = 8;
-template <bool kDecrypt, int kRounds>
-__global__ void small_wide_kernel(const KeyTables* kt, const ChunkDesc* chunks_host,
-                                  uint32_t nchunks, const uint8_t* ivs, uint32_t iv_len,
-                                  uint8_t* tags, uint8_t* ok);
 
 __global__ void upload_kernel(uint4* dst, const uint4* src_host, uint32_t n16, uint32_t* clear);
 

@@ -617,14 +617,26 @@ __device__ __forceinline__ void lds_write128(uint32_t addr, u32x4 v) {
     *reinterpret_cast<lds_u128_wptr>(addr) = v;
 }
 
-// Round-table reads.  `a` already is pair << 16 | x << 8 | lane byte; T selects the table of the
-// pair through the constant part of the address, which also carries `base`, the LDS address of
-// the kernel's BulkLds object (a link-time constant, 0 when it is the kernel's only LDS object,
-// so the sum lands in the instruction's offset field; a[] itself must stay free of it because
-// byte 1 of a[] is rewritten every round).
-template <int T>
+// The round tables' place and replication in LDS.  A lookup address is bytes 0 and 2 of the lane's
+// constants, the looked-up byte in between (so a row of 256 bytes per value), and a constant part
+// in the instruction's offset field that selects the table and carries `base`, the LDS address of
+// the kernel's tables (a link-time constant; a[] itself must stay free of it because byte 1 of a[]
+// is rewritten every round).
+// TeWide: 128 KiB, every entry 32 times, so that no lookups collide: 2 cycles each.
+struct TeWide {
+    static constexpr uint32_t kBase = kLdsTeBase, kBytes = kLdsTeBytes, kPairs = 0x10000u, kLanes = 32;
+    static constexpr uint32_t offset(int t) { return kBase + 128u * (t & 1); }
+};
+// TeNarrow: 64 KiB with all four tables in a row, every entry sixteen times, so that lanes l and
+// l + 16 share a bank: 4 cycles, but half the room and half the time to fill.  For launches of few
+// rows on a compute unit.
+struct TeNarrow {
+    static constexpr uint32_t kBase = 0, kBytes = 4 * 256 * 16 * 4, kPairs = 0, kLanes = 16;
+    static constexpr uint32_t offset(int t) { return kBase + 64u * t; }
+};
+template <class Te, int T>
 __device__ __forceinline__ uint32_t te_read(uint32_t a, uint32_t base) {
-    return lds_read32(a + (base + kLdsTeBase + 128u * (T & 1)));
+    return lds_read32(a + (base + Te::offset(T)));
 }
 
 // a.byte1 = rk.byte[KS] ^ v.byte[KV], every other byte of a kept: one SDWA instruction folds the
@@ -664,9 +676,10 @@ struct AesAddr {
 };
 
 // last_round_key: the four words of round key Nr
+template <class Te>
 __device__ __forceinline__ void aes_addr_init(AesAddr& A, uint32_t lane,
                                               const uint32_t* __restrict__ last_round_key) {
-    const uint32_t lo = (lane & 31) * 4, hi = lo | 0x10000u;
+    const uint32_t lo = (lane & (Te::kLanes - 1)) * 4, hi = lo | Te::kPairs;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         A.a[j][0] = lo;
@@ -703,7 +716,9 @@ struct CtrConsts {
 
 // The counter block of a row that stands alone (a unit of one row): no constants are formed, and
 // round 1 makes its sixteen lookups like any other.
+template <class TeLayout>
 struct CtrBlock {
+    using Te = TeLayout;
     uint32_t iv0, iv1, iv2, ctr;
 };
 
@@ -711,6 +726,7 @@ struct CtrBlock {
 __device__ __forceinline__ CtrConsts ctr_consts(const uint32_t* __restrict__ rk, uint32_t lane,
                                                 uint32_t wave, uint32_t iv0, uint32_t iv1,
                                                 uint32_t iv2, uint32_t first_ctr, uint32_t base) {
+    using Te = TeWide;
     const uint32_t lo = (lane & 31) * 4, hi = lo | 0x10000u;
     auto at = [&](uint32_t w, int k, uint32_t lane_bytes) {
         return (((w >> (8 * k)) & 0xFFu) << 8) | lane_bytes;
@@ -719,26 +735,26 @@ __device__ __forceinline__ CtrConsts ctr_consts(const uint32_t* __restrict__ rk,
     const uint32_t s0 = iv0 ^ rk[0], s1 = iv1 ^ rk[1], s2 = iv2 ^ rk[2],
                    s3 = bswap32(upper) ^ rk[3];
     CtrConsts c;
-    c.k0 = xor3(te_read<0>(at(s0, 0, lo), base), te_read<1>(at(s1, 1, lo), base),
-                te_read<2>(at(s2, 2, hi), base));
-    const uint32_t u1 = xor3(te_read<0>(at(s1, 0, lo), base), te_read<1>(at(s2, 1, lo), base),
-                             te_read<2>(at(s3, 2, hi), base)) ^
-                        te_read<3>(at(s0, 3, hi), base) ^ rk[5];
-    const uint32_t u2 = xor3(te_read<0>(at(s2, 0, lo), base), te_read<1>(at(s3, 1, lo), base),
-                             te_read<2>(at(s0, 2, hi), base)) ^
-                        te_read<3>(at(s1, 3, hi), base) ^ rk[6];
-    const uint32_t u3 = xor3(te_read<0>(at(s3, 0, lo), base), te_read<1>(at(s0, 1, lo), base),
-                             te_read<2>(at(s1, 2, hi), base)) ^
-                        te_read<3>(at(s2, 3, hi), base) ^ rk[7];
+    c.k0 = xor3(te_read<Te, 0>(at(s0, 0, lo), base), te_read<Te, 1>(at(s1, 1, lo), base),
+                te_read<Te, 2>(at(s2, 2, hi), base));
+    const uint32_t u1 = xor3(te_read<Te, 0>(at(s1, 0, lo), base), te_read<Te, 1>(at(s2, 1, lo), base),
+                             te_read<Te, 2>(at(s3, 2, hi), base)) ^
+                        te_read<Te, 3>(at(s0, 3, hi), base) ^ rk[5];
+    const uint32_t u2 = xor3(te_read<Te, 0>(at(s2, 0, lo), base), te_read<Te, 1>(at(s3, 1, lo), base),
+                             te_read<Te, 2>(at(s0, 2, hi), base)) ^
+                        te_read<Te, 3>(at(s1, 3, hi), base) ^ rk[6];
+    const uint32_t u3 = xor3(te_read<Te, 0>(at(s3, 0, lo), base), te_read<Te, 1>(at(s0, 1, lo), base),
+                             te_read<Te, 2>(at(s1, 2, hi), base)) ^
+                        te_read<Te, 3>(at(s2, 3, hi), base) ^ rk[7];
     u32x4 q;
-    q.x = xor3(te_read<1>(at(u1, 1, lo), base), te_read<2>(at(u2, 2, hi), base),
-               te_read<3>(at(u3, 3, hi), base));
-    q.y = xor3(te_read<0>(at(u1, 0, lo), base), te_read<1>(at(u2, 1, lo), base),
-               te_read<2>(at(u3, 2, hi), base));
-    q.z = xor3(te_read<0>(at(u2, 0, lo), base), te_read<1>(at(u3, 1, lo), base),
-               te_read<3>(at(u1, 3, hi), base));
-    q.w = xor3(te_read<0>(at(u3, 0, lo), base), te_read<2>(at(u1, 2, hi), base),
-               te_read<3>(at(u2, 3, hi), base));
+    q.x = xor3(te_read<Te, 1>(at(u1, 1, lo), base), te_read<Te, 2>(at(u2, 2, hi), base),
+               te_read<Te, 3>(at(u3, 3, hi), base));
+    q.y = xor3(te_read<Te, 0>(at(u1, 0, lo), base), te_read<Te, 1>(at(u2, 1, lo), base),
+               te_read<Te, 2>(at(u3, 2, hi), base));
+    q.z = xor3(te_read<Te, 0>(at(u2, 0, lo), base), te_read<Te, 1>(at(u3, 1, lo), base),
+               te_read<Te, 3>(at(u1, 3, hi), base));
+    q.w = xor3(te_read<Te, 0>(at(u3, 0, lo), base), te_read<Te, 2>(at(u1, 2, hi), base),
+               te_read<Te, 3>(at(u2, 3, hi), base));
     c.q_addr = base + kLdsCtrBase + wave * (kCtrEntries * 16);
     if (lane < kCtrEntries) lds_write128(c.q_addr + lane * 16, q);
     // the wavefront's own later reads come after this write: LDS serves a wavefront in order
@@ -972,7 +988,7 @@ struct GhashRowMatrix {
 // issued in rounds 4 c + 3 .. 4 c + 6 (two matrix pieces fetched ahead of each round's lookups,
 // two instructions, one before and one after the round's sums) and its result packed in the
 // middle of the round after, so that neither the fetch nor the matrix pipeline is waited for.
-template <int kFirst, int kRounds, class Hash>
+template <class Te, int kFirst, int kRounds, class Hash>
 __device__ __forceinline__ void aes_rounds_lds(const uint32_t* __restrict__ rk, AesAddr& A,
                                                uint32_t u0, uint32_t u1, uint32_t u2, uint32_t u3,
                                                Hash& G, uint32_t base, uint32_t& o0, uint32_t& o1,
@@ -1007,14 +1023,14 @@ __device__ __forceinline__ void aes_rounds_lds(const uint32_t* __restrict__ rk, 
             key_xor_into_addr<2, 2>(A.a[3][2], k[3], u3);
             key_xor_into_addr<3, 3>(A.a[3][3], k[3], u3);
         }
-        uint32_t t00 = te_read<0>(A.a[0][0], base), t11 = te_read<1>(A.a[1][1], base),
-                 t22 = te_read<2>(A.a[2][2], base), t33 = te_read<3>(A.a[3][3], base);
-        uint32_t t10 = te_read<0>(A.a[1][0], base), t21 = te_read<1>(A.a[2][1], base),
-                 t32 = te_read<2>(A.a[3][2], base), t03 = te_read<3>(A.a[0][3], base);
-        uint32_t t20 = te_read<0>(A.a[2][0], base), t31 = te_read<1>(A.a[3][1], base),
-                 t02 = te_read<2>(A.a[0][2], base), t13 = te_read<3>(A.a[1][3], base);
-        uint32_t t30 = te_read<0>(A.a[3][0], base), t01 = te_read<1>(A.a[0][1], base),
-                 t12 = te_read<2>(A.a[1][2], base), t23 = te_read<3>(A.a[2][3], base);
+        uint32_t t00 = te_read<Te, 0>(A.a[0][0], base), t11 = te_read<Te, 1>(A.a[1][1], base),
+                 t22 = te_read<Te, 2>(A.a[2][2], base), t33 = te_read<Te, 3>(A.a[3][3], base);
+        uint32_t t10 = te_read<Te, 0>(A.a[1][0], base), t21 = te_read<Te, 1>(A.a[2][1], base),
+                 t32 = te_read<Te, 2>(A.a[3][2], base), t03 = te_read<Te, 3>(A.a[0][3], base);
+        uint32_t t20 = te_read<Te, 0>(A.a[2][0], base), t31 = te_read<Te, 1>(A.a[3][1], base),
+                 t02 = te_read<Te, 2>(A.a[0][2], base), t13 = te_read<Te, 3>(A.a[1][3], base);
+        uint32_t t30 = te_read<Te, 0>(A.a[3][0], base), t01 = te_read<Te, 1>(A.a[0][1], base),
+                 t12 = te_read<Te, 2>(A.a[1][2], base), t23 = te_read<Te, 3>(A.a[2][3], base);
         if constexpr (Hash::kMatrix) {
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (r == 7) G.template consume<0>();
@@ -1065,10 +1081,11 @@ __device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, Aes
                                             const CtrConsts& C, Hash& G, uint32_t base,
                                             uint32_t& o0, uint32_t& o1, uint32_t& o2,
                                             uint32_t& o3) {
+    using Te = TeWide;
     const u32x4 q = lds_read128(C.q_addr + ((C.rel >> 4) & (16 * (kCtrEntries - 1))));
     // round 1: the counter is the last word, big endian: its lowest byte is state byte 3
     key_xor_into_addr<3, 0>(A.a[3][3], rk[3], C.rel);
-    uint32_t u0 = te_read<3>(A.a[3][3], base) ^ C.k0;
+    uint32_t u0 = te_read<Te, 3>(A.a[3][3], base) ^ C.k0;
     if constexpr (Hash::kTable) {
         G.template step<0>();
         G.template step<1>();
@@ -1078,21 +1095,21 @@ __device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, Aes
     key_xor_into_addr<1, 1>(A.a[0][1], rk[4], u0);
     key_xor_into_addr<2, 2>(A.a[0][2], rk[4], u0);
     key_xor_into_addr<3, 3>(A.a[0][3], rk[4], u0);
-    u0 = te_read<0>(A.a[0][0], base) ^ q.x;
-    const uint32_t u3 = te_read<1>(A.a[0][1], base) ^ q.w, u2 = te_read<2>(A.a[0][2], base) ^ q.z,
-                   u1 = te_read<3>(A.a[0][3], base) ^ q.y;
+    u0 = te_read<Te, 0>(A.a[0][0], base) ^ q.x;
+    const uint32_t u3 = te_read<Te, 1>(A.a[0][1], base) ^ q.w, u2 = te_read<Te, 2>(A.a[0][2], base) ^ q.z,
+                   u1 = te_read<Te, 3>(A.a[0][3], base) ^ q.y;
     if constexpr (Hash::kTable) {
         G.template step<2>();
         G.template step<3>();
     }
     __builtin_amdgcn_sched_barrier(0);
-    aes_rounds_lds<3, kRounds>(rk, A, u0, u1, u2, u3, G, base, o0, o1, o2, o3);
+    aes_rounds_lds<Te, 3, kRounds>(rk, A, u0, u1, u2, u3, G, base, o0, o1, o2, o3);
 }
 
 // ... and in a row that stands alone
-template <int kRounds>
+template <int kRounds, class Te>
 __device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, AesAddr& A,
-                                            const CtrBlock& C, GhashNone& G, uint32_t base,
+                                            const CtrBlock<Te>& C, GhashNone& G, uint32_t base,
                                             uint32_t& o0, uint32_t& o1, uint32_t& o2,
                                             uint32_t& o3) {
     key_xor_into_addr<0, 0>(A.a[0][0], rk[0], C.iv0);
@@ -1112,7 +1129,7 @@ __device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, Aes
     key_xor_into_addr<1, 2>(A.a[3][1], rk[3], C.ctr);
     key_xor_into_addr<2, 1>(A.a[3][2], rk[3], C.ctr);
     key_xor_into_addr<3, 0>(A.a[3][3], rk[3], C.ctr);
-    aes_rounds_lds<1, kRounds>(rk, A, 0, 0, 0, 0, G, base, o0, o1, o2, o3);
+    aes_rounds_lds<Te, 1, kRounds>(rk, A, 0, 0, 0, 0, G, base, o0, o1, o2, o3);
 }
 
 // Y * C from C's nibble table at LDS address `base`, on its own (not riding along with AES):
@@ -1259,18 +1276,18 @@ namespace {
 // a wavefront's store covers four whole rows, so the stores run at the full LDS width.
 // kHash: the operands of the row hash, none, the nibble table or the matrix images.
 enum class FillHash { kNone, kTable, kMatrix };
-template <FillHash kHash, uint32_t kThreads>
-__device__ __forceinline__ void fill_bulk_lds(BulkLds& lds, const KeyTables* __restrict__ kt,
-                                              uint32_t tid) {
-    constexpr uint32_t kPieces = kLdsTeBytes / 16;
+template <class Te, uint32_t kThreads>
+__device__ __forceinline__ void fill_te(uint32_t* te, const KeyTables* __restrict__ kt, uint32_t tid) {
+    constexpr uint32_t kPieces = Te::kBytes / 16, kPerTable = Te::kLanes / 4;
     static_assert(kPieces % (8 * kThreads) == 0, "pieces per thread");
-    u32x4* te4 = reinterpret_cast<u32x4*>(lds.te);
+    u32x4* te4 = reinterpret_cast<u32x4*>(te);
     for (uint32_t first = tid; first < kPieces; first += 8 * kThreads) {
         uint32_t v[8];
 #pragma unroll
         for (uint32_t k = 0; k < 8; ++k) {
             const uint32_t g = first + k * kThreads;  // piece number
-            const uint32_t pair = g >> 12, row = (g >> 4) & 255, t = 2 * pair + ((g >> 3) & 1);
+            const uint32_t pair = Te::kPairs ? g >> 12 : 0, row = (g >> 4) & 255,
+                           t = 2 * pair + (g & 15) / kPerTable;
             v[k] = kt->te[t][row];
         }
 #pragma unroll
@@ -1279,6 +1296,11 @@ __device__ __forceinline__ void fill_bulk_lds(BulkLds& lds, const KeyTables* __r
             te4[first + k * kThreads] = q;
         }
     }
+}
+template <FillHash kHash, uint32_t kThreads>
+__device__ __forceinline__ void fill_bulk_lds(BulkLds& lds, const KeyTables* __restrict__ kt,
+                                              uint32_t tid) {
+    fill_te<TeWide, kThreads>(lds.te, kt, tid);
     if constexpr (kHash != FillHash::kNone) {
         constexpr bool kMatrix = kHash == FillHash::kMatrix;
         const Block* from = kMatrix ? reinterpret_cast<const Block*>(kt->hash_image) : kt->ghash[kRowPower];
@@ -1364,7 +1386,7 @@ __global__ __launch_bounds__(kGroupThreads) void bulk_kernel(
 #pragma unroll
     for (int i = 0; i < 4 * (kRounds + 1); ++i) rk[i] = kt->rk[i];
     AesAddr A;
-    aes_addr_init(A, lane, rk + 4 * kRounds);
+    aes_addr_init<TeWide>(A, lane, rk + 4 * kRounds);
 
     const uint32_t nwaves = gridDim.x * kWavesPerGroup;
     const bool one_each = nunits_total <= nwaves;
@@ -1774,7 +1796,8 @@ template __global__ void final_kernel<true>(const KeyTables*, const ChunkDesc*, 
 // ------------------------------------------------------------------------------------------
 // A few chunks in ONE launch (the paper's swaps come a few chunks at a time, section 5.1): here
 // the length of the chain of dependent steps counts, not the work.  Descriptors are kernel
-// arguments.  Every wavefront walks one unit; units are of one row as long as the chip has a
+// arguments, or, for more chunks than fit those, one per workgroup in pinned memory.  Every
+// wavefront walks one unit; units are of one row as long as the chip has a
 // wavefront for each, and workgroups of four wavefronts as long as there is a compute unit for
 // each (a row takes a lone wavefront 2.6 us, sixteen on one compute unit 4.3 us).  Then
 //   1. the workgroup folds its units' sets into one as a tree in LDS (two to four multiplications
@@ -1792,8 +1815,8 @@ template __global__ void final_kernel<true>(const KeyTables*, const ChunkDesc*, 
 //      anybody: every workgroup runs to its end whatever the others do.  An arrival word serves
 //      about one workgroup per 11 ns, so those of a chunk of more than 64 are counted in
 //      sixteens first.
-// What a step needs from memory is fetched before the row (tree tables, powers) or by wavefronts
-// that the tree leaves idle.
+// What a step needs from memory is fetched before the row.  Workgroups of fewer than sixteen
+// wavefronts have one more, which makes E_K(J0) and prepares the finish meanwhile.
 // LDS after the round tables are done with, in tables of 8 KiB: 0..3 H^(2^(p + j)), the tree over the
 // workgroup's units (p = unit_power); 4..5 and 6 its sets.
 // Measured against the kernel this replaces (a tree over lanes and workgroups by tables, an extra
@@ -1866,70 +1889,95 @@ __device__ __forceinline__ Block length_block_entry(const Block* __restrict__ h_
 
 }  // namespace
 
-template <bool kDecrypt, int kRounds>
+// Tables of the round function, then of the tree.
+struct NarrowLds {
+    uint32_t te[TeNarrow::kBytes / 4];
+};
+
+template <bool kDecrypt, int kRounds, SwapKind kKind>
 __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
-    const KeyTables* __restrict__ kt, const ArgBatch batch, const uint8_t* __restrict__ ivs,
-    Block* __restrict__ slots, uint32_t* __restrict__ arrive, uint8_t* __restrict__ tags,
-    uint8_t* __restrict__ ok) {
-    __shared__ BulkLds lds;
-    __shared__ Block mask;                       // E_K(J0), in the workgroup with "block -1"
+    const KeyTables* __restrict__ kt, const ArgBatch batch, const GroupDesc* __restrict__ staged,
+    const uint8_t* __restrict__ ivs, uint32_t iv_len, Block* __restrict__ slots,
+    uint32_t* __restrict__ arrive, uint8_t* __restrict__ tags, uint8_t* __restrict__ ok) {
+    constexpr bool kNarrow = kKind == SwapKind::kNarrow, single = kKind != SwapKind::kUnits;
+    using Te = std::conditional_t<kNarrow, TeNarrow, TeWide>;
+    __shared__ std::conditional_t<kNarrow, NarrowLds, BulkLds> lds;
+    __shared__ Block mask_lds;                   // E_K(J0), where a wavefront with units makes it
     __shared__ GfWords shares[kWavesPerGroup];
     const uint32_t lds_base = lds_offset(&lds);
     const uint32_t tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t wave_power = batch.wave_power, nwaves = 1u << wave_power;
-    const uint32_t p = batch.unit_power;
+    const uint32_t p = single ? kRowPower : batch.unit_power;
+    // The wavefront that finishes the workgroup's part: one beyond those with units, or, where a
+    // workgroup can have no more, the last of them, which the tree leaves idle.
+    const bool beyond = wave_power < 4;
+    const bool finisher = wave == (beyond ? nwaves : nwaves - 1);
+    const bool worker = wave < nwaves;
 
     // this workgroup's chunk: the last one whose first workgroup is not behind it
-    const uint32_t first = lane < batch.nchunks ? batch.group_base[lane] : ~0u;
-    const uint32_t chunk = __builtin_amdgcn_readfirstlane(
-        (uint32_t)__popcll(__ballot(first <= blockIdx.x)) - 1u);
-    const ArgChunk cd = batch.c[chunk];
-    const uint32_t ngroups = batch.group_base[chunk + 1] - batch.group_base[chunk];
-    const uint32_t g = blockIdx.x - batch.group_base[chunk];
+    ArgChunk cd;
+    uint32_t group_base, ngroups;
+    if (staged != nullptr) {
+        const GroupDesc d = staged[blockIdx.x];
+        cd = d.c, group_base = d.group_base, ngroups = d.ngroups;
+    } else {
+        const uint32_t first = lane < batch.nchunks ? batch.group_base[lane] : ~0u;
+        const uint32_t chunk = __builtin_amdgcn_readfirstlane(
+            (uint32_t)__popcll(__ballot(first <= blockIdx.x)) - 1u);
+        cd = batch.c[chunk];
+        group_base = batch.group_base[chunk];
+        ngroups = batch.group_base[chunk + 1] - group_base;
+    }
+    const uint32_t g = blockIdx.x - group_base;
     // its units, counted back from the chunk's end; a negative number is a wavefront without one
     const int64_t nblk = (int64_t)((cd.len + 15) / 16);
-    const int64_t lead = lead_blocks(cd.aad_len);
+    const int64_t lead = swap_lead_blocks(cd.aad_len, beyond);
     const int32_t nunits = (int32_t)((nblk + lead + ((int64_t)1 << p) - 1) >> p);
-    const int32_t unit = nunits - (int32_t)((ngroups - g) << wave_power) + (int32_t)wave;
+    const int32_t unit =
+        worker ? nunits - (int32_t)((ngroups - g) << wave_power) + (int32_t)wave : -1;
     const int64_t b1 = nblk - ((int64_t)(nunits - 1 - unit) << p);
     const int64_t b0 = unit == 0 ? -lead : b1 - ((int64_t)1 << p);
-    // is "block -1" in this workgroup?
+    // is E_K(J0) made in this workgroup?  By the wavefront beyond the others in the chunk's first
+    // workgroup, or in "block -1" of the unit that has it
     const int64_t end = nblk - ((int64_t)(ngroups - 1 - g) << (p + wave_power));
-    const bool has_mask = end >= 0 && end - ((int64_t)1 << (p + wave_power)) < 0;
+    const bool has_mask = beyond ? g == 0
+                                 : end >= 0 && end - ((int64_t)1 << (p + wave_power)) < 0;
 
     uint32_t rk[4 * (kRounds + 1)];
 #pragma unroll
     for (int i = 0; i < 4 * (kRounds + 1); ++i) rk[i] = kt->rk[i];
-    const Block j = j0_from_iv(kt, ivs + (uint64_t)cd.index * 12, 12);
-    const bool single = p == kRowPower;
-    if (wave_power == 2) fill_bulk_lds<FillHash::kNone, 256>(lds, kt, tid);
-    else if (wave_power == 3) fill_bulk_lds<FillHash::kNone, 512>(lds, kt, tid);
-    else fill_bulk_lds<FillHash::kNone, 1024>(lds, kt, tid);
-    if (!single)
-        for (uint32_t i = tid; i < kNibbleTableEntries; i += 64u << wave_power)
-            lds.gh[i] = kt->ghash[kRowPower][i];
+    const Block j = j0_from_iv(kt, ivs + (uint64_t)cd.index * iv_len, iv_len);
+    if (worker) {
+        if (wave_power == 2) fill_te<Te, 256>(lds.te, kt, tid);
+        else if (wave_power == 3) fill_te<Te, 512>(lds.te, kt, tid);
+        else if (!kNarrow || tid < 512) fill_te<Te, kNarrow ? 512 : 1024>(lds.te, kt, tid);
+        if constexpr (!single) {
+            for (uint32_t i = tid; i < kNibbleTableEntries; i += 64u << wave_power)
+                lds.gh[i] = kt->ghash[kRowPower][i];
+        }
+    }
 
     // tree tables and powers of H: entry k * threads + tid of the 512 * wave_power, slices
     // 16 / nwaves * wave .. of lane's
     u32x4 tree[4];
     GfWords q[4];
-    // the last wavefront, idle in the tree, finishes the chunk
-    const bool finisher = wave == nwaves - 1;
     uint8_t* const tag_at = tags + (uint64_t)cd.index * 16;
-    Block extra{{0, 0, 0, 0}};     // what the workgroup with "block -1" adds to the tag
+    Block extra{{0, 0, 0, 0}};     // what the workgroup with E_K(J0) adds to the tag
     GfWords hop{{0, 0, 0, 0}};     // the power of H to the chunk's end, then times x^(8 (lane % 16))
     Block received{{0, 0, 0, 0}};  // the tag to compare with
     auto fetch_ahead = [&]() __attribute__((always_inline)) {
         const u32x4* from = reinterpret_cast<const u32x4*>(kt->ghash[p]);
         const uint32_t per_thread = (8 * wave_power) >> wave_power;  // 4, 3, 2
-#pragma unroll
-        for (uint32_t k = 0; k < 4; ++k)
-            if (k < per_thread) tree[k] = from[(k << (6 + wave_power)) + tid];
         const uint32_t slices = kDotSlices >> wave_power;            // 4, 2, 1
+        if (worker) {
 #pragma unroll
-        for (uint32_t s = 0; s < 4; ++s)
-            if (s < slices) q[s] = kt->dot[lane][slices * wave + s];
+            for (uint32_t k = 0; k < 4; ++k)
+                if (k < per_thread) tree[k] = from[(k << (6 + wave_power)) + tid];
+#pragma unroll
+            for (uint32_t s = 0; s < 4; ++s)
+                if (s < slices) q[s] = kt->dot[lane][slices * wave + s];
+        }
         if (finisher) {
             hop = kt->hop[p + wave_power - kHopMinPower][ngroups - 1 - g];
             if (has_mask) extra = length_block_entry(kt->ghash[0], cd.aad_len, cd.len, lane);
@@ -1937,60 +1985,49 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
         }
     };
 
-    AadBlocks aad = aad_blocks(cd.aad, cd.aad_len);
+    AadBlocks aad = aad_blocks(cd.aad, worker ? cd.aad_len : 0);
     auto keep_mask = [&](uint32_t s0, uint32_t s1, uint32_t s2, uint32_t s3)
-        __attribute__((always_inline)) { mask = Block{{s0, s1, s2, s3}}; };
+        __attribute__((always_inline)) { mask_lds = Block{{s0, s1, s2, s3}}; };
     uint32_t y[4] = {0, 0, 0, 0};
-    if (single) {
-        // one row of 64 blocks up to b1
-        const int64_t blk = b1 - kRowBlocks + lane;
-        const bool edge = b1 < kRowBlocks || b1 == nblk;
+    const bool at_start = unit == 0 && cd.aad_len != 0;
+    // one row of 64 blocks up to b1, or J0 in every lane of the wavefront beyond
+    const int64_t blk = worker ? b1 - kRowBlocks + lane : -1;
+    if (single || !worker) {
+        const bool edge = !worker || b1 < kRowBlocks || b1 == nblk;
         RowPayload row{0, 0, 0, 0, 0, false};
         if (unit >= 0) row = load_row(cd.src, cd.len, blk, edge);
         fetch_ahead();
         __syncthreads();  // the tables are in place
-        if (unit >= 0) {
-            if (unit == 0) aad.prepare(kt->ghash[0]);
+        if (unit >= 0 || (!worker && has_mask)) {
+            if (at_start) aad.prepare(kt->ghash[0]);
             AesAddr A;
-            aes_addr_init(A, lane, rk + 4 * kRounds);
+            aes_addr_init<Te>(A, lane, rk + 4 * kRounds);
             GhashNone G;
-            const CtrBlock C{j.w[0], j.w[1], j.w[2], (uint32_t)blk + bswap32(j.w[3]) + 1u};
+            const CtrBlock<Te> C{j.w[0], j.w[1], j.w[2], (uint32_t)blk + bswap32(j.w[3]) + 1u};
             bulk_row<kDecrypt, kRounds, kDecrypt>(rk, A, C, row, cd.dst, blk, edge, aad, keep_mask,
                                                   lds_base, G);
             for (int k = 0; k < 4; ++k) y[k] = G.w[k];
         }
-    } else {
-        __syncthreads();
-        if (unit >= 0) {
-            if (unit == 0) aad.prepare(kt->ghash[0]);
-            AesAddr A;
-            aes_addr_init(A, lane, rk + 4 * kRounds);
-            walk_unit<kDecrypt, kRounds, kDecrypt, false>(rk, A, lane, wave, lds_base, cd.src,
-                                                          cd.dst, cd.len, b0, b1, b1 == nblk, aad,
-                                                          j, keep_mask, y);
+    }
+    if constexpr (!single) {
+        if (worker) {
+            __syncthreads();
+            if (unit >= 0) {
+                if (at_start) aad.prepare(kt->ghash[0]);
+                AesAddr A;
+                aes_addr_init<Te>(A, lane, rk + 4 * kRounds);
+                walk_unit<kDecrypt, kRounds, kDecrypt, false>(rk, A, lane, wave, lds_base, cd.src,
+                                                              cd.dst, cd.len, b0, b1, b1 == nblk,
+                                                              aad, j, keep_mask, y);
+            }
+            fetch_ahead();
         }
-        fetch_ahead();
     }
-    __syncthreads();  // the round tables are done with: their LDS now takes the tree's
-
-    Block(*tables)[kNibbleTableEntries] = reinterpret_cast<Block(*)[kNibbleTableEntries]>(&lds);
-    Block(*sets[2])[64] = {reinterpret_cast<Block(*)[64]>(tables[4]),
-                           reinterpret_cast<Block(*)[64]>(tables[6])};
-    {
-        u32x4* to = reinterpret_cast<u32x4*>(tables);
-        const uint32_t per_thread = (8 * wave_power) >> wave_power;
-#pragma unroll
-        for (uint32_t k = 0; k < 4; ++k)
-            if (k < per_thread) to[(k << (6 + wave_power)) + tid] = tree[k];
-    }
-    sets[0][wave][lane] = Block{{y[0], y[1], y[2], y[3]}};
-    __syncthreads();
-
     if (finisher) {
+        // what the finish takes, while the others still walk (or fold)
         if (has_mask) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) extra.w[k] = rows_summed(row_summed(extra.w[k]));
-            block_xor(extra, mask);
         }
         GfWords t = hop;
         gfw_mul_x8(t);
@@ -2005,6 +2042,21 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
         gfw_mul_x32(t), gfw_mul_x32(t);
         if (lane & 8) hop = t;
     }
+    __syncthreads();  // the round tables are done with: their LDS now takes the tree's
+
+    Block(*tables)[kNibbleTableEntries] = reinterpret_cast<Block(*)[kNibbleTableEntries]>(&lds);
+    Block(*sets[2])[64] = {reinterpret_cast<Block(*)[64]>(tables[4]),
+                           reinterpret_cast<Block(*)[64]>(tables[6])};
+    if (worker) {
+        u32x4* to = reinterpret_cast<u32x4*>(tables);
+        const uint32_t per_thread = (8 * wave_power) >> wave_power;
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k)
+            if (k < per_thread) to[(k << (6 + wave_power)) + tid] = tree[k];
+        sets[0][wave][lane] = Block{{y[0], y[1], y[2], y[3]}};
+    }
+    __syncthreads();
+
     // 1. every wavefront passes every barrier; only the shrinking front half has work to do
     for (uint32_t level = 0; level < wave_power; ++level) {
         if (wave < (nwaves >> (level + 1))) {
@@ -2017,7 +2069,7 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
         __syncthreads();
     }
     // 2.
-    {
+    if (worker) {
         const Block set = sets[wave_power & 1][0][lane];
         const GfWords share = wave_power == 2   ? dot_share<4>(set, wave, q)
                               : wave_power == 3 ? dot_share<2>(set, wave, q)
@@ -2044,7 +2096,11 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
         for (int k = 0; k < 4; ++k) sum.a[k] = row_summed(sum.a[k]);
     }
     Block tag = gfw_to_block(sum);
-    block_xor(tag, extra);
+    if (has_mask) {
+        block_xor(tag, extra);
+        const Block m = mask_lds;
+        block_xor(tag, m);
+    }
     // 4.
     if (ngroups > 1) {
         if (lane == 0) store_block_device_scope(slots + blockIdx.x, tag.w[0], tag.w[1], tag.w[2], tag.w[3]);
@@ -2062,20 +2118,19 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
                 __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return last;
         };
-        uint32_t* const main_word = arrive + chunk * kArriveStride;
+        uint32_t* const main_word = arrive + group_base * kArriveStride;
         if (ngroups <= 64) {
             if (!last_of(main_word, ngroups)) return;
         } else {
-            const uint32_t sixteen = g / 16, base = batch.group_base[chunk] + 16 * sixteen;
-            const uint32_t in_it = ngroups - 16 * sixteen < 16 ? ngroups - 16 * sixteen : 16;
-            if (!last_of(arrive + (64 + base) * kArriveStride, in_it)) return;
+            const uint32_t first = g & ~15u, in_it = ngroups - first < 16 ? ngroups - first : 16;
+            if (!last_of(main_word + (kSwapMaxGroups + first) * kArriveStride, in_it)) return;
             if (!last_of(main_word, (ngroups + 15) / 16)) return;
         }
         // the others' results are read with device-scope loads, issued after the arrival count was
         // seen: they come from memory, not from this XCD's caches
         tag = Block{{0, 0, 0, 0}};
         for (uint32_t i = lane; i < ngroups; i += 64) {
-            const Block b = load_block_device_scope(slots + batch.group_base[chunk] + i);
+            const Block b = load_block_device_scope(slots + group_base + i);
             block_xor(tag, b);
         }
 #pragma unroll
@@ -2085,8 +2140,15 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
 }
 
 #define PGCM_INSTANTIATE_SWAP(D, R)                                                          \
-    template __global__ void swap_kernel<D, R>(const KeyTables*, ArgBatch, const uint8_t*, Block*, \
-                                               uint32_t*, uint8_t*, uint8_t*)
+    template __global__ void swap_kernel<D, R, SwapKind::kNarrow>(                                  \
+        const KeyTables*, ArgBatch, const GroupDesc*, const uint8_t*, uint32_t, Block*, uint32_t*, \
+        uint8_t*, uint8_t*);                                                                       \
+    template __global__ void swap_kernel<D, R, SwapKind::kRows>(                                    \
+        const KeyTables*, ArgBatch, const GroupDesc*, const uint8_t*, uint32_t, Block*, uint32_t*, \
+        uint8_t*, uint8_t*);                                                                       \
+    template __global__ void swap_kernel<D, R, SwapKind::kUnits>(                                   \
+        const KeyTables*, ArgBatch, const GroupDesc*, const uint8_t*, uint32_t, Block*, uint32_t*, \
+        uint8_t*, uint8_t*)
 PGCM_INSTANTIATE_SWAP(false, 10);
 PGCM_INSTANTIATE_SWAP(false, 12);
 PGCM_INSTANTIATE_SWAP(false, 14);
@@ -2268,87 +2330,6 @@ PGCM_INSTANTIATE_SMALL(true, 10);
 PGCM_INSTANTIATE_SMALL(true, 12);
 PGCM_INSTANTIATE_SMALL(true, 14);
 #undef PGCM_INSTANTIATE_SMALL
-
-// Chunks of up to eight rows (8 KiB): one workgroup of eight wavefronts per chunk, a row each, so
-// that the rows' cipher passes run side by side; the rows' lane sums are then folded across the
-// wavefronts as a tree through LDS (H^64, H^128, H^256), and wavefront 0 finishes the chunk.
-// Rows are aligned to the chunk's end and sit in the last wavefronts of the smallest power of two
-// that holds them; E_K(J0) is one more cipher pass in wavefront 0.
-template <bool kDecrypt, int kRounds>
-__global__ __launch_bounds__(kSmallWideWaves * 64) void small_wide_kernel(
-    const KeyTables* __restrict__ kt, const ChunkDesc* __restrict__ chunks_host, uint32_t nchunks,
-    const uint8_t* __restrict__ ivs, uint32_t iv_len, uint8_t* __restrict__ tags,
-    uint8_t* __restrict__ ok) {
-    constexpr uint32_t kTables = kRowPower + 3;  // H^(2^k), k = 0 .. 8
-    static_assert(kSmallWideWaves == 8, "three tree levels over the wavefronts");
-    __shared__ uint32_t te[4][256];
-    __shared__ Block tables[kTables][kNibbleTableEntries];
-    __shared__ Block partial[kSmallWideWaves][64];
-    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (blockIdx.x >= nchunks) return;  // uniform over the workgroup
-    const ChunkDesc cd = chunks_host[blockIdx.x];
-    const uint32_t nblk = (uint32_t)((cd.len + 15) / 16);          // <= 512
-    const uint32_t nrows = (nblk + kRowBlocks - 1) / kRowBlocks;   // 0 .. 8, without block -1
-    uint32_t wave_levels = 0;                                      // tree levels over wavefronts
-    while ((1u << wave_levels) < nrows) ++wave_levels;
-    const uint32_t lane_levels = nrows > 1 ? 6u : lane_tree_levels(nblk);
-
-    uint32_t needed = 1u | ((1u << lane_levels) - 1u);
-    needed |= ((1u << wave_levels) - 1u) << kRowPower;
-    load_small_tables<kTables>(te, tables, kt, needed, tid);
-    __syncthreads();
-    const uint32_t* __restrict__ rk = kt->rk;
-    const Block j = j0_from_iv(kt, ivs + (uint64_t)cd.index * iv_len, iv_len);
-    const uint32_t ctr1 = bswap32(j.w[3]) + 1u;
-
-    // wavefront w of the first 2^wave_levels takes row w - (2^wave_levels - nrows), if there is one
-    uint32_t y[4] = {0, 0, 0, 0};
-    const int row = (int)wave - (int)((1u << wave_levels) - nrows);
-    if (wave < (1u << wave_levels) && row >= 0) {
-        Block aad_y{{0, 0, 0, 0}};
-        if (row == 0 && cd.aad_len != 0) aad_y = aad_hash(kt, cd.aad, cd.aad_len);
-        const int64_t blk = (int64_t)nblk - (int64_t)(nrows - (uint32_t)row) * kRowBlocks + lane;
-        uint32_t s[4];
-        small_row<kDecrypt, kRounds>(rk, te, cd, j, ctr1, blk, aad_y, s, y);
-    }
-    uint32_t mask[4] = {j.w[0], j.w[1], j.w[2], j.w[3]};
-    if (wave == 0) aes_block_lds_plain<kRounds>(rk, te, mask);  // E_K(J0)
-
-    // every wavefront passes every barrier; only the shrinking front has work to do
-    for (uint32_t l = 0; l < wave_levels; ++l) {
-        partial[wave][lane] = Block{{y[0], y[1], y[2], y[3]}};
-        __syncthreads();
-        if (wave < ((1u << wave_levels) >> (l + 1))) {
-            const Block a = partial[2 * wave][lane], b = partial[2 * wave + 1][lane];
-            y[0] = a.w[0], y[1] = a.w[1], y[2] = a.w[2], y[3] = a.w[3];
-            ghash_mul_lds(lds_offset(tables[kRowPower + l]), y);
-            y[0] ^= b.w[0], y[1] ^= b.w[1], y[2] ^= b.w[2], y[3] ^= b.w[3];
-        }
-        __syncthreads();
-    }
-    if (wave != 0) return;
-
-    if (nblk == 0) {
-        // nothing was hashed: the state is what the AAD left
-        const Block a = aad_hash(kt, cd.aad, cd.aad_len);
-        y[0] = a.w[0], y[1] = a.w[1], y[2] = a.w[2], y[3] = a.w[3];
-    } else {
-        fold_lanes(lds_offset(tables[0]), y, lane_levels);
-    }
-    finish_chunk<kDecrypt>(lds_offset(tables[0]), y, mask, cd, tags, ok, lane);
-}
-
-#define PGCM_INSTANTIATE_SMALL_WIDE(D, R)                                                   \
-    template __global__ void small_wide_kernel<D, R>(const KeyTables*, const ChunkDesc*,       \
-                                                     uint32_t, const uint8_t*, uint32_t,       \
-                                                     uint8_t*, uint8_t*)
-PGCM_INSTANTIATE_SMALL_WIDE(false, 10);
-PGCM_INSTANTIATE_SMALL_WIDE(false, 12);
-PGCM_INSTANTIATE_SMALL_WIDE(false, 14);
-PGCM_INSTANTIATE_SMALL_WIDE(true, 10);
-PGCM_INSTANTIATE_SMALL_WIDE(true, 12);
-PGCM_INSTANTIATE_SMALL_WIDE(true, 14);
-#undef PGCM_INSTANTIATE_SMALL_WIDE
 
 // Brings a batch's descriptors from pinned host memory into the device workspace.  Done by a
 // kernel so that the batch stays on one hardware queue: a DMA copy between kernels costs two

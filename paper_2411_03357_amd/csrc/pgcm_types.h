@@ -124,13 +124,21 @@ constexpr uint32_t lead_blocks(uint32_t aad_len) {
     return aad_len <= 16 || aad_len > 64 * 16 ? 1 : (aad_len + 15) / 16;
 }
 
+// ... and where another wavefront makes E_K(J0): the AAD's blocks alone.
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+constexpr uint32_t swap_lead_blocks(uint32_t aad_len, bool mask_elsewhere) {
+    return mask_elsewhere && aad_len == 0 ? 0 : lead_blocks(aad_len);
+}
+
 // A batch of few chunks that does not fill the chip (every unit gets a wavefront of its own) is
 // done by ONE kernel, its descriptors travelling as kernel arguments: the paper's swaps arrive a
 // few chunks at a time between synchronisations (section 5.1), and for them the time of a call
 // counts, not the rate.  Every chunk gets workgroups of its own, as many units each as a workgroup
 // has wavefronts, counted back from the chunk's end so that only its first workgroup can be short.
 // A chunk's units cover the blocks before its block 0 as well.
-constexpr uint32_t kArgChunks = 60;
+constexpr uint32_t kArgChunks = 64;
 struct ArgChunk {
     const uint8_t* src;
     uint8_t* dst;
@@ -147,24 +155,29 @@ struct ArgBatch {
     uint32_t group_base[kArgChunks + 1];  // first workgroup of every chunk; their number
     ArgChunk c[kArgChunks];
 };
-// Workgroups of a launch, and so of a chunk (KeyTables::hop has their distances).
-constexpr uint32_t kSwapMaxGroups = kHopEntries;
-// Arrival words, 64 bytes apart: one per chunk, and one per workgroup for the sixteens that the
-// workgroups of a chunk of many are counted in.
+// Workgroups of a chunk (KeyTables::hop has their distances) and of a launch.
+constexpr uint32_t kSwapChunkGroups = kHopEntries;
+constexpr uint32_t kSwapMaxGroups = 512;
+// Arrival words, 64 bytes apart: a chunk's is that of its first workgroup; the workgroups of a chunk
+// of many are counted in sixteens first, on the words of every sixteenth in the upper half.
 constexpr uint32_t kArriveStride = 16;
-constexpr uint32_t kSwapArriveWords = (64 + kSwapMaxGroups) * kArriveStride;
-static_assert(kArgChunks <= 64, "arrival words of the chunks");
+constexpr uint32_t kSwapArriveWords = 2 * kSwapMaxGroups * kArriveStride;
+// Batches of more chunks than fit the arguments have a descriptor per workgroup in pinned memory.
+struct alignas(16) GroupDesc {
+    ArgChunk c;
+    uint32_t group_base, ngroups;  // the chunk's first workgroup and their number
+};
 
 // A batch whose chunks are all at most this long takes the small-transfer path: one kernel (the
 // paper's non-swap transfers are usually < 8 KB, section 4.2): eight rows of 64 blocks.
 constexpr uint64_t kSmallChunkBytes = 8192;
-// ... and when they are all at most this long (63 blocks: one row together with "block -1") the
-// kernel is the one with a wavefront per chunk
+// The one-launch kernel is there for the latency of a few transfers, a workgroup each; of more
+// chunks than this (two workgroups per compute unit are resident) ...
+constexpr size_t kSmallMaxChunks = 512;
+// ... those of at most this length (63 blocks: one row together with "block -1") take a kernel with
+// a wavefront per chunk, and longer ones the unit schedule, which gets more chunks per second
+// out of the chip.
 constexpr uint64_t kSmallRowBytes = 1008;
-// The kernel with a workgroup per chunk is there for the latency of a few transfers; a batch of
-// more chunks than this (two rounds of resident workgroups; measured crossover) longer than one
-// row goes through the unit schedule instead, which gets more chunks per second out of the chip.
-constexpr size_t kSmallWideMaxChunks = 512;
 
 // Items of the dynamic schedule are grabbed from a counter; to find an item's chunk a wavefront
 // starts at coarse_map[item >> kCoarseShift] and walks unit_base[] forward.
