@@ -21,6 +21,8 @@ FLAGS = [
     "-Wall", "-Wno-unused-command-line-argument",
     # keep the compiler from forming packed-FP32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # the leading kernel arguments come in registers instead of being loaded from host memory
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",
 ]
 
 

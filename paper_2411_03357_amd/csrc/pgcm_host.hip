@@ -368,10 +368,17 @@ void launch_bulk(int rounds, bool matrix_hash, dim3 grid, hipStream_t stream, Ar
 template <bool kDecrypt, SwapKind kKind, class... Args>
 void launch_swap(int rounds, dim3 grid, dim3 block, hipStream_t stream, bool capturing,
                  hipEvent_t done, Args... args) {
-    auto* kernel = rounds == 10   ? swap_kernel<kDecrypt, 10, kKind>
-                   : rounds == 12 ? swap_kernel<kDecrypt, 12, kKind>
-                                  : swap_kernel<kDecrypt, 14, kKind>;
-    launch_last(kernel, grid, block, stream, capturing || done == nullptr, done, args...);
+    auto launch = [&](auto* kernel) {
+        launch_last(kernel, grid, block, stream, capturing || done == nullptr, done, args...);
+    };
+    if constexpr (kKind != SwapKind::kUnits)
+        launch(swap_kernel<kDecrypt, 0, kKind>);
+    else if (rounds == 10)
+        launch(swap_kernel<kDecrypt, 10, kKind>);
+    else if (rounds == 12)
+        launch(swap_kernel<kDecrypt, 12, kKind>);
+    else
+        launch(swap_kernel<kDecrypt, 14, kKind>);
 }
 
 // many chunks of one row: a wavefront per chunk
@@ -643,7 +650,6 @@ int run_small_batch(pgcm_key* key, Context* ctx, const BatchArgs& a) {
 }
 
 // Workspace of the one-launch path: arrival words, one result per workgroup.
-constexpr size_t kSwapArriveBytes = round_up(sizeof(uint32_t) * kSwapArriveWords, 256);
 constexpr size_t kSwapWorkBytes = kSwapArriveBytes + sizeof(Block) * kSwapMaxGroups;
 
 // How a batch is cut for the one-launch path, if it takes it.
@@ -714,15 +720,18 @@ bool swap_shape(const pgcm_key* key, const BatchArgs& a, bool all_small, SwapSha
 template <SwapKind kKind>
 void launch_swap_batch(const pgcm_key* key, const BatchArgs& a, const SwapShape& shape,
                        hipEvent_t done, const ArgBatch& batch, const GroupDesc* staged,
-                       Block* slots, uint32_t* arrive) {
+                       uint8_t* work) {
     const dim3 grid(shape.groups), block(64u * ((1u << shape.wave_power) + (shape.wave_power < 4)));
     const KeyTables* kt = key->tables;
+    const SwapMeta meta = swap_meta(staged ? 0 : (uint32_t)a.n, shape.unit_power, shape.wave_power,
+                                    shape.alone, a.order == nullptr, shape.groups,
+                                    (uint32_t)key->rounds);
     if (a.decrypt)
-        launch_swap<true, kKind>(key->rounds, grid, block, a.stream, a.capturing, done, kt, batch,
-                                   staged, a.ivs, a.iv_len, slots, arrive, a.tags, a.ok);
+        launch_swap<true, kKind>(key->rounds, grid, block, a.stream, a.capturing, done, kt, a.ivs,
+                                 a.iv_len, meta, work, a.tags, a.ok, staged, batch);
     else
-        launch_swap<false, kKind>(key->rounds, grid, block, a.stream, a.capturing, done, kt,
-                                    batch, staged, a.ivs, a.iv_len, slots, arrive, a.tags, a.ok);
+        launch_swap<false, kKind>(key->rounds, grid, block, a.stream, a.capturing, done, kt, a.ivs,
+                                  a.iv_len, meta, work, a.tags, a.ok, staged, batch);
 }
 
 // A batch of few chunks that does not fill the chip: one kernel.  Up to kArgChunks chunks travel as
@@ -730,9 +739,6 @@ void launch_swap_batch(const pgcm_key* key, const BatchArgs& a, const SwapShape&
 // workspace, the call needs no context at all (ctx is null).
 int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapShape& shape) {
     ArgBatch batch;
-    batch.nchunks = (uint32_t)a.n;
-    batch.unit_power = shape.unit_power;
-    batch.wave_power = shape.wave_power;
     const bool in_args = a.n <= kArgChunks;
     GroupDesc* h_groups = nullptr;
     int s = 0;
@@ -763,18 +769,16 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapSh
         groups += of_chunk;
     }
     if (in_args) batch.group_base[a.n] = groups;
-    uint32_t* d_arrive = nullptr;
-    Block* d_slots = nullptr;
+    uint8_t* d_work = nullptr;
     if (!shape.alone) {
         const int rc = ensure_work(ctx, kSwapWorkBytes, a.stream);
         if (rc != PGCM_OK) return rc;
-        d_arrive = reinterpret_cast<uint32_t*>(ctx->work);
-        d_slots = reinterpret_cast<Block*>(ctx->work + kSwapArriveBytes);
+        d_work = ctx->work;
         // the arrival words are left at zero by every batch of this kind; they need clearing when
         // the workspace is new, was used by a batch of the other kind, or is shared between keys
         if (!ctx->arrive_clean || !ctx->growable)
-            hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(1024), 0, a.stream, d_arrive,
-                               kSwapArriveWords);
+            hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(1024), 0, a.stream,
+                               reinterpret_cast<uint32_t*>(d_work), kSwapArriveWords);
         ctx->arrive_clean = false;
         ctx->counter_at = nullptr;  // the unit counter of other batches may lie under this
     }
@@ -785,11 +789,11 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapSh
     // using it again only moves the guard later.)
     const hipEvent_t done = ctx != nullptr ? ctx->stage_done[s] : nullptr;
     if (shape.narrow)
-        launch_swap_batch<SwapKind::kNarrow>(key, a, shape, done, batch, h_groups, d_slots, d_arrive);
+        launch_swap_batch<SwapKind::kNarrow>(key, a, shape, done, batch, h_groups, d_work);
     else if (shape.unit_power == kRowPower)
-        launch_swap_batch<SwapKind::kRows>(key, a, shape, done, batch, h_groups, d_slots, d_arrive);
+        launch_swap_batch<SwapKind::kRows>(key, a, shape, done, batch, h_groups, d_work);
     else
-        launch_swap_batch<SwapKind::kUnits>(key, a, shape, done, batch, h_groups, d_slots, d_arrive);
+        launch_swap_batch<SwapKind::kUnits>(key, a, shape, done, batch, h_groups, d_work);
     if (rc_timing == PGCM_OK) rc_timing = record_timing_stop(key, a.stream);
     int rc_end = PGCM_OK;
     if (!in_args) {

@@ -21,15 +21,18 @@ __global__ void bulk_kernel(const KeyTables* kt, const ChunkDesc* chunks,
 
 // The whole invocation of a few chunks in one launch, 2^wave_power wavefronts of units a workgroup (at
 // least four) and, below sixteen, one more.  The chunks come as arguments, or, when `staged` is not
-// null, with a descriptor per workgroup there (batch then only has unit_power and wave_power).
-// slots: one block per workgroup; arrive: kSwapArriveWords words, zero on entry and left zero;
-// neither is touched if no chunk has more than one workgroup.  kRows: units of one row; kNarrow: likewise, and
-// the round tables take half the room; kUnits: units of two to sixteen rows.
+// null, with a descriptor per workgroup there (batch is not looked at then).
+// work: kSwapArriveWords arrival words, zero on entry and left zero, then one block per workgroup;
+// not touched if no chunk has more than one workgroup.  kRows: units of one row; kNarrow: likewise,
+// and the round tables take half the room (both with kRounds 0, they serve any key); kUnits: units of
+// two to sixteen rows.
+// The arguments before `batch` come in registers (compiled for that, they are the first fourteen
+// words), so that the tables are fetched while the rest of the arguments is.
 enum class SwapKind { kNarrow, kRows, kUnits };
 template <bool kDecrypt, int kRounds, SwapKind kKind>
-__global__ void swap_kernel(const KeyTables* kt, ArgBatch batch, const GroupDesc* staged,
-                            const uint8_t* ivs, uint32_t iv_len, Block* slots, uint32_t* arrive,
-                            uint8_t* tags, uint8_t* ok);
+__global__ void swap_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t iv_len, SwapMeta meta,
+                            uint8_t* work, uint8_t* tags, uint8_t* ok, const GroupDesc* staged,
+                            ArgBatch batch);
 
 __global__ void clear_words_kernel(uint32_t* words, uint32_t n);
 

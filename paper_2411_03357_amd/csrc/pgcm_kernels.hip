@@ -228,7 +228,7 @@ __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict_
     __shared__ GfWords constants[kConstants];
     __shared__ Block basis[kConstants][128];  // x^b * constant, b = bit b % 32 of word b / 32
     __shared__ Block nibbles[kLevels][kNibbleTableEntries];
-    __shared__ GfWords h_power[65];
+    __shared__ GfWords h_power[66];
     __shared__ uint32_t te[4][256], rk[60];
     __shared__ uint8_t sbox[256];
     const uint32_t tid = threadIdx.x;
@@ -352,7 +352,7 @@ __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict_
         kt->hash_image[m][e % kRowMatrixWords] = v;
     }
 
-    // H^1 .. H^64, doubling: H^(2^j + i) = H^i * H^(2^j)
+    // H^1 .. H^65, doubling: H^(2^j + i) = H^i * H^(2^j)
     if (tid == 0) h_power[1] = constants[0];
     __syncthreads();
     for (uint32_t j = 0; j < kLevels; ++j) {
@@ -362,14 +362,17 @@ __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict_
         }
         __syncthreads();
     }
+    if (tid == 0)
+        h_power[65] = gfw_from_block(gf_mul_table(nibbles[0], gfw_to_block(h_power[64])));
+    __syncthreads();
     for (uint32_t e = tid; e < 64 * kDotSlices; e += blockDim.x) {
         const uint32_t l = e / kDotSlices, t = e % kDotSlices;
-        GfWords p = h_power[64 - l];
+        GfWords p = h_power[65 - l];
         for (uint32_t i = 0; i < t; ++i) gfw_mul_x8(p);
         kt->dot[l][t] = p;
     }
     // hop[d][k] likewise: k = 2^j + i from i with H^(2^(8 + d + j)), from its nibble table
-    if (tid < kHopPowers) kt->hop[tid][0] = constants[0];
+    if (tid < kHopPowers) kt->hop[tid][0] = GfWords{{0x80000000u, 0, 0, 0}};
     for (uint32_t j = 0; (1u << j) < kHopEntries; ++j) {
         __syncthreads();
         for (uint32_t e = tid; e < kHopPowers << j; e += blockDim.x) {
@@ -624,7 +627,7 @@ __device__ __forceinline__ void lds_write128(uint32_t addr, u32x4 v) {
 // is rewritten every round).
 // TeWide: 128 KiB, every entry 32 times, so that no lookups collide: 2 cycles each.
 struct TeWide {
-    static constexpr uint32_t kBase = kLdsTeBase, kBytes = kLdsTeBytes, kPairs = 0x10000u, kLanes = 32;
+    static constexpr uint32_t kBase = kLdsTeBase, kPairs = 0x10000u, kLanes = 32;
     static constexpr uint32_t offset(int t) { return kBase + 128u * (t & 1); }
 };
 // TeNarrow: 64 KiB with all four tables in a row, every entry sixteen times, so that lanes l and
@@ -677,8 +680,7 @@ struct AesAddr {
 
 // last_round_key: the four words of round key Nr
 template <class Te>
-__device__ __forceinline__ void aes_addr_init(AesAddr& A, uint32_t lane,
-                                              const uint32_t* __restrict__ last_round_key) {
+__device__ __forceinline__ void aes_addr_init(AesAddr& A, uint32_t lane) {
     const uint32_t lo = (lane & (Te::kLanes - 1)) * 4, hi = lo | Te::kPairs;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -686,6 +688,14 @@ __device__ __forceinline__ void aes_addr_init(AesAddr& A, uint32_t lane,
         A.a[j][1] = lo;
         A.a[j][2] = hi;
         A.a[j][3] = hi;
+    }
+}
+template <class Te>
+__device__ __forceinline__ void aes_addr_init(AesAddr& A, uint32_t lane,
+                                              const uint32_t* __restrict__ last_round_key) {
+    aes_addr_init<Te>(A, lane);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
         A.last_key[j] = last_round_key[j];
         asm volatile("" : "+v"(A.last_key[j]));  // a vector register, and kept there
     }
@@ -716,6 +726,10 @@ struct CtrConsts {
 
 // The counter block of a row that stands alone (a unit of one row): no constants are formed, and
 // round 1 makes its sixteen lookups like any other.
+struct LaneKeys {
+    uint32_t word;    // lane i: round key word i
+    uint32_t rounds;
+};
 template <class TeLayout>
 struct CtrBlock {
     using Te = TeLayout;
@@ -793,7 +807,6 @@ __device__ __forceinline__ uint32_t nibble_offset(uint32_t v, uint32_t mask_f0) 
 
 // A unit of one row: its sums are its blocks, and nothing is multiplied.
 struct GhashNone {
-    static constexpr bool kMatrix = false, kTable = false;
     uint32_t w[4];
     __device__ __forceinline__ void begin() {}
     __device__ __forceinline__ void absorb(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3) {
@@ -980,8 +993,7 @@ struct GhashRowMatrix {
 
 // Rounds kFirst .. kRounds of AES with the row's GHASH multiplication G riding along; rk is
 // wave-uniform (scalar registers).  Between rounds the state u0 .. u3 is carried without its round
-// key: the key bytes are added while the next round's addresses are formed.  With kFirst = 1 the
-// addresses of round 1 are in A already.
+// key: the key bytes are added while the next round's addresses are formed.
 // The byte steps of a table hash from step 4 on are spread evenly over rounds 3 .. kRounds (one
 // each for AES-256, one or two each for the shorter keys).
 // On the matrix cores the multiplication is two chains of eight instructions instead: chain c is
@@ -1005,24 +1017,22 @@ __device__ __forceinline__ void aes_rounds_lds(const uint32_t* __restrict__ rk, 
             if constexpr (r <= 10) G.template load<r - 3>();
             __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (r > 1) {
-            key_xor_into_addr<0, 0>(A.a[0][0], k[0], u0);
-            key_xor_into_addr<1, 1>(A.a[0][1], k[0], u0);
-            key_xor_into_addr<2, 2>(A.a[0][2], k[0], u0);
-            key_xor_into_addr<3, 3>(A.a[0][3], k[0], u0);
-            key_xor_into_addr<0, 0>(A.a[1][0], k[1], u1);
-            key_xor_into_addr<1, 1>(A.a[1][1], k[1], u1);
-            key_xor_into_addr<2, 2>(A.a[1][2], k[1], u1);
-            key_xor_into_addr<3, 3>(A.a[1][3], k[1], u1);
-            key_xor_into_addr<0, 0>(A.a[2][0], k[2], u2);
-            key_xor_into_addr<1, 1>(A.a[2][1], k[2], u2);
-            key_xor_into_addr<2, 2>(A.a[2][2], k[2], u2);
-            key_xor_into_addr<3, 3>(A.a[2][3], k[2], u2);
-            key_xor_into_addr<0, 0>(A.a[3][0], k[3], u3);
-            key_xor_into_addr<1, 1>(A.a[3][1], k[3], u3);
-            key_xor_into_addr<2, 2>(A.a[3][2], k[3], u3);
-            key_xor_into_addr<3, 3>(A.a[3][3], k[3], u3);
-        }
+        key_xor_into_addr<0, 0>(A.a[0][0], k[0], u0);
+        key_xor_into_addr<1, 1>(A.a[0][1], k[0], u0);
+        key_xor_into_addr<2, 2>(A.a[0][2], k[0], u0);
+        key_xor_into_addr<3, 3>(A.a[0][3], k[0], u0);
+        key_xor_into_addr<0, 0>(A.a[1][0], k[1], u1);
+        key_xor_into_addr<1, 1>(A.a[1][1], k[1], u1);
+        key_xor_into_addr<2, 2>(A.a[1][2], k[1], u1);
+        key_xor_into_addr<3, 3>(A.a[1][3], k[1], u1);
+        key_xor_into_addr<0, 0>(A.a[2][0], k[2], u2);
+        key_xor_into_addr<1, 1>(A.a[2][1], k[2], u2);
+        key_xor_into_addr<2, 2>(A.a[2][2], k[2], u2);
+        key_xor_into_addr<3, 3>(A.a[2][3], k[2], u2);
+        key_xor_into_addr<0, 0>(A.a[3][0], k[3], u3);
+        key_xor_into_addr<1, 1>(A.a[3][1], k[3], u3);
+        key_xor_into_addr<2, 2>(A.a[3][2], k[3], u3);
+        key_xor_into_addr<3, 3>(A.a[3][3], k[3], u3);
         uint32_t t00 = te_read<Te, 0>(A.a[0][0], base), t11 = te_read<Te, 1>(A.a[1][1], base),
                  t22 = te_read<Te, 2>(A.a[2][2], base), t33 = te_read<Te, 3>(A.a[3][3], base);
         uint32_t t10 = te_read<Te, 0>(A.a[1][0], base), t21 = te_read<Te, 1>(A.a[2][1], base),
@@ -1106,30 +1116,58 @@ __device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, Aes
     aes_rounds_lds<Te, 3, kRounds>(rk, A, u0, u1, u2, u3, G, base, o0, o1, o2, o3);
 }
 
-// ... and in a row that stands alone
+// ... and in a row that stands alone, where latency counts.  The keys wait in the lanes of a
+// register, fetched with everything else a launch starts with (in scalar registers they would be a
+// second load to wait for, 0.3 us), and one kernel serves every round count.  A wavefront being
+// alone on its SIMD, every column's lookups go out as soon as their four addresses are formed, and
+// its sum is formed while the later columns' are under way.  (As a loop over the rounds, a tenth
+// of the code, it takes 0.4 us more.)
 template <int kRounds, class Te>
-__device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, AesAddr& A,
-                                            const CtrBlock<Te>& C, GhashNone& G, uint32_t base,
-                                            uint32_t& o0, uint32_t& o1, uint32_t& o2,
-                                            uint32_t& o3) {
-    key_xor_into_addr<0, 0>(A.a[0][0], rk[0], C.iv0);
-    key_xor_into_addr<1, 1>(A.a[0][1], rk[0], C.iv0);
-    key_xor_into_addr<2, 2>(A.a[0][2], rk[0], C.iv0);
-    key_xor_into_addr<3, 3>(A.a[0][3], rk[0], C.iv0);
-    key_xor_into_addr<0, 0>(A.a[1][0], rk[1], C.iv1);
-    key_xor_into_addr<1, 1>(A.a[1][1], rk[1], C.iv1);
-    key_xor_into_addr<2, 2>(A.a[1][2], rk[1], C.iv1);
-    key_xor_into_addr<3, 3>(A.a[1][3], rk[1], C.iv1);
-    key_xor_into_addr<0, 0>(A.a[2][0], rk[2], C.iv2);
-    key_xor_into_addr<1, 1>(A.a[2][1], rk[2], C.iv2);
-    key_xor_into_addr<2, 2>(A.a[2][2], rk[2], C.iv2);
-    key_xor_into_addr<3, 3>(A.a[2][3], rk[2], C.iv2);
-    // the counter word is big endian: state byte k is counter byte 3 - k
-    key_xor_into_addr<0, 3>(A.a[3][0], rk[3], C.ctr);
-    key_xor_into_addr<1, 2>(A.a[3][1], rk[3], C.ctr);
-    key_xor_into_addr<2, 1>(A.a[3][2], rk[3], C.ctr);
-    key_xor_into_addr<3, 0>(A.a[3][3], rk[3], C.ctr);
-    aes_rounds_lds<Te, 1, kRounds>(rk, A, 0, 0, 0, 0, G, base, o0, o1, o2, o3);
+__device__ __forceinline__ void aes_ctr_lds(const LaneKeys& keys, AesAddr& A, const CtrBlock<Te>& C,
+                                            GhashNone&, uint32_t base, uint32_t& o0, uint32_t& o1,
+                                            uint32_t& o2, uint32_t& o3) {
+    static_assert(kRounds == 0, "any round count");
+    uint32_t u[4] = {C.iv0, C.iv1, C.iv2, bswap32(C.ctr)}, t[4][4];
+    auto lookups = [&](uint32_t r) __attribute__((always_inline)) {
+        uint32_t k[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) k[c] = __builtin_amdgcn_readlane(keys.word, 4 * (r - 1) + c);
+        static_for<0, 4>([&](auto col) __attribute__((always_inline)) {
+            constexpr int c = decltype(col)::value;
+            static_for<0, 4>([&](auto b) __attribute__((always_inline)) {
+                constexpr int B = decltype(b)::value, J = (c + B) & 3;
+                key_xor_into_addr<B, B>(A.a[J][B], k[J], u[J]);
+            });
+            t[c][0] = te_read<Te, 0>(A.a[c][0], base);
+            t[c][1] = te_read<Te, 1>(A.a[(c + 1) & 3][1], base);
+            t[c][2] = te_read<Te, 2>(A.a[(c + 2) & 3][2], base);
+            t[c][3] = te_read<Te, 3>(A.a[(c + 3) & 3][3], base);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    auto round = [&](uint32_t r) __attribute__((always_inline)) {
+        lookups(r);
+        static_for<0, 4>([&](auto col) __attribute__((always_inline)) {
+            constexpr int c = decltype(col)::value;
+            u[c] = xor3(t[c][0], t[c][1], t[c][2]) ^ t[c][3];
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+#pragma unroll
+    for (uint32_t r = 1; r < 10; ++r) round(r);
+    if (keys.rounds > 10) {
+        round(10), round(11);
+        if (keys.rounds > 12) round(12), round(13);
+    }
+    lookups(keys.rounds);
+    // last round, no MixColumns: S(x) is byte 1 of te[0], byte 2 of te[1], byte 0 of te[2] and te[3]
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const uint32_t lo = __builtin_amdgcn_perm(t[c][0], t[c][1], 0x0c0c0205u);
+        const uint32_t hi = __builtin_amdgcn_perm(t[c][2], t[c][3], 0x00040c0cu);
+        u[c] = xor3(lo, hi, __builtin_amdgcn_readlane(keys.word, 4 * keys.rounds + c));
+    }
+    o0 = u[0], o1 = u[1], o2 = u[2], o3 = u[3];
 }
 
 // Y * C from C's nibble table at LDS address `base`, on its own (not riding along with AES):
@@ -1169,8 +1207,9 @@ struct RowPayload {
     bool whole;
 };
 
+// Lanes before the chunk's start get the AAD's blocks, or zero blocks.
 __device__ __forceinline__ RowPayload load_row(const uint8_t* src, uint64_t len, int64_t blk,
-                                               bool edge) {
+                                               bool edge, const AadBlocks& aad) {
     RowPayload r{0, 0, 0, 0, 0, true};
     const uint8_t* sp = src + blk * 16;
     if (!edge) {
@@ -1184,7 +1223,11 @@ __device__ __forceinline__ RowPayload load_row(const uint8_t* src, uint64_t len,
             const u32x4 v = global_read128(sp);
             r.x0 = v.x, r.x1 = v.y, r.x2 = v.z, r.x3 = v.w;
         }
-        if (r.tail) {
+        if (blk < 0) {
+            const Block a = aad.at(blk);
+            r.x0 = a.w[0], r.x1 = a.w[1], r.x2 = a.w[2], r.x3 = a.w[3];
+        }
+        if (__builtin_expect(r.tail != 0, 0)) {
 #pragma unroll
             for (uint32_t b = 0; b < 15; ++b) {
                 if (b < r.tail) {
@@ -1201,19 +1244,17 @@ __device__ __forceinline__ RowPayload load_row(const uint8_t* src, uint64_t len,
 }
 
 // One row of a unit: the payload loaded by load_row is encrypted or decrypted, stored and hashed.
-// On edge rows lanes before the chunk's start touch no payload; they hash the AAD's blocks, which
-// come right before block 0, or a zero block.  The counter block of "block -1" is J0, so the idle
+// On edge rows lanes before the chunk's start store nothing; they hash what load_row gave them.  The counter block of "block -1" is J0, so the idle
 // lane there computes E_K(J0), the mask of the chunk's tag (SP 800-38D 7.1 steps 2 and 6), which
 // is handed to store_mask.
 // kThrough: the payload is written through to memory (see global_write128_through).
 // G: the row hash engine, on the matrix cores or from a table.
 // `edge` is the same in every lane and held in a scalar register (walk_unit sees to that), so
 // the rows that are no edge rows branch past all of the checks.
-template <bool kDecrypt, int kRounds, bool kThrough, class Ctr, class Hash, class StoreMask>
-__device__ __forceinline__ void bulk_row(const uint32_t* __restrict__ rk, AesAddr& A,
+template <bool kDecrypt, int kRounds, bool kThrough, class Keys, class Ctr, class Hash, class StoreMask>
+__device__ __forceinline__ void bulk_row(const Keys& rk, AesAddr& A,
                                          const Ctr& C, const RowPayload& r, uint8_t* dst,
-                                         int64_t blk, bool edge, const AadBlocks& aad,
-                                         StoreMask&& store_mask, uint32_t lds_base, Hash& G) {
+                                         int64_t blk, bool edge, StoreMask&& store_mask, uint32_t lds_base, Hash& G) {
     uint8_t* dp = dst + blk * 16;
     const uint32_t x0 = r.x0, x1 = r.x1, x2 = r.x2, x3 = r.x3, tail = r.tail;
     // the keystream block ... while the hash state moves one row along
@@ -1234,7 +1275,7 @@ __device__ __forceinline__ void bulk_row(const uint32_t* __restrict__ rk, AesAdd
     } else if (r.whole) {
         store_block();
     }
-    if (edge && tail) {
+    if (__builtin_expect(edge && tail, 0)) {
 #pragma unroll
         for (uint32_t b = 0; b < 15; ++b) {
             if (b < tail) {
@@ -1259,8 +1300,7 @@ __device__ __forceinline__ void bulk_row(const uint32_t* __restrict__ rk, AesAdd
              c3 = kDecrypt ? x3 : o3;
     if (edge && blk < 0) {
         if (blk == -1) store_mask(s0, s1, s2, s3);
-        const Block a = aad.at(blk);
-        c0 = a.w[0], c1 = a.w[1], c2 = a.w[2], c3 = a.w[3];
+        c0 = x0, c1 = x1, c2 = x2, c3 = x3;
     }
     G.absorb(c0, c1, c2, c3);
 }
@@ -1270,37 +1310,41 @@ __device__ __forceinline__ void bulk_row(const uint32_t* __restrict__ rk, AesAdd
 namespace {
 
 // Brings the bulk kernels' tables into LDS; every one of the kThreads threads calls it, and a
-// barrier must follow.  Round tables: 32 copies of every entry, lane-interleaved.  A row of the map
-// is sixteen 16-byte pieces, eight per table of its pair; every thread fetches eight of the entries
-// its pieces need at once (independent loads) and writes each four times over in one store, and
-// a wavefront's store covers four whole rows, so the stores run at the full LDS width.
-// kHash: the operands of the row hash, none, the nibble table or the matrix images.
+// barrier must follow.  kHash: the operands of the row hash, none, the nibble table or the matrix
+// images.
 enum class FillHash { kNone, kTable, kMatrix };
+// The round tables, 1024 / kThreads neighbouring entries of one table a thread, fetched in one load.
+// An entry's copies are kLanes / 4 pieces of 16 bytes; neighbouring threads have different tables
+// and start with different pieces, so that a wavefront's store covers all banks evenly.
 template <class Te, uint32_t kThreads>
-__device__ __forceinline__ void fill_te(uint32_t* te, const KeyTables* __restrict__ kt, uint32_t tid) {
-    constexpr uint32_t kPieces = Te::kBytes / 16, kPerTable = Te::kLanes / 4;
-    static_assert(kPieces % (8 * kThreads) == 0, "pieces per thread");
-    u32x4* te4 = reinterpret_cast<u32x4*>(te);
-    for (uint32_t first = tid; first < kPieces; first += 8 * kThreads) {
-        uint32_t v[8];
+struct TeFill {
+    static constexpr uint32_t kEntries = 1024 / kThreads, kPieces = Te::kLanes / 4;
+    uint32_t v[kEntries];
+
+    __device__ __forceinline__ void fetch(const KeyTables* __restrict__ kt, uint32_t tid) {
+        const uint32_t* from = kt->te[tid & 3] + kEntries * (tid >> 2);
 #pragma unroll
-        for (uint32_t k = 0; k < 8; ++k) {
-            const uint32_t g = first + k * kThreads;  // piece number
-            const uint32_t pair = Te::kPairs ? g >> 12 : 0, row = (g >> 4) & 255,
-                           t = 2 * pair + (g & 15) / kPerTable;
-            v[k] = kt->te[t][row];
-        }
+        for (uint32_t e = 0; e < kEntries; ++e) v[e] = from[e];
+    }
+    __device__ __forceinline__ void store(uint32_t* te, uint32_t tid) const {
+        const uint32_t t = tid & 3, i = tid >> 2;
+        u32x4* te4 = reinterpret_cast<u32x4*>(te);
+        const uint32_t table = Te::kPairs ? (t >> 1) * (Te::kPairs / 16) + (t & 1) * kPieces : t * kPieces;
 #pragma unroll
-        for (uint32_t k = 0; k < 8; ++k) {
-            const u32x4 q = {v[k], v[k], v[k], v[k]};
-            te4[first + k * kThreads] = q;
+        for (uint32_t e = 0; e < kEntries; ++e) {
+            const u32x4 q = {v[e], v[e], v[e], v[e]};
+#pragma unroll
+            for (uint32_t k = 0; k < kPieces; ++k)
+                te4[table + (kEntries * i + e) * 16 + ((k + i) & (kPieces - 1))] = q;
         }
     }
-}
+};
 template <FillHash kHash, uint32_t kThreads>
 __device__ __forceinline__ void fill_bulk_lds(BulkLds& lds, const KeyTables* __restrict__ kt,
                                               uint32_t tid) {
-    fill_te<TeWide, kThreads>(lds.te, kt, tid);
+    TeFill<TeWide, kThreads> te;
+    te.fetch(kt, tid);
+    te.store(lds.te, tid);
     if constexpr (kHash != FillHash::kNone) {
         constexpr bool kMatrix = kHash == FillHash::kMatrix;
         const Block* from = kMatrix ? reinterpret_cast<const Block*>(kt->hash_image) : kt->ghash[kRowPower];
@@ -1335,8 +1379,8 @@ __device__ __forceinline__ void walk_unit(const uint32_t* __restrict__ rk, AesAd
         const uint32_t end = left <= kSegmentRows + 1 ? nrows : r + kSegmentRows;
         for (; r < end; ++r, row_blk += kRowBlocks, C.rel += kRowBlocks) {
             const bool edge = row_blk < 0 || (last && r + 1 == nrows);
-            const RowPayload p = load_row(src, len, row_blk + lane, edge);
-            bulk_row<kDecrypt, kRounds, kThrough>(rk, A, C, p, dst, row_blk + lane, edge, aad,
+            const RowPayload p = load_row(src, len, row_blk + lane, edge, aad);
+            bulk_row<kDecrypt, kRounds, kThrough>(rk, A, C, p, dst, row_blk + lane, edge,
                                                   store_mask, lds_base, G);
         }
     }
@@ -1806,7 +1850,7 @@ template __global__ void final_kernel<true>(const KeyTables*, const ChunkDesc*, 
 //      the powers themselves (KeyTables::dot), eight to thirty-two bits of a lane each, and add
 //      them up: no further tables, and one step where a tree over the lanes takes six;
 //   3. one wavefront multiplies the sum by the power of H that takes it to the chunk's end
-//      (KeyTables::hop).  The workgroup with "block -1" adds the length block and E_K(J0), so
+//      (KeyTables::hop), unless it is there.  The workgroup with "block -1" adds the length block and E_K(J0), so
 //      that a chunk's tag is plainly the sum of its workgroups' results;
 //   4. a chunk of one workgroup is finished there and then.  Otherwise the result is written
 //      through to memory (device-scope stores, no cache-wide fence), waited for, and the
@@ -1833,16 +1877,18 @@ __device__ __forceinline__ uint32_t row_summed(uint32_t v) {
     return v;
 }
 
-// acc * x + (top bit first: bit 7 - i of `byte` at step i ? q : 0), for all eight bits
+// sum over the slices s of (the eight coefficients of byte[s]) * q[s], by Horner's rule; the byte's
+// top bit is its first coefficient
 template <int kSlices>
-__device__ __forceinline__ GfWords bits_times(const uint32_t byte[kSlices], const GfWords q[kSlices]) {
+__device__ __forceinline__ GfWords bits_times(uint32_t byte[kSlices], const GfWords q[kSlices]) {
     GfWords acc{{0, 0, 0, 0}};
 #pragma unroll
-    for (int bit = 0; bit < 8; ++bit) {  // the byte's lowest bit is its highest coefficient
+    for (int bit = 0; bit < 8; ++bit) {
         if (bit != 0) gfw_mul_x(acc);
 #pragma unroll
         for (int s = 0; s < kSlices; ++s) {
-            const uint32_t m = (uint32_t)((int32_t)(byte[s] << (31 - bit)) >> 31);
+            const uint32_t m = 0u - (byte[s] & 1u);
+            byte[s] >>= 1;
 #pragma unroll
             for (int k = 0; k < 4; ++k) acc.a[k] ^= q[s].a[k] & m;
         }
@@ -1896,39 +1942,68 @@ struct NarrowLds {
 
 template <bool kDecrypt, int kRounds, SwapKind kKind>
 __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
-    const KeyTables* __restrict__ kt, const ArgBatch batch, const GroupDesc* __restrict__ staged,
-    const uint8_t* __restrict__ ivs, uint32_t iv_len, Block* __restrict__ slots,
-    uint32_t* __restrict__ arrive, uint8_t* __restrict__ tags, uint8_t* __restrict__ ok) {
+    const KeyTables* __restrict__ kt, const uint8_t* __restrict__ ivs, uint32_t iv_len,
+    SwapMeta meta, uint8_t* __restrict__ work, uint8_t* __restrict__ tags,
+    uint8_t* __restrict__ ok, const GroupDesc* __restrict__ staged, const ArgBatch batch) {
     constexpr bool kNarrow = kKind == SwapKind::kNarrow, single = kKind != SwapKind::kUnits;
     using Te = std::conditional_t<kNarrow, TeNarrow, TeWide>;
     __shared__ std::conditional_t<kNarrow, NarrowLds, BulkLds> lds;
     __shared__ Block mask_lds;                   // E_K(J0), where a wavefront with units makes it
     __shared__ GfWords shares[kWavesPerGroup];
+    uint32_t* const arrive = reinterpret_cast<uint32_t*>(work);
+    Block* const slots = reinterpret_cast<Block*>(work + kSwapArriveBytes);
     const uint32_t lds_base = lds_offset(&lds);
     const uint32_t tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t wave_power = batch.wave_power, nwaves = 1u << wave_power;
-    const uint32_t p = single ? kRowPower : batch.unit_power;
+    const uint32_t wave_power = meta.wave_power(), nwaves = 1u << wave_power;
+    const uint32_t p = single ? kRowPower : meta.unit_power();
     // The wavefront that finishes the workgroup's part: one beyond those with units, or, where a
     // workgroup can have no more, the last of them, which the tree leaves idle.
     const bool beyond = wave_power < 4;
     const bool finisher = wave == (beyond ? nwaves : nwaves - 1);
     const bool worker = wave < nwaves;
 
-    // this workgroup's chunk: the last one whose first workgroup is not behind it
+    // Everything the workgroup needs from memory is asked for as early as it can be: a launch starts
+    // with cold caches, and every further round of dependent loads costs it a microsecond (the
+    // arguments that do not come in registers are a load from host memory themselves).
+    TeFill<Te, 256> te4;
+    TeFill<Te, 512> te2;
+    TeFill<Te, 1024> te1;
+    if (worker) {
+        if (wave_power == 2) te4.fetch(kt, tid);
+        else if (wave_power == 3) te2.fetch(kt, tid);
+        else te1.fetch(kt, tid);
+    }
+    const LaneKeys lane_keys{lane < 60 ? kt->rk[lane] : 0u, meta.rounds()};
+
+    // this workgroup's chunk: the last one whose first workgroup is not behind it.  Of the chunks of
+    // the caller's arrays in order, one or a workgroup each, it is known before any argument is
+    // loaded, and so is the place of the IV.
+    const bool alone = meta.nchunks() == 1, each = meta.one_group_each();
+    const bool iv_known = staged == nullptr && meta.in_order() && (alone || each);
+    Block j{{0, 0, 0, 0}};
+    if (iv_known) j = j0_from_iv(kt, ivs + (uint64_t)(alone ? 0 : blockIdx.x) * iv_len, iv_len);
     ArgChunk cd;
     uint32_t group_base, ngroups;
     if (staged != nullptr) {
         const GroupDesc d = staged[blockIdx.x];
         cd = d.c, group_base = d.group_base, ngroups = d.ngroups;
     } else {
-        const uint32_t first = lane < batch.nchunks ? batch.group_base[lane] : ~0u;
-        const uint32_t chunk = __builtin_amdgcn_readfirstlane(
-            (uint32_t)__popcll(__ballot(first <= blockIdx.x)) - 1u);
+        uint32_t chunk = 0;
+        if (alone) {
+            group_base = 0, ngroups = meta.groups();
+        } else if (each) {
+            chunk = group_base = blockIdx.x, ngroups = 1;
+        } else {
+            const uint32_t first = lane < meta.nchunks() ? batch.group_base[lane] : ~0u;
+            chunk = __builtin_amdgcn_readfirstlane(
+                (uint32_t)__popcll(__ballot(first <= blockIdx.x)) - 1u);
+            group_base = batch.group_base[chunk];
+            ngroups = batch.group_base[chunk + 1] - group_base;
+        }
         cd = batch.c[chunk];
-        group_base = batch.group_base[chunk];
-        ngroups = batch.group_base[chunk + 1] - group_base;
     }
+    if (!iv_known) j = j0_from_iv(kt, ivs + (uint64_t)cd.index * iv_len, iv_len);
     const uint32_t g = blockIdx.x - group_base;
     // its units, counted back from the chunk's end; a negative number is a wavefront without one
     const int64_t nblk = (int64_t)((cd.len + 15) / 16);
@@ -1944,19 +2019,26 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
     const bool has_mask = beyond ? g == 0
                                  : end >= 0 && end - ((int64_t)1 << (p + wave_power)) < 0;
 
-    uint32_t rk[4 * (kRounds + 1)];
+    u32x4 gh[2];
+    if constexpr (!single) {
+        if (worker)
 #pragma unroll
-    for (int i = 0; i < 4 * (kRounds + 1); ++i) rk[i] = kt->rk[i];
-    const Block j = j0_from_iv(kt, ivs + (uint64_t)cd.index * iv_len, iv_len);
-    if (worker) {
-        if (wave_power == 2) fill_te<Te, 256>(lds.te, kt, tid);
-        else if (wave_power == 3) fill_te<Te, 512>(lds.te, kt, tid);
-        else if (!kNarrow || tid < 512) fill_te<Te, kNarrow ? 512 : 1024>(lds.te, kt, tid);
-        if constexpr (!single) {
-            for (uint32_t i = tid; i < kNibbleTableEntries; i += 64u << wave_power)
-                lds.gh[i] = kt->ghash[kRowPower][i];
-        }
+            for (uint32_t k = 0; k < 2; ++k)
+                if (tid + (k << (6 + wave_power)) < kNibbleTableEntries)
+                    gh[k] = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower])[tid + (k << (6 + wave_power))];
     }
+    auto store_tables = [&]() __attribute__((always_inline)) {
+        if (!worker) return;
+        if (wave_power == 2) te4.store(lds.te, tid);
+        else if (wave_power == 3) te2.store(lds.te, tid);
+        else te1.store(lds.te, tid);
+        if constexpr (!single) {
+#pragma unroll
+            for (uint32_t k = 0; k < 2; ++k)
+                if (tid + (k << (6 + wave_power)) < kNibbleTableEntries)
+                    reinterpret_cast<u32x4*>(lds.gh)[tid + (k << (6 + wave_power))] = gh[k];
+        }
+    };
 
     // tree tables and powers of H: entry k * threads + tid of the 512 * wave_power, slices
     // 16 / nwaves * wave .. of lane's
@@ -1979,56 +2061,20 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
                 if (s < slices) q[s] = kt->dot[lane][slices * wave + s];
         }
         if (finisher) {
-            hop = kt->hop[p + wave_power - kHopMinPower][ngroups - 1 - g];
+            if (ngroups - 1 != g) hop = kt->hop[p + wave_power - kHopMinPower][ngroups - 1 - g];
             if (has_mask) extra = length_block_entry(kt->ghash[0], cd.aad_len, cd.len, lane);
             if (kDecrypt) received = global_read_block_any(tag_at);
         }
     };
 
-    AadBlocks aad = aad_blocks(cd.aad, worker ? cd.aad_len : 0);
-    auto keep_mask = [&](uint32_t s0, uint32_t s1, uint32_t s2, uint32_t s3)
-        __attribute__((always_inline)) { mask_lds = Block{{s0, s1, s2, s3}}; };
-    uint32_t y[4] = {0, 0, 0, 0};
-    const bool at_start = unit == 0 && cd.aad_len != 0;
-    // one row of 64 blocks up to b1, or J0 in every lane of the wavefront beyond
-    const int64_t blk = worker ? b1 - kRowBlocks + lane : -1;
-    if (single || !worker) {
-        const bool edge = !worker || b1 < kRowBlocks || b1 == nblk;
-        RowPayload row{0, 0, 0, 0, 0, false};
-        if (unit >= 0) row = load_row(cd.src, cd.len, blk, edge);
-        fetch_ahead();
-        __syncthreads();  // the tables are in place
-        if (unit >= 0 || (!worker && has_mask)) {
-            if (at_start) aad.prepare(kt->ghash[0]);
-            AesAddr A;
-            aes_addr_init<Te>(A, lane, rk + 4 * kRounds);
-            GhashNone G;
-            const CtrBlock<Te> C{j.w[0], j.w[1], j.w[2], (uint32_t)blk + bswap32(j.w[3]) + 1u};
-            bulk_row<kDecrypt, kRounds, kDecrypt>(rk, A, C, row, cd.dst, blk, edge, aad, keep_mask,
-                                                  lds_base, G);
-            for (int k = 0; k < 4; ++k) y[k] = G.w[k];
-        }
-    }
-    if constexpr (!single) {
-        if (worker) {
-            __syncthreads();
-            if (unit >= 0) {
-                if (at_start) aad.prepare(kt->ghash[0]);
-                AesAddr A;
-                aes_addr_init<Te>(A, lane, rk + 4 * kRounds);
-                walk_unit<kDecrypt, kRounds, kDecrypt, false>(rk, A, lane, wave, lds_base, cd.src,
-                                                              cd.dst, cd.len, b0, b1, b1 == nblk,
-                                                              aad, j, keep_mask, y);
-            }
-            fetch_ahead();
-        }
-    }
-    if (finisher) {
-        // what the finish takes, while the others still walk (or fold)
+    // by the finisher, from what fetch_ahead brought
+    auto prepare_finish = [&]() __attribute__((always_inline)) {
+        if (!finisher) return;
         if (has_mask) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) extra.w[k] = rows_summed(row_summed(extra.w[k]));
         }
+        if (ngroups - 1 == g) return;  // this workgroup's part ends with the chunk
         GfWords t = hop;
         gfw_mul_x8(t);
         if (lane & 1) hop = t;
@@ -2041,12 +2087,63 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
         t = hop;
         gfw_mul_x32(t), gfw_mul_x32(t);
         if (lane & 8) hop = t;
+    };
+
+    AadBlocks aad = aad_blocks(cd.aad, worker ? cd.aad_len : 0);
+    auto keep_mask = [&](uint32_t s0, uint32_t s1, uint32_t s2, uint32_t s3)
+        __attribute__((always_inline)) { mask_lds = Block{{s0, s1, s2, s3}}; };
+    uint32_t y[4] = {0, 0, 0, 0};
+    const bool at_start = unit == 0 && cd.aad_len != 0;
+    // one row of 64 blocks up to b1, or J0 in every lane of the wavefront beyond
+    const int64_t blk = worker ? b1 - kRowBlocks + lane : -1;
+    if (single || !worker) {
+        const bool edge = !worker || b1 < kRowBlocks || b1 == nblk;
+        RowPayload row{0, 0, 0, 0, 0, false};
+        if (at_start) aad.prepare(kt->ghash[0]);
+        if (unit >= 0) row = load_row(cd.src, cd.len, blk, edge, aad);
+        fetch_ahead();
+        store_tables();
+        if (beyond) prepare_finish();
+        __syncthreads();  // the tables are in place
+        if (unit >= 0 || (!worker && has_mask)) {
+            AesAddr A;
+            aes_addr_init<Te>(A, lane);
+            GhashNone G;
+            const CtrBlock<Te> C{j.w[0], j.w[1], j.w[2], (uint32_t)blk + bswap32(j.w[3]) + 1u};
+            bulk_row<kDecrypt, 0, kDecrypt>(lane_keys, A, C, row, cd.dst, blk, edge, keep_mask,
+                                                  lds_base, G);
+            for (int k = 0; k < 4; ++k) y[k] = G.w[k];
+        }
     }
+    if constexpr (!single) {
+        if (worker) {
+            store_tables();
+            __syncthreads();
+            if (unit >= 0) {
+                if (at_start) aad.prepare(kt->ghash[0]);
+                uint32_t rk[4 * (kRounds + 1)];
+#pragma unroll
+                for (int i = 0; i < 4 * (kRounds + 1); ++i)
+                    rk[i] = __builtin_amdgcn_readlane(lane_keys.word, i);
+                AesAddr A;
+                aes_addr_init<Te>(A, lane, rk + 4 * kRounds);
+                walk_unit<kDecrypt, kRounds, kDecrypt, false>(rk, A, lane, wave, lds_base, cd.src,
+                                                              cd.dst, cd.len, b0, b1, b1 == nblk,
+                                                              aad, j, keep_mask, y);
+            }
+            fetch_ahead();
+        }
+    }
+    if (!beyond) prepare_finish();
     __syncthreads();  // the round tables are done with: their LDS now takes the tree's
 
     Block(*tables)[kNibbleTableEntries] = reinterpret_cast<Block(*)[kNibbleTableEntries]>(&lds);
     Block(*sets[2])[64] = {reinterpret_cast<Block(*)[64]>(tables[4]),
                            reinterpret_cast<Block(*)[64]>(tables[6])};
+    const uint32_t here = (uint32_t)nunits >= (ngroups - g) << wave_power
+                              ? nwaves : (uint32_t)nunits - ((ngroups - g - 1) << wave_power);
+    uint32_t levels = 0;
+    while ((1u << levels) < here) ++levels;
     if (worker) {
         u32x4* to = reinterpret_cast<u32x4*>(tables);
         const uint32_t per_thread = (8 * wave_power) >> wave_power;
@@ -2057,8 +2154,9 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
     }
     __syncthreads();
 
-    // 1. every wavefront passes every barrier; only the shrinking front half has work to do
-    for (uint32_t level = 0; level < wave_power; ++level) {
+    // 1. every wavefront passes every barrier; only the shrinking front half has work to do.  The
+    // units at hand are the last of the workgroup's leaves: the tree goes as far up as they reach.
+    for (uint32_t level = 0; level < levels; ++level) {
         if (wave < (nwaves >> (level + 1))) {
             const Block a = sets[level & 1][2 * wave][lane], b = sets[level & 1][2 * wave + 1][lane];
             y[0] = a.w[0], y[1] = a.w[1], y[2] = a.w[2], y[3] = a.w[3];
@@ -2070,7 +2168,7 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
     }
     // 2.
     if (worker) {
-        const Block set = sets[wave_power & 1][0][lane];
+        const Block set = sets[levels & 1][(nwaves >> levels) - 1][lane];
         const GfWords share = wave_power == 2   ? dot_share<4>(set, wave, q)
                               : wave_power == 3 ? dot_share<2>(set, wave, q)
                                                 : dot_share<1>(set, wave, q);
@@ -2087,10 +2185,10 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
     if (lane < nwaves) sum = shares[lane];
 #pragma unroll
     for (int k = 0; k < 4; ++k) sum.a[k] = __builtin_amdgcn_readfirstlane(row_summed(sum.a[k]));
-    {
+    if (ngroups - 1 != g) {
         const uint32_t w = (lane / 4) % 4;
         const uint32_t word = w == 0 ? sum.a[0] : w == 1 ? sum.a[1] : w == 2 ? sum.a[2] : sum.a[3];
-        const uint32_t byte[1] = {word >> (24 - 8 * (lane % 4))};
+        uint32_t byte[1] = {word >> (24 - 8 * (lane % 4))};
         sum = bits_times<1>(byte, &hop);
 #pragma unroll
         for (int k = 0; k < 4; ++k) sum.a[k] = row_summed(sum.a[k]);
@@ -2139,22 +2237,18 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
     write_or_compare_tag<kDecrypt>(tag, tag_at, received, ok + cd.index, cd.dst, cd.len, lane);
 }
 
-#define PGCM_INSTANTIATE_SWAP(D, R)                                                          \
-    template __global__ void swap_kernel<D, R, SwapKind::kNarrow>(                                  \
-        const KeyTables*, ArgBatch, const GroupDesc*, const uint8_t*, uint32_t, Block*, uint32_t*, \
-        uint8_t*, uint8_t*);                                                                       \
-    template __global__ void swap_kernel<D, R, SwapKind::kRows>(                                    \
-        const KeyTables*, ArgBatch, const GroupDesc*, const uint8_t*, uint32_t, Block*, uint32_t*, \
-        uint8_t*, uint8_t*);                                                                       \
-    template __global__ void swap_kernel<D, R, SwapKind::kUnits>(                                   \
-        const KeyTables*, ArgBatch, const GroupDesc*, const uint8_t*, uint32_t, Block*, uint32_t*, \
-        uint8_t*, uint8_t*)
-PGCM_INSTANTIATE_SWAP(false, 10);
-PGCM_INSTANTIATE_SWAP(false, 12);
-PGCM_INSTANTIATE_SWAP(false, 14);
-PGCM_INSTANTIATE_SWAP(true, 10);
-PGCM_INSTANTIATE_SWAP(true, 12);
-PGCM_INSTANTIATE_SWAP(true, 14);
+#define PGCM_SWAP_SIGNATURE                                                                    \
+    (const KeyTables*, const uint8_t*, uint32_t, SwapMeta, uint8_t*, uint8_t*, uint8_t*,           \
+     const GroupDesc*, ArgBatch)
+#define PGCM_INSTANTIATE_SWAP(D)                                                               \
+    template __global__ void swap_kernel<D, 0, SwapKind::kNarrow> PGCM_SWAP_SIGNATURE;             \
+    template __global__ void swap_kernel<D, 0, SwapKind::kRows> PGCM_SWAP_SIGNATURE;               \
+    template __global__ void swap_kernel<D, 10, SwapKind::kUnits> PGCM_SWAP_SIGNATURE;             \
+    template __global__ void swap_kernel<D, 12, SwapKind::kUnits> PGCM_SWAP_SIGNATURE;             \
+    template __global__ void swap_kernel<D, 14, SwapKind::kUnits> PGCM_SWAP_SIGNATURE
+PGCM_INSTANTIATE_SWAP(false);
+PGCM_INSTANTIATE_SWAP(true);
+#undef PGCM_SWAP_SIGNATURE
 #undef PGCM_INSTANTIATE_SWAP
 
 __global__ __launch_bounds__(1024) void clear_words_kernel(uint32_t* __restrict__ words, uint32_t n) {

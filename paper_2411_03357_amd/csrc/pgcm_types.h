@@ -58,7 +58,8 @@ constexpr uint32_t kNumLanePowers = 3;
 // The latency path sums a set's 64 lanes as 64 products of a sum with a known power of H, all
 // at once and bit by bit, and moves a workgroup's result to its place with one more such product:
 // it needs powers of H as plain values, held as four words with coefficient x^0 in the top bit of
-// the first (GfWords).  dot[l][t] = H^(64 - l) * x^(8 t);  hop[d][k] = H^(k 2^(8 + d) + 1).
+// the first (GfWords).  dot[l][t] = H^(65 - l) * x^(8 t), the multiplication by H that follows the
+// length block included;  hop[d][k] = H^(k 2^(8 + d)).
 constexpr uint32_t kDotSlices = 16;
 constexpr uint32_t kHopMinPower = 8;    // the shortest stretch of a workgroup: 4 units of 64 blocks
 constexpr uint32_t kHopPowers = 7;      // ... and the longest: 16 units of 1024 blocks
@@ -149,9 +150,6 @@ struct ArgChunk {
 };
 static_assert(sizeof(ArgChunk) == 40, "argument layout");
 struct ArgBatch {
-    uint32_t nchunks;
-    uint32_t unit_power;
-    uint32_t wave_power;                  // log2 of the wavefronts per workgroup: 2, 3, 4
     uint32_t group_base[kArgChunks + 1];  // first workgroup of every chunk; their number
     ArgChunk c[kArgChunks];
 };
@@ -162,6 +160,31 @@ constexpr uint32_t kSwapMaxGroups = 512;
 // of many are counted in sixteens first, on the words of every sixteenth in the upper half.
 constexpr uint32_t kArriveStride = 16;
 constexpr uint32_t kSwapArriveWords = 2 * kSwapMaxGroups * kArriveStride;
+constexpr uint32_t kSwapArriveBytes = 4 * kSwapArriveWords;
+// What a workgroup has to know first, in one word: it travels in a register.
+struct SwapMeta {
+    uint32_t w;
+#ifdef __HIPCC__
+#define PGCM_BOTH __host__ __device__
+#else
+#define PGCM_BOTH
+#endif
+    PGCM_BOTH uint32_t nchunks() const { return w & 0x7Fu; }          // in the arguments: 0 .. 64
+    PGCM_BOTH uint32_t unit_power() const { return (w >> 7) & 0x1Fu; }
+    PGCM_BOTH uint32_t wave_power() const { return (w >> 12) & 7u; }  // log2 of the wavefronts per
+                                                                      // workgroup: 2, 3, 4
+    PGCM_BOTH bool one_group_each() const { return (w >> 15) & 1u; }  // every chunk has a workgroup
+    PGCM_BOTH bool in_order() const { return (w >> 16) & 1u; }        // chunk k is the caller's k
+    PGCM_BOTH uint32_t groups() const { return (w >> 17) & 0x3FFu; }  // workgroups of the launch
+    PGCM_BOTH uint32_t rounds() const { return w >> 27; }
+#undef PGCM_BOTH
+};
+constexpr SwapMeta swap_meta(uint32_t nchunks, uint32_t unit_power, uint32_t wave_power,
+                             bool one_group_each, bool in_order, uint32_t groups,
+                             uint32_t rounds) {
+    return SwapMeta{nchunks | unit_power << 7 | wave_power << 12 | (uint32_t)one_group_each << 15 |
+                    (uint32_t)in_order << 16 | groups << 17 | rounds << 27};
+}
 // Batches of more chunks than fit the arguments have a descriptor per workgroup in pinned memory.
 struct alignas(16) GroupDesc {
     ArgChunk c;
