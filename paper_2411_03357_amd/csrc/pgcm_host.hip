@@ -44,6 +44,7 @@ constexpr int kMaxDevices = 64;
 // a fold level with at most this many items (one workgroup each fits the chip at once) is folded
 // by the tree kernel
 constexpr uint32_t kFoldTreeMaxItems = 256;
+constexpr uint64_t kSpanMaxRows = 1u << 27;
 
 // Per-chunk schedule: units are counted back from the chunk's end, so that every unit but the
 // first is full and all row boundaries line up with the end of the chunk.
@@ -836,7 +837,7 @@ int run_unit_batch(pgcm_key* key, Context* ctx, const BatchArgs& a, const BatchP
         hipLaunchKernelGGL(upload_kernel, dim3(groups), dim3(256), 0, a.stream,
                            reinterpret_cast<uint4*>(ctx->work),
                            reinterpret_cast<const uint4*>(ctx->stage[s]), n16,
-                           clear ? d_counter : (uint32_t*)nullptr);
+                           reinterpret_cast<uint4*>(d_counter), clear ? 1u : 0u);
     }
 
     const KeyTables* kt = key->tables;
@@ -896,6 +897,188 @@ int run_unit_batch(pgcm_key* key, Context* ctx, const BatchArgs& a, const BatchP
     return PGCM_OK;
 }
 
+// ---- Spans (span_kernel) ----
+
+// One key's chunks of a batch: n of them from the batch's chunk `first` on.
+struct KeyPart {
+    pgcm_key* key;
+    size_t first, n;
+    uint64_t rows;
+    uint32_t groups;  // workgroups
+
+    // what the rows cost, in rows: finishing a piece takes about as long as one
+    uint64_t weight() const { return rows + n; }
+};
+
+inline uint64_t span_rows(const BatchArgs& a, size_t i) {
+    const uint64_t blocks = (a.len[i] + 15) / 16 + lead_blocks(a.aad_len ? a.aad_len[i] : 0);
+    return (blocks + kRowBlocks - 1) / kRowBlocks;
+}
+
+// Counts the rows of every part.  False if the batch is not one for spans.
+bool count_span_rows(const BatchArgs& a, KeyPart* parts, size_t nparts) {
+    uint64_t total = 0;
+    for (size_t q = 0; q < nparts; ++q) {
+        const pgcm_key* key = parts[q].key;
+        if (!key->one_launch || key->matrix_hash || key->forced_unit_power) return false;
+        parts[q].rows = 0;
+        for (size_t k = parts[q].first; k < parts[q].first + parts[q].n; ++k) {
+            const uint64_t rows = span_rows(a, a.at(k));
+            if (rows > (uint64_t)kRowHopEntries * kFarHopEntries) return false;
+            parts[q].rows += rows;
+        }
+        total += parts[q].rows;
+    }
+    return total <= kSpanMaxRows;
+}
+
+// Deals the compute units out to the parts, a workgroup each, so that the one with the most work per
+// workgroup has as little as can be: a row costs a table lookup per round and byte and the hash as
+// much as three rounds.  Every wavefront of a workgroup gets a row at least, if there are that
+// many.  Returns the number of workgroups.
+uint32_t deal_groups(KeyPart* parts, size_t nparts, uint32_t num_cu) {
+    uint64_t work = 0;
+    auto cost = [](const KeyPart& p) { return p.weight() * (uint64_t)(p.key->rounds + 3); };
+    auto most = [](const KeyPart& p) { return p.rows < kWavesPerGroup ? 1 : p.rows / kWavesPerGroup; };
+    for (size_t q = 0; q < nparts; ++q) work += cost(parts[q]);
+    uint32_t total = 0;
+    for (size_t q = 0; q < nparts; ++q) {
+        uint64_t g = cost(parts[q]) * num_cu / work;
+        if (g > most(parts[q])) g = most(parts[q]);
+        parts[q].groups = g == 0 ? 1 : (uint32_t)g;
+        total += parts[q].groups;
+    }
+    while (total < num_cu) {
+        KeyPart* worst = nullptr;
+        for (size_t q = 0; q < nparts; ++q) {
+            KeyPart& p = parts[q];
+            if (p.groups < most(p) &&
+                (worst == nullptr || cost(p) * worst->groups > cost(*worst) * p.groups))
+                worst = &p;
+        }
+        if (worst == nullptr) break;
+        ++worst->groups, ++total;
+    }
+    return total;
+}
+
+struct SpanLayout {
+    size_t groups, row_base, chunks, upload_bytes, slots, bytes;
+};
+SpanLayout lay_out_spans(size_t n, size_t groups) {
+    SpanLayout w;
+    w.groups = 0;
+    w.row_base = round_up(sizeof(SpanGroup) * groups, 256);
+    w.chunks = round_up(w.row_base + sizeof(uint32_t) * n, 256);
+    w.upload_bytes = round_up(w.chunks + sizeof(SpanChunk) * n, 256);
+    w.slots = w.upload_bytes;
+    w.bytes = w.slots + sizeof(SpanSlot) * (groups * kWavesPerGroup + n);
+    return w;
+}
+
+void fill_spans(const BatchArgs& a, const KeyPart* parts, size_t nparts, const SpanLayout& w,
+                uint8_t* stage) {
+    SpanGroup* const groups = reinterpret_cast<SpanGroup*>(stage + w.groups);
+    uint32_t* const row_base = reinterpret_cast<uint32_t*>(stage + w.row_base);
+    SpanChunk* const chunks = reinterpret_cast<SpanChunk*>(stage + w.chunks);
+    uint32_t row = 0, group = 0, wave = 0;
+    for (size_t q = 0; q < nparts; ++q) {
+        const KeyPart& part = parts[q];
+        const uint32_t first_group = group;
+        // a workgroup begins where the weight so far reaches its share; a chunk's own comes before
+        // its rows'
+        uint64_t weight = 0, next = 0;
+        for (size_t k = part.first; k < part.first + part.n; ++k) {
+            const size_t i = a.at(k);
+            SpanChunk& c = chunks[k];
+            c.src = (const uint8_t*)a.src[i];
+            c.dst = (uint8_t*)a.dst[i];
+            c.len = a.len[i];
+            c.aad_len = a.aad_len ? a.aad_len[i] : 0;
+            c.aad = c.aad_len ? (const uint8_t*)a.aad[i] : nullptr;
+            c.index = (uint32_t)i;
+            c.first_row = row_base[k] = row;
+            c.rows = (uint32_t)span_rows(a, i);
+            c.pad_[0] = c.pad_[1] = 0;
+            while (group < first_group + part.groups && next < weight + c.rows + 1) {
+                const uint32_t at = next > weight ? row + (uint32_t)(next - weight) - 1 : row;
+                groups[group++] = SpanGroup{part.key->tables, at, 0, (uint32_t)k, 0, 0, 0};
+                next = part.weight() * (group - first_group) / part.groups;
+            }
+            row += c.rows;
+            weight += c.rows + 1;
+        }
+        for (uint32_t g = first_group; g < group; ++g) {
+            const bool more = g + 1 < group;
+            groups[g].rows = (more ? groups[g + 1].first_row : row) - groups[g].first_row;
+            groups[g].nchunks = (more ? groups[g + 1].chunk + 1 : (uint32_t)(part.first + part.n)) -
+                                groups[g].chunk;
+            groups[g].first_wave = wave;
+            wave += groups[g].rows < kWavesPerGroup ? groups[g].rows : kWavesPerGroup;
+        }
+        // the wavefront of row r, in the workgroup `at` or a later one of the part
+        auto wave_of = [&](uint32_t r, uint32_t& at) {
+            while (r >= groups[at].first_row + groups[at].rows) ++at;
+            const SpanGroup& g = groups[at];
+            const uint32_t waves = g.rows < kWavesPerGroup ? g.rows : kWavesPerGroup;
+            return g.first_wave + ((r - g.first_row + 1) * waves - 1) / g.rows;
+        };
+        uint32_t at = first_group;
+        for (size_t k = part.first; k < part.first + part.n; ++k) {
+            SpanChunk& c = chunks[k];
+            const uint32_t first = wave_of(c.first_row, at);
+            c.slot = first + (uint32_t)k;
+            c.pieces = wave_of(c.first_row + c.rows - 1, at) - first + 1;
+        }
+    }
+}
+
+// One batch in spans, of one key or of several: the context is that of the first.
+int run_span_batch(Context* ctx, const BatchArgs& a, const KeyPart* parts, size_t nparts,
+                   uint32_t ngroups) {
+    const SpanLayout w = lay_out_spans(a.n, ngroups);
+    const int s = ctx->next_stage;
+    int rc = ensure_stage(ctx, s, w.upload_bytes);
+    if (rc != PGCM_OK) return rc;
+    rc = ensure_work(ctx, w.bytes, a.stream);
+    if (rc != PGCM_OK) return rc;
+    fill_spans(a, parts, nparts, w, ctx->stage[s]);
+    // the places where the other paths have their counters
+    ctx->arrive_clean = false;
+    ctx->counter_at = nullptr;
+    const uint32_t n16 = (uint32_t)(w.upload_bytes / 16), n_clear = (uint32_t)((w.bytes - w.slots) / 16);
+    uint32_t groups = ((n16 > n_clear ? n16 : n_clear) + 255) / 256;
+    if (groups > 1024) groups = 1024;
+    hipLaunchKernelGGL(upload_kernel, dim3(groups), dim3(256), 0, a.stream,
+                       reinterpret_cast<uint4*>(ctx->work),
+                       reinterpret_cast<const uint4*>(ctx->stage[s]), n16,
+                       reinterpret_cast<uint4*>(ctx->work + w.slots), n_clear);
+    int rc_timing = PGCM_OK;
+    for (size_t q = 0; q < nparts && rc_timing == PGCM_OK; ++q)
+        rc_timing = record_timing_start(parts[q].key, a.stream);
+    launch_last(a.decrypt ? span_kernel<true> : span_kernel<false>, dim3(ngroups),
+                dim3(kGroupThreads), a.stream, a.capturing, ctx->stage_done[s],
+                (const KeyTables*)(nparts == 1 ? parts[0].key->tables : nullptr),
+                (const SpanGroup*)(ctx->work + w.groups), (const uint32_t*)(ctx->work + w.row_base),
+                (const SpanChunk*)(ctx->work + w.chunks), (SpanSlot*)(ctx->work + w.slots), a.ivs,
+                a.tags, a.ok, a.iv_len);
+    for (size_t q = 0; q < nparts && rc_timing == PGCM_OK; ++q)
+        rc_timing = record_timing_stop(parts[q].key, a.stream);
+    const int rc_end = end_of_batch(ctx, s, a.stream, a.capturing);
+    if (rc_timing != PGCM_OK) return rc_timing;
+    PGCM_HIP(hipGetLastError());
+    return rc_end;
+}
+
+int note_capture(BatchArgs& a) {
+    if (a.stream != nullptr) {
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        PGCM_HIP(hipStreamIsCapturing(a.stream, &status));
+        a.capturing = status == hipStreamCaptureStatusActive;
+    }
+    return PGCM_OK;
+}
+
 // One batch under one key: validate everything, pick a context, then enqueue upload, J0 (if
 // needed), bulk, fold levels and final kernels on the stream.
 int run_batch(pgcm_key* key, BatchArgs a) {
@@ -908,11 +1091,8 @@ int run_batch(pgcm_key* key, BatchArgs a) {
     int cur_device = -1;
     PGCM_HIP(hipGetDevice(&cur_device));
     if (cur_device != key->device) return PGCM_ERR_ARG;  // the key lives on another GPU
-    if (a.stream != nullptr) {
-        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-        PGCM_HIP(hipStreamIsCapturing(a.stream, &status));
-        a.capturing = status == hipStreamCaptureStatusActive;
-    }
+    rc = note_capture(a);
+    if (rc != PGCM_OK) return rc;
     if (a.fixed && a.n > kFixedMaxChunks) return PGCM_ERR_CAPACITY;
     SwapShape shape{};
     const bool one_launch = swap_shape(key, a, p.all_small, &shape);
@@ -925,12 +1105,28 @@ int run_batch(pgcm_key* key, BatchArgs a) {
         rc = acquire_context(key, a.stream, &ctx);
         if (rc != PGCM_OK) return rc;
     }
+    KeyPart part{key, 0, a.n, 0, 0};
     if (one_launch)
         rc = run_one_launch(key, ctx, a, shape);
     else if (p.all_one_row)
         rc = run_small_batch(key, ctx, a);
+    else if (count_span_rows(a, &part, 1) && !a.fixed)
+        rc = run_span_batch(ctx, a, &part, 1, deal_groups(&part, 1, (uint32_t)key->num_cu));
     else
         rc = run_unit_batch(key, ctx, a, p);
+    release_context(key, ctx);
+    return rc;
+}
+
+// All of a batch's parts as one batch in spans, in a context of the first part's key.
+int run_span_parts(BatchArgs a, KeyPart* parts, size_t nparts) {
+    int rc = note_capture(a);
+    if (rc != PGCM_OK) return rc;
+    pgcm_key* const key = parts[0].key;
+    Context* ctx = nullptr;
+    rc = acquire_context(key, a.stream, &ctx);
+    if (rc != PGCM_OK) return rc;
+    rc = run_span_batch(ctx, a, parts, nparts, deal_groups(parts, nparts, (uint32_t)key->num_cu));
     release_context(key, ctx);
     return rc;
 }
@@ -965,13 +1161,28 @@ int run_batch_keys(pgcm_key* const* keys, size_t nkeys, const uint32_t* key_inde
     }
     for (size_t k = 0; k < nkeys; ++k) first[k + 1] += first[k];
     for (size_t k = 0; k < nkeys; ++k) fill[k] = first[k];
-    for (size_t i = 0; i < all.n; ++i) order[fill[key_index[i]]++] = (uint32_t)i;
-    for (size_t k = 0; k < nkeys; ++k) {
+    for (size_t i = 0; i < all.n; ++i) order[fill[key_index[i]]++] = (uint32_t)i;  // fill: then the end
+    // all keys' chunks at once, in spans ...
+    std::vector<KeyPart> parts;
+    try {
+        for (size_t k = 0; k < nkeys; ++k)
+            if (fill[k] != first[k])
+                parts.push_back(KeyPart{keys[k], first[k], first[k + 1] - first[k], 0, 0});
+    } catch (const std::bad_alloc&) {
+        return PGCM_ERR_NOMEM;
+    }
+    if (parts.size() > 1 && parts.size() <= (size_t)keys[0]->num_cu) {
+        BatchArgs a = all;
+        a.order = order.data();
+        if (count_span_rows(a, parts.data(), parts.size()))
+            return run_span_parts(a, parts.data(), parts.size());
+    }
+    // ... or one key's after the other's
+    for (const KeyPart& part : parts) {
         BatchArgs group = all;
-        group.n = first[k + 1] - first[k];
-        group.order = order.data() + first[k];
-        if (group.n == 0) continue;
-        rc = run_batch(keys[k], group);
+        group.n = part.n;
+        group.order = order.data() + part.first;
+        rc = run_batch(part.key, group);
         if (rc != PGCM_OK) return rc;
     }
     return PGCM_OK;

@@ -34,6 +34,13 @@ __global__ void swap_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t iv
                             uint8_t* work, uint8_t* tags, uint8_t* ok, const GroupDesc* staged,
                             ArgBatch batch);
 
+// Spans of rows, one per wavefront, of chunks of one key (`key`) or of several (null; every
+// workgroup has its own in `groups`).  row_base: first row of every chunk.  slots: zero on entry.
+template <bool kDecrypt>
+__global__ void span_kernel(const KeyTables* key, const SpanGroup* groups, const uint32_t* row_base,
+                            const SpanChunk* chunks, SpanSlot* slots, const uint8_t* ivs,
+                            uint8_t* tags, uint8_t* ok, uint32_t iv_len);
+
 __global__ void clear_words_kernel(uint32_t* words, uint32_t n);
 
 __global__ void fold_kernel(const KeyTables* kt, const FoldItem* items, uint32_t power,
@@ -57,7 +64,8 @@ template <bool kDecrypt, int kRounds>
 __global__ void small_kernel(const KeyTables* kt, const ChunkDesc* chunks_host, uint32_t nchunks,
                              const uint8_t* ivs, uint32_t iv_len, uint8_t* tags, uint8_t* ok);
 
-__global__ void upload_kernel(uint4* dst, const uint4* src_host, uint32_t n16, uint32_t* clear);
+__global__ void upload_kernel(uint4* dst, const uint4* src_host, uint32_t n16, uint4* clear,
+                              uint32_t n_clear);
 
 }  // namespace pgcm
 

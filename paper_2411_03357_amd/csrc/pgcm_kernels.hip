@@ -371,14 +371,27 @@ __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict_
         for (uint32_t i = 0; i < t; ++i) gfw_mul_x8(p);
         kt->dot[l][t] = p;
     }
-    // hop[d][k] likewise: k = 2^j + i from i with H^(2^(8 + d + j)), from its nibble table
-    if (tid < kHopPowers) kt->hop[tid][0] = GfWords{{0x80000000u, 0, 0, 0}};
-    for (uint32_t j = 0; (1u << j) < kHopEntries; ++j) {
+    // hop[d][k] likewise: k = 2^j + i from i with H^(2^(8 + d + j)), from its nibble table; and the
+    // rows' hops
+    auto one = [&](GfWords* first) { *first = GfWords{{0x80000000u, 0, 0, 0}}; };
+    if (tid < kHopPowers) one(kt->hop[tid]);
+    if (tid == kHopPowers) one(kt->row_hop);
+    if (tid == kHopPowers + 1) one(kt->far_hop);
+    auto next = [&](GfWords* table, uint32_t power, uint32_t j, uint32_t i) {
+        const Block b = gf_mul_table(kt->ghash[power + j], gfw_to_block(table[i]));
+        table[(1u << j) + i] = gfw_from_block(b);
+    };
+    for (uint32_t j = 0; j < kRowHopPower; ++j) {
         __syncthreads();
-        for (uint32_t e = tid; e < kHopPowers << j; e += blockDim.x) {
+        const uint32_t tables = (1u << j) < kHopEntries ? kHopPowers + 2 : 1;
+        for (uint32_t e = tid; e < tables << j; e += blockDim.x) {
             const uint32_t d = e >> j, i = e & ((1u << j) - 1);
-            const Block b = gf_mul_table(kt->ghash[kHopMinPower + d + j], gfw_to_block(kt->hop[d][i]));
-            kt->hop[d][(1u << j) + i] = gfw_from_block(b);
+            if (d == 0)
+                next(kt->row_hop, kRowPower, j, i);
+            else if (d == 1)
+                next(kt->far_hop, kRowPower + kRowHopPower, j, i);
+            else
+                next(kt->hop[d - 2], kHopMinPower + d - 2, j, i);
         }
     }
 }
@@ -465,8 +478,10 @@ struct alignas(16) BulkLds {
     Block gh[kHashImages * kNibbleTableEntries];
     uint32_t te[kLdsTeBytes / 4];
     Block ctr[kWavesPerGroup * kCtrEntries];
+    Block long_aad[kWavesPerGroup];  // see AadBlocks
+    uint32_t rows_done[4];           // see Pace; the first word
 };
-static_assert(sizeof(BulkLds) == kLdsBytes && offsetof(BulkLds, gh) == 0 &&
+static_assert(sizeof(BulkLds) == kLdsBytes + 16 * (kWavesPerGroup + 1) && offsetof(BulkLds, gh) == 0 &&
                   offsetof(BulkLds, te) == kLdsTeBase && offsetof(BulkLds, ctr) == kLdsCtrBase,
               "LDS map");
 
@@ -540,12 +555,15 @@ __device__ __forceinline__ Block serial_hash(const Block* __restrict__ h_table, 
 struct AadBlocks {
     const uint8_t* bytes = nullptr;
     uint32_t len = 0, blocks = 0;
-    Block stand_in{{0, 0, 0, 0}};  // of a long AAD, at block -1
+    uint32_t stand_in = 0;  // LDS address of what a long AAD has at block -1 (rare: no registers for it)
 
     __device__ __forceinline__ Block at(int64_t blk) const {
         Block b{{0, 0, 0, 0}};
         if (blocks > kAadLaneBlocks) {
-            if (blk == -1) b = stand_in;
+            if (blk == -1) {
+                const u32x4 v = *reinterpret_cast<lds_u128_ptr>(stand_in);
+                b = Block{{v.x, v.y, v.z, v.w}};
+            }
         } else if (blk >= -(int64_t)blocks) {
             b = padded_block(bytes, len, blocks + (uint32_t)(int32_t)blk);
         }
@@ -554,16 +572,20 @@ struct AadBlocks {
     // to be called by the wavefront that walks the blocks before block 0
     __device__ __forceinline__ void prepare(const Block* __restrict__ h_table) {
         if (blocks > kAadLaneBlocks) {
-            stand_in = serial_hash(h_table, bytes, len, blocks - 1);
+            Block y = serial_hash(h_table, bytes, len, blocks - 1);
             const Block b = padded_block(bytes, len, blocks - 1);
-            block_xor(stand_in, b);
+            block_xor(y, b);
+            const u32x4 v = {y.w[0], y.w[1], y.w[2], y.w[3]};
+            *reinterpret_cast<lds_u128_wptr>(stand_in) = v;
         }
     }
 };
 
-__device__ __forceinline__ AadBlocks aad_blocks(const uint8_t* p, uint32_t len) {
+// stand_in: LDS for this wavefront
+__device__ __forceinline__ AadBlocks aad_blocks(const uint8_t* p, uint32_t len, const Block* stand_in) {
     AadBlocks a;
     a.bytes = p, a.len = len, a.blocks = (uint32_t)(((uint64_t)len + 15) / 16);
+    a.stand_in = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)stand_in;
     return a;
 }
 
@@ -712,9 +734,9 @@ __device__ __forceinline__ void aes_addr_init(AesAddr& A, uint32_t lane,
 // LDS accesses and by the board's power together, and both go down: per row of 64 blocks 555 -> 532
 // LDS cycles and 448 -> 432 vector instructions, 1.424 -> 1.389 ms for 4096 chunks of 320 KiB
 // (AES-256, alternating on one box), against keeping only round 1's constant sums.
-constexpr uint32_t kSegmentRows = kUnitBlocks / kRowBlocks;
+constexpr uint32_t kSegmentRows = 27;
 static_assert(255 + (kSegmentRows + 1) * kRowBlocks <= 256 * kCtrEntries,
-              "upper counter values of a segment of kSegmentRows rows, or one more in unit 0");
+              "upper counter values of a segment of kSegmentRows rows, or one more");
 struct CtrConsts {
     uint32_t k0;
     uint32_t q_addr;  // LDS address of the wavefront's entries
@@ -1353,16 +1375,40 @@ __device__ __forceinline__ void fill_bulk_lds(BulkLds& lds, const KeyTables* __r
     }
 }
 
+// Keeps the wavefronts of a workgroup abreast where each has its fixed share of the rows.  Of four
+// wavefronts on a SIMD the oldest is served first: left alone, the four oldest of sixteen finish
+// 320 rows in 957 us and the four youngest in 1625, most of a compute unit's lookups going idle
+// towards the end.  So a wavefront that is ahead of the workgroup's average steps back in
+// priority: all finish within 1445 to 1468 us (4096 chunks of 320 KiB, 2883 -> 2654 us both ways).
+struct Pace {
+    uint32_t* rows_done;  // LDS: by the workgroup, zero at the start
+    uint32_t mine = 0, all = 0;
+
+    __device__ __forceinline__ void start_row(uint32_t lane) {
+        // `all` was fetched a row ago: nothing waits for it
+        if (mine * kWavesPerGroup > (uint32_t)__builtin_amdgcn_readfirstlane(all))
+            __builtin_amdgcn_s_setprio(0);
+        else
+            __builtin_amdgcn_s_setprio(2);
+        if (lane == 0)
+            all = __hip_atomic_fetch_add(rows_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        ++mine;
+    }
+};
+struct NoPace {
+    __device__ __forceinline__ void start_row(uint32_t) {}
+};
+
 // The blocks [b0, b1) of one chunk, walked by one wavefront in rows of 64 that end at b1: keystream,
 // XOR, and the lane's GHASH sum over the rows, sum over rows r of C(r, lane) * (H^64)^(rows after
 // r), left in y.  Negative block numbers are those of the AAD and "block -1" (see bulk_row).
 // last: b1 is the chunk's end.
-template <bool kDecrypt, int kRounds, bool kThrough, bool kMatrixHash, class StoreMask>
+template <bool kDecrypt, int kRounds, bool kThrough, bool kMatrixHash, class Pace, class StoreMask>
 __device__ __forceinline__ void walk_unit(const uint32_t* __restrict__ rk, AesAddr& A,
                                           uint32_t lane, uint32_t wave, uint32_t lds_base,
                                           const uint8_t* src, uint8_t* dst, uint64_t len,
                                           int64_t b0, int64_t b1, bool last, const AadBlocks& aad,
-                                          const Block& j, StoreMask&& store_mask, uint32_t y[4]) {
+                                          const Block& j, Pace& pace, StoreMask&& store_mask, uint32_t y[4]) {
     const uint32_t nrows = (uint32_t)((b1 - b0 + kRowBlocks - 1) / kRowBlocks);
     // a row's counter blocks: inc32^(blk + 1)(J0), the first 96 bits of J0, then its counter field
     // plus blk + 1 modulo 2^32 (SP 800-38D 6.2, 7.1 step 3; ctr1 is that field plus 1, 2 for a
@@ -1372,13 +1418,14 @@ __device__ __forceinline__ void walk_unit(const uint32_t* __restrict__ rk, AesAd
     G.start(lds_base, lane);
     int64_t row_blk = b1 - (int64_t)nrows * kRowBlocks;
     for (uint32_t r = 0; r < nrows;) {
-        // a segment: kSegmentRows rows, or all seventeen of a unit 0 that has that many
+        // a segment: kSegmentRows rows, or one more when that is all
         const uint32_t first_ctr = (uint32_t)row_blk + ctr1;
         CtrConsts C = ctr_consts(rk, lane, wave, j.w[0], j.w[1], j.w[2], first_ctr, lds_base);
         const uint32_t left = nrows - r;
         const uint32_t end = left <= kSegmentRows + 1 ? nrows : r + kSegmentRows;
         for (; r < end; ++r, row_blk += kRowBlocks, C.rel += kRowBlocks) {
             const bool edge = row_blk < 0 || (last && r + 1 == nrows);
+            pace.start_row(lane);
             const RowPayload p = load_row(src, len, row_blk + lane, edge, aad);
             bulk_row<kDecrypt, kRounds, kThrough>(rk, A, C, p, dst, row_blk + lane, edge,
                                                   store_mask, lds_base, G);
@@ -1456,7 +1503,7 @@ __global__ __launch_bounds__(kGroupThreads) void bulk_kernel(
         const uint32_t unit = __builtin_amdgcn_readfirstlane(item - cd->unit_base);
         const uint32_t nunits = __builtin_amdgcn_readfirstlane(cd->nunits);
         const uint32_t first_blocks = __builtin_amdgcn_readfirstlane(cd->first_blocks);
-        AadBlocks aad = aad_blocks(cd->aad, cd->aad_len);
+        AadBlocks aad = aad_blocks(cd->aad, cd->aad_len, lds.long_aad + (tid >> 6));
         uint64_t len = cd->len;
         asm volatile("" : "+v"(len), "+v"(aad.bytes), "+v"(aad.len), "+v"(aad.blocks));  // (1) for these
         // unit 0 also takes the blocks before block 0
@@ -1468,8 +1515,9 @@ __global__ __launch_bounds__(kGroupThreads) void bulk_kernel(
         }
         Block* mask_out = ekj0 + chunk;
         uint32_t y[4];
+        NoPace pace;
         walk_unit<kDecrypt, kRounds, false, kMatrixHash>(
-            rk, A, lane, tid >> 6, lds_base, src, dst, len, b0, b1, unit + 1 == nunits, aad, j,
+            rk, A, lane, tid >> 6, lds_base, src, dst, len, b0, b1, unit + 1 == nunits, aad, j, pace,
             [&](uint32_t s0, uint32_t s1, uint32_t s2, uint32_t s3) __attribute__((always_inline)) {
                 *mask_out = Block{{s0, s1, s2, s3}};
             },
@@ -1921,6 +1969,43 @@ __device__ __forceinline__ GfWords dot_share(const Block& y, uint32_t wave, cons
     return acc;
 }
 
+// Lane l gets v * x^(8 (l % 16)), to be multiplied by a value that is the same in all lanes, a byte a
+// lane.
+__device__ __forceinline__ void spread_over_row(GfWords& v, uint32_t lane) {
+    GfWords t = v;
+    gfw_mul_x8(t);
+    if (lane & 1) v = t;
+    t = v;
+    gfw_mul_x8(t), gfw_mul_x8(t);
+    if (lane & 2) v = t;
+    t = v;
+    gfw_mul_x32(t);
+    if (lane & 4) v = t;
+    t = v;
+    gfw_mul_x32(t), gfw_mul_x32(t);
+    if (lane & 8) v = t;
+}
+__device__ __forceinline__ GfWords times_spread(const GfWords& v, const GfWords& spread, uint32_t lane) {
+    const uint32_t w = (lane / 4) % 4;
+    const uint32_t word = w == 0 ? v.a[0] : w == 1 ? v.a[1] : w == 2 ? v.a[2] : v.a[3];
+    uint32_t byte[1] = {word >> (24 - 8 * (lane % 4))};
+    GfWords z = bits_times<1>(byte, &spread);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) z.a[k] = row_summed(z.a[k]);
+    return z;
+}
+
+// counts one arrival of `of`; true in every lane if it was the last, and the word is left zero
+__device__ __forceinline__ bool last_to_arrive(uint32_t* word, uint32_t of, uint32_t lane) {
+    uint32_t before = 0;
+    if (lane == 0)
+        before = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool last = __builtin_amdgcn_readfirstlane(before) + 1 == of;
+    if (last && lane == 0)
+        __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return last;
+}
+
 // this lane's share of (the length block) * H, to be summed over the lanes, from H's nibble table in
 // memory: lane p < 32 looks up nibble p
 __device__ __forceinline__ Block length_block_entry(const Block* __restrict__ h_table,
@@ -1938,6 +2023,7 @@ __device__ __forceinline__ Block length_block_entry(const Block* __restrict__ h_
 // Tables of the round function, then of the tree.
 struct NarrowLds {
     uint32_t te[TeNarrow::kBytes / 4];
+    Block long_aad[kWavesPerGroup];
 };
 
 template <bool kDecrypt, int kRounds, SwapKind kKind>
@@ -2074,22 +2160,10 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
 #pragma unroll
             for (int k = 0; k < 4; ++k) extra.w[k] = rows_summed(row_summed(extra.w[k]));
         }
-        if (ngroups - 1 == g) return;  // this workgroup's part ends with the chunk
-        GfWords t = hop;
-        gfw_mul_x8(t);
-        if (lane & 1) hop = t;
-        t = hop;
-        gfw_mul_x8(t), gfw_mul_x8(t);
-        if (lane & 2) hop = t;
-        t = hop;
-        gfw_mul_x32(t);
-        if (lane & 4) hop = t;
-        t = hop;
-        gfw_mul_x32(t), gfw_mul_x32(t);
-        if (lane & 8) hop = t;
+        if (ngroups - 1 != g) spread_over_row(hop, lane);  // otherwise the part ends with the chunk
     };
 
-    AadBlocks aad = aad_blocks(cd.aad, worker ? cd.aad_len : 0);
+    AadBlocks aad = aad_blocks(cd.aad, worker ? cd.aad_len : 0, lds.long_aad + wave);
     auto keep_mask = [&](uint32_t s0, uint32_t s1, uint32_t s2, uint32_t s3)
         __attribute__((always_inline)) { mask_lds = Block{{s0, s1, s2, s3}}; };
     uint32_t y[4] = {0, 0, 0, 0};
@@ -2127,9 +2201,10 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
                     rk[i] = __builtin_amdgcn_readlane(lane_keys.word, i);
                 AesAddr A;
                 aes_addr_init<Te>(A, lane, rk + 4 * kRounds);
+                NoPace pace;
                 walk_unit<kDecrypt, kRounds, kDecrypt, false>(rk, A, lane, wave, lds_base, cd.src,
                                                               cd.dst, cd.len, b0, b1, b1 == nblk,
-                                                              aad, j, keep_mask, y);
+                                                              aad, j, pace, keep_mask, y);
             }
             fetch_ahead();
         }
@@ -2185,14 +2260,7 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
     if (lane < nwaves) sum = shares[lane];
 #pragma unroll
     for (int k = 0; k < 4; ++k) sum.a[k] = __builtin_amdgcn_readfirstlane(row_summed(sum.a[k]));
-    if (ngroups - 1 != g) {
-        const uint32_t w = (lane / 4) % 4;
-        const uint32_t word = w == 0 ? sum.a[0] : w == 1 ? sum.a[1] : w == 2 ? sum.a[2] : sum.a[3];
-        uint32_t byte[1] = {word >> (24 - 8 * (lane % 4))};
-        sum = bits_times<1>(byte, &hop);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) sum.a[k] = row_summed(sum.a[k]);
-    }
+    if (ngroups - 1 != g) sum = times_spread(sum, hop, lane);
     Block tag = gfw_to_block(sum);
     if (has_mask) {
         block_xor(tag, extra);
@@ -2205,24 +2273,13 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
         // the result must have reached memory before the arrival is counted: it is a device-scope
         // store, so waiting for it to complete is enough, and no cache needs writing back
         wait_for_own_global_accesses();
-        // counts one arrival of `of`; true in every lane if it was the last, and the word is left
-        // zero for the next batch
-        auto last_of = [&](uint32_t* word, uint32_t of) __attribute__((always_inline)) {
-            uint32_t before = 0;
-            if (lane == 0)
-                before = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const bool last = __builtin_amdgcn_readfirstlane(before) + 1 == of;
-            if (last && lane == 0)
-                __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return last;
-        };
         uint32_t* const main_word = arrive + group_base * kArriveStride;
         if (ngroups <= 64) {
-            if (!last_of(main_word, ngroups)) return;
+            if (!last_to_arrive(main_word, ngroups, lane)) return;
         } else {
             const uint32_t first = g & ~15u, in_it = ngroups - first < 16 ? ngroups - first : 16;
-            if (!last_of(main_word + (kSwapMaxGroups + first) * kArriveStride, in_it)) return;
-            if (!last_of(main_word, (ngroups + 15) / 16)) return;
+            if (!last_to_arrive(main_word + (kSwapMaxGroups + first) * kArriveStride, in_it, lane)) return;
+            if (!last_to_arrive(main_word, (ngroups + 15) / 16, lane)) return;
         }
         // the others' results are read with device-scope loads, issued after the arrival count was
         // seen: they come from memory, not from this XCD's caches
@@ -2250,6 +2307,223 @@ PGCM_INSTANTIATE_SWAP(false);
 PGCM_INSTANTIATE_SWAP(true);
 #undef PGCM_SWAP_SIGNATURE
 #undef PGCM_INSTANTIATE_SWAP
+
+// ------------------------------------------------------------------------------------------
+// Batches of any number of chunks, and of any number of keys, in one launch after the upload of their
+// descriptors: every wavefront walks a span of rows, and the spans are equally long to a row.
+// A row takes every wavefront the same time, so a compute unit is busy to the end, where units of a
+// fixed size leave most of the chip idle in their last round, and keys one after the other all of it
+// between them.  A piece (the part of a chunk in a span) is summed over its lanes at once, as in
+// the one-launch kernel but by one wavefront: the 64 products with H^64 .. H^1 bit by bit from
+// KeyTables::dot, then one or two more with the power that takes the sum to the chunk's end.  The
+// results of a chunk's pieces then only have to be added; the wavefront that finishes the last
+// piece does that and writes the tag or the verdict (see the one-launch kernel).
+namespace {
+
+// the sum over the lanes of y * H^(65 - lane), in all lanes
+__device__ __forceinline__ GfWords lanes_summed(const GfWords* __restrict__ powers, const uint32_t y[4]) {
+    GfWords q[kDotSlices];
+#pragma unroll
+    for (uint32_t t = 0; t < kDotSlices; ++t) q[t] = powers[t];
+    GfWords acc{{0, 0, 0, 0}};
+    uint32_t v[4] = {y[0], y[1], y[2], y[3]};
+    // (a loop: unrolled, its masks are made ahead of their use and take the registers of the powers)
+#pragma unroll 1
+    for (int bit = 0; bit < 8; ++bit) {
+        gfw_mul_x(acc);
+#pragma unroll
+        for (uint32_t t = 0; t < kDotSlices; ++t) {
+            const uint32_t m = (uint32_t)((int32_t)(v[t / 4] << (31 - 8 * (t % 4))) >> 31);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc.a[k] ^= q[t].a[k] & m;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] >>= 1;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc.a[k] = rows_summed(row_summed(acc.a[k]));
+    return acc;
+}
+
+struct SpanArgs {
+    const SpanChunk* chunks;
+    SpanSlot* slots;
+    const uint8_t* ivs;
+    uint32_t iv_len;
+    uint8_t *tags, *ok;
+};
+
+// rows [row, end) of the batch; `chunk` has the first of them, `slot` is to be added to a chunk's
+// number for the slot of the piece; key_word: lane i has round key word i
+template <bool kDecrypt, int kRounds>
+__device__ __forceinline__ void walk_span(const KeyTables* __restrict__ kt, uint32_t key_word,
+                                          const SpanArgs& args,
+                                          uint32_t row, uint32_t end, uint32_t chunk, uint32_t slot,
+                                          uint32_t lane_id, uint32_t wave, uint32_t lds_base,
+                                          Block* mask_lds, const Block* long_aad,
+                                          uint32_t* rows_done) {
+    Pace pace{rows_done};
+    uint32_t rk[4 * (kRounds + 1)];
+#pragma unroll
+    for (int i = 0; i < 4 * (kRounds + 1); ++i) rk[i] = __builtin_amdgcn_readlane(key_word, i);
+    for (; row < end; ++chunk) {
+        uint32_t lane = lane_id;
+        asm volatile("" : "+v"(lane));  // what depends on it is not to take registers between pieces
+        AesAddr A;
+        aes_addr_init<TeWide>(A, lane, rk + 4 * kRounds);
+        const SpanChunk* cd = args.chunks + chunk;
+        Block j = j0_from_iv(kt, args.ivs + (uint64_t)cd->index * args.iv_len, args.iv_len);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) j.w[k] = __builtin_amdgcn_readfirstlane(j.w[k]);
+        // to scalar registers or kept in vector ones, as in the unit kernel
+        const uint8_t* src = reinterpret_cast<const uint8_t*>(
+            same_in_all_lanes(reinterpret_cast<uint64_t>(cd->src)));
+        uint8_t* dst = reinterpret_cast<uint8_t*>(
+            same_in_all_lanes(reinterpret_cast<uint64_t>(cd->dst)));
+        AadBlocks aad = aad_blocks(cd->aad, cd->aad_len, long_aad + wave);
+        uint64_t len = cd->len;
+        asm volatile("" : "+v"(len), "+v"(aad.bytes), "+v"(aad.len), "+v"(aad.blocks));
+        const uint32_t first_row = __builtin_amdgcn_readfirstlane(cd->first_row);
+        const uint32_t to_end = first_row + __builtin_amdgcn_readfirstlane(cd->rows);
+        const uint32_t stop = to_end < end ? to_end : end;
+        const uint32_t behind = to_end - stop;  // rows of the chunk after this piece
+        const int64_t nblk = (int64_t)same_in_all_lanes((cd->len + 15) / 16);
+        const int64_t b1 = nblk - (int64_t)behind * kRowBlocks;
+        int64_t b0 = b1 - (int64_t)(stop - row) * kRowBlocks;
+        if (row == first_row) b0 = -(int64_t)__builtin_amdgcn_readfirstlane(lead_blocks(cd->aad_len));
+        if (b0 < 0) aad.prepare(kt->ghash[0]);
+        uint32_t y[4];
+        walk_unit<kDecrypt, kRounds, kDecrypt, false>(
+            rk, A, lane, wave, lds_base, src, dst, len, b0, b1, behind == 0, aad, j, pace,
+            [&](uint32_t s0, uint32_t s1, uint32_t s2, uint32_t s3) __attribute__((always_inline)) {
+                mask_lds[wave] = Block{{s0, s1, s2, s3}};
+            },
+            y);
+        GfWords sum = lanes_summed(kt->dot[lane], y);
+        asm volatile("" : "+s"(cd));  // what is needed only from here on is loaded only here
+        if (behind % kRowHopEntries != 0) {
+            GfWords hop = kt->row_hop[behind % kRowHopEntries];
+            spread_over_row(hop, lane);
+            sum = times_spread(sum, hop, lane);
+        }
+        if (behind >= kRowHopEntries) {
+            GfWords hop = kt->far_hop[behind / kRowHopEntries];
+            spread_over_row(hop, lane);
+            sum = times_spread(sum, hop, lane);
+        }
+        Block tag = gfw_to_block(sum);
+        if (b0 < 0 && b1 >= 0) {
+            // the piece with "block -1": the length block's product and E_K(J0)
+            Block extra = length_block_entry(kt->ghash[0], cd->aad_len, cd->len, lane);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) extra.w[k] = rows_summed(row_summed(extra.w[k]));
+            block_xor(tag, extra);
+            const Block m = mask_lds[wave];
+            block_xor(tag, m);
+        }
+        uint8_t* const tag_at = args.tags + (uint64_t)cd->index * 16;
+        Block received{{0, 0, 0, 0}};  // asked for here: on its way while the arrival is counted
+        if (kDecrypt) received = global_read_block_any(tag_at);
+        bool last = true;
+        const uint32_t n = cd->pieces;
+        if (n > 1) {
+            SpanSlot* const first = args.slots + cd->slot;
+            SpanSlot* const mine = args.slots + slot + chunk;
+            if (lane == 0)
+                store_block_device_scope(&mine->sum, tag.w[0], tag.w[1], tag.w[2], tag.w[3]);
+            // result and plaintext have reached memory before the arrival is counted
+            wait_for_own_global_accesses();
+            if (n <= 64) {
+                last = last_to_arrive(&first->arrived, n, lane);
+            } else {
+                const uint32_t at = (uint32_t)(mine - first) & ~15u, in_it = n - at < 16 ? n - at : 16;
+                last = last_to_arrive(&first[at].arrived_of_sixteen, in_it, lane) &&
+                       last_to_arrive(&first->arrived, (n + 15) / 16, lane);
+            }
+            if (last) {
+                tag = Block{{0, 0, 0, 0}};
+                for (uint32_t i = lane; i < n; i += 64) {
+                    const Block b = load_block_device_scope(&first[i].sum);
+                    block_xor(tag, b);
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) tag.w[k] = rows_summed(row_summed(tag.w[k]));
+            }
+        }
+        if (last) {
+            write_or_compare_tag<kDecrypt>(tag, tag_at, received, args.ok + cd->index, cd->dst,
+                                           cd->len, lane);
+        }
+        row = stop;
+    }
+}
+
+}  // namespace
+
+// key: the batch's key, or null: every workgroup has its own
+template <bool kDecrypt>
+__global__ __launch_bounds__(kGroupThreads) void span_kernel(
+    const KeyTables* __restrict__ key, const SpanGroup* __restrict__ groups,
+    const uint32_t* __restrict__ row_base, const SpanChunk* __restrict__ chunks,
+    SpanSlot* __restrict__ slots, const uint8_t* __restrict__ ivs, uint8_t* __restrict__ tags,
+    uint8_t* __restrict__ ok, uint32_t iv_len) {
+    __shared__ BulkLds lds;
+    __shared__ Block mask_lds[kWavesPerGroup];
+    const uint32_t lds_base = lds_offset(&lds);
+    const uint32_t tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const SpanGroup* __restrict__ gd = groups + blockIdx.x;
+    const KeyTables* __restrict__ kt = key != nullptr ? key : gd->kt;
+    // The tables are asked for, then what the first piece needs, in the rounds of loads that take:
+    // they overlap, and the loads that walk_span repeats find their lines in the caches.
+    TeFill<TeWide, kGroupThreads> te;
+    te.fetch(kt, tid);
+    Block gh{{0, 0, 0, 0}};
+    if (tid < kNibbleTableEntries) gh = kt->ghash[kRowPower][tid];
+    const uint32_t key_word = lane < 60 ? kt->rk[lane] : 0u;
+    const uint32_t rounds = __builtin_amdgcn_readfirstlane(kt->rounds);
+    // the workgroup's rows dealt to its wavefronts, none without any before one that has some
+    const uint32_t rows = gd->rows, waves = rows < kWavesPerGroup ? rows : kWavesPerGroup;
+    const uint32_t place = wave < waves ? wave : waves - 1;
+    const uint32_t row = gd->first_row + rows * place / waves;
+    const uint32_t end = gd->first_row + rows * (place + 1) / waves;
+    // its first chunk: the last one that does not begin behind `row`
+    uint32_t chunk = gd->chunk;
+    for (uint32_t i = 1; i < gd->nchunks; i += 64) {
+        const bool begins = i + lane < gd->nchunks && row_base[gd->chunk + i + lane] <= row;
+        const uint32_t more = __builtin_amdgcn_readfirstlane((uint32_t)__popcll(__ballot(begins)));
+        chunk += more;
+        if (more < 64) break;
+    }
+    const uint8_t* iv = ivs + (uint64_t)chunks[chunk].index * iv_len;
+    const uint32_t touched = (uint32_t)global_read8(iv) + global_read8(iv + iv_len - 1);
+    te.store(lds.te, tid);
+    if (tid < kNibbleTableEntries) lds.gh[tid] = gh;
+    if (tid == 0) lds.rows_done[0] = 0;
+    asm volatile("" : : "v"(touched));
+    __syncthreads();
+
+    if (wave >= waves) return;
+    const SpanArgs args{chunks, slots, ivs, iv_len, tags, ok};
+    const uint32_t slot = gd->first_wave + wave;
+    if (rounds == 14)
+        walk_span<kDecrypt, 14>(kt, key_word, args, row, end, chunk, slot, lane, wave, lds_base, mask_lds,
+                             lds.long_aad, lds.rows_done);
+    else if (rounds == 12)
+        walk_span<kDecrypt, 12>(kt, key_word, args, row, end, chunk, slot, lane, wave, lds_base, mask_lds,
+                             lds.long_aad, lds.rows_done);
+    else
+        walk_span<kDecrypt, 10>(kt, key_word, args, row, end, chunk, slot, lane, wave, lds_base, mask_lds,
+                             lds.long_aad, lds.rows_done);
+}
+
+#define PGCM_INSTANTIATE_SPAN(D)                                                                 \
+    template __global__ void span_kernel<D>(const KeyTables*, const SpanGroup*, const uint32_t*, \
+                                            const SpanChunk*, SpanSlot*, const uint8_t*, uint8_t*, \
+                                            uint8_t*, uint32_t)
+PGCM_INSTANTIATE_SPAN(false);
+PGCM_INSTANTIATE_SPAN(true);
+#undef PGCM_INSTANTIATE_SPAN
 
 __global__ __launch_bounds__(1024) void clear_words_kernel(uint32_t* __restrict__ words, uint32_t n) {
     for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) words[i] = 0;
@@ -2427,15 +2701,16 @@ PGCM_INSTANTIATE_SMALL(true, 14);
 
 // Brings a batch's descriptors from pinned host memory into the device workspace.  Done by a
 // kernel so that the batch stays on one hardware queue: a DMA copy between kernels costs two
-// cross-queue hand-overs.  `clear`, when not null, is a word to set to zero as well (the unit
-// counter of a new workspace: a fill by a kernel, not a memset node, so that the stream's work
+// cross-queue hand-overs.  The n_clear pieces of sixteen bytes from `clear` on are set to zero as well
+// (counters of a new workspace: a fill by a kernel, not a memset node, so that the stream's work
 // stays of one kind).
 __global__ __launch_bounds__(256) void upload_kernel(uint4* __restrict__ dst,
                                                      const uint4* __restrict__ src_host,
-                                                     uint32_t n16, uint32_t* __restrict__ clear) {
-    if (clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += gridDim.x * blockDim.x)
-        dst[i] = src_host[i];
+                                                     uint32_t n16, uint4* __restrict__ clear,
+                                                     uint32_t n_clear) {
+    const uint32_t first = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+    for (uint32_t i = first; i < n_clear; i += step) clear[i] = make_uint4(0, 0, 0, 0);
+    for (uint32_t i = first; i < n16; i += step) dst[i] = src_host[i];
 }
 
 }  // namespace pgcm

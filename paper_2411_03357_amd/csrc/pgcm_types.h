@@ -64,6 +64,11 @@ constexpr uint32_t kDotSlices = 16;
 constexpr uint32_t kHopMinPower = 8;    // the shortest stretch of a workgroup: 4 units of 64 blocks
 constexpr uint32_t kHopPowers = 7;      // ... and the longest: 16 units of 1024 blocks
 constexpr uint32_t kHopEntries = 256;   // workgroups of a chunk
+// The span kernel cuts chunks between any two rows: row_hop[k] = H^(64 k), and far_hop[k] =
+// H^(64 k kRowHopEntries) for what is further from a chunk's end.
+constexpr uint32_t kRowHopPower = 12;
+constexpr uint32_t kRowHopEntries = 1u << kRowHopPower;
+constexpr uint32_t kFarHopEntries = 256;
 
 struct alignas(16) GfWords {
     uint32_t a[4];
@@ -88,6 +93,8 @@ struct alignas(16) KeyTables {
     uint32_t hash_image[kHashImages][kRowMatrixWords];
     GfWords dot[64][kDotSlices];
     GfWords hop[kHopPowers][kHopEntries];
+    GfWords row_hop[kRowHopEntries];
+    GfWords far_hop[kFarHopEntries];
 };
 constexpr size_t kPublicTablesBytes = offsetof(KeyTables, hash_image);
 
@@ -190,6 +197,38 @@ struct alignas(16) GroupDesc {
     ArgChunk c;
     uint32_t group_base, ngroups;  // the chunk's first workgroup and their number
 };
+
+// Spans: the rows of all chunks of a batch, each chunk's counted back from its end and the blocks
+// before its block 0 among them, are numbered through, and every wavefront takes its share of them,
+// cutting chunks wherever its share ends.  The part of one chunk in one wavefront's span is a piece.
+struct alignas(16) SpanGroup {      // a workgroup
+    const KeyTables* kt;
+    uint32_t first_row, rows;       // its rows
+    uint32_t chunk, nchunks;        // the chunk of the first one; the chunks it has rows of
+    uint32_t first_wave;            // wavefronts with rows are numbered through as well
+    uint32_t pad_;
+};
+static_assert(sizeof(SpanGroup) == 32, "descriptor layout");
+struct alignas(16) SpanChunk {
+    const uint8_t* src;
+    uint8_t* dst;
+    const uint8_t* aad;
+    uint64_t len;
+    uint32_t aad_len;
+    uint32_t index;                 // the chunk's place in the caller's ivs, tags and ok arrays
+    uint32_t first_row, rows;
+    uint32_t slot, pieces;          // its pieces have consecutive slots from `slot`
+    uint32_t pad_[2];
+};
+static_assert(sizeof(SpanChunk) == 64, "descriptor layout");
+// A piece's result and, in the slot of a chunk's first piece, the count of the chunk's pieces that
+// are done (of many pieces, they are counted in sixteens first, in the slot of the first of them).
+struct alignas(64) SpanSlot {
+    Block sum;
+    uint32_t arrived, arrived_of_sixteen;
+    uint32_t pad_[10];
+};
+static_assert(sizeof(SpanSlot) == 64, "a cache line each");
 
 // A batch whose chunks are all at most this long takes the small-transfer path: one kernel (the
 // paper's non-swap transfers are usually < 8 KB, section 4.2): eight rows of 64 blocks.
