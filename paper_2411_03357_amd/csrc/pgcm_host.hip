@@ -106,6 +106,13 @@ inline uint32_t choose_unit_power(size_t n, const uint32_t* order, const uint64_
 
 namespace {
 
+// How a batch is cut into spans: the workgroups' shares and what each has of which chunk.
+struct SpanPlan {
+    std::vector<SpanGroup> groups;
+    std::vector<SpanPart> parts;
+    uint32_t longest = 0;  // list of parts of a workgroup
+};
+
 // What one batch in flight needs besides the key's tables: pinned staging buffers for the
 // descriptors the host writes, and the device workspace the kernels of the batch share.  Batches
 // that use one context are ordered by the stream the context is bound to, which is what makes
@@ -119,12 +126,13 @@ struct Context {
     bool stage_used[kStages] = {};
     int next_stage = 0;
     // device workspace: descriptors, unit maps, fold lists, unit counter, per-chunk E_K(J0),
-    // partial sets
+    // partial sets; or arrival slots, then descriptors
     uint8_t* work = nullptr;
     size_t work_cap = 0;
     uint32_t* counter_at = nullptr;  // where the unit counter was last known to be zero
     bool counter_dirty = true;
-    bool arrive_clean = false;  // the one-launch path's arrival words (start of `work`) are zero
+    size_t clean_slots = 0;  // so many ArriveSlots at the start of `work` have counts of zero
+    SpanPlan plan;           // of the call that is using the context
     // binding
     hipStream_t stream = nullptr;
     bool bound = false;        // has run a batch on `stream`
@@ -238,7 +246,7 @@ int ensure_work(Context* c, size_t bytes, hipStream_t stream) {
         c->work_cap = 0;
     }
     c->counter_at = nullptr;  // new memory holds anything, even if it lands at the old address
-    c->arrive_clean = false;
+    c->clean_slots = 0;
     size_t cap = bytes + bytes / 2 + 65536;
     void* p = nullptr;
     if (hip_failed(hipMalloc(&p, cap))) return PGCM_ERR_NOMEM;
@@ -650,8 +658,23 @@ int run_small_batch(pgcm_key* key, Context* ctx, const BatchArgs& a) {
     return rc_end;
 }
 
-// Workspace of the one-launch path: arrival words, one result per workgroup.
-constexpr size_t kSwapWorkBytes = kSwapArriveBytes + sizeof(Block) * kSwapMaxGroups;
+// Workspace of the one-launch path: a slot per workgroup.
+constexpr size_t kSwapWorkBytes = sizeof(ArriveSlot) * kSwapMaxGroups;
+
+// Makes the counts of the first n slots of the workspace zero.  Every batch leaves them zero; they
+// need clearing when the workspace is new, was used by a batch with units, or is shared between
+// keys, and in a graph, before whose replays any of that may happen.
+void use_slots(Context* ctx, size_t n, hipStream_t stream, bool capturing) {
+    if (ctx->clean_slots < n || !ctx->growable || capturing) {
+        const uint32_t n_clear = (uint32_t)(n * (sizeof(ArriveSlot) / 16));
+        const uint32_t groups = (n_clear + 255) / 256;
+        hipLaunchKernelGGL(upload_kernel, dim3(groups < 1024 ? groups : 1024), dim3(256), 0, stream,
+                           (uint4*)nullptr, (const uint4*)nullptr, 0u,
+                           reinterpret_cast<uint4*>(ctx->work), n_clear);
+        if (ctx->clean_slots < n) ctx->clean_slots = n;
+    }
+    ctx->counter_at = nullptr;  // the unit counter of other batches may lie under them
+}
 
 // How a batch is cut for the one-launch path, if it takes it.
 struct SwapShape {
@@ -721,7 +744,7 @@ bool swap_shape(const pgcm_key* key, const BatchArgs& a, bool all_small, SwapSha
 template <SwapKind kKind>
 void launch_swap_batch(const pgcm_key* key, const BatchArgs& a, const SwapShape& shape,
                        hipEvent_t done, const ArgBatch& batch, const GroupDesc* staged,
-                       uint8_t* work) {
+                       ArriveSlot* slots) {
     const dim3 grid(shape.groups), block(64u * ((1u << shape.wave_power) + (shape.wave_power < 4)));
     const KeyTables* kt = key->tables;
     const SwapMeta meta = swap_meta(staged ? 0 : (uint32_t)a.n, shape.unit_power, shape.wave_power,
@@ -729,10 +752,10 @@ void launch_swap_batch(const pgcm_key* key, const BatchArgs& a, const SwapShape&
                                     (uint32_t)key->rounds);
     if (a.decrypt)
         launch_swap<true, kKind>(key->rounds, grid, block, a.stream, a.capturing, done, kt, a.ivs,
-                                 a.iv_len, meta, work, a.tags, a.ok, staged, batch);
+                                 a.iv_len, meta, slots, a.tags, a.ok, staged, batch);
     else
         launch_swap<false, kKind>(key->rounds, grid, block, a.stream, a.capturing, done, kt, a.ivs,
-                                  a.iv_len, meta, work, a.tags, a.ok, staged, batch);
+                                  a.iv_len, meta, slots, a.tags, a.ok, staged, batch);
 }
 
 // A batch of few chunks that does not fill the chip: one kernel.  Up to kArgChunks chunks travel as
@@ -770,18 +793,12 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapSh
         groups += of_chunk;
     }
     if (in_args) batch.group_base[a.n] = groups;
-    uint8_t* d_work = nullptr;
+    ArriveSlot* slots = nullptr;
     if (!shape.alone) {
         const int rc = ensure_work(ctx, kSwapWorkBytes, a.stream);
         if (rc != PGCM_OK) return rc;
-        d_work = ctx->work;
-        // the arrival words are left at zero by every batch of this kind; they need clearing when
-        // the workspace is new, was used by a batch of the other kind, or is shared between keys
-        if (!ctx->arrive_clean || !ctx->growable)
-            hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(1024), 0, a.stream,
-                               reinterpret_cast<uint32_t*>(d_work), kSwapArriveWords);
-        ctx->arrive_clean = false;
-        ctx->counter_at = nullptr;  // the unit counter of other batches may lie under this
+        use_slots(ctx, shape.groups, a.stream, a.capturing);
+        slots = reinterpret_cast<ArriveSlot*>(ctx->work);
     }
     int rc_timing = record_timing_start(key, a.stream);
     // Where no staging buffer is used but the workspace is, the batch's end is marked on the event
@@ -790,11 +807,11 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapSh
     // using it again only moves the guard later.)
     const hipEvent_t done = ctx != nullptr ? ctx->stage_done[s] : nullptr;
     if (shape.narrow)
-        launch_swap_batch<SwapKind::kNarrow>(key, a, shape, done, batch, h_groups, d_work);
+        launch_swap_batch<SwapKind::kNarrow>(key, a, shape, done, batch, h_groups, slots);
     else if (shape.unit_power == kRowPower)
-        launch_swap_batch<SwapKind::kRows>(key, a, shape, done, batch, h_groups, d_work);
+        launch_swap_batch<SwapKind::kRows>(key, a, shape, done, batch, h_groups, slots);
     else
-        launch_swap_batch<SwapKind::kUnits>(key, a, shape, done, batch, h_groups, d_work);
+        launch_swap_batch<SwapKind::kUnits>(key, a, shape, done, batch, h_groups, slots);
     if (rc_timing == PGCM_OK) rc_timing = record_timing_stop(key, a.stream);
     int rc_end = PGCM_OK;
     if (!in_args) {
@@ -805,8 +822,10 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapSh
         ctx->bound = true;
     }
     if (rc_timing != PGCM_OK) return rc_timing;
-    PGCM_HIP(hipGetLastError());
-    if (!shape.alone) ctx->arrive_clean = true;
+    if (hip_failed(hipGetLastError())) {
+        if (ctx != nullptr) ctx->clean_slots = 0;
+        return PGCM_ERR_HIP;
+    }
     return rc_end;
 }
 
@@ -822,7 +841,7 @@ int run_unit_batch(pgcm_key* key, Context* ctx, const BatchArgs& a, const BatchP
     rc = ensure_work(ctx, w.bytes, a.stream);
     if (rc != PGCM_OK) return rc;
     fill_schedule(a, p, w, ctx->stage[s]);
-    ctx->arrive_clean = false;  // the descriptors land where the one-launch path counts arrivals
+    ctx->clean_slots = 0;  // the descriptors land there
     uint32_t* d_counter = reinterpret_cast<uint32_t*>(ctx->work + w.counter);
     {
         // the unit counter is left at zero by the last kernel of every batch; it only needs
@@ -962,112 +981,151 @@ uint32_t deal_groups(KeyPart* parts, size_t nparts, uint32_t num_cu) {
     return total;
 }
 
-struct SpanLayout {
-    size_t groups, row_base, chunks, upload_bytes, slots, bytes;
-};
-SpanLayout lay_out_spans(size_t n, size_t groups) {
-    SpanLayout w;
-    w.groups = 0;
-    w.row_base = round_up(sizeof(SpanGroup) * groups, 256);
-    w.chunks = round_up(w.row_base + sizeof(uint32_t) * n, 256);
-    w.upload_bytes = round_up(w.chunks + sizeof(SpanChunk) * n, 256);
-    w.slots = w.upload_bytes;
-    w.bytes = w.slots + sizeof(SpanSlot) * (groups * kWavesPerGroup + n);
-    return w;
-}
-
-void fill_spans(const BatchArgs& a, const KeyPart* parts, size_t nparts, const SpanLayout& w,
-                uint8_t* stage) {
-    SpanGroup* const groups = reinterpret_cast<SpanGroup*>(stage + w.groups);
-    uint32_t* const row_base = reinterpret_cast<uint32_t*>(stage + w.row_base);
-    SpanChunk* const chunks = reinterpret_cast<SpanChunk*>(stage + w.chunks);
-    uint32_t row = 0, group = 0, wave = 0;
-    for (size_t q = 0; q < nparts; ++q) {
-        const KeyPart& part = parts[q];
-        const uint32_t first_group = group;
-        // a workgroup begins where the weight so far reaches its share; a chunk's own comes before
-        // its rows'
+// Cuts the keys' chunks.
+void plan_spans(const BatchArgs& a, const KeyPart* keys, size_t nkeys, SpanPlan* plan) {
+    std::vector<SpanGroup>& groups = plan->groups;
+    std::vector<SpanPart>& parts = plan->parts;
+    groups.clear();
+    parts.clear();
+    uint32_t row = 0;
+    for (size_t q = 0; q < nkeys; ++q) {
+        const KeyPart& key = keys[q];
+        const size_t first_group = groups.size();
+        // a workgroup begins where the weight so far reaches its share; a chunk's own weight comes
+        // before its rows'
         uint64_t weight = 0, next = 0;
-        for (size_t k = part.first; k < part.first + part.n; ++k) {
+        for (size_t k = key.first; k < key.first + key.n; ++k) {
             const size_t i = a.at(k);
-            SpanChunk& c = chunks[k];
+            SpanPart c;
             c.src = (const uint8_t*)a.src[i];
             c.dst = (uint8_t*)a.dst[i];
             c.len = a.len[i];
             c.aad_len = a.aad_len ? a.aad_len[i] : 0;
             c.aad = c.aad_len ? (const uint8_t*)a.aad[i] : nullptr;
             c.index = (uint32_t)i;
-            c.first_row = row_base[k] = row;
+            c.first_row = row;
             c.rows = (uint32_t)span_rows(a, i);
-            c.pad_[0] = c.pad_[1] = 0;
-            while (group < first_group + part.groups && next < weight + c.rows + 1) {
+            c.slot = (uint32_t)parts.size();
+            c.waves = 0;
+            // the workgroups that begin in this chunk: the one before has its part before theirs
+            bool begun = false;
+            while (groups.size() < first_group + key.groups && next < weight + c.rows + 1) {
                 const uint32_t at = next > weight ? row + (uint32_t)(next - weight) - 1 : row;
-                groups[group++] = SpanGroup{part.key->tables, at, 0, (uint32_t)k, 0, 0, 0};
-                next = part.weight() * (group - first_group) / part.groups;
+                if (at > row && !begun) {
+                    c.own_slot = (uint32_t)parts.size();
+                    parts.push_back(c);
+                }
+                begun = true;
+                c.own_slot = (uint32_t)parts.size();
+                groups.push_back(SpanGroup{key.key->tables, at, 0, c.own_slot, 0, {0, 0}});
+                parts.push_back(c);
+                next = key.weight() * (groups.size() - first_group) / key.groups;
             }
+            if (!begun) {
+                c.own_slot = (uint32_t)parts.size();
+                parts.push_back(c);
+            }
+            for (size_t p = c.slot; p < parts.size(); ++p)
+                parts[p].slots = (uint32_t)parts.size() - c.slot;
             row += c.rows;
             weight += c.rows + 1;
         }
-        for (uint32_t g = first_group; g < group; ++g) {
-            const bool more = g + 1 < group;
+        for (size_t g = first_group; g < groups.size(); ++g) {
+            const bool more = g + 1 < groups.size();
             groups[g].rows = (more ? groups[g + 1].first_row : row) - groups[g].first_row;
-            groups[g].nchunks = (more ? groups[g + 1].chunk + 1 : (uint32_t)(part.first + part.n)) -
-                                groups[g].chunk;
-            groups[g].first_wave = wave;
-            wave += groups[g].rows < kWavesPerGroup ? groups[g].rows : kWavesPerGroup;
+            groups[g].nparts = (more ? groups[g + 1].part : (uint32_t)parts.size()) - groups[g].part;
         }
-        // the wavefront of row r, in the workgroup `at` or a later one of the part
-        auto wave_of = [&](uint32_t r, uint32_t& at) {
-            while (r >= groups[at].first_row + groups[at].rows) ++at;
-            const SpanGroup& g = groups[at];
-            const uint32_t waves = g.rows < kWavesPerGroup ? g.rows : kWavesPerGroup;
-            return g.first_wave + ((r - g.first_row + 1) * waves - 1) / g.rows;
-        };
-        uint32_t at = first_group;
-        for (size_t k = part.first; k < part.first + part.n; ++k) {
-            SpanChunk& c = chunks[k];
-            const uint32_t first = wave_of(c.first_row, at);
-            c.slot = first + (uint32_t)k;
-            c.pieces = wave_of(c.first_row + c.rows - 1, at) - first + 1;
+    }
+    plan->longest = 0;
+    for (const SpanGroup& g : groups) {
+        if (g.nparts > plan->longest) plan->longest = g.nparts;
+        // the wavefront of row r of the workgroup
+        const uint32_t waves = g.rows < kWavesPerGroup ? g.rows : kWavesPerGroup;
+        auto wave_of = [&](uint32_t r) { return ((r + 1) * waves - 1) / g.rows; };
+        for (uint32_t p = g.part; p < g.part + g.nparts; ++p) {
+            SpanPart& c = parts[p];
+            const uint32_t from = c.first_row > g.first_row ? c.first_row - g.first_row : 0;
+            const uint32_t end = c.first_row + c.rows - g.first_row;
+            const uint32_t first = wave_of(from), last = wave_of((end < g.rows ? end : g.rows) - 1);
+            c.waves = (last - first + 1) << 8 | first;
         }
     }
 }
 
+// Bytes of descriptors up to which the workgroups read theirs from host memory themselves.
+constexpr size_t kSpanHostBytes = 128 << 10;
+
+// Upper bounds for any batch of at most n chunks on a device of num_cu compute units.
+inline size_t span_stage_bytes(size_t n, size_t num_cu) {
+    const size_t uploaded = sizeof(SpanGroup) * num_cu + sizeof(SpanPart) * (n + num_cu) + 256;
+    return uploaded > kSpanHostBytes ? uploaded : kSpanHostBytes;
+}
+inline size_t span_work_bytes(size_t n, size_t num_cu) {
+    return 2 * sizeof(ArriveSlot) * (n + num_cu) + span_stage_bytes(n, num_cu) + 512;
+}
+
 // One batch in spans, of one key or of several: the context is that of the first.
-int run_span_batch(Context* ctx, const BatchArgs& a, const KeyPart* parts, size_t nparts,
-                   uint32_t ngroups) {
-    const SpanLayout w = lay_out_spans(a.n, ngroups);
+int run_span_batch(Context* ctx, const BatchArgs& a, KeyPart* keys, size_t nkeys) {
+    SpanPlan& plan = ctx->plan;
+    const uint32_t ngroups = deal_groups(keys, nkeys, (uint32_t)keys[0].key->num_cu);
+    try {
+        plan_spans(a, keys, nkeys, &plan);
+    } catch (const std::bad_alloc&) {
+        return PGCM_ERR_NOMEM;
+    }
+    // each workgroup's list right behind its descriptor, to be read from host memory, if they are few
+    // and of much the same length; otherwise uploaded, one list after the other
+    size_t stride = sizeof(SpanGroup) + sizeof(SpanPart) * plan.longest;
+    const bool in_host = plan.longest <= kSpanLdsParts && stride * ngroups <= kSpanHostBytes;
+    const size_t parts_at = round_up(sizeof(SpanGroup) * ngroups, 256);
+    const size_t bytes = in_host ? stride * ngroups
+                                 : round_up(parts_at + sizeof(SpanPart) * plan.parts.size(), 256);
+    const size_t nslots = plan.parts.size();
     const int s = ctx->next_stage;
-    int rc = ensure_stage(ctx, s, w.upload_bytes);
+    int rc = ensure_stage(ctx, s, bytes);
     if (rc != PGCM_OK) return rc;
-    rc = ensure_work(ctx, w.bytes, a.stream);
+    // the descriptors go behind every slot that is kept clean
+    size_t image = sizeof(ArriveSlot) * (nslots > ctx->clean_slots ? nslots : ctx->clean_slots);
+    image = round_up(image, 256);
+    rc = ensure_work(ctx, image + (in_host ? 0 : bytes), a.stream);
     if (rc != PGCM_OK) return rc;
-    fill_spans(a, parts, nparts, w, ctx->stage[s]);
-    // the places where the other paths have their counters
-    ctx->arrive_clean = false;
-    ctx->counter_at = nullptr;
-    const uint32_t n16 = (uint32_t)(w.upload_bytes / 16), n_clear = (uint32_t)((w.bytes - w.slots) / 16);
-    uint32_t groups = ((n16 > n_clear ? n16 : n_clear) + 255) / 256;
-    if (groups > 1024) groups = 1024;
-    hipLaunchKernelGGL(upload_kernel, dim3(groups), dim3(256), 0, a.stream,
-                       reinterpret_cast<uint4*>(ctx->work),
-                       reinterpret_cast<const uint4*>(ctx->stage[s]), n16,
-                       reinterpret_cast<uint4*>(ctx->work + w.slots), n_clear);
+    use_slots(ctx, nslots, a.stream, a.capturing);
+    uint8_t* const stage = ctx->stage[s];
+    const uint8_t* packets = stage;
+    const SpanPart* parts = nullptr;
+    if (in_host) {
+        for (uint32_t g = 0; g < ngroups; ++g) {
+            const SpanGroup& d = plan.groups[g];
+            memcpy(stage + g * stride, &d, sizeof(d));
+            memcpy(stage + g * stride + sizeof(d), &plan.parts[d.part], sizeof(SpanPart) * d.nparts);
+        }
+    } else {
+        memcpy(stage, plan.groups.data(), sizeof(SpanGroup) * ngroups);
+        memcpy(stage + parts_at, plan.parts.data(), sizeof(SpanPart) * nslots);
+        const uint32_t n16 = (uint32_t)(bytes / 16);
+        hipLaunchKernelGGL(upload_kernel, dim3((n16 + 255) / 256 < 1024 ? (n16 + 255) / 256 : 1024),
+                           dim3(256), 0, a.stream, reinterpret_cast<uint4*>(ctx->work + image),
+                           reinterpret_cast<const uint4*>(stage), n16, (uint4*)nullptr, 0u);
+        packets = ctx->work + image;
+        parts = reinterpret_cast<const SpanPart*>(packets + parts_at);
+        stride = 0;
+    }
     int rc_timing = PGCM_OK;
-    for (size_t q = 0; q < nparts && rc_timing == PGCM_OK; ++q)
-        rc_timing = record_timing_start(parts[q].key, a.stream);
+    for (size_t q = 0; q < nkeys && rc_timing == PGCM_OK; ++q)
+        rc_timing = record_timing_start(keys[q].key, a.stream);
     launch_last(a.decrypt ? span_kernel<true> : span_kernel<false>, dim3(ngroups),
                 dim3(kGroupThreads), a.stream, a.capturing, ctx->stage_done[s],
-                (const KeyTables*)(nparts == 1 ? parts[0].key->tables : nullptr),
-                (const SpanGroup*)(ctx->work + w.groups), (const uint32_t*)(ctx->work + w.row_base),
-                (const SpanChunk*)(ctx->work + w.chunks), (SpanSlot*)(ctx->work + w.slots), a.ivs,
-                a.tags, a.ok, a.iv_len);
-    for (size_t q = 0; q < nparts && rc_timing == PGCM_OK; ++q)
-        rc_timing = record_timing_stop(parts[q].key, a.stream);
+                (const KeyTables*)(nkeys == 1 ? keys[0].key->tables : nullptr), packets, parts,
+                (uint32_t)stride, a.iv_len, a.ivs, reinterpret_cast<ArriveSlot*>(ctx->work), a.tags,
+                a.ok);
+    for (size_t q = 0; q < nkeys && rc_timing == PGCM_OK; ++q)
+        rc_timing = record_timing_stop(keys[q].key, a.stream);
     const int rc_end = end_of_batch(ctx, s, a.stream, a.capturing);
-    if (rc_timing != PGCM_OK) return rc_timing;
-    PGCM_HIP(hipGetLastError());
-    return rc_end;
+    if (hip_failed(hipGetLastError())) {
+        ctx->clean_slots = 0;
+        return PGCM_ERR_HIP;
+    }
+    return rc_timing != PGCM_OK ? rc_timing : rc_end;
 }
 
 int note_capture(BatchArgs& a) {
@@ -1095,7 +1153,18 @@ int run_batch(pgcm_key* key, BatchArgs a) {
     if (rc != PGCM_OK) return rc;
     if (a.fixed && a.n > kFixedMaxChunks) return PGCM_ERR_CAPACITY;
     SwapShape shape{};
-    const bool one_launch = swap_shape(key, a, p.all_small, &shape);
+    bool one_launch = swap_shape(key, a, p.all_small, &shape);
+    KeyPart part{key, 0, a.n, 0, 0};
+    const bool spans = !a.fixed && !p.all_one_row && !(one_launch && p.all_small) &&
+                       count_span_rows(a, &part, 1);
+    // Both kernels take about 4 us a row; the spans' rows are fewer where chunks leave units or
+    // workgroups short, but each piece of them takes some 6 us more.  Measured, one-launch against
+    // spans: 147 chunks of 60 to 450 KB (16 rows a unit, 7 a span) 83 and 54 us, 5 of 5 MiB (8, 6.3)
+    // 48 and 47, 3 of 5 MiB (4, 3.8) 32 and 38.
+    if (one_launch && spans) {
+        const uint64_t unit_rows = 1u << (shape.unit_power - kRowPower);
+        if (2 * unit_rows * key->wave_slots > 2 * part.rows + 3 * (uint64_t)key->wave_slots) one_launch = false;
+    }
     if (one_launch && shape.alone && a.n <= kArgChunks) return run_one_launch(key, nullptr, a, shape);
     Context* ctx = nullptr;
     if (a.fixed) {
@@ -1105,13 +1174,12 @@ int run_batch(pgcm_key* key, BatchArgs a) {
         rc = acquire_context(key, a.stream, &ctx);
         if (rc != PGCM_OK) return rc;
     }
-    KeyPart part{key, 0, a.n, 0, 0};
     if (one_launch)
         rc = run_one_launch(key, ctx, a, shape);
     else if (p.all_one_row)
         rc = run_small_batch(key, ctx, a);
-    else if (count_span_rows(a, &part, 1) && !a.fixed)
-        rc = run_span_batch(ctx, a, &part, 1, deal_groups(&part, 1, (uint32_t)key->num_cu));
+    else if (spans)
+        rc = run_span_batch(ctx, a, &part, 1);
     else
         rc = run_unit_batch(key, ctx, a, p);
     release_context(key, ctx);
@@ -1126,7 +1194,7 @@ int run_span_parts(BatchArgs a, KeyPart* parts, size_t nparts) {
     Context* ctx = nullptr;
     rc = acquire_context(key, a.stream, &ctx);
     if (rc != PGCM_OK) return rc;
-    rc = run_span_batch(ctx, a, parts, nparts, deal_groups(parts, nparts, (uint32_t)key->num_cu));
+    rc = run_span_batch(ctx, a, parts, nparts);
     release_context(key, ctx);
     return rc;
 }
@@ -1314,7 +1382,10 @@ int pgcm_reserve(pgcm_key_t* key, void* hip_stream, size_t n_max, uint64_t paylo
     int rc = acquire_context(key, stream, &ctx);
     if (rc != PGCM_OK) return rc;
     for (int s = 0; s < kStages && rc == PGCM_OK; ++s) rc = ensure_stage(ctx, s, stage_bytes);
+    const size_t num_cu = (size_t)key->num_cu;
+    if (stage_bytes < span_stage_bytes(n_max, num_cu)) stage_bytes = span_stage_bytes(n_max, num_cu);
     if (work_bytes < kSwapWorkBytes) work_bytes = kSwapWorkBytes;
+    if (work_bytes < span_work_bytes(n_max, num_cu)) work_bytes = span_work_bytes(n_max, num_cu);
     if (rc == PGCM_OK) rc = ensure_work(ctx, work_bytes, stream);
     if (rc == PGCM_OK) {
         // the context now belongs to this stream, so that the stream's batches find it

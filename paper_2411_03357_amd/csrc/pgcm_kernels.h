@@ -22,8 +22,7 @@ __global__ void bulk_kernel(const KeyTables* kt, const ChunkDesc* chunks,
 // The whole invocation of a few chunks in one launch, 2^wave_power wavefronts of units a workgroup (at
 // least four) and, below sixteen, one more.  The chunks come as arguments, or, when `staged` is not
 // null, with a descriptor per workgroup there (batch is not looked at then).
-// work: kSwapArriveWords arrival words, zero on entry and left zero, then one block per workgroup;
-// not touched if no chunk has more than one workgroup.  kRows: units of one row; kNarrow: likewise,
+// slots: one per workgroup; not touched if no chunk has more than one workgroup.  kRows: units of one row; kNarrow: likewise,
 // and the round tables take half the room (both with kRounds 0, they serve any key); kUnits: units of
 // two to sixteen rows.
 // The arguments before `batch` come in registers (compiled for that, they are the first fourteen
@@ -31,17 +30,17 @@ __global__ void bulk_kernel(const KeyTables* kt, const ChunkDesc* chunks,
 enum class SwapKind { kNarrow, kRows, kUnits };
 template <bool kDecrypt, int kRounds, SwapKind kKind>
 __global__ void swap_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t iv_len, SwapMeta meta,
-                            uint8_t* work, uint8_t* tags, uint8_t* ok, const GroupDesc* staged,
+                            ArriveSlot* slots, uint8_t* tags, uint8_t* ok, const GroupDesc* staged,
                             ArgBatch batch);
 
 // Spans of rows, one per wavefront, of chunks of one key (`key`) or of several (null; every
-// workgroup has its own in `groups`).  row_base: first row of every chunk.  slots: zero on entry.
+// workgroup has its own).  packets: stride 0: the workgroups' SpanGroup, and their parts in `parts`;
+// otherwise a workgroup's SpanGroup and its parts, at most kSpanLdsParts, every `stride` bytes,
+// and these may lie in host memory.  slots: one per part.
 template <bool kDecrypt>
-__global__ void span_kernel(const KeyTables* key, const SpanGroup* groups, const uint32_t* row_base,
-                            const SpanChunk* chunks, SpanSlot* slots, const uint8_t* ivs,
-                            uint8_t* tags, uint8_t* ok, uint32_t iv_len);
-
-__global__ void clear_words_kernel(uint32_t* words, uint32_t n);
+__global__ void span_kernel(const KeyTables* key, const uint8_t* packets, const SpanPart* parts,
+                            uint32_t stride, uint32_t iv_len, const uint8_t* ivs, ArriveSlot* slots,
+                            uint8_t* tags, uint8_t* ok);
 
 __global__ void fold_kernel(const KeyTables* kt, const FoldItem* items, uint32_t power,
                             Block* sets);
@@ -64,6 +63,7 @@ template <bool kDecrypt, int kRounds>
 __global__ void small_kernel(const KeyTables* kt, const ChunkDesc* chunks_host, uint32_t nchunks,
                              const uint8_t* ivs, uint32_t iv_len, uint8_t* tags, uint8_t* ok);
 
+// copies, and sets the n_clear pieces of sixteen bytes from `clear` on to zero
 __global__ void upload_kernel(uint4* dst, const uint4* src_host, uint32_t n16, uint4* clear,
                               uint32_t n_clear);
 

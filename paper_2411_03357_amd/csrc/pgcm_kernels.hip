@@ -2006,6 +2006,32 @@ __device__ __forceinline__ bool last_to_arrive(uint32_t* word, uint32_t of, uint
     return last;
 }
 
+// The result of workgroup g of the n of a chunk, whose slots begin at `slots`, is in `sum`.  True in
+// the workgroup that arrives last, with the sum of all results.
+__device__ __forceinline__ bool last_of_chunk(ArriveSlot* slots, uint32_t g, uint32_t n, Block& sum,
+                                              uint32_t lane) {
+    if (lane == 0)
+        store_block_device_scope(&slots[g].sum, sum.w[0], sum.w[1], sum.w[2], sum.w[3]);
+    // the result must have reached memory before the arrival is counted: it is a device-scope
+    // store, so waiting for it to complete is enough, and no cache needs writing back
+    wait_for_own_global_accesses();
+    if (n > 64) {
+        const uint32_t first = g & ~15u, in_it = n - first < 16 ? n - first : 16;
+        if (!last_to_arrive(&slots[first].arrived_of_sixteen, in_it, lane)) return false;
+    }
+    if (!last_to_arrive(&slots->arrived, n > 64 ? (n + 15) / 16 : n, lane)) return false;
+    // the others' results are read with device-scope loads, issued after the arrival count was
+    // seen: they come from memory, not from this XCD's caches
+    sum = Block{{0, 0, 0, 0}};
+    for (uint32_t i = lane; i < n; i += 64) {
+        const Block b = load_block_device_scope(&slots[i].sum);
+        block_xor(sum, b);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sum.w[k] = rows_summed(row_summed(sum.w[k]));
+    return true;
+}
+
 // this lane's share of (the length block) * H, to be summed over the lanes, from H's nibble table in
 // memory: lane p < 32 looks up nibble p
 __device__ __forceinline__ Block length_block_entry(const Block* __restrict__ h_table,
@@ -2029,15 +2055,13 @@ struct NarrowLds {
 template <bool kDecrypt, int kRounds, SwapKind kKind>
 __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
     const KeyTables* __restrict__ kt, const uint8_t* __restrict__ ivs, uint32_t iv_len,
-    SwapMeta meta, uint8_t* __restrict__ work, uint8_t* __restrict__ tags,
+    SwapMeta meta, ArriveSlot* __restrict__ slots, uint8_t* __restrict__ tags,
     uint8_t* __restrict__ ok, const GroupDesc* __restrict__ staged, const ArgBatch batch) {
     constexpr bool kNarrow = kKind == SwapKind::kNarrow, single = kKind != SwapKind::kUnits;
     using Te = std::conditional_t<kNarrow, TeNarrow, TeWide>;
     __shared__ std::conditional_t<kNarrow, NarrowLds, BulkLds> lds;
     __shared__ Block mask_lds;                   // E_K(J0), where a wavefront with units makes it
     __shared__ GfWords shares[kWavesPerGroup];
-    uint32_t* const arrive = reinterpret_cast<uint32_t*>(work);
-    Block* const slots = reinterpret_cast<Block*>(work + kSwapArriveBytes);
     const uint32_t lds_base = lds_offset(&lds);
     const uint32_t tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2268,34 +2292,12 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
         block_xor(tag, m);
     }
     // 4.
-    if (ngroups > 1) {
-        if (lane == 0) store_block_device_scope(slots + blockIdx.x, tag.w[0], tag.w[1], tag.w[2], tag.w[3]);
-        // the result must have reached memory before the arrival is counted: it is a device-scope
-        // store, so waiting for it to complete is enough, and no cache needs writing back
-        wait_for_own_global_accesses();
-        uint32_t* const main_word = arrive + group_base * kArriveStride;
-        if (ngroups <= 64) {
-            if (!last_to_arrive(main_word, ngroups, lane)) return;
-        } else {
-            const uint32_t first = g & ~15u, in_it = ngroups - first < 16 ? ngroups - first : 16;
-            if (!last_to_arrive(main_word + (kSwapMaxGroups + first) * kArriveStride, in_it, lane)) return;
-            if (!last_to_arrive(main_word, (ngroups + 15) / 16, lane)) return;
-        }
-        // the others' results are read with device-scope loads, issued after the arrival count was
-        // seen: they come from memory, not from this XCD's caches
-        tag = Block{{0, 0, 0, 0}};
-        for (uint32_t i = lane; i < ngroups; i += 64) {
-            const Block b = load_block_device_scope(slots + group_base + i);
-            block_xor(tag, b);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) tag.w[k] = rows_summed(row_summed(tag.w[k]));
-    }
+    if (ngroups > 1 && !last_of_chunk(slots + group_base, g, ngroups, tag, lane)) return;
     write_or_compare_tag<kDecrypt>(tag, tag_at, received, ok + cd.index, cd.dst, cd.len, lane);
 }
 
 #define PGCM_SWAP_SIGNATURE                                                                    \
-    (const KeyTables*, const uint8_t*, uint32_t, SwapMeta, uint8_t*, uint8_t*, uint8_t*,           \
+    (const KeyTables*, const uint8_t*, uint32_t, SwapMeta, ArriveSlot*, uint8_t*, uint8_t*,        \
      const GroupDesc*, ArgBatch)
 #define PGCM_INSTANTIATE_SWAP(D)                                                               \
     template __global__ void swap_kernel<D, 0, SwapKind::kNarrow> PGCM_SWAP_SIGNATURE;             \
@@ -2346,188 +2348,258 @@ __device__ __forceinline__ GfWords lanes_summed(const GfWords* __restrict__ powe
 }
 
 struct SpanArgs {
-    const SpanChunk* chunks;
-    SpanSlot* slots;
+    const SpanPart* parts;  // in memory, of the workgroup
     const uint8_t* ivs;
     uint32_t iv_len;
+    ArriveSlot* slots;
     uint8_t *tags, *ok;
 };
+struct SpanLds {
+    BulkLds tables;
+    Block mask[kWavesPerGroup];     // E_K(J0), by the wavefront with "block -1"
+    // results of parts that several wavefronts have rows of, at the place of the first of them, and
+    // how many of those are done
+    Block sums[kWavesPerGroup];
+    uint32_t arrived[kWavesPerGroup];
+    u32x4 packet[(sizeof(SpanGroup) + kSpanLdsParts * sizeof(SpanPart)) / 16];
 
-// rows [row, end) of the batch; `chunk` has the first of them, `slot` is to be added to a chunk's
-// number for the slot of the piece; key_word: lane i has round key word i
+    __device__ __forceinline__ const SpanGroup* group() const {
+        return reinterpret_cast<const SpanGroup*>(packet);
+    }
+    __device__ __forceinline__ const SpanPart* parts() const {
+        return reinterpret_cast<const SpanPart*>(packet + sizeof(SpanGroup) / 16);
+    }
+};
+
+// A part's descriptor in one register: lane i has its word i.
+struct PartWords {
+    uint32_t v;
+    static constexpr uint32_t kWords = sizeof(SpanPart) / 4;
+
+    __device__ __forceinline__ PartWords(const SpanLds& lds, const SpanPart* parts, uint32_t part,
+                                         uint32_t lane) {
+        v = 0;
+        if (lane >= kWords) return;
+        if (part < kSpanLdsParts)
+            v = reinterpret_cast<const uint32_t*>(lds.parts() + part)[lane];
+        else
+            v = reinterpret_cast<const uint32_t*>(parts + part)[lane];
+    }
+    template <size_t kOffset>
+    __device__ __forceinline__ uint32_t word() const {
+        return __builtin_amdgcn_readlane(v, kOffset / 4);
+    }
+    template <size_t kOffset>
+    __device__ __forceinline__ uint64_t pair() const {
+        return word<kOffset>() | (uint64_t)word<kOffset + 4>() << 32;
+    }
+};
+
+// rows [row, end) of the batch, of which the workgroup's part number `part` has the first;
+// key_word: lane i has round key word i
 template <bool kDecrypt, int kRounds>
 __device__ __forceinline__ void walk_span(const KeyTables* __restrict__ kt, uint32_t key_word,
-                                          const SpanArgs& args,
-                                          uint32_t row, uint32_t end, uint32_t chunk, uint32_t slot,
-                                          uint32_t lane_id, uint32_t wave, uint32_t lds_base,
-                                          Block* mask_lds, const Block* long_aad,
-                                          uint32_t* rows_done) {
-    Pace pace{rows_done};
+                                          const SpanArgs& args, uint32_t row, uint32_t end,
+                                          uint32_t part, uint32_t lane_id, uint32_t wave,
+                                          SpanLds& lds) {
+    Pace pace{lds.tables.rows_done};
+    const uint32_t lds_base = lds_offset(&lds.tables);
     uint32_t rk[4 * (kRounds + 1)];
 #pragma unroll
     for (int i = 0; i < 4 * (kRounds + 1); ++i) rk[i] = __builtin_amdgcn_readlane(key_word, i);
-    for (; row < end; ++chunk) {
+    for (; row < end; ++part) {
         uint32_t lane = lane_id;
         asm volatile("" : "+v"(lane));  // what depends on it is not to take registers between pieces
         AesAddr A;
         aes_addr_init<TeWide>(A, lane, rk + 4 * kRounds);
-        const SpanChunk* cd = args.chunks + chunk;
-        Block j = j0_from_iv(kt, args.ivs + (uint64_t)cd->index * args.iv_len, args.iv_len);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) j.w[k] = __builtin_amdgcn_readfirstlane(j.w[k]);
-        // to scalar registers or kept in vector ones, as in the unit kernel
-        const uint8_t* src = reinterpret_cast<const uint8_t*>(
-            same_in_all_lanes(reinterpret_cast<uint64_t>(cd->src)));
-        uint8_t* dst = reinterpret_cast<uint8_t*>(
-            same_in_all_lanes(reinterpret_cast<uint64_t>(cd->dst)));
-        AadBlocks aad = aad_blocks(cd->aad, cd->aad_len, long_aad + wave);
-        uint64_t len = cd->len;
-        asm volatile("" : "+v"(len), "+v"(aad.bytes), "+v"(aad.len), "+v"(aad.blocks));
-        const uint32_t first_row = __builtin_amdgcn_readfirstlane(cd->first_row);
-        const uint32_t to_end = first_row + __builtin_amdgcn_readfirstlane(cd->rows);
-        const uint32_t stop = to_end < end ? to_end : end;
-        const uint32_t behind = to_end - stop;  // rows of the chunk after this piece
-        const int64_t nblk = (int64_t)same_in_all_lanes((cd->len + 15) / 16);
+        const PartWords cd(lds, args.parts, part, lane);
+#define PGCM_WORD(f) cd.word<offsetof(SpanPart, f)>()
+#define PGCM_PAIR(f) cd.pair<offsetof(SpanPart, f)>()
+        Block j = j0_from_iv(kt, args.ivs + (uint64_t)PGCM_WORD(index) * args.iv_len, args.iv_len);
+        const uint32_t aad_len = PGCM_WORD(aad_len), first_row = PGCM_WORD(first_row),
+                       last_row = first_row + PGCM_WORD(rows);
+        const uint32_t stop = last_row < end ? last_row : end;
+        const uint32_t behind = last_row - stop;  // rows of the chunk after this piece
+        // the power of H that takes the piece to the chunk's end: asked for here, used after the rows
+        GfWords hop = kt->row_hop[behind % kRowHopEntries];
+        const int64_t nblk = (int64_t)((PGCM_PAIR(len) + 15) / 16);
         const int64_t b1 = nblk - (int64_t)behind * kRowBlocks;
         int64_t b0 = b1 - (int64_t)(stop - row) * kRowBlocks;
-        if (row == first_row) b0 = -(int64_t)__builtin_amdgcn_readfirstlane(lead_blocks(cd->aad_len));
+        if (row == first_row) b0 = -(int64_t)lead_blocks(aad_len);
+        // scalar registers are short: what only edge rows look at is kept in vector registers
+        AadBlocks aad = aad_blocks(reinterpret_cast<const uint8_t*>(PGCM_PAIR(aad)), aad_len,
+                                   lds.tables.long_aad + wave);
+        uint64_t len = PGCM_PAIR(len);
+        asm volatile("" : "+v"(len), "+v"(aad.bytes), "+v"(aad.len), "+v"(aad.blocks));
         if (b0 < 0) aad.prepare(kt->ghash[0]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) j.w[k] = __builtin_amdgcn_readfirstlane(j.w[k]);
         uint32_t y[4];
         walk_unit<kDecrypt, kRounds, kDecrypt, false>(
-            rk, A, lane, wave, lds_base, src, dst, len, b0, b1, behind == 0, aad, j, pace,
+            rk, A, lane, wave, lds_base, reinterpret_cast<const uint8_t*>(PGCM_PAIR(src)),
+            reinterpret_cast<uint8_t*>(PGCM_PAIR(dst)), len, b0, b1, behind == 0, aad, j, pace,
             [&](uint32_t s0, uint32_t s1, uint32_t s2, uint32_t s3) __attribute__((always_inline)) {
-                mask_lds[wave] = Block{{s0, s1, s2, s3}};
+                lds.mask[wave] = Block{{s0, s1, s2, s3}};
             },
             y);
+        row = stop;
         GfWords sum = lanes_summed(kt->dot[lane], y);
-        asm volatile("" : "+s"(cd));  // what is needed only from here on is loaded only here
         if (behind % kRowHopEntries != 0) {
-            GfWords hop = kt->row_hop[behind % kRowHopEntries];
             spread_over_row(hop, lane);
             sum = times_spread(sum, hop, lane);
         }
         if (behind >= kRowHopEntries) {
-            GfWords hop = kt->far_hop[behind / kRowHopEntries];
+            hop = kt->far_hop[behind / kRowHopEntries];
             spread_over_row(hop, lane);
             sum = times_spread(sum, hop, lane);
         }
         Block tag = gfw_to_block(sum);
         if (b0 < 0 && b1 >= 0) {
             // the piece with "block -1": the length block's product and E_K(J0)
-            Block extra = length_block_entry(kt->ghash[0], cd->aad_len, cd->len, lane);
+            Block extra = length_block_entry(kt->ghash[0], PGCM_WORD(aad_len), PGCM_PAIR(len), lane);
 #pragma unroll
             for (int k = 0; k < 4; ++k) extra.w[k] = rows_summed(row_summed(extra.w[k]));
             block_xor(tag, extra);
-            const Block m = mask_lds[wave];
+            const Block m = lds.mask[wave];
             block_xor(tag, m);
         }
-        uint8_t* const tag_at = args.tags + (uint64_t)cd->index * 16;
+        const uint32_t waves = PGCM_WORD(waves) >> 8, slots = PGCM_WORD(slots);
+        uint8_t* const tag_at = args.tags + (uint64_t)PGCM_WORD(index) * 16;
         Block received{{0, 0, 0, 0}};  // asked for here: on its way while the arrival is counted
-        if (kDecrypt) received = global_read_block_any(tag_at);
-        bool last = true;
-        const uint32_t n = cd->pieces;
-        if (n > 1) {
-            SpanSlot* const first = args.slots + cd->slot;
-            SpanSlot* const mine = args.slots + slot + chunk;
+        if (kDecrypt) {
+            received = global_read_block_any(tag_at);
+            // the plaintext is in memory before the piece counts as done: whoever finishes the chunk may
+            // have to wipe it
+            if (waves > 1 || slots > 1) wait_for_own_global_accesses();
+        }
+        if (waves > 1) {
+            // LDS serves a wavefront's accesses in order: the sum is there before the count
+            const uint32_t at = PGCM_WORD(waves) & 0xFF;
+            const uint32_t word = lane == 0 ? tag.w[0] : lane == 1 ? tag.w[1] : lane == 2 ? tag.w[2] : tag.w[3];
+            uint32_t before = 0;
+            if (lane < 4)
+                __hip_atomic_fetch_xor(&lds.sums[at].w[lane], word, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+            asm volatile("" ::: "memory");
             if (lane == 0)
-                store_block_device_scope(&mine->sum, tag.w[0], tag.w[1], tag.w[2], tag.w[3]);
-            // result and plaintext have reached memory before the arrival is counted
-            wait_for_own_global_accesses();
-            if (n <= 64) {
-                last = last_to_arrive(&first->arrived, n, lane);
-            } else {
-                const uint32_t at = (uint32_t)(mine - first) & ~15u, in_it = n - at < 16 ? n - at : 16;
-                last = last_to_arrive(&first[at].arrived_of_sixteen, in_it, lane) &&
-                       last_to_arrive(&first->arrived, (n + 15) / 16, lane);
-            }
-            if (last) {
-                tag = Block{{0, 0, 0, 0}};
-                for (uint32_t i = lane; i < n; i += 64) {
-                    const Block b = load_block_device_scope(&first[i].sum);
-                    block_xor(tag, b);
-                }
-#pragma unroll
-                for (int k = 0; k < 4; ++k) tag.w[k] = rows_summed(row_summed(tag.w[k]));
-            }
+                before = __hip_atomic_fetch_add(&lds.arrived[at], 1u, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (__builtin_amdgcn_readfirstlane(before) + 1 != waves) continue;
+            asm volatile("" ::: "memory");
+            tag = lds.sums[at];
         }
-        if (last) {
-            write_or_compare_tag<kDecrypt>(tag, tag_at, received, args.ok + cd->index, cd->dst,
-                                           cd->len, lane);
+        if (slots > 1) {
+            const uint32_t slot = PGCM_WORD(slot);
+            if (!last_of_chunk(args.slots + slot, PGCM_WORD(own_slot) - slot, slots, tag, lane)) continue;
         }
-        row = stop;
+        write_or_compare_tag<kDecrypt>(tag, tag_at, received, args.ok + PGCM_WORD(index),
+                                       reinterpret_cast<uint8_t*>(PGCM_PAIR(dst)), PGCM_PAIR(len), lane);
+#undef PGCM_WORD
+#undef PGCM_PAIR
     }
 }
 
 }  // namespace
 
-// key: the batch's key, or null: every workgroup has its own
 template <bool kDecrypt>
 __global__ __launch_bounds__(kGroupThreads) void span_kernel(
-    const KeyTables* __restrict__ key, const SpanGroup* __restrict__ groups,
-    const uint32_t* __restrict__ row_base, const SpanChunk* __restrict__ chunks,
-    SpanSlot* __restrict__ slots, const uint8_t* __restrict__ ivs, uint8_t* __restrict__ tags,
-    uint8_t* __restrict__ ok, uint32_t iv_len) {
-    __shared__ BulkLds lds;
-    __shared__ Block mask_lds[kWavesPerGroup];
-    const uint32_t lds_base = lds_offset(&lds);
+    const KeyTables* __restrict__ key, const uint8_t* __restrict__ packets,
+    const SpanPart* __restrict__ all_parts, uint32_t stride, uint32_t iv_len,
+    const uint8_t* __restrict__ ivs, ArriveSlot* __restrict__ slots, uint8_t* __restrict__ tags,
+    uint8_t* __restrict__ ok) {
+    __shared__ SpanLds lds;
     const uint32_t tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const SpanGroup* __restrict__ gd = groups + blockIdx.x;
-    const KeyTables* __restrict__ kt = key != nullptr ? key : gd->kt;
-    // The tables are asked for, then what the first piece needs, in the rounds of loads that take:
-    // they overlap, and the loads that walk_span repeats find their lines in the caches.
+
+    // Everything is asked for at once: the tables, if the key is known already, and the descriptors, by
+    // the first wavefronts only, as they may come from host memory.
+    const KeyTables* __restrict__ kt = key;
     TeFill<TeWide, kGroupThreads> te;
-    te.fetch(kt, tid);
-    Block gh{{0, 0, 0, 0}};
-    if (tid < kNibbleTableEntries) gh = kt->ghash[kRowPower][tid];
-    const uint32_t key_word = lane < 60 ? kt->rk[lane] : 0u;
-    const uint32_t rounds = __builtin_amdgcn_readfirstlane(kt->rounds);
-    // the workgroup's rows dealt to its wavefronts, none without any before one that has some
-    const uint32_t rows = gd->rows, waves = rows < kWavesPerGroup ? rows : kWavesPerGroup;
-    const uint32_t place = wave < waves ? wave : waves - 1;
-    const uint32_t row = gd->first_row + rows * place / waves;
-    const uint32_t end = gd->first_row + rows * (place + 1) / waves;
-    // its first chunk: the last one that does not begin behind `row`
-    uint32_t chunk = gd->chunk;
-    for (uint32_t i = 1; i < gd->nchunks; i += 64) {
-        const bool begins = i + lane < gd->nchunks && row_base[gd->chunk + i + lane] <= row;
-        const uint32_t more = __builtin_amdgcn_readfirstlane((uint32_t)__popcll(__ballot(begins)));
-        chunk += more;
-        if (more < 64) break;
+    u32x4 gh{};
+    uint32_t key_word = 0;
+    auto fetch_tables = [&]() __attribute__((always_inline)) {
+        te.fetch(kt, tid);
+        // the threads without an entry of the row hash bring what the end needs into the caches: a
+        // line each of the powers and of H's table
+        const uint32_t t = tid - kNibbleTableEntries;
+        const uint8_t* const from =
+            tid < kNibbleTableEntries ? reinterpret_cast<const uint8_t*>(&kt->ghash[kRowPower][tid])
+            : t < sizeof(kt->dot) / 128 ? reinterpret_cast<const uint8_t*>(kt->dot) + t * 128
+                                        : reinterpret_cast<const uint8_t*>(kt->ghash[0]) + t % 64 * 128;
+        gh = global_read128(from);
+        key_word = lane < 60 ? kt->rk[lane] : lane == 60 ? kt->rounds : 0u;
+    };
+    if (key != nullptr) fetch_tables();
+    const SpanPart* parts = nullptr;
+    if (stride != 0) {
+        if (tid < stride / 16)
+            lds.packet[tid] = reinterpret_cast<const u32x4*>(packets + (uint64_t)blockIdx.x * stride)[tid];
+    } else {
+        constexpr uint32_t kGroup16 = sizeof(SpanGroup) / 16, kPart16 = sizeof(SpanPart) / 16;
+        const SpanGroup* const gd = reinterpret_cast<const SpanGroup*>(packets) + blockIdx.x;
+        parts = all_parts + gd->part;
+        const uint32_t n = gd->nparts < kSpanLdsParts ? gd->nparts : kSpanLdsParts;
+        if (tid < kGroup16)
+            lds.packet[tid] = reinterpret_cast<const u32x4*>(gd)[tid];
+        else if (tid < kGroup16 + n * kPart16)
+            lds.packet[tid] = reinterpret_cast<const u32x4*>(parts)[tid - kGroup16];
     }
-    const uint8_t* iv = ivs + (uint64_t)chunks[chunk].index * iv_len;
-    const uint32_t touched = (uint32_t)global_read8(iv) + global_read8(iv + iv_len - 1);
-    te.store(lds.te, tid);
-    if (tid < kNibbleTableEntries) lds.gh[tid] = gh;
-    if (tid == 0) lds.rows_done[0] = 0;
-    asm volatile("" : : "v"(touched));
+    if (tid == 0) lds.tables.rows_done[0] = 0;
+    if (tid < kWavesPerGroup) {
+        lds.sums[tid] = Block{{0, 0, 0, 0}};
+        lds.arrived[tid] = 0;
+    }
+    const SpanGroup* const group = lds.group();
+    if (key == nullptr) {
+        __syncthreads();
+        kt = reinterpret_cast<const KeyTables*>(same_in_all_lanes(reinterpret_cast<uint64_t>(group->kt)));
+        fetch_tables();
+    }
+    te.store(lds.tables.te, tid);
+    if (tid < kNibbleTableEntries)
+        reinterpret_cast<u32x4*>(lds.tables.gh)[tid] = gh;
+    else
+        asm volatile("" : : "v"(gh));
     __syncthreads();
 
+    // the workgroup's rows dealt to its wavefronts
+    const uint32_t rows = __builtin_amdgcn_readfirstlane(group->rows);
+    const uint32_t waves = rows < kWavesPerGroup ? rows : kWavesPerGroup;
     if (wave >= waves) return;
-    const SpanArgs args{chunks, slots, ivs, iv_len, tags, ok};
-    const uint32_t slot = gd->first_wave + wave;
+    const uint32_t first_row = __builtin_amdgcn_readfirstlane(group->first_row);
+    const uint32_t row = first_row + rows * wave / waves;
+    const uint32_t end = first_row + rows * (wave + 1) / waves;
+    // its first part: the last one that does not begin behind `row`
+    const uint32_t nparts = __builtin_amdgcn_readfirstlane(group->nparts);
+    uint32_t part = 0;
+    for (uint32_t i = 1; i < nparts; i += 64) {
+        bool begins = false;
+        if (i + lane < nparts) {
+            const uint32_t first = i + lane < kSpanLdsParts ? lds.parts()[i + lane].first_row
+                                                            : parts[i + lane].first_row;
+            begins = first <= row;
+        }
+        const uint32_t more = __builtin_amdgcn_readfirstlane((uint32_t)__popcll(__ballot(begins)));
+        part += more;
+        if (more < 64) break;
+    }
+    const SpanArgs args{parts, ivs, iv_len, slots, tags, ok};
+    const uint32_t rounds = __builtin_amdgcn_readlane(key_word, 60);
     if (rounds == 14)
-        walk_span<kDecrypt, 14>(kt, key_word, args, row, end, chunk, slot, lane, wave, lds_base, mask_lds,
-                             lds.long_aad, lds.rows_done);
+        walk_span<kDecrypt, 14>(kt, key_word, args, row, end, part, lane, wave, lds);
     else if (rounds == 12)
-        walk_span<kDecrypt, 12>(kt, key_word, args, row, end, chunk, slot, lane, wave, lds_base, mask_lds,
-                             lds.long_aad, lds.rows_done);
+        walk_span<kDecrypt, 12>(kt, key_word, args, row, end, part, lane, wave, lds);
     else
-        walk_span<kDecrypt, 10>(kt, key_word, args, row, end, chunk, slot, lane, wave, lds_base, mask_lds,
-                             lds.long_aad, lds.rows_done);
+        walk_span<kDecrypt, 10>(kt, key_word, args, row, end, part, lane, wave, lds);
 }
 
-#define PGCM_INSTANTIATE_SPAN(D)                                                                 \
-    template __global__ void span_kernel<D>(const KeyTables*, const SpanGroup*, const uint32_t*, \
-                                            const SpanChunk*, SpanSlot*, const uint8_t*, uint8_t*, \
-                                            uint8_t*, uint32_t)
+#define PGCM_INSTANTIATE_SPAN(D)                                                                  \
+    template __global__ void span_kernel<D>(const KeyTables*, const uint8_t*, const SpanPart*,    \
+                                            uint32_t, uint32_t, const uint8_t*, ArriveSlot*,      \
+                                            uint8_t*, uint8_t*)
 PGCM_INSTANTIATE_SPAN(false);
 PGCM_INSTANTIATE_SPAN(true);
 #undef PGCM_INSTANTIATE_SPAN
-
-__global__ __launch_bounds__(1024) void clear_words_kernel(uint32_t* __restrict__ words, uint32_t n) {
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) words[i] = 0;
-}
 
 // ------------------------------------------------------------------------------------------
 // The small-transfer path: a batch whose chunks are all at most kSmallChunkBytes long (the

@@ -163,11 +163,16 @@ struct ArgBatch {
 // Workgroups of a chunk (KeyTables::hop has their distances) and of a launch.
 constexpr uint32_t kSwapChunkGroups = kHopEntries;
 constexpr uint32_t kSwapMaxGroups = 512;
-// Arrival words, 64 bytes apart: a chunk's is that of its first workgroup; the workgroups of a chunk
-// of many are counted in sixteens first, on the words of every sixteenth in the upper half.
-constexpr uint32_t kArriveStride = 16;
-constexpr uint32_t kSwapArriveWords = 2 * kSwapMaxGroups * kArriveStride;
-constexpr uint32_t kSwapArriveBytes = 4 * kSwapArriveWords;
+// A workgroup's result and, in the slot of a chunk's first workgroup, the number of those that have
+// arrived; of a chunk with many, they are counted in sixteens first, in the slot of every sixteenth.
+// The counts are zero between batches.
+struct alignas(64) ArriveSlot {
+    uint32_t arrived, arrived_of_sixteen;
+    uint32_t pad_[2];
+    Block sum;
+    uint32_t pad2_[8];
+};
+static_assert(sizeof(ArriveSlot) == 64, "counters of different chunks are not to share a cache line");
 // What a workgroup has to know first, in one word: it travels in a register.
 struct SwapMeta {
     uint32_t w;
@@ -199,38 +204,32 @@ struct alignas(16) GroupDesc {
 };
 
 // Spans: the rows of all chunks of a batch, each chunk's counted back from its end and the blocks
-// before its block 0 among them, are numbered through, and every wavefront takes its share of them,
-// cutting chunks wherever its share ends.  The part of one chunk in one wavefront's span is a piece.
+// before its block 0 among them, are numbered through.  Every workgroup takes its share of them, dealt
+// out to its wavefronts, and chunks are cut wherever a share ends.
 struct alignas(16) SpanGroup {      // a workgroup
     const KeyTables* kt;
     uint32_t first_row, rows;       // its rows
-    uint32_t chunk, nchunks;        // the chunk of the first one; the chunks it has rows of
-    uint32_t first_wave;            // wavefronts with rows are numbered through as well
-    uint32_t pad_;
+    uint32_t part, nparts;          // where its chunks are described, if not right behind this
+    uint32_t pad_[2];
 };
 static_assert(sizeof(SpanGroup) == 32, "descriptor layout");
-struct alignas(16) SpanChunk {
+struct alignas(16) SpanPart {       // a chunk as far as one workgroup has rows of it
     const uint8_t* src;
     uint8_t* dst;
     const uint8_t* aad;
     uint64_t len;
     uint32_t aad_len;
     uint32_t index;                 // the chunk's place in the caller's ivs, tags and ok arrays
-    uint32_t first_row, rows;
-    uint32_t slot, pieces;          // its pieces have consecutive slots from `slot`
-    uint32_t pad_[2];
+    uint32_t first_row, rows;       // of the whole chunk
+    uint32_t slot, slots;           // its workgroups, of which it may have several, have
+    uint32_t own_slot;              // consecutive slots from `slot`; this one's
+    uint32_t waves;                 // this one's wavefronts with rows of it, << 8; the first of them
 };
-static_assert(sizeof(SpanChunk) == 64, "descriptor layout");
-// A piece's result and, in the slot of a chunk's first piece, the count of the chunk's pieces that
-// are done (of many pieces, they are counted in sixteens first, in the slot of the first of them).
-struct alignas(64) SpanSlot {
-    Block sum;
-    uint32_t arrived, arrived_of_sixteen;
-    uint32_t pad_[10];
-};
-static_assert(sizeof(SpanSlot) == 64, "a cache line each");
+static_assert(sizeof(SpanPart) == 64, "descriptor layout");
+// The parts of a workgroup that are held in LDS; those of longer lists are read from memory.
+constexpr uint32_t kSpanLdsParts = 31;
 
-// A batch whose chunks are all at most this long takes the small-transfer path: one kernel (the
+// A batch whose chunks are all at most this long takes// A batch whose chunks are all at most this long takes the small-transfer path: one kernel (the
 // paper's non-swap transfers are usually < 8 KB, section 4.2): eight rows of 64 blocks.
 constexpr uint64_t kSmallChunkBytes = 8192;
 // The one-launch kernel is there for the latency of a few transfers, a workgroup each; of more
