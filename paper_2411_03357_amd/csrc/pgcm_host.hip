@@ -918,6 +918,10 @@ int run_unit_batch(pgcm_key* key, Context* ctx, const BatchArgs& a, const BatchP
 
 // ---- Spans (span_kernel) ----
 
+// What one more piece costs a workgroup, in rows: it ends 2 us later for it, 0.27 for a row more (300
+// adapters both ways with 2, 8: 198, 191 us).
+constexpr uint32_t kPieceRows = 8;
+
 // One key's chunks of a batch: n of them from the batch's chunk `first` on.
 struct KeyPart {
     pgcm_key* key;
@@ -925,8 +929,7 @@ struct KeyPart {
     uint64_t rows;
     uint32_t groups;  // workgroups
 
-    // what the rows cost, in rows: finishing a piece takes about as long as one
-    uint64_t weight() const { return rows + n; }
+    uint64_t weight() const { return rows + kPieceRows * n; }
 };
 
 inline uint64_t span_rows(const BatchArgs& a, size_t i) {
@@ -1009,8 +1012,9 @@ void plan_spans(const BatchArgs& a, const KeyPart* keys, size_t nkeys, SpanPlan*
             c.waves = 0;
             // the workgroups that begin in this chunk: the one before has its part before theirs
             bool begun = false;
-            while (groups.size() < first_group + key.groups && next < weight + c.rows + 1) {
-                const uint32_t at = next > weight ? row + (uint32_t)(next - weight) - 1 : row;
+            while (groups.size() < first_group + key.groups && next < weight + c.rows + kPieceRows) {
+                const uint32_t at =
+                    next > weight + kPieceRows ? row + (uint32_t)(next - weight - kPieceRows) : row;
                 if (at > row && !begun) {
                     c.own_slot = (uint32_t)parts.size();
                     parts.push_back(c);
@@ -1028,7 +1032,7 @@ void plan_spans(const BatchArgs& a, const KeyPart* keys, size_t nkeys, SpanPlan*
             for (size_t p = c.slot; p < parts.size(); ++p)
                 parts[p].slots = (uint32_t)parts.size() - c.slot;
             row += c.rows;
-            weight += c.rows + 1;
+            weight += c.rows + kPieceRows;
         }
         for (size_t g = first_group; g < groups.size(); ++g) {
             const bool more = g + 1 < groups.size();
@@ -1157,13 +1161,14 @@ int run_batch(pgcm_key* key, BatchArgs a) {
     KeyPart part{key, 0, a.n, 0, 0};
     const bool spans = !a.fixed && !p.all_one_row && !(one_launch && p.all_small) &&
                        count_span_rows(a, &part, 1);
-    // Both kernels take about 4 us a row; the spans' rows are fewer where chunks leave units or
-    // workgroups short, but each piece of them takes some 6 us more.  Measured, one-launch against
-    // spans: 147 chunks of 60 to 450 KB (16 rows a unit, 7 a span) 83 and 54 us, 5 of 5 MiB (8, 6.3)
-    // 48 and 47, 3 of 5 MiB (4, 3.8) 32 and 38.
-    if (one_launch && spans) {
+    // Where units or workgroups are left short, spans have fewer rows for a wavefront, but they begin
+    // and end later.  With sixteen wavefronts a workgroup, a batch of one launch takes 14 us and
+    // 4.3 a row of its units, with eight 12 and 2.4; spans take 25 and 3.6 a row (147 chunks of
+    // 60 to 450 KB: units of 16 rows, spans of 7, 83 and 54 us; 3 of 5 MiB: 4 and 3.8, 32 and 38).
+    if (one_launch && spans && shape.wave_power == 4) {
         const uint64_t unit_rows = 1u << (shape.unit_power - kRowPower);
-        if (2 * unit_rows * key->wave_slots > 2 * part.rows + 3 * (uint64_t)key->wave_slots) one_launch = false;
+        if (43 * unit_rows * key->wave_slots > 110 * (uint64_t)key->wave_slots + 36 * part.rows)
+            one_launch = false;
     }
     if (one_launch && shape.alone && a.n <= kArgChunks) return run_one_launch(key, nullptr, a, shape);
     Context* ctx = nullptr;
