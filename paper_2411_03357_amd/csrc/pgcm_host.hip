@@ -106,13 +106,6 @@ inline uint32_t choose_unit_power(size_t n, const uint32_t* order, const uint64_
 
 namespace {
 
-// How a batch is cut into spans: the workgroups' shares and what each has of which chunk.
-struct SpanPlan {
-    std::vector<SpanGroup> groups;
-    std::vector<SpanPart> parts;
-    uint32_t longest = 0;  // list of parts of a workgroup
-};
-
 // What one batch in flight needs besides the key's tables: pinned staging buffers for the
 // descriptors the host writes, and the device workspace the kernels of the batch share.  Batches
 // that use one context are ordered by the stream the context is bound to, which is what makes
@@ -132,7 +125,7 @@ struct Context {
     uint32_t* counter_at = nullptr;  // where the unit counter was last known to be zero
     bool counter_dirty = true;
     size_t clean_slots = 0;  // so many ArriveSlots at the start of `work` have counts of zero
-    SpanPlan plan;           // of the call that is using the context
+    std::vector<uint8_t> image;  // descriptors of the call that is using the context
     // binding
     hipStream_t stream = nullptr;
     bool bound = false;        // has run a batch on `stream`
@@ -457,10 +450,37 @@ inline void describe_chunk(const BatchArgs& a, size_t i, ChunkDesc& d) {
     d.index = (uint32_t)i;
 }
 
-// Sizes of a batch's schedule; filled by plan_batch, which also validates every chunk.
+inline uint64_t span_rows(const BatchArgs& a, size_t i) {
+    const uint64_t blocks = (a.len[i] + 15) / 16 + lead_blocks(a.aad_len ? a.aad_len[i] : 0);
+    return (blocks + kRowBlocks - 1) / kRowBlocks;
+}
+
+// What decides which way a batch goes.
+struct BatchSurvey {
+    bool all_small = true;     // every chunk fits the small-transfer path
+    bool all_one_row = true;   // ... and its one-wavefront-per-chunk kernel
+    uint64_t rows = 0;         // in spans
+    uint64_t longest = 0;      // in bytes
+};
+
+// ... found while every chunk is validated
+int survey_batch(const BatchArgs& a, BatchSurvey* out) {
+    BatchSurvey v;
+    for (size_t k = 0; k < a.n; ++k) {
+        const size_t i = a.at(k);
+        const int rc = check_chunk(a, i);
+        if (rc != PGCM_OK) return rc;
+        if (a.len[i] > v.longest) v.longest = a.len[i];
+        v.rows += span_rows(a, i);
+    }
+    v.all_small = v.longest <= kSmallChunkBytes;
+    v.all_one_row = v.longest <= kSmallRowBytes;
+    *out = v;
+    return PGCM_OK;
+}
+
+// Sizes of a batch's schedule of units; filled by plan_batch.
 struct BatchPlan {
-    bool all_small;       // every chunk fits the small-transfer path
-    bool all_one_row;     // ... and its one-wavefront-per-chunk kernel
     uint32_t unit_power;  // log2 of the blocks per unit
     uint32_t nunits;
     uint32_t nslots;      // partial sets: one per unit and one per fold output
@@ -473,15 +493,10 @@ int plan_batch(uint32_t forced_unit_power, uint32_t wave_slots, const BatchArgs&
                BatchPlan* plan) {
     plan->unit_power = forced_unit_power ? forced_unit_power
                                          : choose_unit_power(a.n, a.order, a.len, wave_slots);
-    plan->all_small = plan->all_one_row = true;
     uint64_t nunits = 0, nslots = 0;
     uint64_t fold_items[kMaxLevels] = {0, 0, 0, 0};
     for (size_t k = 0; k < a.n; ++k) {
         const size_t i = a.at(k);
-        const int rc = check_chunk(a, i);
-        if (rc != PGCM_OK) return rc;
-        if (a.len[i] > kSmallChunkBytes) plan->all_small = false;
-        if (a.len[i] > kSmallRowBytes) plan->all_one_row = false;
         const uint32_t nu = plan_chunk(a.len[i], plan->unit_power).nunits;
         uint32_t outs[kMaxLevels];
         const uint32_t levels = fold_levels(nu, outs);
@@ -932,26 +947,11 @@ struct KeyPart {
     uint64_t weight() const { return rows + kPieceRows * n; }
 };
 
-inline uint64_t span_rows(const BatchArgs& a, size_t i) {
-    const uint64_t blocks = (a.len[i] + 15) / 16 + lead_blocks(a.aad_len ? a.aad_len[i] : 0);
-    return (blocks + kRowBlocks - 1) / kRowBlocks;
-}
-
-// Counts the rows of every part.  False if the batch is not one for spans.
-bool count_span_rows(const BatchArgs& a, KeyPart* parts, size_t nparts) {
-    uint64_t total = 0;
-    for (size_t q = 0; q < nparts; ++q) {
-        const pgcm_key* key = parts[q].key;
-        if (!key->one_launch || key->matrix_hash || key->forced_unit_power) return false;
-        parts[q].rows = 0;
-        for (size_t k = parts[q].first; k < parts[q].first + parts[q].n; ++k) {
-            const uint64_t rows = span_rows(a, a.at(k));
-            if (rows > (uint64_t)kRowHopEntries * kFarHopEntries) return false;
-            parts[q].rows += rows;
-        }
-        total += parts[q].rows;
-    }
-    return total <= kSpanMaxRows;
+// May a batch of chunks of at most this length, and this many rows in all, go in spans?  (The bounds
+// are those of the powers of H a key has and of 32-bit row numbers.)
+inline bool takes_spans(const pgcm_key* key, const BatchSurvey& v) {
+    return key->one_launch && !key->matrix_hash && !key->forced_unit_power && v.rows <= kSpanMaxRows &&
+           v.longest / (16 * kRowBlocks) + 2 < (uint64_t)kRowHopEntries * kFarHopEntries;
 }
 
 // Deals the compute units out to the parts, a workgroup each, so that the one with the most work per
@@ -985,15 +985,17 @@ uint32_t deal_groups(KeyPart* parts, size_t nparts, uint32_t num_cu) {
 }
 
 // Cuts the keys' chunks.
-void plan_spans(const BatchArgs& a, const KeyPart* keys, size_t nkeys, SpanPlan* plan) {
-    std::vector<SpanGroup>& groups = plan->groups;
-    std::vector<SpanPart>& parts = plan->parts;
-    groups.clear();
-    parts.clear();
-    uint32_t row = 0;
+// parts: room for n and the number of workgroups.
+struct SpanPlan {
+    uint32_t nparts;
+    uint32_t longest;  // list of parts of a workgroup
+};
+SpanPlan plan_spans(const BatchArgs& a, const KeyPart* keys, size_t nkeys, SpanGroup* groups,
+                    SpanPart* parts) {
+    uint32_t row = 0, group = 0, np = 0;
     for (size_t q = 0; q < nkeys; ++q) {
         const KeyPart& key = keys[q];
-        const size_t first_group = groups.size();
+        const uint32_t first_group = group, end_group = group + key.groups;
         // a workgroup begins where the weight so far reaches its share; a chunk's own weight comes
         // before its rows'
         uint64_t weight = 0, next = 0;
@@ -1008,41 +1010,38 @@ void plan_spans(const BatchArgs& a, const KeyPart* keys, size_t nkeys, SpanPlan*
             c.index = (uint32_t)i;
             c.first_row = row;
             c.rows = (uint32_t)span_rows(a, i);
-            c.slot = (uint32_t)parts.size();
+            c.slot = c.own_slot = np;
+            c.slots = 1;
             c.waves = 0;
-            // the workgroups that begin in this chunk: the one before has its part before theirs
-            bool begun = false;
-            while (groups.size() < first_group + key.groups && next < weight + c.rows + kPieceRows) {
-                const uint32_t at =
-                    next > weight + kPieceRows ? row + (uint32_t)(next - weight - kPieceRows) : row;
-                if (at > row && !begun) {
-                    c.own_slot = (uint32_t)parts.size();
-                    parts.push_back(c);
+            const uint64_t weight_end = weight + c.rows + kPieceRows;
+            if (group == end_group || next >= weight_end) {
+                parts[np++] = c;
+            } else {
+                // workgroups begin in this chunk: the one before has its part before theirs
+                while (group < end_group && next < weight_end) {
+                    const uint32_t at =
+                        next > weight + kPieceRows ? row + (uint32_t)(next - weight - kPieceRows) : row;
+                    if (at > row && np == c.slot) parts[np++] = c;
+                    c.own_slot = np;
+                    groups[group++] = SpanGroup{key.key->tables, at, 0, np, 0, {0, 0}};
+                    parts[np++] = c;
+                    next = key.weight() * (group - first_group) / key.groups;
                 }
-                begun = true;
-                c.own_slot = (uint32_t)parts.size();
-                groups.push_back(SpanGroup{key.key->tables, at, 0, c.own_slot, 0, {0, 0}});
-                parts.push_back(c);
-                next = key.weight() * (groups.size() - first_group) / key.groups;
+                for (uint32_t p = c.slot; p < np; ++p) parts[p].slots = np - c.slot;
             }
-            if (!begun) {
-                c.own_slot = (uint32_t)parts.size();
-                parts.push_back(c);
-            }
-            for (size_t p = c.slot; p < parts.size(); ++p)
-                parts[p].slots = (uint32_t)parts.size() - c.slot;
             row += c.rows;
-            weight += c.rows + kPieceRows;
+            weight = weight_end;
         }
-        for (size_t g = first_group; g < groups.size(); ++g) {
-            const bool more = g + 1 < groups.size();
+        for (uint32_t g = first_group; g < group; ++g) {
+            const bool more = g + 1 < group;
             groups[g].rows = (more ? groups[g + 1].first_row : row) - groups[g].first_row;
-            groups[g].nparts = (more ? groups[g + 1].part : (uint32_t)parts.size()) - groups[g].part;
+            groups[g].nparts = (more ? groups[g + 1].part : np) - groups[g].part;
         }
     }
-    plan->longest = 0;
-    for (const SpanGroup& g : groups) {
-        if (g.nparts > plan->longest) plan->longest = g.nparts;
+    SpanPlan plan{np, 0};
+    for (uint32_t i = 0; i < group; ++i) {
+        const SpanGroup& g = groups[i];
+        if (g.nparts > plan.longest) plan.longest = g.nparts;
         // the wavefront of row r of the workgroup
         const uint32_t waves = g.rows < kWavesPerGroup ? g.rows : kWavesPerGroup;
         auto wave_of = [&](uint32_t r) { return ((r + 1) * waves - 1) / g.rows; };
@@ -1054,6 +1053,7 @@ void plan_spans(const BatchArgs& a, const KeyPart* keys, size_t nkeys, SpanPlan*
             c.waves = (last - first + 1) << 8 | first;
         }
     }
+    return plan;
 }
 
 // Bytes of descriptors up to which the workgroups read theirs from host memory themselves.
@@ -1070,47 +1070,53 @@ inline size_t span_work_bytes(size_t n, size_t num_cu) {
 
 // One batch in spans, of one key or of several: the context is that of the first.
 int run_span_batch(Context* ctx, const BatchArgs& a, KeyPart* keys, size_t nkeys) {
-    SpanPlan& plan = ctx->plan;
     const uint32_t ngroups = deal_groups(keys, nkeys, (uint32_t)keys[0].key->num_cu);
-    try {
-        plan_spans(a, keys, nkeys, &plan);
-    } catch (const std::bad_alloc&) {
-        return PGCM_ERR_NOMEM;
-    }
-    // each workgroup's list right behind its descriptor, to be read from host memory, if they are few
-    // and of much the same length; otherwise uploaded, one list after the other
-    size_t stride = sizeof(SpanGroup) + sizeof(SpanPart) * plan.longest;
-    const bool in_host = plan.longest <= kSpanLdsParts && stride * ngroups <= kSpanHostBytes;
     const size_t parts_at = round_up(sizeof(SpanGroup) * ngroups, 256);
-    const size_t bytes = in_host ? stride * ngroups
-                                 : round_up(parts_at + sizeof(SpanPart) * plan.parts.size(), 256);
-    const size_t nslots = plan.parts.size();
+    const size_t most = parts_at + round_up(sizeof(SpanPart) * (a.n + ngroups), 256);
     const int s = ctx->next_stage;
-    int rc = ensure_stage(ctx, s, bytes);
+    int rc = ensure_stage(ctx, s, most > kSpanHostBytes ? most : kSpanHostBytes);
     if (rc != PGCM_OK) return rc;
+    // Each workgroup's list right behind its descriptor, to be read from host memory, if they are few
+    // and of much the same length; otherwise uploaded, one list after the other.
+    uint8_t* const stage = ctx->stage[s];
+    uint8_t* image = stage;
+    if (most <= kSpanHostBytes) {
+        try {
+            ctx->image.resize(kSpanHostBytes);
+        } catch (const std::bad_alloc&) {
+            return PGCM_ERR_NOMEM;
+        }
+        image = ctx->image.data();
+    }
+    SpanGroup* const groups = reinterpret_cast<SpanGroup*>(image);
+    SpanPart* const all_parts = reinterpret_cast<SpanPart*>(image + parts_at);
+    const SpanPlan plan = plan_spans(a, keys, nkeys, groups, all_parts);
+    size_t stride = sizeof(SpanGroup) + sizeof(SpanPart) * plan.longest;
+    const bool in_host =
+        image != stage && plan.longest <= kSpanLdsParts && stride * ngroups <= kSpanHostBytes;
+    const size_t bytes = in_host ? 0 : parts_at + round_up(sizeof(SpanPart) * plan.nparts, 256);
     // the descriptors go behind every slot that is kept clean
-    size_t image = sizeof(ArriveSlot) * (nslots > ctx->clean_slots ? nslots : ctx->clean_slots);
-    image = round_up(image, 256);
-    rc = ensure_work(ctx, image + (in_host ? 0 : bytes), a.stream);
+    const size_t nslots = plan.nparts;
+    const size_t behind =
+        round_up(sizeof(ArriveSlot) * (nslots > ctx->clean_slots ? nslots : ctx->clean_slots), 256);
+    rc = ensure_work(ctx, behind + bytes, a.stream);
     if (rc != PGCM_OK) return rc;
     use_slots(ctx, nslots, a.stream, a.capturing);
-    uint8_t* const stage = ctx->stage[s];
     const uint8_t* packets = stage;
     const SpanPart* parts = nullptr;
     if (in_host) {
         for (uint32_t g = 0; g < ngroups; ++g) {
-            const SpanGroup& d = plan.groups[g];
+            const SpanGroup& d = groups[g];
             memcpy(stage + g * stride, &d, sizeof(d));
-            memcpy(stage + g * stride + sizeof(d), &plan.parts[d.part], sizeof(SpanPart) * d.nparts);
+            memcpy(stage + g * stride + sizeof(d), all_parts + d.part, sizeof(SpanPart) * d.nparts);
         }
     } else {
-        memcpy(stage, plan.groups.data(), sizeof(SpanGroup) * ngroups);
-        memcpy(stage + parts_at, plan.parts.data(), sizeof(SpanPart) * nslots);
+        if (image != stage) memcpy(stage, image, bytes);
         const uint32_t n16 = (uint32_t)(bytes / 16);
         hipLaunchKernelGGL(upload_kernel, dim3((n16 + 255) / 256 < 1024 ? (n16 + 255) / 256 : 1024),
-                           dim3(256), 0, a.stream, reinterpret_cast<uint4*>(ctx->work + image),
+                           dim3(256), 0, a.stream, reinterpret_cast<uint4*>(ctx->work + behind),
                            reinterpret_cast<const uint4*>(stage), n16, (uint4*)nullptr, 0u);
-        packets = ctx->work + image;
+        packets = ctx->work + behind;
         parts = reinterpret_cast<const SpanPart*>(packets + parts_at);
         stride = 0;
     }
@@ -1147,8 +1153,13 @@ int run_batch(pgcm_key* key, BatchArgs a) {
     if (key == nullptr || key->tables == nullptr) return PGCM_ERR_ARG;
     int rc = check_batch(a);
     if (rc != PGCM_OK || a.n == 0) return rc;
-    BatchPlan p;
-    rc = plan_batch(key->forced_unit_power, key->wave_slots, a, &p);  // nothing touched so far
+    BatchSurvey v;
+    rc = survey_batch(a, &v);
+    if (rc != PGCM_OK) return rc;
+    // the units, unless they are not wanted anyway; nothing touched so far
+    const bool spans = !a.fixed && !v.all_one_row && takes_spans(key, v);
+    BatchPlan p{};
+    if (!spans) rc = plan_batch(key->forced_unit_power, key->wave_slots, a, &p);
     if (rc != PGCM_OK) return rc;
     int cur_device = -1;
     PGCM_HIP(hipGetDevice(&cur_device));
@@ -1157,17 +1168,14 @@ int run_batch(pgcm_key* key, BatchArgs a) {
     if (rc != PGCM_OK) return rc;
     if (a.fixed && a.n > kFixedMaxChunks) return PGCM_ERR_CAPACITY;
     SwapShape shape{};
-    bool one_launch = swap_shape(key, a, p.all_small, &shape);
-    KeyPart part{key, 0, a.n, 0, 0};
-    const bool spans = !a.fixed && !p.all_one_row && !(one_launch && p.all_small) &&
-                       count_span_rows(a, &part, 1);
+    bool one_launch = swap_shape(key, a, v.all_small, &shape);
     // Where units or workgroups are left short, spans have fewer rows for a wavefront, but they begin
     // and end later.  With sixteen wavefronts a workgroup, a batch of one launch takes 14 us and
     // 4.3 a row of its units, with eight 12 and 2.4; spans take 25 and 3.6 a row (147 chunks of
     // 60 to 450 KB: units of 16 rows, spans of 7, 83 and 54 us; 3 of 5 MiB: 4 and 3.8, 32 and 38).
-    if (one_launch && spans && shape.wave_power == 4) {
+    if (one_launch && spans && !v.all_small && shape.wave_power == 4) {
         const uint64_t unit_rows = 1u << (shape.unit_power - kRowPower);
-        if (43 * unit_rows * key->wave_slots > 110 * (uint64_t)key->wave_slots + 36 * part.rows)
+        if (43 * unit_rows * key->wave_slots > 110 * (uint64_t)key->wave_slots + 36 * v.rows)
             one_launch = false;
     }
     if (one_launch && shape.alone && a.n <= kArgChunks) return run_one_launch(key, nullptr, a, shape);
@@ -1181,12 +1189,14 @@ int run_batch(pgcm_key* key, BatchArgs a) {
     }
     if (one_launch)
         rc = run_one_launch(key, ctx, a, shape);
-    else if (p.all_one_row)
+    else if (v.all_one_row)
         rc = run_small_batch(key, ctx, a);
-    else if (spans)
+    else if (spans) {
+        KeyPart part{key, 0, a.n, v.rows, 0};
         rc = run_span_batch(ctx, a, &part, 1);
-    else
+    } else {
         rc = run_unit_batch(key, ctx, a, p);
+    }
     release_context(key, ctx);
     return rc;
 }
@@ -1247,7 +1257,18 @@ int run_batch_keys(pgcm_key* const* keys, size_t nkeys, const uint32_t* key_inde
     if (parts.size() > 1 && parts.size() <= (size_t)keys[0]->num_cu) {
         BatchArgs a = all;
         a.order = order.data();
-        if (count_span_rows(a, parts.data(), parts.size()))
+        bool spans = true;
+        BatchSurvey v;
+        for (KeyPart& part : parts) {
+            for (size_t k = part.first; k < part.first + part.n; ++k) {
+                const uint64_t rows = span_rows(a, order[k]), len = all.len[order[k]];
+                part.rows += rows;
+                v.rows += rows;
+                if (len > v.longest) v.longest = len;
+            }
+        }
+        for (const KeyPart& part : parts) spans = spans && takes_spans(part.key, v);
+        if (spans)
             return run_span_parts(a, parts.data(), parts.size());
     }
     // ... or one key's after the other's
@@ -1503,8 +1524,11 @@ int pgcm_describe_schedule(size_t n, const uint64_t* len, uint32_t unit_bytes, u
     BatchArgs a{false, n, nullptr, reinterpret_cast<const uint8_t*>((uintptr_t)4096), 12, nullptr,
                 nullptr, ptrs.data(), len, const_cast<void* const*>(ptrs.data()),
                 reinterpret_cast<uint8_t*>((uintptr_t)4096), nullptr, nullptr};
+    BatchSurvey v;
+    int rc = survey_batch(a, &v);
+    if (rc != PGCM_OK) return rc;
     BatchPlan p{};
-    int rc = plan_batch(forced, wave_slots ? wave_slots : kWaveSlots, a, &p);
+    rc = plan_batch(forced, wave_slots ? wave_slots : kWaveSlots, a, &p);
     if (rc != PGCM_OK) return rc;
     const WorkLayout w = lay_out(a, p);
     info->desc_offset = w.desc;
@@ -1522,7 +1546,7 @@ int pgcm_describe_schedule(size_t n, const uint64_t* len, uint32_t unit_bytes, u
         info->fold_count[l] = p.fold_count[l];
         info->fold_first[l] = p.fold_first[l];
     }
-    info->path = n == 0 ? 0 : p.all_one_row ? 1 : (p.all_small && n <= kSmallMaxChunks) ? 2 : 0;
+    info->path = n == 0 ? 0 : v.all_one_row ? 1 : (v.all_small && n <= kSmallMaxChunks) ? 2 : 0;
     if (image != nullptr) {
         if (image_capacity < w.upload_bytes) return PGCM_ERR_CAPACITY;
         memset(image, 0, w.upload_bytes);
