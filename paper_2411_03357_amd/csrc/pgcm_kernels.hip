@@ -2583,13 +2583,10 @@ __global__ __launch_bounds__(kGroupThreads) void span_kernel(
         asm volatile("" : : "v"(gh));
     __syncthreads();
 
-    // the workgroup's rows dealt to its wavefronts
-    const uint32_t rows = __builtin_amdgcn_readfirstlane(group->rows);
-    const uint32_t waves = rows < kWavesPerGroup ? rows : kWavesPerGroup;
-    if (wave >= waves) return;
+    if (wave >= __builtin_amdgcn_readfirstlane(group->waves)) return;
     const uint32_t first_row = __builtin_amdgcn_readfirstlane(group->first_row);
-    const uint32_t row = first_row + rows * wave / waves;
-    const uint32_t end = first_row + rows * (wave + 1) / waves;
+    const uint32_t row = first_row + __builtin_amdgcn_readfirstlane(group->cut[wave]);
+    const uint32_t end = first_row + __builtin_amdgcn_readfirstlane(group->cut[wave + 1]);
     // its first part: the last one that does not begin behind `row`
     const uint32_t nparts = __builtin_amdgcn_readfirstlane(group->nparts);
     uint32_t part = 0;

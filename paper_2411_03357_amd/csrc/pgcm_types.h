@@ -204,15 +204,17 @@ struct alignas(16) GroupDesc {
 };
 
 // Spans: the rows of all chunks of a batch, each chunk's counted back from its end and the blocks
-// before its block 0 among them, are numbered through.  Every workgroup takes its share of them, dealt
-// out to its wavefronts, and chunks are cut wherever a share ends.
+// before its block 0 among them, are numbered through.  Every wavefront takes a share of them, and
+// chunks are cut wherever a share ends.
 struct alignas(16) SpanGroup {      // a workgroup
     const KeyTables* kt;
-    uint32_t first_row, rows;       // its rows
+    uint32_t first_row;
     uint32_t part, nparts;          // where its chunks are described, if not right behind this
-    uint32_t pad_[2];
+    uint32_t waves;                 // its wavefronts with rows, at most kWavesPerGroup
+    uint32_t cut[kWavesPerGroup + 1];  // the first row of each, counted from the workgroup's; the end
+    uint32_t pad_;
 };
-static_assert(sizeof(SpanGroup) == 32, "descriptor layout");
+static_assert(sizeof(SpanGroup) == 96, "descriptor layout");
 struct alignas(16) SpanPart {       // a chunk as far as one workgroup has rows of it
     const uint8_t* src;
     uint8_t* dst;

@@ -1,0 +1,96 @@
+"""Batches cut into spans of rows: chunks that a wavefront, a workgroup or several share, that end at
+and next to the edges of a row, keys with fewer rows than a workgroup has wavefronts, and lists of
+chunks longer than a workgroup keeps in LDS — against the CPU oracle, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from device_batch import DeviceBatch
+
+import paper_2411_03357_amd as pgcm
+
+pytestmark = pytest.mark.gpu
+
+KIB, MIB = 1024, 1 << 20
+
+
+def _even(rng, n, lo, hi):
+    return [int(v) for v in np.exp(rng.uniform(np.log(lo), np.log(hi), n))]
+
+
+# name: (chunk lengths, bytes of each key, how the keys go round the chunks, bytes of an IV)
+SHAPES = {
+    # next to nothing: a key with one row, one with a few, and empty chunks
+    "least": lambda r: ([1, 0, 4 * KIB, 16, 0, 1041], (32, 16), 2, 12),
+    # the edges of rows, with a row in front for the blocks before block 0 and without
+    "edges": lambda r: ([k * KIB + d for k in (1, 2, 3, 15, 16, 17) for d in (-16, -1, 0, 1, 16)],
+                        (16, 24, 32), 3, 16),
+    # a few long chunks: shares of few rows, every chunk in many workgroups
+    "long": lambda r: (_even(r, 17, 700 * KIB, 2 * MIB), (32, 24), 2, 12),
+    # as many chunks as wavefronts, one key with nearly all of them
+    "dealt": lambda r: (_even(r, 700, 30 * KIB, 90 * KIB), (32, 16, 32), 40, 12),
+    # more chunks than shares: cut in equal parts, lists longer than LDS has room for
+    "many": lambda r: (_even(r, 9000, 40, 3 * KIB), (32,), 1, 12),
+    # shares of many rows
+    "big": lambda r: (_even(r, 60, 500 * KIB, 2 * MIB) + [9 * MIB + 5], (16,), 1, 12),
+}
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_spans(shape):
+    rng = np.random.default_rng([workloads.BASE_SEED, 1618, len(shape)])
+    lens, key_bytes, cycle, iv_bytes = SHAPES[shape](rng)
+    n = len(lens)
+    lens = np.array(lens, np.uint64)
+    alens = rng.integers(0, 70, n)
+    offsets, total = workloads._layout(lens)
+    aad_off = np.zeros(n + 1, np.uint64)
+    aad_off[1:] = np.cumsum(alens)
+    ivs = rng.integers(0, 256, (n, iv_bytes), dtype=np.uint8)
+    raw_keys = [rng.integers(0, 256, b, dtype=np.uint8) for b in key_bytes]
+    w = workloads.Workload("spans_" + shape, 900, raw_keys[0], ivs, lens, offsets, total, "u8",
+                           rng.integers(0, 256, int(alens.sum()), dtype=np.uint8), aad_off)
+    index = np.minimum(np.arange(n) % cycle, len(raw_keys) - 1).astype(np.uint32)
+    keys = [pgcm.expand_key_bytes(k) for k in raw_keys]
+    host = w.payload_host()
+    expect = np.full(total, 0xEE, np.uint8)
+    expect_tags = np.zeros((n, 16), np.uint8)
+    for q, raw in enumerate(raw_keys):
+        mine = np.flatnonzero(index == q)
+        cts, tags, _ = oracle.encrypt_batch(
+            raw, ivs[mine], [np.frombuffer(w.aad_of(i), np.uint8) for i in mine],
+            [w.chunk(host, i) for i in mine], nthreads=16)
+        expect_tags[mine] = tags
+        for i, ct in zip(mine, cts):
+            expect[int(offsets[i]):int(offsets[i]) + ct.size] = ct
+
+    b = DeviceBatch(w, torch.from_numpy(host).cuda())
+    b.cipher.fill_(0xEE)
+    for _ in range(2):                   # twice: the arrival words must be left clean
+        b.tags.zero_()
+        pgcm.encrypt_batch_keys(keys, index, b.ivs, iv_bytes, b.aad_ptrs, b.aad_lens,
+                                b.ptrs(b.plain), b.lens, b.ptrs(b.cipher), b.tags)
+    torch.cuda.synchronize()
+    bad = np.flatnonzero(b.cipher.cpu().numpy() != expect)
+    assert bad.size == 0, "ciphertext byte %d" % bad[0]
+    bad = np.flatnonzero((b.tags.cpu().numpy().reshape(n, 16) != expect_tags).any(1))
+    assert bad.size == 0, "tag of chunk %d (length %d)" % (bad[0], lens[bad[0]])
+
+    tampered = set(rng.integers(0, n, 2).tolist())
+    for i in tampered:
+        b.tags[16 * i + 5] ^= 0x10
+    b.back.fill_(0xDD)
+    pgcm.decrypt_verify_batch_keys(keys, index, b.ivs, iv_bytes, b.aad_ptrs, b.aad_lens,
+                                   b.ptrs(b.cipher), b.lens, b.ptrs(b.back), b.tags, b.ok)
+    torch.cuda.synchronize()
+    assert np.array_equal(np.flatnonzero(b.ok.cpu().numpy() == 0), sorted(tampered))
+    expect = np.full(total, 0xDD, np.uint8)
+    for i in range(n):
+        end = int(offsets[i] + lens[i])
+        expect[int(offsets[i]):end] = 0 if i in tampered else host[int(offsets[i]):end]
+    bad = np.flatnonzero(b.back.cpu().numpy() != expect)
+    assert bad.size == 0, "plaintext byte %d" % bad[0]
+    for k in keys:
+        k.free()
