@@ -1,0 +1,261 @@
+// How a batch is cut into spans of rows (span_kernel): which workgroups and wavefronts take which rows
+// of which chunks, and the descriptors they read.  Host only, plain C++.
+#pragma once
+#include <stddef.h>
+#include <stdint.h>
+
+#include <vector>
+
+#include "pgcm_types.h"
+
+struct pgcm_key;
+
+namespace pgcm {
+
+// The caller's arrays as far as the cutter looks at them.
+struct SpanBatch {
+    size_t n;
+    const uint32_t* order;  // chunk k of the batch is the caller's chunk order[k]; null: chunk k
+    const void* const* aad;
+    const uint32_t* aad_len;
+    const void* const* src;
+    const uint64_t* len;
+    void* const* dst;
+
+    size_t at(size_t k) const { return order ? order[k] : k; }
+};
+
+inline uint64_t span_rows(uint64_t len, uint32_t aad_len) {
+    const uint64_t blocks = (len + 15) / 16 + lead_blocks(aad_len);
+    return (blocks + kRowBlocks - 1) / kRowBlocks;
+}
+
+// What is kept from call to call for cutting batches.
+struct SpanScratch {
+    std::vector<uint8_t> image;                // descriptors
+    std::vector<uint32_t> rows, cuts, waves;
+};
+
+// What one more piece costs a workgroup of sixteen wavefronts, in rows: it ends 2 us later for it, 0.27
+// for a row more (300 adapters both ways with 2, 8: 198, 191 us); and a wavefront among them, in half
+// rows, which are 2.2 us.
+constexpr uint32_t kPieceRows = 8;
+constexpr uint32_t kPieceHalfRows = 6;
+// Shares of up to so many rows are cut with regard to the pieces they make (17 long chunks of two
+// keys both ways 57 -> 35 us, 284 chunks of 44 to 97 KB 87 -> 79); longer ones are better cut equal
+// (300 adapters, 17 rows a share: 187 and 194).
+constexpr uint32_t kFineRows = 12;
+
+// One key's chunks of a batch: n of them from the batch's chunk `first` on.
+struct KeyPart {
+    pgcm_key* key;
+    const KeyTables* tables;  // of the key
+    uint32_t rounds;
+    size_t first, n;
+    uint64_t rows;
+    uint32_t groups;  // workgroups
+
+    uint64_t weight() const { return rows + kPieceRows * n; }
+};
+
+// Deals the compute units out to the parts, a workgroup each, so that the one with the most work per
+// workgroup has as little as can be: a row costs a table lookup per round and byte and the hash as
+// much as three rounds.  A workgroup gets four rows at least, if there are that many: with no more
+// wavefronts than that a row takes 2.6 us instead of 4.3.  Returns the number of workgroups.
+inline uint32_t deal_groups(KeyPart* parts, size_t nparts, uint32_t num_cu) {
+    uint64_t work = 0;
+    auto cost = [](const KeyPart& p) { return p.weight() * (uint64_t)(p.rounds + 3); };
+    auto most = [](const KeyPart& p) { return p.rows < 4 ? 1 : p.rows / 4; };
+    for (size_t q = 0; q < nparts; ++q) work += cost(parts[q]);
+    uint32_t total = 0;
+    for (size_t q = 0; q < nparts; ++q) {
+        uint64_t g = cost(parts[q]) * num_cu / work;
+        if (g > most(parts[q])) g = most(parts[q]);
+        parts[q].groups = g == 0 ? 1 : (uint32_t)g;
+        total += parts[q].groups;
+    }
+    while (total < num_cu) {
+        KeyPart* worst = nullptr;
+        for (size_t q = 0; q < nparts; ++q) {
+            KeyPart& p = parts[q];
+            if (p.groups < most(p) &&
+                (worst == nullptr || cost(p) * worst->groups > cost(*worst) * p.groups))
+                worst = &p;
+        }
+        if (worst == nullptr) break;
+        ++worst->groups, ++total;
+    }
+    return total;
+}
+
+// Cuts a key's rows, which begin at `row`, into shares of at most 16 * key.groups wavefronts and deals
+// these out to its workgroups: the first rows of all wavefronts are appended to `cuts`, and
+// waves[g] is the number of the first wavefront of workgroup g.  rows: of each chunk.
+inline void cut_key(const KeyPart& key, uint32_t row, const uint32_t* rows, std::vector<uint32_t>& cuts,
+             uint32_t* waves) {
+    const uint32_t most = key.groups * kWavesPerGroup, base = (uint32_t)cuts.size();
+    if (key.rows <= (uint64_t)most * kFineRows && key.n <= 2 * (size_t)most) {
+        // Where shares are short, what a wavefront spends on beginning and finishing pieces decides: a
+        // share holds `limit` half rows, pieces among them, as many as it takes for the wavefronts
+        // to do.  A chunk that follows in a share with no room for a row more goes to the next.
+        constexpr uint32_t kP = kPieceHalfRows;
+        uint32_t limit = (uint32_t)((2 * key.rows + kP * (key.n + most) + most - 1) / most);
+        if (limit < kP + 2) limit = kP + 2;
+        for (;; limit += 1 + limit / 32) {
+            const uint32_t whole = (limit - kP) / 2;  // rows of a share with one piece
+            uint32_t used = 1, left = limit;
+            for (size_t k = 0; k < key.n; ++k) {
+                uint32_t r = rows[k];
+                if (left >= kP + 2) {
+                    const uint32_t room = (left - kP) / 2;
+                    if (r <= room) {
+                        left -= kP + 2 * r;
+                        continue;
+                    }
+                    r -= room;
+                }
+                const uint32_t n = (r + whole - 1) / whole;
+                used += n;
+                left = limit - kP - 2 * (r - (n - 1) * whole);
+            }
+            if (used <= most) break;
+        }
+        const uint32_t whole = (limit - kP) / 2;
+        uint32_t left = limit;
+        cuts.push_back(row);
+        for (size_t k = 0; k < key.n; ++k) {
+            uint32_t r = rows[k], at = row;
+            row += r;
+            if (left >= kP + 2) {
+                const uint32_t room = (left - kP) / 2;
+                if (r <= room) {
+                    left -= kP + 2 * r;
+                    continue;
+                }
+                r -= room;
+                at += room;
+            }
+            for (; r > whole; r -= whole, at += whole) cuts.push_back(at);
+            cuts.push_back(at);
+            left = limit - kP - 2 * r;
+        }
+        const uint32_t used = (uint32_t)cuts.size() - base;
+        for (uint32_t g = 0; g < key.groups; ++g)
+            waves[g] = base + (uint32_t)((uint64_t)used * g / key.groups);
+        return;
+    }
+    // A workgroup begins where the weight so far reaches its share; a chunk's own weight comes before
+    // its rows'.  Its rows go to its wavefronts in equal parts.
+    uint64_t weight = 0, next = 0;
+    uint32_t group = 0, begin = row;
+    auto deal = [&](uint32_t end) {
+        if (group > 0) {
+            const uint32_t n = end - begin, w = n < kWavesPerGroup ? n : kWavesPerGroup;
+            for (uint32_t i = 0; i < w; ++i) cuts.push_back(begin + (uint32_t)((uint64_t)n * i / w));
+        }
+        begin = end;
+    };
+    for (size_t k = 0; k < key.n; ++k) {
+        const uint64_t weight_end = weight + rows[k] + kPieceRows;
+        while (group < key.groups && next < weight_end) {
+            deal(next > weight + kPieceRows ? row + (uint32_t)(next - weight - kPieceRows) : row);
+            waves[group++] = (uint32_t)cuts.size();
+            next = key.weight() * group / key.groups;
+        }
+        row += rows[k];
+        weight = weight_end;
+    }
+    deal(row);
+}
+
+// Cuts the keys' chunks.  parts: room for n and the number of workgroups.
+struct SpanPlan {
+    uint32_t nparts;
+    uint32_t longest;  // list of parts of a workgroup
+};
+inline SpanPlan plan_spans(const SpanBatch& a, const KeyPart* keys, size_t nkeys, SpanScratch& scratch,
+                    SpanGroup* groups, SpanPart* parts) {
+    std::vector<uint32_t>&rows = scratch.rows, &cuts = scratch.cuts, &waves = scratch.waves;
+    rows.resize(a.n);
+    for (size_t k = 0; k < a.n; ++k) {
+        const size_t i = a.at(k);
+        rows[k] = (uint32_t)span_rows(a.len[i], a.aad_len ? a.aad_len[i] : 0);
+    }
+    cuts.clear();
+    uint32_t row = 0, group = 0;
+    for (size_t q = 0; q < nkeys; ++q) {
+        waves.resize(group + keys[q].groups + 1);
+        cut_key(keys[q], row, rows.data() + keys[q].first, cuts, waves.data() + group);
+        row += (uint32_t)keys[q].rows;
+        group += keys[q].groups;
+    }
+    waves[group] = (uint32_t)cuts.size();
+    cuts.push_back(row);
+
+    SpanPlan plan{0, 0};
+    uint32_t g = 0, np = 0;
+    row = 0;
+    for (size_t q = 0; q < nkeys; ++q) {
+        bool begun = false;  // workgroup g has a part already
+        uint32_t wave = 0;   // of the workgroup, the one with `row`
+        for (size_t k = keys[q].first; k < keys[q].first + keys[q].n; ++k) {
+            const size_t i = a.at(k);
+            SpanPart c;
+            c.src = (const uint8_t*)a.src[i];
+            c.dst = (uint8_t*)a.dst[i];
+            c.len = a.len[i];
+            c.aad_len = a.aad_len ? a.aad_len[i] : 0;
+            c.aad = c.aad_len ? (const uint8_t*)a.aad[i] : nullptr;
+            c.index = (uint32_t)i;
+            c.first_row = row;
+            c.rows = rows[k];
+            c.slot = np;
+            const uint32_t chunk_end = row + rows[k];
+            while (row < chunk_end) {
+                SpanGroup& d = groups[g];
+                const uint32_t *cut = cuts.data() + waves[g], n = waves[g + 1] - waves[g];
+                if (!begun) {
+                    begun = true;
+                    wave = 0;
+                    d.kt = keys[q].tables;
+                    d.first_row = row;
+                    d.part = np;
+                    d.waves = n;
+                    for (uint32_t w = 0; w <= n; ++w) d.cut[w] = cut[w] - row;
+                    d.pad_ = 0;
+                }
+                const uint32_t end = cut[n] < chunk_end ? cut[n] : chunk_end;
+                while (cut[wave + 1] <= row) ++wave;
+                const uint32_t first = wave;
+                while (cut[wave + 1] < end) ++wave;
+                c.waves = (wave - first + 1) << 8 | first;
+                c.own_slot = np;
+                parts[np++] = c;
+                row = end;
+                if (end == cut[n]) {
+                    d.nparts = np - d.part;
+                    if (d.nparts > plan.longest) plan.longest = d.nparts;
+                    begun = false;
+                    ++g;
+                }
+            }
+            for (uint32_t p = c.slot; p < np; ++p) parts[p].slots = np - c.slot;
+        }
+    }
+    plan.nparts = np;
+    return plan;
+}
+
+// Bytes of descriptors up to which the workgroups read theirs from host memory themselves.
+constexpr size_t kSpanHostBytes = 256 << 10;
+
+// Upper bounds for any batch of at most n chunks on a device of num_cu compute units.
+inline size_t span_stage_bytes(size_t n, size_t num_cu) {
+    const size_t uploaded = sizeof(SpanGroup) * num_cu + sizeof(SpanPart) * (n + num_cu) + 256;
+    return uploaded > kSpanHostBytes ? uploaded : kSpanHostBytes;
+}
+inline size_t span_work_bytes(size_t n, size_t num_cu) {
+    return 2 * sizeof(ArriveSlot) * (n + num_cu) + span_stage_bytes(n, num_cu) + 512;
+}
+
+}  // namespace pgcm
