@@ -452,7 +452,7 @@ inline void describe_chunk(const BatchArgs& a, size_t i, ChunkDesc& d) {
 }
 
 inline uint64_t span_rows(const BatchArgs& a, size_t i) {
-    return span_rows(a.len[i], a.aad_len ? a.aad_len[i] : 0);
+    return pgcm::span_rows(a.len[i], a.aad_len ? a.aad_len[i] : 0);
 }
 
 // What decides which way a batch goes.
