@@ -149,9 +149,10 @@ int pgcm_encrypt_batch_static(pgcm_key_t *key, size_t n, const uint8_t *ivs,
 /*
  * Prepares the key's context for `hip_stream` (section 5.1: the transport knows the sizes of the
  * swaps it will be asked for) so that batch calls on that stream with at most n_max chunks and at
- * most payload_bytes_max bytes in all neither allocate nor wait for the stream: pinned staging
- * for the descriptors and device workspace for the schedule and the partial hash sums (about
- * 1/16 of the payload).  May allocate and synchronise the stream itself.  Call it again after
+ * most payload_bytes_max bytes in all neither allocate nor wait for the stream, whichever way they
+ * go: pinned staging for the descriptors (four buffers of at least 256 KiB), device workspace for
+ * the schedule and the partial hash sums (about 1/16 of the payload), and host memory for the
+ * planner.  May allocate and synchronise the stream itself.  Call it again after
  * pgcm_set_unit_bytes.  PGCM_ERR_ARG when the numbers are beyond what a batch can be.
  */
 int pgcm_reserve(pgcm_key_t *key, void *hip_stream, size_t n_max, uint64_t payload_bytes_max);
@@ -271,6 +272,22 @@ typedef struct pgcm_schedule_info {
 int pgcm_describe_schedule(size_t n, const uint64_t *len, uint32_t unit_bytes,
                            uint32_t wave_slots, pgcm_schedule_info *info, void *image,
                            size_t image_capacity);
+
+/*
+ * Test aid: the buffers that the key keeps for the batch calls on one stream.
+ *   info       HOST, filled: how often a batch or pgcm_reserve had to allocate for them (pinned
+ *              staging, device workspace, host memory of the planner), the size of the workspace
+ *              and of the smallest of the staging buffers.
+ *   workspace  HOST or NULL; receives the first `bytes` bytes of the workspace, after the device is
+ *              synchronised.  The copy holds what is derived from keys: wipe it after use.
+ * PGCM_ERR_ARG when no batch and no pgcm_reserve has used the stream with this key, or a call is
+ * using it now; PGCM_ERR_CAPACITY when the workspace is smaller than `bytes`.
+ */
+typedef struct pgcm_context_info {
+    uint64_t allocations, workspace_bytes, stage_bytes;
+} pgcm_context_info;
+int pgcm_describe_context(pgcm_key_t *key, void *hip_stream, pgcm_context_info *info,
+                          void *workspace, size_t bytes);
 
 /*
  * Test aid: copies the key object's device tables to out (HOST), synchronising the device: 60

@@ -15,7 +15,7 @@ EXPORTS = ("pgcm_expand_key", "pgcm_expand_key_bytes", "pgcm_free_key", "pgcm_en
            "pgcm_encrypt_batch_keys", "pgcm_decrypt_verify_batch_keys",
            "pgcm_strerror", "pgcm_last_hip_error", "pgcm_plan_units", "pgcm_unit_bytes",
            "pgcm_batch_unit_bytes", "pgcm_set_unit_bytes", "pgcm_key_tables_bytes",
-           "pgcm_copy_key_tables",
+           "pgcm_copy_key_tables", "pgcm_describe_context",
            "pgcm_set_timing", "pgcm_last_bulk_kernel_ms", "pgcm_bulk_kernel_ms_history",
            "pgcm_measure_passes", "pgcm_set_one_launch", "pgcm_set_matrix_hash",
            "pgcm_bitsliced_keystream")
@@ -80,6 +80,8 @@ def load_library():
     lib.pgcm_unit_bytes.restype = C.c_uint32
     lib.pgcm_batch_unit_bytes.argtypes = [sz, vp]
     lib.pgcm_batch_unit_bytes.restype = C.c_uint32
+    lib.pgcm_describe_context.argtypes = [vp, vp, vp, vp, sz]
+    lib.pgcm_describe_context.restype = C.c_int
     lib.pgcm_key_tables_bytes.argtypes = []
     lib.pgcm_key_tables_bytes.restype = sz
     lib.pgcm_copy_key_tables.argtypes = [vp, vp, sz]
@@ -268,6 +270,23 @@ def reserve(key: Key, n_max: int, payload_bytes_max: int, stream=None):
     """pgcm_reserve"""
     _check(load_library().pgcm_reserve(key.handle, _stream_handle(stream), n_max,
                                        payload_bytes_max))
+
+
+class _ContextInfo(C.Structure):
+    _fields_ = [(n, C.c_uint64) for n in ("allocations", "workspace_bytes", "stage_bytes")]
+
+
+def describe_context(key: Key, stream=None, workspace_bytes=0) -> dict:
+    """pgcm_describe_context: its counts, and the first workspace_bytes of the workspace as
+    `workspace` (uint8)."""
+    info, work = _ContextInfo(), np.zeros(workspace_bytes, np.uint8)
+    _check(load_library().pgcm_describe_context(key.handle, _stream_handle(stream),
+                                                C.addressof(info),
+                                                work.ctypes.data if workspace_bytes else None,
+                                                workspace_bytes))
+    out = {k: int(getattr(info, k)) for k, _ in _ContextInfo._fields_}
+    out["workspace"] = work
+    return out
 
 
 class _ScheduleInfo(C.Structure):

@@ -127,6 +127,7 @@ struct Context {
     bool counter_dirty = true;
     size_t clean_slots = 0;  // so many ArriveSlots at the start of `work` have counts of zero
     SpanScratch scratch;     // of the call that is using the context
+    uint64_t allocations = 0;  // times a batch or pgcm_reserve had to get any of these more room
     // binding
     hipStream_t stream = nullptr;
     bool bound = false;        // has run a batch on `stream`
@@ -226,6 +227,7 @@ int ensure_stage(Context* c, int s, size_t bytes) {
     if (hip_failed(hipHostMalloc(&p, cap, hipHostMallocDefault))) return PGCM_ERR_NOMEM;
     c->stage[s] = (uint8_t*)p;
     c->stage_cap[s] = cap;
+    ++c->allocations;
     return PGCM_OK;
 }
 
@@ -246,6 +248,7 @@ int ensure_work(Context* c, size_t bytes, hipStream_t stream) {
     if (hip_failed(hipMalloc(&p, cap))) return PGCM_ERR_NOMEM;
     c->work = (uint8_t*)p;
     c->work_cap = cap;
+    ++c->allocations;
     return PGCM_OK;
 }
 
@@ -943,8 +946,7 @@ inline bool takes_spans(const pgcm_key* key, const BatchSurvey& v) {
 // One batch in spans, of one key or of several: the context is that of the first.
 int run_span_batch(Context* ctx, const BatchArgs& a, KeyPart* keys, size_t nkeys) {
     const uint32_t ngroups = deal_groups(keys, nkeys, (uint32_t)keys[0].key->num_cu);
-    const size_t parts_at = round_up(sizeof(SpanGroup) * ngroups, 256);
-    const size_t most = parts_at + round_up(sizeof(SpanPart) * (a.n + ngroups), 256);
+    const size_t parts_at = span_parts_at(ngroups), most = span_image_bytes(a.n + ngroups, ngroups);
     const int s = ctx->next_stage;
     int rc = ensure_stage(ctx, s, most > kSpanHostBytes ? most : kSpanHostBytes);
     if (rc != PGCM_OK) return rc;
@@ -955,6 +957,7 @@ int run_span_batch(Context* ctx, const BatchArgs& a, KeyPart* keys, size_t nkeys
     SpanPlan plan;
     SpanGroup* groups;
     SpanPart* all_parts;
+    const size_t held = ctx->scratch.capacity();
     try {
         if (most <= kSpanHostBytes) {
             ctx->scratch.image.resize(kSpanHostBytes);
@@ -967,10 +970,11 @@ int run_span_batch(Context* ctx, const BatchArgs& a, KeyPart* keys, size_t nkeys
     } catch (const std::bad_alloc&) {
         return PGCM_ERR_NOMEM;
     }
+    if (ctx->scratch.capacity() != held) ++ctx->allocations;
     size_t stride = sizeof(SpanGroup) + sizeof(SpanPart) * plan.longest;
     const bool in_host =
         image != stage && plan.longest <= kSpanLdsParts && stride * ngroups <= kSpanHostBytes;
-    const size_t bytes = in_host ? 0 : parts_at + round_up(sizeof(SpanPart) * plan.nparts, 256);
+    const size_t bytes = in_host ? 0 : span_image_bytes(plan.nparts, ngroups);
     // the descriptors go behind every slot that is kept clean
     const size_t nslots = plan.nparts;
     const size_t behind =
@@ -1284,12 +1288,23 @@ int pgcm_reserve(pgcm_key_t* key, void* hip_stream, size_t n_max, uint64_t paylo
     Context* ctx = nullptr;
     int rc = acquire_context(key, stream, &ctx);
     if (rc != PGCM_OK) return rc;
-    for (int s = 0; s < kStages && rc == PGCM_OK; ++s) rc = ensure_stage(ctx, s, stage_bytes);
+    // for whichever path such a batch takes: units (above), one launch, spans
     const size_t num_cu = (size_t)key->num_cu;
-    if (stage_bytes < span_stage_bytes(n_max, num_cu)) stage_bytes = span_stage_bytes(n_max, num_cu);
+    const size_t clean = ctx->clean_slots > kSwapMaxGroups ? ctx->clean_slots : kSwapMaxGroups;
+    const size_t span_stage = span_stage_bytes(n_max, num_cu);
+    const size_t span_work = span_work_bytes(n_max, num_cu, clean);
+    if (stage_bytes < span_stage) stage_bytes = span_stage;
     if (work_bytes < kSwapWorkBytes) work_bytes = kSwapWorkBytes;
-    if (work_bytes < span_work_bytes(n_max, num_cu)) work_bytes = span_work_bytes(n_max, num_cu);
+    if (work_bytes < span_work) work_bytes = span_work;
+    for (int s = 0; s < kStages && rc == PGCM_OK; ++s) rc = ensure_stage(ctx, s, stage_bytes);
     if (rc == PGCM_OK) rc = ensure_work(ctx, work_bytes, stream);
+    if (rc == PGCM_OK) {
+        try {
+            ctx->scratch.reserve(n_max, num_cu);
+        } catch (const std::bad_alloc&) {
+            rc = PGCM_ERR_NOMEM;
+        }
+    }
     if (rc == PGCM_OK) {
         // the context now belongs to this stream, so that the stream's batches find it
         std::lock_guard<std::mutex> lock(key->mu);
@@ -1430,6 +1445,28 @@ int pgcm_describe_schedule(size_t n, const uint64_t* len, uint32_t unit_bytes, u
         if (n != 0) fill_schedule(a, p, w, static_cast<uint8_t*>(image));
     }
     return PGCM_OK;
+}
+
+int pgcm_describe_context(pgcm_key_t* key, void* hip_stream, pgcm_context_info* info,
+                          void* workspace, size_t bytes) {
+    if (key == nullptr || info == nullptr || (workspace == nullptr && bytes != 0))
+        return PGCM_ERR_ARG;
+    std::lock_guard<std::mutex> lock(key->mu);
+    for (const Context* c : key->contexts) {
+        if (c->in_call || !c->bound || c->stream != (hipStream_t)hip_stream) continue;
+        info->allocations = c->allocations;
+        info->workspace_bytes = c->work_cap;
+        info->stage_bytes = c->stage_cap[0];
+        for (int s = 1; s < kStages; ++s)
+            if (c->stage_cap[s] < info->stage_bytes) info->stage_bytes = c->stage_cap[s];
+        if (bytes > c->work_cap) return PGCM_ERR_CAPACITY;
+        if (bytes != 0) {
+            PGCM_HIP(hipDeviceSynchronize());
+            PGCM_HIP(hipMemcpy(workspace, c->work, bytes, hipMemcpyDeviceToHost));
+        }
+        return PGCM_OK;
+    }
+    return PGCM_ERR_ARG;
 }
 
 size_t pgcm_key_tables_bytes(void) { return kPublicTablesBytes; }

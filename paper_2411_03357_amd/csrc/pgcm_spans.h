@@ -30,10 +30,45 @@ inline uint64_t span_rows(uint64_t len, uint32_t aad_len) {
     return (blocks + kRowBlocks - 1) / kRowBlocks;
 }
 
+// Bytes of descriptors up to which the workgroups read theirs from host memory themselves.
+constexpr size_t kSpanHostBytes = 256 << 10;
+
+// Descriptors of a batch: the workgroups', then, at a multiple of 256, the parts'.
+constexpr size_t span_parts_at(size_t ngroups) { return (sizeof(SpanGroup) * ngroups + 255) / 256 * 256; }
+constexpr size_t span_image_bytes(size_t nparts, size_t ngroups) {
+    return span_parts_at(ngroups) + (sizeof(SpanPart) * nparts + 255) / 256 * 256;
+}
+
+// What a batch of at most n chunks takes at most on a device of num_cu compute units.  Workgroups: every
+// key's share of the compute units may be rounded up to one (deal_groups), and there are at most as
+// many keys as chunks and compute units.
+constexpr size_t span_most_groups(size_t n, size_t num_cu) { return num_cu + (n < num_cu ? n : num_cu); }
+constexpr size_t span_stage_bytes(size_t n, size_t num_cu) {
+    const size_t groups = span_most_groups(n, num_cu), bytes = span_image_bytes(n + groups, groups);
+    return bytes > kSpanHostBytes ? bytes : kSpanHostBytes;
+}
+// clean_slots: those a workspace keeps clean already; descriptors go behind them
+constexpr size_t span_work_bytes(size_t n, size_t num_cu, size_t clean_slots) {
+    const size_t parts = n + span_most_groups(n, num_cu);
+    return (sizeof(ArriveSlot) * (parts > clean_slots ? parts : clean_slots) + 255) / 256 * 256 +
+           span_stage_bytes(n, num_cu);
+}
+
 // What is kept from call to call for cutting batches.
 struct SpanScratch {
     std::vector<uint8_t> image;                // descriptors
     std::vector<uint32_t> rows, cuts, waves;
+
+    void reserve(size_t n, size_t num_cu) {
+        const size_t groups = span_most_groups(n, num_cu);
+        image.resize(kSpanHostBytes);
+        rows.reserve(n);
+        cuts.reserve(groups * kWavesPerGroup + 1);
+        waves.reserve(groups + 1);
+    }
+    size_t capacity() const {
+        return image.capacity() + rows.capacity() + cuts.capacity() + waves.capacity();
+    }
 };
 
 // What one more piece costs a workgroup of sixteen wavefronts, in rows: it ends 2 us later for it, 0.27
@@ -244,18 +279,6 @@ inline SpanPlan plan_spans(const SpanBatch& a, const KeyPart* keys, size_t nkeys
     }
     plan.nparts = np;
     return plan;
-}
-
-// Bytes of descriptors up to which the workgroups read theirs from host memory themselves.
-constexpr size_t kSpanHostBytes = 256 << 10;
-
-// Upper bounds for any batch of at most n chunks on a device of num_cu compute units.
-inline size_t span_stage_bytes(size_t n, size_t num_cu) {
-    const size_t uploaded = sizeof(SpanGroup) * num_cu + sizeof(SpanPart) * (n + num_cu) + 256;
-    return uploaded > kSpanHostBytes ? uploaded : kSpanHostBytes;
-}
-inline size_t span_work_bytes(size_t n, size_t num_cu) {
-    return 2 * sizeof(ArriveSlot) * (n + num_cu) + span_stage_bytes(n, num_cu) + 512;
 }
 
 }  // namespace pgcm

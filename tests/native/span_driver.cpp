@@ -56,11 +56,18 @@ static void check(const std::vector<uint64_t>& len, const std::vector<uint32_t>&
     }
     CHECK(dealt == ngroups && ngroups <= num_cu + keys.size() - 1);
 
-    static SpanScratch scratch;  // as a context keeps it: what is in it is what the last batch left
+    // as a context keeps it: what is in it is what the last batch left; once reserved it does not grow
+    static SpanScratch scratch;
+    scratch.reserve(n, num_cu);
+    const size_t held = scratch.capacity();
     std::vector<SpanGroup> groups(ngroups);
     std::vector<SpanPart> parts(n + ngroups);
     const SpanPlan plan = plan_spans(b, keys.data(), keys.size(), scratch, groups.data(), parts.data());
     CHECK(plan.nparts >= n && plan.nparts <= n + ngroups);
+    CHECK(scratch.capacity() == held && ngroups <= span_most_groups(n, num_cu));
+    CHECK(span_image_bytes(n + ngroups, ngroups) <= span_stage_bytes(n, num_cu));
+    CHECK(sizeof(ArriveSlot) * plan.nparts + span_image_bytes(plan.nparts, ngroups) <=
+          span_work_bytes(n, num_cu, 0));
 
     // the workgroups tile the rows and the parts, and their wavefronts tile each of them
     uint64_t row = 0;
@@ -134,7 +141,8 @@ int main() {
         const double lo = log_between(1, 300000), hi = lo * log_between(1, 1000);
         std::vector<uint64_t> len(n);
         std::vector<uint32_t> aad_len(below(3) ? n : 0), key_of(n), order;
-        const size_t nkeys = below(2) ? 1 : 1 + below(below(4) ? 6 : num_cu);
+        // as many keys as compute units at most
+        const size_t nkeys = below(2) ? 1 : 1 + below(below(4) && num_cu > 6 ? 6 : num_cu);
         for (size_t i = 0; i < n; ++i) {
             len[i] = kind == 0   ? log_between(lo, hi)
                      : kind == 1 ? 1024 * below(20) + below(3) * 16 + below(3)
