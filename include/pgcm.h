@@ -183,10 +183,14 @@ int pgcm_decrypt_verify_batch_iv(pgcm_key_t *key, size_t n, const uint8_t *ivs, 
  *   key_index  HOST array of n entries: chunk i is processed under keys[key_index[i]];
  *              an entry >= nkeys is PGCM_ERR_ARG.
  *   ivs, iv_bytes, tags, ok and the other arrays: as for the _iv calls, indexed by chunk.
- * The chunks are grouped by key, keeping their order, and each group runs as one batch of its key
- * (so each key object's one-stream rule applies), the groups one after the other on hip_stream.
+ * The chunks are grouped by key, keeping their order.  As many keys' chunks as have room for their
+ * descriptors in 256 KiB (some 3400 chunks) go in one launch, with the buffers of one of these keys,
+ * and nothing that is derived from the others stays in them; a key with more chunks, one whose
+ * schedule is forced by a test aid, or one alone, runs as a batch of its own; all one after the
+ * other on hip_stream.  After pgcm_reserve of each key for its share on that stream the call gets no
+ * memory from the GPU's runtime (it sorts the chunks in ordinary process memory).
  * All arguments are checked before anything is enqueued; if an allocation or a HIP call fails in
- * a later group, the groups before it stay enqueued.
+ * a later launch, those before it stay enqueued.
  */
 int pgcm_encrypt_batch_keys(pgcm_key_t *const *keys, size_t nkeys, const uint32_t *key_index,
                             size_t n, const uint8_t *ivs, uint32_t iv_bytes,

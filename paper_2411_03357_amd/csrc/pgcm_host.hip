@@ -45,7 +45,6 @@ constexpr int kMaxDevices = 64;
 // a fold level with at most this many items (one workgroup each fits the chip at once) is folded
 // by the tree kernel
 constexpr uint32_t kFoldTreeMaxItems = 256;
-constexpr uint64_t kSpanMaxRows = 1u << 27;
 
 // Per-chunk schedule: units are counted back from the chunk's end, so that every unit but the
 // first is full and all row boundaries line up with the end of the chunk.
@@ -938,9 +937,9 @@ int run_unit_batch(pgcm_key* key, Context* ctx, const BatchArgs& a, const BatchP
 
 // May a batch of chunks of at most this length, and this many rows in all, go in spans?  (The bounds
 // are those of the powers of H a key has and of 32-bit row numbers.)
-inline bool takes_spans(const pgcm_key* key, const BatchSurvey& v) {
-    return key->one_launch && !key->matrix_hash && !key->forced_unit_power && v.rows <= kSpanMaxRows &&
-           v.longest / (16 * kRowBlocks) + 2 < (uint64_t)kRowHopEntries * kFarHopEntries;
+inline bool takes_spans(const pgcm_key* key, uint64_t rows, uint64_t longest) {
+    return key->one_launch && !key->matrix_hash && !key->forced_unit_power && rows <= kSpanMaxRows &&
+           longest / (16 * kRowBlocks) + 2 < (uint64_t)kRowHopEntries * kFarHopEntries;
 }
 
 // One batch in spans, of one key or of several: the context is that of the first.
@@ -1037,7 +1036,7 @@ int run_batch(pgcm_key* key, BatchArgs a) {
     rc = survey_batch(a, &v);
     if (rc != PGCM_OK) return rc;
     // the units, unless they are not wanted anyway; nothing touched so far
-    const bool spans = !a.fixed && !v.all_one_row && takes_spans(key, v);
+    const bool spans = !a.fixed && !v.all_one_row && takes_spans(key, v.rows, v.longest);
     BatchPlan p{};
     if (!spans) rc = plan_batch(key->forced_unit_power, key->wave_slots, a, &p);
     if (rc != PGCM_OK) return rc;
@@ -1072,7 +1071,7 @@ int run_batch(pgcm_key* key, BatchArgs a) {
     else if (v.all_one_row)
         rc = run_small_batch(key, ctx, a);
     else if (spans) {
-        KeyPart part{key, key->tables, (uint32_t)key->rounds, 0, a.n, v.rows, 0};
+        KeyPart part{key, key->tables, (uint32_t)key->rounds, 0, a.n, v.rows, v.longest, 0};
         rc = run_span_batch(ctx, a, &part, 1);
     } else {
         rc = run_unit_batch(key, ctx, a, p);
@@ -1081,7 +1080,8 @@ int run_batch(pgcm_key* key, BatchArgs a) {
     return rc;
 }
 
-// All of a batch's parts as one batch in spans, in a context of the first part's key.
+// The parts of several keys as one batch in spans, in a context of the first part's key.  (Nothing that
+// is derived from the other keys outlives the batch in there: the kernel wipes what it puts down.)
 int run_span_parts(BatchArgs a, KeyPart* parts, size_t nparts) {
     int rc = note_capture(a);
     if (rc != PGCM_OK) return rc;
@@ -1094,8 +1094,9 @@ int run_span_parts(BatchArgs a, KeyPart* parts, size_t nparts) {
     return rc;
 }
 
-// A batch whose chunks name their key: the chunks are grouped by key (keeping their order) and
-// every group runs as one batch of its key, one after the other on the stream.
+// A batch whose chunks name their key: the chunks are grouped by key (keeping their order), and the
+// keys' parts go in as few launches as share_launch allows, a part that does not go with others as
+// a batch of its key, one after the other on the stream.
 int run_batch_keys(pgcm_key* const* keys, size_t nkeys, const uint32_t* key_index,
                    const BatchArgs& all) {
     if (keys == nullptr || nkeys == 0 || nkeys > 0x7FFFFFFFull) return PGCM_ERR_ARG;
@@ -1107,57 +1108,78 @@ int run_batch_keys(pgcm_key* const* keys, size_t nkeys, const uint32_t* key_inde
     int rc = check_batch(all);
     if (rc != PGCM_OK || all.n == 0) return rc;
     if (key_index == nullptr) return PGCM_ERR_ARG;
-    // every chunk is checked before the first group is enqueued
-    std::vector<uint32_t> first, fill, order;
+    // every chunk is checked before anything is enqueued
+    std::vector<KeyPart> parts;  // of each key; then of those with chunks, in the order they go in
+    std::vector<size_t> keys_in_turn, alone, launches;  // launches: the first part of each, the end
+    std::vector<uint32_t> fill, order;
     try {
-        first.assign(nkeys + 1, 0);
-        fill.assign(nkeys, 0);
+        parts.resize(nkeys);
+        for (size_t i = 0; i < all.n; ++i) {
+            if (key_index[i] >= nkeys) return PGCM_ERR_ARG;
+            rc = check_chunk(all, i);
+            if (rc != PGCM_OK) return rc;
+            KeyPart& part = parts[key_index[i]];
+            ++part.n;
+            part.rows += span_rows(all, i);
+            if (all.len[i] > part.longest) part.longest = all.len[i];
+        }
+        const size_t num_cu = (size_t)keys[0]->num_cu;
+        size_t n = 0;
+        uint64_t rows = 0;
+        for (size_t k = 0; k < nkeys; ++k) {
+            const KeyPart& part = parts[k];
+            if (part.n == 0) continue;
+            if (!takes_spans(keys[k], part.rows, part.longest) ||
+                !share_launch(1, part.n, part.rows, num_cu)) {
+                alone.push_back(k);
+                continue;
+            }
+            const size_t at = keys_in_turn.size();
+            if (launches.empty() ||
+                !share_launch(at - launches.back() + 1, n + part.n, rows + part.rows, num_cu)) {
+                launches.push_back(at);
+                n = 0, rows = 0;
+            }
+            n += part.n, rows += part.rows;
+            keys_in_turn.push_back(k);
+        }
+        for (size_t k : alone) {
+            launches.push_back(keys_in_turn.size());
+            keys_in_turn.push_back(k);
+        }
+        launches.push_back(keys_in_turn.size());
+        fill.resize(nkeys);
+        std::vector<KeyPart> sorted;
+        sorted.reserve(keys_in_turn.size());
+        size_t first = 0;
+        for (size_t k : keys_in_turn) {
+            KeyPart part = parts[k];
+            part.key = keys[k];
+            part.tables = keys[k]->tables;
+            part.rounds = (uint32_t)keys[k]->rounds;
+            part.first = first;
+            fill[k] = (uint32_t)first;
+            first += part.n;
+            sorted.push_back(part);
+        }
+        parts.swap(sorted);
         order.resize(all.n);
     } catch (const std::bad_alloc&) {
         return PGCM_ERR_NOMEM;
     }
-    for (size_t i = 0; i < all.n; ++i) {
-        if (key_index[i] >= nkeys) return PGCM_ERR_ARG;
-        rc = check_chunk(all, i);
-        if (rc != PGCM_OK) return rc;
-        ++first[key_index[i] + 1];
-    }
-    for (size_t k = 0; k < nkeys; ++k) first[k + 1] += first[k];
-    for (size_t k = 0; k < nkeys; ++k) fill[k] = first[k];
-    for (size_t i = 0; i < all.n; ++i) order[fill[key_index[i]]++] = (uint32_t)i;  // fill: then the end
-    // all keys' chunks at once, in spans ...
-    std::vector<KeyPart> parts;
-    try {
-        for (size_t k = 0; k < nkeys; ++k)
-            if (fill[k] != first[k])
-                parts.push_back(KeyPart{keys[k], keys[k]->tables, (uint32_t)keys[k]->rounds, first[k],
-                                        first[k + 1] - first[k], 0, 0});
-    } catch (const std::bad_alloc&) {
-        return PGCM_ERR_NOMEM;
-    }
-    if (parts.size() > 1 && parts.size() <= (size_t)keys[0]->num_cu) {
+    for (size_t i = 0; i < all.n; ++i) order[fill[key_index[i]]++] = (uint32_t)i;
+    for (size_t l = 0; l + 1 < launches.size(); ++l) {
+        KeyPart *const begin = parts.data() + launches[l], *const end = parts.data() + launches[l + 1];
         BatchArgs a = all;
-        a.order = order.data();
-        bool spans = true;
-        BatchSurvey v;
-        for (KeyPart& part : parts) {
-            for (size_t k = part.first; k < part.first + part.n; ++k) {
-                const uint64_t rows = span_rows(a, order[k]), len = all.len[order[k]];
-                part.rows += rows;
-                v.rows += rows;
-                if (len > v.longest) v.longest = len;
-            }
+        a.order = order.data() + begin->first;
+        a.n = end[-1].first + end[-1].n - begin->first;
+        if (end - begin == 1) {
+            rc = run_batch(begin->key, a);
+        } else {
+            const size_t first = begin->first;
+            for (KeyPart* part = begin; part < end; ++part) part->first -= first;
+            rc = run_span_parts(a, begin, (size_t)(end - begin));
         }
-        for (const KeyPart& part : parts) spans = spans && takes_spans(part.key, v);
-        if (spans)
-            return run_span_parts(a, parts.data(), parts.size());
-    }
-    // ... or one key's after the other's
-    for (const KeyPart& part : parts) {
-        BatchArgs group = all;
-        group.n = part.n;
-        group.order = order.data() + part.first;
-        rc = run_batch(part.key, group);
         if (rc != PGCM_OK) return rc;
     }
     return PGCM_OK;

@@ -2007,9 +2007,10 @@ __device__ __forceinline__ bool last_to_arrive(uint32_t* word, uint32_t of, uint
 }
 
 // The result of workgroup g of the n of a chunk, whose slots begin at `slots`, is in `sum`.  True in
-// the workgroup that arrives last, with the sum of all results.
+// the workgroup that arrives last, with the sum of all results.  wipe: nothing of the results is to
+// stay behind.
 __device__ __forceinline__ bool last_of_chunk(ArriveSlot* slots, uint32_t g, uint32_t n, Block& sum,
-                                              uint32_t lane) {
+                                              uint32_t lane, bool wipe = false) {
     if (lane == 0)
         store_block_device_scope(&slots[g].sum, sum.w[0], sum.w[1], sum.w[2], sum.w[3]);
     // the result must have reached memory before the arrival is counted: it is a device-scope
@@ -2027,6 +2028,8 @@ __device__ __forceinline__ bool last_of_chunk(ArriveSlot* slots, uint32_t g, uin
         const Block b = load_block_device_scope(&slots[i].sum);
         block_xor(sum, b);
     }
+    if (wipe)
+        for (uint32_t i = lane; i < n; i += 64) store_block_device_scope(&slots[i].sum, 0, 0, 0, 0);
 #pragma unroll
     for (int k = 0; k < 4; ++k) sum.w[k] = rows_summed(row_summed(sum.w[k]));
     return true;
@@ -2374,6 +2377,7 @@ struct SpanArgs {
     uint32_t iv_len;
     ArriveSlot* slots;
     uint8_t *tags, *ok;
+    bool wipe;              // the slots lie in another key's workspace: see last_of_chunk
 };
 struct SpanLds {
     BulkLds tables;
@@ -2511,7 +2515,9 @@ __device__ __forceinline__ void walk_span(const KeyTables* __restrict__ kt, uint
         }
         if (slots > 1) {
             const uint32_t slot = PGCM_WORD(slot);
-            if (!last_of_chunk(args.slots + slot, PGCM_WORD(own_slot) - slot, slots, tag, lane)) continue;
+            if (!last_of_chunk(args.slots + slot, PGCM_WORD(own_slot) - slot, slots, tag, lane,
+                               args.wipe))
+                continue;
         }
         write_or_compare_tag<kDecrypt>(tag, tag_at, received, args.ok + PGCM_WORD(index),
                                        reinterpret_cast<uint8_t*>(PGCM_PAIR(dst)), PGCM_PAIR(len), lane);
@@ -2601,7 +2607,7 @@ __global__ __launch_bounds__(kGroupThreads) void span_kernel(
         part += more;
         if (more < 64) break;
     }
-    const SpanArgs args{parts, ivs, iv_len, slots, tags, ok};
+    const SpanArgs args{parts, ivs, iv_len, slots, tags, ok, key == nullptr};
     const uint32_t rounds = __builtin_amdgcn_readlane(key_word, 60);
     if (rounds == 14)
         walk_span<kDecrypt, 14>(kt, key_word, args, row, end, part, lane, wave, lds);

@@ -39,17 +39,33 @@ constexpr size_t span_image_bytes(size_t nparts, size_t ngroups) {
     return span_parts_at(ngroups) + (sizeof(SpanPart) * nparts + 255) / 256 * 256;
 }
 
-// What a batch of at most n chunks takes at most on a device of num_cu compute units.  Workgroups: every
-// key's share of the compute units may be rounded up to one (deal_groups), and there are at most as
-// many keys as chunks and compute units.
-constexpr size_t span_most_groups(size_t n, size_t num_cu) { return num_cu + (n < num_cu ? n : num_cu); }
+// (the bound of 32-bit row numbers, with room for sums of them)
+constexpr uint64_t kSpanMaxRows = 1u << 27;
+
+// Several keys' chunks share a launch, and with it a context of one of the keys, if their descriptors
+// fit what every context that was reserved for spans has room for, however little it was reserved
+// for: kSpanHostBytes of staging, a slot for each of so many descriptors, and such an image behind.
+constexpr bool share_launch(size_t nkeys, size_t n, uint64_t rows, size_t num_cu) {
+    return nkeys <= num_cu && rows <= kSpanMaxRows &&
+           span_image_bytes(n + num_cu + nkeys, num_cu + nkeys) <= kSpanHostBytes;
+}
+constexpr size_t kSharedParts = kSpanHostBytes / sizeof(SpanPart);
+
+// What a batch of one key and at most n chunks, or one of several keys that share a launch, takes at
+// most on a device of num_cu compute units.  Workgroups: every key's share of the compute units may
+// be rounded up to one (deal_groups).
+constexpr size_t span_most_groups(size_t num_cu) { return 2 * num_cu; }
+constexpr size_t span_most_parts(size_t n, size_t num_cu) {
+    const size_t parts = n + span_most_groups(num_cu);
+    return parts > kSharedParts ? parts : kSharedParts;
+}
 constexpr size_t span_stage_bytes(size_t n, size_t num_cu) {
-    const size_t groups = span_most_groups(n, num_cu), bytes = span_image_bytes(n + groups, groups);
+    const size_t groups = span_most_groups(num_cu), bytes = span_image_bytes(n + groups, groups);
     return bytes > kSpanHostBytes ? bytes : kSpanHostBytes;
 }
 // clean_slots: those a workspace keeps clean already; descriptors go behind them
 constexpr size_t span_work_bytes(size_t n, size_t num_cu, size_t clean_slots) {
-    const size_t parts = n + span_most_groups(n, num_cu);
+    const size_t parts = span_most_parts(n, num_cu);
     return (sizeof(ArriveSlot) * (parts > clean_slots ? parts : clean_slots) + 255) / 256 * 256 +
            span_stage_bytes(n, num_cu);
 }
@@ -60,9 +76,9 @@ struct SpanScratch {
     std::vector<uint32_t> rows, cuts, waves;
 
     void reserve(size_t n, size_t num_cu) {
-        const size_t groups = span_most_groups(n, num_cu);
+        const size_t groups = span_most_groups(num_cu);
         image.resize(kSpanHostBytes);
-        rows.reserve(n);
+        rows.reserve(span_most_parts(n, num_cu));
         cuts.reserve(groups * kWavesPerGroup + 1);
         waves.reserve(groups + 1);
     }
@@ -87,8 +103,8 @@ struct KeyPart {
     const KeyTables* tables;  // of the key
     uint32_t rounds;
     size_t first, n;
-    uint64_t rows;
-    uint32_t groups;  // workgroups
+    uint64_t rows, longest;   // the longest in bytes
+    uint32_t groups;          // workgroups
 
     uint64_t weight() const { return rows + kPieceRows * n; }
 };

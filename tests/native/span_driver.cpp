@@ -30,7 +30,7 @@ static uint64_t log_between(double lo, double hi) {
             exit(1);                                                                      \
         }                                                                                 \
     } while (0)
-static uint64_t g_batch, g_groups, g_parts;
+static uint64_t g_batch, g_groups, g_parts, g_shared;
 
 static void check(const std::vector<uint64_t>& len, const std::vector<uint32_t>& aad_len,
                   const std::vector<uint32_t>& order, std::vector<KeyPart>& keys, uint32_t num_cu) {
@@ -56,18 +56,24 @@ static void check(const std::vector<uint64_t>& len, const std::vector<uint32_t>&
     }
     CHECK(dealt == ngroups && ngroups <= num_cu + keys.size() - 1);
 
-    // as a context keeps it: what is in it is what the last batch left; once reserved it does not grow
-    static SpanScratch scratch;
-    scratch.reserve(n, num_cu);
+    // as a context keeps it: what is in it is what the last batch left; once reserved it does not grow,
+    // for keys that share a launch even if it was reserved for one chunk
+    static SpanScratch kept;
+    SpanScratch fresh;
+    const bool shared = share_launch(keys.size(), n, total, num_cu);
+    SpanScratch& scratch = shared ? fresh : kept;
+    const size_t reserved = shared ? 1 : n;
+    scratch.reserve(reserved, num_cu);
     const size_t held = scratch.capacity();
     std::vector<SpanGroup> groups(ngroups);
     std::vector<SpanPart> parts(n + ngroups);
     const SpanPlan plan = plan_spans(b, keys.data(), keys.size(), scratch, groups.data(), parts.data());
     CHECK(plan.nparts >= n && plan.nparts <= n + ngroups);
-    CHECK(scratch.capacity() == held && ngroups <= span_most_groups(n, num_cu));
-    CHECK(span_image_bytes(n + ngroups, ngroups) <= span_stage_bytes(n, num_cu));
-    CHECK(sizeof(ArriveSlot) * plan.nparts + span_image_bytes(plan.nparts, ngroups) <=
-          span_work_bytes(n, num_cu, 0));
+    CHECK(scratch.capacity() == held && ngroups <= span_most_groups(num_cu));
+    CHECK(span_image_bytes(n + ngroups, ngroups) <= span_stage_bytes(reserved, num_cu));
+    CHECK((sizeof(ArriveSlot) * plan.nparts + 255) / 256 * 256 + span_image_bytes(plan.nparts, ngroups) <=
+          span_work_bytes(reserved, num_cu, 0));
+    g_shared += shared && keys.size() > 1;
 
     // the workgroups tile the rows and the parts, and their wavefronts tile each of them
     uint64_t row = 0;
@@ -156,7 +162,7 @@ int main() {
         }
         std::vector<KeyPart> keys;
         for (size_t q = 0; q < nkeys; ++q) {
-            KeyPart key{nullptr, reinterpret_cast<const KeyTables*>((uintptr_t)tables + 16 * q), (uint32_t)(10 + 2 * below(3)), order.size(), 0, 0, 0};
+            KeyPart key{nullptr, reinterpret_cast<const KeyTables*>((uintptr_t)tables + 16 * q), (uint32_t)(10 + 2 * below(3)), order.size(), 0, 0, 0, 0};
             for (size_t i = 0; i < n; ++i)
                 if (key_of[i] == q) order.push_back((uint32_t)i);
             key.n = order.size() - key.first;
@@ -167,10 +173,11 @@ int main() {
     // the longest chunk that goes in spans: as many rows as there are powers of H for
     {
         const uint64_t rows = (uint64_t)kRowHopEntries * kFarHopEntries - 3;
-        std::vector<KeyPart> keys{KeyPart{nullptr, tables, 14, 0, 2, 0, 0}};
+        std::vector<KeyPart> keys{KeyPart{nullptr, tables, 14, 0, 2, 0, 0, 0}};
         check({rows * 16 * kRowBlocks, 5}, {1024, 1025}, {1, 0}, keys, 256);
     }
-    printf("batches %llu, workgroups %llu, parts %llu\n", (unsigned long long)g_batch,
-           (unsigned long long)g_groups, (unsigned long long)g_parts);
+    printf("batches %llu, %llu of them of keys that share a launch, workgroups %llu, parts %llu\n",
+           (unsigned long long)g_batch, (unsigned long long)g_shared, (unsigned long long)g_groups,
+           (unsigned long long)g_parts);
     return 0;
 }
