@@ -164,7 +164,9 @@ int pgcm_reserve(pgcm_key_t *key, void *hip_stream, size_t n_max, uint64_t paylo
  *   ivs       DEVICE, n * iv_bytes bytes; chunk i uses ivs[iv_bytes i .. iv_bytes (i + 1) - 1].
  *   iv_bytes  length of every IV of the batch, >= 1; 0 is PGCM_ERR_ARG.  With 12 these calls are
  *             pgcm_encrypt_batch / pgcm_decrypt_verify_batch.
- * Everything else as above.  Long IVs are hashed by one GPU thread per chunk.
+ * Everything else as above.  The wavefronts that work on a chunk hash its IV themselves, a kilobyte
+ * in one step; only batches of more than 512 chunks that all are at most 1008 bytes long, and those
+ * cut into units (see pgcm_describe_schedule), hash it block after block.
  */
 int pgcm_encrypt_batch_iv(pgcm_key_t *key, size_t n, const uint8_t *ivs, uint32_t iv_bytes,
                           const void *const *aad, const uint32_t *aad_len,

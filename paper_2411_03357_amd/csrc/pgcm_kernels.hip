@@ -2035,12 +2035,80 @@ __device__ __forceinline__ bool last_of_chunk(ArriveSlot* slots, uint32_t g, uin
     return true;
 }
 
+// this lane's share of (the length block) * H, to be summed over the lanes, from H's nibble table in
+// memory: lane p < 32 looks up nibble p
+__device__ __forceinline__ Block length_block_entry(const Block* __restrict__ h_table,
+                                                    uint64_t aad_len, uint64_t len, uint32_t lane) {
+    const uint64_t abits = aad_len * 8, cbits = len * 8;
+    const uint32_t w = (lane / 8) % 4;
+    const uint32_t be = w == 0 ? (uint32_t)(abits >> 32) : w == 1 ? (uint32_t)abits
+                        : w == 2 ? (uint32_t)(cbits >> 32) : (uint32_t)cbits;
+    const uint32_t nibble = (be >> (28 - 4 * (lane % 8))) & 15;
+    return lane < 32 ? h_table[lane * 16 + nibble] : Block{{0, 0, 0, 0}};
+}
+
+// the sum over the lanes of y * H^(65 - lane), in all lanes
+__device__ __forceinline__ GfWords lanes_summed(const GfWords* __restrict__ powers, const uint32_t y[4]) {
+    GfWords q[kDotSlices];
+#pragma unroll
+    for (uint32_t t = 0; t < kDotSlices; ++t) q[t] = powers[t];
+    GfWords acc{{0, 0, 0, 0}};
+    uint32_t v[4] = {y[0], y[1], y[2], y[3]};
+    // (a loop: unrolled, its masks are made ahead of their use and take the registers of the powers)
+#pragma unroll 1
+    for (int bit = 0; bit < 8; ++bit) {
+        gfw_mul_x(acc);
+#pragma unroll
+        for (uint32_t t = 0; t < kDotSlices; ++t) {
+            const uint32_t m = (uint32_t)((int32_t)(v[t / 4] << (31 - 8 * (t % 4))) >> 31);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc.a[k] ^= q[t].a[k] & m;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] >>= 1;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc.a[k] = rows_summed(row_summed(acc.a[k]));
+    return acc;
+}
+
+// J0 (see j0_from_iv) of an IV of more than one block, by a wavefront, in all lanes.  The blocks go into
+// rows counted back from the last one, like a chunk's: one round of loads and a sum over the lanes
+// for 1 KiB of IV, where hashing it block after block from the table in memory takes 2.1 us a block,
+// and that for every piece of a chunk again (300 adapters, 16-byte IVs: 102 us; of 200 bytes
+// 174 -> 106, of 1000 499 -> 106; one 320 KiB chunk, 12 us, with 200 bytes 40 -> 16).
+__device__ __forceinline__ Block wave_j0_rows(const KeyTables* __restrict__ kt, const uint8_t* iv,
+                                              uint32_t iv_len, uint32_t lane) {
+    const uint32_t blocks = iv_len / 16 + (iv_len % 16 != 0);
+    const uint32_t rows = (blocks - 1) / kRowBlocks + 1;
+    GfWords sum{{0, 0, 0, 0}}, hop{{0, 0, 0, 0}};
+#pragma unroll 1
+    for (uint32_t r = 0; r < rows; ++r) {
+        if (r == 1) {
+            hop = kt->row_hop[1];
+            spread_over_row(hop, lane);
+        }
+        if (r != 0) sum = times_spread(sum, hop, lane);
+        Block b{{0, 0, 0, 0}};
+        const uint32_t end = blocks - (rows - 1 - r) * kRowBlocks;  // of the row
+        if (end + lane >= kRowBlocks) b = padded_block(iv, iv_len, end + lane - kRowBlocks);
+        const GfWords row = lanes_summed(kt->dot[lane], b.w);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) sum.a[k] ^= row.a[k];
+    }
+    Block j = gfw_to_block(sum), last = length_block_entry(kt->ghash[0], 0, iv_len, lane);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) j.w[k] ^= rows_summed(row_summed(last.w[k]));
+    return j;
+}
+
 // J0 (see j0_from_iv) of an IV of at most one block by a wavefront, in all lanes: IV * H^2 + (length
 // block) * H, a nibble of the one or the other per lane, in one round of loads instead of two
 // products one after the other (16-byte IVs, 240 chunks of three keys: first row after 13.4 us).
 __device__ __forceinline__ Block wave_j0(const KeyTables* __restrict__ kt, const uint8_t* iv,
                                          uint32_t iv_len, uint32_t lane) {
-    if (iv_len == 12 || iv_len > 16) return j0_from_iv(kt, iv, iv_len);
+    if (iv_len == 12) return j0_from_iv(kt, iv, iv_len);
+    if (iv_len > 16) return wave_j0_rows(kt, iv, iv_len, lane);
     const bool of_iv = lane < 32;
     const uint32_t place = lane % 32, at = place / 2;
     uint32_t byte = 0;
@@ -2054,18 +2122,6 @@ __device__ __forceinline__ Block wave_j0(const KeyTables* __restrict__ kt, const
 #pragma unroll
     for (int k = 0; k < 4; ++k) z.w[k] = rows_summed(row_summed(z.w[k]));
     return z;
-}
-
-// this lane's share of (the length block) * H, to be summed over the lanes, from H's nibble table in
-// memory: lane p < 32 looks up nibble p
-__device__ __forceinline__ Block length_block_entry(const Block* __restrict__ h_table,
-                                                    uint64_t aad_len, uint64_t len, uint32_t lane) {
-    const uint64_t abits = aad_len * 8, cbits = len * 8;
-    const uint32_t w = (lane / 8) % 4;
-    const uint32_t be = w == 0 ? (uint32_t)(abits >> 32) : w == 1 ? (uint32_t)abits
-                        : w == 2 ? (uint32_t)(cbits >> 32) : (uint32_t)cbits;
-    const uint32_t nibble = (be >> (28 - 4 * (lane % 8))) & 15;
-    return lane < 32 ? h_table[lane * 16 + nibble] : Block{{0, 0, 0, 0}};
 }
 
 }  // namespace
@@ -2345,31 +2401,6 @@ PGCM_INSTANTIATE_SWAP(true);
 // results of a chunk's pieces then only have to be added; the wavefront that finishes the last
 // piece does that and writes the tag or the verdict (see the one-launch kernel).
 namespace {
-
-// the sum over the lanes of y * H^(65 - lane), in all lanes
-__device__ __forceinline__ GfWords lanes_summed(const GfWords* __restrict__ powers, const uint32_t y[4]) {
-    GfWords q[kDotSlices];
-#pragma unroll
-    for (uint32_t t = 0; t < kDotSlices; ++t) q[t] = powers[t];
-    GfWords acc{{0, 0, 0, 0}};
-    uint32_t v[4] = {y[0], y[1], y[2], y[3]};
-    // (a loop: unrolled, its masks are made ahead of their use and take the registers of the powers)
-#pragma unroll 1
-    for (int bit = 0; bit < 8; ++bit) {
-        gfw_mul_x(acc);
-#pragma unroll
-        for (uint32_t t = 0; t < kDotSlices; ++t) {
-            const uint32_t m = (uint32_t)((int32_t)(v[t / 4] << (31 - 8 * (t % 4))) >> 31);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) acc.a[k] ^= q[t].a[k] & m;
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] >>= 1;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) acc.a[k] = rows_summed(row_summed(acc.a[k]));
-    return acc;
-}
 
 struct SpanArgs {
     const SpanPart* parts;  // in memory, of the workgroup

@@ -1,6 +1,7 @@
 """Batches cut into spans of rows: chunks that a wavefront, a workgroup or several share, that end at
-and next to the edges of a row, keys with fewer rows than a workgroup has wavefronts, and lists of
-chunks longer than a workgroup keeps in LDS — against the CPU oracle, bit for bit."""
+and next to the edges of a row, keys with fewer rows than a workgroup has wavefronts, lists of
+chunks longer than a workgroup keeps in LDS, and IVs of many blocks — against the CPU oracle, bit for
+bit."""
 import numpy as np
 import pytest
 import torch
@@ -35,6 +36,14 @@ SHAPES = {
     "many": lambda r: (_even(r, 9000, 40, 3 * KIB), (32,), 1, 12),
     # shares of many rows
     "big": lambda r: (_even(r, 60, 500 * KIB, 2 * MIB) + [9 * MIB + 5], (16,), 1, 12),
+    # IVs of several blocks, up to the edges of a row of 64 and beyond, hashed by the wavefronts that
+    # need them: chunks cut into spans, and the three kinds of one-launch batches
+    "iv_17": lambda r: (_even(r, 90, 4 * KIB, 500 * KIB), (32, 16), 2, 17),
+    "iv_1000": lambda r: (_even(r, 900, 40, 30 * KIB), (24,), 1, 1000),
+    "iv_1024": lambda r: ([1, 5000, 0, 8 * KIB], (32,), 1, 1024),
+    "iv_1025": lambda r: ([300 * KIB + 5], (32,), 1, 1025),
+    "iv_2064": lambda r: (_even(r, 12, 300 * KIB, 350 * KIB), (16,), 1, 2064),
+    "iv_3089": lambda r: (_even(r, 20, KIB, 90 * KIB), (24, 32), 2, 3089),
 }
 
 
