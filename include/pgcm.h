@@ -36,6 +36,12 @@
  *     batch needs more descriptor or workspace memory than its context has: the first batches on
  *     a stream, and any batch larger than those before it.  pgcm_reserve does that work ahead of
  *     time; pgcm_encrypt_batch_static never allocates at all.
+ *   - A batch call that need not allocate can be captured into a graph: after pgcm_reserve for its
+ *     stream, four calls for each time that is called again.  (A call of at most 64 chunks that
+ *     goes in one launch takes none of the four.)  Replays take their place in the order of the
+ *     stream's batches: they go on that stream or are ordered with it.  The buffers that a replay
+ *     reads and writes stay the graph's until pgcm_free_key; other batches of the stream may run
+ *     between the capture and the replays.
  */
 #ifndef PGCM_H
 #define PGCM_H
@@ -138,6 +144,8 @@ int pgcm_decrypt_verify_batch(pgcm_key_t *key, size_t n, const uint8_t *ivs,
  * GPU work can overlap (different streams without ordering between them) race and give wrong
  * results; calls on one stream are safe.  The array keeps the last call's contents; what a call
  * needs at zero it clears itself.  pgcm_free_key wipes the array if the key used it.
+ * The four staging buffers are used in turn: a graph that such calls were captured into holds at
+ * most four of them, and is not to be replayed once another four calls have been made under the key.
  */
 #define PGCM_STATIC_WORKSPACE_BYTES ((size_t)8 << 20)
 #define PGCM_STATIC_MAX_CHUNKS ((size_t)1024)

@@ -106,6 +106,12 @@ inline uint32_t choose_unit_power(size_t n, const uint32_t* order, const uint64_
 
 namespace {
 
+struct KeptBuffer {
+    uint8_t* p;
+    size_t bytes;
+    bool host;  // pinned host memory; otherwise device memory
+};
+
 // What one batch in flight needs besides the key's tables: pinned staging buffers for the
 // descriptors the host writes, and the device workspace the kernels of the batch share.  Batches
 // that use one context are ordered by the stream the context is bound to, which is what makes
@@ -125,6 +131,11 @@ struct Context {
     uint32_t* counter_at = nullptr;  // where the unit counter was last known to be zero
     bool counter_dirty = true;
     size_t clean_slots = 0;  // so many ArriveSlots at the start of `work` have counts of zero
+    // A batch of its was captured into a graph, whose replays may come between any two other batches:
+    // nothing is taken for clean from one batch to the next any more, the context keeps its stream,
+    // and what a replay reads or writes is kept until the key is freed.
+    bool captured = false;
+    std::vector<KeptBuffer> graph_buffers;
     SpanScratch scratch;     // of the call that is using the context
     uint64_t allocations = 0;  // times a batch or pgcm_reserve had to get any of these more room
     // binding
@@ -193,6 +204,15 @@ int create_stage_events(Context* c) {
 }
 
 void destroy_context(Context* c, bool wipe_work) {
+    for (const KeptBuffer& b : c->graph_buffers) {
+        if (b.host) {
+            memset(b.p, 0, b.bytes);
+            (void)hipHostFree(b.p);
+        } else {
+            if (wipe_work) (void)hipMemset(b.p, 0, b.bytes);
+            (void)hipFree(b.p);
+        }
+    }
     if (c->work && c->growable) {
         // the workspace holds key-dependent values (tag masks, partial hashes)
         if (wipe_work) (void)hipMemset(c->work, 0, c->work_cap);
@@ -234,9 +254,17 @@ int ensure_work(Context* c, size_t bytes, hipStream_t stream) {
     if (c->work_cap >= bytes) return PGCM_OK;
     if (!c->growable) return PGCM_ERR_CAPACITY;
     if (c->work) {
-        // earlier batches on this stream may still read the old workspace
-        PGCM_HIP(hipStreamSynchronize(stream));
-        PGCM_HIP(hipFree(c->work));
+        if (c->captured) {
+            try {
+                c->graph_buffers.push_back(KeptBuffer{c->work, c->work_cap, false});
+            } catch (const std::bad_alloc&) {
+                return PGCM_ERR_NOMEM;
+            }
+        } else {
+            // earlier batches on this stream may still read the old workspace
+            PGCM_HIP(hipStreamSynchronize(stream));
+            PGCM_HIP(hipFree(c->work));
+        }
         c->work = nullptr;
         c->work_cap = 0;
     }
@@ -264,7 +292,7 @@ int acquire_context(pgcm_key* key, hipStream_t stream, Context** out) {
     if (pick == nullptr) {
         Context* lru = nullptr;
         for (Context* c : key->contexts) {
-            if (c->in_call) continue;
+            if (c->in_call || c->captured) continue;
             // free for re-binding: never bound, or its last batch has ended.  (A context that
             // pgcm_reserve has bound and no batch has used yet is left for its stream.)
             if (!c->bound || (c->last_stage >= 0 &&
@@ -324,7 +352,8 @@ void release_context(pgcm_key* key, Context* c) {
 // The event that marks the end of a batch is attached to the batch's last kernel: the kernel's own
 // completion signal serves, where a recorded event is a packet of its own that the next kernel
 // waits behind (2.8 us per call between back-to-back kernels of 5 us; 0.1 us this way).  A stream
-// that is being captured into a graph takes no such launch, so there the event is recorded.
+// that is being captured into a graph takes no such launch; nothing waits for a captured batch
+// (end_of_batch).
 template <class... P, class... A>
 void launch_last(void (*kernel)(P...), dim3 grid, dim3 block, hipStream_t stream, bool capturing,
                  hipEvent_t done, A... args) {
@@ -334,13 +363,30 @@ void launch_last(void (*kernel)(P...), dim3 grid, dim3 block, hipStream_t stream
         hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, nullptr, done, 0, P(args)...);
 }
 
-// marks the end of a batch that used stage s of the context
-int end_of_batch(Context* c, int s, hipStream_t stream, bool capturing) {
-    if (capturing) PGCM_HIP(hipEventRecord(c->stage_done[s], stream));
-    c->stage_used[s] = true;
-    c->last_stage = s;
+// The end of a batch whose last kernel was enqueued with stage s's event.  staged: it reads the staging
+// buffer as well.  A captured batch has not run, and its replays read the buffer whenever they come:
+// the buffer goes to the graph.  (The fixed context has no other; its buffers are used in turn again.)
+int end_of_batch(Context* c, int s, bool capturing, bool staged) {
     c->bound = true;
-    c->next_stage = (s + 1) % kStages;
+    if (staged) c->next_stage = (s + 1) % kStages;
+    if (!capturing) {
+        if (staged) c->stage_used[s] = true;
+        c->last_stage = s;
+        return PGCM_OK;
+    }
+    c->captured = true;
+    c->clean_slots = 0;
+    c->counter_at = nullptr;
+    if (staged && c->growable) {
+        try {
+            c->graph_buffers.push_back(KeptBuffer{c->stage[s], c->stage_cap[s], true});
+        } catch (const std::bad_alloc&) {
+            return PGCM_ERR_NOMEM;
+        }
+        c->stage[s] = nullptr;
+        c->stage_cap[s] = 0;
+        c->stage_used[s] = false;
+    }
     return PGCM_OK;
 }
 
@@ -668,7 +714,7 @@ int run_small_batch(pgcm_key* key, Context* ctx, const BatchArgs& a) {
                             nchunks, a.ivs, a.iv_len, a.tags, (uint8_t*)nullptr);
     // from here on the stream will read the staging buffer: mark its end even if a later call
     // fails, so that the buffer is not rewritten under a running kernel
-    const int rc_end = end_of_batch(ctx, s, a.stream, a.capturing);
+    const int rc_end = end_of_batch(ctx, s, a.capturing, true);
     rc = record_timing_stop(key, a.stream);
     if (rc != PGCM_OK) return rc;
     PGCM_HIP(hipGetLastError());
@@ -680,15 +726,17 @@ constexpr size_t kSwapWorkBytes = sizeof(ArriveSlot) * kSwapMaxGroups;
 
 // Makes the counts of the first n slots of the workspace zero.  Every batch leaves them zero; they
 // need clearing when the workspace is new, was used by a batch with units, or is shared between
-// keys, and in a graph, before whose replays any of that may happen.
+// keys, and in a graph, before whose replays any of that may happen, as well as wherever a replay may
+// have come in between.
 void use_slots(Context* ctx, size_t n, hipStream_t stream, bool capturing) {
-    if (ctx->clean_slots < n || !ctx->growable || capturing) {
+    const bool trusted = ctx->growable && !capturing && !ctx->captured;
+    if (ctx->clean_slots < n || !trusted) {
         const uint32_t n_clear = (uint32_t)(n * (sizeof(ArriveSlot) / 16));
         const uint32_t groups = (n_clear + 255) / 256;
         hipLaunchKernelGGL(upload_kernel, dim3(groups < 1024 ? groups : 1024), dim3(256), 0, stream,
                            (uint4*)nullptr, (const uint4*)nullptr, 0u,
                            reinterpret_cast<uint4*>(ctx->work), n_clear);
-        if (ctx->clean_slots < n) ctx->clean_slots = n;
+        if (trusted && ctx->clean_slots < n) ctx->clean_slots = n;
     }
     ctx->counter_at = nullptr;  // the unit counter of other batches may lie under them
 }
@@ -832,11 +880,9 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapSh
     if (rc_timing == PGCM_OK) rc_timing = record_timing_stop(key, a.stream);
     int rc_end = PGCM_OK;
     if (!in_args) {
-        rc_end = end_of_batch(ctx, s, a.stream, a.capturing);
+        rc_end = end_of_batch(ctx, s, a.capturing, true);
     } else if (ctx != nullptr) {
-        if (a.capturing) PGCM_HIP(hipEventRecord(done, a.stream));
-        ctx->last_stage = s;
-        ctx->bound = true;
+        rc_end = end_of_batch(ctx, s, a.capturing, false);
     }
     if (rc_timing != PGCM_OK) return rc_timing;
     if (hip_failed(hipGetLastError())) {
@@ -863,8 +909,10 @@ int run_unit_batch(pgcm_key* key, Context* ctx, const BatchArgs& a, const BatchP
     {
         // the unit counter is left at zero by the last kernel of every batch; it only needs
         // clearing when the workspace is new, the counter's place in it has moved, an earlier
-        // batch was cut short, or the workspace is shared with other keys (the fixed context)
-        const bool clear = ctx->counter_at != d_counter || ctx->counter_dirty || !ctx->growable;
+        // batch was cut short, or the workspace is shared with other keys (the fixed context) or with
+        // replays of a graph
+        const bool clear = ctx->counter_at != d_counter || ctx->counter_dirty || !ctx->growable ||
+                           ctx->captured || a.capturing;
         ctx->counter_at = d_counter;
         ctx->counter_dirty = true;
         const uint32_t n16 = (uint32_t)(w.upload_bytes / 16);
@@ -925,7 +973,7 @@ int run_unit_batch(pgcm_key* key, Context* ctx, const BatchArgs& a, const BatchP
                 per_group);
     // the stream now reads the staging buffer and the workspace: their end is marked whatever
     // else fails below
-    const int rc_end = end_of_batch(ctx, s, a.stream, a.capturing);
+    const int rc_end = end_of_batch(ctx, s, a.capturing, true);
     if (rc_timing != PGCM_OK) return rc_timing;
     PGCM_HIP(hipGetLastError());
     if (rc_end != PGCM_OK) return rc_end;
@@ -1009,7 +1057,7 @@ int run_span_batch(Context* ctx, const BatchArgs& a, KeyPart* keys, size_t nkeys
                 a.ok);
     for (size_t q = 0; q < nkeys && rc_timing == PGCM_OK; ++q)
         rc_timing = record_timing_stop(keys[q].key, a.stream);
-    const int rc_end = end_of_batch(ctx, s, a.stream, a.capturing);
+    const int rc_end = end_of_batch(ctx, s, a.capturing, true);
     if (hip_failed(hipGetLastError())) {
         ctx->clean_slots = 0;
         return PGCM_ERR_HIP;
