@@ -1047,16 +1047,23 @@ int run_span_batch(Context* ctx, const BatchArgs& a, KeyPart* keys, size_t nkeys
         parts = reinterpret_cast<const SpanPart*>(packets + parts_at);
         stride = 0;
     }
+    // one pair of events per key object, which may be listed more than once
+    auto timed_already = [&](size_t q) {
+        if (keys[q].key->timing)
+            for (size_t p = 0; p < q; ++p)
+                if (keys[p].key == keys[q].key) return true;
+        return false;
+    };
     int rc_timing = PGCM_OK;
     for (size_t q = 0; q < nkeys && rc_timing == PGCM_OK; ++q)
-        rc_timing = record_timing_start(keys[q].key, a.stream);
+        if (!timed_already(q)) rc_timing = record_timing_start(keys[q].key, a.stream);
     launch_last(a.decrypt ? span_kernel<true> : span_kernel<false>, dim3(ngroups),
                 dim3(kGroupThreads), a.stream, a.capturing, ctx->stage_done[s],
                 (const KeyTables*)(nkeys == 1 ? keys[0].key->tables : nullptr), packets, parts,
                 (uint32_t)stride, a.iv_len, a.ivs, reinterpret_cast<ArriveSlot*>(ctx->work), a.tags,
                 a.ok);
     for (size_t q = 0; q < nkeys && rc_timing == PGCM_OK; ++q)
-        rc_timing = record_timing_stop(keys[q].key, a.stream);
+        if (!timed_already(q)) rc_timing = record_timing_stop(keys[q].key, a.stream);
     const int rc_end = end_of_batch(ctx, s, a.capturing, true);
     if (hip_failed(hipGetLastError())) {
         ctx->clean_slots = 0;

@@ -103,3 +103,21 @@ def test_spans(shape):
     assert bad.size == 0, "plaintext byte %d" % bad[0]
     for k in keys:
         k.free()
+
+
+def test_a_key_listed_twice_is_timed_once():
+    w = workloads.mini(2)
+    key = pgcm.expand_key(w.key)
+    b = DeviceBatch(w, torch.from_numpy(w.payload_host()).cuda())
+    index = (np.arange(w.n) % 2).astype(np.uint32)
+    pgcm.set_timing(key, True)
+    for calls in (1, 2, 3):
+        pgcm.encrypt_batch_keys([key, key], index, b.ivs, 12, b.aad_ptrs, b.aad_lens,
+                                b.ptrs(b.plain), b.lens, b.ptrs(b.cipher), b.tags)
+        times = pgcm.bulk_kernel_ms_history(key)
+        assert len(times) == calls and all(t > 0 for t in times), times
+    tags = b.tags.clone()
+    b.encrypt(key)
+    torch.cuda.synchronize()
+    assert torch.equal(tags, b.tags)
+    key.free()
