@@ -144,8 +144,9 @@ int pgcm_decrypt_verify_batch(pgcm_key_t *key, size_t n, const uint8_t *ivs,
  * GPU work can overlap (different streams without ordering between them) race and give wrong
  * results; calls on one stream are safe.  The array keeps the last call's contents; what a call
  * needs at zero it clears itself.  pgcm_free_key wipes the array if the key used it.
- * The four staging buffers are used in turn: a graph that such calls were captured into holds at
- * most four of them, and is not to be replayed once another four calls have been made under the key.
+ * The four staging buffers are used in turn.  A fifth call that needs one in the capture of one graph
+ * is refused with PGCM_ERR_CAPACITY, and the graph is not to be replayed once another four calls have
+ * been made under the key.
  */
 #define PGCM_STATIC_WORKSPACE_BYTES ((size_t)8 << 20)
 #define PGCM_STATIC_MAX_CHUNKS ((size_t)1024)

@@ -123,6 +123,7 @@ struct Context {
     size_t stage_cap[kStages] = {};
     hipEvent_t stage_done[kStages] = {};  // end of the batch that last used the buffer
     bool stage_used[kStages] = {};
+    unsigned long long stage_capture[kStages] = {};  // fixed buffers: the capture that last took it
     int next_stage = 0;
     // device workspace: descriptors, unit maps, fold lists, unit counter, per-chunk E_K(J0),
     // partial sets; or arrival slots, then descriptors
@@ -228,8 +229,9 @@ void destroy_context(Context* c, bool wipe_work) {
 }
 
 // Makes stage s of the context free (waits for the batch that last used it) and at least `bytes`
-// large.
-int ensure_stage(Context* c, int s, size_t bytes) {
+// large.  capture: the one under way, or 0; it cannot have the same buffer twice.
+int ensure_stage(Context* c, int s, size_t bytes, unsigned long long capture = 0) {
+    if (capture != 0 && c->stage_capture[s] == capture) return PGCM_ERR_CAPACITY;
     if (c->stage_used[s]) {
         PGCM_HIP(hipEventSynchronize(c->stage_done[s]));
         c->stage_used[s] = false;
@@ -366,10 +368,10 @@ void launch_last(void (*kernel)(P...), dim3 grid, dim3 block, hipStream_t stream
 // The end of a batch whose last kernel was enqueued with stage s's event.  staged: it reads the staging
 // buffer as well.  A captured batch has not run, and its replays read the buffer whenever they come:
 // the buffer goes to the graph.  (The fixed context has no other; its buffers are used in turn again.)
-int end_of_batch(Context* c, int s, bool capturing, bool staged) {
+int end_of_batch(Context* c, int s, unsigned long long capture, bool staged) {
     c->bound = true;
     if (staged) c->next_stage = (s + 1) % kStages;
-    if (!capturing) {
+    if (capture == 0) {
         if (staged) c->stage_used[s] = true;
         c->last_stage = s;
         return PGCM_OK;
@@ -377,6 +379,7 @@ int end_of_batch(Context* c, int s, bool capturing, bool staged) {
     c->captured = true;
     c->clean_slots = 0;
     c->counter_at = nullptr;
+    if (staged && !c->growable) c->stage_capture[s] = capture;
     if (staged && c->growable) {
         try {
             c->graph_buffers.push_back(KeptBuffer{c->stage[s], c->stage_cap[s], true});
@@ -460,6 +463,7 @@ struct BatchArgs {
     uint8_t* ok;
     hipStream_t stream;
     bool capturing = false;  // the stream is being captured into a graph
+    unsigned long long capture = 0;  // ... which capture that is
     bool fixed = false;  // run in the key's fixed context: allocate nothing, refuse what does not fit
 
     size_t at(size_t k) const { return order ? order[k] : k; }
@@ -699,7 +703,7 @@ int record_timing_stop(pgcm_key* key, hipStream_t stream) {
 int run_small_batch(pgcm_key* key, Context* ctx, const BatchArgs& a) {
     const uint32_t nchunks = (uint32_t)a.n;
     const int s = ctx->next_stage;
-    int rc = ensure_stage(ctx, s, sizeof(ChunkDesc) * a.n);
+    int rc = ensure_stage(ctx, s, sizeof(ChunkDesc) * a.n, a.capture);
     if (rc != PGCM_OK) return rc;
     ChunkDesc* h_desc = reinterpret_cast<ChunkDesc*>(ctx->stage[s]);
     for (size_t k = 0; k < a.n; ++k) describe_chunk(a, a.at(k), h_desc[k]);
@@ -714,7 +718,7 @@ int run_small_batch(pgcm_key* key, Context* ctx, const BatchArgs& a) {
                             nchunks, a.ivs, a.iv_len, a.tags, (uint8_t*)nullptr);
     // from here on the stream will read the staging buffer: mark its end even if a later call
     // fails, so that the buffer is not rewritten under a running kernel
-    const int rc_end = end_of_batch(ctx, s, a.capturing, true);
+    const int rc_end = end_of_batch(ctx, s, a.capture, true);
     rc = record_timing_stop(key, a.stream);
     if (rc != PGCM_OK) return rc;
     PGCM_HIP(hipGetLastError());
@@ -833,7 +837,7 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapSh
     int s = 0;
     if (ctx != nullptr) s = ctx->next_stage;
     if (!in_args) {
-        const int rc = ensure_stage(ctx, s, sizeof(GroupDesc) * shape.groups);
+        const int rc = ensure_stage(ctx, s, sizeof(GroupDesc) * shape.groups, a.capture);
         if (rc != PGCM_OK) return rc;
         h_groups = reinterpret_cast<GroupDesc*>(ctx->stage[s]);
     }
@@ -880,9 +884,9 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapSh
     if (rc_timing == PGCM_OK) rc_timing = record_timing_stop(key, a.stream);
     int rc_end = PGCM_OK;
     if (!in_args) {
-        rc_end = end_of_batch(ctx, s, a.capturing, true);
+        rc_end = end_of_batch(ctx, s, a.capture, true);
     } else if (ctx != nullptr) {
-        rc_end = end_of_batch(ctx, s, a.capturing, false);
+        rc_end = end_of_batch(ctx, s, a.capture, false);
     }
     if (rc_timing != PGCM_OK) return rc_timing;
     if (hip_failed(hipGetLastError())) {
@@ -899,7 +903,7 @@ int run_unit_batch(pgcm_key* key, Context* ctx, const BatchArgs& a, const BatchP
     if (!ctx->growable && (a.n > kFixedMaxChunks || w.bytes > ctx->work_cap))
         return PGCM_ERR_CAPACITY;
     const int s = ctx->next_stage;
-    int rc = ensure_stage(ctx, s, w.upload_bytes);
+    int rc = ensure_stage(ctx, s, w.upload_bytes, a.capture);
     if (rc != PGCM_OK) return rc;
     rc = ensure_work(ctx, w.bytes, a.stream);
     if (rc != PGCM_OK) return rc;
@@ -973,7 +977,7 @@ int run_unit_batch(pgcm_key* key, Context* ctx, const BatchArgs& a, const BatchP
                 per_group);
     // the stream now reads the staging buffer and the workspace: their end is marked whatever
     // else fails below
-    const int rc_end = end_of_batch(ctx, s, a.capturing, true);
+    const int rc_end = end_of_batch(ctx, s, a.capture, true);
     if (rc_timing != PGCM_OK) return rc_timing;
     PGCM_HIP(hipGetLastError());
     if (rc_end != PGCM_OK) return rc_end;
@@ -1064,7 +1068,7 @@ int run_span_batch(Context* ctx, const BatchArgs& a, KeyPart* keys, size_t nkeys
                 a.ok);
     for (size_t q = 0; q < nkeys && rc_timing == PGCM_OK; ++q)
         if (!timed_already(q)) rc_timing = record_timing_stop(keys[q].key, a.stream);
-    const int rc_end = end_of_batch(ctx, s, a.capturing, true);
+    const int rc_end = end_of_batch(ctx, s, a.capture, true);
     if (hip_failed(hipGetLastError())) {
         ctx->clean_slots = 0;
         return PGCM_ERR_HIP;
@@ -1077,6 +1081,7 @@ int note_capture(BatchArgs& a) {
         hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
         PGCM_HIP(hipStreamIsCapturing(a.stream, &status));
         a.capturing = status == hipStreamCaptureStatusActive;
+        if (a.capturing) PGCM_HIP(hipStreamGetCaptureInfo(a.stream, &status, &a.capture));
     }
     return PGCM_OK;
 }

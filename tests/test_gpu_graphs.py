@@ -91,3 +91,40 @@ def test_captured_between_eager_batches(shape):
             eager(r + k).check("after replay %d, %d" % (r, k))
     torch.cuda.synchronize()
     key.free()
+
+
+def test_static_calls_captured_until_the_staging_is_used_up():
+    rng = np.random.default_rng([workloads.BASE_SEED, 5041])
+    raw_key = rng.integers(0, 256, 32, dtype=np.uint8)
+    batches = [_Checked("static_%d" % i, rng, [int(v) for v in rng.integers(1, 40 * KIB, 100 + i)],
+                        raw_key) for i in range(4)]
+    key = pgcm.expand_key(raw_key)
+    stream = torch.cuda.Stream()
+
+    def encrypt(c):
+        pgcm.encrypt_batch_static(key, c.b.ivs, c.b.aad_ptrs, c.b.aad_lens, c.b.ptrs(c.b.plain),
+                                  c.b.lens, c.b.ptrs(c.b.cipher), c.b.tags, stream)
+
+    torch.cuda.synchronize()
+    for c in batches[:3]:
+        encrypt(c)
+    torch.cuda.synchronize()
+    for _ in range(2):                 # a second graph may have the buffers again
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            for c in batches:
+                encrypt(c)
+            with pytest.raises(pgcm.PgcmError) as e:
+                encrypt(batches[0])
+            assert e.value.status == -7
+        for _ in range(3):
+            for c in batches:
+                c.clear()
+            torch.cuda.synchronize()
+            with torch.cuda.stream(stream):
+                graph.replay()
+            torch.cuda.synchronize()
+            for c in batches:
+                assert np.array_equal(c.b.cipher.cpu().numpy(), c.cipher)
+                assert np.array_equal(c.b.tags.cpu().numpy().reshape(-1, 16), c.tags)
+    key.free()
