@@ -98,10 +98,10 @@ def test_lengths_the_cipher_does_not_have_are_errors():
     key.free()
 
 
-@pytest.mark.parametrize("iv_bytes", [12, 16])
-def test_several_keys_in_one_batch(iv_bytes):
-    """every chunk names its key; groups of one key take the bulk or the small-transfer path on
-    their own (key 3 only gets chunks of at most 8 KiB), ivs / tags / ok stay indexed by chunk"""
+@pytest.mark.parametrize("iv_bytes,forced_unit", [(12, 0), (16, 0), (16, 4096)])
+def test_several_keys_in_one_batch(iv_bytes, forced_unit):
+    """every chunk names its key; the keys' chunks go in one launch (key 3 only gets chunks of at most
+    8 KiB), or, where a key's schedule is forced, apart; ivs / tags / ok stay indexed by chunk"""
     w = workloads.with_cipher(workloads.ragged_small(), 32, iv_bytes)
     rng = np.random.default_rng(workloads.BASE_SEED + 99 + iv_bytes)
     raw_keys = [rng.integers(0, 256, kb, dtype=np.uint8) for kb in (32, 16, 24, 32, 16)]
@@ -109,6 +109,7 @@ def test_several_keys_in_one_batch(iv_bytes):
     key_index[w.lens <= 8192] = rng.integers(0, 4, int((w.lens <= 8192).sum()))   # key 4: unused
     assert set(key_index.tolist()) == {0, 1, 2, 3}
     keys = [pgcm.expand_key_bytes(k) for k in raw_keys]
+    pgcm.set_unit_bytes(keys[2], forced_unit)
     host = w.payload_host()
     b = DeviceBatch(w, torch.from_numpy(host).cuda())
     b.cipher.fill_(0xEE)

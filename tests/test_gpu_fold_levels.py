@@ -35,11 +35,12 @@ def _levels(nunits):
     return levels
 
 
-@pytest.mark.parametrize("forced_unit,levels", [(None, 2), (16384, 2), (1024, 2), (32768, 1),
+@pytest.mark.parametrize("forced_unit,levels", [(None, 2), (8192, 2), (16384, 2), (1024, 2), (32768, 1),
                                                 (512 * 1024, 1), (16 << 20, 0)])
 def test_fold_levels_against_the_oracle(forced_unit, levels):
-    """a 16 MiB chunk: two fold levels with 16 KiB units (1025 sets -> 33, the first group short,
-    -> 2), with the 8 KiB units a batch of this size gets by itself (2049 -> 65 -> 3) and with
+    """a 16 MiB chunk: in spans where no unit is forced; two fold levels with 16 KiB units (1025
+    sets -> 33, the first group short, -> 2), with the 8 KiB units the schedule of units has for a
+    batch of this size (2049 -> 65 -> 3) and with
     1 KiB units (16385 -> 513 -> 17); one with 32 KiB units (513 -> 17) and 512 KiB units
     (33 -> 2, the first group a single short unit); none with 16 MiB units (2 sets)"""
     unit = pgcm.unit_bytes()
@@ -118,7 +119,10 @@ def test_one_forced_large_unit_per_wavefront_against_libcrypto():
     key.free()
 
 
-def test_three_fold_levels_against_libcrypto():
+@pytest.mark.parametrize("forced_unit", [None, 16384])
+def test_three_fold_levels_against_libcrypto(forced_unit):
+    """in units; and the same chunk in spans, whose sums are further from its end than the first
+    table of powers of H reaches"""
     unit = pgcm.unit_bytes()
     big = (32 * 32 * 32 + 40) * unit + 16 * 9 + 11      # 512 MiB + 640 KiB + ...
     w = _workload([big], 1, 13)
@@ -126,6 +130,8 @@ def test_three_fold_levels_against_libcrypto():
     plan = pgcm.plan_units(w.lens)
     assert int(plan["final_power"][0]) == 25
     key = pgcm.expand_key(w.key)
+    if forced_unit:
+        pgcm.set_unit_bytes(key, forced_unit)
     b = DeviceBatch(w, w.payload_device())
     b.encrypt(key)
     b.decrypt(key)

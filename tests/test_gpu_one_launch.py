@@ -2,8 +2,8 @@
 swaps come a few chunks at a time, section 5.1).  Every shape that path has — a chunk of one
 unit, of one workgroup, of several workgroups whose sets the last one to arrive folds, runs of
 1, 2, 4, 8 and 16 sets per wavefront, empty chunks, ragged ends, AAD, in place, each forced unit
-size, decryption with rejected chunks — against the CPU oracle, bit for bit; and against the
-sequence of kernels that larger batches take, which must give the same bytes."""
+size, decryption with rejected chunks — against the CPU oracle, bit for bit; and against the units'
+sequence of kernels, which must give the same bytes."""
 import numpy as np
 import pytest
 import torch
@@ -112,8 +112,10 @@ def test_several_chunks_mixed():
     lens = [int(v) for v in np.exp(rng.uniform(np.log(1), np.log(300 * KIB), 24))]
     lens[3], lens[11] = 0, 150 * KIB
     _check_against_oracle(_workload(32, lens), tamper=(3, 11, 23))
-    # 25 chunks: one more than the arguments hold, so the other kernels serve it
+    # as many chunks as the arguments hold, and one more: descriptors in pinned memory
     _check_against_oracle(_workload(33, [40 * KIB] * 25))
+    _check_against_oracle(_workload(34, [20 * KIB] * 64))
+    _check_against_oracle(_workload(35, [20 * KIB] * 65))
 
 
 @pytest.mark.parametrize("unit", [1024, 2048, 4096, 8192, 16384])
@@ -123,20 +125,24 @@ def test_forced_unit_sizes(unit):
 
 
 def test_two_keys_alternate_on_one_stream_and_other_batches_in_between():
-    """the arrival words live at the start of the context's workspace, where a batch of the
-    other kind puts its descriptors: alternating the two kinds must keep both right"""
+    """the arrival words live at the start of the context's workspace, where a batch in units puts
+    its descriptors: alternating batches in one launch, in spans and in units must keep all right"""
     small = _workload(50, [300 * KIB, 2 * MIB, 0, 11 * KIB])
-    big = _workload(51, [64 * KIB] * 600)          # 600 chunks: the sequence of kernels
+    big = _workload(51, [64 * KIB] * 600)          # in spans, every other time in units
     hs, hb = small.payload_host(), big.payload_host()
     key = pgcm.expand_key(small.key)
     big.key = small.key.copy()
     bs = DeviceBatch(small, torch.from_numpy(hs).cuda())
     bb = DeviceBatch(big, torch.from_numpy(hb).cuda())
-    for _ in range(3):
+    for turn in range(4):
         bs.encrypt(key)
+        pgcm.set_unit_bytes(key, 16 * KIB if turn % 2 else 0)
         bb.encrypt(key)
+        pgcm.set_unit_bytes(key, 0)
         bs.decrypt(key)
+        pgcm.set_unit_bytes(key, 16 * KIB if turn % 2 else 0)
         bb.decrypt(key)
+        pgcm.set_unit_bytes(key, 0)
     torch.cuda.synchronize()
     assert bool((bs.ok == 1).all()) and torch.equal(bs.back, bs.plain)
     assert bool((bb.ok == 1).all()) and torch.equal(bb.back, bb.plain)

@@ -256,9 +256,8 @@ def test_two_keys_on_two_streams_at_once():
 
 @pytest.mark.parametrize("lens", [[0, 40, 1000], [0, 3000, 8192], [0, 5, 70000, 1 << 20]])
 def test_long_aad_on_every_path(lens):
-    """AAD of thousands of bytes (ragged, block-aligned, and 70 001 bytes) with chunks that take
-    the one-row kernel, the workgroup-per-chunk kernel and the unit schedule; the empty chunk's
-    AAD is hashed by the final step"""
+    """AAD of thousands of bytes (ragged, block-aligned, and 70 001 bytes) with an empty chunk, chunks
+    of one row, of a workgroup and of many"""
     seed, rng, key, iv0 = workloads._base(11, len(lens))
     alens = [4099, 4096, 70001, 17][:len(lens)]
     la = np.array(lens, np.uint64)

@@ -103,10 +103,10 @@ def test_random_batches_against_libcrypto(first_seed):
 
 
 def test_many_short_chunks():
-    """more short multi-row chunks than the workgroup-per-chunk kernel is used for: the batch goes
-    through the unit schedule, most chunks being a single short unit; and as many one-row chunks,
-    which stay on the wavefront-per-chunk kernel"""
-    for hi, seed in ((8192, 1), (1008, 2)):
+    """more short multi-row chunks than the one-launch kernel is used for: the batch goes in spans,
+    or, where these are switched off, through the unit schedule, most chunks being a single short
+    unit; and as many one-row chunks, which stay on the wavefront-per-chunk kernel"""
+    for hi, seed, spans in ((8192, 1, True), (8192, 1, False), (1008, 2, True)):
         rng = np.random.default_rng([workloads.BASE_SEED, 777, seed])
         n = 700
         lens = rng.integers(0, hi + 1, n).astype(np.uint64)
@@ -122,6 +122,7 @@ def test_many_short_chunks():
                                rng.integers(0, 256, int(alens.sum()), dtype=np.uint8), aad_off)
         host = w.payload_host()
         key = expand(w)
+        pgcm.set_one_launch(key, spans)
         b = DeviceBatch(w, torch.from_numpy(host).cuda())
         b.encrypt(key)
         bad_chunk = 123
