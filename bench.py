@@ -26,22 +26,22 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published peak
 VALU_PEAK_TOPS = 256 * 128 * 2.4e9 / 1e12
 LDS_PEAK_GCYCLES = 256 * 2.4               # 256 CUs, one LDS pipe each, 2.4 GHz: port cycles per ns
 
-# Hardware counters of one bulk_kernel launch on the default workload, taken with
+# Hardware counters of one span_kernel launch on the default workload, taken with
 # `rocprofv3 --pmc` (summaries and commands: profiles/).  They describe the kernel sources
 # (pgcm_kernels.hip and the two headers it includes) whose hash is given; once those change the
 # counters no longer apply and bench.py reports null.
 COUNTERS = {
-    "sources_sha256": "23d93b85df471d2e331f0279dbec7481c4e09c6246208d02277e6dbc7621b70a",
+    "sources_sha256": "a43c6e55e03421166e8ddfa990b3dfef6524afdbada7bcb68807dcd5599d802b",
     "workload": "c2_opt13b_kv_4096x320KiB",
-    "fetch_size_kib": 657146.8,     # FETCH_SIZE per launch
-    "fetch_scale": 1310720.0 / 655383.0,   # a 1 310 720 KiB device copy reads 655 383
-    "write_size_kib": 1395456.0,    # WRITE_SIZE per launch
+    "fetch_size_kib": 656001.4,     # FETCH_SIZE per launch
+    "fetch_scale": 1310720.0 / 655388.0,   # a 1 310 720 KiB device copy reads 655 388
+    "write_size_kib": 1310795.4,    # WRITE_SIZE per launch
     "write_scale": 1310720.0 / 1310720.0,  # the same copy writes 1 310 720.0
-    "valu_wave_instructions": 588482560.0,  # SQ_INSTS_VALU per launch
-    "lds_wave_instructions": 321832960.0,   # SQ_INSTS_LDS per launch
-    "lds_active_cycles": 728154112.0,   # SQ_LDS_IDX_ACTIVE per launch, summed over the 256 CUs
-    "gui_active_cycles": 24682199.5 / 8,  # GRBM_GUI_ACTIVE per launch (summed over the 8 XCDs) ...
-    "pmc_launch_ms": 1.5139392,           # ... and the launch's duration in that same run
+    "valu_wave_instructions": 575656960.0,  # SQ_INSTS_VALU per launch
+    "lds_wave_instructions": 305161728.0,   # SQ_INSTS_LDS per launch
+    "lds_active_cycles": 698790912.0,   # SQ_LDS_IDX_ACTIVE per launch, summed over the 256 CUs
+    "gui_active_cycles": 24283126.3 / 8,  # GRBM_GUI_ACTIVE per launch (summed over the 8 XCDs) ...
+    "pmc_launch_ms": 1.4645,              # ... and the launch's duration in that same run
 }
 
 
@@ -199,8 +199,8 @@ def bitsliced_bench(args):
     """--bitsliced: the cost of the one alternative to table-driven AES rounds, measured.  The
     bitsliced kernel writes the counter-mode keystream for as many blocks as the KV-cache swap
     shape has (no payload is read, nothing is hashed: the round function alone plus the store);
-    the table-driven bulk kernel of the batch calls is timed beside it on that shape, doing the
-    whole of AES-GCM.  Prints ONE JSON line."""
+    the table-driven kernel of the batch calls is timed beside it on that shape, doing the whole of
+    AES-GCM.  Prints ONE JSON line."""
     import re
     import torch
 
@@ -246,7 +246,7 @@ def bitsliced_bench(args):
         "config": {"workload": "%d counter blocks (the block count of %s), keystream only"
                                % (nblocks, w.name)},
         "bitsliced_kernel_ms": round(bs_ms, 4),
-        "table_driven_bulk_kernel_ms": round(table_ms, 4),
+        "table_driven_kernel_ms": round(table_ms, 4),
         "table_driven_GBps_whole_gcm": round(w.payload_bytes / (table_ms * 1e-3) / 1e9, 2),
         "sbox_instructions": sbox, "mixcolumn_addkey_instructions_per_column": mix,
         "valu_instructions_per_round_per_64_blocks": round(per_round / 32.0, 2),
@@ -305,8 +305,8 @@ def latency_bench(args):
 def measure_workload(pgcm, torch, w, args, steps, warmup, headline):
     """One workload through the library's own timing loop.  Returns (results dict, batch, key);
     the caller frees them.  steps passes (encrypt + decrypt-verify) are timed by the host clock,
-    synchronised on both sides, with a pair of events around every bulk kernel; then each
-    direction alone."""
+    synchronised on both sides, with a pair of events around every kernel that touches the payload; then
+    each direction alone."""
     import numpy as np
     from device_batch import DeviceBatch, apply_tampers
 
@@ -358,7 +358,7 @@ def measure_workload(pgcm, torch, w, args, steps, warmup, headline):
     kern_avg_ms = sum(launches) / len(launches)
     # algorithmic HBM bytes of one launch: every payload byte read once and written once, plus
     # per chunk its IV, tag (16), AAD and descriptor (64); what the implementation moves on
-    # top of that (1 KiB of partial hash sums per 16 KiB unit) is overhead, not counted here
+    # top of that (tables, partial results of chunks in several workgroups) is not counted
     aad_total = 0 if w.aad is None else int(w.aad.size)
     algo_bytes = 2 * payload + w.n * (int(w.ivs.shape[1]) + 16 + 64) + aad_total
     achieved = algo_bytes / (kern_avg_ms * 1e-3) / 1e9
@@ -370,7 +370,7 @@ def measure_workload(pgcm, torch, w, args, steps, warmup, headline):
            "enc_GBps": round(payload / (enc_ms * 1e-3) / 1e9, 2),
            "dec_verify_GBps": round(payload / (dec_ms * 1e-3) / 1e9, 2),
            "chunks_rejected_in_dec_verify": len(rejected),
-           "unit_bytes": args.unit_bytes or pgcm.batch_unit_bytes(w.lens),
+           "unit_bytes": (args.unit_bytes or pgcm.batch_unit_bytes(w.lens)) if in_units(args) else None,
            "avg_launch_ms": round(kern_avg_ms, 4),
            "roofline_frac": round(achieved / HBM_PEAK_GBS, 4)}
     detail = {"launches": launches, "algo_bytes": algo_bytes, "achieved": achieved,
@@ -378,13 +378,22 @@ def measure_workload(pgcm, torch, w, args, steps, warmup, headline):
     return res, detail, b, key
 
 
-def timed_kernel_name(w):
+def in_units(args):
+    """batches are cut into units of one size only where the schedule is forced"""
+    return bool(args.unit_bytes or args.matrix_hash)
+
+
+def timed_kernel_name(w, args):
+    """the kernel that touches the payload of these workloads: they either are short transfers or
+    fill the chip"""
     longest = int(w.lens.max())
+    if longest <= 8192 and w.n <= 512:
+        return "swap_kernel (a workgroup per chunk: the whole invocation)"
     if longest <= 1008:
         return "small_kernel (one wavefront per chunk: the whole invocation)"
-    if longest <= 8192 and w.n <= 512:
-        return "small_wide_kernel (one workgroup per chunk: the whole invocation)"
-    return "bulk_kernel (CTR keystream + XOR + GHASH)"
+    if in_units(args):
+        return "bulk_kernel (CTR keystream + XOR + GHASH of units)"
+    return "span_kernel (an equal span of rows per wavefront: the whole invocation)"
 
 
 def main():
@@ -527,7 +536,7 @@ def main():
         "enc_GBps": res["enc_GBps"],
         "dec_verify_GBps": res["dec_verify_GBps"],
         "pct_hbm_roofline": round(100.0 * 2.0 * res["value"] / HBM_PEAK_GBS, 2),
-        "roofline": {"bound": "hbm", "kernel": timed_kernel_name(w),
+        "roofline": {"bound": "hbm", "kernel": timed_kernel_name(w, args),
                      "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "algorithmic_bytes": det["algo_bytes"],
@@ -545,7 +554,7 @@ def main():
         out["copy_ceiling"] = {"kind": "device-to-device copy of the payload buffer (HBM read + "
                                        "write), median of %d" % det["reps"],
                                "traffic_GBps": round(copy_gbs, 1),
-                               "bulk_kernel_frac_of_copy": round(achieved / copy_gbs, 4)}
+                               "kernel_frac_of_copy": round(achieved / copy_gbs, 4)}
     import hashlib
     h = hashlib.sha256()
     for arr in (w.key, w.ivs, w.lens, w.aad if w.aad is not None else np.zeros(0, np.uint8)):
@@ -565,12 +574,12 @@ def main():
             steps = min(args.steps, 200 if cfg == 1 else 30)
             rc, _, bc, kc = measure_workload(pgcm, torch, wc, args, steps, min(args.warmup, 10),
                                              False)
-            rc["timed_kernel"] = timed_kernel_name(wc)
+            rc["timed_kernel"] = timed_kernel_name(wc, args)
             configs[str(cfg)] = rc
             kc.free()
             del bc
             torch.cuda.empty_cache()
-    res["timed_kernel"] = timed_kernel_name(w)
+    res["timed_kernel"] = timed_kernel_name(w, args)
     out["configs"] = {k: configs[k] for k in sorted(configs)}
 
     if not args.no_cpu_baseline:

@@ -97,9 +97,9 @@ void pgcm_free_key(pgcm_key_t *key);
  *   ivs      DEVICE, n * 12 bytes; chunk i uses ivs[12 i .. 12 i + 11].
  *   aad      HOST array of n DEVICE pointers (any alignment); entries with aad_len[i] == 0 are
  *            not read.  Must be NULL exactly when aad_len is NULL.
- *   aad_len  HOST array of n byte counts, or NULL for "no chunk has AAD".  A chunk's AAD is
- *            hashed block after block by one wavefront: meant for headers of tens of bytes
- *            (any length is correct; a megabyte of AAD takes milliseconds).
+ *   aad_len  HOST array of n byte counts, or NULL for "no chunk has AAD".  Meant for headers: up to
+ *            1 KiB of a chunk's AAD is hashed along with its payload, more than that block after
+ *            block by one wavefront, some 2 us each (any length is correct).
  *   src      HOST array of n DEVICE pointers, each 16-byte aligned (unused when len[i] == 0).
  *   len      HOST array of n byte counts, 0 <= len[i] <= PGCM_MAX_CHUNK_BYTES; need not be a
  *            multiple of 16.  Exactly len[i] bytes are read and written, never more.
@@ -222,12 +222,21 @@ const char *pgcm_strerror(int status);
 int pgcm_last_hip_error(void);
 
 /*
- * Host-only view of the chunk-to-wavefront schedule (section 5.1: requests arrive as batches of
- * copies of differing sizes).  Every chunk is cut into units of pgcm_batch_unit_bytes(n, len)
- * bytes counted back from its end, so only a chunk's first unit can be short; every wavefront
- * starts with a unit of its own and, when there are more units than wavefronts, takes further
- * ones from a shared counter.  Every unit leaves 64 partial hash sums; a chunk's sums are folded
- * 32 units at a time, level by level, until at most 32 remain for the chunk's final step.
+ * Which way a batch goes (section 5.1: requests arrive as batches of copies of differing sizes):
+ *   - at most 512 chunks of at most 8 KiB, and up to as many longer ones as there are compute units
+ *     if they do not fill the chip: one kernel launch, every chunk in workgroups of its own;
+ *   - more chunks of at most 1008 bytes each: one launch, a wavefront per chunk;
+ *   - everything else, of one key or of several: one launch, every wavefront of the chip an equal
+ *     span of the rows of 1 KiB of all chunks, which are cut wherever a span ends;
+ *   - pgcm_encrypt_batch_static beyond the first two, batches with a chunk of more than 1 GiB or
+ *     128 GiB in all, and whatever the test aids below force: chunks cut into units of one size.
+ *
+ * Host-only view of that last schedule.  Every chunk is cut into units of
+ * pgcm_batch_unit_bytes(n, len) bytes counted back from its end, so only a chunk's first unit can be
+ * short; every wavefront starts with a unit of its own and, when there are more units than
+ * wavefronts, takes further ones from a shared counter.  Every unit leaves 64 partial hash sums; a
+ * chunk's sums are folded 32 units at a time, level by level, until at most 32 remain for the
+ * chunk's final step.
  * Fills, for chunk i: nunits[i] (0 for an empty chunk), first_blocks[i] (16-byte blocks in its
  * first unit), unit_base[i] (index of its first unit among all units of the batch),
  * final_count[i] (partial sets left for the final step, 0..32) and final_power[i] (log2 of the
@@ -241,30 +250,29 @@ int64_t pgcm_plan_units(size_t n, const uint64_t *len, uint32_t *nunits, uint32_
 uint32_t pgcm_unit_bytes(void);
 
 /*
- * Bytes per unit for a batch with these chunk lengths (len: HOST array of n byte counts): the
+ * Bytes per unit, where a batch with these chunk lengths (len: HOST array of n byte counts) is cut
+ * into units and no size is forced: the
  * smallest power of two from 1 KiB to pgcm_unit_bytes() with which the batch has at most 4096
  * units (the wavefront slots of an MI355X, sixteen on each of 256 compute units: every unit then
  * has a wavefront of its own at once, so a batch of a few swap-sized chunks spreads over the
  * whole chip), and pgcm_unit_bytes() when none has (wavefronts then take further units in turn).
  * The batch calls count sixteen slots per compute unit of the key's device, so on a partition of
  * the chip they choose accordingly; this function and pgcm_plan_units describe the whole chip.
- * 0 when len is NULL and n is not 0.  Batches that take the small-transfer path (every chunk at
- * most 8 KiB) are not cut into units at all.
+ * 0 when len is NULL and n is not 0.
  */
 uint32_t pgcm_batch_unit_bytes(size_t n, const uint64_t *len);
 
 /*
- * Test aid, host only: the complete schedule the batch calls would upload for chunks of these
- * lengths (section 5.1: batches of copies of differing sizes), so that its invariants can be
- * checked without a GPU.
+ * Test aid, host only: the complete schedule of units that would be uploaded for chunks of these
+ * lengths if they are cut into units, so that its invariants can be checked without a GPU.
  *   unit_bytes   0 = chosen for the batch, else a forced unit size as for pgcm_set_unit_bytes.
  *   wave_slots   wavefront slots of the device (16 per compute unit); 0 = 4096, an MI355X.
  *   info         HOST, filled: offsets of the four arrays inside the image, the image's size, the
  *                device workspace the batch would need, the unit size as log2 of its 16-byte
  *                blocks, the numbers of units, partial-set slots (units + fold outputs), coarse
  *                map entries and fold items, per fold level the count of items and the index of
- *                the first, and the path the batch would take (0: the unit schedule, 1: the
- *                one-kernel path with a wavefront per chunk, 2: with a workgroup per chunk).
+ *                the first, and whether the batch is one of short transfers only (1: every chunk
+ *                at most 1008 bytes, 2: at most 8 KiB and at most 512 of them, 0: neither).
  *   image        HOST or NULL; when given it receives, at the offsets in info:
  *                descriptors, 64 bytes per chunk: src, dst, aad (pointers, here dummies), len
  *                  (u64), then u32 aad_len, unit_base, nunits, first_blocks, final_base,
@@ -317,8 +325,9 @@ size_t pgcm_key_tables_bytes(void);
 int pgcm_copy_key_tables(pgcm_key_t *key, void *out, size_t bytes);
 
 /*
- * Tuning and test aid: fixes the unit size of every later batch under this key to unit_bytes
- * (a power of two from 1 KiB to 16 MiB), or returns to the per-batch choice with 0.
+ * Tuning and test aid: has every later batch under this key cut into units of unit_bytes (a power
+ * of two from 1 KiB to 16 MiB; short transfers excepted), or returns to the library's choice of way
+ * and unit with 0.
  * Anything else is PGCM_ERR_ARG.  A chunk that a forced unit cannot serve (more than 32^5 units
  * of it; or more than 32 GiB with units of 32 KiB or 1 MiB, where the last fold would need a
  * power of H the key object has no table for) is refused with PGCM_ERR_LEN by the batch calls.
@@ -326,30 +335,29 @@ int pgcm_copy_key_tables(pgcm_key_t *key, void *out, size_t bytes);
 int pgcm_set_unit_bytes(pgcm_key_t *key, uint32_t unit_bytes);
 
 /*
- * Tuning and test aid.  A batch of at most 24 chunks with 96-bit IVs that does not fill the chip
- * (every unit gets a wavefront of its own: up to a few megabytes on an MI355X) is done by one
- * kernel launch, the whole invocation from the first block to the tag, its descriptors passed as
- * kernel arguments (section 5.1: swaps come a few chunks at a time, and what counts for them is
- * the time of the call).  enable = 0 sends such batches through the same sequence of kernels as
- * larger ones instead (descriptor upload, unit kernel, fold, final step); results are identical.
+ * Tuning and test aid.  Batches are done by one kernel launch, the whole invocation from the first
+ * block to the tag; few chunks travel as kernel arguments (section 5.1: swaps come a few chunks at
+ * a time, and what counts for them is the time of the call).  enable = 0 sends all but short
+ * transfers through the schedule of units instead (descriptor upload, unit kernel, fold, final
+ * step); results are identical.
  */
 int pgcm_set_one_launch(pgcm_key_t *key, int enable);
 
 /*
- * Tuning and test aid.  The kernel that does batches which fill the chip multiplies every
- * lane's running GHASH sum by H^64 once per 1 KiB row: thirty-two lookups in a table in LDS.
- * enable = 1 makes it a product with a fixed 128 x 128 matrix over GF(2) on the matrix cores
- * instead (SP 800-38D 6.3: multiplication by a constant is linear), which takes a fifth of the
- * LDS lookups' time off the LDS pipe and puts more work on the vector ALUs; measured 8 % slower
- * on an MI355X, hence off by default.  Results are identical.
+ * Tuning and test aid.  Every lane's running GHASH sum is multiplied by H^64 once per 1 KiB row:
+ * thirty-two lookups in a table in LDS.  enable = 1 has batches cut into units and makes it a
+ * product with a fixed 128 x 128 matrix over GF(2) on the matrix cores instead (SP 800-38D 6.3:
+ * multiplication by a constant is linear), which takes a fifth of the LDS lookups' time off the LDS
+ * pipe and puts more work on the vector ALUs; measured 4 % slower than the table in the same
+ * kernel on an MI355X (1.47 and 1.42 ms for 1.34 GB), hence off by default.  Results are identical.
  */
 int pgcm_set_matrix_hash(pgcm_key_t *key, int enable);
 
 /*
  * Measurement aid.  With timing enabled, every batch call also records a pair of HIP events on
- * its stream around the bulk kernel (the one launch that touches the payload: keystream, XOR
- * and GHASH of every unit; for the small-transfer path, its one kernel).  The library keeps the
- * pairs of the 256 most recent timed launches, so a run of batches can be enqueued back to back
+ * its stream around the one launch that touches the payload (in most batches the only one; a launch
+ * for several keys counts for each of them).  The library keeps the pairs of the 256 most recent
+ * timed launches, so a run of batches can be enqueued back to back
  * and read afterwards.  Switching timing on (again) forgets earlier launches.
  * pgcm_last_bulk_kernel_ms waits for the most recent timed launch and returns its duration in
  * milliseconds; PGCM_ERR_ARG when nothing was timed.

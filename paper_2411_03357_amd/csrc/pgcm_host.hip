@@ -1,5 +1,5 @@
-// Host side of libpgcm: the C ABI of include/pgcm.h — argument checks, the chunk-to-wavefront
-// schedule, descriptor upload and kernel launches.  No cipher arithmetic happens on the host.
+// Host side of libpgcm: the C ABI of include/pgcm.h — argument checks, which way a batch goes and how it
+// is cut, descriptors and kernel launches.  No cipher arithmetic happens on the host.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -165,7 +165,7 @@ struct pgcm_key {
     // device's static scratch array as workspace
     Context fixed;
     bool fixed_used = false;
-    // optional timing of the bulk kernel alone (pgcm_set_timing)
+    // optional timing of the kernel that touches the payload (pgcm_set_timing):
     // a ring of event pairs, one pair per timed launch, so that a run of batches can be timed
     // without a host wait in between
     bool timing = false;
@@ -1086,8 +1086,8 @@ int note_capture(BatchArgs& a) {
     return PGCM_OK;
 }
 
-// One batch under one key: validate everything, pick a context, then enqueue upload, J0 (if
-// needed), bulk, fold levels and final kernels on the stream.
+// One batch under one key: validate everything, choose the way it goes, pick a context unless it
+// needs none, then enqueue its kernels on the stream.
 int run_batch(pgcm_key* key, BatchArgs a) {
     if (key == nullptr || key->tables == nullptr) return PGCM_ERR_ARG;
     int rc = check_batch(a);

@@ -3,21 +3,26 @@
 // What is computed is the AES-GCM transform the paper's transport applies to every transfer
 // (paper sections 2.2 and 4.1), i.e. FIPS-197 AES-256 in the GCM mode of NIST SP 800-38D with a
 // 96-bit IV; the other two key lengths and other IV lengths are served by the same kernels
-// (round count as a template parameter, pre-counter blocks hashed beforehand).  How:
+// (round count as a template parameter).  How:
 //   * AES rounds read four 1 KiB round tables, each replicated 32 times in LDS so that lane l
 //     always reads bank l % 32: table lookups never collide, whatever the data.  AddRoundKey is
 //     folded into forming the next round's lookup addresses (one SDWA XOR per state byte).
-//   * GHASH multiplies by fixed powers of H with 4-bit tables (Shoup).  In the bulk kernel the
-//     row power H^64 sits in LDS and its thirty-two lookups are spread over the AES rounds;
-//     as an alternative the same multiplication runs on the matrix cores, as a product with a
-//     128 x 128 matrix over GF(2) (GhashRowMatrix).
-//   * One wavefront walks one unit (1 to 16 KiB of one chunk, the size chosen per batch) in rows
-//     of 64 blocks, one block per lane, 16-byte coalesced loads and stores, ciphertext hashed
-//     from registers.  Wavefront w starts with unit w; what is left is handed out by a
-//     device-side counter.  Each unit leaves 64 per-lane hash sums; fold kernels (a chain per
-//     wavefront, or a tree per workgroup when there are few) and the final kernel combine them
-//     per chunk (powers of H from tables; the 64 lanes are folded in groups of four).
-//   * A batch of short chunks only is done by one kernel, a wavefront per chunk.
+//   * GHASH multiplies by fixed powers of H with 4-bit tables (Shoup).  The row power H^64 sits in
+//     LDS and its thirty-two lookups are spread over the AES rounds; as an alternative, in the unit
+//     kernel, the same multiplication runs on the matrix cores, as a product with a 128 x 128
+//     matrix over GF(2) (GhashRowMatrix).  Sums over the 64 lanes are formed bit by bit from powers
+//     of H themselves (GfWords).
+//   * A wavefront walks rows of 64 blocks of one chunk, one block per lane, 16-byte coalesced loads
+//     and stores, ciphertext hashed from registers.
+// Which rows, and how their sums become tags, differs:
+//   * swap_kernel: a few chunks that do not fill the chip, in one launch, cut as finely as it takes
+//     for all of it to work at once.
+//   * span_kernel: everything else, of one key or of several, in one launch: every wavefront of the
+//     chip an equal share of all rows.
+//   * small_kernel: many chunks of one row each, a wavefront per chunk.
+//   * bulk_kernel, then fold kernels and final_kernel: chunks cut into units of one size, which the
+//     wavefronts take in turn, each leaving 64 per-lane sums.  For what the others do not take: the
+//     entry point with fixed buffers, chunks of more than 1 GiB, forced unit sizes, the matrix cores.
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
@@ -456,7 +461,7 @@ __global__ __launch_bounds__(64) void j0_kernel(const KeyTables* __restrict__ kt
 }
 
 // ------------------------------------------------------------------------------------------
-// The bulk kernel.  LDS map (byte addresses; the object below is the kernel's only LDS):
+// Rows.  LDS map of the kernels that walk units and spans (byte addresses):
 //   [0, 16 KiB)          operands of the row hash: the matrix images of H^64 and H^96, or the nibble
 //                        table of H^64 (entry offsets fit the 16-bit DS offset field)
 //   [16 KiB, 80 KiB)     row x (256 B): te[0][x] in dwords 0..31, te[1][x] in dwords 32..63
@@ -1911,9 +1916,9 @@ template __global__ void final_kernel<true>(const KeyTables*, const ChunkDesc*, 
 // wavefronts have one more, which makes E_K(J0) and prepares the finish meanwhile.
 // LDS after the round tables are done with, in tables of 8 KiB: 0..3 H^(2^(p + j)), the tree over the
 // workgroup's units (p = unit_power); 4..5 and 6 its sets.
-// Measured against the kernel this replaces (a tree over lanes and workgroups by tables, an extra
-// row for E_K(J0)), per call back to back: one 320 KiB chunk 19.8 -> 14.1 us, one of 2 MiB decrypted
-// 27.9 -> 15.7 us.
+// Measured against the kernel this replaced (a tree over lanes and workgroups by tables, an extra
+// row for E_K(J0)), per call back to back: one 320 KiB chunk 19.8 -> 11.3 us, one of 2 MiB decrypted
+// 27.9 -> 13.7 us.
 namespace {
 
 // XOR of the sixteen lanes of a row, left in all of them (DPP: pairs, quads, halves, row)
@@ -2391,11 +2396,12 @@ PGCM_INSTANTIATE_SWAP(true);
 #undef PGCM_INSTANTIATE_SWAP
 
 // ------------------------------------------------------------------------------------------
-// Batches of any number of chunks, and of any number of keys, in one launch after the upload of their
-// descriptors: every wavefront walks a span of rows, and the spans are equally long to a row.
-// A row takes every wavefront the same time, so a compute unit is busy to the end, where units of a
-// fixed size leave most of the chip idle in their last round, and keys one after the other all of it
-// between them.  A piece (the part of a chunk in a span) is summed over its lanes at once, as in
+// Batches of any number of chunks, and of any number of keys, in one launch: every wavefront walks a
+// span of rows, and the spans are equally long but for what their pieces cost (pgcm_spans.h).  The
+// workgroups read their descriptors from host memory themselves if those are few (kSpanHostBytes);
+// otherwise they are uploaded before.  A row takes every wavefront the same time, so a compute unit is
+// busy to the end, where units of a fixed size leave most of the chip idle in their last round, and
+// keys one after the other all of it between them.  A piece (the part of a chunk in a span) is summed over its lanes at once, as in
 // the one-launch kernel but by one wavefront: the 64 products with H^64 .. H^1 bit by bit from
 // KeyTables::dot, then one or two more with the power that takes the sum to the chunk's end.  The
 // results of a chunk's pieces then only have to be added; the wavefront that finishes the last
@@ -2657,13 +2663,11 @@ PGCM_INSTANTIATE_SPAN(true);
 #undef PGCM_INSTANTIATE_SPAN
 
 // ------------------------------------------------------------------------------------------
-// The small-transfer path: a batch whose chunks are all at most kSmallChunkBytes long (the
-// paper's "other I/O", usually < 8 KB, and the 1-byte NOPs of its error handler, sections 4.2 and
-// 5.3) is done by ONE kernel from the first block to the tag, reading its descriptors straight
-// from pinned host memory: what matters here is the latency of the call, not bandwidth.  Two
-// shapes: a wavefront per chunk when every chunk fits one row, a workgroup of eight wavefronts
-// per chunk otherwise.  LDS: the four round tables once (lookups may collide; there are few)
-// and the nibble tables the chunks at hand need.
+// Many chunks of one row (of the paper's "other I/O", usually < 8 KB, and the 1-byte NOPs of its
+// error handler, sections 4.2 and 5.3; up to kSmallMaxChunks of them go to swap_kernel): ONE kernel
+// from the first block to the tag, a wavefront per chunk, descriptors read straight from pinned
+// host memory.  LDS: the four round tables once (lookups may collide; there are few) and the nibble
+// tables the chunks at hand need.
 namespace {
 
 template <int kRounds>

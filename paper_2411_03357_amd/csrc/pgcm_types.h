@@ -6,13 +6,13 @@
 namespace pgcm {
 
 // A wavefront handles 64 consecutive 16-byte blocks (one 1 KiB "row") per step, one block per
-// lane.  A unit is the piece of a chunk one wavefront walks in one go, and the granule of the
-// dynamic schedule; units are counted back from the chunk's end, so only a chunk's first unit
-// can be short.  A unit is 2^unit_power blocks.  Batches that do not fill the chip get the
-// smallest size, from one row up, that still gives every unit a wavefront of its own, so that the
-// batch spreads over as many wavefronts as there are and no unit waits.  Batches that do fill it
-// get sixteen rows, handed out dynamically.  Larger units (up to 2^kMaxUnitPower blocks) can be
-// forced for measurements.
+// lane.  Where chunks are cut into units of one size (swap_kernel, and the schedule of bulk_kernel), a
+// unit is the piece of a chunk one wavefront walks in one go; units are counted back from the
+// chunk's end, so only a chunk's first unit can be short.  A unit is 2^unit_power blocks.  In the
+// schedule of bulk_kernel, batches that do not fill the chip get the smallest size, from one row
+// up, that still gives every unit a wavefront of its own, so that the batch spreads over as many
+// wavefronts as there are and no unit waits; batches that do fill it get sixteen rows, handed out
+// dynamically.  Larger units (up to 2^kMaxUnitPower blocks) can be forced for measurements.
 constexpr uint32_t kRowBlocks = 64;
 constexpr uint32_t kRowPower = 6;      // H^64: one row further along a lane's stripe
 constexpr uint32_t kUnitPower = 10;    // the unit of the dynamic schedule: 1024 blocks = 16 KiB
@@ -231,15 +231,15 @@ static_assert(sizeof(SpanPart) == 64, "descriptor layout");
 // The parts of a workgroup that are held in LDS; those of longer lists are read from memory.
 constexpr uint32_t kSpanLdsParts = 31;
 
-// A batch whose chunks are all at most this long takes// A batch whose chunks are all at most this long takes the small-transfer path: one kernel (the
-// paper's non-swap transfers are usually < 8 KB, section 4.2): eight rows of 64 blocks.
+// A batch whose chunks are all at most this long (the paper's non-swap transfers are usually < 8 KB,
+// section 4.2; eight rows of 64 blocks) goes to the one-launch kernel with small tables.
 constexpr uint64_t kSmallChunkBytes = 8192;
-// The one-launch kernel is there for the latency of a few transfers, a workgroup each; of more
-// chunks than this (two workgroups per compute unit are resident) ...
+// That kernel is there for the latency of a few transfers, a workgroup each; of more chunks than this
+// (two workgroups per compute unit are resident) ...
 constexpr size_t kSmallMaxChunks = 512;
 // ... those of at most this length (63 blocks: one row together with "block -1") take a kernel with
-// a wavefront per chunk, and longer ones the unit schedule, which gets more chunks per second
-// out of the chip.
+// a wavefront per chunk, and longer ones go in spans, which get more chunks per second out of the
+// chip.
 constexpr uint64_t kSmallRowBytes = 1008;
 
 // Items of the dynamic schedule are grabbed from a counter; to find an item's chunk a wavefront
