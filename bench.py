@@ -465,7 +465,7 @@ def main():
     launches, achieved, kern_avg_ms = det["launches"], det["achieved"], det["kern_avg_ms"]
     kern = {"enc": launches[0::2], "dec": launches[1::2]}      # a pass is encrypt, then decrypt
 
-    # what a plain device copy of the same buffer reaches on this machine, in the same run: the
+    # what a plain device copy of the same buffer reaches in the same run: the
     # achievable ceiling for a kernel that reads and writes every payload byte once
     copy_gbs = None
     if not args.host_bounce:
@@ -490,7 +490,7 @@ def main():
                               COUNTERS["write_size_kib"] * COUNTERS["write_scale"]))
         # The clock the chip ran at under this kernel, measured in the counter run:
         # GRBM_GUI_ACTIVE (cycles of the graphics clock while the launch was in flight) over the
-        # launch's duration in that run.  Boxes of the pool differ in the clock they sustain, so
+        # launch's duration in that run.  Machines differ in the clock they sustain, so
         # the fractions "at the measured clock" are taken inside the counter run alone (busy
         # cycles over elapsed cycles of the same launch), not against this run's kernel time.
         cycles = COUNTERS["gui_active_cycles"]
