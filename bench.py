@@ -31,17 +31,17 @@ LDS_PEAK_GCYCLES = 256 * 2.4               # 256 CUs, one LDS pipe each, 2.4 GHz
 # (pgcm_kernels.hip and the two headers it includes) whose hash is given; once those change the
 # counters no longer apply and bench.py reports null.
 COUNTERS = {
-    "sources_sha256": "a43c6e55e03421166e8ddfa990b3dfef6524afdbada7bcb68807dcd5599d802b",
+    "sources_sha256": "d246e8456c378e50f5108fb4beb9d0d29a693e0fb315c8c697f11e4069fb0f21",
     "workload": "c2_opt13b_kv_4096x320KiB",
-    "fetch_size_kib": 656001.4,     # FETCH_SIZE per launch
+    "fetch_size_kib": 655997.3,     # FETCH_SIZE per launch
     "fetch_scale": 1310720.0 / 655388.0,   # a 1 310 720 KiB device copy reads 655 388
-    "write_size_kib": 1310795.4,    # WRITE_SIZE per launch
+    "write_size_kib": 1310795.5,    # WRITE_SIZE per launch
     "write_scale": 1310720.0 / 1310720.0,  # the same copy writes 1 310 720.0
-    "valu_wave_instructions": 575656960.0,  # SQ_INSTS_VALU per launch
+    "valu_wave_instructions": 575734784.0,  # SQ_INSTS_VALU per launch
     "lds_wave_instructions": 305161728.0,   # SQ_INSTS_LDS per launch
     "lds_active_cycles": 698790912.0,   # SQ_LDS_IDX_ACTIVE per launch, summed over the 256 CUs
-    "gui_active_cycles": 24283126.3 / 8,  # GRBM_GUI_ACTIVE per launch (summed over the 8 XCDs) ...
-    "pmc_launch_ms": 1.4645,              # ... and the launch's duration in that same run
+    "gui_active_cycles": 24046221.1 / 8,  # GRBM_GUI_ACTIVE per launch (summed over the 8 XCDs) ...
+    "pmc_launch_ms": 1.4593,              # ... and the launch's duration in that same run
 }
 
 

@@ -1061,8 +1061,10 @@ int run_span_batch(Context* ctx, const BatchArgs& a, KeyPart* keys, size_t nkeys
     int rc_timing = PGCM_OK;
     for (size_t q = 0; q < nkeys && rc_timing == PGCM_OK; ++q)
         if (!timed_already(q)) rc_timing = record_timing_start(keys[q].key, a.stream);
-    launch_last(a.decrypt ? span_kernel<true> : span_kernel<false>, dim3(ngroups),
-                dim3(kGroupThreads), a.stream, a.capturing, ctx->stage_done[s],
+    const bool long_iv = a.iv_len > kShortIvBytes;
+    auto* const kernel = a.decrypt ? (long_iv ? span_kernel<true, true> : span_kernel<true, false>)
+                                   : (long_iv ? span_kernel<false, true> : span_kernel<false, false>);
+    launch_last(kernel, dim3(ngroups), dim3(kGroupThreads), a.stream, a.capturing, ctx->stage_done[s],
                 (const KeyTables*)(nkeys == 1 ? keys[0].key->tables : nullptr), packets, parts,
                 (uint32_t)stride, a.iv_len, a.ivs, reinterpret_cast<ArriveSlot*>(ctx->work), a.tags,
                 a.ok);

@@ -36,8 +36,8 @@ __global__ void swap_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t iv
 // Spans of rows, one per wavefront, of chunks of one key (`key`) or of several (null; every
 // workgroup has its own).  packets: stride 0: the workgroups' SpanGroup, and their parts in `parts`;
 // otherwise a workgroup's SpanGroup and its parts, at most kSpanLdsParts, every `stride` bytes,
-// and these may lie in host memory.  slots: one per part.
-template <bool kDecrypt>
+// and these may lie in host memory.  slots: one per part.  kLongIv: iv_len exceeds kShortIvBytes.
+template <bool kDecrypt, bool kLongIv>
 __global__ void span_kernel(const KeyTables* key, const uint8_t* packets, const SpanPart* parts,
                             uint32_t stride, uint32_t iv_len, const uint8_t* ivs, ArriveSlot* slots,
                             uint8_t* tags, uint8_t* ok);

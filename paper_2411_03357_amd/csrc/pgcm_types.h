@@ -228,6 +228,8 @@ struct alignas(16) SpanPart {       // a chunk as far as one workgroup has rows 
     uint32_t waves;                 // this one's wavefronts with rows of it, << 8; the first of them
 };
 static_assert(sizeof(SpanPart) == 64, "descriptor layout");
+// IVs of at most one block are hashed in one round of lookups.
+constexpr uint32_t kShortIvBytes = 16;
 // The parts of a workgroup that are held in LDS; those of longer lists are read from memory.
 constexpr uint32_t kSpanLdsParts = 31;
 

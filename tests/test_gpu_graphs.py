@@ -7,7 +7,7 @@ import torch
 
 import workloads
 from device_batch import DeviceBatch
-from test_gpu_reservations import KIB, MIB, expected, workload
+from test_gpu_reservations import KIB, MIB, _encrypt_keys, _keys_batch, expected, workload
 
 import paper_2411_03357_amd as pgcm
 
@@ -91,6 +91,37 @@ def test_captured_between_eager_batches(shape):
             eager(r + k).check("after replay %d, %d" % (r, k))
     torch.cuda.synchronize()
     key.free()
+
+
+def test_several_keys_captured():
+    """two keys' chunks in one launch, with buffers of the first; eager batches of that key between the
+    replays"""
+    rng = np.random.default_rng([workloads.BASE_SEED, 5042])
+    b, keys, index, cipher, tags = _keys_batch(rng, [int(v) for v in rng.integers(1, 900 * KIB, 40)],
+                                               (32, 24))
+    other = _Checked("eager_first_key", rng, [MIB + 3] * 9, b.w.key)
+    stream = torch.cuda.Stream()
+    for q, key in enumerate(keys):
+        mine = np.flatnonzero(index == q)
+        pgcm.reserve(key, max(mine.size, 9), max(int(b.lens[mine].sum()), 10 * MIB), stream)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        _encrypt_keys(b, keys, index)
+    for r in range(3):
+        other.clear()
+        b.cipher.zero_()
+        b.tags.zero_()
+        torch.cuda.synchronize()
+        other.b.encrypt(keys[0], stream=stream)
+        other.b.decrypt(keys[0], stream=stream)
+        with torch.cuda.stream(stream):
+            graph.replay()
+        other.check("eager %d" % r)
+        assert np.array_equal(b.cipher.cpu().numpy(), cipher), r
+        assert np.array_equal(b.tags.cpu().numpy().reshape(-1, 16), tags), r
+    for key in keys:
+        key.free()
 
 
 def test_static_calls_captured_until_the_staging_is_used_up():

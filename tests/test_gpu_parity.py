@@ -102,9 +102,8 @@ def test_ragged_edge_cases_full_parity():
 @pytest.mark.parametrize("unit_bytes", [1024, 2048, 4096, 8192, 16384, 32768, 128 * 1024,
                                         16 << 20])
 def test_every_unit_size_full_parity(unit_bytes):
-    """small batches get small units by themselves; here every unit size is forced on the
-    edge-case batch and on a ragged mixed-size batch, so that unit boundaries, short first units
-    and fold levels of each size are compared byte for byte"""
+    """every unit size is forced on the edge-case batch and on a ragged mixed-size batch, so that unit
+    boundaries, short first units and fold levels of each size are compared byte for byte"""
     w = workloads.ragged_small()
     last = int(w.lens[13]) - 1
     _full_parity(w, flip=[(13, last, 7, "ct"), (25, 0, 0, "ct"), (2, 15, 3, "tag")],

@@ -1,6 +1,6 @@
-"""The chunk-to-wavefront schedule the batch calls upload (descriptors, unit map, coarse map,
-fold lists), built on the host by pgcm_describe_schedule and checked here without a GPU against
-what the kernels assume when they read it:
+"""The schedule of units that is uploaded for batches that are cut into them (descriptors, unit map,
+coarse map, fold lists), built on the host by pgcm_describe_schedule and checked here without a GPU
+against what the kernels assume when they read it (test_span_cuts.py does that for spans):
 
   * units: every unit belongs to exactly one chunk; a chunk's units are consecutive, cover its
     blocks exactly, and only its first unit may be short;
