@@ -618,8 +618,10 @@ __device__ __forceinline__ Block load_block_device_scope(const Block* p) {
 // for output that a wavefront on another XCD may overwrite later in the same kernel (the wipe of
 // a rejected chunk), where two L2s holding different dirty versions of a line would leave it to
 // chance which one memory keeps.
+// (A store of more than 64 bits still reads its registers when the next instruction issues: the next
+// two must not write them, and only in code of its own does the compiler see to that.)
 __device__ __forceinline__ void global_write128_through(uint8_t* p, u32x4 v) {
-    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" : : "v"(p), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
 }
 __device__ __forceinline__ void global_write8_through(uint8_t* p, uint8_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
