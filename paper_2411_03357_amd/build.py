@@ -23,6 +23,8 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # the leading kernel arguments come in registers instead of being loaded from host memory
     "-mllvm", "-amdgpu-kernarg-preload-count=14",
+    # one lane's atomic stays one instruction, whose result is waited for where it is used
+    "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
 ]
 
 

@@ -466,7 +466,7 @@ __global__ __launch_bounds__(64) void j0_kernel(const KeyTables* __restrict__ kt
 //                        table of H^64 (entry offsets fit the 16-bit DS offset field)
 //   [16 KiB, 80 KiB)     row x (256 B): te[0][x] in dwords 0..31, te[1][x] in dwords 32..63
 //   [80 KiB, 144 KiB)    the same for te[2], te[3]
-//   [144 KiB, 146 KiB)   every wavefront's second-round constants (see ctr_consts)
+//   [144 KiB, 152 KiB)   every wavefront's second-round constants (see ctr_consts)
 // A round-table lookup address is  pair << 16 | x << 8 | 4 * (lane % 32)  plus a constant DS
 // offset, so lane l always reads bank l % 32: lookups never collide, whatever the data.
 namespace {
@@ -475,7 +475,7 @@ constexpr uint32_t kLdsGhBytes = kNibbleTableEntries * 16;
 constexpr uint32_t kLdsTeBase = kHashImages * kLdsGhBytes;
 constexpr uint32_t kLdsTeBytes = 4 * 256 * 32 * 4;
 // counter values that differ above their lowest byte and occur in one segment of a unit
-constexpr uint32_t kCtrEntries = 8;
+constexpr uint32_t kCtrEntries = 32;
 constexpr uint32_t kLdsCtrBase = kLdsTeBase + kLdsTeBytes;
 constexpr uint32_t kLdsBytes = kLdsCtrBase + kWavesPerGroup * kCtrEntries * 16;
 
@@ -623,6 +623,10 @@ __device__ __forceinline__ Block load_block_device_scope(const Block* p) {
 __device__ __forceinline__ void global_write128_through(uint8_t* p, u32x4 v) {
     asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
 }
+__device__ __forceinline__ void global_write128_through(uint8_t* base, uint32_t offset, u32x4 v) {
+    asm volatile("global_store_dwordx4 %0, %1, %2 sc0 sc1\n\ts_nop 1"
+                 : : "v"(offset), "v"(v), "s"(base) : "memory");
+}
 __device__ __forceinline__ void global_write8_through(uint8_t* p, uint8_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
@@ -737,11 +741,12 @@ __device__ __forceinline__ void aes_addr_init(AesAddr& A, uint32_t lane,
 // column; the other three depend on the IV and the counter's upper bytes: their sums, four words,
 // are kept in LDS for every upper value the segment meets (lane i of the wavefront forms the one
 // i above the first).  So a block takes one lookup in round 1 and four in round 2 instead of
-// sixteen each, for 27 lookups per segment and one 16-byte read per row.  The kernel is bound by
+// sixteen each, for 27 lookups per segment and one 16-byte read per row; in most rows of longer pieces
+// it takes none, see CtrClass.  The kernel is bound by
 // LDS accesses and by the board's power together, and both go down: per row of 64 blocks 555 -> 532
 // LDS cycles and 448 -> 432 vector instructions, 1.424 -> 1.389 ms for 4096 chunks of 320 KiB
 // (AES-256, alternating on one box), against keeping only round 1's constant sums.
-constexpr uint32_t kSegmentRows = 27;
+constexpr uint32_t kSegmentRows = 123;
 static_assert(255 + (kSegmentRows + 1) * kRowBlocks <= 256 * kCtrEntries,
               "upper counter values of a segment of kSegmentRows rows, or one more");
 struct CtrConsts {
@@ -751,6 +756,24 @@ struct CtrConsts {
     // segment's first counter, so that its lowest byte is the counter's and rel >> 8 the number
     // of the upper counter value
     uint32_t rel;
+};
+
+// Rows four apart have the same lowest counter byte in a lane, and what round 2 makes of it, one lookup
+// of every column, is then the same as well: it is kept in registers, for four classes of rows, and
+// their rounds 1 and 2 take no lookup at all but that of q, fetched a row ahead.  Sixteen registers
+// and four copies of a row's code, for 10 of 532 LDS cycles and, with the checks that rows within a
+// piece do without, some 30 of 438 vector instructions: 4096 chunks of 320 KiB both ways 2658 -> 2592
+// us, 2000 of 16 KiB to 8 MiB 2889 -> 2813 (alternating).  What binds is the board's power: without
+// those 10 cycles alone it was 2.3 %, and taking the checks out as well gave next to nothing.
+constexpr uint32_t kRowClasses = 4;
+static_assert(kRowClasses * kRowBlocks == 256, "the lowest counter byte's period in rows");
+struct CtrClass {
+    uint32_t s[4];
+};
+struct CtrInner {
+    const CtrClass& low;
+    u32x4& q;
+    uint32_t next;  // LDS address of the next row's q
 };
 
 // The counter block of a row that stands alone (a unit of one row): no constants are formed, and
@@ -804,6 +827,10 @@ __device__ __forceinline__ CtrConsts ctr_consts(const uint32_t* __restrict__ rk,
     asm volatile("" ::: "memory");
     c.rel = (first_ctr & 0xFFu) + lane;
     return c;
+}
+
+__device__ __forceinline__ uint32_t ctr_q_addr(const CtrConsts& C, uint32_t rel) {
+    return C.q_addr + ((rel >> 8) << 4);
 }
 
 template <int B, int E, class F>
@@ -1121,7 +1148,7 @@ __device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, Aes
                                             uint32_t& o0, uint32_t& o1, uint32_t& o2,
                                             uint32_t& o3) {
     using Te = TeWide;
-    const u32x4 q = lds_read128(C.q_addr + ((C.rel >> 4) & (16 * (kCtrEntries - 1))));
+    const u32x4 q = lds_read128(ctr_q_addr(C, C.rel));
     // round 1: the counter is the last word, big endian: its lowest byte is state byte 3
     key_xor_into_addr<3, 0>(A.a[3][3], rk[3], C.rel);
     uint32_t u0 = te_read<Te, 3>(A.a[3][3], base) ^ C.k0;
@@ -1143,6 +1170,42 @@ __device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, Aes
     }
     __builtin_amdgcn_sched_barrier(0);
     aes_rounds_lds<Te, 3, kRounds>(rk, A, u0, u1, u2, u3, G, base, o0, o1, o2, o3);
+}
+
+// round 2's lookups of the lowest counter byte of the row `row` behind the one at hand
+__device__ __forceinline__ CtrClass ctr_class(const uint32_t* __restrict__ rk, AesAddr& A,
+                                              const CtrConsts& C, uint32_t row, uint32_t base) {
+    using Te = TeWide;
+    CtrClass c;
+    key_xor_into_addr<3, 0>(A.a[3][3], rk[3], C.rel + row * kRowBlocks);
+    const uint32_t u0 = te_read<Te, 3>(A.a[3][3], base) ^ C.k0;
+    key_xor_into_addr<0, 0>(A.a[0][0], rk[4], u0);
+    key_xor_into_addr<1, 1>(A.a[0][1], rk[4], u0);
+    key_xor_into_addr<2, 2>(A.a[0][2], rk[4], u0);
+    key_xor_into_addr<3, 3>(A.a[0][3], rk[4], u0);
+    c.s[0] = te_read<Te, 0>(A.a[0][0], base);
+    c.s[3] = te_read<Te, 1>(A.a[0][1], base);
+    c.s[2] = te_read<Te, 2>(A.a[0][2], base);
+    c.s[1] = te_read<Te, 3>(A.a[0][3], base);
+    return c;
+}
+// The same in a row of which every lane has a whole block, with its class's lookups made.
+template <int kRounds, class Hash>
+__device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, AesAddr& A,
+                                            const CtrInner& C, Hash& G, uint32_t base,
+                                            uint32_t& o0, uint32_t& o1, uint32_t& o2,
+                                            uint32_t& o3) {
+    const uint32_t u0 = C.low.s[0] ^ C.q.x, u1 = C.low.s[1] ^ C.q.y, u2 = C.low.s[2] ^ C.q.z,
+                   u3 = C.low.s[3] ^ C.q.w;
+    C.q = lds_read128(C.next);
+    if constexpr (Hash::kTable) {
+        G.template step<0>();
+        G.template step<1>();
+        G.template step<2>();
+        G.template step<3>();
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    aes_rounds_lds<TeWide, 3, kRounds>(rk, A, u0, u1, u2, u3, G, base, o0, o1, o2, o3);
 }
 
 // ... and in a row that stands alone, where latency counts.  The keys wait in the lanes of a
@@ -1334,6 +1397,25 @@ __device__ __forceinline__ void bulk_row(const Keys& rk, AesAddr& A,
     G.absorb(c0, c1, c2, c3);
 }
 
+// The same for a row that is no edge row, with the payload's places as scalar bases and the lane's
+// offset.
+template <bool kDecrypt, int kRounds, bool kThrough, class Hash>
+__device__ __forceinline__ void inner_row(const uint32_t* __restrict__ rk, AesAddr& A,
+                                          const CtrInner& C, const uint8_t* src, uint8_t* dst,
+                                          uint32_t lane16, uint32_t lds_base, Hash& G) {
+    const u32x4 x = global_read128(src + lane16);
+    G.begin();
+    uint32_t s0, s1, s2, s3;
+    aes_ctr_lds<kRounds>(rk, A, C, G, lds_base, s0, s1, s2, s3);
+    const u32x4 o = {x.x ^ s0, x.y ^ s1, x.z ^ s2, x.w ^ s3};
+    if constexpr (kThrough)
+        global_write128_through(dst, lane16, o);
+    else
+        global_write128(dst + lane16, o);
+    const u32x4 c = kDecrypt ? x : o;
+    G.absorb(c.x, c.y, c.z, c.w);
+}
+
 }  // namespace
 
 namespace {
@@ -1410,7 +1492,9 @@ struct NoPace {
 // XOR, and the lane's GHASH sum over the rows, sum over rows r of C(r, lane) * (H^64)^(rows after
 // r), left in y.  Negative block numbers are those of the AAD and "block -1" (see bulk_row).
 // last: b1 is the chunk's end.
-template <bool kDecrypt, int kRounds, bool kThrough, bool kMatrixHash, class Pace, class StoreMask>
+// kClasses: pieces may be long enough for CtrClass to pay.
+template <bool kDecrypt, int kRounds, bool kThrough, bool kMatrixHash, bool kClasses, class Pace,
+          class StoreMask>
 __device__ __forceinline__ void walk_unit(const uint32_t* __restrict__ rk, AesAddr& A,
                                           uint32_t lane, uint32_t wave, uint32_t lds_base,
                                           const uint8_t* src, uint8_t* dst, uint64_t len,
@@ -1430,7 +1514,32 @@ __device__ __forceinline__ void walk_unit(const uint32_t* __restrict__ rk, AesAd
         CtrConsts C = ctr_consts(rk, lane, wave, j.w[0], j.w[1], j.w[2], first_ctr, lds_base);
         const uint32_t left = nrows - r;
         const uint32_t end = left <= kSegmentRows + 1 ? nrows : r + kSegmentRows;
+        const uint32_t inner_end = last && end == nrows ? end - 1 : end;
         for (; r < end; ++r, row_blk += kRowBlocks, C.rel += kRowBlocks) {
+            // (one group of four rows repays the classes' lookups: 300 adapters both ways 178.3 us
+            // without; 175.2, 176.0, 180.2 with from four, eight and sixteen rows on)
+            if (kClasses && row_blk >= 0 && r + kRowClasses <= inner_end) {
+                CtrClass low[kRowClasses];
+#pragma unroll
+                for (uint32_t i = 0; i < kRowClasses; ++i) low[i] = ctr_class(rk, A, C, i, lds_base);
+                u32x4 q = lds_read128(ctr_q_addr(C, C.rel));
+                const uint8_t* s = src + row_blk * 16;
+                uint8_t* d = dst + row_blk * 16;
+#pragma unroll 1
+                do {
+                    static_for<0, kRowClasses>([&](auto i) __attribute__((always_inline)) {
+                        constexpr uint32_t I = decltype(i)::value;
+                        pace.start_row(lane);
+                        C.rel += kRowBlocks;
+                        const CtrInner c{low[I], q, ctr_q_addr(C, C.rel)};
+                        inner_row<kDecrypt, kRounds, kThrough>(rk, A, c, s + 1024 * I, d + 1024 * I,
+                                                               lane * 16, lds_base, G);
+                    });
+                    s += 1024 * kRowClasses, d += 1024 * kRowClasses;
+                    r += kRowClasses, row_blk += kRowClasses * kRowBlocks;
+                } while (r + kRowClasses <= inner_end);
+                if (r == end) break;
+            }
             const bool edge = row_blk < 0 || (last && r + 1 == nrows);
             pace.start_row(lane);
             const RowPayload p = load_row(src, len, row_blk + lane, edge, aad);
@@ -1523,7 +1632,7 @@ __global__ __launch_bounds__(kGroupThreads) void bulk_kernel(
         Block* mask_out = ekj0 + chunk;
         uint32_t y[4];
         NoPace pace;
-        walk_unit<kDecrypt, kRounds, false, kMatrixHash>(
+        walk_unit<kDecrypt, kRounds, false, kMatrixHash, false>(
             rk, A, lane, tid >> 6, lds_base, src, dst, len, b0, b1, unit + 1 == nunits, aad, j, pace,
             [&](uint32_t s0, uint32_t s1, uint32_t s2, uint32_t s3) __attribute__((always_inline)) {
                 *mask_out = Block{{s0, s1, s2, s3}};
@@ -2317,9 +2426,9 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
                 AesAddr A;
                 aes_addr_init<Te>(A, lane, rk + 4 * kRounds);
                 NoPace pace;
-                walk_unit<kDecrypt, kRounds, kDecrypt, false>(rk, A, lane, wave, lds_base, cd.src,
-                                                              cd.dst, cd.len, b0, b1, b1 == nblk,
-                                                              aad, j, pace, keep_mask, y);
+                walk_unit<kDecrypt, kRounds, kDecrypt, false, false>(
+                    rk, A, lane, wave, lds_base, cd.src, cd.dst, cd.len, b0, b1, b1 == nblk, aad, j,
+                    pace, keep_mask, y);
             }
             fetch_ahead();
         }
@@ -2507,7 +2616,7 @@ __device__ __forceinline__ void walk_span(const KeyTables* __restrict__ kt, uint
 #pragma unroll
         for (int k = 0; k < 4; ++k) j.w[k] = __builtin_amdgcn_readfirstlane(j.w[k]);
         uint32_t y[4];
-        walk_unit<kDecrypt, kRounds, kDecrypt, false>(
+        walk_unit<kDecrypt, kRounds, kDecrypt, false, true>(
             rk, A, lane, wave, lds_base, reinterpret_cast<const uint8_t*>(PGCM_PAIR(src)),
             reinterpret_cast<uint8_t*>(PGCM_PAIR(dst)), len, b0, b1, behind == 0, aad, j, pace,
             [&](uint32_t s0, uint32_t s1, uint32_t s2, uint32_t s3) __attribute__((always_inline)) {

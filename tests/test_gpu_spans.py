@@ -6,6 +6,8 @@ import numpy as np
 import pytest
 import torch
 
+import iv_craft
+import openssl_ref
 import oracle
 import workloads
 from device_batch import DeviceBatch
@@ -120,4 +122,36 @@ def test_a_key_listed_twice_is_timed_once():
     b.encrypt(key)
     torch.cuda.synchronize()
     assert torch.equal(tags, b.tags)
+    key.free()
+
+
+@pytest.mark.parametrize("key_bytes", (16, 24, 32))
+def test_pieces_of_more_rows_than_a_segment(key_bytes):
+    """Shares of some 140 rows, more than the second-round constants of a piece are formed for at once,
+    with counters that wrap in the first chunk: against libcrypto, every byte."""
+    rng = np.random.default_rng([workloads.BASE_SEED, 2718, key_bytes])
+    raw = rng.integers(0, 256, key_bytes, dtype=np.uint8)
+    h = openssl_ref.aes_ecb_block(raw.tobytes(), bytes(16))
+    lens = np.array([300 * MIB + 7, 250 * MIB - 48, 9 * KIB], np.uint64)
+    n = len(lens)
+    wrap = (0xFFFFFFFF - 5_000_001).to_bytes(4, "big")
+    ivs = np.stack([np.frombuffer(iv_craft.iv_for_j0(h, rng.bytes(12) + wrap), np.uint8),
+                    *rng.integers(0, 256, (n - 1, 16), dtype=np.uint8)])
+    offsets, total = workloads._layout(lens)
+    aad_off = np.array([0, 20, 20, 60], np.uint64)
+    w = workloads.Workload("long_pieces", 901, raw, ivs, lens, offsets, total, "u8",
+                           rng.integers(0, 256, 60, dtype=np.uint8), aad_off)
+    host = rng.integers(0, 256, total, dtype=np.uint8)
+    key = pgcm.expand_key_bytes(raw)
+    b = DeviceBatch(w, torch.from_numpy(host).cuda())
+    b.encrypt(key)
+    b.decrypt(key)
+    torch.cuda.synchronize()
+    cipher, tags = b.cipher.cpu().numpy(), b.tags.cpu().numpy().reshape(n, 16)
+    for i in range(n):
+        ref = openssl_ref.GcmEncryptStream(raw.tobytes(), ivs[i].tobytes(), w.aad_of(i))
+        assert np.array_equal(ref.update(w.chunk(host, i)), w.chunk(cipher, i)), i
+        assert ref.tag() == tags[i].tobytes(), i
+    assert bool((b.ok == 1).all())
+    assert torch.equal(b.back, b.plain)
     key.free()
