@@ -402,6 +402,111 @@ __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict_
 }
 
 // ------------------------------------------------------------------------------------------
+// Global memory.
+namespace {
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(1))) const u32x4* global_u128_cptr;
+typedef __attribute__((address_space(1))) u32x4* global_u128_ptr;
+
+// payload accesses go through global (not flat) instructions, so that waiting for LDS results
+// never waits for them
+__device__ __forceinline__ u32x4 global_read128(const uint8_t* p) {
+    return *reinterpret_cast<global_u128_cptr>(reinterpret_cast<uintptr_t>(p));
+}
+__device__ __forceinline__ void global_write128(uint8_t* p, u32x4 v) {
+    *reinterpret_cast<global_u128_ptr>(reinterpret_cast<uintptr_t>(p)) = v;
+}
+// ... and so do the single bytes of a ragged last block: one flat access anywhere in the row loop
+// would make every wait in it a wait for everything
+typedef __attribute__((address_space(1))) const uint8_t* global_u8_cptr;
+__device__ __forceinline__ uint8_t global_read8(const uint8_t* p) {
+    return *reinterpret_cast<global_u8_cptr>(reinterpret_cast<uintptr_t>(p));
+}
+
+// 16 bytes at any alignment
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+typedef __attribute__((address_space(1))) const u32x4_any* global_u128_any_cptr;
+typedef __attribute__((address_space(1))) u32x4_any* global_u128_any_ptr;
+__device__ __forceinline__ Block global_read_block_any(const uint8_t* p) {
+    const u32x4_any v = *reinterpret_cast<global_u128_any_cptr>(reinterpret_cast<uintptr_t>(p));
+    return Block{{v.x, v.y, v.z, v.w}};
+}
+__device__ __forceinline__ void global_write_block_any(uint8_t* p, const Block& b) {
+    const u32x4_any v = {b.w[0], b.w[1], b.w[2], b.w[3]};
+    *reinterpret_cast<global_u128_any_ptr>(reinterpret_cast<uintptr_t>(p)) = v;
+}
+
+// Payload stores that go through to memory at once instead of staying dirty in this XCD's L2:
+// for output that a wavefront on another XCD may overwrite later in the same kernel (the wipe of
+// a rejected chunk), where two L2s holding different dirty versions of a line would leave it to
+// chance which one memory keeps.
+// (A store of more than 64 bits still reads its registers when the next instruction issues: the next
+// two must not write them, and only in code of its own does the compiler see to that.)
+__device__ __forceinline__ void global_write128_through(uint8_t* p, u32x4 v) {
+    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
+}
+__device__ __forceinline__ void global_write128_through(uint8_t* base, uint32_t offset, u32x4 v) {
+    asm volatile("global_store_dwordx4 %0, %1, %2 sc0 sc1\n\ts_nop 1"
+                 : : "v"(offset), "v"(v), "s"(base) : "memory");
+}
+
+// n < 16 bytes at any alignment, zero-padded, and nothing behind them: pieces of 8, 4, 2 and 1 bytes as
+// the bits of n say, all on their way at once.  (Byte by byte, each added to its word before the next
+// was asked for, a ragged block took up to fifteen trips to memory one after the other.)
+template <class T>
+__device__ __forceinline__ T global_read_any(const uint8_t* p) {
+    typedef T any __attribute__((aligned(1)));
+    return *reinterpret_cast<__attribute__((address_space(1))) const any*>(
+        reinterpret_cast<uintptr_t>(p));
+}
+__device__ __forceinline__ Block read_bytes(const uint8_t* p, uint32_t n) {
+    asm volatile("" : "+v"(n));  // what is made of it is not to be kept from row to row
+    uint64_t v8 = 0;
+    uint32_t v4 = 0, v2 = 0, v1 = 0;
+    if (n & 8) v8 = global_read_any<uint64_t>(p);
+    if (n & 4) v4 = global_read_any<uint32_t>(p + (n & 8));
+    if (n & 2) v2 = global_read_any<uint16_t>(p + (n & 12));
+    if (n & 1) v1 = global_read8(p + (n & 14));
+    const uint32_t last = (n & 2) ? v2 | v1 << 16 : v1;  // the up to three bytes of the last word
+    const uint32_t from4 = (n & 4) ? v4 : last, then = (n & 4) ? last : 0;
+    Block b;
+    b.w[0] = (n & 8) ? (uint32_t)v8 : from4;
+    b.w[1] = (n & 8) ? (uint32_t)(v8 >> 32) : then;
+    b.w[2] = (n & 8) ? from4 : 0;
+    b.w[3] = (n & 8) ? then : 0;
+    return b;
+}
+// ... and written, to a 16-byte boundary
+template <bool kThrough, class T>
+__device__ __forceinline__ void global_write_piece(uint8_t* p, T v) {
+    auto* const to = reinterpret_cast<__attribute__((address_space(1))) T*>(reinterpret_cast<uintptr_t>(p));
+    if constexpr (kThrough)
+        __hip_atomic_store(to, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    else
+        *to = v;
+}
+template <bool kThrough>
+__device__ __forceinline__ void write_bytes(uint8_t* p, uint32_t n, uint32_t w0, uint32_t w1,
+                                            uint32_t w2, uint32_t w3) {
+    asm volatile("" : "+v"(n), "+v"(w0), "+v"(w1), "+v"(w2), "+v"(w3));
+    if (n & 8) global_write_piece<kThrough>(p, (uint64_t)w0 | (uint64_t)w1 << 32);
+    if (n & 8) w0 = w2, w1 = w3;  // what is behind that piece
+    if (n & 4) global_write_piece<kThrough>(p + (n & 8), w0);
+    const uint32_t last = (n & 4) ? w1 : w0;
+    if (n & 2) global_write_piece<kThrough>(p + (n & 12), (uint16_t)last);
+    if (n & 1) global_write_piece<kThrough>(p + (n & 14), (uint8_t)((n & 2) ? last >> 16 : last));
+}
+
+// block i of a byte string, zero-padded (SP 800-38D 6.4)
+__device__ __forceinline__ Block padded_block(const uint8_t* p, uint32_t bytes, uint32_t i) {
+    const uint32_t off = 16 * i, m = bytes - off;
+    if (m >= 16) return global_read_block_any(p + off);
+    return read_bytes(p + off, m);
+}
+}  // namespace
+
+// ------------------------------------------------------------------------------------------
 // GHASH state after the AAD of a chunk (SP 800-38D 6.4 over A || 0-pad), hashed serially with the
 // table of H in global memory: meant for the short headers AAD is used for.  All lanes that call
 // it with the same arguments compute the same value.
@@ -410,13 +515,8 @@ __device__ Block aad_hash(const KeyTables* __restrict__ kt, const uint8_t* __res
                           uint32_t aad_len) {
     Block y{{0, 0, 0, 0}};
     for (uint32_t off = 0; off < aad_len; off += 16) {
-        uint32_t m = aad_len - off < 16 ? aad_len - off : 16;
-        uint32_t x[4] = {0, 0, 0, 0};
-#pragma unroll
-        for (uint32_t b = 0; b < 16; ++b) {
-            if (b < m) x[b / 4] |= (uint32_t)aad[off + b] << (8 * (b % 4));
-        }
-        y.w[0] ^= x[0], y.w[1] ^= x[1], y.w[2] ^= x[2], y.w[3] ^= x[3];
+        const Block x = padded_block(aad, aad_len, off / 16);
+        block_xor(y, x);
         y = gf_mul_table(kt->ghash[0], y);
     }
     return y;
@@ -491,55 +591,8 @@ static_assert(sizeof(BulkLds) == kLdsBytes + 16 * (kWavesPerGroup + 1) && offset
               "LDS map");
 
 typedef __attribute__((address_space(3))) const uint32_t* lds_u32_ptr;
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) const u32x4* lds_u128_ptr;
 typedef __attribute__((address_space(3))) u32x4* lds_u128_wptr;
-typedef __attribute__((address_space(1))) const u32x4* global_u128_cptr;
-typedef __attribute__((address_space(1))) u32x4* global_u128_ptr;
-
-// payload accesses go through global (not flat) instructions, so that waiting for LDS results
-// never waits for them
-__device__ __forceinline__ u32x4 global_read128(const uint8_t* p) {
-    return *reinterpret_cast<global_u128_cptr>(reinterpret_cast<uintptr_t>(p));
-}
-__device__ __forceinline__ void global_write128(uint8_t* p, u32x4 v) {
-    *reinterpret_cast<global_u128_ptr>(reinterpret_cast<uintptr_t>(p)) = v;
-}
-// ... and so do the single bytes of a ragged last block: one flat access anywhere in the row loop
-// would make every wait in it a wait for everything
-typedef __attribute__((address_space(1))) const uint8_t* global_u8_cptr;
-typedef __attribute__((address_space(1))) uint8_t* global_u8_ptr;
-__device__ __forceinline__ uint8_t global_read8(const uint8_t* p) {
-    return *reinterpret_cast<global_u8_cptr>(reinterpret_cast<uintptr_t>(p));
-}
-__device__ __forceinline__ void global_write8(uint8_t* p, uint8_t v) {
-    *reinterpret_cast<global_u8_ptr>(reinterpret_cast<uintptr_t>(p)) = v;
-}
-
-// 16 bytes at any alignment
-typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
-typedef __attribute__((address_space(1))) const u32x4_any* global_u128_any_cptr;
-typedef __attribute__((address_space(1))) u32x4_any* global_u128_any_ptr;
-__device__ __forceinline__ Block global_read_block_any(const uint8_t* p) {
-    const u32x4_any v = *reinterpret_cast<global_u128_any_cptr>(reinterpret_cast<uintptr_t>(p));
-    return Block{{v.x, v.y, v.z, v.w}};
-}
-__device__ __forceinline__ void global_write_block_any(uint8_t* p, const Block& b) {
-    const u32x4_any v = {b.w[0], b.w[1], b.w[2], b.w[3]};
-    *reinterpret_cast<global_u128_any_ptr>(reinterpret_cast<uintptr_t>(p)) = v;
-}
-
-// block i of a byte string, zero-padded (SP 800-38D 6.4)
-__device__ __forceinline__ Block padded_block(const uint8_t* p, uint32_t bytes, uint32_t i) {
-    const uint32_t off = 16 * i, m = bytes - off;
-    if (m >= 16) return global_read_block_any(p + off);
-    Block b{{0, 0, 0, 0}};
-#pragma unroll
-    for (uint32_t k = 0; k < 15; ++k)
-        if (k < m) b.w[k / 4] |= (uint32_t)global_read8(p + off + k) << (8 * (k % 4));
-    return b;
-}
-
 // The AAD comes right before the ciphertext in what is hashed, so its blocks are given the numbers
 // -n .. -1 and are hashed by the lanes that lie before the chunk's start: no multiplications of
 // their own, where hashing 64 bytes ahead of block 0 from the table in memory takes some 5 us.
@@ -612,23 +665,6 @@ __device__ __forceinline__ Block load_block_device_scope(const Block* p) {
     const uint64_t a = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const uint64_t b = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return Block{{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32)}};
-}
-
-// Payload stores that go through to memory at once instead of staying dirty in this XCD's L2:
-// for output that a wavefront on another XCD may overwrite later in the same kernel (the wipe of
-// a rejected chunk), where two L2s holding different dirty versions of a line would leave it to
-// chance which one memory keeps.
-// (A store of more than 64 bits still reads its registers when the next instruction issues: the next
-// two must not write them, and only in code of its own does the compiler see to that.)
-__device__ __forceinline__ void global_write128_through(uint8_t* p, u32x4 v) {
-    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
-}
-__device__ __forceinline__ void global_write128_through(uint8_t* base, uint32_t offset, u32x4 v) {
-    asm volatile("global_store_dwordx4 %0, %1, %2 sc0 sc1\n\ts_nop 1"
-                 : : "v"(offset), "v"(v), "s"(base) : "memory");
-}
-__device__ __forceinline__ void global_write8_through(uint8_t* p, uint8_t v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // waits until every global load and store this wavefront has issued is complete (for a
@@ -1320,16 +1356,8 @@ __device__ __forceinline__ RowPayload load_row(const uint8_t* src, uint64_t len,
             r.x0 = a.w[0], r.x1 = a.w[1], r.x2 = a.w[2], r.x3 = a.w[3];
         }
         if (__builtin_expect(r.tail != 0, 0)) {
-#pragma unroll
-            for (uint32_t b = 0; b < 15; ++b) {
-                if (b < r.tail) {
-                    const uint32_t v = (uint32_t)global_read8(sp + b) << (8 * (b % 4));
-                    if (b / 4 == 0) r.x0 |= v;
-                    if (b / 4 == 1) r.x1 |= v;
-                    if (b / 4 == 2) r.x2 |= v;
-                    if (b / 4 == 3) r.x3 |= v;
-                }
-            }
+            const Block v = read_bytes(sp, r.tail);
+            r.x0 = v.w[0], r.x1 = v.w[1], r.x2 = v.w[2], r.x3 = v.w[3];
         }
     }
     return r;
@@ -1368,16 +1396,7 @@ __device__ __forceinline__ void bulk_row(const Keys& rk, AesAddr& A,
         store_block();
     }
     if (__builtin_expect(edge && tail, 0)) {
-#pragma unroll
-        for (uint32_t b = 0; b < 15; ++b) {
-            if (b < tail) {
-                const uint32_t w = b / 4 == 0 ? o0 : b / 4 == 1 ? o1 : b / 4 == 2 ? o2 : o3;
-                if constexpr (kThrough)
-                    global_write8_through(dp + b, (uint8_t)(w >> (8 * (b % 4))));
-                else
-                    global_write8(dp + b, (uint8_t)(w >> (8 * (b % 4))));
-            }
-        }
+        write_bytes<kThrough>(dp, tail, o0, o1, o2, o3);
         // bytes past the end count as zero in the hash
         const uint32_t keep = tail % 4 ? (1u << (8 * (tail % 4))) - 1u : 0u;  // in the partial word
         const uint32_t q = tail / 4;
@@ -2839,9 +2858,8 @@ __device__ __forceinline__ void small_row(const uint32_t* __restrict__ rk,
         x[0] = v.x, x[1] = v.y, x[2] = v.z, x[3] = v.w;
     }
     if (tail) {
-#pragma unroll
-        for (uint32_t b = 0; b < 15; ++b)
-            if (b < tail) x[b / 4] |= (uint32_t)sp[b] << (8 * (b % 4));
+        const Block v = read_bytes(sp, tail);
+        for (int w = 0; w < 4; ++w) x[w] = v.w[w];
     }
     s[0] = j.w[0], s[1] = j.w[1], s[2] = j.w[2], s[3] = bswap32((uint32_t)blk + ctr1);
     aes_block_lds_plain<kRounds>(rk, te, s);
@@ -2851,9 +2869,7 @@ __device__ __forceinline__ void small_row(const uint32_t* __restrict__ rk,
         global_write128(dp, v);
     }
     if (tail) {
-#pragma unroll
-        for (uint32_t b = 0; b < 15; ++b)
-            if (b < tail) dp[b] = (uint8_t)(o[b / 4] >> (8 * (b % 4)));
+        write_bytes<false>(dp, tail, o[0], o[1], o[2], o[3]);
         // bytes past the end count as zero in the hash
 #pragma unroll
         for (uint32_t b = 1; b < 16; ++b)
