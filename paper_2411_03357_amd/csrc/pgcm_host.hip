@@ -6,6 +6,8 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <type_traits>
+
 #include <chrono>
 #include <mutex>
 #include <new>
@@ -418,23 +420,6 @@ void launch_bulk(int rounds, bool matrix_hash, dim3 grid, hipStream_t stream, Ar
         launch_bulk_rounds<kDecrypt, false>(rounds, grid, stream, args...);
 }
 
-// the kernel of a batch that takes one launch: `done`, if not null, marks its end
-template <bool kDecrypt, SwapKind kKind, class... Args>
-void launch_swap(int rounds, dim3 grid, dim3 block, hipStream_t stream, bool capturing,
-                 hipEvent_t done, Args... args) {
-    auto launch = [&](auto* kernel) {
-        launch_last(kernel, grid, block, stream, capturing || done == nullptr, done, args...);
-    };
-    if constexpr (kKind != SwapKind::kUnits)
-        launch(swap_kernel<kDecrypt, 0, kKind>);
-    else if (rounds == 10)
-        launch(swap_kernel<kDecrypt, 10, kKind>);
-    else if (rounds == 12)
-        launch(swap_kernel<kDecrypt, 12, kKind>);
-    else
-        launch(swap_kernel<kDecrypt, 14, kKind>);
-}
-
 // many chunks of one row: a wavefront per chunk
 template <bool kDecrypt, class... Args>
 void launch_small(int rounds, uint32_t nchunks, hipStream_t stream, bool capturing, hipEvent_t done,
@@ -747,9 +732,9 @@ void use_slots(Context* ctx, size_t n, hipStream_t stream, bool capturing) {
 
 // How a batch is cut for the one-launch path, if it takes it.
 struct SwapShape {
-    bool narrow;                              // only short chunks: the kernel with small tables
+    bool burst;                               // burst_kernel
     bool alone;                               // every chunk has one workgroup
-    uint32_t unit_power, wave_power, groups;
+    uint32_t unit_power, wave_power, groups;  // burst: log2 of a workgroup's passes for unit_power
 };
 
 inline uint32_t swap_groups(const BatchArgs& a, size_t i, uint32_t unit_power, uint32_t wave_power) {
@@ -760,10 +745,22 @@ inline uint32_t swap_groups(const BatchArgs& a, size_t i, uint32_t unit_power, u
     return groups == 0 ? 1 : (uint32_t)groups;
 }
 
-// Batches of short chunks: units of one row.  As long as there is a compute unit for every chunk a
-// workgroup takes a whole chunk; of more chunks, several workgroups of four wavefronts share a
-// compute unit, and the longer chunks take two or three.
-// Others: the smallest unit with which the batch fits the compute units, a workgroup each, at
+// burst_kernel: what a chunk's passes cover, and its workgroups if they make 2^pass_power passes each
+inline uint64_t burst_blocks(const BatchArgs& a, size_t i) {
+    return (a.len[i] + 15) / 16 + swap_lead_blocks(a.aad_len ? a.aad_len[i] : 0, true);
+}
+inline uint64_t burst_groups(uint64_t blocks, uint32_t wave_power, uint32_t pass_power) {
+    const uint32_t shift = 4 + wave_power + pass_power;
+    const uint64_t groups = (blocks + ((uint64_t)1 << shift) - 1) >> shift;
+    return groups == 0 ? 1 : groups;
+}
+
+// Batches of short chunks, and others of at most four passes for every compute unit, go to burst_kernel.
+// As long as there is a compute unit for every short chunk, a workgroup takes a whole one, with no
+// more wavefronts than it has blocks for; of more chunks, workgroups of at most eight wavefronts share
+// a compute unit, and the longer chunks take several.  Longer chunks are spread over as many
+// workgroups of sixteen as there are compute units.
+// What is left: the smallest unit with which the batch fits the compute units, a workgroup each, at
 // sixteen wavefronts, then the fewest wavefronts a workgroup with which it still does.
 bool swap_shape(const pgcm_key* key, const BatchArgs& a, bool all_small, SwapShape* shape) {
     if (a.n > kSmallMaxChunks || (!all_small && !key->one_launch)) return false;
@@ -778,13 +775,29 @@ bool swap_shape(const pgcm_key* key, const BatchArgs& a, bool all_small, SwapSha
         }
         return sum;
     };
-    uint32_t up = kMinUnitPower, wp = 2, longest = 0;
+    uint32_t up = kMinUnitPower + 1, wp = 2, longest = 0;
     uint64_t total = 0;
+    // burst_kernel's workgroups
+    uint64_t blocks[kSmallMaxChunks], most_blocks = 0;
+    for (size_t k = 0; k < a.n; ++k) {
+        blocks[k] = burst_blocks(a, a.at(k));
+        if (blocks[k] > most_blocks) most_blocks = blocks[k];
+    }
+    auto bursts = [&](uint32_t wave_power, uint32_t pass_power) {
+        uint64_t sum = 0;
+        for (size_t k = 0; k < a.n; ++k) sum += burst_groups(blocks[k], wave_power, pass_power);
+        return sum;
+    };
     if (all_small) {
-        total = groups(up, wp, &longest);
-        if (a.n <= num_cu || total > kSwapMaxGroups)
-            while (longest > 1 && wp < 4) total = groups(up, ++wp, &longest);
-        if (total > kSwapMaxGroups) return false;
+        while (wp < 4 && most_blocks > (uint64_t)16 << wp) ++wp;
+        uint32_t pp = 2;
+        total = a.n;
+        if (a.n > num_cu && wp > 2 && bursts(3, 0) <= kSwapMaxGroups) {
+            wp = 3, pp = 0;
+            total = bursts(wp, pp);
+        }
+        *shape = SwapShape{true, total == a.n, pp, wp, (uint32_t)total};
+        return true;
     } else {
         const uint32_t most = num_cu < kSwapChunkGroups ? num_cu : kSwapChunkGroups;
         if (a.n > most) return false;
@@ -792,6 +805,12 @@ bool swap_shape(const pgcm_key* key, const BatchArgs& a, bool all_small, SwapSha
         for (size_t k = 0; k < a.n; ++k) bytes += a.len[a.at(k)];
         if (bytes > (uint64_t)most * kWavesPerGroup * kUnitBytes) return false;
         const uint32_t forced = key->forced_unit_power;
+        if (forced <= kMinUnitPower)
+            for (uint32_t pp = 0; pp <= kFoldPassPower; ++pp)
+                if ((total = bursts(4, pp)) <= most) {
+                    *shape = SwapShape{true, total == a.n, pp, 4, (uint32_t)total};
+                    return true;
+                }
         if (forced) up = forced;
         if (up > kUnitPower) return false;
         wp = 4;
@@ -806,25 +825,36 @@ bool swap_shape(const pgcm_key* key, const BatchArgs& a, bool all_small, SwapSha
             --wp, total = t, longest = l;
         }
     }
-    *shape = SwapShape{all_small, longest <= 1, up, wp, (uint32_t)total};
+    *shape = SwapShape{false, longest <= 1, up, wp, (uint32_t)total};
     return true;
 }
 
-template <SwapKind kKind>
 void launch_swap_batch(const pgcm_key* key, const BatchArgs& a, const SwapShape& shape,
                        hipEvent_t done, const ArgBatch& batch, const GroupDesc* staged,
                        ArriveSlot* slots) {
-    const dim3 grid(shape.groups), block(64u * ((1u << shape.wave_power) + (shape.wave_power < 4)));
+    const uint32_t more = !shape.burst && shape.wave_power < 4;  // a wavefront beyond those with units
+    const dim3 grid(shape.groups), block(64u * ((1u << shape.wave_power) + more));
     const KeyTables* kt = key->tables;
     const SwapMeta meta = swap_meta(staged ? 0 : (uint32_t)a.n, shape.unit_power, shape.wave_power,
                                     shape.alone, a.order == nullptr, shape.groups,
                                     (uint32_t)key->rounds);
-    if (a.decrypt)
-        launch_swap<true, kKind>(key->rounds, grid, block, a.stream, a.capturing, done, kt, a.ivs,
-                                 a.iv_len, meta, slots, a.tags, a.ok, staged, batch);
-    else
-        launch_swap<false, kKind>(key->rounds, grid, block, a.stream, a.capturing, done, kt, a.ivs,
-                                  a.iv_len, meta, slots, a.tags, a.ok, staged, batch);
+    auto burst = [&](auto kind) {
+        constexpr BurstKind kKind = decltype(kind)::value;
+        const bool long_iv = a.iv_len > kShortIvBytes;
+        return a.decrypt ? (long_iv ? burst_kernel<true, true, kKind> : burst_kernel<true, false, kKind>)
+                         : (long_iv ? burst_kernel<false, true, kKind> : burst_kernel<false, false, kKind>);
+    };
+    const bool shared = shape.groups > (uint32_t)key->num_cu;
+    auto* const kernel =
+        shape.burst && shape.wave_power < 4
+            ? burst(std::integral_constant<BurstKind, BurstKind::kWords>{})
+        : shape.burst && shared ? burst(std::integral_constant<BurstKind, BurstKind::kFoldShared>{})
+        : shape.burst           ? burst(std::integral_constant<BurstKind, BurstKind::kFold>{})
+        : key->rounds == 10 ? (a.decrypt ? swap_kernel<true, 10> : swap_kernel<false, 10>)
+        : key->rounds == 12 ? (a.decrypt ? swap_kernel<true, 12> : swap_kernel<false, 12>)
+                            : (a.decrypt ? swap_kernel<true, 14> : swap_kernel<false, 14>);
+    launch_last(kernel, grid, block, a.stream, a.capturing || done == nullptr, done, kt, a.ivs,
+                a.iv_len, meta, slots, a.tags, a.ok, staged, batch);
 }
 
 // A batch of few chunks that does not fill the chip: one kernel.  Up to kArgChunks chunks travel as
@@ -851,7 +881,9 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapSh
         c.aad_len = a.aad_len ? a.aad_len[i] : 0;
         c.aad = c.aad_len ? (const uint8_t*)a.aad[i] : nullptr;
         c.index = (uint32_t)i;
-        const uint32_t of_chunk = swap_groups(a, i, shape.unit_power, shape.wave_power);
+        const uint32_t of_chunk =
+            !shape.burst ? swap_groups(a, i, shape.unit_power, shape.wave_power)
+            : shape.alone ? 1 : (uint32_t)burst_groups(burst_blocks(a, i), shape.wave_power, shape.unit_power);
         if (in_args) {
             batch.c[k] = c;
             batch.group_base[k] = groups;
@@ -875,12 +907,7 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapSh
     // earlier batch's staging buffer, that batch ends before this one on the same stream, so
     // using it again only moves the guard later.)
     const hipEvent_t done = ctx != nullptr ? ctx->stage_done[s] : nullptr;
-    if (shape.narrow)
-        launch_swap_batch<SwapKind::kNarrow>(key, a, shape, done, batch, h_groups, slots);
-    else if (shape.unit_power == kRowPower)
-        launch_swap_batch<SwapKind::kRows>(key, a, shape, done, batch, h_groups, slots);
-    else
-        launch_swap_batch<SwapKind::kUnits>(key, a, shape, done, batch, h_groups, slots);
+    launch_swap_batch(key, a, shape, done, batch, h_groups, slots);
     if (rc_timing == PGCM_OK) rc_timing = record_timing_stop(key, a.stream);
     int rc_end = PGCM_OK;
     if (!in_args) {
@@ -1114,7 +1141,7 @@ int run_batch(pgcm_key* key, BatchArgs a) {
     // and end later.  With sixteen wavefronts a workgroup, a batch of one launch takes 14 us and
     // 4.3 a row of its units, with eight 12 and 2.4; spans take 25 and 3.6 a row (147 chunks of
     // 60 to 450 KB: units of 16 rows, spans of 7, 83 and 54 us; 3 of 5 MiB: 4 and 3.8, 32 and 38).
-    if (one_launch && spans && !v.all_small && shape.wave_power == 4) {
+    if (one_launch && spans && !shape.burst && shape.wave_power == 4) {
         const uint64_t unit_rows = 1u << (shape.unit_power - kRowPower);
         if (43 * unit_rows * key->wave_slots > 110 * (uint64_t)key->wave_slots + 36 * v.rows)
             one_launch = false;

@@ -22,16 +22,25 @@ __global__ void bulk_kernel(const KeyTables* kt, const ChunkDesc* chunks,
 // The whole invocation of a few chunks in one launch, 2^wave_power wavefronts of units a workgroup (at
 // least four) and, below sixteen, one more.  The chunks come as arguments, or, when `staged` is not
 // null, with a descriptor per workgroup there (batch is not looked at then).
-// slots: one per workgroup; not touched if no chunk has more than one workgroup.  kRows: units of one row; kNarrow: likewise,
-// and the round tables take half the room (both with kRounds 0, they serve any key); kUnits: units of
-// two to sixteen rows.
+// slots: one per workgroup; not touched if no chunk has more than one workgroup.  Units
+// of two to sixteen rows.
 // The arguments before `batch` come in registers (compiled for that, they are the first fourteen
 // words), so that the tables are fetched while the rest of the arguments is.
-enum class SwapKind { kNarrow, kRows, kUnits };
-template <bool kDecrypt, int kRounds, SwapKind kKind>
+template <bool kDecrypt, int kRounds>
 __global__ void swap_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t iv_len, SwapMeta meta,
                             ArriveSlot* slots, uint8_t* tags, uint8_t* ok, const GroupDesc* staged,
                             ArgBatch batch);
+
+// The same for batches whose time is that of one chain of steps: 2^wave_power wavefronts of sixteen blocks
+// a workgroup, which makes 2^meta.unit_power() passes, or, where a chunk has one workgroup, as many as
+// it takes (at most kBurstPasses).  It serves any key.  kLongIv: iv_len exceeds kShortIvBytes.
+// kWords: at most eight wavefronts.  kFold: sixteen, and at most kFoldPasses passes; kFoldShared: the
+// same, one pass less, and two workgroups fit a compute unit.
+enum class BurstKind { kWords, kFold, kFoldShared };
+template <bool kDecrypt, bool kLongIv, BurstKind kKind>
+__global__ void burst_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t iv_len, SwapMeta meta,
+                             ArriveSlot* slots, uint8_t* tags, uint8_t* ok, const GroupDesc* staged,
+                             ArgBatch batch);
 
 // Spans of rows, one per wavefront, of chunks of one key (`key`) or of several (null; every
 // workgroup has its own).  packets: stride 0: the workgroups' SpanGroup, and their parts in `parts`;

@@ -15,8 +15,10 @@
 //   * A wavefront walks rows of 64 blocks of one chunk, one block per lane, 16-byte coalesced loads
 //     and stores, ciphertext hashed from registers.
 // Which rows, and how their sums become tags, differs:
-//   * swap_kernel: a few chunks that do not fill the chip, in one launch, cut as finely as it takes
-//     for all of it to work at once.
+//   * burst_kernel: up to sixteen rows a compute unit, in one launch: a call is as long as its chain of
+//     dependent steps.
+//   * swap_kernel: more than that, but not enough to fill the chip, in one launch, in units of two to
+//     sixteen rows.
 //   * span_kernel: everything else, of one key or of several, in one launch: every wavefront of the
 //     chip an equal share of all rows.
 //   * small_kernel: many chunks of one row each, a wavefront per chunk.
@@ -227,13 +229,14 @@ __device__ GfWords gfw_square(const GfWords& x) {
 __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict__ kt,
                                                           const uint32_t* __restrict__ key_words,
                                                           uint32_t nk) {
-    // constants with a nibble table: H^(2^k), then H^3, H^12, H^48; then H^96 without one
-    constexpr uint32_t kConstants = kNumPowers + kNumLanePowers + 1, kAt96 = kConstants - 1;
-    constexpr uint32_t kLevels = 6;  // nibble tables of H^1 .. H^32 kept in LDS as well
+    // H^(2^k), then H^3, H^12, H^48, H^96 and H^192; all but H^96 get a nibble table
+    constexpr uint32_t kConstants = kNumPowers + kNumLanePowers + 2, kAt96 = kConstants - 2,
+                       kAt192 = kConstants - 1;
+    constexpr uint32_t kLevels = 8;  // nibble tables of H^1 .. H^128 kept in LDS as well
     __shared__ GfWords constants[kConstants];
     __shared__ Block basis[kConstants][128];  // x^b * constant, b = bit b % 32 of word b / 32
     __shared__ Block nibbles[kLevels][kNibbleTableEntries];
-    __shared__ GfWords h_power[66];
+    __shared__ GfWords h_power[kDotBlocks + 2];
     __shared__ uint32_t te[4][256], rk[60];
     __shared__ uint8_t sbox[256];
     const uint32_t tid = threadIdx.x;
@@ -296,10 +299,15 @@ __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict_
     }
     __syncthreads();
     if (tid < 60) kt->rk[tid] = rk[tid];
-    // H^3, H^12, H^48, H^96 = products of two neighbouring squares
-    if (tid <= kNumLanePowers)
-        constants[kNumPowers + tid] =
-            gfw_mul(constants[tid < 3 ? 2 * tid : 5], constants[tid < 3 ? 2 * tid + 1 : 6]);
+    if (tid < 64) {
+        const uint32_t c = tid / 16, r = tid % 16;
+        kt->column_keys[c][r] = r < 14 ? rk[4 * r + c] : r == 15 ? rk[4 * nr + c] : 0;
+    }
+    // H^3, H^12, H^48, H^96, H^192 = products of two neighbouring squares
+    if (tid <= kNumLanePowers + 1) {
+        const uint32_t first = tid < 3 ? 2 * tid : tid + 2;
+        constants[kNumPowers + tid] = gfw_mul(constants[first], constants[first + 1]);
+    }
     __syncthreads();
 
     // sixteen threads per constant, eight neighbouring coefficients each
@@ -325,6 +333,13 @@ __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict_
         else
             kt->ghash_lane[c - kNumPowers][idx] = z;
         if (c < kLevels) nibbles[c][idx] = z;
+    }
+    for (uint32_t idx = tid; idx < kNibbleTableEntries; idx += blockDim.x) {
+        const Block* from = &basis[kAt192][8 * (idx / 32) + ((idx & 16) ? 0 : 4)];
+        Block z{{0, 0, 0, 0}};
+        for (int i = 0; i < 4; ++i)
+            if (idx & (1u << i)) block_xor(z, from[i]);
+        kt->ghash_rows3[idx] = z;
     }
 
     // Multiplication by H^64 with the bits of every operand quarter in a register of its own lane
@@ -357,7 +372,8 @@ __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict_
         kt->hash_image[m][e % kRowMatrixWords] = v;
     }
 
-    // H^1 .. H^65, doubling: H^(2^j + i) = H^i * H^(2^j)
+    // H^1 .. H^257, doubling: H^(2^j + i) = H^i * H^(2^j)
+    static_assert(kDotBlocks == 1u << kLevels, "and one more");
     if (tid == 0) h_power[1] = constants[0];
     __syncthreads();
     for (uint32_t j = 0; j < kLevels; ++j) {
@@ -368,13 +384,17 @@ __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict_
         __syncthreads();
     }
     if (tid == 0)
-        h_power[65] = gfw_from_block(gf_mul_table(nibbles[0], gfw_to_block(h_power[64])));
+        h_power[kDotBlocks + 1] =
+            gfw_from_block(gf_mul_table(nibbles[0], gfw_to_block(h_power[kDotBlocks])));
     __syncthreads();
-    for (uint32_t e = tid; e < 64 * kDotSlices; e += blockDim.x) {
-        const uint32_t l = e / kDotSlices, t = e % kDotSlices;
-        GfWords p = h_power[65 - l];
+    for (uint32_t e = tid; e < kDotBlocks * 4; e += blockDim.x) {
+        const uint32_t l = e / 4, t = kDotSlices / 4 * (e % 4);
+        GfWords p = h_power[kDotBlocks + 1 - l];
         for (uint32_t i = 0; i < t; ++i) gfw_mul_x8(p);
-        kt->dot[l][t] = p;
+        for (uint32_t i = t; i < t + kDotSlices / 4; ++i) {
+            kt->dot[l][i] = p;
+            gfw_mul_x8(p);
+        }
     }
     // hop[d][k] likewise: k = 2^j + i from i with H^(2^(8 + d + j)), from its nibble table; and the
     // rows' hops
@@ -605,7 +625,19 @@ __device__ __forceinline__ Block serial_hash(const Block* __restrict__ h_table, 
     for (uint32_t i = 0; i < blocks; ++i) {
         const Block b = padded_block(p, bytes, i);
         block_xor(y, b);
-        y = gf_mul_table(h_table, y);
+        // a word at a time: the registers are needed by what is usual
+        Block z{{0, 0, 0, 0}};
+#pragma unroll 1
+        for (uint32_t w = 0; w < 4; ++w) {
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) {
+                const uint32_t byte = (y.w[0] >> (8 * k)) & 0xFF, pos = 2 * (4 * w + k);
+                block_xor(z, h_table[pos * 16 + (byte >> 4)]);
+                block_xor(z, h_table[(pos + 1) * 16 + (byte & 15)]);
+            }
+            y.w[0] = y.w[1], y.w[1] = y.w[2], y.w[2] = y.w[3];
+        }
+        y = z;
     }
     return y;
 }
@@ -698,13 +730,6 @@ __device__ __forceinline__ void lds_write128(uint32_t addr, u32x4 v) {
 struct TeWide {
     static constexpr uint32_t kBase = kLdsTeBase, kPairs = 0x10000u, kLanes = 32;
     static constexpr uint32_t offset(int t) { return kBase + 128u * (t & 1); }
-};
-// TeNarrow: 64 KiB with all four tables in a row, every entry sixteen times, so that lanes l and
-// l + 16 share a bank: 4 cycles, but half the room and half the time to fill.  For launches of few
-// rows on a compute unit.
-struct TeNarrow {
-    static constexpr uint32_t kBase = 0, kBytes = 4 * 256 * 16 * 4, kPairs = 0, kLanes = 16;
-    static constexpr uint32_t offset(int t) { return kBase + 64u * t; }
 };
 template <class Te, int T>
 __device__ __forceinline__ uint32_t te_read(uint32_t a, uint32_t base) {
@@ -812,18 +837,6 @@ struct CtrInner {
     uint32_t next;  // LDS address of the next row's q
 };
 
-// The counter block of a row that stands alone (a unit of one row): no constants are formed, and
-// round 1 makes its sixteen lookups like any other.
-struct LaneKeys {
-    uint32_t word;    // lane i: round key word i
-    uint32_t rounds;
-};
-template <class TeLayout>
-struct CtrBlock {
-    using Te = TeLayout;
-    uint32_t iv0, iv1, iv2, ctr;
-};
-
 // first_ctr: the counter of the segment's first block (the same in every lane)
 __device__ __forceinline__ CtrConsts ctr_consts(const uint32_t* __restrict__ rk, uint32_t lane,
                                                 uint32_t wave, uint32_t iv0, uint32_t iv1,
@@ -896,15 +909,6 @@ __device__ __forceinline__ uint32_t nibble_offset(uint32_t v, uint32_t mask_f0) 
 // own, from row to row: start() clears it, begin() prepares a row's multiplication, its parts
 // ride along with the row's AES rounds, absorb() adds the row's ciphertext, home() leaves the
 // unit's 64 lane sums as blocks.
-
-// A unit of one row: its sums are its blocks, and nothing is multiplied.
-struct GhashNone {
-    uint32_t w[4];
-    __device__ __forceinline__ void begin() {}
-    __device__ __forceinline__ void absorb(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3) {
-        w[0] = c0, w[1] = c1, w[2] = c2, w[3] = c3;
-    }
-};
 
 // Y * H^64 in every lane, from the nibble table in LDS, cut into sixteen byte steps (two 16-byte
 // lookups and eight XORs each) so that the steps can be spread over the AES rounds of the same
@@ -1244,58 +1248,45 @@ __device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, Aes
     aes_rounds_lds<TeWide, 3, kRounds>(rk, A, u0, u1, u2, u3, G, base, o0, o1, o2, o3);
 }
 
-// ... and in a row that stands alone, where latency counts.  The keys wait in the lanes of a
-// register, fetched with everything else a launch starts with (in scalar registers they would be a
-// second load to wait for, 0.3 us), and one kernel serves every round count.  A wavefront being
-// alone on its SIMD, every column's lookups go out as soon as their four addresses are formed, and
-// its sum is formed while the later columns' are under way.  (As a loop over the rounds, a tenth
-// of the code, it takes 0.4 us more.)
-template <int kRounds, class Te>
-__device__ __forceinline__ void aes_ctr_lds(const LaneKeys& keys, AesAddr& A, const CtrBlock<Te>& C,
-                                            GhashNone&, uint32_t base, uint32_t& o0, uint32_t& o1,
-                                            uint32_t& o2, uint32_t& o3) {
-    static_assert(kRounds == 0, "any round count");
-    uint32_t u[4] = {C.iv0, C.iv1, C.iv2, bswap32(C.ctr)}, t[4][4];
+// One block, the same in every lane, by a wavefront that has nothing else to do; lane i of key_word has
+// round key word i.
+template <class Te>
+__device__ __forceinline__ void aes_block_lds(uint32_t key_word, uint32_t rounds, uint32_t lane,
+                                              uint32_t base, uint32_t (&u)[4]) {
+    AesAddr A;
+    aes_addr_init<Te>(A, lane);
+    uint32_t t[4][4];
     auto lookups = [&](uint32_t r) __attribute__((always_inline)) {
-        uint32_t k[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) k[c] = __builtin_amdgcn_readlane(keys.word, 4 * (r - 1) + c);
         static_for<0, 4>([&](auto col) __attribute__((always_inline)) {
             constexpr int c = decltype(col)::value;
-            static_for<0, 4>([&](auto b) __attribute__((always_inline)) {
-                constexpr int B = decltype(b)::value, J = (c + B) & 3;
-                key_xor_into_addr<B, B>(A.a[J][B], k[J], u[J]);
-            });
+            const uint32_t k = __builtin_amdgcn_readlane(key_word, 4 * r + c);
+            key_xor_into_addr<0, 0>(A.a[c][0], k, u[c]);
+            key_xor_into_addr<1, 1>(A.a[c][1], k, u[c]);
+            key_xor_into_addr<2, 2>(A.a[c][2], k, u[c]);
+            key_xor_into_addr<3, 3>(A.a[c][3], k, u[c]);
+        });
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
             t[c][0] = te_read<Te, 0>(A.a[c][0], base);
             t[c][1] = te_read<Te, 1>(A.a[(c + 1) & 3][1], base);
             t[c][2] = te_read<Te, 2>(A.a[(c + 2) & 3][2], base);
             t[c][3] = te_read<Te, 3>(A.a[(c + 3) & 3][3], base);
-            __builtin_amdgcn_sched_barrier(0);
-        });
+        }
     };
-    auto round = [&](uint32_t r) __attribute__((always_inline)) {
+#pragma unroll 1
+    for (uint32_t r = 0; r + 1 < rounds; ++r) {
         lookups(r);
-        static_for<0, 4>([&](auto col) __attribute__((always_inline)) {
-            constexpr int c = decltype(col)::value;
-            u[c] = xor3(t[c][0], t[c][1], t[c][2]) ^ t[c][3];
-            __builtin_amdgcn_sched_barrier(0);
-        });
-    };
 #pragma unroll
-    for (uint32_t r = 1; r < 10; ++r) round(r);
-    if (keys.rounds > 10) {
-        round(10), round(11);
-        if (keys.rounds > 12) round(12), round(13);
+        for (int c = 0; c < 4; ++c) u[c] = xor3(t[c][0], t[c][1], t[c][2]) ^ t[c][3];
     }
-    lookups(keys.rounds);
+    lookups(rounds - 1);
     // last round, no MixColumns: S(x) is byte 1 of te[0], byte 2 of te[1], byte 0 of te[2] and te[3]
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         const uint32_t lo = __builtin_amdgcn_perm(t[c][0], t[c][1], 0x0c0c0205u);
         const uint32_t hi = __builtin_amdgcn_perm(t[c][2], t[c][3], 0x00040c0cu);
-        u[c] = xor3(lo, hi, __builtin_amdgcn_readlane(keys.word, 4 * keys.rounds + c));
+        u[c] = xor3(lo, hi, __builtin_amdgcn_readlane(key_word, 4 * rounds + c));
     }
-    o0 = u[0], o1 = u[1], o2 = u[2], o3 = u[3];
 }
 
 // Y * C from C's nibble table at LDS address `base`, on its own (not riding along with AES):
@@ -2022,11 +2013,11 @@ template __global__ void final_kernel<true>(const KeyTables*, const ChunkDesc*, 
 
 // ------------------------------------------------------------------------------------------
 // A few chunks in ONE launch (the paper's swaps come a few chunks at a time, section 5.1): here
-// the length of the chain of dependent steps counts, not the work.  Descriptors are kernel
+// the length of the chain of dependent steps counts as much as the work.  Descriptors are kernel
 // arguments, or, for more chunks than fit those, one per workgroup in pinned memory.  Every
-// wavefront walks one unit; units are of one row as long as the chip has a
-// wavefront for each, and workgroups of four wavefronts as long as there is a compute unit for
-// each (a row takes a lone wavefront 2.6 us, sixteen on one compute unit 4.3 us).  Then
+// wavefront walks one unit of two to sixteen rows (fewer rows go to burst_kernel); workgroups have as
+// few wavefronts, at least four, as there are compute units for (a row takes a lone wavefront 2.6 us,
+// sixteen on one compute unit 4.3 us).  Then
 //   1. the workgroup folds its units' sets into one as a tree in LDS (two to four multiplications
 //      from nibble tables, which take the round tables' place);
 //   2. all its threads form the 64 products of the set's lanes with H^64 .. H^1, bit by bit from
@@ -2046,9 +2037,6 @@ template __global__ void final_kernel<true>(const KeyTables*, const ChunkDesc*, 
 // wavefronts have one more, which makes E_K(J0) and prepares the finish meanwhile.
 // LDS after the round tables are done with, in tables of 8 KiB: 0..3 H^(2^(p + j)), the tree over the
 // workgroup's units (p = unit_power); 4..5 and 6 its sets.
-// Measured against the kernel this replaced (a tree over lanes and workgroups by tables, an extra
-// row for E_K(J0)), per call back to back: one 320 KiB chunk 19.8 -> 11.3 us, one of 2 MiB decrypted
-// 27.9 -> 13.7 us.
 namespace {
 
 // XOR of the sixteen lanes of a row, left in all of them (DPP: pairs, quads, halves, row)
@@ -2058,6 +2046,22 @@ __device__ __forceinline__ uint32_t row_summed(uint32_t v) {
     v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);  // row_half_mirror
     v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true);  // row_mirror
     return v;
+}
+
+// Four words, each XORed over all lanes, left in every one.  Two swaps of lane halves and one of rows
+// make one register of the four, a row of lanes for each, so that there is one row to add up.
+// kRows: the lanes of a row have the same already.
+template <bool kRows = false>
+__device__ __forceinline__ void sum_over_lanes(uint32_t (&v)[4]) {
+    const auto a = __builtin_amdgcn_permlane32_swap(v[0], v[1], false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(v[2], v[3], false, false);
+    const auto c = __builtin_amdgcn_permlane16_swap(a[0] ^ a[1], b[0] ^ b[1], false, false);
+    uint32_t z = c[0] ^ c[1];  // rows of lanes: words 0, 2, 1, 3
+    if constexpr (!kRows) z = row_summed(z);
+    v[0] = __builtin_amdgcn_readlane(z, 0);
+    v[1] = __builtin_amdgcn_readlane(z, 32);
+    v[2] = __builtin_amdgcn_readlane(z, 16);
+    v[3] = __builtin_amdgcn_readlane(z, 48);
 }
 
 // sum over the slices s of (the eight coefficients of byte[s]) * q[s], by Horner's rule; the byte's
@@ -2099,8 +2103,7 @@ __device__ __forceinline__ GfWords dot_share(const Block& y, uint32_t wave, cons
 #pragma unroll
     for (int s = 0; s < kSlices; ++s) byte[s] = word >> (8 * (first % 4 + s));
     GfWords acc = bits_times<kSlices>(byte, q);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) acc.a[k] = rows_summed(row_summed(acc.a[k]));
+    sum_over_lanes(acc.a);
     return acc;
 }
 
@@ -2165,8 +2168,7 @@ __device__ __forceinline__ bool last_of_chunk(ArriveSlot* slots, uint32_t g, uin
     }
     if (wipe)
         for (uint32_t i = lane; i < n; i += 64) store_block_device_scope(&slots[i].sum, 0, 0, 0, 0);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) sum.w[k] = rows_summed(row_summed(sum.w[k]));
+    sum_over_lanes(sum.w);
     return true;
 }
 
@@ -2202,8 +2204,7 @@ __device__ __forceinline__ GfWords lanes_summed(const GfWords* __restrict__ powe
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] >>= 1;
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) acc.a[k] = rows_summed(row_summed(acc.a[k]));
+    sum_over_lanes(acc.a);
     return acc;
 }
 
@@ -2227,13 +2228,13 @@ __device__ __forceinline__ Block wave_j0_rows(const KeyTables* __restrict__ kt, 
         Block b{{0, 0, 0, 0}};
         const uint32_t end = blocks - (rows - 1 - r) * kRowBlocks;  // of the row
         if (end + lane >= kRowBlocks) b = padded_block(iv, iv_len, end + lane - kRowBlocks);
-        const GfWords row = lanes_summed(kt->dot[lane], b.w);
+        const GfWords row = lanes_summed(kt->dot[kDotBlocks - kRowBlocks + lane], b.w);
 #pragma unroll
         for (int k = 0; k < 4; ++k) sum.a[k] ^= row.a[k];
     }
     Block j = gfw_to_block(sum), last = length_block_entry(kt->ghash[0], 0, iv_len, lane);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) j.w[k] ^= rows_summed(row_summed(last.w[k]));
+    sum_over_lanes(last.w);
+    block_xor(j, last);
     return j;
 }
 
@@ -2257,34 +2258,26 @@ __device__ __forceinline__ Block wave_j0(const KeyTables* __restrict__ kt, const
     }
     const uint32_t nibble = (place & 1) ? byte & 15 : byte >> 4;
     Block z = kt->ghash[of_iv ? 1 : 0][place * 16 + nibble];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) z.w[k] = rows_summed(row_summed(z.w[k]));
+    sum_over_lanes(z.w);
     return z;
 }
 
 }  // namespace
 
-// Tables of the round function, then of the tree.
-struct NarrowLds {
-    uint32_t te[TeNarrow::kBytes / 4];
-    Block long_aad[kWavesPerGroup];
-};
-
-template <bool kDecrypt, int kRounds, SwapKind kKind>
+template <bool kDecrypt, int kRounds>
 __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
     const KeyTables* __restrict__ kt, const uint8_t* __restrict__ ivs, uint32_t iv_len,
     SwapMeta meta, ArriveSlot* __restrict__ slots, uint8_t* __restrict__ tags,
     uint8_t* __restrict__ ok, const GroupDesc* __restrict__ staged, const ArgBatch batch) {
-    constexpr bool kNarrow = kKind == SwapKind::kNarrow, single = kKind != SwapKind::kUnits;
-    using Te = std::conditional_t<kNarrow, TeNarrow, TeWide>;
-    __shared__ std::conditional_t<kNarrow, NarrowLds, BulkLds> lds;
+    using Te = TeWide;
+    __shared__ BulkLds lds;
     __shared__ Block mask_lds;                   // E_K(J0), where a wavefront with units makes it
     __shared__ GfWords shares[kWavesPerGroup];
     const uint32_t lds_base = lds_offset(&lds);
     const uint32_t tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t wave_power = meta.wave_power(), nwaves = 1u << wave_power;
-    const uint32_t p = single ? kRowPower : meta.unit_power();
+    const uint32_t p = meta.unit_power();
     // The wavefront that finishes the workgroup's part: one beyond those with units, or, where a
     // workgroup can have no more, the last of them, which the tree leaves idle.
     const bool beyond = wave_power < 4;
@@ -2302,7 +2295,7 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
         else if (wave_power == 3) te2.fetch(kt, tid);
         else te1.fetch(kt, tid);
     }
-    const LaneKeys lane_keys{lane < 60 ? kt->rk[lane] : 0u, meta.rounds()};
+    const uint32_t key_word = lane < 60 ? kt->rk[lane] : 0u;  // lane i: round key word i
 
     // this workgroup's chunk: the last one whose first workgroup is not behind it.  Of the chunks of
     // the caller's arrays in order, one or a workgroup each, it is known before any argument is
@@ -2349,24 +2342,20 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
                                  : end >= 0 && end - ((int64_t)1 << (p + wave_power)) < 0;
 
     u32x4 gh[2];
-    if constexpr (!single) {
-        if (worker)
+    if (worker)
 #pragma unroll
-            for (uint32_t k = 0; k < 2; ++k)
-                if (tid + (k << (6 + wave_power)) < kNibbleTableEntries)
-                    gh[k] = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower])[tid + (k << (6 + wave_power))];
-    }
+        for (uint32_t k = 0; k < 2; ++k)
+            if (tid + (k << (6 + wave_power)) < kNibbleTableEntries)
+                gh[k] = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower])[tid + (k << (6 + wave_power))];
     auto store_tables = [&]() __attribute__((always_inline)) {
         if (!worker) return;
         if (wave_power == 2) te4.store(lds.te, tid);
         else if (wave_power == 3) te2.store(lds.te, tid);
         else te1.store(lds.te, tid);
-        if constexpr (!single) {
 #pragma unroll
-            for (uint32_t k = 0; k < 2; ++k)
-                if (tid + (k << (6 + wave_power)) < kNibbleTableEntries)
-                    reinterpret_cast<u32x4*>(lds.gh)[tid + (k << (6 + wave_power))] = gh[k];
-        }
+        for (uint32_t k = 0; k < 2; ++k)
+            if (tid + (k << (6 + wave_power)) < kNibbleTableEntries)
+                reinterpret_cast<u32x4*>(lds.gh)[tid + (k << (6 + wave_power))] = gh[k];
     };
 
     // tree tables and powers of H: entry k * threads + tid of the 512 * wave_power, slices
@@ -2387,7 +2376,7 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
                 if (k < per_thread) tree[k] = from[(k << (6 + wave_power)) + tid];
 #pragma unroll
             for (uint32_t s = 0; s < 4; ++s)
-                if (s < slices) q[s] = kt->dot[lane][slices * wave + s];
+                if (s < slices) q[s] = kt->dot[kDotBlocks - kRowBlocks + lane][slices * wave + s];
         }
         if (finisher) {
             if (ngroups - 1 != g) hop = kt->hop[p + wave_power - kHopMinPower][ngroups - 1 - g];
@@ -2400,8 +2389,7 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
     auto prepare_finish = [&]() __attribute__((always_inline)) {
         if (!finisher) return;
         if (has_mask) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) extra.w[k] = rows_summed(row_summed(extra.w[k]));
+            sum_over_lanes(extra.w);
         }
         if (ngroups - 1 != g) spread_over_row(hop, lane);  // otherwise the part ends with the chunk
     };
@@ -2411,46 +2399,32 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
         __attribute__((always_inline)) { mask_lds = Block{{s0, s1, s2, s3}}; };
     uint32_t y[4] = {0, 0, 0, 0};
     const bool at_start = unit == 0 && cd.aad_len != 0;
-    // one row of 64 blocks up to b1, or J0 in every lane of the wavefront beyond
-    const int64_t blk = worker ? b1 - kRowBlocks + lane : -1;
-    if (single || !worker) {
-        const bool edge = !worker || b1 < kRowBlocks || b1 == nblk;
-        RowPayload row{0, 0, 0, 0, 0, false};
-        if (at_start) aad.prepare(kt->ghash[0]);
-        if (unit >= 0) row = load_row(cd.src, cd.len, blk, edge, aad);
+    if (!worker) {
+        // J0 in every lane: its keystream block is the tag's mask
         fetch_ahead();
-        store_tables();
-        if (beyond) prepare_finish();
+        prepare_finish();
         __syncthreads();  // the tables are in place
-        if (unit >= 0 || (!worker && has_mask)) {
-            AesAddr A;
-            aes_addr_init<Te>(A, lane);
-            GhashNone G;
-            const CtrBlock<Te> C{j.w[0], j.w[1], j.w[2], (uint32_t)blk + bswap32(j.w[3]) + 1u};
-            bulk_row<kDecrypt, 0, kDecrypt>(lane_keys, A, C, row, cd.dst, blk, edge, keep_mask,
-                                                  lds_base, G);
-            for (int k = 0; k < 4; ++k) y[k] = G.w[k];
+        if (has_mask) {
+            uint32_t e[4] = {j.w[0], j.w[1], j.w[2], j.w[3]};
+            aes_block_lds<Te>(key_word, meta.rounds(), lane, lds_base, e);
+            keep_mask(e[0], e[1], e[2], e[3]);
         }
-    }
-    if constexpr (!single) {
-        if (worker) {
-            store_tables();
-            __syncthreads();
-            if (unit >= 0) {
-                if (at_start) aad.prepare(kt->ghash[0]);
-                uint32_t rk[4 * (kRounds + 1)];
+    } else {
+        store_tables();
+        __syncthreads();
+        if (unit >= 0) {
+            if (at_start) aad.prepare(kt->ghash[0]);
+            uint32_t rk[4 * (kRounds + 1)];
 #pragma unroll
-                for (int i = 0; i < 4 * (kRounds + 1); ++i)
-                    rk[i] = __builtin_amdgcn_readlane(lane_keys.word, i);
-                AesAddr A;
-                aes_addr_init<Te>(A, lane, rk + 4 * kRounds);
-                NoPace pace;
-                walk_unit<kDecrypt, kRounds, kDecrypt, false, false>(
-                    rk, A, lane, wave, lds_base, cd.src, cd.dst, cd.len, b0, b1, b1 == nblk, aad, j,
-                    pace, keep_mask, y);
-            }
-            fetch_ahead();
+            for (int i = 0; i < 4 * (kRounds + 1); ++i) rk[i] = __builtin_amdgcn_readlane(key_word, i);
+            AesAddr A;
+            aes_addr_init<Te>(A, lane, rk + 4 * kRounds);
+            NoPace pace;
+            walk_unit<kDecrypt, kRounds, kDecrypt, false, false>(
+                rk, A, lane, wave, lds_base, cd.src, cd.dst, cd.len, b0, b1, b1 == nblk, aad, j,
+                pace, keep_mask, y);
         }
+        fetch_ahead();
     }
     if (!beyond) prepare_finish();
     __syncthreads();  // the round tables are done with: their LDS now takes the tree's
@@ -2518,16 +2492,646 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
 #define PGCM_SWAP_SIGNATURE                                                                    \
     (const KeyTables*, const uint8_t*, uint32_t, SwapMeta, ArriveSlot*, uint8_t*, uint8_t*,        \
      const GroupDesc*, ArgBatch)
-#define PGCM_INSTANTIATE_SWAP(D)                                                               \
-    template __global__ void swap_kernel<D, 0, SwapKind::kNarrow> PGCM_SWAP_SIGNATURE;             \
-    template __global__ void swap_kernel<D, 0, SwapKind::kRows> PGCM_SWAP_SIGNATURE;               \
-    template __global__ void swap_kernel<D, 10, SwapKind::kUnits> PGCM_SWAP_SIGNATURE;             \
-    template __global__ void swap_kernel<D, 12, SwapKind::kUnits> PGCM_SWAP_SIGNATURE;             \
-    template __global__ void swap_kernel<D, 14, SwapKind::kUnits> PGCM_SWAP_SIGNATURE
+#define PGCM_INSTANTIATE_SWAP(D)                                    \
+    template __global__ void swap_kernel<D, 10> PGCM_SWAP_SIGNATURE; \
+    template __global__ void swap_kernel<D, 12> PGCM_SWAP_SIGNATURE; \
+    template __global__ void swap_kernel<D, 14> PGCM_SWAP_SIGNATURE
 PGCM_INSTANTIATE_SWAP(false);
 PGCM_INSTANTIATE_SWAP(true);
 #undef PGCM_SWAP_SIGNATURE
 #undef PGCM_INSTANTIATE_SWAP
+
+// ------------------------------------------------------------------------------------------
+// Short bursts in ONE launch: so few rows that the time of a call is that of its chain of dependent steps.
+// A workgroup of 4, 8 or 16 wavefronts makes one or more passes over 64, 128 or 256 blocks.
+//   * Of one pass, a wavefront takes sixteen blocks, a quad of lanes a block and a lane a column of its
+//     state: a round is four lookups in every lane, whose results go to the lanes beside it, where a lane
+//     with a block to itself makes sixteen (64 blocks, four wavefronts instead of one: 1.8 -> 1.3 us).  Of
+//     several passes it takes a row of 64 blocks, a lane a block: more steps, but fewer for each block
+//     (128 KiB... 2 MiB: eight rows a compute unit, 12.5 us in quads, 11.9 in rows).
+//   * The round tables are te[0] and te[1] alone, 32 times each, 64 KiB: te[2] and te[3] are these turned
+//     by two bytes.  Half the room to fill (0.8 us of 3.5), no lookups that collide (te[0..3] sixteen
+//     times each, as short transfers once had them, took twice the cycles), and two workgroups fit a
+//     compute unit.
+//   * What the tables are not needed for is asked for after they are in place: sixteen wavefronts' loads
+//     of keys and powers ahead of the last one's of the tables made that wait 1.2 us longer.
+//   * Sixteen wavefronts: the first three rows of a pass are multiplied by H^192, H^128, H^64 and added to
+//     the fourth, a word of a row a wavefront (eight lookups; 0.4 us, where a tree over the rows, a
+//     multiplication of 32 lookups a level, took 1.5 for four rows and 2.3 for eight); then the row's
+//     64 columns are multiplied with H^64 .. H^1 bit by bit (KeyTables::dot), a word a wavefront.  Fewer
+//     wavefronts: every lane multiplies its own word, by the power that takes its block to the end of the
+//     pass, and there is nothing to fold.
+//   * E_K(J0) is the keystream of "block -1" where there is a lane for it, otherwise a second block in
+//     every quad of one wavefront, its steps between the first one's.
+// A pass's sum is taken to the chunk's end with one more product (KeyTables::row_hop), four passes at
+// once.  Results of several workgroups are added up as in the kernel for units, see there.
+// Against that kernel, with units of a row and the round tables 64 or 128 KiB, per call back to back:
+// 1 byte encrypted 6.1 -> 5.2 us; 64 chunks of 4 KiB both ways 16.4 -> 13.8; 300 of 1 byte to 8 KiB, 70 %
+// of them ragged, decrypted 14.5 -> 12.5; one of 320 KiB encrypted 12.5 -> 11.4; one of 2 MiB decrypted
+// 13.7 -> 12.9; 512 of 8 KiB 25.8 -> 19.8.  (With three and four passes the two are level: 3 MiB 16.2 and
+// 16.0, 100 chunks of 20 KB 15.4 and 15.8.)
+namespace {
+
+struct QuadTables {
+    uint32_t te[256 * 64];  // 256 bytes a value: te[0] 32 times, te[1] 32 times
+    u32x4 keys[4][4];       // KeyTables::column_keys
+    Block long_aad[kWavesPerGroup];
+    GfWords shares[kBurstPasses][kWavesPerGroup];
+    Block mask;  // E_K(J0)
+};
+typedef Block FoldTables[3][kNibbleTableEntries];  // nibble tables of H^64, H^128, H^192
+template <BurstKind kKind>
+struct QuadLds : QuadTables {};
+template <>
+struct QuadLds<BurstKind::kFold> : QuadTables {
+    FoldTables fold;
+    Block rows[kFoldPasses][4 * kRowBlocks];  // what a pass's blocks add to the hash
+};
+template <>
+struct QuadLds<BurstKind::kFoldShared> : QuadTables {  // (its tables take the place of the round tables)
+    Block rows[kFoldPasses - 1][4 * kRowBlocks];
+};
+static_assert(2 * sizeof(QuadLds<BurstKind::kFoldShared>) <= 160 << 10 &&
+                  2 * sizeof(QuadLds<BurstKind::kWords>) <= 160 << 10,
+              "two workgroups on a compute unit");
+// The round tables, by 64 << kWavePower threads: an entry a thread and eight pieces of sixteen bytes, or,
+// of fewer threads, two entries each, of more, half the pieces.  Neighbours have different tables and
+// begin with different pieces, so that a wavefront's store covers all banks evenly.
+template <int kWavePower>
+struct QuadFill {
+    static constexpr uint32_t kEntries = kWavePower == 2 ? 2 : 1, kPieces = kWavePower == 4 ? 4 : 8;
+    uint32_t v[kEntries];
+
+    static __device__ __forceinline__ uint32_t entry(uint32_t tid) {
+        return kWavePower == 4 ? tid >> 2 : (tid >> 1) * kEntries;
+    }
+    __device__ __forceinline__ void fetch(const KeyTables* __restrict__ kt, uint32_t tid) {
+        const uint32_t* from = kt->te[tid & 1] + entry(tid);
+#pragma unroll
+        for (uint32_t e = 0; e < kEntries; ++e) v[e] = from[e];
+    }
+    __device__ __forceinline__ void store(uint32_t* te, uint32_t tid) const {
+        const uint32_t i = entry(tid), first = kWavePower == 4 ? (tid & 2) * 2 : 0;
+        u32x4* const te4 = reinterpret_cast<u32x4*>(te) + (tid & 1) * 8;
+#pragma unroll
+        for (uint32_t e = 0; e < kEntries; ++e) {
+            const u32x4 q = {v[e], v[e], v[e], v[e]};
+#pragma unroll
+            for (uint32_t k = 0; k < kPieces; ++k)
+                te4[(i + e) * 16 + ((first + k + i) & 7)] = q;
+        }
+    }
+};
+
+// this lane's column of every round key; the last one apart
+struct QuadKeys {
+    uint32_t k[14], last, rounds;
+};
+
+template <int kTurn>
+__device__ __forceinline__ uint32_t quad_turned(uint32_t v) {
+    constexpr int kPerm = kTurn == 1 ? 0x39 : kTurn == 2 ? 0x4E : 0x93;  // lane c has column c + kTurn
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kPerm, 0xF, 0xF, true);
+}
+// a lookup address: byte K of v in byte 1, byte 0 that of `lane_bytes`
+template <int K>
+__device__ __forceinline__ uint32_t quad_addr(uint32_t v, uint32_t lane_bytes) {
+    return __builtin_amdgcn_perm(v, lane_bytes, 0x0c0c0000u | (4u + K) << 8);
+}
+// x: a column of the counter block in every lane, and of the keystream block on return.  (With every lane
+// looking up its own column's bytes, and the results turned instead of the bytes, a round takes eight
+// vector instructions and not eleven, but 64 chunks of 4 KiB both ways 14.2 us and not 13.8.)
+template <int kBlocks>
+__device__ __forceinline__ void quad_encrypt(const QuadKeys& keys, uint32_t lane, uint32_t base,
+                                             uint32_t (&x)[kBlocks]) {
+    const uint32_t lane_bytes = (lane & 31) * 4;
+    uint32_t t[kBlocks][4];
+    auto lookups = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kBlocks; ++i) {
+            const uint32_t a0 = quad_addr<0>(x[i], lane_bytes),
+                           a1 = quad_addr<1>(quad_turned<1>(x[i]), lane_bytes),
+                           a2 = quad_addr<2>(quad_turned<2>(x[i]), lane_bytes),
+                           a3 = quad_addr<3>(quad_turned<3>(x[i]), lane_bytes);
+            t[i][2] = lds_read32(a2 + base);
+            t[i][3] = lds_read32(a3 + base + 128);
+            t[i][0] = lds_read32(a0 + base);
+            t[i][1] = lds_read32(a1 + base + 128);
+        }
+    };
+    auto round = [&](uint32_t key) __attribute__((always_inline)) {
+        lookups();
+#pragma unroll
+        for (int i = 0; i < kBlocks; ++i) {
+            const uint32_t turned = t[i][2] ^ t[i][3];
+            x[i] = xor3(t[i][0], t[i][1], key) ^ __builtin_amdgcn_alignbit(turned, turned, 16);
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < kBlocks; ++i) x[i] ^= keys.k[0];
+#pragma unroll
+    for (int r = 1; r < 10; ++r) round(keys.k[r]);
+    if (keys.rounds > 10) {
+        round(keys.k[10]), round(keys.k[11]);
+        if (keys.rounds > 12) round(keys.k[12]), round(keys.k[13]);
+    }
+    lookups();
+    // no MixColumns: S(x) is bytes 1 and 2 of te[0], 2 and 3 of te[1]
+#pragma unroll
+    for (int i = 0; i < kBlocks; ++i) {
+        const uint32_t lo = __builtin_amdgcn_perm(t[i][0], t[i][1], 0x0c0c0205u);
+        const uint32_t hi = __builtin_amdgcn_perm(t[i][2], t[i][3], 0x03060c0cu);
+        x[i] = xor3(lo, hi, keys.last);
+    }
+}
+
+// Where there is a lane for a block: the keys wait in the lanes of a register, fetched with everything
+// else a launch starts with, and one kernel serves every round count.  A wavefront being alone or nearly
+// alone on its SIMD, every column's lookups go out as soon as their four addresses are formed, and its
+// sum is formed while the later columns' are under way.
+struct TeHalf {
+    static constexpr uint32_t kPairs = 0, kLanes = 32;
+    static constexpr uint32_t offset(int t) { return 128u * (t & 1); }
+};
+// a.byte1 = near.byte[K] ^ far.byte[K + 2], every other byte of a kept
+template <int K>
+__device__ __forceinline__ void halves_into_addr(uint32_t& a, uint32_t near, uint32_t far) {
+    if constexpr (K == 0)
+        asm("v_xor_b32_sdwa %0, %1, %2 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_0 src1_sel:BYTE_2" : "+v"(a) : "v"(near), "v"(far));
+    else if constexpr (K == 1)
+        asm("v_xor_b32_sdwa %0, %1, %2 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_1 src1_sel:BYTE_3" : "+v"(a) : "v"(near), "v"(far));
+    else if constexpr (K == 2)
+        asm("v_xor_b32_sdwa %0, %1, %2 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_2 src1_sel:BYTE_0" : "+v"(a) : "v"(near), "v"(far));
+    else
+        asm("v_xor_b32_sdwa %0, %1, %2 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:BYTE_1" : "+v"(a) : "v"(near), "v"(far));
+}
+struct LaneKeys {
+    uint32_t word;    // lane i: round key word i
+    uint32_t rounds;
+};
+struct CtrBlock {
+    uint32_t iv0, iv1, iv2, ctr;
+};
+// in the place of a row hash: the row's blocks
+struct GhashNone {
+    uint32_t w[4];
+    __device__ __forceinline__ void begin() {}
+    __device__ __forceinline__ void absorb(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3) {
+        w[0] = c0, w[1] = c1, w[2] = c2, w[3] = c3;
+    }
+};
+template <int kRounds>
+__device__ __forceinline__ void aes_ctr_lds(const LaneKeys& keys, AesAddr& A, const CtrBlock& C,
+                                            GhashNone&, uint32_t base, uint32_t& o0, uint32_t& o1,
+                                            uint32_t& o2, uint32_t& o3) {
+    static_assert(kRounds == 0, "any round count");
+    using Te = TeHalf;
+    // a column between rounds is near ^ (far turned by two bytes), its key in `near`: nothing is turned, the
+    // bytes meet when the next addresses are formed
+    uint32_t near[4], far[4], t[4][4];
+    auto look_up = [&](int c) __attribute__((always_inline)) {
+        t[c][0] = te_read<Te, 0>(A.a[c][0], base);
+        t[c][1] = te_read<Te, 1>(A.a[(c + 1) & 3][1], base);
+        t[c][2] = te_read<Te, 2>(A.a[(c + 2) & 3][2], base);
+        t[c][3] = te_read<Te, 3>(A.a[(c + 3) & 3][3], base);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    {
+        const uint32_t u[4] = {C.iv0, C.iv1, C.iv2, bswap32(C.ctr)};
+        static_for<0, 4>([&](auto col) __attribute__((always_inline)) {
+            constexpr int c = decltype(col)::value;
+            const uint32_t k = __builtin_amdgcn_readlane(keys.word, c);
+            key_xor_into_addr<0, 0>(A.a[c][0], k, u[c]);
+            key_xor_into_addr<1, 1>(A.a[c][1], k, u[c]);
+            key_xor_into_addr<2, 2>(A.a[c][2], k, u[c]);
+            key_xor_into_addr<3, 3>(A.a[c][3], k, u[c]);
+        });
+#pragma unroll
+        for (int c = 0; c < 4; ++c) look_up(c);
+    }
+    // the sums of round r, and the lookups of the next
+    auto round = [&](uint32_t r) __attribute__((always_inline)) {
+        uint32_t k[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) k[c] = __builtin_amdgcn_readlane(keys.word, 4 * r + c);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            near[c] = xor3(t[c][0], t[c][1], k[c]);
+            far[c] = t[c][2] ^ t[c][3];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        static_for<0, 4>([&](auto col) __attribute__((always_inline)) {
+            constexpr int c = decltype(col)::value;
+            halves_into_addr<0>(A.a[c][0], near[c], far[c]);
+            halves_into_addr<1>(A.a[(c + 1) & 3][1], near[(c + 1) & 3], far[(c + 1) & 3]);
+            halves_into_addr<2>(A.a[(c + 2) & 3][2], near[(c + 2) & 3], far[(c + 2) & 3]);
+            halves_into_addr<3>(A.a[(c + 3) & 3][3], near[(c + 3) & 3], far[(c + 3) & 3]);
+            look_up(c);
+        });
+    };
+#pragma unroll
+    for (uint32_t r = 1; r < 10; ++r) round(r);
+    if (keys.rounds > 10) {
+        round(10), round(11);
+        if (keys.rounds > 12) round(12), round(13);
+    }
+    uint32_t u[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const uint32_t lo = __builtin_amdgcn_perm(t[c][0], t[c][1], 0x0c0c0205u);
+        const uint32_t hi = __builtin_amdgcn_perm(t[c][2], t[c][3], 0x03060c0cu);
+        u[c] = xor3(lo, hi, __builtin_amdgcn_readlane(keys.word, 4 * keys.rounds + c));
+    }
+    o0 = u[0], o1 = u[1], o2 = u[2], o3 = u[3];
+}
+
+// the n <= 4 bytes of a word at any alignment, put together only when they are used
+struct WordPieces {
+    uint32_t v4 = 0, v2 = 0, v1 = 0;
+    bool three = false;
+
+    __device__ __forceinline__ void read(const uint8_t* p, uint32_t n) {
+        if (n == 4) v4 = global_read_any<uint32_t>(p);
+        if (n & 2) v2 = global_read_any<uint16_t>(p);
+        if (n & 1) v1 = global_read8(p + (n & 2));
+        three = n == 3;
+    }
+    __device__ __forceinline__ uint32_t word() const { return v4 | v2 | (three ? v1 << 16 : v1); }
+};
+template <bool kThrough>
+__device__ __forceinline__ void write_word(uint8_t* p, uint32_t n, uint32_t v) {
+    if (n == 4) {
+        global_write_piece<kThrough>(p, v);
+    } else {
+        if (n & 2) global_write_piece<kThrough>(p, (uint16_t)v);
+        if (n & 1) global_write_piece<kThrough>(p + (n & 2), (uint8_t)((n & 2) ? v >> 16 : v));
+    }
+}
+// the sum over the lanes of (the four bytes of v, the first of them the lowest) * powers, in all lanes
+__device__ __forceinline__ GfWords bytes_dot(uint32_t v, const GfWords (&powers)[4]) {
+    GfWords sum{{0, 0, 0, 0}};
+    // (a loop: unrolled, its masks are made ahead of their use and take too many registers)
+#pragma unroll 1
+    for (int bit = 0; bit < 8; ++bit) {
+        gfw_mul_x(sum);
+#pragma unroll
+        for (uint32_t s = 0; s < 4; ++s) {
+            const uint32_t m = (uint32_t)((int32_t)(v << (31 - 8 * s)) >> 31);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sum.a[k] ^= powers[s].a[k] & m;
+        }
+        v >>= 1;
+    }
+    sum_over_lanes(sum.a);
+    return sum;
+}
+// (a word of a block) * C, from the eight nibble positions of that word at LDS address `table`
+__device__ __forceinline__ u32x4 word_times(uint32_t table, uint32_t v) {
+    const uint32_t f0 = 0xF0u, t = v << 4;
+    u32x4 e[8];
+    e[0] = lds_read128(table + nibble_offset<0>(v, f0));
+    e[1] = lds_read128(table + nibble_offset<0>(t, f0) + 256);
+    e[2] = lds_read128(table + nibble_offset<1>(v, f0) + 512);
+    e[3] = lds_read128(table + nibble_offset<1>(t, f0) + 768);
+    e[4] = lds_read128(table + nibble_offset<2>(v, f0) + 1024);
+    e[5] = lds_read128(table + nibble_offset<2>(t, f0) + 1280);
+    e[6] = lds_read128(table + nibble_offset<3>(v, f0) + 1536);
+    e[7] = lds_read128(table + nibble_offset<3>(t, f0) + 1792);
+    u32x4 z = e[0];
+#pragma unroll
+    for (int k = 1; k < 8; ++k) z ^= e[k];
+    return z;
+}
+// how many of the four bytes from `at` on lie before `end`
+__device__ __forceinline__ uint32_t word_bytes(uint64_t at, uint64_t end) {
+    return at + 4 <= end ? 4u : at < end ? (uint32_t)(end - at) : 0u;
+}
+
+}  // namespace
+
+template <bool kDecrypt, bool kLongIv, BurstKind kKind>
+__global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kGroupThreads,
+                             kKind == BurstKind::kFoldShared ? 8 : 4) void burst_kernel(
+    const KeyTables* __restrict__ kt, const uint8_t* __restrict__ ivs, uint32_t iv_len,
+    SwapMeta meta, ArriveSlot* __restrict__ slots, uint8_t* __restrict__ tags,
+    uint8_t* __restrict__ ok, const GroupDesc* __restrict__ staged, const ArgBatch batch) {
+    constexpr bool kFold = kKind != BurstKind::kWords;
+    __shared__ QuadLds<kKind> lds;
+    const uint32_t lds_base = lds_offset(&lds);
+    const uint32_t tid = threadIdx.x, lane = tid & 63, column = lane & 3;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t wave_power = kFold ? 4 : meta.wave_power(), nwaves = 1u << wave_power;
+    const uint32_t pass_power = 4 + wave_power, pass_blocks = 1u << pass_power;
+    const bool finisher = wave == nwaves - 1;
+
+    // Everything the workgroup needs from memory is asked for as early as it can be: a launch starts
+    // with cold caches, and every further round of dependent loads costs it a microsecond.
+    QuadFill<2> te2;
+    QuadFill<3> te3;
+    QuadFill<4> te4;
+    if constexpr (kFold) te4.fetch(kt, tid);
+    else if (wave_power == 3) te3.fetch(kt, tid);
+    else te2.fetch(kt, tid);
+    u32x4 column_keys{};
+    if (tid < 16) column_keys = reinterpret_cast<const u32x4*>(kt->column_keys)[tid];
+    const uint32_t key_word = lane < 60 ? kt->rk[lane] : 0u;  // lane i: round key word i
+
+    // this workgroup's chunk (see swap_kernel)
+    const bool alone = meta.nchunks() == 1, each = meta.one_group_each();
+    const bool iv_known = !kLongIv && staged == nullptr && meta.in_order() && (alone || each);
+    Block j{{0, 0, 0, 0}};
+    if (iv_known)
+        j = wave_j0<false>(kt, ivs + (uint64_t)(alone ? 0 : blockIdx.x) * iv_len, iv_len, lane);
+    ArgChunk cd;
+    uint32_t group_base, ngroups;
+    if (staged != nullptr) {
+        const GroupDesc d = staged[blockIdx.x];
+        cd = d.c, group_base = d.group_base, ngroups = d.ngroups;
+    } else {
+        uint32_t chunk = 0;
+        if (alone) {
+            group_base = 0, ngroups = meta.groups();
+        } else if (each) {
+            chunk = group_base = blockIdx.x, ngroups = 1;
+        } else {
+            const uint32_t first = lane < meta.nchunks() ? batch.group_base[lane] : ~0u;
+            chunk = __builtin_amdgcn_readfirstlane(
+                (uint32_t)__popcll(__ballot(first <= blockIdx.x)) - 1u);
+            group_base = batch.group_base[chunk];
+            ngroups = batch.group_base[chunk + 1] - group_base;
+        }
+        cd = batch.c[chunk];
+    }
+    if constexpr (kFold) te4.store(lds.te, tid);
+    else if (wave_power == 3) te3.store(lds.te, tid);
+    else te2.store(lds.te, tid);
+    if (tid < 16) lds.keys[tid / 4][tid % 4] = column_keys;
+    // What comes next is asked for only now: sixteen wavefronts' loads of it ahead of the last one's of the
+    // tables made that wait 1.2 us longer, and so did a descriptor or ragged payload waited for before.
+    asm volatile("" ::: "memory");
+    if (!iv_known) j = wave_j0<kLongIv>(kt, ivs + (uint64_t)cd.index * iv_len, iv_len, lane);
+
+    // its passes, counted back from the chunk's end: pass q of the workgroup is number `behind` + passes
+    // - 1 - q from there
+    const uint32_t g = blockIdx.x - group_base;
+    const int64_t nblk = (int64_t)((cd.len + 15) / 16);
+    const int64_t lead = swap_lead_blocks(cd.aad_len, true);
+    const uint32_t in_chunk = (uint32_t)((nblk + lead + pass_blocks - 1) >> pass_power);
+    const uint32_t passes = ngroups == 1 ? in_chunk : 1u << meta.unit_power();
+    const uint32_t behind = (ngroups - 1 - g) * passes;
+    const uint32_t have = in_chunk - behind < passes ? in_chunk - behind : passes;
+    const bool has_mask = g == 0;
+    // Several passes: a row a wavefront, a lane a block, which takes fewer instructions a block
+    const bool by_rows = kKind == BurstKind::kFold && nblk - ((int64_t)behind << pass_power) > pass_blocks;
+    // E_K(J0) is the keystream of "block -1", if that is in a pass of this workgroup (the AAD before it may
+    // have one of its own) with payload; otherwise it is made beside the first pass
+    const bool mask_apart =
+        has_mask && (nblk >= (int64_t)(behind + have) << pass_power ||
+                     nblk < (int64_t)behind << pass_power ||
+                     (!by_rows && have > 1 && nblk <= (int64_t)(behind + have - 1) << pass_power));
+
+    const AadBlocks aad = aad_blocks(cd.aad, cd.aad_len, lds.long_aad + wave);
+    // this lane's block in the pass number m from the end
+    auto block_of = [&](uint32_t m) __attribute__((always_inline)) {
+        return nblk - ((int64_t)(m + 1) << pass_power) + (int64_t)(16 * wave + (lane >> 2));
+    };
+    // ... and what it has of it: payload, a word of the AAD, or nothing
+    auto load_word = [&](int64_t blk) __attribute__((always_inline)) {
+        WordPieces v;
+        if (blk >= 0) {
+            const uint64_t at = (uint64_t)blk * 16 + 4 * column;
+            v.read(cd.src + at, word_bytes(at, cd.len));
+        } else if (blk >= -lead) {
+            if (aad.blocks <= kAadLaneBlocks) {
+                const uint32_t at = (aad.blocks + (uint32_t)(int32_t)blk) * 16 + 4 * column;
+                v.read(cd.aad + at, word_bytes(at, cd.aad_len));
+            } else {
+                v.v4 = lds_read32(aad.stand_in + 4 * column);  // block -1
+            }
+        }
+        return v;
+    };
+    if (aad.blocks > kAadLaneBlocks) {  // rare
+        bool mine = by_rows && wave < 4 * have;
+        for (uint32_t q = 0; !by_rows && q < have; ++q)
+            mine |= __ballot(block_of(behind + q) == -1) != 0;
+        if (mine && g == 0) {
+            AadBlocks a = aad;
+            a.prepare(kt->ghash[0]);
+        }
+    }
+    int64_t blk = have != 0 ? block_of(behind + have - 1) : -lead - 1;
+    WordPieces loaded;
+    RowPayload row{0, 0, 0, 0, 0, false};
+    bool row_edge = true;
+    if (by_rows) {
+        if (wave < 4 * have) {
+            blk = nblk - ((int64_t)(behind + have - wave / 4) << pass_power) + (wave & 3) * kRowBlocks + lane;
+            const int64_t first = same_in_all_lanes((uint64_t)(blk - lane));
+            row_edge = first < 0 || first + kRowBlocks == nblk;
+            row = load_row(cd.src, cd.len, blk, row_edge, aad);
+        }
+    } else {
+        loaded = load_word(blk);
+    }
+    Block extra{{0, 0, 0, 0}};     // what the workgroup with E_K(J0) adds to the tag
+    Block received{{0, 0, 0, 0}};  // the tag to compare with
+    GfWords hop{{0, 0, 0, 0}};     // in row r of sixteen lanes: the power of H for pass r
+    const bool hops = behind + have > 1;
+    uint8_t* const tag_at = tags + (uint64_t)cd.index * 16;
+    auto hop_of = [&](uint32_t q) __attribute__((always_inline)) {
+        const uint32_t m = q < have ? behind + have - 1 - q : 0;
+        return kt->row_hop[(m << pass_power) / kRowBlocks];
+    };
+    if (finisher) {
+        if (hops) hop = hop_of(lane >> 4);
+        if (has_mask) extra = length_block_entry(kt->ghash[0], cd.aad_len, cd.len, lane);
+        if (kDecrypt) received = global_read_block_any(tag_at);
+    }
+    // a word's four bytes: of the lane's own, or of a column of the pass when its rows are folded
+    GfWords powers[4];
+    auto fetch_powers = [&]() __attribute__((always_inline)) {
+        const GfWords* const from =
+            kFold ? kt->dot[kDotBlocks - kRowBlocks + lane] + 4 * (wave & 3)
+                  : kt->dot[kDotBlocks - pass_blocks + 16 * wave + (lane >> 2)] + 4 * column;
+        if (!kFold || wave < 4 * have)
+#pragma unroll
+            for (uint32_t s = 0; s < 4; ++s) powers[s] = from[s];
+    };
+    if constexpr (kKind != BurstKind::kFoldShared) fetch_powers();
+    u32x4 fold[2];
+    auto fetch_fold = [&]() __attribute__((always_inline)) {
+        fold[0] = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower])[tid];  // and the next power's
+        if (tid < kNibbleTableEntries) fold[1] = reinterpret_cast<const u32x4*>(kt->ghash_rows3)[tid];
+    };
+    if constexpr (kKind == BurstKind::kFold) fetch_fold();
+    __syncthreads();  // the tables are in place
+    QuadKeys keys;
+    keys.rounds = meta.rounds();
+    {
+        u32x4 k[4];
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) k[i] = lds.keys[column][i];
+#pragma unroll
+        for (uint32_t r = 0; r < 14; ++r) keys.k[r] = k[r / 4][r % 4];
+        keys.last = k[3].w;
+    }
+    Block(*fold_tables)[kNibbleTableEntries] = nullptr;
+    if constexpr (kKind == BurstKind::kFold) fold_tables = lds.fold;
+    if constexpr (kKind == BurstKind::kFoldShared)
+        fold_tables = reinterpret_cast<Block(*)[kNibbleTableEntries]>(lds.te);
+    auto store_fold = [&]() __attribute__((always_inline)) {
+        reinterpret_cast<u32x4*>(fold_tables)[tid] = fold[0];
+        if (tid < kNibbleTableEntries) reinterpret_cast<u32x4*>(fold_tables[2])[tid] = fold[1];
+    };
+    if constexpr (kKind == BurstKind::kFold) store_fold();
+
+    const uint32_t first_ctr = __builtin_amdgcn_readfirstlane(bswap32(j.w[3])) + 1u;
+    const uint32_t iv_word = column == 0 ? j.w[0] : column == 1 ? j.w[1] : j.w[2];
+    if constexpr (kKind == BurstKind::kFold) {
+        if (by_rows) {
+            if (wave < 4 * have) {
+                GhashNone G;
+                const CtrBlock C{j.w[0], j.w[1], j.w[2], (uint32_t)blk + first_ctr};
+                auto keep_mask = [&](uint32_t s0, uint32_t s1, uint32_t s2, uint32_t s3)
+                    __attribute__((always_inline)) {
+                        if (!mask_apart) lds.mask = Block{{s0, s1, s2, s3}};
+                    };
+                AesAddr A;
+                aes_addr_init<TeHalf>(A, lane);
+                bulk_row<kDecrypt, 0, kDecrypt>(LaneKeys{key_word, meta.rounds()}, A, C, row, cd.dst, blk,
+                                                row_edge, keep_mask, lds_base, G);
+                lds.rows[wave / 4][(wave & 3) * kRowBlocks + lane] = Block{{G.w[0], G.w[1], G.w[2], G.w[3]}};
+            }
+            if (mask_apart && wave == (have < kFoldPasses ? kWavesPerGroup - 1 : 0)) {
+                uint32_t y[1] = {j.w[0]};
+                y[0] = column == 3 ? j.w[3] : iv_word;
+                quad_encrypt<1>(keys, lane, lds_base, y);
+                if (lane < 4) lds.mask.w[lane] = y[0];
+            }
+        }
+    }
+    for (uint32_t q = 0; !by_rows && (q < have || (q == 0 && mask_apart)); ++q) {
+        uint32_t x[2] = {column == 3 ? bswap32((uint32_t)blk + first_ctr) : iv_word,
+                         column == 3 ? j.w[3] : iv_word};
+        const bool mask_here = q == 0 && mask_apart && wave == 0;
+        const bool mine = __ballot(blk >= (has_mask && !mask_apart ? -1 : 0)) != 0;
+        if (mask_here && mine) {
+            quad_encrypt<2>(keys, lane, lds_base, x);
+        } else if (mask_here || mine) {
+            uint32_t y[1] = {mine ? x[0] : x[1]};
+            quad_encrypt<1>(keys, lane, lds_base, y);
+            x[0] = x[1] = y[0];
+        }
+        if (mask_here && lane < 4) lds.mask.w[lane] = x[1];
+        if (has_mask && !mask_apart && blk == -1) lds.mask.w[column] = x[0];
+        const uint32_t word = loaded.word();
+        uint32_t hashed = word;  // the ciphertext, or the AAD
+        if (blk >= 0) {
+            const uint64_t at = (uint64_t)blk * 16 + 4 * column;
+            const uint32_t n = word_bytes(at, cd.len);
+            uint32_t out = word ^ x[0];
+            write_word<kDecrypt>(cd.dst + at, n, out);
+            // bytes past the end count as zero in the hash
+            if (!kDecrypt) hashed = n == 4 ? out : out & ((1u << (8 * n)) - 1u);
+        }
+        if (q + 1 < have) {
+            blk = block_of(behind + have - 2 - q);
+            loaded = load_word(blk);
+        }
+        if (q < have) {
+            if constexpr (kFold)
+                lds.rows[q][16 * wave + (lane >> 2)].w[column] = hashed;
+            else
+                lds.shares[q][wave] = bytes_dot(hashed, powers);
+        }
+    }
+    if constexpr (kFold) {
+        // the first three rows of every pass, a word a wavefront, times H^192, H^128, H^64, and added to
+        // the fourth
+        if constexpr (kKind == BurstKind::kFoldShared) {
+            fetch_fold();
+            asm volatile("" ::: "memory");
+            fetch_powers();  // no registers for them before
+        }
+        __syncthreads();
+        if constexpr (kKind == BurstKind::kFoldShared) {
+            store_fold();
+            __syncthreads();
+        }
+        for (uint32_t i = wave; i < 12 * have; i += kWavesPerGroup) {
+            const uint32_t q = i / 12, row = i % 12 / 4, w = i % 4;
+            const uint32_t v = lds.rows[q][row * kRowBlocks + lane].w[w];
+            u32x4 z = word_times(lds_offset(fold_tables[2 - row]) + w * 2048, v);
+            uint64_t* const to = reinterpret_cast<uint64_t*>(&lds.rows[q][3 * kRowBlocks + lane]);
+            __hip_atomic_fetch_xor(to, (uint64_t)z.x | (uint64_t)z.y << 32, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+            __hip_atomic_fetch_xor(to + 1, (uint64_t)z.z | (uint64_t)z.w << 32, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        __syncthreads();
+        if (wave < 4 * have)
+            lds.shares[wave / 4][wave % 4] =
+                bytes_dot(lds.rows[wave / 4][3 * kRowBlocks + lane].w[wave % 4], powers);
+    }
+    if (finisher) {
+        if (has_mask) {
+            sum_over_lanes(extra.w);
+        }
+        if (hops) spread_over_row(hop, lane);
+    }
+    // When decrypting, the wavefront that finishes the chunk may have to wipe plaintext that
+    // others (on other XCDs) wrote: their stores go through to memory, and must be there before
+    // the arrival is counted.
+    if (kDecrypt) wait_for_own_global_accesses();
+    __syncthreads();
+    if (!finisher) return;
+
+    GfWords sum{{0, 0, 0, 0}};
+    for (uint32_t q0 = 0; q0 < have; q0 += 4) {
+        const uint32_t q = q0 + (lane >> 4), w = lane & 15;
+        GfWords part{{0, 0, 0, 0}};
+        if (q < have && w < (kFold ? 4 : nwaves)) part = lds.shares[q][w];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) part.a[k] = row_summed(part.a[k]);
+        if (hops) {
+            if (q0 != 0) {
+                hop = hop_of(q);
+                spread_over_row(hop, lane);
+            }
+            part = times_spread(part, hop, lane);
+        }
+        sum_over_lanes<true>(part.a);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) sum.a[k] ^= part.a[k];
+    }
+    Block tag = gfw_to_block(sum);
+    if (has_mask) {
+        block_xor(tag, extra);
+        const Block m = lds.mask;
+        block_xor(tag, m);
+    }
+    if (ngroups > 1 && !last_of_chunk(slots + group_base, g, ngroups, tag, lane)) return;
+    write_or_compare_tag<kDecrypt>(tag, tag_at, received, ok + cd.index, cd.dst, cd.len, lane);
+}
+
+#define PGCM_INSTANTIATE_BURST(D, L, K)                                                              \
+    template __global__ void burst_kernel<D, L, BurstKind::K>(                                        \
+        const KeyTables*, const uint8_t*, uint32_t, SwapMeta, ArriveSlot*, uint8_t*, uint8_t*,        \
+        const GroupDesc*, ArgBatch)
+PGCM_INSTANTIATE_BURST(false, false, kWords);
+PGCM_INSTANTIATE_BURST(true, false, kWords);
+PGCM_INSTANTIATE_BURST(false, true, kWords);
+PGCM_INSTANTIATE_BURST(true, true, kWords);
+PGCM_INSTANTIATE_BURST(false, false, kFold);
+PGCM_INSTANTIATE_BURST(true, false, kFold);
+PGCM_INSTANTIATE_BURST(false, true, kFold);
+PGCM_INSTANTIATE_BURST(true, true, kFold);
+PGCM_INSTANTIATE_BURST(false, false, kFoldShared);
+PGCM_INSTANTIATE_BURST(true, false, kFoldShared);
+PGCM_INSTANTIATE_BURST(false, true, kFoldShared);
+PGCM_INSTANTIATE_BURST(true, true, kFoldShared);
+#undef PGCM_INSTANTIATE_BURST
 
 // ------------------------------------------------------------------------------------------
 // Batches of any number of chunks, and of any number of keys, in one launch: every wavefront walks a
@@ -2643,7 +3247,7 @@ __device__ __forceinline__ void walk_span(const KeyTables* __restrict__ kt, uint
             },
             y);
         row = stop;
-        GfWords sum = lanes_summed(kt->dot[lane], y);
+        GfWords sum = lanes_summed(kt->dot[kDotBlocks - kRowBlocks + lane], y);
         if (behind % kRowHopEntries != 0) {
             spread_over_row(hop, lane);
             sum = times_spread(sum, hop, lane);
@@ -2657,8 +3261,7 @@ __device__ __forceinline__ void walk_span(const KeyTables* __restrict__ kt, uint
         if (b0 < 0 && b1 >= 0) {
             // the piece with "block -1": the length block's product and E_K(J0)
             Block extra = length_block_entry(kt->ghash[0], PGCM_WORD(aad_len), PGCM_PAIR(len), lane);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) extra.w[k] = rows_summed(row_summed(extra.w[k]));
+            sum_over_lanes(extra.w);
             block_xor(tag, extra);
             const Block m = lds.mask[wave];
             block_xor(tag, m);
@@ -2726,7 +3329,8 @@ __global__ __launch_bounds__(kGroupThreads) void span_kernel(
         const uint32_t t = tid - kNibbleTableEntries;
         const uint8_t* const from =
             tid < kNibbleTableEntries ? reinterpret_cast<const uint8_t*>(&kt->ghash[kRowPower][tid])
-            : t < sizeof(kt->dot) / 128 ? reinterpret_cast<const uint8_t*>(kt->dot) + t * 128
+            : t < kRowBlocks * sizeof(kt->dot[0]) / 128
+                ? reinterpret_cast<const uint8_t*>(kt->dot[kDotBlocks - kRowBlocks]) + t * 128
                                         : reinterpret_cast<const uint8_t*>(kt->ghash[0]) + t % 64 * 128;
         gh = global_read128(from);
         key_word = lane < 60 ? kt->rk[lane] : lane == 60 ? kt->rounds : 0u;

@@ -58,9 +58,10 @@ constexpr uint32_t kNumLanePowers = 3;
 // The latency path sums a set's 64 lanes as 64 products of a sum with a known power of H, all
 // at once and bit by bit, and moves a workgroup's result to its place with one more such product:
 // it needs powers of H as plain values, held as four words with coefficient x^0 in the top bit of
-// the first (GfWords).  dot[l][t] = H^(65 - l) * x^(8 t), the multiplication by H that follows the
-// length block included;  hop[d][k] = H^(k 2^(8 + d)).
+// the first (GfWords).  dot[i][t] = H^(257 - i) * x^(8 t), the multiplication by H that follows
+// the length block included (a row of 64 blocks takes the last 64 of them);  hop[d][k] = H^(k 2^(8 + d)).
 constexpr uint32_t kDotSlices = 16;
+constexpr uint32_t kDotBlocks = 256;
 constexpr uint32_t kHopMinPower = 8;    // the shortest stretch of a workgroup: 4 units of 64 blocks
 constexpr uint32_t kHopPowers = 7;      // ... and the longest: 16 units of 1024 blocks
 constexpr uint32_t kHopEntries = 256;   // workgroups of a chunk
@@ -91,7 +92,10 @@ struct alignas(16) KeyTables {
     // ---- up to here the tables are part of what pgcm_copy_key_tables returns ----
     // multiplications by H^64 and by H^96 as the unit kernel's matrix operands
     uint32_t hash_image[kHashImages][kRowMatrixWords];
-    GfWords dot[64][kDotSlices];
+    Block ghash_rows3[kNibbleTableEntries];  // nibble table of H^192
+    // round key words by columns: [c][r] = rk[4 r + c], r < 14, and of the last round key [c][15]
+    uint32_t column_keys[4][16];
+    GfWords dot[kDotBlocks][kDotSlices];
     GfWords hop[kHopPowers][kHopEntries];
     GfWords row_hop[kRowHopEntries];
     GfWords far_hop[kFarHopEntries];
@@ -160,6 +164,10 @@ struct ArgBatch {
     uint32_t group_base[kArgChunks + 1];  // first workgroup of every chunk; their number
     ArgChunk c[kArgChunks];
 };
+// Passes a workgroup of the kernel for short bursts makes at most, and where chunks have several
+// workgroups.
+constexpr uint32_t kBurstPasses = 8;  // of up to eight wavefronts; of sixteen:
+constexpr uint32_t kFoldPassPower = 2, kFoldPasses = 1u << kFoldPassPower;
 // Workgroups of a chunk (KeyTables::hop has their distances) and of a launch.
 constexpr uint32_t kSwapChunkGroups = kHopEntries;
 constexpr uint32_t kSwapMaxGroups = 512;
@@ -198,7 +206,7 @@ constexpr SwapMeta swap_meta(uint32_t nchunks, uint32_t unit_power, uint32_t wav
                     (uint32_t)in_order << 16 | groups << 17 | rounds << 27};
 }
 // Batches of more chunks than fit the arguments have a descriptor per workgroup in pinned memory.
-struct alignas(16) GroupDesc {
+struct alignas(64) GroupDesc {   // one line of host memory
     ArgChunk c;
     uint32_t group_base, ngroups;  // the chunk's first workgroup and their number
 };
@@ -234,9 +242,9 @@ constexpr uint32_t kShortIvBytes = 16;
 constexpr uint32_t kSpanLdsParts = 31;
 
 // A batch whose chunks are all at most this long (the paper's non-swap transfers are usually < 8 KB,
-// section 4.2; eight rows of 64 blocks) goes to the one-launch kernel with small tables.
+// section 4.2; eight rows of 64 blocks) goes to the kernel for short bursts.
 constexpr uint64_t kSmallChunkBytes = 8192;
-// That kernel is there for the latency of a few transfers, a workgroup each; of more chunks than this
+// That kernel is there for the latency of a few transfers; of more chunks than this
 // (two workgroups per compute unit are resident) ...
 constexpr size_t kSmallMaxChunks = 512;
 // ... those of at most this length (63 blocks: one row together with "block -1") take a kernel with

@@ -1,0 +1,70 @@
+"""Batches that go to burst_kernel, at the edges of its shapes: the blocks of a wavefront, of a workgroup of
+four, eight and sixteen wavefronts and of two to four passes, with "block -1" in a pass, in one of its
+own and beside the first; chunks in one workgroup and in several; more chunks than compute units; AAD of
+every kind and IVs of other lengths — against the CPU oracle, bit for bit."""
+import numpy as np
+import pytest
+
+import workloads
+from test_gpu_parity import _full_parity
+
+pytestmark = pytest.mark.gpu
+
+KIB = 1024
+
+
+def _workload(name, lens, alens, key_bytes=32, iv_bytes=12):
+    rng = np.random.default_rng([workloads.BASE_SEED, 577, len(name), len(lens)])
+    n = len(lens)
+    lens = np.array(lens, np.uint64)
+    alens = np.resize(np.array(alens, np.int64), n)
+    offsets, total = workloads._layout(lens)
+    aad_off = np.zeros(n + 1, np.uint64)
+    aad_off[1:] = np.cumsum(alens)
+    ivs = (workloads.iv_sequence((1 << 61) + 5, n) if iv_bytes == 12 else
+           rng.integers(0, 256, (n, iv_bytes), dtype=np.uint8))
+    return workloads.Workload(name, 960, rng.integers(0, 256, key_bytes, dtype=np.uint8), ivs, lens,
+                              offsets, total, "u8",
+                              rng.integers(0, 256, int(alens.sum()), dtype=np.uint8), aad_off)
+
+
+# bytes around the blocks of 16, 64, 128, 256, 512, 768 blocks
+_EDGES = [16 * b + d for b in (16, 64, 128, 256) for d in (-17, -16, -1, 0, 1, 16)]
+_MORE = [16 * b + d for b in (256, 512, 768, 1024) for d in (-16, 0, 1)]
+
+SHAPES = {
+    # one chunk a call is by far the usual case: every edge by itself
+    **{"one_%d" % v: ([v], [0]) for v in (1, 16, 255, 256, 257, 1024, 2048, 4096, 8192)},
+    **{"one_aad_%d" % v: ([v], [16]) for v in (16, 1008, 1024, 2048, 4080, 4096)},
+    # the workgroup of the AAD's first blocks ends before "block -1", and with it
+    "aad_before": ([1023 * 16 - 12], [33]),
+    "aad_with_last": ([1024 * 16], [33]),
+    "short": ([0, 1] + _EDGES, [0]),
+    "short_aad": ([0, 1] + _EDGES, [16, 0, 5, 64, 17, 1, 48]),
+    # the AAD fills lanes, a pass, and is longer than goes in lanes
+    "long_aad": ([0, 5, 1024, 4096, 4097, 8192], [1008, 1024, 1025, 16, 3000, 1024]),
+    # workgroups of 1, 2 and 4 passes, some of them short
+    "two": ([300 * KIB, 8 * KIB + 16, 9000, 1], [0, 16, 70]),
+    "passes_1": (_MORE + [200 * KIB], [0, 16]),
+    "passes_2": ([v + 40 * 4096 for v in _MORE], [16, 0, 33]),
+    "passes_4": ([v + 60 * 4096 for v in _MORE], [0, 0, 20]),
+    # more chunks than compute units: mixed, and all of much the same length
+    "many_mixed": ([(37 * i * i) % 8192 + 1 for i in range(40)] + [20] * 260, [0, 9]),
+    "many_even": ([4096 + 16 * (i % 3) for i in range(300)], [0, 16]),
+    "many_long": ([8192 - i % 20 for i in range(270)], [0, 64]),
+}
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_shapes(shape):
+    lens, alens = SHAPES[shape]
+    w = _workload(shape, lens, alens)
+    flips = [(i, 3, 1, "tag") for i in {0, w.n // 2}] if w.n > 1 else []
+    _full_parity(w, flip=flips)
+
+
+@pytest.mark.parametrize("key_bytes,iv_bytes", [(16, 12), (24, 16), (32, 8), (16, 40), (32, 1040)])
+@pytest.mark.parametrize("shape", ["short_aad", "passes_1", "passes_4", "many_even"])
+def test_other_keys_and_ivs(shape, key_bytes, iv_bytes):
+    lens, alens = SHAPES[shape]
+    _full_parity(_workload(shape, lens[:40] if shape != "many_even" else lens, alens, key_bytes, iv_bytes))
