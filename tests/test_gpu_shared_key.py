@@ -119,6 +119,39 @@ def test_many_streams_share_and_rebind_contexts():
     key.free()
 
 
+def test_streams_come_and_go_beside_settled_ones():
+    """streams that have used the key for long leave no mark at the end of their batches: more streams
+    than there are contexts come and go beside them, and all results stay exact"""
+    w = workloads.mini(2)
+    host = w.payload_host()
+    key = pgcm.expand_key(w.key)
+    cts, tags = _oracle_results(w, host)
+    streams = [torch.cuda.Stream() for _ in range(27)]
+    settled = streams[:3]
+    batches = [DeviceBatch(w, torch.from_numpy(host).cuda()) for _ in range(6)]
+
+    def check(what):
+        torch.cuda.synchronize()
+        for k, b in enumerate(batches):
+            cipher = b.cipher.cpu().numpy()
+            for i in range(w.n):
+                assert np.array_equal(w.chunk(cipher, i), cts[i]), (what, k, i)
+            assert np.array_equal(b.tags.cpu().numpy().reshape(-1, 16), tags), (what, k)
+            b.cipher.zero_()
+            b.tags.zero_()
+        torch.cuda.synchronize()
+
+    for turn in range(2):
+        for _ in range(40):
+            for st, b in zip(settled, batches):
+                b.encrypt(key, stream=st)
+        for r in range(0, 24, 3):
+            for st, b in zip(streams[3 + r:6 + r] + settled, batches[3:] + batches[:3]):
+                b.encrypt(key, stream=st)
+            check((turn, r))
+    key.free()
+
+
 def test_reserve_then_batches_do_not_allocate():
     w = workloads.mini(3)                      # three 2 MiB chunks
     host = w.payload_host()
