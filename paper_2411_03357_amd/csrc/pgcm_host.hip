@@ -135,7 +135,7 @@ struct Context {
     size_t work_cap = 0;
     uint32_t* counter_at = nullptr;  // where the unit counter was last known to be zero
     bool counter_dirty = true;
-    size_t clean_slots = 0;  // so many ArriveSlots at the start of `work` have counts of zero
+    size_t clean_slots = 0;  // so many ArriveSlots at the start of `work` are zero
     // A batch of its was captured into a graph, whose replays may come between any two other batches:
     // nothing is taken for clean from one batch to the next any more, the context keeps its stream,
     // and what a replay reads or writes is kept until the key is freed.
@@ -732,7 +732,7 @@ int run_small_batch(pgcm_key* key, Context* ctx, const BatchArgs& a) {
 // Workspace of the one-launch path: a slot per workgroup.
 constexpr size_t kSwapWorkBytes = sizeof(ArriveSlot) * kSwapMaxGroups;
 
-// Makes the counts of the first n slots of the workspace zero.  Every batch leaves them zero; they
+// Makes the first n slots of the workspace zero.  Every batch leaves them zero; they
 // need clearing when the workspace is new, was used by a batch with units, or is shared between
 // keys, and in a graph, before whose replays any of that may happen, as well as wherever a replay may
 // have come in between.
@@ -1190,7 +1190,7 @@ int run_batch(pgcm_key* key, BatchArgs a) {
 }
 
 // The parts of several keys as one batch in spans, in a context of the first part's key.  (Nothing that
-// is derived from the other keys outlives the batch in there: the kernel wipes what it puts down.)
+// is derived from the other keys outlives the batch in there: the kernel leaves its slots zero.)
 int run_span_parts(BatchArgs a, KeyPart* parts, size_t nparts) {
     int rc = note_capture(a);
     if (rc != PGCM_OK) return rc;

@@ -171,15 +171,16 @@ constexpr uint32_t kFoldPassPower = 2, kFoldPasses = 1u << kFoldPassPower;
 // Workgroups of a chunk (KeyTables::hop has their distances) and of a launch.
 constexpr uint32_t kSwapChunkGroups = kHopEntries;
 constexpr uint32_t kSwapMaxGroups = 512;
-// A workgroup's result and, in the slot of a chunk's first workgroup, the number of those that have
-// arrived; of a chunk with many, they are counted in sixteens first, in the slot of every sixteenth.
-// The counts are zero between batches.
+// Where the workgroups of a chunk add up their shares of its tag, a word each by one atomic that counts
+// them in as well: a chunk has as many slots as workgroups and uses the first one's, and those of more
+// than kArriveSet add up in sets of so many first, in the slot of the first of each.  All zero between
+// batches.
+constexpr uint32_t kArriveSet = 32;  // bits of half an accumulator, and as many sets at most
 struct alignas(64) ArriveSlot {
-    uint32_t arrived, arrived_of_sixteen;
-    uint32_t pad_[2];
-    Block sum;
-    uint32_t pad2_[8];
+    uint64_t of_chunk[4];  // in the second slot: decryption's verdict
+    uint64_t of_set[4];
 };
+static_assert(kSwapChunkGroups <= kArriveSet * kArriveSet, "a bit for every set");
 static_assert(sizeof(ArriveSlot) == 64, "counters of different chunks are not to share a cache line");
 // What a workgroup has to know first, in one word: it travels in a register.
 struct SwapMeta {
