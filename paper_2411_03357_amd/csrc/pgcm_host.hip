@@ -753,7 +753,8 @@ void use_slots(Context* ctx, size_t n, hipStream_t stream, bool capturing) {
 struct SwapShape {
     bool burst;                               // burst_kernel
     bool alone;                               // every chunk has one workgroup
-    uint32_t unit_power, wave_power, groups;  // burst: log2 of a workgroup's passes for unit_power
+    // burst: a workgroup's passes for unit_power, and what a chunk's first workgroup may have beyond them
+    uint32_t unit_power, wave_power, groups, spare;
 };
 
 inline uint32_t swap_groups(const BatchArgs& a, size_t i, uint32_t unit_power, uint32_t wave_power) {
@@ -764,21 +765,25 @@ inline uint32_t swap_groups(const BatchArgs& a, size_t i, uint32_t unit_power, u
     return groups == 0 ? 1 : (uint32_t)groups;
 }
 
-// burst_kernel: what a chunk's passes cover, and its workgroups if they make 2^pass_power passes each
+// burst_kernel: what a chunk's passes cover, and its workgroups if they make so many passes each, the
+// first of them up to `spare` more
 inline uint64_t burst_blocks(const BatchArgs& a, size_t i) {
     return (a.len[i] + 15) / 16 + swap_lead_blocks(a.aad_len ? a.aad_len[i] : 0, true);
 }
-inline uint64_t burst_groups(uint64_t blocks, uint32_t wave_power, uint32_t pass_power) {
-    const uint32_t shift = 4 + wave_power + pass_power;
-    const uint64_t groups = (blocks + ((uint64_t)1 << shift) - 1) >> shift;
-    return groups == 0 ? 1 : groups;
+inline uint64_t burst_groups(uint64_t blocks, uint32_t wave_power, uint32_t passes, uint32_t spare) {
+    const uint32_t shift = 4 + wave_power;
+    const uint64_t of_chunk = (blocks + ((uint64_t)1 << shift) - 1) >> shift;
+    return of_chunk <= passes + spare ? 1 : (of_chunk - spare + passes - 1) / passes;
 }
 
 // Batches of short chunks, and others of at most four passes for every compute unit, go to burst_kernel.
 // As long as there is a compute unit for every short chunk, a workgroup takes a whole one, with no
 // more wavefronts than it has blocks for; of more chunks, workgroups of at most eight wavefronts share
 // a compute unit, and the longer chunks take several.  Longer chunks are spread over as many
-// workgroups of sixteen as there are compute units.
+// workgroups of sixteen as there are compute units, with the fewest passes that go: first with none spare,
+// then with one for the first workgroup of each chunk, which is what a few blocks too many take (2 MiB
+// with AAD in 257 workgroups of two passes: 256 take 11.8 us, four passes in 129 took 14.8; 8 of
+// 256 KiB with AAD 12.3, were 14.7), then with one more (2.3 to 3 MB in three 12.1, in four 14.2).
 // What is left: the smallest unit with which the batch fits the compute units, a workgroup each, at
 // sixteen wavefronts, then the fewest wavefronts a workgroup with which it still does.
 bool swap_shape(const pgcm_key* key, const BatchArgs& a, bool all_small, SwapShape* shape) {
@@ -802,20 +807,20 @@ bool swap_shape(const pgcm_key* key, const BatchArgs& a, bool all_small, SwapSha
         blocks[k] = burst_blocks(a, a.at(k));
         if (blocks[k] > most_blocks) most_blocks = blocks[k];
     }
-    auto bursts = [&](uint32_t wave_power, uint32_t pass_power) {
+    auto bursts = [&](uint32_t wave_power, uint32_t passes, uint32_t spare) {
         uint64_t sum = 0;
-        for (size_t k = 0; k < a.n; ++k) sum += burst_groups(blocks[k], wave_power, pass_power);
+        for (size_t k = 0; k < a.n; ++k) sum += burst_groups(blocks[k], wave_power, passes, spare);
         return sum;
     };
     if (all_small) {
         while (wp < 4 && most_blocks > (uint64_t)16 << wp) ++wp;
-        uint32_t pp = 2;
+        uint32_t passes = kFoldPasses;
         total = a.n;
-        if (a.n > num_cu && wp > 2 && bursts(3, 0) <= kSwapMaxGroups) {
-            wp = 3, pp = 0;
-            total = bursts(wp, pp);
+        if (a.n > num_cu && wp > 2 && bursts(3, 1, 0) <= kSwapMaxGroups) {
+            wp = 3, passes = 1;
+            total = bursts(wp, passes, 0);
         }
-        *shape = SwapShape{true, total == a.n, pp, wp, (uint32_t)total};
+        *shape = SwapShape{true, total == a.n, passes, wp, (uint32_t)total, 0};
         return true;
     } else {
         const uint32_t most = num_cu < kSwapChunkGroups ? num_cu : kSwapChunkGroups;
@@ -825,11 +830,12 @@ bool swap_shape(const pgcm_key* key, const BatchArgs& a, bool all_small, SwapSha
         if (bytes > (uint64_t)most * kWavesPerGroup * kUnitBytes) return false;
         const uint32_t forced = key->forced_unit_power;
         if (forced <= kMinUnitPower)
-            for (uint32_t pp = 0; pp <= kFoldPassPower; ++pp)
-                if ((total = bursts(4, pp)) <= most) {
-                    *shape = SwapShape{true, total == a.n, pp, 4, (uint32_t)total};
-                    return true;
-                }
+            for (uint32_t passes = 1; passes <= kFoldPasses; ++passes)
+                for (uint32_t spare = 0; spare <= (passes < kFoldPasses ? 1u : 0u); ++spare)
+                    if ((total = bursts(4, passes, spare)) <= most) {
+                        *shape = SwapShape{true, total == a.n, passes, 4, (uint32_t)total, spare};
+                        return true;
+                    }
         if (forced) up = forced;
         if (up > kUnitPower) return false;
         wp = 4;
@@ -844,7 +850,7 @@ bool swap_shape(const pgcm_key* key, const BatchArgs& a, bool all_small, SwapSha
             --wp, total = t, longest = l;
         }
     }
-    *shape = SwapShape{false, longest <= 1, up, wp, (uint32_t)total};
+    *shape = SwapShape{false, longest <= 1, up, wp, (uint32_t)total, 0};
     return true;
 }
 
@@ -902,7 +908,8 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapSh
         c.index = (uint32_t)i;
         const uint32_t of_chunk =
             !shape.burst ? swap_groups(a, i, shape.unit_power, shape.wave_power)
-            : shape.alone ? 1 : (uint32_t)burst_groups(burst_blocks(a, i), shape.wave_power, shape.unit_power);
+            : shape.alone ? 1 : (uint32_t)burst_groups(burst_blocks(a, i), shape.wave_power, shape.unit_power,
+                                             shape.spare);
         if (in_args) {
             batch.c[k] = c;
             batch.group_base[k] = groups;

@@ -32,8 +32,8 @@ __global__ void swap_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t iv
                             ArgBatch batch);
 
 // The same for batches whose time is that of one chain of steps: 2^wave_power wavefronts of sixteen blocks
-// a workgroup, which makes 2^meta.unit_power() passes, or, where a chunk has one workgroup, as many as
-// it takes (at most kBurstPasses).  It serves any key.  kLongIv: iv_len exceeds kShortIvBytes.
+// a workgroup, which makes meta.unit_power() passes, or, if it is a chunk's first, as many as are left
+// (at most kBurstPasses).  It serves any key.  kLongIv: iv_len exceeds kShortIvBytes.
 // kWords: at most eight wavefronts.  kFold: sixteen, and at most kFoldPasses passes; kFoldShared: the
 // same, one pass less, and two workgroups fit a compute unit.
 enum class BurstKind { kWords, kFold, kFoldShared };

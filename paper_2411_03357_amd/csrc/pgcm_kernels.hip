@@ -2883,15 +2883,15 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     asm volatile("" ::: "memory");
     if (!iv_known) j = wave_j0<kLongIv>(kt, ivs + (uint64_t)cd.index * iv_len, iv_len, lane);
 
-    // its passes, counted back from the chunk's end: pass q of the workgroup is number `behind` + passes
-    // - 1 - q from there
+    // its passes, counted back from the chunk's end: pass q of the workgroup is number `behind` + have
+    // - 1 - q from there; the chunk's first workgroup has what is left (burst_groups)
     const uint32_t g = blockIdx.x - group_base;
     const int64_t nblk = (int64_t)((cd.len + 15) / 16);
     const int64_t lead = swap_lead_blocks(cd.aad_len, true);
     const uint32_t in_chunk = (uint32_t)((nblk + lead + pass_blocks - 1) >> pass_power);
-    const uint32_t passes = ngroups == 1 ? in_chunk : 1u << meta.unit_power();
+    const uint32_t passes = ngroups == 1 ? in_chunk : meta.unit_power();
     const uint32_t behind = (ngroups - 1 - g) * passes;
-    const uint32_t have = in_chunk - behind < passes ? in_chunk - behind : passes;
+    const uint32_t have = g == 0 ? in_chunk - behind : passes;
     const bool has_mask = g == 0;
     // Several passes: a row a wavefront, a lane a block, which takes fewer instructions a block
     const bool by_rows = kKind == BurstKind::kFold && nblk - ((int64_t)behind << pass_power) > pass_blocks;

@@ -167,7 +167,7 @@ struct ArgBatch {
 // Passes a workgroup of the kernel for short bursts makes at most, and where chunks have several
 // workgroups.
 constexpr uint32_t kBurstPasses = 8;  // of up to eight wavefronts; of sixteen:
-constexpr uint32_t kFoldPassPower = 2, kFoldPasses = 1u << kFoldPassPower;
+constexpr uint32_t kFoldPasses = 4;
 // Workgroups of a chunk (KeyTables::hop has their distances) and of a launch.
 constexpr uint32_t kSwapChunkGroups = kHopEntries;
 constexpr uint32_t kSwapMaxGroups = 512;
@@ -191,7 +191,7 @@ struct SwapMeta {
 #define PGCM_BOTH
 #endif
     PGCM_BOTH uint32_t nchunks() const { return w & 0x7Fu; }          // in the arguments: 0 .. 64
-    PGCM_BOTH uint32_t unit_power() const { return (w >> 7) & 0x1Fu; }
+    PGCM_BOTH uint32_t unit_power() const { return (w >> 7) & 0x1Fu; }  // burst_kernel: the passes
     PGCM_BOTH uint32_t wave_power() const { return (w >> 12) & 7u; }  // log2 of the wavefronts per
                                                                       // workgroup: 2, 3, 4
     PGCM_BOTH bool one_group_each() const { return (w >> 15) & 1u; }  // every chunk has a workgroup

@@ -48,6 +48,15 @@ SHAPES = {
     "passes_1": (_MORE + [200 * KIB], [0, 16]),
     "passes_2": ([v + 40 * 4096 for v in _MORE], [16, 0, 33]),
     "passes_4": ([v + 60 * 4096 for v in _MORE], [0, 0, 20]),
+    # three passes, and chunks whose first workgroup makes one more than the others: of AAD alone, with
+    # payload, and of a short last chunk
+    "passes_3": ([600 * 4096 - 5], [0]),
+    "spare_1": ([256 * 4096], [16]),
+    "spare_1_payload": ([256 * 4096 + 100], [0]),
+    "spare_1_long_aad": ([256 * 4096 - 16], [3000]),
+    "spare_2": ([512 * 4096 - 48 * 16], [1008]),
+    "spare_3": ([768 * 4096 + 4095], [0]),
+    "spare_of_some": ([64 * 4096] * 7 + [63 * 4096 + 1, 5], [16, 0, 40]),
     # more chunks than compute units: mixed, and all of much the same length
     "many_mixed": ([(37 * i * i) % 8192 + 1 for i in range(40)] + [20] * 260, [0, 9]),
     "many_even": ([4096 + 16 * (i % 3) for i in range(300)], [0, 16]),
