@@ -776,7 +776,7 @@ inline uint64_t burst_groups(uint64_t blocks, uint32_t wave_power, uint32_t pass
     return of_chunk <= passes + spare ? 1 : (of_chunk - spare + passes - 1) / passes;
 }
 
-// Batches of short chunks, and others of at most four passes for every compute unit, go to burst_kernel.
+// Batches of short chunks, and others of at most sixteen passes for every compute unit, go to burst_kernel.
 // As long as there is a compute unit for every short chunk, a workgroup takes a whole one, with no
 // more wavefronts than it has blocks for; of more chunks, workgroups of at most eight wavefronts share
 // a compute unit, and the longer chunks take several.  Longer chunks are spread over as many
@@ -830,8 +830,8 @@ bool swap_shape(const pgcm_key* key, const BatchArgs& a, bool all_small, SwapSha
         if (bytes > (uint64_t)most * kWavesPerGroup * kUnitBytes) return false;
         const uint32_t forced = key->forced_unit_power;
         if (forced <= kMinUnitPower)
-            for (uint32_t passes = 1; passes <= kFoldPasses; ++passes)
-                for (uint32_t spare = 0; spare <= (passes < kFoldPasses ? 1u : 0u); ++spare)
+            for (uint32_t passes = 1; passes <= kSweptPasses; ++passes)
+                for (uint32_t spare = 0; spare <= (passes < kSweptPasses ? 1u : 0u); ++spare)
                     if ((total = bursts(4, passes, spare)) <= most) {
                         *shape = SwapShape{true, total == a.n, passes, 4, (uint32_t)total, spare};
                         return true;

@@ -1995,7 +1995,7 @@ template __global__ void final_kernel<true>(const KeyTables*, const ChunkDesc*, 
 // A few chunks in ONE launch (the paper's swaps come a few chunks at a time, section 5.1): here
 // the length of the chain of dependent steps counts as much as the work.  Descriptors are kernel
 // arguments, or, for more chunks than fit those, one per workgroup in pinned memory.  Every
-// wavefront walks one unit of two to sixteen rows (fewer rows go to burst_kernel); workgroups have as
+// wavefront walks one unit of two to sixteen rows (up to four go to burst_kernel); workgroups have as
 // few wavefronts, at least four, as there are compute units for (a row takes a lone wavefront 2.6 us,
 // sixteen on one compute unit 4.3 us).  Then
 //   1. the workgroup folds its units' sets into one as a tree in LDS (two to four multiplications
@@ -2138,7 +2138,9 @@ template <bool kDecrypt>
 __device__ __forceinline__ bool last_of_chunk(ArriveSlot* slots, uint32_t g, uint32_t n, Block& tag,
                                               uint8_t* __restrict__ tag_at, const Block& received,
                                               uint32_t lane) {
-    uint32_t word = lane == 0 ? tag.w[0] : lane == 1 ? tag.w[1] : lane == 2 ? tag.w[2] : tag.w[3];
+    uint32_t t0 = tag.w[0], t1 = tag.w[1], t2 = tag.w[2], t3 = tag.w[3];
+    asm volatile("" : "+v"(t0), "+v"(t1), "+v"(t2), "+v"(t3));  // (chosen from as an array, they go by way of memory)
+    uint32_t word = lane == 0 ? t0 : lane == 1 ? t1 : lane == 2 ? t2 : t3;
     bool whole = lane < 4;
     uint32_t member = g, of = n;
     if (n > kArriveSet) {
@@ -2535,13 +2537,13 @@ PGCM_INSTANTIATE_SWAP(true);
 //     pass, and there is nothing to fold.
 //   * E_K(J0) is the keystream of "block -1" where there is a lane for it, otherwise a second block in
 //     every quad of one wavefront, its steps between the first one's.
-// A pass's sum is taken to the chunk's end with one more product (KeyTables::row_hop), four passes at
-// once.  Results of several workgroups are added up as in the kernel for units, see there.
+// A pass's sum is taken to the chunk's end with one more product (KeyTables::row_hop; past 4 MiB, one
+// with far_hop as well), four passes at once.  Results of several workgroups are added up as in the kernel for units, see there.
 // Against that kernel, with units of a row and the round tables 64 or 128 KiB, per call back to back:
 // 1 byte encrypted 6.1 -> 5.2 us; 64 chunks of 4 KiB both ways 16.4 -> 13.8; 300 of 1 byte to 8 KiB, 70 %
 // of them ragged, decrypted 14.5 -> 12.5; one of 320 KiB encrypted 12.5 -> 11.4; one of 2 MiB decrypted
-// 13.7 -> 12.9; 512 of 8 KiB 25.8 -> 19.8.  (With three and four passes the two are level: 3 MiB 16.2 and
-// 16.0, 100 chunks of 20 KB 15.4 and 15.8.)
+// 13.7 -> 12.9; 512 of 8 KiB 25.8 -> 19.8.  With what came later (an event less, shares added up by
+// atomics, any number of passes): 1 byte 5.2, 320 KiB 8.2, 2 MiB 10.1, 100 chunks of 20 KB 13.3 (were 15.4).
 namespace {
 
 struct QuadTables {
@@ -2557,6 +2559,7 @@ struct QuadLds : QuadTables {};
 template <>
 struct QuadLds<BurstKind::kFold> : QuadTables {
     FoldTables fold;
+    Block sweep[kNibbleTableEntries];  // H^1024's
     Block rows[kFoldPasses][4 * kRowBlocks];  // what a pass's blocks add to the hash
 };
 template <>
@@ -2892,6 +2895,12 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     const uint32_t passes = ngroups == 1 ? in_chunk : meta.unit_power();
     const uint32_t behind = (ngroups - 1 - g) * passes;
     const uint32_t have = g == 0 ? in_chunk - behind : passes;
+    // More passes than kFoldPasses are made in sweeps of so many, the last of them at the end, and the
+    // sweeps' rows moved along and added up: what follows them knows kFoldPasses passes.  A sweep takes
+    // 4.5 us (4 MiB 15 us, 6 MB 18.9, 8 MiB decrypted 22, 12 MB 25.9; in units of swap_kernel 21.7 for
+    // the first two, 29.3, 30.8, and 30.9 for 16 MB, where four sweeps take as long).
+    const uint32_t sweeps = kKind == BurstKind::kFold ? (have + kFoldPasses - 1) / kFoldPasses : 1;
+    const uint32_t folded = sweeps > 1 ? kFoldPasses : have;
     const bool has_mask = g == 0;
     // Several passes: a row a wavefront, a lane a block, which takes fewer instructions a block
     const bool by_rows = kKind == BurstKind::kFold && nblk - ((int64_t)behind << pass_power) > pass_blocks;
@@ -2924,7 +2933,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
         return v;
     };
     if (aad.blocks > kAadLaneBlocks) {  // rare
-        bool mine = by_rows && wave < 4 * have;
+        bool mine = by_rows && wave < 4 * folded;
         for (uint32_t q = 0; !by_rows && q < have; ++q)
             mine |= __ballot(block_of(behind + q) == -1) != 0;
         if (mine && g == 0) {
@@ -2936,25 +2945,35 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     WordPieces loaded;
     RowPayload row{0, 0, 0, 0, 0, false};
     bool row_edge = true;
-    if (by_rows) {
-        if (wave < 4 * have) {
-            blk = nblk - ((int64_t)(behind + have - wave / 4) << pass_power) + (wave & 3) * kRowBlocks + lane;
+    // this wavefront's row of a sweep, if it has one: of the first sweep's passes some may be missing
+    auto has_row = [&](uint32_t sweep) __attribute__((always_inline)) {
+        return wave < 4 * folded && (sweep > 0 || wave / 4 >= sweeps * folded - have);
+    };
+    auto fetch_row = [&](uint32_t sweep) __attribute__((always_inline)) {
+        if (has_row(sweep)) {
+            const uint32_t m1 = behind + folded - wave / 4 + kFoldPasses * (sweeps - 1 - sweep);
+            blk = nblk - ((int64_t)m1 << pass_power) + (wave & 3) * kRowBlocks + lane;
             const int64_t first = same_in_all_lanes((uint64_t)(blk - lane));
             row_edge = first < 0 || first + kRowBlocks == nblk;
             row = load_row(cd.src, cd.len, blk, row_edge, aad);
         }
+    };
+    if (by_rows) {
+        fetch_row(0);
     } else {
         loaded = load_word(blk);
     }
     Block extra{{0, 0, 0, 0}};     // what the workgroup with E_K(J0) adds to the tag
     Block received{{0, 0, 0, 0}};  // the tag to compare with
     GfWords hop{{0, 0, 0, 0}};     // in row r of sixteen lanes: the power of H for pass r
-    const bool hops = behind + have > 1;
+    const bool hops = behind + folded > 1;
     uint8_t* const tag_at = tags + (uint64_t)cd.index * 16;
     auto hop_of = [&](uint32_t q) __attribute__((always_inline)) {
-        const uint32_t m = q < have ? behind + have - 1 - q : 0;
-        return kt->row_hop[(m << pass_power) / kRowBlocks];
+        const uint32_t m = q < folded ? behind + folded - 1 - q : 0;
+        return kt->row_hop[((m << pass_power) / kRowBlocks) % kRowHopEntries];
     };
+    // ... times this one, if there is a pass so far from the chunk's end
+    const bool far = kKind == BurstKind::kFold && (behind + folded - 1) << pass_power >= kRowHopEntries * kRowBlocks;
     if (finisher) {
         if (hops) hop = hop_of(lane >> 4);
         if (has_mask) extra = length_block_entry(kt->ghash[0], cd.aad_len, cd.len, lane);
@@ -2966,15 +2985,17 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
         const GfWords* const from =
             kFold ? kt->dot[kDotBlocks - kRowBlocks + lane] + 4 * (wave & 3)
                   : kt->dot[kDotBlocks - pass_blocks + 16 * wave + (lane >> 2)] + 4 * column;
-        if (!kFold || wave < 4 * have)
+        if (!kFold || wave < 4 * folded)
 #pragma unroll
             for (uint32_t s = 0; s < 4; ++s) powers[s] = from[s];
     };
     if constexpr (kKind != BurstKind::kFoldShared) fetch_powers();
-    u32x4 fold[2];
+    u32x4 fold[2];  // the latter only of the first half of the threads, or in the other half for sweeps
     auto fetch_fold = [&]() __attribute__((always_inline)) {
         fold[0] = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower])[tid];  // and the next power's
         if (tid < kNibbleTableEntries) fold[1] = reinterpret_cast<const u32x4*>(kt->ghash_rows3)[tid];
+        else if (sweeps > 1)
+            fold[1] = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower + 4])[tid - kNibbleTableEntries];
     };
     if constexpr (kKind == BurstKind::kFold) fetch_fold();
     __syncthreads();  // the tables are in place
@@ -2995,6 +3016,9 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     auto store_fold = [&]() __attribute__((always_inline)) {
         reinterpret_cast<u32x4*>(fold_tables)[tid] = fold[0];
         if (tid < kNibbleTableEntries) reinterpret_cast<u32x4*>(fold_tables[2])[tid] = fold[1];
+        if constexpr (kKind == BurstKind::kFold)
+            if (tid >= kNibbleTableEntries && sweeps > 1)
+                reinterpret_cast<u32x4*>(lds.sweep)[tid - kNibbleTableEntries] = fold[1];
     };
     if constexpr (kKind == BurstKind::kFold) store_fold();
 
@@ -3002,20 +3026,34 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     const uint32_t iv_word = column == 0 ? j.w[0] : column == 1 ? j.w[1] : j.w[2];
     if constexpr (kKind == BurstKind::kFold) {
         if (by_rows) {
-            if (wave < 4 * have) {
+            auto keep_mask = [&](uint32_t s0, uint32_t s1, uint32_t s2, uint32_t s3)
+                __attribute__((always_inline)) {
+                    if (!mask_apart) lds.mask = Block{{s0, s1, s2, s3}};
+                };
+            AesAddr A;
+            aes_addr_init<TeHalf>(A, lane);
+            uint32_t y[4] = {0, 0, 0, 0};
+            auto make_row = [&](uint32_t sweep) __attribute__((always_inline)) {
+                if (!has_row(sweep)) return;
                 GhashNone G;
                 const CtrBlock C{j.w[0], j.w[1], j.w[2], (uint32_t)blk + first_ctr};
-                auto keep_mask = [&](uint32_t s0, uint32_t s1, uint32_t s2, uint32_t s3)
-                    __attribute__((always_inline)) {
-                        if (!mask_apart) lds.mask = Block{{s0, s1, s2, s3}};
-                    };
-                AesAddr A;
-                aes_addr_init<TeHalf>(A, lane);
                 bulk_row<kDecrypt, 0, kDecrypt>(LaneKeys{key_word, meta.rounds()}, A, C, row, cd.dst, blk,
                                                 row_edge, keep_mask, lds_base, G);
-                lds.rows[wave / 4][(wave & 3) * kRowBlocks + lane] = Block{{G.w[0], G.w[1], G.w[2], G.w[3]}};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) y[k] ^= G.w[k];
+            };
+            if (sweeps > 1) __syncthreads();  // lds.sweep is in place
+            // (the last sweep, mostly the only one, apart: in the loop it would wait for its row first)
+#pragma unroll 1
+            for (uint32_t sweep = 0; sweep + 1 < sweeps; ++sweep) {
+                make_row(sweep);
+                fetch_row(sweep + 1);  // wanted when the keystream is there
+                ghash_mul_lds(lds_offset(lds.sweep), y);
             }
-            if (mask_apart && wave == (have < kFoldPasses ? kWavesPerGroup - 1 : 0)) {
+            make_row(sweeps - 1);
+            if (wave < 4 * folded)
+                lds.rows[wave / 4][(wave & 3) * kRowBlocks + lane] = Block{{y[0], y[1], y[2], y[3]}};
+            if (mask_apart && wave == (folded < kFoldPasses ? kWavesPerGroup - 1 : 0)) {
                 uint32_t y[1] = {j.w[0]};
                 y[0] = column == 3 ? j.w[3] : iv_word;
                 quad_encrypt<1>(keys, lane, lds_base, y);
@@ -3071,7 +3109,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
             store_fold();
             __syncthreads();
         }
-        for (uint32_t i = wave; i < 12 * have; i += kWavesPerGroup) {
+        for (uint32_t i = wave; i < 12 * folded; i += kWavesPerGroup) {
             const uint32_t q = i / 12, row = i % 12 / 4, w = i % 4;
             const uint32_t v = lds.rows[q][row * kRowBlocks + lane].w[w];
             u32x4 z = word_times(lds_offset(fold_tables[2 - row]) + w * 2048, v);
@@ -3082,15 +3120,21 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
                                    __HIP_MEMORY_SCOPE_WORKGROUP);
         }
         __syncthreads();
-        if (wave < 4 * have)
+        if (wave < 4 * folded)
             lds.shares[wave / 4][wave % 4] =
                 bytes_dot(lds.rows[wave / 4][3 * kRowBlocks + lane].w[wave % 4], powers);
     }
+    GfWords far_hop{{0, 0, 0, 0}};
     if (finisher) {
+        if (far) {
+            const uint32_t m = lane >> 4 < folded ? behind + folded - 1 - (lane >> 4) : 0;
+            far_hop = kt->far_hop[(m << pass_power) / kRowBlocks / kRowHopEntries];
+        }
         if (has_mask) {
             sum_over_lanes(extra.w);
         }
         if (hops) spread_over_row(hop, lane);
+        if (far) spread_over_row(far_hop, lane);
     }
     // When decrypting, the wavefront that finishes the chunk may have to wipe plaintext that
     // others (on other XCDs) wrote: their stores go through to memory, and must be there before
@@ -3100,10 +3144,10 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     if (!finisher) return;
 
     GfWords sum{{0, 0, 0, 0}};
-    for (uint32_t q0 = 0; q0 < have; q0 += 4) {
+    for (uint32_t q0 = 0; q0 < folded; q0 += 4) {
         const uint32_t q = q0 + (lane >> 4), w = lane & 15;
         GfWords part{{0, 0, 0, 0}};
-        if (q < have && w < (kFold ? 4 : nwaves)) part = lds.shares[q][w];
+        if (q < folded && w < (kFold ? 4 : nwaves)) part = lds.shares[q][w];
 #pragma unroll
         for (int k = 0; k < 4; ++k) part.a[k] = row_summed(part.a[k]);
         if (hops) {
@@ -3112,6 +3156,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
                 spread_over_row(hop, lane);
             }
             part = times_spread(part, hop, lane);
+            if (far) part = times_spread(part, far_hop, lane);
         }
         sum_over_lanes<true>(part.a);
 #pragma unroll

@@ -167,7 +167,7 @@ struct ArgBatch {
 // Passes a workgroup of the kernel for short bursts makes at most, and where chunks have several
 // workgroups.
 constexpr uint32_t kBurstPasses = 8;  // of up to eight wavefronts; of sixteen:
-constexpr uint32_t kFoldPasses = 4;
+constexpr uint32_t kFoldPasses = 4, kSweptPasses = 16;  // at a time, and in all
 // Workgroups of a chunk (KeyTables::hop has their distances) and of a launch.
 constexpr uint32_t kSwapChunkGroups = kHopEntries;
 constexpr uint32_t kSwapMaxGroups = 512;

@@ -57,6 +57,16 @@ SHAPES = {
     "spare_2": ([512 * 4096 - 48 * 16], [1008]),
     "spare_3": ([768 * 4096 + 4095], [0]),
     "spare_of_some": ([64 * 4096] * 7 + [63 * 4096 + 1, 5], [16, 0, 40]),
+    # sweeps of four passes, the first of them whole or not; with block -1, AAD or the chunk's start in the
+    # spare one, in a missing one; rows further from the end than KeyTables::row_hop reaches
+    "sweeps_2": ([256 * 5 * 4096 - 5], [0]),
+    "sweeps_2_whole": ([256 * 8 * 4096 - 16], [3000]),
+    "sweeps_2_spare": ([256 * 8 * 4096], [16]),
+    "sweeps_2_missing": ([2 << 20] * 3, [0]),
+    "sweeps_2_missing_2": ([85 * 6 * 4096] * 3, [0]),
+    "sweeps_3": ([100 * 9 * 4096 + 1, 150 * 9 * 4096 - 16, 70000, 8200], [0, 1008, 40, 16]),
+    "sweeps_4": ([256 * 14 * 4096 + 33], [20]),
+    "sweeps_of_each": ([14 * 4096 + 513 * i for i in range(200)], [16, 0, 3000, 7]),
     # more chunks than compute units: mixed, and all of much the same length
     "many_mixed": ([(37 * i * i) % 8192 + 1 for i in range(40)] + [20] * 260, [0, 9]),
     "many_even": ([4096 + 16 * (i % 3) for i in range(300)], [0, 16]),
