@@ -31,17 +31,17 @@ LDS_PEAK_GCYCLES = 256 * 2.4               # 256 CUs, one LDS pipe each, 2.4 GHz
 # (pgcm_kernels.hip and the two headers it includes) whose hash is given; once those change the
 # counters no longer apply and bench.py reports null.
 COUNTERS = {
-    "sources_sha256": "d246e8456c378e50f5108fb4beb9d0d29a693e0fb315c8c697f11e4069fb0f21",
+    "sources_sha256": "4e061b6ae901b03bc050c95e9677589c56d12ba5a15aa6f314a046090dfb8d8f",
     "workload": "c2_opt13b_kv_4096x320KiB",
-    "fetch_size_kib": 655997.3,     # FETCH_SIZE per launch
+    "fetch_size_kib": 656166.4,     # FETCH_SIZE per launch
     "fetch_scale": 1310720.0 / 655388.0,   # a 1 310 720 KiB device copy reads 655 388
-    "write_size_kib": 1310795.5,    # WRITE_SIZE per launch
+    "write_size_kib": 1310799.5,    # WRITE_SIZE per launch
     "write_scale": 1310720.0 / 1310720.0,  # the same copy writes 1 310 720.0
-    "valu_wave_instructions": 575734784.0,  # SQ_INSTS_VALU per launch
-    "lds_wave_instructions": 305161728.0,   # SQ_INSTS_LDS per launch
-    "lds_active_cycles": 698790912.0,   # SQ_LDS_IDX_ACTIVE per launch, summed over the 256 CUs
-    "gui_active_cycles": 24046221.1 / 8,  # GRBM_GUI_ACTIVE per launch (summed over the 8 XCDs) ...
-    "pmc_launch_ms": 1.4593,              # ... and the launch's duration in that same run
+    "valu_wave_instructions": 547574784.0,  # SQ_INSTS_VALU per launch
+    "lds_wave_instructions": 297997824.0,   # SQ_INSTS_LDS per launch
+    "lds_active_cycles": 684266496.0,   # SQ_LDS_IDX_ACTIVE per launch, summed over the 256 CUs
+    "gui_active_cycles": 23472316.4 / 8,  # GRBM_GUI_ACTIVE per launch (summed over the 8 XCDs) ...
+    "pmc_launch_ms": 1.4112,              # ... and the launch's duration in that same run
 }
 
 
@@ -388,7 +388,7 @@ def timed_kernel_name(w, args):
     fill the chip"""
     longest = int(w.lens.max())
     if longest <= 8192 and w.n <= 512:
-        return "swap_kernel (a workgroup per chunk: the whole invocation)"
+        return "burst_kernel (a workgroup per chunk: the whole invocation)"
     if longest <= 1008:
         return "small_kernel (one wavefront per chunk: the whole invocation)"
     if in_units(args):
