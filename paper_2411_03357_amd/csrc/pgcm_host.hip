@@ -15,6 +15,7 @@
 
 #include "../../include/pgcm.h"
 #include "pgcm_kernels.h"
+#include "pgcm_one_launch.h"
 #include "pgcm_spans.h"
 
 using namespace pgcm;
@@ -749,111 +750,6 @@ void use_slots(Context* ctx, size_t n, hipStream_t stream, bool capturing) {
     ctx->counter_at = nullptr;  // the unit counter of other batches may lie under them
 }
 
-// How a batch is cut for the one-launch path, if it takes it.
-struct SwapShape {
-    bool burst;                               // burst_kernel
-    bool alone;                               // every chunk has one workgroup
-    // burst: a workgroup's passes for unit_power, and what a chunk's first workgroup may have beyond them
-    uint32_t unit_power, wave_power, groups, spare;
-};
-
-inline uint32_t swap_groups(const BatchArgs& a, size_t i, uint32_t unit_power, uint32_t wave_power) {
-    const uint32_t lead = swap_lead_blocks(a.aad_len ? a.aad_len[i] : 0, wave_power < 4);
-    const uint64_t blocks = (a.len[i] + 15) / 16 + lead;
-    const uint64_t units = (blocks + ((uint64_t)1 << unit_power) - 1) >> unit_power;
-    const uint64_t groups = (units + ((uint64_t)1 << wave_power) - 1) >> wave_power;
-    return groups == 0 ? 1 : (uint32_t)groups;
-}
-
-// burst_kernel: what a chunk's passes cover, and its workgroups if they make so many passes each, the
-// first of them up to `spare` more
-inline uint64_t burst_blocks(const BatchArgs& a, size_t i) {
-    return (a.len[i] + 15) / 16 + swap_lead_blocks(a.aad_len ? a.aad_len[i] : 0, true);
-}
-inline uint64_t burst_groups(uint64_t blocks, uint32_t wave_power, uint32_t passes, uint32_t spare) {
-    const uint32_t shift = 4 + wave_power;
-    const uint64_t of_chunk = (blocks + ((uint64_t)1 << shift) - 1) >> shift;
-    return of_chunk <= passes + spare ? 1 : (of_chunk - spare + passes - 1) / passes;
-}
-
-// Batches of short chunks, and others of at most sixteen passes for every compute unit, go to burst_kernel.
-// As long as there is a compute unit for every short chunk, a workgroup takes a whole one, with no
-// more wavefronts than it has blocks for; of more chunks, workgroups of at most eight wavefronts share
-// a compute unit, and the longer chunks take several.  Longer chunks are spread over as many
-// workgroups of sixteen as there are compute units, with the fewest passes that go: first with none spare,
-// then with one for the first workgroup of each chunk, which is what a few blocks too many take (2 MiB
-// with AAD in 257 workgroups of two passes: 256 take 11.8 us, four passes in 129 took 14.8; 8 of
-// 256 KiB with AAD 12.3, were 14.7), then with one more (2.3 to 3 MB in three 12.1, in four 14.2).
-// What is left: the smallest unit with which the batch fits the compute units, a workgroup each, at
-// sixteen wavefronts, then the fewest wavefronts a workgroup with which it still does.
-bool swap_shape(const pgcm_key* key, const BatchArgs& a, bool all_small, SwapShape* shape) {
-    if (a.n > kSmallMaxChunks || (!all_small && !key->one_launch)) return false;
-    const uint32_t num_cu = (uint32_t)key->num_cu;
-    auto groups = [&](uint32_t unit_power, uint32_t wave_power, uint32_t* most_of_one) {
-        uint64_t sum = 0;
-        *most_of_one = 0;
-        for (size_t k = 0; k < a.n; ++k) {
-            const uint32_t g = swap_groups(a, a.at(k), unit_power, wave_power);
-            if (g > *most_of_one) *most_of_one = g;
-            sum += g;
-        }
-        return sum;
-    };
-    uint32_t up = kMinUnitPower + 1, wp = 2, longest = 0;
-    uint64_t total = 0;
-    // burst_kernel's workgroups
-    uint64_t blocks[kSmallMaxChunks], most_blocks = 0;
-    for (size_t k = 0; k < a.n; ++k) {
-        blocks[k] = burst_blocks(a, a.at(k));
-        if (blocks[k] > most_blocks) most_blocks = blocks[k];
-    }
-    auto bursts = [&](uint32_t wave_power, uint32_t passes, uint32_t spare) {
-        uint64_t sum = 0;
-        for (size_t k = 0; k < a.n; ++k) sum += burst_groups(blocks[k], wave_power, passes, spare);
-        return sum;
-    };
-    if (all_small) {
-        while (wp < 4 && most_blocks > (uint64_t)16 << wp) ++wp;
-        uint32_t passes = kFoldPasses;
-        total = a.n;
-        if (a.n > num_cu && wp > 2 && bursts(3, 1, 0) <= kSwapMaxGroups) {
-            wp = 3, passes = 1;
-            total = bursts(wp, passes, 0);
-        }
-        *shape = SwapShape{true, total == a.n, passes, wp, (uint32_t)total, 0};
-        return true;
-    } else {
-        const uint32_t most = num_cu < kSwapChunkGroups ? num_cu : kSwapChunkGroups;
-        if (a.n > most) return false;
-        uint64_t bytes = 0;
-        for (size_t k = 0; k < a.n; ++k) bytes += a.len[a.at(k)];
-        if (bytes > (uint64_t)most * kWavesPerGroup * kUnitBytes) return false;
-        const uint32_t forced = key->forced_unit_power;
-        if (forced <= kMinUnitPower)
-            for (uint32_t passes = 1; passes <= kSweptPasses; ++passes)
-                for (uint32_t spare = 0; spare <= (passes < kSweptPasses ? 1u : 0u); ++spare)
-                    if ((total = bursts(4, passes, spare)) <= most) {
-                        *shape = SwapShape{true, total == a.n, passes, 4, (uint32_t)total, spare};
-                        return true;
-                    }
-        if (forced) up = forced;
-        if (up > kUnitPower) return false;
-        wp = 4;
-        while ((total = groups(up, wp, &longest)) > most) {
-            if (forced || up == kUnitPower) return false;
-            ++up;
-        }
-        while (wp > 2) {
-            uint32_t l = 0;
-            const uint64_t t = groups(up, wp - 1, &l);
-            if (t > most) break;
-            --wp, total = t, longest = l;
-        }
-    }
-    *shape = SwapShape{false, longest <= 1, up, wp, (uint32_t)total, 0};
-    return true;
-}
-
 void launch_swap_batch(const pgcm_key* key, const BatchArgs& a, const SwapShape& shape,
                        hipEvent_t done, const ArgBatch& batch, const GroupDesc* staged,
                        ArriveSlot* slots) {
@@ -896,6 +792,7 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapSh
         if (rc != PGCM_OK) return rc;
         h_groups = reinterpret_cast<GroupDesc*>(ctx->stage[s]);
     }
+    const ShapeBatch lens{a.n, a.order, a.aad_len, a.len};
     uint32_t groups = 0;
     for (size_t k = 0; k < a.n; ++k) {
         const size_t i = a.at(k);
@@ -907,9 +804,10 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapSh
         c.aad = c.aad_len ? (const uint8_t*)a.aad[i] : nullptr;
         c.index = (uint32_t)i;
         const uint32_t of_chunk =
-            !shape.burst ? swap_groups(a, i, shape.unit_power, shape.wave_power)
-            : shape.alone ? 1 : (uint32_t)burst_groups(burst_blocks(a, i), shape.wave_power, shape.unit_power,
-                                             shape.spare);
+            !shape.burst  ? swap_groups(lens, i, shape.unit_power, shape.wave_power)
+            : shape.alone ? 1
+                          : (uint32_t)burst_groups(burst_passes(burst_blocks(lens, i), shape.wave_power),
+                                                   shape.unit_power, shape.spare);
         if (in_args) {
             batch.c[k] = c;
             batch.group_base[k] = groups;
@@ -1163,7 +1061,8 @@ int run_batch(pgcm_key* key, BatchArgs a) {
     if (rc != PGCM_OK) return rc;
     if (a.fixed && a.n > kFixedMaxChunks) return PGCM_ERR_CAPACITY;
     SwapShape shape{};
-    bool one_launch = swap_shape(key, a, v.all_small, &shape);
+    bool one_launch = swap_shape(ShapeBatch{a.n, a.order, a.aad_len, a.len}, (uint32_t)key->num_cu,
+                                 key->one_launch, key->forced_unit_power, v.all_small, &shape);
     // Where units or workgroups are left short, spans have fewer rows for a wavefront, but they begin
     // and end later.  With sixteen wavefronts a workgroup, a batch of one launch takes 14 us and
     // 4.3 a row of its units, with eight 12 and 2.4; spans take 25 and 3.6 a row (147 chunks of

@@ -1,0 +1,176 @@
+// How a batch of few chunks is cut for the kernels that do it in one launch (burst_kernel, swap_kernel).
+// Host only, plain C++.
+#pragma once
+#include <stddef.h>
+#include <stdint.h>
+
+#include "pgcm_types.h"
+
+namespace pgcm {
+
+// The caller's arrays as far as the shape depends on them.
+struct ShapeBatch {
+    size_t n;
+    const uint32_t* order;  // chunk k of the batch is the caller's chunk order[k]; null: chunk k
+    const uint32_t* aad_len;
+    const uint64_t* len;
+
+    size_t at(size_t k) const { return order ? order[k] : k; }
+    uint32_t aad(size_t i) const { return aad_len ? aad_len[i] : 0; }
+};
+
+// How a batch is cut for the one-launch path, if it takes it.
+struct SwapShape {
+    bool burst;                               // burst_kernel
+    bool alone;                               // every chunk has one workgroup
+    // burst: a workgroup's passes for unit_power, and what a chunk's first workgroup may have beyond them
+    uint32_t unit_power, wave_power, groups, spare;
+};
+
+inline uint32_t swap_groups(const ShapeBatch& a, size_t i, uint32_t unit_power, uint32_t wave_power) {
+    const uint32_t lead = swap_lead_blocks(a.aad(i), wave_power < 4);
+    const uint64_t blocks = (a.len[i] + 15) / 16 + lead;
+    const uint64_t units = (blocks + ((uint64_t)1 << unit_power) - 1) >> unit_power;
+    const uint64_t groups = (units + ((uint64_t)1 << wave_power) - 1) >> wave_power;
+    return groups == 0 ? 1 : (uint32_t)groups;
+}
+
+// burst_kernel: the passes that a chunk takes, and its workgroups if they make so many each, the first of
+// them up to `spare` more
+inline uint64_t burst_blocks(const ShapeBatch& a, size_t i) {
+    return (a.len[i] + 15) / 16 + swap_lead_blocks(a.aad(i), true);
+}
+inline uint64_t burst_passes(uint64_t blocks, uint32_t wave_power) {
+    const uint32_t shift = 4 + wave_power;
+    return (blocks + ((uint64_t)1 << shift) - 1) >> shift;
+}
+inline uint64_t burst_groups(uint64_t of_chunk, uint32_t passes, uint32_t spare) {
+    return of_chunk <= passes + spare ? 1 : (of_chunk - spare + passes - 1) / passes;
+}
+
+// What workgroups of sixteen wavefronts may make, in the order in which it is looked for: one pass, one and
+// a spare one for a chunk's first workgroup, two, and so on to kSweptPasses with none to spare.  A later
+// choice never takes more workgroups than an earlier one.
+struct BurstChoice {
+    uint32_t passes, spare;
+};
+constexpr uint32_t kBurstChoices = 2 * kSweptPasses - 1;
+constexpr BurstChoice burst_choice(uint32_t i) { return BurstChoice{i / 2 + 1, i % 2}; }
+
+// Workgroups of chunks of so many passes each, fewer than 2^28: multiplied by the passes' inverse, rounded
+// up, which is exact for these and goes several chunks at a time.
+inline uint64_t burst_groups_of_all(const uint32_t* of_chunk, size_t n, BurstChoice c) {
+    const uint64_t inverse = (((uint64_t)1 << 32) + c.passes - 1) / c.passes;
+    uint64_t sum = 0;
+    for (size_t k = 0; k < n; ++k) {
+        const uint64_t g = ((of_chunk[k] - c.spare + c.passes - 1) * inverse) >> 32;
+        sum += of_chunk[k] <= c.passes + c.spare ? 1 : g;
+    }
+    return sum;
+}
+
+// The first choice with which n chunks, of `passes` passes in all, have at most `most` workgroups, n <= most;
+// groups(choice): how many they have.  False: none.  A chunk has at least (its passes - spare) / passes
+// workgroups, which bounds the choice from below, and mostly hits it; the rest is bisection, so that the
+// chunks are gone over seven times at most.  With all choices in turn a call's host time was up to 30 us
+// longer: 256 chunks that fit none 30 us, now 0.1; 256 of 64 KiB 29, now 0.25; 200 of 30 to 60 KB, where
+// it takes the bisection, 15, now 1.8.
+template <class Groups>
+inline bool first_burst_choice(uint64_t passes, size_t n, uint64_t most, Groups groups, BurstChoice* choice,
+                               uint64_t* total) {
+    if (passes > kSweptPasses * most) return false;
+    const uint64_t least = passes > n ? (passes - n + most - 1) / most : 0;
+    uint32_t low = least > 1 ? 2 * (uint32_t)(least - 1) : 0;  // everything before it has too many
+    if (passes > burst_choice(low).passes * most) ++low;
+    uint32_t fits = low;
+    *total = groups(burst_choice(low));
+    if (*total > most) {
+        fits = kBurstChoices - 1;
+        if (low == fits || (*total = groups(burst_choice(fits))) > most) return false;
+        while (fits - low > 1) {
+            const uint32_t mid = (low + fits) / 2;
+            const uint64_t t = groups(burst_choice(mid));
+            if (t > most) low = mid;
+            else fits = mid, *total = t;
+        }
+    }
+    *choice = burst_choice(fits);
+    return true;
+}
+
+// Batches of short chunks, and others of at most sixteen passes for every compute unit, go to burst_kernel.
+// As long as there is a compute unit for every short chunk, a workgroup takes a whole one, with no
+// more wavefronts than it has blocks for; of more chunks, workgroups of at most eight wavefronts share
+// a compute unit, and the longer chunks take several.  Longer chunks are spread over as many
+// workgroups of sixteen as there are compute units, with the fewest passes that go: first with none spare,
+// then with one for the first workgroup of each chunk, which is what a few blocks too many take (2 MiB
+// with AAD in 257 workgroups of two passes: 256 take 11.8 us, four passes in 129 took 14.8; 8 of
+// 256 KiB with AAD 12.3, were 14.7), then with one more (2.3 to 3 MB in three 12.1, in four 14.2).
+// What is left: the smallest unit with which the batch fits the compute units, a workgroup each, at
+// sixteen wavefronts, then the fewest wavefronts a workgroup with which it still does.
+// forced: log2 of the blocks of a unit, or 0; all_small: no chunk is longer than kSmallChunkBytes.
+inline bool swap_shape(const ShapeBatch& a, uint32_t num_cu, bool one_launch, uint32_t forced, bool all_small,
+                       SwapShape* shape) {
+    if (a.n > kSmallMaxChunks || (!all_small && !one_launch)) return false;
+    uint64_t total = 0;
+    if (all_small) {
+        uint64_t most_blocks = 0, of_eight = 0;
+        for (size_t k = 0; k < a.n; ++k) {
+            const uint64_t blocks = burst_blocks(a, a.at(k));
+            if (blocks > most_blocks) most_blocks = blocks;
+            of_eight += burst_groups(burst_passes(blocks, 3), 1, 0);
+        }
+        uint32_t wp = 2, passes = kFoldPasses;
+        while (wp < 4 && most_blocks > (uint64_t)16 << wp) ++wp;
+        total = a.n;
+        if (a.n > num_cu && wp > 2 && of_eight <= kSwapMaxGroups) wp = 3, passes = 1, total = of_eight;
+        *shape = SwapShape{true, total == a.n, passes, wp, (uint32_t)total, 0};
+        return true;
+    }
+    const uint32_t most = num_cu < kSwapChunkGroups ? num_cu : kSwapChunkGroups;
+    if (a.n > most) return false;
+    uint64_t bytes = 0;
+    for (size_t k = 0; k < a.n; ++k) bytes += a.len[a.at(k)];
+    if (bytes > (uint64_t)most * kWavesPerGroup * kUnitBytes) return false;
+    if (forced <= kMinUnitPower) {
+        uint32_t of_chunk[kSwapChunkGroups];
+        uint64_t passes = 0;
+        for (size_t k = 0; k < a.n; ++k) {
+            of_chunk[k] = (uint32_t)burst_passes(burst_blocks(a, a.at(k)), 4);
+            passes += of_chunk[k];
+        }
+        BurstChoice c;
+        if (first_burst_choice(
+                passes, a.n, most, [&](BurstChoice b) { return burst_groups_of_all(of_chunk, a.n, b); },
+                &c, &total)) {
+            *shape = SwapShape{true, total == a.n, c.passes, 4, (uint32_t)total, c.spare};
+            return true;
+        }
+    }
+    auto groups = [&](uint32_t unit_power, uint32_t wave_power, uint32_t* most_of_one) {
+        uint64_t sum = 0;
+        *most_of_one = 0;
+        for (size_t k = 0; k < a.n; ++k) {
+            const uint32_t g = swap_groups(a, a.at(k), unit_power, wave_power);
+            if (g > *most_of_one) *most_of_one = g;
+            sum += g;
+        }
+        return sum;
+    };
+    uint32_t up = forced ? forced : kMinUnitPower + 1, wp = 4, longest = 0;
+    if (up > kUnitPower) return false;
+    while ((total = groups(up, wp, &longest)) > most) {
+        if (forced || up == kUnitPower) return false;
+        ++up;
+    }
+    while (wp > 2) {
+        uint32_t l = 0;
+        const uint64_t t = groups(up, wp - 1, &l);
+        if (t > most) break;
+        --wp, total = t, longest = l;
+    }
+    *shape = SwapShape{false, longest <= 1, up, wp, (uint32_t)total, 0};
+    return true;
+}
+
+}  // namespace pgcm
