@@ -39,8 +39,11 @@ inline bool hip_failed(hipError_t e) {
 // used it has ended on its stream, so this is how many batches the host may run ahead of the GPU
 constexpr int kStages = 4;
 constexpr uint32_t kTimingRing = 256;
-// contexts a key keeps before it starts re-binding the least recently used one to a new stream
+// contexts that could go to another stream a key keeps before it starts re-binding the least recently
+// used one of them to a new stream
 constexpr size_t kMaxContexts = 16;
+// contexts up to which a key lets them become such that could not
+constexpr size_t kMaxQuietContexts = 8;
 // batches in a row on one stream after which a context may leave their end unmarked
 constexpr uint32_t kQuietStreak = 32;
 // limits of the entry point that allocates nothing (pgcm_encrypt_batch_static)
@@ -155,8 +158,8 @@ struct Context {
     // which use no staging buffer end unmarked: an event a batch costs the host up to 3.3 us, 2.3 us a
     // call where calls follow each other (one 320 KiB block 11.9 -> 9.2 us, a 2 MiB piece 13.4 -> 11.8;
     // on machines that take its interrupts quickly nothing).  Without that mark the context is never
-    // given to another stream, so only while there are few of them: the other kMaxContexts / 2 stay
-    // for streams that come and go.
+    // given to another stream, so only while there are few of them; streams that come and go have
+    // kMaxContexts beside those.
     uint32_t streak = 0;       // batches in a row on `stream`
     bool quiet = false;
 };
@@ -297,9 +300,10 @@ int ensure_work(Context* c, size_t bytes, hipStream_t stream) {
 
 // The context a batch on `stream` runs with.  In order of preference: a context already bound to
 // the stream; one whose last batch has ended (it is re-bound); a new one; and, once the key has
-// kMaxContexts of them, the least recently used one, after waiting for its last batch.  Never taken are
-// contexts that another host thread is using at this moment, and those whose last batch left no mark to
-// wait for: at most kMaxContexts / 2 of them (`quiet`), which stay with their streams.
+// kMaxContexts that can be re-bound, the least recently used one, after waiting for its last batch.  Never
+// taken are contexts that another host thread is using at this moment.  Never re-bound are those whose
+// batches a graph replays, and those whose last batch left no mark to wait for, at most kMaxQuietContexts
+// (`quiet`); they stay with their streams and leave the others their number.
 int acquire_context(pgcm_key* key, hipStream_t stream, Context** out) {
     std::unique_lock<std::mutex> lock(key->mu);
     Context* pick = nullptr;
@@ -308,8 +312,11 @@ int acquire_context(pgcm_key* key, hipStream_t stream, Context** out) {
     bool must_wait = false;
     if (pick == nullptr) {
         Context* lru = nullptr;
+        size_t kept = 0;  // that can be re-bound
         for (Context* c : key->contexts) {
-            if (c->in_call || c->captured || c->unmarked) continue;
+            if (c->captured || c->unmarked) continue;
+            ++kept;
+            if (c->in_call) continue;
             // free for re-binding: never bound, or its last batch has ended.  (A context that
             // pgcm_reserve has bound and no batch has used yet is left for its stream.)
             if (!c->bound || (c->last_stage >= 0 &&
@@ -320,7 +327,7 @@ int acquire_context(pgcm_key* key, hipStream_t stream, Context** out) {
             if (lru == nullptr || c->last_use < lru->last_use) lru = c;
         }
         (void)hipGetLastError();  // a query that said "not ready" is not an error of this call
-        if (pick == nullptr && lru != nullptr && key->contexts.size() >= kMaxContexts) {
+        if (pick == nullptr && lru != nullptr && kept >= kMaxContexts) {
             pick = lru;
             must_wait = pick->last_stage >= 0;
         }
@@ -349,7 +356,7 @@ int acquire_context(pgcm_key* key, hipStream_t stream, Context** out) {
     if (!same_stream) pick->streak = 0;
     else if (pick->streak < kQuietStreak) ++pick->streak;
     pick->quiet = pick->streak >= kQuietStreak && !pick->captured &&
-                  key->contexts.size() <= kMaxContexts / 2;
+                  key->contexts.size() <= kMaxQuietContexts;
     lock.unlock();
     if (pick->bound && pick->stream != stream) {
         // re-binding: everything it enqueued on its old stream must have ended

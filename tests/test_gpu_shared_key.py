@@ -152,6 +152,47 @@ def test_streams_come_and_go_beside_settled_ones():
     key.free()
 
 
+def test_settled_streams_take_no_contexts_from_others():
+    """beside eight streams that have settled, sixteen others at once have a context each, none of which is
+    waited for and taken away: as many as a key without settled streams has"""
+    w = workloads.mini(2)
+    host = w.payload_host()
+    key = pgcm.expand_key(w.key)
+    cts, tags = _oracle_results(w, host)
+    settled = [torch.cuda.Stream() for _ in range(8)]
+    passing = [torch.cuda.Stream() for _ in range(16)]
+    batches = [DeviceBatch(w, torch.from_numpy(host).cuda()) for _ in range(24)]
+    for _ in range(40):
+        for st, b in zip(settled, batches):
+            b.encrypt(key, stream=st)
+    torch.cuda.synchronize()
+    # some 80 ms of work that all of them come behind, so that no batch of theirs ends meanwhile
+    gate, opened = torch.cuda.Stream(), torch.cuda.Event()
+    with torch.cuda.stream(gate):
+        a = torch.ones(8192, 8192, device="cuda")
+        for _ in range(8):
+            a = (a @ a).clamp_(0, 1)
+        opened.record(gate)
+    for st, b in zip(passing, batches[8:]):
+        st.wait_event(opened)
+        b.encrypt(key, stream=st)
+    ended = opened.query()
+    without = []
+    for k, st in enumerate(settled + passing):
+        try:
+            pgcm.describe_context(key, st)
+        except pgcm.PgcmError:
+            without.append(k)
+    assert not without and not ended, (without, ended)
+    torch.cuda.synchronize()
+    for k, b in enumerate(batches):
+        cipher = b.cipher.cpu().numpy()
+        for i in range(w.n):
+            assert np.array_equal(w.chunk(cipher, i), cts[i]), (k, i)
+        assert np.array_equal(b.tags.cpu().numpy().reshape(-1, 16), tags), k
+    key.free()
+
+
 def test_reserve_then_batches_do_not_allocate():
     w = workloads.mini(3)                      # three 2 MiB chunks
     host = w.payload_host()
