@@ -777,6 +777,8 @@ void launch_swap_batch(const pgcm_key* key, const BatchArgs& a, const SwapShape&
         shape.burst && shape.wave_power < 4
             ? burst(std::integral_constant<BurstKind, BurstKind::kWords>{})
         : shape.burst && shared ? burst(std::integral_constant<BurstKind, BurstKind::kFoldShared>{})
+        : shape.burst && shape.unit_power + shape.spare > kFoldPasses
+            ? burst(std::integral_constant<BurstKind, BurstKind::kSweep>{})
         : shape.burst           ? burst(std::integral_constant<BurstKind, BurstKind::kFold>{})
         : key->rounds == 10 ? (a.decrypt ? swap_kernel<true, 10> : swap_kernel<false, 10>)
         : key->rounds == 12 ? (a.decrypt ? swap_kernel<true, 12> : swap_kernel<false, 12>)

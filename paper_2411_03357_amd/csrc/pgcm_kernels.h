@@ -34,9 +34,9 @@ __global__ void swap_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t iv
 // The same for batches whose time is that of one chain of steps: 2^wave_power wavefronts of sixteen blocks
 // a workgroup, which makes meta.unit_power() passes, or, if it is a chunk's first, as many as are left
 // (at most kBurstPasses).  It serves any key.  kLongIv: iv_len exceeds kShortIvBytes.
-// kWords: at most eight wavefronts.  kFold: sixteen, and at most kFoldPasses passes; kFoldShared: the
-// same, one pass less, and two workgroups fit a compute unit.
-enum class BurstKind { kWords, kFold, kFoldShared };
+// kWords: at most eight wavefronts.  kFold: sixteen, and at most kFoldPasses passes; kSweep: up to
+// kSweptPasses and the spare one; kFoldShared: one pass less than kFold, and two workgroups fit a compute unit.
+enum class BurstKind { kWords, kFold, kSweep, kFoldShared };
 template <bool kDecrypt, bool kLongIv, BurstKind kKind>
 __global__ void burst_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t iv_len, SwapMeta meta,
                              ArriveSlot* slots, uint8_t* tags, uint8_t* ok, const GroupDesc* staged,

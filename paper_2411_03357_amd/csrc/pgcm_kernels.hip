@@ -2559,8 +2559,11 @@ struct QuadLds : QuadTables {};
 template <>
 struct QuadLds<BurstKind::kFold> : QuadTables {
     FoldTables fold;
-    Block sweep[kNibbleTableEntries];  // H^1024's
     Block rows[kFoldPasses][4 * kRowBlocks];  // what a pass's blocks add to the hash
+};
+template <>
+struct QuadLds<BurstKind::kSweep> : QuadLds<BurstKind::kFold> {
+    Block sweep[kNibbleTableEntries];  // H^1024's
 };
 template <>
 struct QuadLds<BurstKind::kFoldShared> : QuadTables {  // (its tables take the place of the round tables)
@@ -2830,7 +2833,8 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     const KeyTables* __restrict__ kt, const uint8_t* __restrict__ ivs, uint32_t iv_len,
     SwapMeta meta, ArriveSlot* __restrict__ slots, uint8_t* __restrict__ tags,
     uint8_t* __restrict__ ok, const GroupDesc* __restrict__ staged, const ArgBatch batch) {
-    constexpr bool kFold = kKind != BurstKind::kWords;
+    constexpr bool kFold = kKind != BurstKind::kWords, kSweep = kKind == BurstKind::kSweep;
+    constexpr bool kRows = kKind == BurstKind::kFold || kSweep;  // a compute unit to itself
     __shared__ QuadLds<kKind> lds;
     const uint32_t lds_base = lds_offset(&lds);
     const uint32_t tid = threadIdx.x, lane = tid & 63, column = lane & 3;
@@ -2899,11 +2903,14 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     // sweeps' rows moved along and added up: what follows them knows kFoldPasses passes.  A sweep takes
     // 4.5 us (4 MiB 15 us, 6 MB 18.9, 8 MiB decrypted 22, 12 MB 25.9; in units of swap_kernel 21.7 for
     // the first two, 29.3, 30.8, and 30.9 for 16 MB, where four sweeps take as long).
-    const uint32_t sweeps = kKind == BurstKind::kFold ? (have + kFoldPasses - 1) / kFoldPasses : 1;
+    // A kind of its own has them: in kFold they were 23 more registers and 29 more scalar ones, and a call
+    // of any number of passes was 0.1 to 0.3 us longer (2 MiB with AAD decrypted 11.80 -> 11.52, 1 MiB
+    // 9.52 -> 9.30, 320 KiB encrypted 8.18 -> 8.06, 100 of 20 KB 13.2 -> 12.9; 8 MiB 20.4 either way).
+    const uint32_t sweeps = kSweep ? (have + kFoldPasses - 1) / kFoldPasses : 1;
     const uint32_t folded = sweeps > 1 ? kFoldPasses : have;
     const bool has_mask = g == 0;
     // Several passes: a row a wavefront, a lane a block, which takes fewer instructions a block
-    const bool by_rows = kKind == BurstKind::kFold && nblk - ((int64_t)behind << pass_power) > pass_blocks;
+    const bool by_rows = kRows && nblk - ((int64_t)behind << pass_power) > pass_blocks;
     // E_K(J0) is the keystream of "block -1", if that is in a pass of this workgroup (the AAD before it may
     // have one of its own) with payload; otherwise it is made beside the first pass
     const bool mask_apart =
@@ -2973,7 +2980,8 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
         return kt->row_hop[((m << pass_power) / kRowBlocks) % kRowHopEntries];
     };
     // ... times this one, if there is a pass so far from the chunk's end
-    const bool far = kKind == BurstKind::kFold && (behind + folded - 1) << pass_power >= kRowHopEntries * kRowBlocks;
+    static_assert(kSwapChunkGroups * kFoldPasses * 4 <= kRowHopEntries, "none, of kFoldPasses a workgroup");
+    const bool far = kSweep && (behind + folded - 1) << pass_power >= kRowHopEntries * kRowBlocks;
     if (finisher) {
         if (hops) hop = hop_of(lane >> 4);
         if (has_mask) extra = length_block_entry(kt->ghash[0], cd.aad_len, cd.len, lane);
@@ -2994,10 +3002,10 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     auto fetch_fold = [&]() __attribute__((always_inline)) {
         fold[0] = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower])[tid];  // and the next power's
         if (tid < kNibbleTableEntries) fold[1] = reinterpret_cast<const u32x4*>(kt->ghash_rows3)[tid];
-        else if (sweeps > 1)
+        else if (kSweep && sweeps > 1)
             fold[1] = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower + 4])[tid - kNibbleTableEntries];
     };
-    if constexpr (kKind == BurstKind::kFold) fetch_fold();
+    if constexpr (kRows) fetch_fold();
     __syncthreads();  // the tables are in place
     QuadKeys keys;
     keys.rounds = meta.rounds();
@@ -3010,21 +3018,21 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
         keys.last = k[3].w;
     }
     Block(*fold_tables)[kNibbleTableEntries] = nullptr;
-    if constexpr (kKind == BurstKind::kFold) fold_tables = lds.fold;
+    if constexpr (kRows) fold_tables = lds.fold;
     if constexpr (kKind == BurstKind::kFoldShared)
         fold_tables = reinterpret_cast<Block(*)[kNibbleTableEntries]>(lds.te);
     auto store_fold = [&]() __attribute__((always_inline)) {
         reinterpret_cast<u32x4*>(fold_tables)[tid] = fold[0];
         if (tid < kNibbleTableEntries) reinterpret_cast<u32x4*>(fold_tables[2])[tid] = fold[1];
-        if constexpr (kKind == BurstKind::kFold)
+        if constexpr (kSweep)
             if (tid >= kNibbleTableEntries && sweeps > 1)
                 reinterpret_cast<u32x4*>(lds.sweep)[tid - kNibbleTableEntries] = fold[1];
     };
-    if constexpr (kKind == BurstKind::kFold) store_fold();
+    if constexpr (kRows) store_fold();
 
     const uint32_t first_ctr = __builtin_amdgcn_readfirstlane(bswap32(j.w[3])) + 1u;
     const uint32_t iv_word = column == 0 ? j.w[0] : column == 1 ? j.w[1] : j.w[2];
-    if constexpr (kKind == BurstKind::kFold) {
+    if constexpr (kRows) {
         if (by_rows) {
             auto keep_mask = [&](uint32_t s0, uint32_t s1, uint32_t s2, uint32_t s3)
                 __attribute__((always_inline)) {
@@ -3042,13 +3050,15 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
 #pragma unroll
                 for (int k = 0; k < 4; ++k) y[k] ^= G.w[k];
             };
-            if (sweeps > 1) __syncthreads();  // lds.sweep is in place
-            // (the last sweep, mostly the only one, apart: in the loop it would wait for its row first)
+            if constexpr (kSweep) {
+                if (sweeps > 1) __syncthreads();  // lds.sweep is in place
+                // (the last sweep apart: in the loop it would wait for its row first)
 #pragma unroll 1
-            for (uint32_t sweep = 0; sweep + 1 < sweeps; ++sweep) {
-                make_row(sweep);
-                fetch_row(sweep + 1);  // wanted when the keystream is there
-                ghash_mul_lds(lds_offset(lds.sweep), y);
+                for (uint32_t sweep = 0; sweep + 1 < sweeps; ++sweep) {
+                    make_row(sweep);
+                    fetch_row(sweep + 1);  // wanted when the keystream is there
+                    ghash_mul_lds(lds_offset(lds.sweep), y);
+                }
             }
             make_row(sweeps - 1);
             if (wave < 4 * folded)
@@ -3186,6 +3196,10 @@ PGCM_INSTANTIATE_BURST(false, false, kFold);
 PGCM_INSTANTIATE_BURST(true, false, kFold);
 PGCM_INSTANTIATE_BURST(false, true, kFold);
 PGCM_INSTANTIATE_BURST(true, true, kFold);
+PGCM_INSTANTIATE_BURST(false, false, kSweep);
+PGCM_INSTANTIATE_BURST(true, false, kSweep);
+PGCM_INSTANTIATE_BURST(false, true, kSweep);
+PGCM_INSTANTIATE_BURST(true, true, kSweep);
 PGCM_INSTANTIATE_BURST(false, false, kFoldShared);
 PGCM_INSTANTIATE_BURST(true, false, kFoldShared);
 PGCM_INSTANTIATE_BURST(false, true, kFoldShared);
