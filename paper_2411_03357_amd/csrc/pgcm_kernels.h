@@ -32,10 +32,10 @@ __global__ void swap_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t iv
                             ArgBatch batch);
 
 // The same for batches whose time is that of one chain of steps: 2^wave_power wavefronts of sixteen blocks
-// a workgroup, which makes meta.unit_power() passes, or, if it is a chunk's first, as many as are left
-// (at most kBurstPasses).  It serves any key.  kLongIv: iv_len exceeds kShortIvBytes.
-// kWords: at most eight wavefronts.  kFold: sixteen, and at most kFoldPasses passes; kSweep: up to
-// kSweptPasses and the spare one; kFoldShared: one pass less than kFold, and two workgroups fit a compute unit.
+// a workgroup, which makes meta.unit_power() passes, or, if it is a chunk's first, as many as are left,
+// or, if it has a chunk to itself, as many as that takes.  It serves any key.  kLongIv: iv_len exceeds
+// kShortIvBytes.  kWords: at most eight wavefronts, and one pass.  kFold: sixteen, and at most kFoldPasses;
+// kSweep: kSweptPasses; kFoldShared: kFoldPasses - 1, and two workgroups fit a compute unit.
 enum class BurstKind { kWords, kFold, kSweep, kFoldShared };
 template <bool kDecrypt, bool kLongIv, BurstKind kKind>
 __global__ void burst_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t iv_len, SwapMeta meta,

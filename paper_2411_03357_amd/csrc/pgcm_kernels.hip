@@ -2550,7 +2550,7 @@ struct QuadTables {
     uint32_t te[256 * 64];  // 256 bytes a value: te[0] 32 times, te[1] 32 times
     u32x4 keys[4][4];       // KeyTables::column_keys
     Block long_aad[kWavesPerGroup];
-    GfWords shares[kBurstPasses][kWavesPerGroup];
+    GfWords shares[kFoldPasses][kWavesPerGroup];
     Block mask;  // E_K(J0)
 };
 typedef Block FoldTables[3][kNibbleTableEntries];  // nibble tables of H^64, H^128, H^192
@@ -2975,15 +2975,14 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     GfWords hop{{0, 0, 0, 0}};     // in row r of sixteen lanes: the power of H for pass r
     const bool hops = behind + folded > 1;
     uint8_t* const tag_at = tags + (uint64_t)cd.index * 16;
-    auto hop_of = [&](uint32_t q) __attribute__((always_inline)) {
-        const uint32_t m = q < folded ? behind + folded - 1 - q : 0;
-        return kt->row_hop[((m << pass_power) / kRowBlocks) % kRowHopEntries];
-    };
-    // ... times this one, if there is a pass so far from the chunk's end
+    // ... times one more, if there is a pass so far from the chunk's end
     static_assert(kSwapChunkGroups * kFoldPasses * 4 <= kRowHopEntries, "none, of kFoldPasses a workgroup");
     const bool far = kSweep && (behind + folded - 1) << pass_power >= kRowHopEntries * kRowBlocks;
     if (finisher) {
-        if (hops) hop = hop_of(lane >> 4);
+        if (hops) {
+            const uint32_t m = lane >> 4 < folded ? behind + folded - 1 - (lane >> 4) : 0;
+            hop = kt->row_hop[((m << pass_power) / kRowBlocks) % kRowHopEntries];
+        }
         if (has_mask) extra = length_block_entry(kt->ghash[0], cd.aad_len, cd.len, lane);
         if (kDecrypt) received = global_read_block_any(tag_at);
     }
@@ -3153,24 +3152,19 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     __syncthreads();
     if (!finisher) return;
 
+    // a pass in every row of sixteen lanes
+    static_assert(kFoldPasses * 16 == 64, "all passes at once");
     GfWords sum{{0, 0, 0, 0}};
-    for (uint32_t q0 = 0; q0 < folded; q0 += 4) {
-        const uint32_t q = q0 + (lane >> 4), w = lane & 15;
-        GfWords part{{0, 0, 0, 0}};
-        if (q < folded && w < (kFold ? 4 : nwaves)) part = lds.shares[q][w];
+    {
+        const uint32_t q = lane >> 4, w = lane & 15;
+        if (q < folded && w < (kFold ? 4 : nwaves)) sum = lds.shares[q][w];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) part.a[k] = row_summed(part.a[k]);
+        for (int k = 0; k < 4; ++k) sum.a[k] = row_summed(sum.a[k]);
         if (hops) {
-            if (q0 != 0) {
-                hop = hop_of(q);
-                spread_over_row(hop, lane);
-            }
-            part = times_spread(part, hop, lane);
-            if (far) part = times_spread(part, far_hop, lane);
+            sum = times_spread(sum, hop, lane);
+            if (far) sum = times_spread(sum, far_hop, lane);
         }
-        sum_over_lanes<true>(part.a);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) sum.a[k] ^= part.a[k];
+        sum_over_lanes<true>(sum.a);
     }
     Block tag = gfw_to_block(sum);
     if (has_mask) {

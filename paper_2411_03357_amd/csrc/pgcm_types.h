@@ -164,10 +164,9 @@ struct ArgBatch {
     uint32_t group_base[kArgChunks + 1];  // first workgroup of every chunk; their number
     ArgChunk c[kArgChunks];
 };
-// Passes a workgroup of the kernel for short bursts makes at most, and where chunks have several
-// workgroups.
-constexpr uint32_t kBurstPasses = 8;  // of up to eight wavefronts; of sixteen:
-constexpr uint32_t kFoldPasses = 4, kSweptPasses = 16;  // at a time, and in all
+// Passes a workgroup of sixteen wavefronts of the kernel for short bursts makes at most, at a time and in
+// all (of fewer wavefronts: one).
+constexpr uint32_t kFoldPasses = 4, kSweptPasses = 16;
 // Workgroups of a chunk (KeyTables::hop has their distances) and of a launch.
 constexpr uint32_t kSwapChunkGroups = kHopEntries;
 constexpr uint32_t kSwapMaxGroups = 512;

@@ -49,6 +49,19 @@ static uint64_t groups_of(const ShapeBatch& a, uint64_t pass_blocks, uint64_t pa
     return sum;
 }
 
+// the passes of a chunk's first workgroup, which makes the most
+static uint64_t most_passes(const ShapeBatch& a, const SwapShape& s) {
+    uint64_t most = 0;
+    for (size_t k = 0; k < a.n; ++k) {
+        const uint64_t of_chunk = burst_passes(burst_blocks(a, a.at(k)), s.wave_power);
+        const uint64_t g = s.alone ? 1 : burst_groups(of_chunk, s.unit_power, s.spare);
+        CHECK(of_chunk >= (g - 1) * s.unit_power);
+        const uint64_t first = of_chunk - (g - 1) * s.unit_power;
+        if (first > most) most = first;
+    }
+    return most;
+}
+
 static void check(const ShapeBatch& a, uint32_t num_cu, uint32_t forced) {
     uint64_t bytes = 0, longest = 0;
     for (size_t k = 0; k < a.n; ++k) {
@@ -66,6 +79,8 @@ static void check(const ShapeBatch& a, uint32_t num_cu, uint32_t forced) {
         CHECK(s.alone == (s.groups == a.n));
         if (s.alone) CHECK(groups_of(a, (uint64_t)16 << s.wave_power, s.unit_power, 0) == a.n || a.n > num_cu);
         else CHECK(s.wave_power == 3 && groups_of(a, 128, 1, 0) == s.groups);
+        // what the kinds of burst_kernel are compiled for
+        CHECK(most_passes(a, s) <= (s.wave_power < 4 ? 1 : s.groups > num_cu ? kFoldPasses - 1 : kFoldPasses));
         ++g_bursts;
         return;
     }
@@ -80,6 +95,8 @@ static void check(const ShapeBatch& a, uint32_t num_cu, uint32_t forced) {
             CHECK(goes && s.burst && s.wave_power == 4);
             CHECK(s.unit_power == passes && s.spare == spare && s.groups == total);
             CHECK(s.alone == (total == a.n));
+            CHECK(s.groups <= num_cu);
+            CHECK(most_passes(a, s) <= (passes + spare <= kFoldPasses ? kFoldPasses : kSweptPasses));
             // as the descriptors are filled in
             uint64_t sum = 0;
             for (size_t k = 0; k < a.n; ++k)
