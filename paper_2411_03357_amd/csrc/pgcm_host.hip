@@ -1072,15 +1072,8 @@ int run_batch(pgcm_key* key, BatchArgs a) {
     SwapShape shape{};
     bool one_launch = swap_shape(ShapeBatch{a.n, a.order, a.aad_len, a.len}, (uint32_t)key->num_cu,
                                  key->one_launch, key->forced_unit_power, v.all_small, &shape);
-    // Where units or workgroups are left short, spans have fewer rows for a wavefront, but they begin
-    // and end later.  With sixteen wavefronts a workgroup, a batch of one launch takes 14 us and
-    // 4.3 a row of its units, with eight 12 and 2.4; spans take 25 and 3.6 a row (147 chunks of
-    // 60 to 450 KB: units of 16 rows, spans of 7, 83 and 54 us; 3 of 5 MiB: 4 and 3.8, 32 and 38).
-    if (one_launch && spans && !shape.burst && shape.wave_power == 4) {
-        const uint64_t unit_rows = 1u << (shape.unit_power - kRowPower);
-        if (43 * unit_rows * key->wave_slots > 110 * (uint64_t)key->wave_slots + 36 * v.rows)
-            one_launch = false;
-    }
+    if (one_launch && spans && !shape.burst && !units_before_spans(shape.unit_power, v.rows, key->wave_slots))
+        one_launch = false;
     if (one_launch && shape.alone && a.n <= kArgChunks) return run_one_launch(key, nullptr, a, shape);
     Context* ctx = nullptr;
     if (a.fixed) {

@@ -106,8 +106,10 @@ inline bool first_burst_choice(uint64_t passes, size_t n, uint64_t most, Groups 
 // then with one for the first workgroup of each chunk, which is what a few blocks too many take (2 MiB
 // with AAD in 257 workgroups of two passes: 256 take 11.8 us, four passes in 129 took 14.8; 8 of
 // 256 KiB with AAD 12.3, were 14.7), then with one more (2.3 to 3 MB in three 12.1, in four 14.2).
-// What is left: the smallest unit with which the batch fits the compute units, a workgroup each, at
-// sixteen wavefronts, then the fewest wavefronts a workgroup with which it still does.
+// What is left has more than four rows for each wavefront of the device, and takes units of eight rows or
+// sixteen, a wavefront each, with a workgroup of sixteen a compute unit; units of a forced size take
+// the fewest wavefronts a workgroup, four at least, with which they still fit.
+constexpr uint32_t kLongUnitPower = kRowPower + 3;
 // forced: log2 of the blocks of a unit, or 0; all_small: no chunk is longer than kSmallChunkBytes.
 inline bool swap_shape(const ShapeBatch& a, uint32_t num_cu, bool one_launch, uint32_t forced, bool all_small,
                        SwapShape* shape) {
@@ -157,13 +159,13 @@ inline bool swap_shape(const ShapeBatch& a, uint32_t num_cu, bool one_launch, ui
         }
         return sum;
     };
-    uint32_t up = forced ? forced : kMinUnitPower + 1, wp = 4, longest = 0;
+    uint32_t up = forced ? forced : kLongUnitPower, wp = 4, longest = 0;
     if (up > kUnitPower) return false;
     while ((total = groups(up, wp, &longest)) > most) {
         if (forced || up == kUnitPower) return false;
         ++up;
     }
-    while (wp > 2) {
+    while (forced && wp > 2) {
         uint32_t l = 0;
         const uint64_t t = groups(up, wp - 1, &l);
         if (t > most) break;
@@ -171,6 +173,17 @@ inline bool swap_shape(const ShapeBatch& a, uint32_t num_cu, bool one_launch, ui
     }
     *shape = SwapShape{false, longest <= 1, up, wp, (uint32_t)total, 0};
     return true;
+}
+
+// Where units of swap_kernel and spans could both take a batch of so many rows: are units no longer?  Spans
+// have fewer rows for a wavefront, as units are a power of two, but their descriptors are planned on the
+// host.  Units of eight rows take 46 us decrypting and 47.5 encrypting, whatever part of them is filled;
+// spans 21.5 and 3.75 a row of a wavefront, and 4 more on the host, which shows where a call is waited for
+// (back to back / waited for, units and spans: 12 of 2 MiB 47.4 / 60.4, 44.8 / 63.6; one of 28 MB
+// 47.5 / 60.1, 47.4 / 66.1; 14 of 2 MiB decrypted 46.3 / 59.1, 45.9 / 64.9; one of 31 MB decrypted
+// 46.4 / 59.1, 49.1 / 67.8).  Units of sixteen rows take 81, and spans no longer than that.
+inline bool units_before_spans(uint32_t unit_power, uint64_t rows, uint64_t wave_slots) {
+    return unit_power == kLongUnitPower && 2 * rows >= 13 * wave_slots;
 }
 
 }  // namespace pgcm

@@ -131,6 +131,14 @@ static void check(const ShapeBatch& a, uint32_t num_cu, uint32_t forced) {
     }
     ++g_units;
     CHECK(considered && !s.burst && s.groups <= most && s.unit_power <= kUnitPower && s.wave_power >= 2);
+    // of the sizes and numbers of wavefronts that would go, the smallest
+    auto units_fit = [&](uint32_t up, uint32_t wp) {
+        uint64_t sum = 0;
+        for (size_t k = 0; k < a.n; ++k) sum += swap_groups(a, a.at(k), up, wp);
+        return sum <= most;
+    };
+    CHECK(units_fit(s.unit_power, s.wave_power) && (s.wave_power == 2 || !units_fit(s.unit_power, s.wave_power - 1)));
+    if (!forced) CHECK(s.wave_power == 4 && !units_fit(s.unit_power - 1, 4) && s.unit_power >= kLongUnitPower);
     uint64_t sum = 0;
     bool alone = true;
     for (size_t k = 0; k < a.n; ++k) {
