@@ -16,6 +16,7 @@
 #include "../../include/pgcm.h"
 #include "pgcm_kernels.h"
 #include "pgcm_one_launch.h"
+#include "pgcm_routes.h"
 #include "pgcm_spans.h"
 
 using namespace pgcm;
@@ -519,26 +520,15 @@ inline uint64_t span_rows(const BatchArgs& a, size_t i) {
     return pgcm::span_rows(a.len[i], a.aad_len ? a.aad_len[i] : 0);
 }
 
-// What decides which way a batch goes.
-struct BatchSurvey {
-    bool all_small = true;     // every chunk fits the small-transfer path
-    bool all_one_row = true;   // ... and its one-wavefront-per-chunk kernel
-    uint64_t rows = 0;         // in spans
-    uint64_t longest = 0;      // in bytes
-};
-
-// ... found while every chunk is validated
+// What decides which way a batch goes, found while every chunk is validated.
 int survey_batch(const BatchArgs& a, BatchSurvey* out) {
     BatchSurvey v;
     for (size_t k = 0; k < a.n; ++k) {
         const size_t i = a.at(k);
         const int rc = check_chunk(a, i);
         if (rc != PGCM_OK) return rc;
-        if (a.len[i] > v.longest) v.longest = a.len[i];
-        v.rows += span_rows(a, i);
+        v.add(a.len[i], a.aad_len ? a.aad_len[i] : 0);
     }
-    v.all_small = v.longest <= kSmallChunkBytes;
-    v.all_one_row = v.longest <= kSmallRowBytes;
     *out = v;
     return PGCM_OK;
 }
@@ -766,23 +756,22 @@ void launch_swap_batch(const pgcm_key* key, const BatchArgs& a, const SwapShape&
     const SwapMeta meta = swap_meta(staged ? 0 : (uint32_t)a.n, shape.unit_power, shape.wave_power,
                                     shape.alone, a.order == nullptr, shape.groups,
                                     (uint32_t)key->rounds);
-    auto burst = [&](auto kind) {
-        constexpr BurstKind kKind = decltype(kind)::value;
+    auto* const swap = key->rounds == 10   ? (a.decrypt ? swap_kernel<true, 10> : swap_kernel<false, 10>)
+                       : key->rounds == 12 ? (a.decrypt ? swap_kernel<true, 12> : swap_kernel<false, 12>)
+                                           : (a.decrypt ? swap_kernel<true, 14> : swap_kernel<false, 14>);
+    auto burst = [&](auto of) {
+        constexpr BurstKind kKind = decltype(of)::value;
         const bool long_iv = a.iv_len > kShortIvBytes;
         return a.decrypt ? (long_iv ? burst_kernel<true, true, kKind> : burst_kernel<true, false, kKind>)
                          : (long_iv ? burst_kernel<false, true, kKind> : burst_kernel<false, false, kKind>);
     };
-    const bool shared = shape.groups > (uint32_t)key->num_cu;
+    const BurstKind kind = burst_kind(shape, (uint32_t)key->num_cu);
     auto* const kernel =
-        shape.burst && shape.wave_power < 4
-            ? burst(std::integral_constant<BurstKind, BurstKind::kWords>{})
-        : shape.burst && shared ? burst(std::integral_constant<BurstKind, BurstKind::kFoldShared>{})
-        : shape.burst && shape.unit_power + shape.spare > kFoldPasses
-            ? burst(std::integral_constant<BurstKind, BurstKind::kSweep>{})
-        : shape.burst           ? burst(std::integral_constant<BurstKind, BurstKind::kFold>{})
-        : key->rounds == 10 ? (a.decrypt ? swap_kernel<true, 10> : swap_kernel<false, 10>)
-        : key->rounds == 12 ? (a.decrypt ? swap_kernel<true, 12> : swap_kernel<false, 12>)
-                            : (a.decrypt ? swap_kernel<true, 14> : swap_kernel<false, 14>);
+        !shape.burst ? swap
+        : kind == BurstKind::kWords ? burst(std::integral_constant<BurstKind, BurstKind::kWords>{})
+        : kind == BurstKind::kFold  ? burst(std::integral_constant<BurstKind, BurstKind::kFold>{})
+        : kind == BurstKind::kSweep ? burst(std::integral_constant<BurstKind, BurstKind::kSweep>{})
+                                    : burst(std::integral_constant<BurstKind, BurstKind::kFoldShared>{});
     launch_last(kernel, grid, block, a.stream, a.capturing || done == nullptr, done, kt, a.ivs,
                 a.iv_len, meta, slots, a.tags, a.ok, staged, batch);
 }
@@ -948,13 +937,6 @@ int run_unit_batch(pgcm_key* key, Context* ctx, const BatchArgs& a, const BatchP
 
 // ---- Spans (span_kernel) ----
 
-// May a batch of chunks of at most this length, and this many rows in all, go in spans?  (The bounds
-// are those of the powers of H a key has and of 32-bit row numbers.)
-inline bool takes_spans(const pgcm_key* key, uint64_t rows, uint64_t longest) {
-    return key->one_launch && !key->matrix_hash && !key->forced_unit_power && rows <= kSpanMaxRows &&
-           longest / (16 * kRowBlocks) + 2 < (uint64_t)kRowHopEntries * kFarHopEntries;
-}
-
 // One batch in spans, of one key or of several: the context is that of the first.
 int run_span_batch(Context* ctx, const BatchArgs& a, KeyPart* keys, size_t nkeys) {
     const uint32_t ngroups = deal_groups(keys, nkeys, (uint32_t)keys[0].key->num_cu);
@@ -1049,6 +1031,10 @@ int note_capture(BatchArgs& a) {
     return PGCM_OK;
 }
 
+RouteOptions route_options(const pgcm_key* key, bool fixed) {
+    return RouteOptions{(uint32_t)key->num_cu, key->one_launch, key->matrix_hash, key->forced_unit_power, fixed};
+}
+
 // One batch under one key: validate everything, choose the way it goes, pick a context unless it
 // needs none, then enqueue its kernels on the stream.
 int run_batch(pgcm_key* key, BatchArgs a) {
@@ -1058,10 +1044,12 @@ int run_batch(pgcm_key* key, BatchArgs a) {
     BatchSurvey v;
     rc = survey_batch(a, &v);
     if (rc != PGCM_OK) return rc;
+    const RouteOptions options = route_options(key, a.fixed);
+    SwapShape shape{};
+    const Route route = route_batch(ShapeBatch{a.n, a.order, a.aad_len, a.len}, options, v, &shape);
     // the units, unless they are not wanted anyway; nothing touched so far
-    const bool spans = !a.fixed && !v.all_one_row && takes_spans(key, v.rows, v.longest);
     BatchPlan p{};
-    if (!spans) rc = plan_batch(key->forced_unit_power, key->wave_slots, a, &p);
+    if (!may_go_in_spans(options, v)) rc = plan_batch(key->forced_unit_power, key->wave_slots, a, &p);
     if (rc != PGCM_OK) return rc;
     int cur_device = -1;
     PGCM_HIP(hipGetDevice(&cur_device));
@@ -1069,11 +1057,7 @@ int run_batch(pgcm_key* key, BatchArgs a) {
     rc = note_capture(a);
     if (rc != PGCM_OK) return rc;
     if (a.fixed && a.n > kFixedMaxChunks) return PGCM_ERR_CAPACITY;
-    SwapShape shape{};
-    bool one_launch = swap_shape(ShapeBatch{a.n, a.order, a.aad_len, a.len}, (uint32_t)key->num_cu,
-                                 key->one_launch, key->forced_unit_power, v.all_small, &shape);
-    if (one_launch && spans && !shape.burst && !units_before_spans(shape.unit_power, v.rows, key->wave_slots))
-        one_launch = false;
+    const bool one_launch = route == Route::kOneLaunch;
     if (one_launch && shape.alone && a.n <= kArgChunks) return run_one_launch(key, nullptr, a, shape);
     Context* ctx = nullptr;
     if (a.fixed) {
@@ -1083,11 +1067,11 @@ int run_batch(pgcm_key* key, BatchArgs a) {
         rc = acquire_context(key, a.stream, &ctx);
         if (rc != PGCM_OK) return rc;
     }
-    if (one_launch)
+    if (one_launch) {
         rc = run_one_launch(key, ctx, a, shape);
-    else if (v.all_one_row)
+    } else if (route == Route::kOneRow) {
         rc = run_small_batch(key, ctx, a);
-    else if (spans) {
+    } else if (route == Route::kSpans) {
         KeyPart part{key, key->tables, (uint32_t)key->rounds, 0, a.n, v.rows, v.longest, 0};
         rc = run_span_batch(ctx, a, &part, 1);
     } else {
@@ -1146,7 +1130,7 @@ int run_batch_keys(pgcm_key* const* keys, size_t nkeys, const uint32_t* key_inde
         for (size_t k = 0; k < nkeys; ++k) {
             const KeyPart& part = parts[k];
             if (part.n == 0) continue;
-            if (!takes_spans(keys[k], part.rows, part.longest) ||
+            if (!takes_spans(route_options(keys[k], false), part.rows, part.longest) ||
                 !share_launch(1, part.n, part.rows, num_cu)) {
                 alone.push_back(k);
                 continue;
@@ -1477,7 +1461,7 @@ int pgcm_describe_schedule(size_t n, const uint64_t* len, uint32_t unit_bytes, u
         info->fold_count[l] = p.fold_count[l];
         info->fold_first[l] = p.fold_first[l];
     }
-    info->path = n == 0 ? 0 : v.all_one_row ? 1 : (v.all_small && n <= kSmallMaxChunks) ? 2 : 0;
+    info->path = n == 0 ? 0 : v.all_one_row() ? 1 : (v.all_small() && n <= kSmallMaxChunks) ? 2 : 0;
     if (image != nullptr) {
         if (image_capacity < w.upload_bytes) return PGCM_ERR_CAPACITY;
         memset(image, 0, w.upload_bytes);

@@ -36,7 +36,6 @@ __global__ void swap_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t iv
 // or, if it has a chunk to itself, as many as that takes.  It serves any key.  kLongIv: iv_len exceeds
 // kShortIvBytes.  kWords: at most eight wavefronts, and one pass.  kFold: sixteen, and at most kFoldPasses;
 // kSweep: kSweptPasses; kFoldShared: kFoldPasses - 1, and two workgroups fit a compute unit.
-enum class BurstKind { kWords, kFold, kSweep, kFoldShared };
 template <bool kDecrypt, bool kLongIv, BurstKind kKind>
 __global__ void burst_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t iv_len, SwapMeta meta,
                              ArriveSlot* slots, uint8_t* tags, uint8_t* ok, const GroupDesc* staged,

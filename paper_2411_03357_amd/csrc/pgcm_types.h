@@ -167,6 +167,7 @@ struct ArgBatch {
 // Passes a workgroup of sixteen wavefronts of the kernel for short bursts makes at most, at a time and in
 // all (of fewer wavefronts: one).
 constexpr uint32_t kFoldPasses = 4, kSweptPasses = 16;
+enum class BurstKind { kWords, kFold, kSweep, kFoldShared };
 // Workgroups of a chunk (KeyTables::hop has their distances) and of a launch.
 constexpr uint32_t kSwapChunkGroups = kHopEntries;
 constexpr uint32_t kSwapMaxGroups = 512;

@@ -1,0 +1,48 @@
+// Reads batches, a line each: compute units, one launch (0, 1), matrix hash, forced unit bytes, fixed
+// buffers, then for every chunk its length and its AAD's.  Prints which kernel takes each.
+// Test infrastructure.
+#include <cstdint>
+#include <iostream>
+#include <sstream>
+#include <string>
+#include <vector>
+
+#include "pgcm_routes.h"
+
+using namespace pgcm;
+
+int main() {
+    std::string line;
+    while (std::getline(std::cin, line)) {
+        std::istringstream in(line);
+        uint32_t num_cu = 0, unit_bytes = 0;
+        int one_launch = 0, matrix_hash = 0, fixed = 0;
+        in >> num_cu >> one_launch >> matrix_hash >> unit_bytes >> fixed;
+        uint32_t forced = 0;
+        while (unit_bytes >= 16u << (forced + 1)) ++forced;
+        std::vector<uint64_t> len;
+        std::vector<uint32_t> aad_len;
+        for (uint64_t l, a; in >> l >> a;) len.push_back(l), aad_len.push_back((uint32_t)a);
+        BatchSurvey v;
+        for (size_t i = 0; i < len.size(); ++i) v.add(len[i], aad_len[i]);
+        const RouteOptions o{num_cu, one_launch != 0, matrix_hash != 0, forced, fixed != 0};
+        SwapShape s{};
+        switch (route_batch(ShapeBatch{len.size(), nullptr, aad_len.data(), len.data()}, o, v, &s)) {
+            case Route::kOneRow: std::cout << "small\n"; break;
+            case Route::kSpans: std::cout << "span\n"; break;
+            case Route::kUnits: std::cout << "bulk\n"; break;
+            case Route::kOneLaunch:
+                if (!s.burst) {
+                    std::cout << "swap " << (16u << s.unit_power) << "\n";
+                    break;
+                }
+                switch (burst_kind(s, num_cu)) {
+                    case BurstKind::kWords: std::cout << "words\n"; break;
+                    case BurstKind::kFold: std::cout << "fold " << s.unit_power + s.spare << "\n"; break;
+                    case BurstKind::kSweep: std::cout << "sweep " << s.unit_power + s.spare << "\n"; break;
+                    case BurstKind::kFoldShared: std::cout << "shared\n"; break;
+                }
+        }
+    }
+    return 0;
+}

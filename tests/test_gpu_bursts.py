@@ -1,7 +1,8 @@
 """Batches that go to burst_kernel, at the edges of its shapes: the blocks of a wavefront, of a workgroup of
 four, eight and sixteen wavefronts and of two to four passes, with "block -1" in a pass, in one of its
 own and beside the first; chunks in one workgroup and in several; more chunks than compute units; AAD of
-every kind and IVs of other lengths — against the CPU oracle, bit for bit."""
+every kind and IVs of other lengths — against the CPU oracle, bit for bit.  (Which kind of burst_kernel
+and how many passes a shape takes: tests/test_routes.py.)"""
 import numpy as np
 import pytest
 
@@ -43,17 +44,20 @@ SHAPES = {
     "short_aad": ([0, 1] + _EDGES, [16, 0, 5, 64, 17, 1, 48]),
     # the AAD fills lanes, a pass, and is longer than goes in lanes
     "long_aad": ([0, 5, 1024, 4096, 4097, 8192], [1008, 1024, 1025, 16, 3000, 1024]),
-    # workgroups of 1, 2 and 4 passes, some of them short
+    # workgroups of one to four passes, some of them short; in 2 and 4 a chunk's first may make one more
     "two": ([300 * KIB, 8 * KIB + 16, 9000, 1], [0, 16, 70]),
     "passes_1": (_MORE + [200 * KIB], [0, 16]),
     "passes_2": ([v + 40 * 4096 for v in _MORE], [16, 0, 33]),
     "passes_4": ([v + 60 * 4096 for v in _MORE], [0, 0, 20]),
+    "even_2": ([512 * 4096 - 16], [0]),
+    "even_4": ([1024 * 4096 - 16 * 64], [1008]),
+    "even_4_some": ([v + 70 * 4096 for v in _MORE], [0, 0, 20]),
     # three passes, and chunks whose first workgroup makes one more than the others: of AAD alone, with
     # payload, and of a short last chunk
     "passes_3": ([600 * 4096 - 5], [0]),
     "spare_1": ([256 * 4096], [16]),
     "spare_1_payload": ([256 * 4096 + 100], [0]),
-    "spare_1_long_aad": ([256 * 4096 - 16], [3000]),
+    "spare_1_long_aad": ([256 * 4096], [3000]),
     "spare_2": ([512 * 4096 - 48 * 16], [1008]),
     "spare_3": ([768 * 4096 + 4095], [0]),
     "spare_of_some": ([64 * 4096] * 7 + [63 * 4096 + 1, 5], [16, 0, 40]),
@@ -66,7 +70,7 @@ SHAPES = {
     "sweeps_2_missing_2": ([85 * 6 * 4096] * 3, [0]),
     "sweeps_3": ([100 * 9 * 4096 + 1, 150 * 9 * 4096 - 16, 70000, 8200], [0, 1008, 40, 16]),
     "sweeps_4": ([256 * 14 * 4096 + 33], [20]),
-    "sweeps_of_each": ([14 * 4096 + 513 * i for i in range(200)], [16, 0, 3000, 7]),
+    "sweeps_of_each": ([14 * 4096 + 13 * i for i in range(200)], [16, 0, 3000, 7]),
     # more chunks than compute units: mixed, and all of much the same length
     "many_mixed": ([(37 * i * i) % 8192 + 1 for i in range(40)] + [20] * 260, [0, 9]),
     "many_even": ([4096 + 16 * (i % 3) for i in range(300)], [0, 16]),
@@ -83,7 +87,8 @@ def test_shapes(shape):
 
 
 @pytest.mark.parametrize("key_bytes,iv_bytes", [(16, 12), (24, 16), (32, 8), (16, 40), (32, 1040)])
-@pytest.mark.parametrize("shape", ["short_aad", "passes_1", "passes_4", "many_even"])
+@pytest.mark.parametrize("shape", ["short_aad", "passes_1", "passes_4", "sweeps_2_missing", "many_even",
+                                   "many_mixed"])
 def test_other_keys_and_ivs(shape, key_bytes, iv_bytes):
     lens, alens = SHAPES[shape]
-    _full_parity(_workload(shape, lens[:40] if shape != "many_even" else lens, alens, key_bytes, iv_bytes))
+    _full_parity(_workload(shape, lens[:40] if shape == "short_aad" else lens, alens, key_bytes, iv_bytes))

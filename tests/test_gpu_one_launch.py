@@ -1,9 +1,8 @@
 """Batches of few chunks that do not fill the chip are done by one kernel launch (the paper's
-swaps come a few chunks at a time, section 5.1).  Every shape that path has — a chunk of one
-unit, of one workgroup, of several workgroups whose sets the last one to arrive folds, runs of
-1, 2, 4, 8 and 16 sets per wavefront, empty chunks, ragged ends, AAD, in place, each forced unit
-size, decryption with rejected chunks — against the CPU oracle, bit for bit; and against the units'
-sequence of kernels, which must give the same bytes."""
+swaps come a few chunks at a time, section 5.1): in passes or, with a forced unit size, in units — a chunk
+of one workgroup, of several whose shares of the tag are added up, empty chunks, ragged ends, AAD, in
+place, each forced unit size, decryption with rejected chunks — against the CPU oracle, bit for bit;
+and against the units' sequence of kernels, which must give the same bytes."""
 import numpy as np
 import pytest
 import torch
@@ -95,9 +94,8 @@ def _check_against_oracle(w, unit_bytes=0, tamper=()):
 
 
 def test_one_chunk_of_each_shape():
-    # one unit (more than the 8 KiB of the short-transfer path); a few units in one workgroup;
-    # exactly 16, 17, 32, 33 units; several workgroups; runs of 1 .. 16 sets per wavefront
-    # (1 KiB units up to 4096 of them: 16 workgroups -> run 1, 256 -> run 16)
+    # around a whole number of passes (4 KiB) and of rows, from a few passes (more than the 8 KiB of a
+    # short transfer) to four for each of 256 workgroups
     for seed, ln in enumerate([8193, 9 * KIB, 16 * KIB, 16 * KIB + 1, 17 * KIB - 5, 32 * KIB,
                                33 * KIB + 7, 100 * KIB + 3, 320 * KIB, 512 * KIB + 9, MIB,
                                2 * MIB, 4 * MIB - 11, 4 * MIB]):

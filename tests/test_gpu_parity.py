@@ -26,13 +26,15 @@ def _oracle_encrypt(w, host_buf, idx=None):
     return cts, tags
 
 
-def _full_parity(w, flip=None, iv_entry=None, unit_bytes=0, matrix_hash=False):
+def _full_parity(w, flip=None, iv_entry=None, unit_bytes=0, matrix_hash=False, one_launch=True):
     """encrypt + decrypt-verify of the whole workload compared with the oracle on every byte;
     unit_bytes forces the scheduler's unit size (0: its own choice for the batch); matrix_hash
-    sends the batch through the unit kernel with its row hash on the matrix cores"""
+    sends the batch through the unit kernel with its row hash on the matrix cores; one_launch False
+    keeps longer chunks from the one-launch kernels and from spans"""
     host = w.payload_host()
     key = expand(w)
     pgcm.set_unit_bytes(key, unit_bytes)
+    pgcm.set_one_launch(key, one_launch)
     if matrix_hash:
         pgcm.set_matrix_hash(key, True)
         pgcm.set_one_launch(key, False)     # few chunks would otherwise skip the unit kernel

@@ -9,19 +9,22 @@ from test_gpu_parity import _full_parity
 
 pytestmark = pytest.mark.gpu
 
-# chunks, bytes of their whole blocks, forced unit size
+# chunks, bytes of their whole blocks, forced unit size, one launch; which kernel each takes:
+# tests/test_routes.py
 PATHS = {
-    "one launch, a row": (48, 16 * 20, 0),
-    "one launch, units": (64, 16 * 900, 0),
-    "a wavefront a chunk": (528, 16 * 7, 0),
-    "spans": (560, 16 * 700, 0),
-    "units": (48, 16 * 300, 2048),
+    "one launch, a pass": (48, 16 * 20, 0, True),
+    "one launch, a row a wavefront": (64, 16 * 900, 0, True),
+    "one launch, sweeps": (64, 16 * 5000, 0, True),
+    "one launch, units": (48, 16 * 700, 2048, True),
+    "one launch, units as they go": (240, 16 * 7700, 0, True),
+    "a wavefront a chunk": (528, 16 * 7, 0, True),
+    "spans": (560, 16 * 700, 0, True),
+    "units": (48, 16 * 700, 2048, False),
 }
 
 
-@pytest.mark.parametrize("path", PATHS)
-def test_every_length_of_a_last_block(path):
-    n, whole, unit_bytes = PATHS[path]
+def batch_of(path):
+    n, whole, unit_bytes, one_launch = PATHS[path]
     rng = np.random.default_rng([workloads.BASE_SEED, 1414, n])
     k = np.arange(n)
     lens = (whole + 1 + k % 16).astype(np.uint64)
@@ -29,9 +32,15 @@ def test_every_length_of_a_last_block(path):
     offsets, total = workloads._layout(lens)
     aad_off = np.zeros(n + 1, np.uint64)
     aad_off[1:] = np.cumsum(alens)
-    w = workloads.Workload(path, 950, rng.integers(0, 256, 32, dtype=np.uint8),
-                           workloads.iv_sequence(1 << 61, n), lens, offsets, total, "u8",
-                           rng.integers(0, 256, int(alens.sum()), dtype=np.uint8), aad_off)
+    return workloads.Workload(path, 950, rng.integers(0, 256, 32, dtype=np.uint8),
+                              workloads.iv_sequence(1 << 61, n), lens, offsets, total, "u8",
+                              rng.integers(0, 256, int(alens.sum()), dtype=np.uint8),
+                              aad_off), unit_bytes, one_launch
+
+
+@pytest.mark.parametrize("path", PATHS)
+def test_every_length_of_a_last_block(path):
+    w, unit_bytes, one_launch = batch_of(path)
     # rejected by the last bit of a last block of 1, 7 and 15 bytes
-    flips = [(i, int(lens[i]) - 1, 7, "ct") for i in (0, 6, 14)]
-    _full_parity(w, flip=flips, unit_bytes=unit_bytes)
+    flips = [(i, int(w.lens[i]) - 1, 7, "ct") for i in (0, 6, 14)]
+    _full_parity(w, flip=flips, unit_bytes=unit_bytes, one_launch=one_launch)

@@ -33,7 +33,7 @@ def _draw_length(rng):
 
 def _random_workload(seed):
     rng = np.random.default_rng([workloads.BASE_SEED, 4242, seed])
-    n = int(rng.integers(1, 48))
+    n = int(rng.integers(1, 48) if seed < 90 else rng.integers(300, 500))
     if seed % 5 == 0:
         lens = [min(_draw_length(rng), 8192) for _ in range(n)]     # small-transfer path
     else:
@@ -51,14 +51,35 @@ def _random_workload(seed):
     return workloads.with_cipher(w, key_bytes, iv_bytes), rng
 
 
+# seeds, forced unit size, one launch, and the kernels these batches take (tests/test_routes.py)
+WAYS = {
+    "as they go": (range(0, 48), 0, True, "fold sweep"),
+    "units in one launch": (range(61, 65), 2048, True, "swap"),
+    "units": (range(66, 70), 0, False, "bulk"),
+    "many": (range(91, 94), 0, True, "span"),
+}
+
+
 @pytest.mark.parametrize("first_seed", [0, 12, 24, 36])
 def test_random_batches_against_libcrypto(first_seed):
-    for seed in range(first_seed, first_seed + 12):
+    _compare(range(first_seed, first_seed + 12))
+
+
+@pytest.mark.parametrize("way", [w for w in WAYS if w != "as they go"])
+def test_random_batches_on_the_other_kernels(way):
+    seeds, unit_bytes, one_launch, _ = WAYS[way]
+    _compare(seeds, unit_bytes, one_launch)
+
+
+def _compare(seeds, unit_bytes=0, one_launch=True):
+    for seed in seeds:
         w, rng = _random_workload(seed)
         what = "seed %d: %d chunks, %d bytes, key %d, iv %d" % (
             seed, w.n, w.payload_bytes, w.key.size, w.ivs.shape[1])
         host = w.payload_host()
         key = expand(w)
+        pgcm.set_unit_bytes(key, unit_bytes)
+        pgcm.set_one_launch(key, one_launch)
         b = DeviceBatch(w, torch.from_numpy(host).cuda())
         b.cipher.fill_(0xEE)
         b.encrypt(key)

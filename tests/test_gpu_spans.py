@@ -39,7 +39,7 @@ SHAPES = {
     # shares of many rows
     "big": lambda r: (_even(r, 60, 500 * KIB, 2 * MIB) + [9 * MIB + 5], (16,), 1, 12),
     # IVs of several blocks, up to the edges of a row of 64 and beyond, hashed by the wavefronts that
-    # need them: chunks cut into spans, and the three kinds of one-launch batches
+    # need them: chunks cut into spans, and one-launch batches of one pass and of four
     "iv_17": lambda r: (_even(r, 90, 4 * KIB, 500 * KIB), (32, 16), 2, 17),
     "iv_1000": lambda r: (_even(r, 900, 40, 30 * KIB), (24,), 1, 1000),
     "iv_1024": lambda r: ([1, 5000, 0, 8 * KIB], (32,), 1, 1024),

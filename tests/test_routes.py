@@ -1,0 +1,87 @@
+"""The batches of the GPU tests go to the kernels that those tests name: the library's own rules
+(csrc/pgcm_routes.h), built for the CPU, say so for a device of 256 compute units.  Of burst_kernel the kind and
+the passes of a chunk's first workgroup are told apart, of swap_kernel the bytes of a unit."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import test_gpu_bursts
+import test_gpu_ragged_ends
+import test_gpu_random_batches
+import test_gpu_units_in_one_launch
+from test_sanitized_host_code import ENV, NATIVE, ROOT, SAN
+
+
+@pytest.fixture(scope="module")
+def kernels_of(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("routes") / "driver")
+    build = subprocess.run(["g++"] + SAN + ["-std=c++17", "-I" + os.path.join(ROOT, "paper_2411_03357_amd", "csrc"),
+                                            os.path.join(NATIVE, "route_driver.cpp"), "-o", exe],
+                           stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert build.returncode == 0, build.stdout
+
+    def run(batches):
+        """batches: (lengths, AAD lengths or None, forced unit bytes, one launch)"""
+        lines = []
+        for lens, alens, unit_bytes, one_launch in batches:
+            alens = np.zeros(len(lens), int) if alens is None else alens
+            lines.append("256 %d 0 %d 0 " % (one_launch, unit_bytes) +
+                         " ".join("%d %d" % (n, a) for n, a in zip(lens, alens)))
+        out = subprocess.run([exe], input="\n".join(lines) + "\n", stdout=subprocess.PIPE,
+                             stderr=subprocess.PIPE, text=True, env=ENV)
+        assert out.returncode == 0, out.stderr
+        return out.stdout.split("\n")[:-1]
+    return run
+
+
+def _of_workload(w, unit_bytes=0, one_launch=1):
+    return w.lens, [len(w.aad_of(i)) for i in range(w.n)], unit_bytes, one_launch
+
+
+def test_ragged_ends(kernels_of):
+    expected = {"one launch, a pass": "words", "one launch, a row a wavefront": "fold 1",
+                "one launch, sweeps": "sweep 5", "one launch, units": "swap 2048",
+                "one launch, units as they go": "swap 8192", "a wavefront a chunk": "small",
+                "spans": "span", "units": "bulk"}
+    got = {}
+    for path in test_gpu_ragged_ends.PATHS:
+        w, unit_bytes, one_launch = test_gpu_ragged_ends.batch_of(path)
+        got[path], = kernels_of([_of_workload(w, unit_bytes, one_launch)])
+    assert got == expected
+
+
+def test_bursts(kernels_of):
+    shapes = test_gpu_bursts.SHAPES
+    got = dict(zip(shapes, kernels_of([(lens, np.resize(alens, len(lens)), 0, 1)
+                                       for lens, alens in shapes.values()])))
+    # the most passes of a workgroup, a chunk's first
+    most = {"passes_1": 1, "passes_2": 3, "passes_3": 3, "passes_4": 3, "even_2": 2, "even_4": 4, "even_4_some": 4,
+            "spare_1": 2, "spare_1_payload": 2, "spare_1_long_aad": 2, "spare_2": 3, "spare_3": 4,
+            "spare_of_some": 3}
+    sweeps = {"sweeps_2": 2, "sweeps_2_whole": 2, "sweeps_2_spare": 3, "sweeps_2_missing": 2,
+              "sweeps_2_missing_2": 2, "sweeps_3": 3, "sweeps_4": 4, "sweeps_of_each": 4}
+    for name, kernel in got.items():
+        kind, passes = (kernel.split() + ["0"])[:2]
+        if name in most:
+            assert kernel == "fold %d" % most[name], (name, kernel)
+        elif name in sweeps:
+            assert kind == "sweep" and -(-int(passes) // 4) == sweeps[name], (name, kernel)
+        else:
+            assert kind in ("words", "fold", "shared"), (name, kernel)
+    assert {got[n] for n in ("many_even", "many_long")} == {"shared"} and got["many_mixed"] == "words"
+
+
+def test_units_in_one_launch(kernels_of):
+    for name, (lens, alens, unit_bytes, _, _) in test_gpu_units_in_one_launch.SHAPES.items():
+        got, = kernels_of([(lens, np.resize(alens, len(lens)), unit_bytes, 1)])
+        assert got == "swap %d" % (unit_bytes or 8192), name
+
+
+def test_random_batches(kernels_of):
+    ways = test_gpu_random_batches.WAYS
+    for way, (seeds, unit_bytes, one_launch, kinds) in ways.items():
+        batches = [_of_workload(test_gpu_random_batches._random_workload(s)[0], unit_bytes, one_launch)
+                   for s in seeds]
+        assert {k.split()[0] for k in kernels_of(batches)} == set(kinds.split()), way
