@@ -23,8 +23,10 @@ FLIPS_SMALL = [(0, 0, 0, "ct"), (12, 1023, 7, "ct"), (27, 8191, 0, "ct"), (1, 5,
 @pytest.mark.parametrize("key_bytes,iv_bytes", [(16, 12), (24, 12), (16, 8), (24, 16), (32, 60),
                                                 (32, 1), (16, 13), (24, 128)])
 def test_key_and_iv_lengths_both_paths(key_bytes, iv_bytes):
-    _full_parity(workloads.with_cipher(workloads.ragged_small(), key_bytes, iv_bytes),
-                 flip=FLIPS_RAGGED)
+    """bursts, units in one launch, units one kernel after the other, and short transfers"""
+    for unit_bytes, one_launch in ((0, True), (2048, True), (0, False)):
+        _full_parity(workloads.with_cipher(workloads.ragged_small(), key_bytes, iv_bytes),
+                     flip=FLIPS_RAGGED, unit_bytes=unit_bytes, one_launch=one_launch)
     _full_parity(workloads.with_cipher(workloads.small_transfers(), key_bytes, iv_bytes),
                  flip=FLIPS_SMALL)
 
@@ -36,8 +38,9 @@ def test_iv_entry_points_with_96_bit_ivs_equal_the_plain_ones():
 
 @pytest.mark.parametrize("key_bytes", [16, 24])
 def test_shorter_keys_on_a_kv_swap_batch(key_bytes):
-    """multi-unit chunks with a fold level, as in the headline workload, under the other keys"""
-    _full_parity(workloads.with_cipher(workloads.mini(2), key_bytes, 12))
+    """chunks of the headline workload under the other keys, in passes, and in units with a fold level"""
+    for one_launch in (True, False):
+        _full_parity(workloads.with_cipher(workloads.mini(2), key_bytes, 12), one_launch=one_launch)
 
 
 def test_counter_wrap_inside_chunks():
@@ -65,7 +68,8 @@ def test_counter_wrap_inside_chunks():
             offsets, total = workloads._layout(sub)
             w = workloads.Workload("wrap_%s_k%d" % (name, key_bytes), 5, key, ivs[sel], sub,
                                    offsets, total, "u8")
-            _full_parity(w, flip=[(0, 0, 0, "ct")])
+            for one_launch in (True, False) if name == "bulk" else (True,):
+                _full_parity(w, flip=[(0, 0, 0, "ct")], one_launch=one_launch)
             # and against libcrypto, which the oracle's wrap is pinned to as well
             host = w.payload_host()
             k = expand(w)

@@ -59,6 +59,7 @@ def test_fold_levels_against_the_oracle(forced_unit, levels):
     key = pgcm.expand_key(w.key)
     if forced_unit:
         pgcm.set_unit_bytes(key, forced_unit)
+        pgcm.set_one_launch(key, False)    # which few units of up to 16 KiB would go in
     b = DeviceBatch(w, w.payload_device())
     b.encrypt(key)
     b.decrypt(key)

@@ -21,7 +21,8 @@ SHAPES = {
     "spans": (lambda r: [int(v) for v in r.integers(200 * KIB, 450 * KIB, 60)], 0),
     "spans_uploaded": (lambda r: [int(v) for v in r.integers(1, 3 * KIB, 9000)], 0),
     "one_row": (lambda r: [int(v) for v in r.integers(0, 1009, 2000)], 0),
-    "units": (lambda r: [int(v) for v in r.integers(KIB, 900 * KIB, 40)], 16 * KIB),
+    "units": (lambda r: [int(v) for v in r.integers(KIB, 150 * KIB, 300)], 16 * KIB),
+    "one_launch_units": (lambda r: [int(v) for v in r.integers(KIB, 900 * KIB, 40)], 16 * KIB),
 }
 
 

@@ -111,6 +111,9 @@ def test_every_unit_size_full_parity(unit_bytes):
     _full_parity(w, flip=[(13, last, 7, "ct"), (25, 0, 0, "ct"), (2, 15, 3, "tag")],
                  unit_bytes=unit_bytes)
     _full_parity(workloads.mini(4), unit_bytes=unit_bytes)
+    if unit_bytes <= 16384:     # otherwise these go in one launch
+        _full_parity(w, unit_bytes=unit_bytes, one_launch=False)
+        _full_parity(workloads.mini(4), unit_bytes=unit_bytes, one_launch=False)
     key = pgcm.expand_key(w.key)
     for bad in (1, 512, 1000, 3000, 3 << 14, 1 << 25):
         with pytest.raises(pgcm.PgcmError) as e:
@@ -255,12 +258,23 @@ def test_two_keys_on_two_streams_at_once():
     kb.free()
 
 
-@pytest.mark.parametrize("lens", [[0, 40, 1000], [0, 3000, 8192], [0, 5, 70000, 1 << 20]])
-def test_long_aad_on_every_path(lens):
+# lengths, forced unit size, one launch, and the kernel (tests/test_routes.py)
+LONG_AAD = [([0, 40, 1000], 0, True, "words"), ([0, 3000, 8192], 0, True, "fold"),
+            ([0, 5, 70000, 1 << 20], 0, True, "fold"), ([0, 5, 70000, 1 << 20], 4096, True, "swap"),
+            ([0, 5, 70000, 1 << 20], 0, False, "bulk"), ([0, 40, 900] * 180, 0, True, "small"),
+            ([0, 40, 9000] * 90, 0, True, "span")]
+
+
+def _long_aad_lens(n):
+    return [[4099, 4096, 70001, 17][i % 4] if i % 50 < 4 else 20 for i in range(n)]
+
+
+@pytest.mark.parametrize("lens,unit_bytes,one_launch", [t[:3] for t in LONG_AAD])
+def test_long_aad_on_every_path(lens, unit_bytes, one_launch):
     """AAD of thousands of bytes (ragged, block-aligned, and 70 001 bytes) with an empty chunk, chunks
-    of one row, of a workgroup and of many"""
+    of one row, of a workgroup and of many; a wavefront a chunk, and spans"""
     seed, rng, key, iv0 = workloads._base(11, len(lens))
-    alens = [4099, 4096, 70001, 17][:len(lens)]
+    alens = _long_aad_lens(len(lens))
     la = np.array(lens, np.uint64)
     offsets, total = workloads._layout(la)
     aad_off = np.zeros(len(alens) + 1, np.uint64)
@@ -269,7 +283,7 @@ def test_long_aad_on_every_path(lens):
     w = workloads.Workload("long_aad", seed, key, workloads.iv_sequence(iv0, la.size), la, offsets,
                            total, "u8", aad, aad_off)
     last = len(lens) - 1
-    _full_parity(w, flip=[(last, int(lens[last]) - 1, 0, "ct")])
+    _full_parity(w, flip=[(last, int(lens[last]) - 1, 0, "ct")], unit_bytes=unit_bytes, one_launch=one_launch)
 
 
 def test_two_host_threads_each_with_its_key_and_stream():

@@ -8,9 +8,14 @@ import numpy as np
 import pytest
 
 import test_gpu_bursts
+import test_gpu_graphs
+import test_gpu_parity
 import test_gpu_ragged_ends
 import test_gpu_random_batches
+import test_gpu_reservations
 import test_gpu_units_in_one_launch
+import test_zz_no_alloc
+import workloads
 from test_sanitized_host_code import ENV, NATIVE, ROOT, SAN
 
 
@@ -23,11 +28,10 @@ def kernels_of(tmp_path_factory):
     assert build.returncode == 0, build.stdout
 
     def run(batches):
-        """batches: (lengths, AAD lengths or None, forced unit bytes, one launch)"""
+        """batches: (lengths, AAD lengths, forced unit bytes, one launch[, fixed buffers])"""
         lines = []
-        for lens, alens, unit_bytes, one_launch in batches:
-            alens = np.zeros(len(lens), int) if alens is None else alens
-            lines.append("256 %d 0 %d 0 " % (one_launch, unit_bytes) +
+        for lens, alens, unit_bytes, one_launch, *fixed in batches:
+            lines.append("256 %d 0 %d %d " % (one_launch, unit_bytes, bool(fixed)) +
                          " ".join("%d %d" % (n, a) for n, a in zip(lens, alens)))
         out = subprocess.run([exe], input="\n".join(lines) + "\n", stdout=subprocess.PIPE,
                              stderr=subprocess.PIPE, text=True, env=ENV)
@@ -85,3 +89,29 @@ def test_random_batches(kernels_of):
         batches = [_of_workload(test_gpu_random_batches._random_workload(s)[0], unit_bytes, one_launch)
                    for s in seeds]
         assert {k.split()[0] for k in kernels_of(batches)} == set(kinds.split()), way
+
+
+def test_captured_and_reserved_batches(kernels_of):
+    expected = {"alone": "fold", "one_launch": "fold", "one_launch_staged": "shared", "spans": "span",
+                "spans_uploaded": "span", "one_row": "small", "units": "bulk", "one_launch_units": "swap"}
+    for name, (lens, unit_bytes) in test_gpu_graphs.SHAPES.items():
+        lens = lens(np.random.default_rng([workloads.BASE_SEED, 5040, len(name)]))
+        got, = kernels_of([(lens, [20] * len(lens), unit_bytes, 1)])
+        assert got.split()[0] == expected[name], (name, got)
+    expected = {"one_launch": "sweep", "spans_few": "span", "spans_host": "span", "spans_uploaded": "span",
+                "one_row": "small"}
+    for name, lens in test_gpu_reservations.SHAPES.items():
+        lens = lens(np.random.default_rng([workloads.BASE_SEED, 8128, len(name)]))
+        got, = kernels_of([(lens, [20] * len(lens), 0, 1)])
+        assert got.split()[0] == expected[name], (name, got)
+
+
+def test_batches_in_fixed_buffers(kernels_of):
+    got = kernels_of([_of_workload(w) + (True,) for w in test_zz_no_alloc._batches()])
+    assert got == ["bulk", "swap 8192", "fold 1", "fold 4"], got
+
+
+def test_long_aad(kernels_of):
+    for lens, unit_bytes, one_launch, kernel in test_gpu_parity.LONG_AAD:
+        got, = kernels_of([(lens, test_gpu_parity._long_aad_lens(len(lens)), unit_bytes, one_launch)])
+        assert got.split()[0] == kernel, (lens[:4], got)

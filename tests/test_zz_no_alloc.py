@@ -31,18 +31,22 @@ def _workload(name, seed, lens, alens):
 
 def _batches():
     rng = np.random.default_rng([workloads.BASE_SEED, 31337])
-    # about 21 MB in 24 chunks: 8 KiB units, some 2600 partial sets and a fold level
+    # about 27 MB in 268 chunks: 8 KiB units, some 3500 partial sets and a fold level
+    many = [0, 1, 3 * MIB + 5, 2 * MIB, 320 * KIB, 16 * KIB - 1, 8 * KIB + 1, 33 * 16 * KIB] + \
+           [int(v) for v in rng.integers(1, 150 * KIB, 260)]
+    many_aad = [int(v) for v in rng.integers(0, 70, len(many))]
+    # about 18 MB in 24: 8 KiB units, a wavefront each, in one launch
     big = [0, 1, 3 * MIB + 5, 2 * MIB, 320 * KIB, 16 * KIB - 1, 8 * KIB + 1, 33 * 16 * KIB] + \
           [int(v) for v in rng.integers(1, 1400 * KIB, 16)]
     big_aad = [int(v) for v in rng.integers(0, 70, len(big))]
-    # a smaller one right after it: 1 KiB units
+    # a smaller one right after it: a pass a workgroup
     mid = [320 * KIB, 100 * KIB + 3, 0, 17, 64 * KIB]
     mid_aad = [16, 0, 5, 0, 33]
     # ... and one that takes the one-kernel path for short transfers (no device workspace)
     small = [1, 4096, 8192, 0, 1000]
     small_aad = [0, 0, 12, 7, 0]
-    return [_workload("static_big", 1, big, big_aad), _workload("static_mid", 2, mid, mid_aad),
-            _workload("static_small", 3, small, small_aad)]
+    return [_workload("static_many", 4, many, many_aad), _workload("static_big", 1, big, big_aad),
+            _workload("static_mid", 2, mid, mid_aad), _workload("static_small", 3, small, small_aad)]
 
 
 def test_static_entry_point_equals_encrypt_batch_on_calls_in_a_row():
@@ -62,13 +66,13 @@ def test_static_entry_point_equals_encrypt_batch_on_calls_in_a_row():
     first_cipher, first_tags = torch.empty_like(bs[0].cipher), torch.empty_like(bs[0].tags)
     torch.cuda.synchronize()
     free_before = torch.cuda.mem_get_info()[0]
-    # the static entry point: three calls back to back on one stream, sharing its one workspace,
+    # the static entry point: four calls back to back on one stream, sharing its one workspace,
     # then the first (largest) once more over what the smaller ones left there
-    order = [0, 1, 2, 0]
+    order = [0, 1, 2, 3, 0]
     got = []
     for k, i in enumerate(order):
         b = bs[i]
-        if k == 3:
+        if k == 4:
             torch.cuda.synchronize()
             first_cipher.copy_(b.cipher)                     # result of the first call
             first_tags.copy_(b.tags)
@@ -79,7 +83,7 @@ def test_static_entry_point_equals_encrypt_batch_on_calls_in_a_row():
                                   b.ptrs(b.cipher), b.tags, stream)
     torch.cuda.synchronize()
     assert torch.cuda.mem_get_info()[0] == free_before, "device memory was allocated or freed"
-    got += [(bs[1].cipher, bs[1].tags), (bs[2].cipher, bs[2].tags), (bs[0].cipher, bs[0].tags)]
+    got += [(bs[i].cipher, bs[i].tags) for i in order[1:]]
     for k, i in enumerate(order):
         assert torch.equal(got[k][0], want[i][0]), "ciphertext of call %d (%s)" % (k, ws[i].name)
         assert torch.equal(got[k][1], want[i][1]), "tags of call %d (%s)" % (k, ws[i].name)
