@@ -18,7 +18,7 @@
 //   * burst_kernel: up to sixty-four rows a compute unit, in one launch: a call is as long as its chain of
 //     dependent steps.
 //   * swap_kernel: more than that, in one launch, in units of one size, where they are filled well enough
-//     (eight rows, some 26 to 32 MiB) or spans are not to be had.
+//     (eight rows or sixteen, some 26 to 32 MiB) or spans are not to be had.
 //   * span_kernel: everything else, of one key or of several, in one launch: every wavefront of the
 //     chip an equal share of all rows.
 //   * small_kernel: many chunks of one row each, a wavefront per chunk.
@@ -1996,8 +1996,8 @@ template __global__ void final_kernel<true>(const KeyTables*, const ChunkDesc*, 
 // the length of the chain of dependent steps counts as much as the work.  Descriptors are kernel
 // arguments, or, for more chunks than fit those, one per workgroup in pinned memory.  Every
 // wavefront walks one unit, of eight or sixteen rows (batches of up to four go to burst_kernel) or of a
-// forced size, and then workgroups have as few wavefronts, at least four, as there are compute units for (a
-// row takes a lone wavefront 2.6 us, sixteen on one compute unit 4.3 us).  Then
+// forced size; unless the unit is of eight, workgroups have as few wavefronts, at least four, as there are
+// compute units for (a row takes a lone wavefront 2.6 us, sixteen on one compute unit 4.3 us).  Then
 //   1. the workgroup folds its units' sets into one as a tree in LDS (two to four multiplications
 //      from nibble tables, which take the round tables' place);
 //   2. all its threads form the 64 products of the set's lanes with H^64 .. H^1, bit by bit from

@@ -107,8 +107,10 @@ inline bool first_burst_choice(uint64_t passes, size_t n, uint64_t most, Groups 
 // with AAD in 257 workgroups of two passes: 256 take 11.8 us, four passes in 129 took 14.8; 8 of
 // 256 KiB with AAD 12.3, were 14.7), then with one more (2.3 to 3 MB in three 12.1, in four 14.2).
 // What is left has more than four rows for each wavefront of the device, and takes units of eight rows or
-// sixteen, a wavefront each, with a workgroup of sixteen a compute unit; units of a forced size take
-// the fewest wavefronts a workgroup, four at least, with which they still fit.
+// sixteen, a wavefront each, with a workgroup of sixteen a compute unit.  Units of sixteen rows, and those of a
+// forced size, take the fewest wavefronts a workgroup, four at least, with which they still fit: chunks
+// of whole 128 KiB without AAD, which eight wavefronts with units of sixteen rows cover, are a block
+// ("block -1") too long for sixteen with units of eight, as these have no further wavefront for it.
 constexpr uint32_t kLongUnitPower = kRowPower + 3;
 // forced: log2 of the blocks of a unit, or 0; all_small: no chunk is longer than kSmallChunkBytes.
 inline bool swap_shape(const ShapeBatch& a, uint32_t num_cu, bool one_launch, uint32_t forced, bool all_small,
@@ -165,7 +167,7 @@ inline bool swap_shape(const ShapeBatch& a, uint32_t num_cu, bool one_launch, ui
         if (forced || up == kUnitPower) return false;
         ++up;
     }
-    while (forced && wp > 2) {
+    while ((forced || up == kUnitPower) && wp > 2) {
         uint32_t l = 0;
         const uint64_t t = groups(up, wp - 1, &l);
         if (t > most) break;
@@ -181,9 +183,12 @@ inline bool swap_shape(const ShapeBatch& a, uint32_t num_cu, bool one_launch, ui
 // spans 21.5 and 3.75 a row of a wavefront, and 4 more on the host, which shows where a call is waited for
 // (back to back / waited for, units and spans: 12 of 2 MiB 47.4 / 60.4, 44.8 / 63.6; one of 28 MB
 // 47.5 / 60.1, 47.4 / 66.1; 14 of 2 MiB decrypted 46.3 / 59.1, 45.9 / 64.9; one of 31 MB decrypted
-// 46.4 / 59.1, 49.1 / 67.8).  Units of sixteen rows take 81, and spans no longer than that.
-inline bool units_before_spans(uint32_t unit_power, uint64_t rows, uint64_t wave_slots) {
-    return unit_power == kLongUnitPower && 2 * rows >= 13 * wave_slots;
+// 46.4 / 59.1, 49.1 / 67.8).  Units of sixteen rows take 50 with eight wavefronts a workgroup (one of 32 MiB
+// 50.0 / 62.8, 52.0 / 71.0, decrypted 48.8 / 62.0, 51.0 / 70.2; 256 of 128 KiB 50.2 / 68.1, 51.2 / 73.0; 228 of
+// them, 7.1 rows a wavefront, back to back 50.1, 49.1) and 81 with sixteen, and spans no longer than that.
+inline bool units_before_spans(const SwapShape& s, uint64_t rows, uint64_t wave_slots) {
+    if (s.unit_power == kLongUnitPower) return 2 * rows >= 13 * wave_slots;
+    return s.wave_power == 3 && 2 * rows >= 15 * wave_slots;
 }
 
 }  // namespace pgcm

@@ -53,7 +53,7 @@ inline Route route_batch(const ShapeBatch& a, const RouteOptions& o, const Batch
     const bool spans = may_go_in_spans(o, v);
     if (swap_shape(a, o.num_cu, o.one_launch, o.forced_unit_power, v.all_small(), shape) &&
         (!spans || shape->burst ||
-         units_before_spans(shape->unit_power, v.rows, (uint64_t)o.num_cu * kWavesPerGroup)))
+         units_before_spans(*shape, v.rows, (uint64_t)o.num_cu * kWavesPerGroup)))
         return Route::kOneLaunch;
     return v.all_one_row() ? Route::kOneRow : spans ? Route::kSpans : Route::kUnits;
 }

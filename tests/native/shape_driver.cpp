@@ -131,14 +131,16 @@ static void check(const ShapeBatch& a, uint32_t num_cu, uint32_t forced) {
     }
     ++g_units;
     CHECK(considered && !s.burst && s.groups <= most && s.unit_power <= kUnitPower && s.wave_power >= 2);
-    // of the sizes and numbers of wavefronts that would go, the smallest
+    // the smallest size that would go with sixteen wavefronts, and then the fewest wavefronts
     auto units_fit = [&](uint32_t up, uint32_t wp) {
         uint64_t sum = 0;
         for (size_t k = 0; k < a.n; ++k) sum += swap_groups(a, a.at(k), up, wp);
         return sum <= most;
     };
-    CHECK(units_fit(s.unit_power, s.wave_power) && (s.wave_power == 2 || !units_fit(s.unit_power, s.wave_power - 1)));
-    if (!forced) CHECK(s.wave_power == 4 && !units_fit(s.unit_power - 1, 4) && s.unit_power >= kLongUnitPower);
+    uint32_t up = forced ? forced : kMinUnitPower + 1, wp = 4;
+    while (!forced && up < kUnitPower && !units_fit(up, wp)) ++up;
+    while (wp > 2 && units_fit(up, wp - 1)) --wp;
+    CHECK(s.unit_power == up && s.wave_power == wp);
     uint64_t sum = 0;
     bool alone = true;
     for (size_t k = 0; k < a.n; ++k) {
@@ -156,17 +158,19 @@ int main() {
         const size_t n = log_between(1, trial % 4 ? 290 : 600);
         const int kind = trial % 5;
         const double lo = log_between(1, 3e6), hi = lo * log_between(1, 1000);
+        const bool whole = kind == 4 && below(2);  // whole 128 KiB, which sixteen rows of eight wavefronts cover
         std::vector<uint64_t> len(n);
-        std::vector<uint32_t> aad_len(below(3) ? n : 0), order(n);
+        std::vector<uint32_t> aad_len(!whole && below(3) ? n : 0), order(n);
         for (size_t i = 0; i < n; ++i) {
             order[i] = (uint32_t)(n - 1 - i);
             len[i] = kind == 0   ? log_between(lo, hi)
                      : kind == 1 ? below(kSmallChunkBytes + 1)
                      : kind == 2 ? 4096 * (1 + below(64)) - below(2) * 16
                      : kind == 3 ? (below(5) ? below(2000) : log_between(1000, 3e7))
-                                 : (uint64_t)lo;
+                                 : whole ? (1 + below(16)) << 17
+                                         : (uint64_t)lo;
             // within what is considered, mostly
-            if (below(8)) len[i] = 1 + len[i] % ((size_t)64 * 1024 * num_cu / n + 9000);
+            if (!whole && below(8)) len[i] = 1 + len[i] % ((size_t)64 * 1024 * num_cu / n + 9000);
             if (!aad_len.empty()) aad_len[i] = below(4) ? below(80) : below(1200);
         }
         const ShapeBatch a{n, below(2) ? order.data() : nullptr, aad_len.empty() ? nullptr : aad_len.data(),

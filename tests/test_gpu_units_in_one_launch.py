@@ -16,6 +16,9 @@ SHAPES = {
     "one": ([28 * 10**6 + 5], [40], 0, 32, 12),
     "a_layer": ([2 * MIB] * 14, [0], 0, 24, 40),
     "staged": ([123 * 1000 + 33 * (i % 16) for i in range(240)], [16, 0, 1024], 0, 16, 12),
+    # units of sixteen rows, eight wavefronts: chunks without AAD that they cover to the block
+    "whole": ([32 * MIB], [0], 0, 32, 12),
+    "whole_staged": ([128 * KIB] * 255 + [128 * KIB - 15], [0], 0, 16, 40),
     "sixteen_wavefronts": ([7 * MIB + 100, 0, 50 * KIB], [0, 5, 33], 2048, 16, 60),
     "eight_wavefronts": ([3 * MIB - 11, 0, 50 * KIB, 9 * KIB - 1], [16, 0, 3000, 7], 2048, 24, 16),
     "four_wavefronts": ([70 * KIB + i for i in range(12)], [1008, 20, 0], 2048, 32, 1040),

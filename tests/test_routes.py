@@ -80,7 +80,16 @@ def test_bursts(kernels_of):
 def test_units_in_one_launch(kernels_of):
     for name, (lens, alens, unit_bytes, _, _) in test_gpu_units_in_one_launch.SHAPES.items():
         got, = kernels_of([(lens, np.resize(alens, len(lens)), unit_bytes, 1)])
-        assert got == "swap %d" % (unit_bytes or 8192), name
+        assert got == "swap %d" % (unit_bytes or (16384 if name.startswith("whole") else 8192)), name
+
+
+def test_units_or_spans(kernels_of):
+    """sixteen rows a unit for a batch of 7.5 rows a wavefront and more, if eight wavefronts a workgroup do"""
+    kib = 1024
+    got = kernels_of([([128 * kib] * n, [0] * n, 0, 1) for n in (256, 241, 228, 140)] +
+                     [([2048 * kib] * 16, [0] * 16, 0, 1), ([2048 * kib] * 16, [16] * 16, 0, 1),
+                      ([33 << 20], [0], 0, 1)])
+    assert got == ["swap 16384", "swap 16384", "span", "span", "swap 16384", "span", "span"], got
 
 
 def test_random_batches(kernels_of):
