@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "../../include/pgcm.h"
+#include "pgcm_contexts.h"
 #include "pgcm_kernels.h"
 #include "pgcm_one_launch.h"
 #include "pgcm_routes.h"
@@ -40,13 +41,6 @@ inline bool hip_failed(hipError_t e) {
 // used it has ended on its stream, so this is how many batches the host may run ahead of the GPU
 constexpr int kStages = 4;
 constexpr uint32_t kTimingRing = 256;
-// contexts that could go to another stream a key keeps before it starts re-binding the least recently
-// used one of them to a new stream
-constexpr size_t kMaxContexts = 16;
-// contexts up to which a key lets them become such that could not
-constexpr size_t kMaxQuietContexts = 8;
-// batches in a row on one stream after which a context may leave their end unmarked
-constexpr uint32_t kQuietStreak = 32;
 // limits of the entry point that allocates nothing (pgcm_encrypt_batch_static)
 constexpr size_t kScratchBytes = PGCM_STATIC_WORKSPACE_BYTES;
 constexpr size_t kFixedMaxChunks = PGCM_STATIC_MAX_CHUNKS;
@@ -126,7 +120,7 @@ struct KeptBuffer {
 // that use one context are ordered by the stream the context is bound to, which is what makes
 // reusing its buffers from batch to batch safe; batches on different streams (or from different
 // host threads) take different contexts.
-struct Context {
+struct Context : Binding {
     bool growable = true;   // false: the buffers are fixed and a batch that needs more is refused
     uint8_t* stage[kStages] = {};
     size_t stage_cap[kStages] = {};
@@ -148,21 +142,9 @@ struct Context {
     std::vector<KeptBuffer> graph_buffers;
     SpanScratch scratch;     // of the call that is using the context
     uint64_t allocations = 0;  // times a batch or pgcm_reserve had to get any of these more room
-    // binding
-    hipStream_t stream = nullptr;
-    bool bound = false;        // has run a batch on `stream`
-    bool in_call = false;      // a host thread is inside a batch call with it
-    int last_stage = -1;       // stage whose event marks the end of its most recent batch, unless
-    bool unmarked = false;     // nothing does (see `quiet`)
-    uint64_t last_use = 0;
-    // The stream has used the context long enough, and there are few enough of them, that batches
-    // which use no staging buffer end unmarked: an event a batch costs the host up to 3.3 us, 2.3 us a
-    // call where calls follow each other (one 320 KiB block 11.9 -> 9.2 us, a 2 MiB piece 13.4 -> 11.8;
-    // on machines that take its interrupts quickly nothing).  Without that mark the context is never
-    // given to another stream, so only while there are few of them; streams that come and go have
-    // kMaxContexts beside those.
-    uint32_t streak = 0;       // batches in a row on `stream`
-    bool quiet = false;
+    // stage whose event marks the end of its most recent batch, unless nothing does
+    int last_stage = -1;
+    bool left_no_mark = false;
 };
 
 }  // namespace
@@ -299,40 +281,25 @@ int ensure_work(Context* c, size_t bytes, hipStream_t stream) {
     return PGCM_OK;
 }
 
-// The context a batch on `stream` runs with.  In order of preference: a context already bound to
-// the stream; one whose last batch has ended (it is re-bound); a new one; and, once the key has
-// kMaxContexts that can be re-bound, the least recently used one, after waiting for its last batch.  Never
-// taken are contexts that another host thread is using at this moment.  Never re-bound are those whose
-// batches a graph replays, and those whose last batch left no mark to wait for, at most kMaxQuietContexts
-// (`quiet`); they stay with their streams and leave the others their number.
+void release_context(pgcm_key* key, Context* c) {
+    if (c == &key->fixed) return;
+    std::lock_guard<std::mutex> lock(key->mu);
+    leave_call(c, c->captured, c->left_no_mark);
+}
+
+// The context a batch on `stream` runs with (pick_context).
 int acquire_context(pgcm_key* key, hipStream_t stream, Context** out) {
     std::unique_lock<std::mutex> lock(key->mu);
-    Context* pick = nullptr;
-    for (Context* c : key->contexts)
-        if (!c->in_call && c->bound && c->stream == stream) { pick = c; break; }
     bool must_wait = false;
-    if (pick == nullptr) {
-        Context* lru = nullptr;
-        size_t kept = 0;  // that can be re-bound
-        for (Context* c : key->contexts) {
-            if (c->captured || c->unmarked) continue;
-            ++kept;
-            if (c->in_call) continue;
-            // free for re-binding: never bound, or its last batch has ended.  (A context that
-            // pgcm_reserve has bound and no batch has used yet is left for its stream.)
-            if (!c->bound || (c->last_stage >= 0 &&
-                              hipEventQuery(c->stage_done[c->last_stage]) == hipSuccess)) {
-                pick = c;
-                break;
-            }
-            if (lru == nullptr || c->last_use < lru->last_use) lru = c;
-        }
-        (void)hipGetLastError();  // a query that said "not ready" is not an error of this call
-        if (pick == nullptr && lru != nullptr && kept >= kMaxContexts) {
-            pick = lru;
-            must_wait = pick->last_stage >= 0;
-        }
-    }
+    // (A context that pgcm_reserve has bound and no batch has used yet is left for its stream.)
+    auto ended = [](const Context* c) {
+        if (c->last_stage < 0) return false;
+        if (hipEventQuery(c->stage_done[c->last_stage]) == hipSuccess) return true;
+        (void)hipGetLastError();  // "not ready" is not an error of this call
+        return false;
+    };
+    Context* pick = pick_context(key->contexts, stream, ended, &must_wait);
+    must_wait = must_wait && pick->last_stage >= 0;
     if (pick == nullptr) {
         Context* c = new (std::nothrow) Context();
         if (c == nullptr) return PGCM_ERR_NOMEM;
@@ -351,19 +318,12 @@ int acquire_context(pgcm_key* key, hipStream_t stream, Context** out) {
         }
         pick = c;
     }
-    pick->in_call = true;
-    pick->last_use = ++key->use_tick;
-    const bool same_stream = pick->bound && pick->stream == stream;
-    if (!same_stream) pick->streak = 0;
-    else if (pick->streak < kQuietStreak) ++pick->streak;
-    pick->quiet = pick->streak >= kQuietStreak && !pick->captured &&
-                  key->contexts.size() <= kMaxQuietContexts;
+    enter_call(key->contexts, pick, stream, ++key->use_tick);
     lock.unlock();
     if (pick->bound && pick->stream != stream) {
         // re-binding: everything it enqueued on its old stream must have ended
         if (must_wait && hip_failed(hipEventSynchronize(pick->stage_done[pick->last_stage]))) {
-            std::lock_guard<std::mutex> relock(key->mu);
-            pick->in_call = false;
+            release_context(key, pick);
             return PGCM_ERR_HIP;
         }
         for (int s = 0; s < kStages; ++s) pick->stage_used[s] = false;
@@ -371,12 +331,6 @@ int acquire_context(pgcm_key* key, hipStream_t stream, Context** out) {
     pick->stream = stream;
     *out = pick;
     return PGCM_OK;
-}
-
-void release_context(pgcm_key* key, Context* c) {
-    if (c == &key->fixed) return;
-    std::lock_guard<std::mutex> lock(key->mu);
-    c->in_call = false;
 }
 
 // The event that marks the end of a batch is attached to the batch's last kernel: the kernel's own
@@ -403,7 +357,7 @@ int end_of_batch(Context* c, int s, unsigned long long capture, bool staged, boo
     if (capture == 0) {
         if (staged) c->stage_used[s] = true;
         if (marked) c->last_stage = s;
-        c->unmarked = !marked;
+        c->left_no_mark = !marked;
         return PGCM_OK;
     }
     c->captured = true;
