@@ -10,7 +10,7 @@ namespace pgcm {
 // contexts that could go to another stream a key keeps before it starts re-binding the least recently
 // used one of them to a new stream
 constexpr size_t kMaxContexts = 16;
-// contexts up to which a key lets them become such that could not
+// contexts that could not, at most
 constexpr size_t kMaxQuietContexts = 8;
 // batches in a row on one stream after which a context may leave their end unmarked
 constexpr uint32_t kQuietStreak = 32;
@@ -58,6 +58,16 @@ C* pick_context(const std::vector<C*>& contexts, const void* stream, Ended ended
     return *must_wait ? lru : nullptr;
 }
 
+// The contexts besides c whose last batch left no mark, or may be leaving none now.  (All contexts counted
+// would do as well for the bound, but contexts stay until the key is freed: a key that once had more of
+// them would leave no end unmarked again.)
+template <class C>
+size_t quiet_contexts(const std::vector<C*>& contexts, const C* c) {
+    size_t n = 0;
+    for (const C* o : contexts) n += o != c && (o->unmarked || (o->in_call && o->quiet));
+    return n;
+}
+
 // A call on `stream` begins with c, which is one of `contexts` by now.
 template <class C>
 void enter_call(const std::vector<C*>& contexts, C* c, const void* stream, uint64_t tick) {
@@ -65,7 +75,8 @@ void enter_call(const std::vector<C*>& contexts, C* c, const void* stream, uint6
     c->last_use = tick;
     if (!c->bound || c->stream != stream) c->streak = 0;
     else if (c->streak < kQuietStreak) ++c->streak;
-    c->quiet = c->streak >= kQuietStreak && !c->replayed && contexts.size() <= kMaxQuietContexts;
+    c->quiet = c->streak >= kQuietStreak && !c->replayed &&
+               quiet_contexts(contexts, c) < kMaxQuietContexts;
 }
 
 // ... and ends.

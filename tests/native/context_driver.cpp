@@ -53,7 +53,41 @@ static void batch(void* stream, uint64_t random) {
     CHECK(unmarked <= kMaxQuietContexts && others <= kMaxContexts + 8);  // a new one a thread at a time
 }
 
+// A key that has had many contexts at a time: streams that settle afterwards still leave their ends
+// unmarked, kMaxQuietContexts of them.
+static void settle_late() {
+    std::vector<Context*> own;
+    static char streams[24];
+    Context all[24];
+    for (int i = 0; i < 24; ++i) {
+        own.push_back(&all[i]);
+        all[i].stream = &streams[i], all[i].bound = true;
+    }
+    uint64_t t = 0;
+    size_t quiet = 0;
+    for (int i = 0; i < 24; ++i) {
+        for (uint32_t k = 0; k <= kQuietStreak; ++k) {
+            bool must_wait;
+            Context* c = pick_context(own, &streams[i], [](const Context*) { return false; }, &must_wait);
+            CHECK(c == &all[i] && !must_wait);
+            enter_call(own, c, c->stream, ++t);
+            CHECK(!c->quiet || k + 1 >= kQuietStreak);
+            leave_call(c, false, c->quiet);
+        }
+        quiet += all[i].unmarked;
+    }
+    CHECK(quiet == kMaxQuietContexts);
+    // one that gives its place back
+    enter_call(own, &all[0], all[0].stream, ++t);
+    leave_call(&all[0], false, false);
+    enter_call(own, &all[20], all[20].stream, ++t);
+    CHECK(all[20].quiet);
+    enter_call(own, &all[0], all[0].stream, ++t);
+    CHECK(!all[0].quiet);
+}
+
 int main() {
+    settle_late();
     static char streams[64];
     std::vector<std::thread> threads;
     for (int t = 0; t < 6; ++t)

@@ -120,8 +120,8 @@ def test_many_streams_share_and_rebind_contexts():
 
 
 def test_streams_come_and_go_beside_settled_ones():
-    """streams that have used the key for long leave no mark at the end of their batches: more streams
-    than there are contexts come and go beside them, and all results stay exact"""
+    """streams that have used the key for long leave no mark at the end of their batches: others come and go
+    beside them, their contexts re-bound once their batches have ended, and all results stay exact"""
     w = workloads.mini(2)
     host = w.payload_host()
     key = pgcm.expand_key(w.key)
@@ -149,6 +149,43 @@ def test_streams_come_and_go_beside_settled_ones():
             for st, b in zip(streams[3 + r:6 + r] + settled, batches[3:] + batches[:3]):
                 b.encrypt(key, stream=st)
             check((turn, r))
+    key.free()
+
+
+def test_more_streams_in_flight_than_contexts_beside_settled_ones():
+    """beside three settled streams, batches of 23 others are under way at once: from the seventeenth on the
+    least recently used context that can be re-bound is waited for, and all results stay exact"""
+    w = workloads.mini(2)
+    host = w.payload_host()
+    key = pgcm.expand_key(w.key)
+    cts, tags = _oracle_results(w, host)
+    streams = [torch.cuda.Stream() for _ in range(26)]
+    batches = [DeviceBatch(w, torch.from_numpy(host).cuda()) for _ in range(26)]
+    for _ in range(40):
+        for st, b in zip(streams[:3], batches):
+            b.encrypt(key, stream=st)
+    torch.cuda.synchronize()
+    for turn in range(2):
+        # some 20 ms of work that the others come behind
+        gate, opened = torch.cuda.Stream(), torch.cuda.Event()
+        with torch.cuda.stream(gate):
+            a = torch.ones(8192, 8192, device="cuda")
+            for _ in range(2):
+                a = (a @ a).clamp_(0, 1)
+            opened.record(gate)
+        for k, (st, b) in enumerate(zip(streams[3:], batches[3:])):
+            st.wait_event(opened)
+            b.encrypt(key, stream=st)
+            batches[k % 3].encrypt(key, stream=streams[k % 3])
+        torch.cuda.synchronize()
+        for k, b in enumerate(batches):
+            cipher = b.cipher.cpu().numpy()
+            for i in range(w.n):
+                assert np.array_equal(w.chunk(cipher, i), cts[i]), (turn, k, i)
+            assert np.array_equal(b.tags.cpu().numpy().reshape(-1, 16), tags), (turn, k)
+            b.cipher.zero_()
+            b.tags.zero_()
+        torch.cuda.synchronize()
     key.free()
 
 
