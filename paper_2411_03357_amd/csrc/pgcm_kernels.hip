@@ -31,6 +31,7 @@
 
 #include <type_traits>
 
+#include "pgcm_arrive.h"
 #include "pgcm_kernels.h"
 
 namespace pgcm {
@@ -2110,19 +2111,19 @@ __device__ __forceinline__ GfWords times_spread(const GfWords& v, const GfWords&
     return z;
 }
 
-// Adds `word`, of four lanes of a wavefront, to an accumulator that `of` workgroups add to, the caller's as
-// number `member`, and counts it in, by the same atomic: the lower half holds the words added so far, the
-// upper half a bit for each workgroup that has added its own.  True in the lanes that find theirs complete:
-// `word` is the whole sum, and the accumulator is left zero.
-__device__ __forceinline__ bool add_and_arrive(uint64_t* at, uint32_t member, uint32_t of, uint32_t& word) {
-    const uint64_t own = (uint64_t)(1u << member) << 32 | word;
-    const uint64_t now =
-        own ^ __hip_atomic_fetch_xor(at, own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    word = (uint32_t)now;
-    const bool whole = (uint32_t)(now >> 32) == 0xFFFFFFFFu >> (32 - of);
-    if (whole) __hip_atomic_store(at, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return whole;
-}
+// The slots' operations, at device scope
+struct SlotMemory {
+    static __device__ __forceinline__ uint64_t fetch_xor(uint64_t* at, uint64_t v) {
+        return __hip_atomic_fetch_xor(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    static __device__ __forceinline__ uint32_t fetch_add(uint32_t* at, uint32_t v) {
+        return __hip_atomic_fetch_add(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    template <class T>
+    static __device__ __forceinline__ void clear(T* at) {
+        __hip_atomic_store(at, (T)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+};
 
 // One trip to memory and back where it was three (the share stored, an arrival counted when it had got
 // there, the shares read by the last), or two instead of four: a chunk of 64 KiB in 7.7 us instead of 8.2,
@@ -2142,15 +2143,12 @@ __device__ __forceinline__ bool last_of_chunk(ArriveSlot* slots, uint32_t g, uin
     asm volatile("" : "+v"(t0), "+v"(t1), "+v"(t2), "+v"(t3));  // (chosen from as an array, they go by way of memory)
     uint32_t word = lane == 0 ? t0 : lane == 1 ? t1 : lane == 2 ? t2 : t3;
     bool whole = lane < 4;
-    uint32_t member = g, of = n;
+    ChunkMember member{g, n};
     if (n > kArriveSet) {
-        const uint32_t set = g / kArriveSet, first = set * kArriveSet;
-        if (whole)
-            whole = add_and_arrive(&slots[first].of_set[lane], g - first,
-                                   n - first < kArriveSet ? n - first : kArriveSet, word);
-        member = set, of = (n + kArriveSet - 1) / kArriveSet;
+        if (whole) whole = add_in_set<SlotMemory>(slots, g, n, lane, word);
+        member = set_of_chunk(g, n);
     }
-    if (whole) whole = add_and_arrive(&slots->of_chunk[lane], member, of, word);
+    if (whole) whole = add_in_chunk<SlotMemory>(slots, member, lane, word);
     const uint32_t mine = (uint32_t)__ballot(whole);
     if (mine == 0) return false;
     if (mine == 0xF) {
@@ -2170,17 +2168,13 @@ __device__ __forceinline__ bool last_of_chunk(ArriveSlot* slots, uint32_t g, uin
                               : lane == 2 ? received.w[2]
                                           : received.w[3];
     const bool differs = __ballot(whole && word != expected) != 0;
-    // words compared, and above them the workgroups that found a difference
-    uint32_t* const verdict = reinterpret_cast<uint32_t*>(slots[1].of_chunk);
-    const uint32_t own = (uint32_t)__popc(mine) + (differs ? 256u : 0u);
-    uint32_t now = 0;
-    if (lane == 0)
-        now = own + __hip_atomic_fetch_add(verdict, own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    now = __builtin_amdgcn_readfirstlane(now);
-    if (now % 256 != 4) return false;
-    if (lane == 0) __hip_atomic_store(verdict, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t count = 0;
+    if (lane == 0) count = count_verdict<SlotMemory>(slots, (uint32_t)__popc(mine), differs);
+    count = __builtin_amdgcn_readfirstlane(count);
+    if (!verdict_whole(count)) return false;
+    if (lane == 0) clear_verdict<SlotMemory>(slots);
     tag = received;
-    if (now >= 256) tag.w[0] = ~tag.w[0];
+    if (verdict_differs(count)) tag.w[0] = ~tag.w[0];
     return true;
 }
 
