@@ -2512,11 +2512,15 @@ PGCM_INSTANTIATE_SWAP(true);
 // ------------------------------------------------------------------------------------------
 // Short bursts in ONE launch: so few rows that the time of a call is that of its chain of dependent steps.
 // A workgroup of 4, 8 or 16 wavefronts makes one or more passes over 64, 128 or 256 blocks.
-//   * Of one pass, a wavefront takes sixteen blocks, a quad of lanes a block and a lane a column of its
-//     state: a round is four lookups in every lane, whose results go to the lanes beside it, where a lane
-//     with a block to itself makes sixteen (64 blocks, four wavefronts instead of one: 1.8 -> 1.3 us).  Of
-//     several passes it takes a row of 64 blocks, a lane a block: more steps, but fewer for each block
-//     (128 KiB... 2 MiB: eight rows a compute unit, 12.5 us in quads, 11.9 in rows).
+//   * Of a chunk that begins with one pass, that pass is made in quads: a wavefront takes sixteen blocks, a
+//     quad of lanes a block and a lane a column of its state.  A round is four lookups in every lane,
+//     whose results go to the lanes beside it, where a lane with a block to itself makes sixteen (64
+//     blocks, four wavefronts instead of one: 1.8 -> 1.3 us).  Workgroups of sixteen wavefronts whose last
+//     block has more than a pass of payload before its end take rows, a wavefront 64 blocks, a lane a
+//     block: more steps, but fewer for each block (128 KiB... 2 MiB: eight rows a compute unit, 12.5 us in
+//     quads, 11.9 in rows).  Where such a workgroup makes a single pass there is nothing in it (us, rows
+//     and quads: 64 KiB 7.1 and 7.0, 320 KiB 7.6 and 7.7, decrypted 7.6 and 7.5, 1 MiB 7.8 and 7.8, 20 of
+//     40 KiB decrypted 7.8 and 7.9), so the number of passes is not asked for.
 //   * The round tables are te[0] and te[1] alone, 32 times each, 64 KiB: te[2] and te[3] are these turned
 //     by two bytes.  Half the room to fill (0.8 us of 3.5), no lookups that collide (te[0..3] sixteen
 //     times each, as short transfers once had them, took twice the cycles), and two workgroups fit a
@@ -2903,7 +2907,8 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     const uint32_t sweeps = kSweep ? (have + kFoldPasses - 1) / kFoldPasses : 1;
     const uint32_t folded = sweeps > 1 ? kFoldPasses : have;
     const bool has_mask = g == 0;
-    // Several passes: a row a wavefront, a lane a block, which takes fewer instructions a block
+    // Behind a chunk's first pass of payload: a row a wavefront, a lane a block, which takes fewer instructions
+    // a block (see above)
     const bool by_rows = kRows && nblk - ((int64_t)behind << pass_power) > pass_blocks;
     // E_K(J0) is the keystream of "block -1", if that is in a pass of this workgroup (the AAD before it may
     // have one of its own) with payload; otherwise it is made beside the first pass
@@ -3468,7 +3473,7 @@ PGCM_INSTANTIATE_SPAN(true, true);
 
 // ------------------------------------------------------------------------------------------
 // Many chunks of one row (of the paper's "other I/O", usually < 8 KB, and the 1-byte NOPs of its
-// error handler, sections 4.2 and 5.3; up to kSmallMaxChunks of them go to swap_kernel): ONE kernel
+// error handler, sections 4.2 and 5.3; up to kSmallMaxChunks of them go to burst_kernel): ONE kernel
 // from the first block to the tag, a wavefront per chunk, descriptors read straight from pinned
 // host memory.  LDS: the four round tables once (lookups may collide; there are few) and the nibble
 // tables the chunks at hand need.
