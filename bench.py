@@ -28,27 +28,27 @@ LDS_PEAK_GCYCLES = 256 * 2.4               # 256 CUs, one LDS pipe each, 2.4 GHz
 
 # Hardware counters of one span_kernel launch on the default workload, taken with
 # `rocprofv3 --pmc` (summaries and commands: profiles/).  They describe the kernel sources
-# (pgcm_kernels.hip and the two headers it includes) whose hash is given; once those change the
+# (pgcm_kernels.hip and the three headers it includes) whose hash is given; once those change the
 # counters no longer apply and bench.py reports null.
 COUNTERS = {
-    "sources_sha256": "4e061b6ae901b03bc050c95e9677589c56d12ba5a15aa6f314a046090dfb8d8f",
+    "sources_sha256": "6711ad17ce920a6af4f7c9d63775e290c6082afb929da1beec80f1fa6265ed86",
     "workload": "c2_opt13b_kv_4096x320KiB",
-    "fetch_size_kib": 656166.4,     # FETCH_SIZE per launch
+    "fetch_size_kib": 656152.4,     # FETCH_SIZE per launch
     "fetch_scale": 1310720.0 / 655388.0,   # a 1 310 720 KiB device copy reads 655 388
-    "write_size_kib": 1310799.5,    # WRITE_SIZE per launch
+    "write_size_kib": 1310798.6,    # WRITE_SIZE per launch
     "write_scale": 1310720.0 / 1310720.0,  # the same copy writes 1 310 720.0
     "valu_wave_instructions": 547574784.0,  # SQ_INSTS_VALU per launch
     "lds_wave_instructions": 297997824.0,   # SQ_INSTS_LDS per launch
     "lds_active_cycles": 684266496.0,   # SQ_LDS_IDX_ACTIVE per launch, summed over the 256 CUs
-    "gui_active_cycles": 23472316.4 / 8,  # GRBM_GUI_ACTIVE per launch (summed over the 8 XCDs) ...
-    "pmc_launch_ms": 1.4112,              # ... and the launch's duration in that same run
+    "gui_active_cycles": 23458949.0 / 8,  # GRBM_GUI_ACTIVE per launch (summed over the 8 XCDs) ...
+    "pmc_launch_ms": 1.4391,              # ... and the launch's duration in that same run
 }
 
 
 def sources_sha256():
     import hashlib
     h = hashlib.sha256()
-    for f in ("pgcm_types.h", "pgcm_kernels.h", "pgcm_kernels.hip"):
+    for f in ("pgcm_types.h", "pgcm_arrive.h", "pgcm_kernels.h", "pgcm_kernels.hip"):
         with open(os.path.join(ROOT, "paper_2411_03357_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
