@@ -618,30 +618,9 @@ typedef __attribute__((address_space(3))) u32x4* lds_u128_wptr;
 // -n .. -1 and are hashed by the lanes that lie before the chunk's start: no multiplications of
 // their own, where hashing 64 bytes ahead of block 0 from the table in memory takes some 5 us.
 // AAD of more than kAadLaneBlocks blocks is meant to be rare: all but its last block is hashed
-// serially first, and the sum with that block stands in for "block -1".
+// first (long_hash), and the sum with that block stands in for "block -1".
 constexpr uint32_t kAadLaneBlocks = 64;
-__device__ __forceinline__ Block serial_hash(const Block* __restrict__ h_table, const uint8_t* p,
-                                             uint32_t bytes, uint32_t blocks) {
-    Block y{{0, 0, 0, 0}};
-    for (uint32_t i = 0; i < blocks; ++i) {
-        const Block b = padded_block(p, bytes, i);
-        block_xor(y, b);
-        // a word at a time: the registers are needed by what is usual
-        Block z{{0, 0, 0, 0}};
-#pragma unroll 1
-        for (uint32_t w = 0; w < 4; ++w) {
-#pragma unroll
-            for (uint32_t k = 0; k < 4; ++k) {
-                const uint32_t byte = (y.w[0] >> (8 * k)) & 0xFF, pos = 2 * (4 * w + k);
-                block_xor(z, h_table[pos * 16 + (byte >> 4)]);
-                block_xor(z, h_table[(pos + 1) * 16 + (byte & 15)]);
-            }
-            y.w[0] = y.w[1], y.w[1] = y.w[2], y.w[2] = y.w[3];
-        }
-        y = z;
-    }
-    return y;
-}
+__device__ Block long_hash(const KeyTables* __restrict__ kt, const uint8_t* p, uint32_t blocks, uint32_t lane);
 
 struct AadBlocks {
     const uint8_t* bytes = nullptr;
@@ -661,9 +640,9 @@ struct AadBlocks {
         return b;
     }
     // to be called by the wavefront that walks the blocks before block 0
-    __device__ __forceinline__ void prepare(const Block* __restrict__ h_table) {
+    __device__ __forceinline__ void prepare(const KeyTables* __restrict__ kt, uint32_t lane) {
         if (blocks > kAadLaneBlocks) {
-            Block y = serial_hash(h_table, bytes, len, blocks - 1);
+            Block y = long_hash(kt, bytes, blocks - 1, lane);
             const Block b = padded_block(bytes, len, blocks - 1);
             block_xor(y, b);
             const u32x4 v = {y.w[0], y.w[1], y.w[2], y.w[3]};
@@ -1618,7 +1597,7 @@ __global__ __launch_bounds__(kGroupThreads) void bulk_kernel(
         int64_t b0 = b1 - ((int64_t)1 << unit_power);
         if (unit == 0) {
             b0 = -(int64_t)__builtin_amdgcn_readfirstlane(lead_blocks(cd->aad_len));
-            aad.prepare(kt->ghash[0]);
+            aad.prepare(kt, lane);
         }
         Block* mask_out = ekj0 + chunk;
         uint32_t y[4];
@@ -2111,6 +2090,59 @@ __device__ __forceinline__ GfWords times_spread(const GfWords& v, const GfWords&
     return z;
 }
 
+// The GHASH state after `blocks` whole blocks, two at least, from p, by a wavefront, in all lanes.  All but the last
+// in rows counted back from the one before it, lane l's block times H^(65 - l); the last one times H, a nibble a lane.
+// (Some 7 us for a row; block after block from the table in memory it takes 0.5 to 0.75 us a block: 20 chunks of 8 KB
+// with AAD of 3000 bytes 142 -> 28 us, one of 320 KiB 114 -> 20.5, 300 of 400 KB in spans 358 -> 78.)
+// The powers one at a time: the registers are needed by what is usual.
+__device__ __forceinline__ Block long_hash(const KeyTables* __restrict__ kt, const uint8_t* p, uint32_t blocks,
+                                           uint32_t lane) {
+    const uint32_t n = blocks - 1, rows = (n - 1) / kRowBlocks + 1;
+    GfWords sum{{0, 0, 0, 0}}, hop{{0, 0, 0, 0}};
+#pragma unroll 1
+    for (uint32_t r = 0; r < rows; ++r) {
+        if (r == 1) {
+            hop = kt->row_hop[1];
+            spread_over_row(hop, lane);
+        }
+        if (r != 0) sum = times_spread(sum, hop, lane);
+        const uint32_t end = n - (rows - 1 - r) * kRowBlocks;  // of the row
+        Block b{{0, 0, 0, 0}};
+        if (end + lane >= kRowBlocks) b = global_read_block_any(p + 16 * (uint64_t)(end + lane - kRowBlocks));
+        GfWords row{{0, 0, 0, 0}};
+#pragma unroll 1
+        for (uint32_t t = 0; t < kDotSlices; ++t) {
+            GfWords q = kt->dot[kDotBlocks - kRowBlocks + lane][t];
+            uint32_t v = b.w[0], bits = 8;
+            // (the power times the bits of the byte, the first coefficient at its top)
+            v <<= 24;
+#pragma unroll 1
+            for (; bits != 0; --bits, v <<= 1) {
+                const uint32_t m = (uint32_t)((int32_t)v >> 31);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) row.a[k] ^= q.a[k] & m;
+                gfw_mul_x(q);
+            }
+            b.w[0] = __builtin_amdgcn_alignbit(b.w[1], b.w[0], 8);
+            b.w[1] = __builtin_amdgcn_alignbit(b.w[2], b.w[1], 8);
+            b.w[2] = __builtin_amdgcn_alignbit(b.w[3], b.w[2], 8);
+            b.w[3] >>= 8;
+        }
+        sum_over_lanes(row.a);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) sum.a[k] ^= row.a[k];
+    }
+    Block last{{0, 0, 0, 0}};
+    if (lane < 32) {
+        const uint32_t byte = global_read8(p + 16 * (uint64_t)n + lane / 2);
+        last = kt->ghash[0][lane * 16 + ((lane & 1) ? byte & 15 : byte >> 4)];
+    }
+    sum_over_lanes(last.w);
+    const Block y = gfw_to_block(sum);
+    block_xor(last, y);
+    return last;
+}
+
 // The slots' operations, at device scope
 struct SlotMemory {
     static __device__ __forceinline__ uint64_t fetch_xor(uint64_t* at, uint64_t v) {
@@ -2419,7 +2451,7 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
         store_tables();
         __syncthreads();
         if (unit >= 0) {
-            if (at_start) aad.prepare(kt->ghash[0]);
+            if (at_start) aad.prepare(kt, lane);
             uint32_t rk[4 * (kRounds + 1)];
 #pragma unroll
             for (int i = 0; i < 4 * (kRounds + 1); ++i) rk[i] = __builtin_amdgcn_readlane(key_word, i);
@@ -2939,12 +2971,14 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
         return v;
     };
     if (aad.blocks > kAadLaneBlocks) {  // rare
-        bool mine = by_rows && wave < 4 * folded;
+        // by the wavefront that has block -1 alone: sixteen at it are in each other's way (8 chunks of 2 MiB
+        // with 3000 bytes 700 us, 48 now)
+        bool mine = by_rows && wave == wave_of_lead((uint32_t)nblk, behind, folded);
         for (uint32_t q = 0; !by_rows && q < have; ++q)
             mine |= __ballot(block_of(behind + q) == -1) != 0;
         if (mine && g == 0) {
             AadBlocks a = aad;
-            a.prepare(kt->ghash[0]);
+            a.prepare(kt, lane);
         }
     }
     int64_t blk = have != 0 ? block_of(behind + have - 1) : -lead - 1;
@@ -3300,7 +3334,7 @@ __device__ __forceinline__ void walk_span(const KeyTables* __restrict__ kt, uint
                                    lds.tables.long_aad + wave);
         uint64_t len = PGCM_PAIR(len);
         asm volatile("" : "+v"(len), "+v"(aad.bytes), "+v"(aad.len), "+v"(aad.blocks));
-        if (b0 < 0) aad.prepare(kt->ghash[0]);
+        if (b0 < 0) aad.prepare(kt, lane);
 #pragma unroll
         for (int k = 0; k < 4; ++k) j.w[k] = __builtin_amdgcn_readfirstlane(j.w[k]);
         uint32_t y[4];

@@ -167,6 +167,16 @@ struct ArgBatch {
 // Passes a workgroup of sixteen wavefronts of the kernel for short bursts makes at most, at a time and in
 // all (of fewer wavefronts: one).
 constexpr uint32_t kFoldPasses = 4, kSweptPasses = 16;
+// Where a wavefront of burst_kernel's takes a row of 64 blocks: wavefront w has row w % 4 of pass w / 4 of every
+// sweep, the last pass of the last sweep being number `behind` from the chunk's end, of `folded` passes a
+// sweep.  Which wavefront has the block before the chunk's first, of nblk?
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+constexpr uint32_t wave_of_lead(uint32_t nblk, uint32_t behind, uint32_t folded) {
+    const uint32_t pass = nblk / 256, at = 255 - nblk % 256;  // number from the end, and the block's place in it
+    return 4 * ((behind + folded - 1 - pass) % kFoldPasses) + at / 64;
+}
 enum class BurstKind { kWords, kFold, kSweep, kFoldShared };
 // Workgroups of a chunk (KeyTables::hop has their distances) and of a launch.
 constexpr uint32_t kSwapChunkGroups = kHopEntries;

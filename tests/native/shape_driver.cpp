@@ -151,7 +151,35 @@ static void check(const ShapeBatch& a, uint32_t num_cu, uint32_t forced) {
     CHECK(sum == s.groups && alone == s.alone);
 }
 
+// A chunk's first workgroup, in rows: one wavefront has the block before the chunk's first, in one of its sweeps,
+// and wave_of_lead names it.
+static void check_lead(uint64_t nblk, uint32_t lead, uint32_t passes, uint32_t spare) {
+    const uint64_t in_chunk = (nblk + lead + 255) / 256;
+    const uint32_t ngroups = (uint32_t)burst_groups(in_chunk, passes, spare);
+    const uint32_t of_each = ngroups == 1 ? (uint32_t)in_chunk : passes;
+    const uint32_t behind = (ngroups - 1) * of_each, have = (uint32_t)in_chunk - behind;
+    CHECK(have >= 1 && have <= kSweptPasses);
+    if (nblk <= ((uint64_t)behind << 8) + 256) return;  // not in rows
+    const uint32_t sweeps = (have + kFoldPasses - 1) / kFoldPasses, folded = sweeps > 1 ? kFoldPasses : have;
+    uint32_t found = 0;
+    for (uint32_t wave = 0; wave < 16; ++wave)
+        for (uint32_t sweep = 0; sweep < sweeps; ++sweep) {
+            // as the kernel has it
+            if (!(wave < 4 * folded && (sweep > 0 || wave / 4 >= sweeps * folded - have))) continue;
+            const uint32_t m1 = behind + folded - wave / 4 + kFoldPasses * (sweeps - 1 - sweep);
+            const int64_t first = (int64_t)nblk - ((int64_t)m1 << 8) + (wave & 3) * 64;
+            if (first > -1 || first + 64 <= -1) continue;
+            ++found;
+            CHECK(wave == wave_of_lead((uint32_t)nblk, behind, folded));
+        }
+    CHECK(found == 1);
+}
+
 int main() {
+    for (int trial = 0; trial < 20000; ++trial) {
+        const uint32_t passes = 1 + (uint32_t)below(kSweptPasses), spare = passes < kSweptPasses ? (uint32_t)below(2) : 0;
+        check_lead(257 + log_between(1, 256 * 256 * 8) - below(257), 1 + (uint32_t)below(64), passes, spare);
+    }
     const uint32_t cus[] = {256, 256, 256, 1, 2, 32, 304};
     for (int trial = 0; trial < 20000; ++trial) {
         const uint32_t num_cu = cus[below(7)];

@@ -9,6 +9,7 @@ import pytest
 
 import test_gpu_bursts
 import test_gpu_graphs
+import test_gpu_long_aad
 import test_gpu_parity
 import test_gpu_ragged_ends
 import test_gpu_random_batches
@@ -124,3 +125,10 @@ def test_long_aad(kernels_of):
     for lens, unit_bytes, one_launch, kernel in test_gpu_parity.LONG_AAD:
         got, = kernels_of([(lens, test_gpu_parity._long_aad_lens(len(lens)), unit_bytes, one_launch)])
         assert got.split()[0] == kernel, (lens[:4], got)
+
+
+def test_long_aad_in_every_place(kernels_of):
+    shapes = test_gpu_long_aad.SHAPES
+    got = kernels_of([(lens, np.resize(test_gpu_long_aad.AADS, len(lens)), unit_bytes, one_launch)
+                      for lens, unit_bytes, one_launch, _ in shapes.values()])
+    assert dict(zip(shapes, got)) == {name: s[3] for name, s in shapes.items()}
