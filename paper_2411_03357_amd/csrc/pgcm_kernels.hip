@@ -2866,6 +2866,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     constexpr bool kFold = kKind != BurstKind::kWords, kSweep = kKind == BurstKind::kSweep;
     constexpr bool kRows = kKind == BurstKind::kFold || kSweep;  // a compute unit to itself
     __shared__ QuadLds<kKind> lds;
+    __shared__ Block long_j0;  // J0, of a long IV
     const uint32_t lds_base = lds_offset(&lds);
     const uint32_t tid = threadIdx.x, lane = tid & 63, column = lane & 3;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2918,7 +2919,16 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     // What comes next is asked for only now: sixteen wavefronts' loads of it ahead of the last one's of the
     // tables made that wait 1.2 us longer, and so did a descriptor or ragged payload waited for before.
     asm volatile("" ::: "memory");
-    if (!iv_known) j = wave_j0<kLongIv>(kt, ivs + (uint64_t)cd.index * iv_len, iv_len, lane);
+    if constexpr (kLongIv) {
+        // by one wavefront for all, the last but one, which mostly has no row: all sixteen at it are in each
+        // other's way (320 KiB with IVs of 60 bytes 17.7 us, 11.1 now; 20 of 8 KB 18.2, 11.9; 8 of 2 MiB 39.6, 34.5)
+        if (wave == nwaves - 2) {
+            j = wave_j0<true>(kt, ivs + (uint64_t)cd.index * iv_len, iv_len, lane);
+            if (lane == 0) long_j0 = j;
+        }
+    } else if (!iv_known) {
+        j = wave_j0<false>(kt, ivs + (uint64_t)cd.index * iv_len, iv_len, lane);
+    }
 
     // its passes, counted back from the chunk's end: pass q of the workgroup is number `behind` + have
     // - 1 - q from there; the chunk's first workgroup has what is left (burst_groups)
@@ -3039,6 +3049,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     };
     if constexpr (kRows) fetch_fold();
     __syncthreads();  // the tables are in place
+    if constexpr (kLongIv) j = long_j0;
     QuadKeys keys;
     keys.rounds = meta.rounds();
     {
