@@ -100,8 +100,10 @@ inline bool first_burst_choice(uint64_t passes, size_t n, uint64_t most, Groups 
 
 // Batches of short chunks, and others of at most sixteen passes for every compute unit, go to burst_kernel.
 // As long as there is a compute unit for every short chunk, a workgroup takes a whole one, with no
-// more wavefronts than it has blocks for; of more chunks, workgroups of at most eight wavefronts share
-// a compute unit, and the longer chunks take several.  Longer chunks are spread over as many
+// more wavefronts than it has blocks for; of more chunks, two workgroups share a compute unit: of at most
+// eight wavefronts and one pass, of which the longer chunks take several, if 512 of them do; otherwise of
+// sixteen and one pass, if 512 of these do (346 chunks of 1.6 to 8.1 KB 13.4 us, a workgroup each 16.2; 450 of up
+// to 8 KB 12.9, 14.7); otherwise of sixteen and a whole chunk.  Longer chunks are spread over as many
 // workgroups of sixteen as there are compute units, with the fewest passes that go: first with none spare,
 // then with one for the first workgroup of each chunk, which is what a few blocks too many take (2 MiB
 // with AAD in 257 workgroups of two passes: 256 take 11.8 us, four passes in 129 took 14.8; 8 of
@@ -118,16 +120,18 @@ inline bool swap_shape(const ShapeBatch& a, uint32_t num_cu, bool one_launch, ui
     if (a.n > kSmallMaxChunks || (!all_small && !one_launch)) return false;
     uint64_t total = 0;
     if (all_small) {
-        uint64_t most_blocks = 0, of_eight = 0;
+        uint64_t most_blocks = 0, of_eight = 0, of_sixteen = 0;
         for (size_t k = 0; k < a.n; ++k) {
             const uint64_t blocks = burst_blocks(a, a.at(k));
             if (blocks > most_blocks) most_blocks = blocks;
             of_eight += burst_groups(burst_passes(blocks, 3), 1, 0);
+            of_sixteen += burst_groups(burst_passes(blocks, 4), 1, 0);
         }
         uint32_t wp = 2, passes = kFoldPasses;
         while (wp < 4 && most_blocks > (uint64_t)16 << wp) ++wp;
         total = a.n;
         if (a.n > num_cu && wp > 2 && of_eight <= kSwapMaxGroups) wp = 3, passes = 1, total = of_eight;
+        else if (a.n > num_cu && wp == 4 && of_sixteen <= kSwapMaxGroups) passes = 1, total = of_sixteen;
         *shape = SwapShape{true, total == a.n, passes, wp, (uint32_t)total, 0};
         return true;
     }

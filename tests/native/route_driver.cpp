@@ -40,7 +40,7 @@ int main() {
                     case BurstKind::kWords: std::cout << "words\n"; break;
                     case BurstKind::kFold: std::cout << "fold " << s.unit_power + s.spare << "\n"; break;
                     case BurstKind::kSweep: std::cout << "sweep " << s.unit_power + s.spare << "\n"; break;
-                    case BurstKind::kFoldShared: std::cout << "shared\n"; break;
+                    case BurstKind::kFoldShared: std::cout << (s.alone ? "shared\n" : "shared apart\n"); break;
                 }
         }
     }

@@ -78,7 +78,15 @@ static void check(const ShapeBatch& a, uint32_t num_cu, uint32_t forced) {
         CHECK(s.burst && s.spare == 0 && s.groups >= a.n && s.groups <= kSwapMaxGroups);
         CHECK(s.alone == (s.groups == a.n));
         if (s.alone) CHECK(groups_of(a, (uint64_t)16 << s.wave_power, s.unit_power, 0) == a.n || a.n > num_cu);
-        else CHECK(s.wave_power == 3 && groups_of(a, 128, 1, 0) == s.groups);
+        if (a.n > num_cu && s.wave_power > 2) {
+            const uint64_t of_eight = groups_of(a, 128, 1, 0), of_sixteen = groups_of(a, 256, 1, 0);
+            CHECK(s.groups == (of_eight <= kSwapMaxGroups     ? of_eight
+                               : of_sixteen <= kSwapMaxGroups ? of_sixteen
+                                                              : a.n));
+            CHECK(s.wave_power == (of_eight <= kSwapMaxGroups ? 3u : 4u) && (s.alone || s.unit_power == 1));
+        } else {
+            CHECK(s.alone);
+        }
         // what the kinds of burst_kernel are compiled for
         CHECK(most_passes(a, s) <= (s.wave_power < 4 ? 1 : s.groups > num_cu ? kFoldPasses - 1 : kFoldPasses));
         ++g_bursts;

@@ -74,6 +74,10 @@ SHAPES = {
     # more chunks than compute units: mixed, and all of much the same length
     "many_mixed": ([(37 * i * i) % 8192 + 1 for i in range(40)] + [20] * 260, [0, 9]),
     "many_even": ([4096 + 16 * (i % 3) for i in range(300)], [0, 16]),
+    # ... so many passes of sixteen wavefronts that chunks of more than one have a workgroup for each
+    "many_apart": ([1600 + (97 * i * i) % 6593 for i in range(300)], [0, 16, 40, 1008, 0, 3000]),
+    "many_apart_512": ([4096, 8192, 4096, 4097, 8177] * 30 + [4096] * 160 + [4097] * 56, [0]),
+    "many_apart_513": ([4096, 8192, 4096, 4097, 8177] * 30 + [4096] * 159 + [4097] * 57, [0]),
     "many_long": ([8192 - i % 20 for i in range(270)], [0, 64]),
 }
 
@@ -88,7 +92,7 @@ def test_shapes(shape):
 
 @pytest.mark.parametrize("key_bytes,iv_bytes", [(16, 12), (24, 16), (32, 8), (16, 40), (32, 1040)])
 @pytest.mark.parametrize("shape", ["short_aad", "passes_1", "passes_4", "sweeps_2_missing", "many_even",
-                                   "many_mixed"])
+                                   "many_mixed", "many_apart"])
 def test_other_keys_and_ivs(shape, key_bytes, iv_bytes):
     lens, alens = SHAPES[shape]
     _full_parity(_workload(shape, lens[:40] if shape == "short_aad" else lens, alens, key_bytes, iv_bytes))

@@ -76,6 +76,7 @@ def test_bursts(kernels_of):
         else:
             assert kind in ("words", "fold", "shared"), (name, kernel)
     assert {got[n] for n in ("many_even", "many_long")} == {"shared"} and got["many_mixed"] == "words"
+    assert {got[n] for n in ("many_apart", "many_apart_512")} == {"shared apart"} and got["many_apart_513"] == "shared"
 
 
 def test_units_in_one_launch(kernels_of):
