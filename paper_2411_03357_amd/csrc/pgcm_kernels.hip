@@ -620,7 +620,8 @@ typedef __attribute__((address_space(3))) u32x4* lds_u128_wptr;
 // AAD of more than kAadLaneBlocks blocks is meant to be rare: all but its last block is hashed
 // first (long_hash), and the sum with that block stands in for "block -1".
 constexpr uint32_t kAadLaneBlocks = 64;
-__device__ Block long_hash(const KeyTables* __restrict__ kt, const uint8_t* p, uint32_t blocks, uint32_t lane);
+__device__ __attribute__((noinline)) Block long_hash(const KeyTables* __restrict__ kt, const uint8_t* p,
+                                                     uint32_t blocks, uint32_t lane);
 
 struct AadBlocks {
     const uint8_t* bytes = nullptr;
@@ -641,7 +642,7 @@ struct AadBlocks {
     }
     // to be called by the wavefront that walks the blocks before block 0
     __device__ __forceinline__ void prepare(const KeyTables* __restrict__ kt, uint32_t lane) {
-        if (blocks > kAadLaneBlocks) {
+        if (__builtin_expect(blocks > kAadLaneBlocks, 0)) {
             Block y = long_hash(kt, bytes, blocks - 1, lane);
             const Block b = padded_block(bytes, len, blocks - 1);
             block_xor(y, b);
@@ -2095,8 +2096,10 @@ __device__ __forceinline__ GfWords times_spread(const GfWords& v, const GfWords&
 // (Some 7 us for a row; block after block from the table in memory it takes 0.5 to 0.75 us a block: 20 chunks of 8 KB
 // with AAD of 3000 bytes 142 -> 28 us, one of 320 KiB 114 -> 20.5, 300 of 400 KB in spans 358 -> 78.)
 // The powers one at a time: the registers are needed by what is usual.
-__device__ __forceinline__ Block long_hash(const KeyTables* __restrict__ kt, const uint8_t* p, uint32_t blocks,
-                                           uint32_t lane) {
+// A function of its own: in the middle of the span kernels' code it cost every launch of few rows 0.1 to 0.4 us (60
+// chunks of up to 8 KB of three keys both ways 32.0 us without, 32.2 so, 31.7 now; three of 0.1 to 2 MB 41.9, 42.6, 42.4).
+__device__ __attribute__((noinline)) Block long_hash(const KeyTables* __restrict__ kt, const uint8_t* p,
+                                                     uint32_t blocks, uint32_t lane) {
     asm volatile("" : "+v"(lane));  // what is made of it is not to be kept for later
     const uint32_t n = blocks - 1, rows = (n - 1) / kRowBlocks + 1;
     GfWords sum{{0, 0, 0, 0}}, hop{{0, 0, 0, 0}};
