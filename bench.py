@@ -31,17 +31,17 @@ LDS_PEAK_GCYCLES = 256 * 2.4               # 256 CUs, one LDS pipe each, 2.4 GHz
 # (pgcm_kernels.hip and the three headers it includes) whose hash is given; once those change the
 # counters no longer apply and bench.py reports null.
 COUNTERS = {
-    "sources_sha256": "6711ad17ce920a6af4f7c9d63775e290c6082afb929da1beec80f1fa6265ed86",
+    "sources_sha256": "1f137cff22b52bece9ba2ce50e547351bd722b3a3ca2fd56542ae36804a41d6d",
     "workload": "c2_opt13b_kv_4096x320KiB",
-    "fetch_size_kib": 656152.4,     # FETCH_SIZE per launch
+    "fetch_size_kib": 656148.2,     # FETCH_SIZE per launch
     "fetch_scale": 1310720.0 / 655388.0,   # a 1 310 720 KiB device copy reads 655 388
-    "write_size_kib": 1310798.6,    # WRITE_SIZE per launch
+    "write_size_kib": 1310799.4,    # WRITE_SIZE per launch
     "write_scale": 1310720.0 / 1310720.0,  # the same copy writes 1 310 720.0
-    "valu_wave_instructions": 547574784.0,  # SQ_INSTS_VALU per launch
+    "valu_wave_instructions": 547480576.0,  # SQ_INSTS_VALU per launch
     "lds_wave_instructions": 297997824.0,   # SQ_INSTS_LDS per launch
     "lds_active_cycles": 684266496.0,   # SQ_LDS_IDX_ACTIVE per launch, summed over the 256 CUs
-    "gui_active_cycles": 23458949.0 / 8,  # GRBM_GUI_ACTIVE per launch (summed over the 8 XCDs) ...
-    "pmc_launch_ms": 1.4391,              # ... and the launch's duration in that same run
+    "gui_active_cycles": 23560182.3 / 8,  # GRBM_GUI_ACTIVE per launch (summed over the 8 XCDs) ...
+    "pmc_launch_ms": 1.4253,              # ... and the launch's duration in that same run
 }
 
 
