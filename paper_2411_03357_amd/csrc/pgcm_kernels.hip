@@ -393,7 +393,7 @@ __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict_
         GfWords p = h_power[kDotBlocks + 1 - l];
         for (uint32_t i = 0; i < t; ++i) gfw_mul_x8(p);
         for (uint32_t i = t; i < t + kDotSlices / 4; ++i) {
-            kt->dot[l][i] = p;
+            kt->dot[i][l] = p;
             gfw_mul_x8(p);
         }
     }
@@ -2116,7 +2116,7 @@ __device__ __attribute__((noinline)) Block long_hash(const KeyTables* __restrict
         GfWords row{{0, 0, 0, 0}};
 #pragma unroll 1
         for (uint32_t t = 0; t < kDotSlices; ++t) {
-            GfWords q = kt->dot[kDotBlocks - kRowBlocks + lane][t];
+            GfWords q = kt->dot[t][kDotBlocks - kRowBlocks + lane];
             uint32_t v = b.w[0], bits = 8;
             // (the power times the bits of the byte, the first coefficient at its top)
             v <<= 24;
@@ -2227,10 +2227,11 @@ __device__ __forceinline__ Block length_block_entry(const Block* __restrict__ h_
 }
 
 // the sum over the lanes of y * H^(65 - lane), in all lanes
-__device__ __forceinline__ GfWords lanes_summed(const GfWords* __restrict__ powers, const uint32_t y[4]) {
+__device__ __forceinline__ GfWords lanes_summed(const KeyTables* __restrict__ kt, uint32_t lane,
+                                                const uint32_t y[4]) {
     GfWords q[kDotSlices];
 #pragma unroll
-    for (uint32_t t = 0; t < kDotSlices; ++t) q[t] = powers[t];
+    for (uint32_t t = 0; t < kDotSlices; ++t) q[t] = kt->dot[t][kDotBlocks - kRowBlocks + lane];
     GfWords acc{{0, 0, 0, 0}};
     uint32_t v[4] = {y[0], y[1], y[2], y[3]};
     // (a loop: unrolled, its masks are made ahead of their use and take the registers of the powers)
@@ -2270,7 +2271,7 @@ __device__ __forceinline__ Block wave_j0_rows(const KeyTables* __restrict__ kt, 
         Block b{{0, 0, 0, 0}};
         const uint32_t end = blocks - (rows - 1 - r) * kRowBlocks;  // of the row
         if (end + lane >= kRowBlocks) b = padded_block(iv, iv_len, end + lane - kRowBlocks);
-        const GfWords row = lanes_summed(kt->dot[kDotBlocks - kRowBlocks + lane], b.w);
+        const GfWords row = lanes_summed(kt, lane, b.w);
 #pragma unroll
         for (int k = 0; k < 4; ++k) sum.a[k] ^= row.a[k];
     }
@@ -2418,7 +2419,7 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
                 if (k < per_thread) tree[k] = from[(k << (6 + wave_power)) + tid];
 #pragma unroll
             for (uint32_t s = 0; s < 4; ++s)
-                if (s < slices) q[s] = kt->dot[kDotBlocks - kRowBlocks + lane][slices * wave + s];
+                if (s < slices) q[s] = kt->dot[slices * wave + s][kDotBlocks - kRowBlocks + lane];
         }
         if (finisher) {
             if (ngroups - 1 != g) hop = kt->hop[p + wave_power - kHopMinPower][ngroups - 1 - g];
@@ -3039,11 +3040,11 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     GfWords powers[4];
     auto fetch_powers = [&]() __attribute__((always_inline)) {
         const GfWords* const from =
-            kFold ? kt->dot[kDotBlocks - kRowBlocks + lane] + 4 * (wave & 3)
-                  : kt->dot[kDotBlocks - pass_blocks + 16 * wave + (lane >> 2)] + 4 * column;
+            kFold ? &kt->dot[4 * (wave & 3)][kDotBlocks - kRowBlocks + lane]
+                  : &kt->dot[4 * column][kDotBlocks - pass_blocks + 16 * wave + (lane >> 2)];
         if (!kFold || wave < 4 * folded)
 #pragma unroll
-            for (uint32_t s = 0; s < 4; ++s) powers[s] = from[s];
+            for (uint32_t s = 0; s < 4; ++s) powers[s] = from[s * kDotBlocks];
     };
     if constexpr (kKind != BurstKind::kFoldShared) fetch_powers();
     u32x4 fold[2];  // the latter only of the first half of the threads, or in the other half for sweeps
@@ -3368,7 +3369,7 @@ __device__ __forceinline__ void walk_span(const KeyTables* __restrict__ kt, uint
             },
             y);
         row = stop;
-        GfWords sum = lanes_summed(kt->dot[kDotBlocks - kRowBlocks + lane], y);
+        GfWords sum = lanes_summed(kt, lane, y);
         if (behind % kRowHopEntries != 0) {
             spread_over_row(hop, lane);
             sum = times_spread(sum, hop, lane);
@@ -3447,11 +3448,12 @@ __global__ __launch_bounds__(kGroupThreads) void span_kernel(
         te.fetch(kt, tid);
         // the threads without an entry of the row hash bring what the end needs into the caches: a
         // line each of the powers and of H's table
+        constexpr uint32_t kLines = kRowBlocks * sizeof(GfWords) / 128;
         const uint32_t t = tid - kNibbleTableEntries;
         const uint8_t* const from =
             tid < kNibbleTableEntries ? reinterpret_cast<const uint8_t*>(&kt->ghash[kRowPower][tid])
-            : t < kRowBlocks * sizeof(kt->dot[0]) / 128
-                ? reinterpret_cast<const uint8_t*>(kt->dot[kDotBlocks - kRowBlocks]) + t * 128
+            : t < kDotSlices * kLines
+                ? reinterpret_cast<const uint8_t*>(&kt->dot[t / kLines][kDotBlocks - kRowBlocks]) + t % kLines * 128
                                         : reinterpret_cast<const uint8_t*>(kt->ghash[0]) + t % 64 * 128;
         gh = global_read128(from);
         key_word = lane < 60 ? kt->rk[lane] : lane == 60 ? kt->rounds : 0u;
