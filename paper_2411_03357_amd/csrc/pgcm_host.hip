@@ -919,9 +919,11 @@ int run_span_batch(Context* ctx, const BatchArgs& a, KeyPart* keys, size_t nkeys
         return PGCM_ERR_NOMEM;
     }
     if (ctx->scratch.capacity() != held) ++ctx->allocations;
-    size_t stride = sizeof(SpanGroup) + sizeof(SpanPart) * plan.longest;
-    const bool in_host =
-        image != stage && plan.longest <= kSpanLdsParts && stride * ngroups <= kSpanHostBytes;
+    SpanMap map;
+    size_t packed = 0;
+    uint32_t mapped = map_spans(keys, nkeys, groups, plan, &map, &packed);
+    if (image == stage) mapped &= ~kSpanPlaced;
+    const bool in_host = mapped & kSpanPlaced;
     const size_t bytes = in_host ? 0 : span_image_bytes(plan.nparts, ngroups);
     // the descriptors go behind every slot that is kept clean
     const size_t nslots = plan.nparts;
@@ -933,10 +935,12 @@ int run_span_batch(Context* ctx, const BatchArgs& a, KeyPart* keys, size_t nkeys
     const uint8_t* packets = stage;
     const SpanPart* parts = nullptr;
     if (in_host) {
+        uint8_t* to = stage;
         for (uint32_t g = 0; g < ngroups; ++g) {
             const SpanGroup& d = groups[g];
-            memcpy(stage + g * stride, &d, sizeof(d));
-            memcpy(stage + g * stride + sizeof(d), all_parts + d.part, sizeof(SpanPart) * d.nparts);
+            memcpy(to, &d, sizeof(d));
+            memcpy(to + sizeof(d), all_parts + d.part, sizeof(SpanPart) * d.nparts);
+            to += packet_bytes(d.nparts);
         }
     } else {
         if (image != stage) memcpy(stage, image, bytes);
@@ -946,7 +950,6 @@ int run_span_batch(Context* ctx, const BatchArgs& a, KeyPart* keys, size_t nkeys
                            reinterpret_cast<const uint4*>(stage), n16, (uint4*)nullptr, 0u);
         packets = ctx->work + behind;
         parts = reinterpret_cast<const SpanPart*>(packets + parts_at);
-        stride = 0;
     }
     // one pair of events per key object, which may be listed more than once
     auto timed_already = [&](size_t q) {
@@ -963,8 +966,7 @@ int run_span_batch(Context* ctx, const BatchArgs& a, KeyPart* keys, size_t nkeys
                                    : (long_iv ? span_kernel<false, true> : span_kernel<false, false>);
     launch_last(kernel, dim3(ngroups), dim3(kGroupThreads), a.stream, a.capturing, ctx->stage_done[s],
                 (const KeyTables*)(nkeys == 1 ? keys[0].key->tables : nullptr), packets, parts,
-                (uint32_t)stride, a.iv_len, a.ivs, reinterpret_cast<ArriveSlot*>(ctx->work), a.tags,
-                a.ok);
+                a.iv_len, mapped, a.ivs, reinterpret_cast<ArriveSlot*>(ctx->work), a.tags, a.ok, map);
     for (size_t q = 0; q < nkeys && rc_timing == PGCM_OK; ++q)
         if (!timed_already(q)) rc_timing = record_timing_stop(keys[q].key, a.stream);
     const int rc_end = end_of_batch(ctx, s, a.capture, true);

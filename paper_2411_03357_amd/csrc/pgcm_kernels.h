@@ -47,8 +47,8 @@ __global__ void burst_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t i
 // and these may lie in host memory.  slots: one per part.  kLongIv: iv_len exceeds kShortIvBytes.
 template <bool kDecrypt, bool kLongIv>
 __global__ void span_kernel(const KeyTables* key, const uint8_t* packets, const SpanPart* parts,
-                            uint32_t stride, uint32_t iv_len, const uint8_t* ivs, ArriveSlot* slots,
-                            uint8_t* tags, uint8_t* ok);
+                            uint32_t iv_len, uint32_t mapped, const uint8_t* ivs, ArriveSlot* slots,
+                            uint8_t* tags, uint8_t* ok, SpanMap map);
 
 __global__ void fold_kernel(const KeyTables* kt, const FoldItem* items, uint32_t power,
                             Block* sets);

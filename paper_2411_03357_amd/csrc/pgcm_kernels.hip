@@ -3431,16 +3431,17 @@ __device__ __forceinline__ void walk_span(const KeyTables* __restrict__ kt, uint
 template <bool kDecrypt, bool kLongIv>
 __global__ __launch_bounds__(kGroupThreads) void span_kernel(
     const KeyTables* __restrict__ key, const uint8_t* __restrict__ packets,
-    const SpanPart* __restrict__ all_parts, uint32_t stride, uint32_t iv_len,
+    const SpanPart* __restrict__ all_parts, uint32_t iv_len, uint32_t mapped,
     const uint8_t* __restrict__ ivs, ArriveSlot* __restrict__ slots, uint8_t* __restrict__ tags,
-    uint8_t* __restrict__ ok) {
+    uint8_t* __restrict__ ok, const SpanMap map) {
     __shared__ SpanLds lds;
     const uint32_t tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     // Everything is asked for at once: the tables, if the key is known already, and the descriptors, by
     // the first wavefronts only, as they may come from host memory.
-    const KeyTables* __restrict__ kt = key;
+    const uint32_t place = mapped != 0 ? map.place[blockIdx.x] : 0;
+    const KeyTables* __restrict__ kt = mapped & kSpanKeysMapped ? map.key[place >> SpanMap::kKeyShift] : key;
     TeFill<TeWide, kGroupThreads> te;
     u32x4 gh{};
     uint32_t key_word = 0;
@@ -3458,11 +3459,12 @@ __global__ __launch_bounds__(kGroupThreads) void span_kernel(
         gh = global_read128(from);
         key_word = lane < 60 ? kt->rk[lane] : lane == 60 ? kt->rounds : 0u;
     };
-    if (key != nullptr) fetch_tables();
+    if (kt != nullptr) fetch_tables();
     const SpanPart* parts = nullptr;
-    if (stride != 0) {
-        if (tid < stride / 16)
-            lds.packet[tid] = reinterpret_cast<const u32x4*>(packets + (uint64_t)blockIdx.x * stride)[tid];
+    if (mapped & kSpanPlaced) {
+        const uint32_t from = place % (1u << SpanMap::kLengthShift), n = (place >> SpanMap::kLengthShift) % 64;
+        if (tid < (sizeof(SpanGroup) + n * sizeof(SpanPart)) / 16)
+            lds.packet[tid] = reinterpret_cast<const u32x4*>(packets + (uint64_t)from * kPacketAlign)[tid];
     } else {
         constexpr uint32_t kGroup16 = sizeof(SpanGroup) / 16, kPart16 = sizeof(SpanPart) / 16;
         const SpanGroup* const gd = reinterpret_cast<const SpanGroup*>(packets) + blockIdx.x;
@@ -3479,7 +3481,7 @@ __global__ __launch_bounds__(kGroupThreads) void span_kernel(
         lds.arrived[tid] = 0;
     }
     const SpanGroup* const group = lds.group();
-    if (key == nullptr) {
+    if (kt == nullptr) {
         __syncthreads();
         kt = reinterpret_cast<const KeyTables*>(same_in_all_lanes(reinterpret_cast<uint64_t>(group->kt)));
         fetch_tables();
@@ -3522,7 +3524,7 @@ __global__ __launch_bounds__(kGroupThreads) void span_kernel(
 #define PGCM_INSTANTIATE_SPAN(D, L)                                                               \
     template __global__ void span_kernel<D, L>(const KeyTables*, const uint8_t*, const SpanPart*, \
                                                uint32_t, uint32_t, const uint8_t*, ArriveSlot*,   \
-                                               uint8_t*, uint8_t*)
+                                               uint8_t*, uint8_t*, SpanMap)
 PGCM_INSTANTIATE_SPAN(false, false);
 PGCM_INSTANTIATE_SPAN(true, false);
 PGCM_INSTANTIATE_SPAN(false, true);

@@ -297,4 +297,27 @@ inline SpanPlan plan_spans(const SpanBatch& a, const KeyPart* keys, size_t nkeys
     return plan;
 }
 
+// Fills in a launch's map as far as it goes: the keys, if there are several and they have a place each, and
+// the workgroups' packets one behind the other, if no list is longer than what is held of one and all of them
+// together are read from host memory.  Returns what is filled in; *bytes: the packets'.
+inline uint32_t map_spans(const KeyPart* keys, size_t nkeys, const SpanGroup* groups, const SpanPlan& plan,
+                          SpanMap* map, size_t* bytes) {
+    uint32_t filled = nkeys > 1 && nkeys <= kSpanMapKeys ? kSpanKeysMapped : 0, g = 0;
+    size_t at = 0;
+    for (size_t q = 0; q < nkeys; ++q) {
+        if (g + keys[q].groups > kSpanMapGroups) return 0;
+        if (filled) map->key[q] = keys[q].tables;
+        for (uint32_t end = g + keys[q].groups; g < end; ++g) {
+            map->place[g] = (filled ? (uint32_t)q << SpanMap::kKeyShift : 0) |
+                            (groups[g].nparts & 63) << SpanMap::kLengthShift | ((uint32_t)(at / kPacketAlign) & 0xFFFF);
+            at += packet_bytes(groups[g].nparts);
+        }
+    }
+    if (plan.longest <= kSpanLdsParts && at <= kSpanHostBytes) filled |= kSpanPlaced;
+    *bytes = at;
+    return filled;
+}
+static_assert(kSpanHostBytes / kPacketAlign <= 1u << SpanMap::kLengthShift, "places of packets");
+static_assert(kSpanLdsParts < 1u << (SpanMap::kKeyShift - SpanMap::kLengthShift), "lengths of lists");
+
 }  // namespace pgcm

@@ -250,6 +250,24 @@ struct alignas(16) SpanPart {       // a chunk as far as one workgroup has rows 
     uint32_t waves;                 // this one's wavefronts with rows of it, << 8; the first of them
 };
 static_assert(sizeof(SpanPart) == 64, "descriptor layout");
+// Where a launch's workgroups find their packets, each a SpanGroup and its parts, and which tables they use:
+// in the kernel's arguments, which are read at once, while a packet in host memory takes 2 us to come.
+// So packets need not be equally long (300 adapters read 67 KB, where all as long as the longest were 139; both
+// ways 171.6 -> 169.3 us), and with several keys the tables are asked for ahead of them (240 chunks of three keys,
+// both ways, 175.2 -> 169.9).
+constexpr uint32_t kSpanMapGroups = 512, kSpanMapKeys = 16;
+constexpr uint32_t kPacketAlign = 64;  // packets begin at multiples of this
+struct SpanMap {
+    const KeyTables* key[kSpanMapKeys];
+    // where the packet begins, in kPacketAlign; from bit kLengthShift on its parts, from kKeyShift on the key
+    uint32_t place[kSpanMapGroups];
+
+    static constexpr uint32_t kLengthShift = 16, kKeyShift = 22;
+};
+constexpr uint32_t kSpanPlaced = 1, kSpanKeysMapped = 2;  // what of a launch's map is filled in
+constexpr uint32_t packet_bytes(uint32_t nparts) {
+    return (uint32_t)((sizeof(SpanGroup) + sizeof(SpanPart) * nparts + kPacketAlign - 1) / kPacketAlign * kPacketAlign);
+}
 // IVs of at most one block are hashed in one round of lookups.
 constexpr uint32_t kShortIvBytes = 16;
 // The parts of a workgroup that are held in LDS; those of longer lists are read from memory.
