@@ -88,6 +88,12 @@ __device__ __forceinline__ uint32_t bswap32(uint32_t v) { return __builtin_bswap
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
+// a ^ (b & c) in one instruction, which the compiler makes of that expression only at the start of a chain:
+// what sums over lanes bit by bit takes 95 instructions a bit instead of 153 (300 adapters both ways 168.5 ->
+// 163.1 us, 2 MiB decrypted 9.04 -> 8.76, 64 chunks of 4 KiB both ways 13.3 -> 12.9)
+__device__ __forceinline__ uint32_t xor_and(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x78);
+}
 
 __device__ __forceinline__ void block_xor(Block& a, const Block& b) {
     a.w[0] ^= b.w[0];
@@ -2035,7 +2041,7 @@ __device__ __forceinline__ GfWords bits_times(uint32_t byte[kSlices], const GfWo
             const uint32_t m = 0u - (byte[s] & 1u);
             byte[s] >>= 1;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) acc.a[k] ^= q[s].a[k] & m;
+            for (int k = 0; k < 4; ++k) acc.a[k] = xor_and(acc.a[k], q[s].a[k], m);
         }
     }
     return acc;
@@ -2124,7 +2130,7 @@ __device__ __attribute__((noinline)) Block long_hash(const KeyTables* __restrict
             for (; bits != 0; --bits, v <<= 1) {
                 const uint32_t m = (uint32_t)((int32_t)v >> 31);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) row.a[k] ^= q.a[k] & m;
+                for (int k = 0; k < 4; ++k) row.a[k] = xor_and(row.a[k], q.a[k], m);
                 gfw_mul_x(q);
             }
             b.w[0] = __builtin_amdgcn_alignbit(b.w[1], b.w[0], 8);
@@ -2242,7 +2248,7 @@ __device__ __forceinline__ GfWords lanes_summed(const KeyTables* __restrict__ kt
         for (uint32_t t = 0; t < kDotSlices; ++t) {
             const uint32_t m = (uint32_t)((int32_t)(v[t / 4] << (31 - 8 * (t % 4))) >> 31);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) acc.a[k] ^= q[t].a[k] & m;
+            for (int k = 0; k < 4; ++k) acc.a[k] = xor_and(acc.a[k], q[t].a[k], m);
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] >>= 1;
@@ -2831,7 +2837,7 @@ __device__ __forceinline__ GfWords bytes_dot(uint32_t v, const GfWords (&powers)
         for (uint32_t s = 0; s < 4; ++s) {
             const uint32_t m = (uint32_t)((int32_t)(v << (31 - 8 * s)) >> 31);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) sum.a[k] ^= powers[s].a[k] & m;
+            for (int k = 0; k < 4; ++k) sum.a[k] = xor_and(sum.a[k], powers[s].a[k], m);
         }
         v >>= 1;
     }
