@@ -87,15 +87,25 @@ struct SpanScratch {
     }
 };
 
-// What one more piece costs a workgroup of sixteen wavefronts, in rows: it ends 2 us later for it, 0.27
-// for a row more (300 adapters both ways with 2, 8: 198, 191 us); and a wavefront among them, in half
-// rows, which are 2.2 us.
-constexpr uint32_t kPieceRows = 8;
+// What one more piece costs a workgroup of sixteen wavefronts, in rows (300 adapters both ways with 8, 6, 5:
+// 159.9, 158.0, 157.9 us; 240 chunks of three keys 158.6 with each); and a wavefront among them, in half
+// rows, which are 2.2 us (300 adapters with 3, 4, 6: 160.1, 160.1, 159.5; 600 of 16 to 128 KB 101.1, 103.2,
+// 101.5; 100 of 0.1 to 1 MB 108.7, 108.8, 106.7).
+constexpr uint32_t kPieceRows = 6;
 constexpr uint32_t kPieceHalfRows = 6;
-// Shares of up to so many rows are cut with regard to the pieces they make (17 long chunks of two
-// keys both ways 57 -> 35 us, 284 chunks of 44 to 97 KB 87 -> 79); longer ones are better cut equal
-// (300 adapters, 17 rows a share: 187 and 194).
+// Shares of up to so many rows are cut with regard to the pieces they make all over the batch (17 long
+// chunks of two keys both ways 57 -> 35 us, 284 chunks of 44 to 97 KB 87 -> 79).  Longer ones are dealt
+// out to the workgroups by weight: with the line at 9, 100 of 0.1 to 1 MB take 104.0 instead of 106.9 us, 120
+// of 320 KiB 106.5 instead of 105.0, 400 of 64 to 128 KB and 50 of 0.2 to 2 MB the same.
 constexpr uint32_t kFineRows = 12;
+// Of these, up to so many rows and four chunks a workgroup, a workgroup's wavefronts get shares with regard
+// to its own pieces: cut equal, the wavefront with a chunk's end and the next one's beginning is the last by
+// 6 half rows (300 adapters both ways, 17 rows a share, 162.0 -> 159.5 us; 240 chunks of three keys 161.9 ->
+// 158.6; 500 of 320 KiB encrypted 171.9 -> 171.0; with up to 256 rows the same).  With more chunks the
+// workgroup has as many such wavefronts as others, and finding the shares takes the host longer (2000 of
+// 64 KiB 142.5 -> 144.6 us, waited for 174 -> 195).
+constexpr uint32_t kEvenRows = 64;
+constexpr uint32_t kEvenChunks = 4;
 
 // One key's chunks of a batch: n of them from the batch's chunk `first` on.
 struct KeyPart {
@@ -139,56 +149,55 @@ inline uint32_t deal_groups(KeyPart* parts, size_t nparts, uint32_t num_cu) {
     return total;
 }
 
+// The rows of neighbouring pieces in shares of wavefronts: a share holds `limit` half rows, the pieces'
+// beginnings and ends (kPieceHalfRows each) among them.  A piece that follows in a share with no room for a
+// row more goes to the next.
+struct ShareFill {
+    uint32_t limit, left, used;
+
+    explicit ShareFill(uint32_t half_rows) : limit(half_rows), left(half_rows), used(1) {}
+    uint32_t whole() const { return (limit - kPieceHalfRows) / 2; }  // rows of a share with one piece
+    // a piece of r rows from row `at` on; cut(row) where a share begins
+    template <class Cut>
+    void add(uint32_t at, uint32_t r, Cut&& cut) {
+        if (left >= kPieceHalfRows + 2) {
+            const uint32_t room = (left - kPieceHalfRows) / 2;
+            if (r <= room) {
+                left -= kPieceHalfRows + 2 * r;
+                return;
+            }
+            r -= room, at += room;
+        }
+        const uint32_t n = (r - 1) / whole() + 1;
+        for (uint32_t i = 0; i < n; ++i) cut(at + i * whole());
+        used += n;
+        left = limit - kPieceHalfRows - 2 * (r - (n - 1) * whole());
+    }
+};
+
 // Cuts a key's rows, which begin at `row`, into shares of at most 16 * key.groups wavefronts and deals
 // these out to its workgroups: the first rows of all wavefronts are appended to `cuts`, and
 // waves[g] is the number of the first wavefront of workgroup g.  rows: of each chunk.
 inline void cut_key(const KeyPart& key, uint32_t row, const uint32_t* rows, std::vector<uint32_t>& cuts,
              uint32_t* waves) {
     const uint32_t most = key.groups * kWavesPerGroup, base = (uint32_t)cuts.size();
+    auto counted = [](uint32_t) {};
+    auto kept = [&](uint32_t at) { cuts.push_back(at); };
     if (key.rows <= (uint64_t)most * kFineRows && key.n <= 2 * (size_t)most) {
-        // Where shares are short, what a wavefront spends on beginning and finishing pieces decides: a
-        // share holds `limit` half rows, pieces among them, as many as it takes for the wavefronts
-        // to do.  A chunk that follows in a share with no room for a row more goes to the next.
-        constexpr uint32_t kP = kPieceHalfRows;
-        uint32_t limit = (uint32_t)((2 * key.rows + kP * (key.n + most) + most - 1) / most);
-        if (limit < kP + 2) limit = kP + 2;
+        // Where shares are short, what a wavefront spends on beginning and finishing pieces decides: as
+        // many half rows a share as it takes for the wavefronts to do.
+        uint32_t limit = (uint32_t)((2 * key.rows + kPieceHalfRows * (key.n + most) + most - 1) / most);
+        if (limit < kPieceHalfRows + 2) limit = kPieceHalfRows + 2;
         for (;; limit += 1 + limit / 32) {
-            const uint32_t whole = (limit - kP) / 2;  // rows of a share with one piece
-            uint32_t used = 1, left = limit;
-            for (size_t k = 0; k < key.n; ++k) {
-                uint32_t r = rows[k];
-                if (left >= kP + 2) {
-                    const uint32_t room = (left - kP) / 2;
-                    if (r <= room) {
-                        left -= kP + 2 * r;
-                        continue;
-                    }
-                    r -= room;
-                }
-                const uint32_t n = (r + whole - 1) / whole;
-                used += n;
-                left = limit - kP - 2 * (r - (n - 1) * whole);
-            }
-            if (used <= most) break;
+            ShareFill fill(limit);
+            for (size_t k = 0; k < key.n; ++k) fill.add(0, rows[k], counted);
+            if (fill.used <= most) break;
         }
-        const uint32_t whole = (limit - kP) / 2;
-        uint32_t left = limit;
+        ShareFill fill(limit);
         cuts.push_back(row);
         for (size_t k = 0; k < key.n; ++k) {
-            uint32_t r = rows[k], at = row;
-            row += r;
-            if (left >= kP + 2) {
-                const uint32_t room = (left - kP) / 2;
-                if (r <= room) {
-                    left -= kP + 2 * r;
-                    continue;
-                }
-                r -= room;
-                at += room;
-            }
-            for (; r > whole; r -= whole, at += whole) cuts.push_back(at);
-            cuts.push_back(at);
-            left = limit - kP - 2 * r;
+            fill.add(row, rows[k], kept);
+            row += rows[k];
         }
         const uint32_t used = (uint32_t)cuts.size() - base;
         for (uint32_t g = 0; g < key.groups; ++g)
@@ -196,13 +205,43 @@ inline void cut_key(const KeyPart& key, uint32_t row, const uint32_t* rows, std:
         return;
     }
     // A workgroup begins where the weight so far reaches its share; a chunk's own weight comes before
-    // its rows'.  Its rows go to its wavefronts in equal parts.
+    // its rows'.  Its rows go to its wavefronts in equal parts, or, where these are not long, with regard
+    // to its pieces.
     uint64_t weight = 0, next = 0;
     uint32_t group = 0, begin = row;
+    const bool even = key.rows <= (uint64_t)most * kEvenRows && key.n <= kEvenChunks * (size_t)key.groups;
+    size_t first = 0;          // the chunk with row `begin`
+    uint32_t first_end = row + rows[0];  // ... and its end
     auto deal = [&](uint32_t end) {
         if (group > 0) {
             const uint32_t n = end - begin, w = n < kWavesPerGroup ? n : kWavesPerGroup;
-            for (uint32_t i = 0; i < w; ++i) cuts.push_back(begin + (uint32_t)((uint64_t)n * i / w));
+            while (first_end <= begin) first_end += rows[++first];
+            if (even && first_end < end) {
+                auto pieces = [&](ShareFill& fill, auto&& cut) {
+                    size_t k = first;
+                    for (uint32_t at = begin, till = first_end; at < end;) {
+                        const uint32_t stop = till < end ? till : end;
+                        fill.add(at, stop - at, cut);
+                        at = stop;
+                        if (at < end) till += rows[++k];
+                    }
+                };
+                uint32_t count = 1;
+                for (uint32_t till = first_end, k = (uint32_t)first; till < end; till += rows[++k]) ++count;
+                if (count < w) count = w;
+                uint32_t limit = (2 * n + kPieceHalfRows * count) / w;
+                if (limit < kPieceHalfRows + 2) limit = kPieceHalfRows + 2;
+                for (;; limit += 1 + limit / 64) {
+                    ShareFill fill(limit);
+                    pieces(fill, counted);
+                    if (fill.used <= w) break;
+                }
+                ShareFill fill(limit);
+                cuts.push_back(begin);
+                pieces(fill, kept);
+            } else {
+                for (uint32_t i = 0; i < w; ++i) cuts.push_back(begin + (uint32_t)((uint64_t)n * i / w));
+            }
         }
         begin = end;
     };

@@ -30,7 +30,7 @@ static uint64_t log_between(double lo, double hi) {
             exit(1);                                                                      \
         }                                                                                 \
     } while (0)
-static uint64_t g_batch, g_groups, g_parts, g_shared;
+static uint64_t g_batch, g_groups, g_parts, g_shared, g_even;
 
 static void check(const std::vector<uint64_t>& len, const std::vector<uint32_t>& aad_len,
                   const std::vector<uint32_t>& order, std::vector<KeyPart>& keys, uint32_t num_cu) {
@@ -85,6 +85,25 @@ static void check(const std::vector<uint64_t>& len, const std::vector<uint32_t>&
             CHECK(d.waves >= 1 && d.waves <= kWavesPerGroup && d.cut[0] == 0);
             for (uint32_t w = 0; w < d.waves; ++w) CHECK(d.cut[w] < d.cut[w + 1]);
             CHECK(d.nparts >= 1 && part + d.nparts <= plan.nparts);
+            // Shares cut with regard to the workgroup's pieces.  A share but the last is full up to the half
+            // rows of a piece of a row, less one, so that with limit >= mean + kPieceHalfRows + 2 no more
+            // are begun than there are wavefronts; the limit is the first tried that will do.
+            const uint64_t most = (uint64_t)key.groups * kWavesPerGroup;
+            if ((key.rows > most * kFineRows || key.n > 2 * most) && key.rows <= most * kEvenRows &&
+                key.n <= (uint64_t)kEvenChunks * key.groups && d.nparts > 1) {
+                const uint32_t rows = d.cut[d.waves], w = rows < kWavesPerGroup ? rows : kWavesPerGroup;
+                uint32_t enough = (2 * rows + kPieceHalfRows * (d.nparts + w)) / w + kPieceHalfRows + 3;
+                enough += 1 + enough / 64;
+                for (uint32_t i = 0; i < d.waves; ++i) {
+                    uint32_t cost = 2 * (d.cut[i + 1] - d.cut[i]);
+                    for (uint32_t q = 0; q < d.nparts; ++q) {
+                        const SpanPart& c = parts[part + q];
+                        cost += i >= (c.waves & 0xFF) && i < (c.waves & 0xFF) + (c.waves >> 8) ? kPieceHalfRows : 0;
+                    }
+                    CHECK(cost <= enough);
+                }
+                ++g_even;
+            }
             row += d.cut[d.waves];
             part += d.nparts;
             if (d.nparts > longest) longest = d.nparts;
@@ -176,6 +195,7 @@ int main() {
         std::vector<KeyPart> keys{KeyPart{nullptr, tables, 14, 0, 2, 0, 0, 0}};
         check({rows * 16 * kRowBlocks, 5}, {1024, 1025}, {1, 0}, keys, 256);
     }
+    CHECK(g_even > 10000);
     printf("batches %llu, %llu of them of keys that share a launch, workgroups %llu, parts %llu\n",
            (unsigned long long)g_batch, (unsigned long long)g_shared, (unsigned long long)g_groups,
            (unsigned long long)g_parts);
