@@ -2576,6 +2576,9 @@ PGCM_INSTANTIATE_SWAP(true);
 //     64 columns are multiplied with H^64 .. H^1 bit by bit (KeyTables::dot), a word a wavefront.  Fewer
 //     wavefronts: every lane multiplies its own word, by the power that takes its block to the end of the
 //     pass, and there is nothing to fold.
+//     Without a fold and with fewer wavefronts to bring the tables in a pass is over sooner, so that batches
+//     of up to a pass of 64 or 128 blocks a compute unit are made so (one_pass_each: 250 KiB 7.5 -> 6.4 us,
+//     320 KiB 7.5 -> 6.9).  Passes of 256 blocks in that way are no gain: 700 KiB 7.6 -> 8.3.
 //   * E_K(J0) is the keystream of "block -1" where there is a lane for it, otherwise a second block in
 //     every quad of one wavefront, its steps between the first one's.
 // A pass's sum is taken to the chunk's end with one more product (KeyTables::row_hop; past 4 MiB, one

@@ -98,13 +98,38 @@ inline bool first_burst_choice(uint64_t passes, size_t n, uint64_t most, Groups 
     return true;
 }
 
+// Passes of 64 blocks, or of 128, if no workgroup has to make more than one.  Their workgroups multiply every
+// word by its own power and have no rows to fold, and four or eight wavefronts bring the tables in and make
+// their blocks sooner than sixteen do.  Of 64 where there are compute units for them, unless only of 128 a
+// chunk's shares are added up in one set (kArriveSet; 40 KiB in 20 workgroups 6.25 us, in 40 6.46).  Per call,
+// passes of 256, 128 and 64 blocks: 16 KiB 6.8, 6.3, 5.9; 96 KiB 7.0, 6.9, 6.4; 250 KiB 7.5, 6.9, 6.4; 16 of
+// 12 KiB 7.5, 6.9, 6.3; 320 KiB 7.5, 6.9; 20 of 20 KiB 7.5, 7.0; three of 100 KiB, which 256 blocks have in one
+// set each, 7.5, 7.3.  A first workgroup with a pass more, two passes of 128 blocks (320 KiB 8.4, 700 KiB 8.8
+// instead of 7.6) and two workgroups on a compute unit (10 of 90 KiB 10.2 instead of 7.6) are all longer.
+inline bool one_pass_each(const ShapeBatch& a, uint32_t most, SwapShape* shape) {
+    uint64_t total[2] = {0, 0}, longest[2] = {0, 0};
+    for (size_t k = 0; k < a.n; ++k) {
+        const uint64_t blocks = burst_blocks(a, a.at(k));
+        for (uint32_t w = 0; w < 2; ++w) {
+            const uint64_t groups = burst_groups(burst_passes(blocks, 2 + w), 1, 0);
+            total[w] += groups;
+            if (groups > longest[w]) longest[w] = groups;
+        }
+    }
+    const bool four = total[0] <= most && (longest[0] <= kArriveSet || longest[1] > kArriveSet);
+    if (!four && total[1] > most) return false;
+    const uint64_t groups = total[four ? 0 : 1];
+    *shape = SwapShape{true, groups == a.n, 1, four ? 2u : 3u, (uint32_t)groups, 0};
+    return true;
+}
+
 // Batches of short chunks, and others of at most sixteen passes for every compute unit, go to burst_kernel.
 // As long as there is a compute unit for every short chunk, a workgroup takes a whole one, with no
 // more wavefronts than it has blocks for; of more chunks, two workgroups share a compute unit: of at most
 // eight wavefronts and one pass, of which the longer chunks take several, if 512 of them do; otherwise of
 // sixteen and one pass, if 512 of these do (346 chunks of 1.6 to 8.1 KB 13.4 us, a workgroup each 16.2; 450 of up
-// to 8 KB 12.9, 14.7); otherwise of sixteen and a whole chunk.  Longer chunks are spread over as many
-// workgroups of sixteen as there are compute units, with the fewest passes that go: first with none spare,
+// to 8 KB 12.9, 14.7); otherwise of sixteen and a whole chunk.  Longer chunks are spread over workgroups of
+// four or eight that make one pass (one_pass_each), or over as many of sixteen as there are compute units, with the fewest passes that go: first with none spare,
 // then with one for the first workgroup of each chunk, which is what a few blocks too many take (2 MiB
 // with AAD in 257 workgroups of two passes: 256 take 11.8 us, four passes in 129 took 14.8; 8 of
 // 256 KiB with AAD 12.3, were 14.7), then with one more (2.3 to 3 MB in three 12.1, in four 14.2).
@@ -148,6 +173,7 @@ inline bool swap_shape(const ShapeBatch& a, uint32_t num_cu, bool one_launch, ui
             passes += of_chunk[k];
         }
         BurstChoice c;
+        if (passes <= most && one_pass_each(a, most, shape)) return true;
         if (first_burst_choice(
                 passes, a.n, most, [&](BurstChoice b) { return burst_groups_of_all(of_chunk, a.n, b); },
                 &c, &total)) {

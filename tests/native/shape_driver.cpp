@@ -24,7 +24,7 @@ static uint64_t log_between(double lo, double hi) {
     return (uint64_t)(lo * std::pow(hi / lo, (double)(rnd() >> 11) / 9007199254740992.0));
 }
 
-static unsigned long long g_batch, g_bursts, g_swept, g_units, g_none, g_most;
+static unsigned long long g_batch, g_words, g_bursts, g_swept, g_units, g_none, g_most;
 #define CHECK(cond)                                                      \
     do {                                                                 \
         if (!(cond)) {                                                   \
@@ -47,6 +47,16 @@ static uint64_t groups_of(const ShapeBatch& a, uint64_t pass_blocks, uint64_t pa
         sum += g;
     }
     return sum;
+}
+
+static uint64_t most_groups(const ShapeBatch& a, uint64_t pass_blocks) {
+    uint64_t most = 0;
+    for (size_t k = 0; k < a.n; ++k) {
+        const uint64_t i = a.at(k), g = groups_of(ShapeBatch{1, nullptr, a.aad_len ? a.aad_len + i : nullptr, a.len + i},
+                                                  pass_blocks, 1, 0);
+        if (g > most) most = g;
+    }
+    return most;
 }
 
 // the passes of a chunk's first workgroup, which makes the most
@@ -95,6 +105,15 @@ static void check(const ShapeBatch& a, uint32_t num_cu, uint32_t forced) {
     const uint32_t most = num_cu < kSwapChunkGroups ? num_cu : kSwapChunkGroups;
     const bool considered = a.n <= most && bytes <= (uint64_t)most * kWavesPerGroup * kUnitBytes;
     bool found = false;
+    // a pass of 64 or 128 blocks for every workgroup
+    for (uint32_t wp = 2; considered && forced <= kMinUnitPower && wp <= 3 && !found; ++wp) {
+        const uint64_t total = groups_of(a, 16u << wp, 1, 0);
+        if (total > most || (wp == 2 && most_groups(a, 64) > kArriveSet && most_groups(a, 128) <= kArriveSet)) continue;
+        CHECK(goes && s.burst && s.wave_power == wp && s.unit_power == 1 && s.spare == 0 && s.groups == total);
+        CHECK(s.alone == (total == a.n) && most_passes(a, s) == 1);
+        ++g_words;
+        return;
+    }
     for (uint32_t passes = 1; considered && forced <= kMinUnitPower && passes <= kSweptPasses && !found; ++passes)
         for (uint32_t spare = 0; spare <= (passes < kSweptPasses ? 1u : 0u) && !found; ++spare) {
             const uint64_t total = groups_of(a, 256, passes, spare);
@@ -213,7 +232,7 @@ int main() {
                            len.data()};
         check(a, num_cu, below(6) ? 0 : kMinUnitPower + below(kUnitPower - kMinUnitPower + 1));
     }
-    printf("batches %llu: bursts %llu, in sweeps %llu, in units %llu, neither %llu; chunks gone over %llu times at most\n",
-           g_batch, g_bursts, g_swept, g_units, g_none, g_most);
+    printf("batches %llu: in passes of 64 and 128 %llu, other bursts %llu, in sweeps %llu, in units %llu, neither %llu; chunks gone over %llu times at most\n",
+           g_batch, g_words, g_bursts, g_swept, g_units, g_none, g_most);
     return 0;
 }

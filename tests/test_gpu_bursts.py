@@ -44,6 +44,18 @@ SHAPES = {
     "short_aad": ([0, 1] + _EDGES, [16, 0, 5, 64, 17, 1, 48]),
     # the AAD fills lanes, a pass, and is longer than goes in lanes
     "long_aad": ([0, 5, 1024, 4096, 4097, 8192], [1008, 1024, 1025, 16, 3000, 1024]),
+    # workgroups of one pass of 64 blocks or of 128: as many as there are compute units, a set of shares and one
+    # more, both in one launch, and payload, AAD and "block -1" at the edges of a pass
+    "apart_64_most": ([256 * 1024], [0]),
+    "apart_64_set": ([32 * 1024, 16 * 1024 + 1], [0]),
+    "apart_128_set": ([32 * 1024 + 1], [0]),
+    "apart_64_sets": ([64 * 1024 + 1], [0]),
+    "apart_128_most": ([512 * 1024 - 16], [16]),
+    "apart_128_over": ([256 * 1024], [7]),
+    "apart_64_edges": ([9000, 0, 1] + [16 * b + d for b in (64, 128, 576) for d in (-1, 0, 1)],
+                       [0, 1008, 16, 1024, 3000, 1025, 33]),
+    "apart_128_edges": ([290 * KIB, 0, 1] + [16 * b + d for b in (128, 256, 640) for d in (-1, 0, 1)],
+                        [1024, 1008, 16, 0, 3000, 1025, 33]),
     # workgroups of one to four passes, some of them short; in 2 and 4 a chunk's first may make one more
     "two": ([300 * KIB, 8 * KIB + 16, 9000, 1], [0, 16, 70]),
     "passes_1": (_MORE + [200 * KIB], [0, 16]),
@@ -91,7 +103,7 @@ def test_shapes(shape):
 
 
 @pytest.mark.parametrize("key_bytes,iv_bytes", [(16, 12), (24, 16), (32, 8), (16, 40), (32, 1040)])
-@pytest.mark.parametrize("shape", ["short_aad", "passes_1", "passes_4", "sweeps_2_missing", "many_even",
+@pytest.mark.parametrize("shape", ["short_aad", "passes_1", "apart_64_edges", "apart_128_edges", "passes_4", "sweeps_2_missing", "many_even",
                                    "many_mixed", "many_apart"])
 def test_other_keys_and_ivs(shape, key_bytes, iv_bytes):
     lens, alens = SHAPES[shape]

@@ -22,7 +22,7 @@ def _lens(passes, n):
 # chunk lengths, forced unit size, one launch, and the kernel with the most passes of a workgroup
 SHAPES = {
     "words": ([1, 16, 40, 1000, 2031, 0, 2032, 300, 17, 5, 64, 100], 0, True, "words"),
-    "one": (_lens(3, 12), 0, True, "fold 1"),
+    "one": (_lens(3, 12), 0, True, "words"),
     "two": (_lens(3, 150), 0, True, "fold 3"),
     "four": (_lens(16, 48), 0, True, "fold 4"),
     "sweeps": (_lens(9, 130) + _lens(6, 100), 0, True, "sweep 9"),

@@ -53,7 +53,7 @@ def _random_workload(seed):
 
 # seeds, forced unit size, one launch, and the kernels these batches take (tests/test_routes.py)
 WAYS = {
-    "as they go": (range(0, 48), 0, True, "fold sweep"),
+    "as they go": (range(0, 48), 0, True, "words fold sweep"),
     "units in one launch": (range(61, 65), 2048, True, "swap"),
     "units": (range(66, 70), 0, False, "bulk"),
     "many": (range(91, 94), 0, True, "span"),

@@ -62,7 +62,7 @@ def test_bursts(kernels_of):
     got = dict(zip(shapes, kernels_of([(lens, np.resize(alens, len(lens)), 0, 1)
                                        for lens, alens in shapes.values()])))
     # the most passes of a workgroup, a chunk's first
-    most = {"passes_1": 1, "passes_2": 3, "passes_3": 3, "passes_4": 3, "even_2": 2, "even_4": 4, "even_4_some": 4,
+    most = {"passes_2": 3, "passes_3": 3, "passes_4": 3, "even_2": 2, "even_4": 4, "even_4_some": 4,
             "spare_1": 2, "spare_1_payload": 2, "spare_1_long_aad": 2, "spare_2": 3, "spare_3": 4,
             "spare_of_some": 3}
     sweeps = {"sweeps_2": 2, "sweeps_2_whole": 2, "sweeps_2_spare": 3, "sweeps_2_missing": 2,
@@ -75,6 +75,7 @@ def test_bursts(kernels_of):
             assert kind == "sweep" and -(-int(passes) // 4) == sweeps[name], (name, kernel)
         else:
             assert kind in ("words", "fold", "shared"), (name, kernel)
+    assert {k for n, k in got.items() if n.startswith("apart_") or n == "passes_1"} == {"words"}
     assert {got[n] for n in ("many_even", "many_long")} == {"shared"} and got["many_mixed"] == "words"
     assert {got[n] for n in ("many_apart", "many_apart_512")} == {"shared apart"} and got["many_apart_513"] == "shared"
 
@@ -119,7 +120,7 @@ def test_captured_and_reserved_batches(kernels_of):
 
 def test_batches_in_fixed_buffers(kernels_of):
     got = kernels_of([_of_workload(w) + (True,) for w in test_zz_no_alloc._batches()])
-    assert got == ["bulk", "swap 8192", "fold 1", "fold 4"], got
+    assert got == ["bulk", "swap 8192", "words", "fold 4"], got
 
 
 def test_long_aad(kernels_of):
