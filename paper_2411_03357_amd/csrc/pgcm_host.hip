@@ -987,8 +987,9 @@ int note_capture(BatchArgs& a) {
     return PGCM_OK;
 }
 
-RouteOptions route_options(const pgcm_key* key, bool fixed) {
-    return RouteOptions{(uint32_t)key->num_cu, key->one_launch, key->matrix_hash, key->forced_unit_power, fixed};
+RouteOptions route_options(const pgcm_key* key, bool fixed, bool capturing) {
+    return RouteOptions{(uint32_t)key->num_cu, key->one_launch, key->matrix_hash, key->forced_unit_power, fixed,
+                        capturing};
 }
 
 // One batch under one key: validate everything, choose the way it goes, pick a context unless it
@@ -1000,18 +1001,19 @@ int run_batch(pgcm_key* key, BatchArgs a) {
     BatchSurvey v;
     rc = survey_batch(a, &v);
     if (rc != PGCM_OK) return rc;
-    const RouteOptions options = route_options(key, a.fixed);
-    SwapShape shape{};
-    const Route route = route_batch(ShapeBatch{a.n, a.order, a.aad_len, a.len}, options, v, &shape);
     // the units, unless they are not wanted anyway; nothing touched so far
     BatchPlan p{};
-    if (!may_go_in_spans(options, v)) rc = plan_batch(key->forced_unit_power, key->wave_slots, a, &p);
+    if (!may_go_in_spans(route_options(key, a.fixed, false), v))
+        rc = plan_batch(key->forced_unit_power, key->wave_slots, a, &p);
     if (rc != PGCM_OK) return rc;
     int cur_device = -1;
     PGCM_HIP(hipGetDevice(&cur_device));
     if (cur_device != key->device) return PGCM_ERR_ARG;  // the key lives on another GPU
     rc = note_capture(a);
     if (rc != PGCM_OK) return rc;
+    SwapShape shape{};
+    const Route route = route_batch(ShapeBatch{a.n, a.order, a.aad_len, a.len},
+                                    route_options(key, a.fixed, a.capturing), v, &shape);
     if (a.fixed && a.n > kFixedMaxChunks) return PGCM_ERR_CAPACITY;
     const bool one_launch = route == Route::kOneLaunch;
     if (one_launch && shape.alone && a.n <= kArgChunks) return run_one_launch(key, nullptr, a, shape);
@@ -1086,7 +1088,7 @@ int run_batch_keys(pgcm_key* const* keys, size_t nkeys, const uint32_t* key_inde
         for (size_t k = 0; k < nkeys; ++k) {
             const KeyPart& part = parts[k];
             if (part.n == 0) continue;
-            if (!takes_spans(route_options(keys[k], false), part.rows, part.longest) ||
+            if (!takes_spans(route_options(keys[k], false, false), part.rows, part.longest) ||
                 !share_launch(1, part.n, part.rows, num_cu)) {
                 alone.push_back(k);
                 continue;

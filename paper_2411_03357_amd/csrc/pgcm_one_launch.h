@@ -125,7 +125,12 @@ inline bool one_pass_each(const ShapeBatch& a, uint32_t most, SwapShape* shape) 
 
 // Batches of short chunks, and others of at most sixteen passes for every compute unit, go to burst_kernel.
 // As long as there is a compute unit for every short chunk, a workgroup takes a whole one, with no
-// more wavefronts than it has blocks for; of more chunks, two workgroups share a compute unit: of at most
+// more wavefronts than it has blocks for.  Up to kArgChunks of them, one longer than a pass of 256 blocks, go in
+// workgroups of one pass instead (one_pass_each), if `spread` lets them: back to back and waited for, one of 8 KiB
+// 7.6 -> 5.8 and 19.6 -> 18.1 us, with AAD 9.1 -> 5.7 and 21.1 -> 18.1, 32 of 8 KiB decrypted 8.2 -> 6.5 and 20.3 ->
+// 18.9, 60 of up to 8 KiB with AAD 7.9 -> 6.8 and 20.5 -> 19.2.  Shorter ones are no better off (16 of 4 KiB 6.6 ->
+// 6.3 and 18.5 -> 18.8, 64 of them decrypted 6.7 -> 7.0), nor are more (120 of up to 8 KiB 9.0 -> 9.7).
+// Of more chunks than compute units, two workgroups share one: of at most
 // eight wavefronts and one pass, of which the longer chunks take several, if 512 of them do; otherwise of
 // sixteen and one pass, if 512 of these do (346 chunks of 1.6 to 8.1 KB 13.4 us, a workgroup each 16.2; 450 of up
 // to 8 KB 12.9, 14.7); otherwise of sixteen and a whole chunk.  Longer chunks are spread over workgroups of
@@ -139,11 +144,13 @@ inline bool one_pass_each(const ShapeBatch& a, uint32_t most, SwapShape* shape) 
 // of whole 128 KiB without AAD, which eight wavefronts with units of sixteen rows cover, are a block
 // ("block -1") too long for sixteen with units of eight, as these have no further wavefront for it.
 constexpr uint32_t kLongUnitPower = kRowPower + 3;
-// forced: log2 of the blocks of a unit, or 0; all_small: no chunk is longer than kSmallChunkBytes.
+// forced: log2 of the blocks of a unit, or 0; all_small: no chunk is longer than kSmallChunkBytes; spread: of
+// these a chunk may have several workgroups, for which the batch needs a workspace.
 inline bool swap_shape(const ShapeBatch& a, uint32_t num_cu, bool one_launch, uint32_t forced, bool all_small,
-                       SwapShape* shape) {
+                       bool spread, SwapShape* shape) {
     if (a.n > kSmallMaxChunks || (!all_small && !one_launch)) return false;
     uint64_t total = 0;
+    const uint32_t most = num_cu < kSwapChunkGroups ? num_cu : kSwapChunkGroups;
     if (all_small) {
         uint64_t most_blocks = 0, of_eight = 0, of_sixteen = 0;
         for (size_t k = 0; k < a.n; ++k) {
@@ -154,13 +161,15 @@ inline bool swap_shape(const ShapeBatch& a, uint32_t num_cu, bool one_launch, ui
         }
         uint32_t wp = 2, passes = kFoldPasses;
         while (wp < 4 && most_blocks > (uint64_t)16 << wp) ++wp;
+        if (spread && a.n <= kArgChunks && a.n <= most && most_blocks > (uint64_t)16 << wp &&
+            one_pass_each(a, most, shape))
+            return true;
         total = a.n;
         if (a.n > num_cu && wp > 2 && of_eight <= kSwapMaxGroups) wp = 3, passes = 1, total = of_eight;
         else if (a.n > num_cu && wp == 4 && of_sixteen <= kSwapMaxGroups) passes = 1, total = of_sixteen;
         *shape = SwapShape{true, total == a.n, passes, wp, (uint32_t)total, 0};
         return true;
     }
-    const uint32_t most = num_cu < kSwapChunkGroups ? num_cu : kSwapChunkGroups;
     if (a.n > most) return false;
     uint64_t bytes = 0;
     for (size_t k = 0; k < a.n; ++k) bytes += a.len[a.at(k)];

@@ -24,7 +24,7 @@ static uint64_t log_between(double lo, double hi) {
     return (uint64_t)(lo * std::pow(hi / lo, (double)(rnd() >> 11) / 9007199254740992.0));
 }
 
-static unsigned long long g_batch, g_words, g_bursts, g_swept, g_units, g_none, g_most;
+static unsigned long long g_batch, g_spread, g_words, g_bursts, g_swept, g_units, g_none, g_most;
 #define CHECK(cond)                                                      \
     do {                                                                 \
         if (!(cond)) {                                                   \
@@ -80,13 +80,23 @@ static void check(const ShapeBatch& a, uint32_t num_cu, uint32_t forced) {
     }
     const bool all_small = longest <= kSmallChunkBytes;
     SwapShape s{};
-    const bool goes = swap_shape(a, num_cu, true, forced, all_small, &s);
+    const bool spread = g_batch % 2 != 0;
+    const bool goes = swap_shape(a, num_cu, true, forced, all_small, spread, &s);
     ++g_batch;
     if (all_small) {
         CHECK(goes == (a.n <= kSmallMaxChunks));
         if (!goes) return;
         CHECK(s.burst && s.spare == 0 && s.groups >= a.n && s.groups <= kSwapMaxGroups);
         CHECK(s.alone == (s.groups == a.n));
+        // a pass of 64 or 128 blocks for every workgroup of few chunks, one of them longer than 256
+        const uint32_t most = num_cu < kSwapChunkGroups ? num_cu : kSwapChunkGroups;
+        if (spread && a.n <= kArgChunks && a.n <= most && most_groups(a, 256) > 1 && groups_of(a, 128, 1, 0) <= most) {
+            const uint64_t of_four = groups_of(a, 64, 1, 0);
+            CHECK(!s.alone && s.unit_power == 1 && s.wave_power == (of_four <= most ? 2u : 3u));
+            CHECK(s.groups == (of_four <= most ? of_four : groups_of(a, 128, 1, 0)) && most_passes(a, s) == 1);
+            ++g_spread;
+            return;
+        }
         if (s.alone) CHECK(groups_of(a, (uint64_t)16 << s.wave_power, s.unit_power, 0) == a.n || a.n > num_cu);
         if (a.n > num_cu && s.wave_power > 2) {
             const uint64_t of_eight = groups_of(a, 128, 1, 0), of_sixteen = groups_of(a, 256, 1, 0);
@@ -232,7 +242,7 @@ int main() {
                            len.data()};
         check(a, num_cu, below(6) ? 0 : kMinUnitPower + below(kUnitPower - kMinUnitPower + 1));
     }
-    printf("batches %llu: in passes of 64 and 128 %llu, other bursts %llu, in sweeps %llu, in units %llu, neither %llu; chunks gone over %llu times at most\n",
-           g_batch, g_words, g_bursts, g_swept, g_units, g_none, g_most);
+    printf("batches %llu: in passes of 64 and 128 %llu, short ones %llu, other bursts %llu, in sweeps %llu, in units %llu, neither %llu; chunks gone over %llu times at most\n",
+           g_batch, g_words, g_spread, g_bursts, g_swept, g_units, g_none, g_most);
     return 0;
 }

@@ -56,6 +56,11 @@ SHAPES = {
                        [0, 1008, 16, 1024, 3000, 1025, 33]),
     "apart_128_edges": ([290 * KIB, 0, 1] + [16 * b + d for b in (128, 256, 640) for d in (-1, 0, 1)],
                         [1024, 1008, 16, 0, 3000, 1025, 33]),
+    # short chunks, some of them in several workgroups of one pass of 64 blocks or of 128; and too many for that
+    "spread_64_most": ([8192] * 32, [0]),
+    "spread_64_edges": ([0, 1, 8192] + _EDGES[12:], [1008, 0, 16, 1025, 3000, 33]),
+    "spread_128_most": ([8192 - 16 * (i % 3) for i in range(56)] + [4096] * 8, [0]),
+    "whole": ([8192] * 65 + _EDGES, [0]),
     # workgroups of one to four passes, some of them short; in 2 and 4 a chunk's first may make one more
     "two": ([300 * KIB, 8 * KIB + 16, 9000, 1], [0, 16, 70]),
     "passes_1": (_MORE + [200 * KIB], [0, 16]),
@@ -103,7 +108,7 @@ def test_shapes(shape):
 
 
 @pytest.mark.parametrize("key_bytes,iv_bytes", [(16, 12), (24, 16), (32, 8), (16, 40), (32, 1040)])
-@pytest.mark.parametrize("shape", ["short_aad", "passes_1", "apart_64_edges", "apart_128_edges", "passes_4", "sweeps_2_missing", "many_even",
+@pytest.mark.parametrize("shape", ["short_aad", "passes_1", "apart_64_edges", "apart_128_edges", "spread_64_edges", "passes_4", "sweeps_2_missing", "many_even",
                                    "many_mixed", "many_apart"])
 def test_other_keys_and_ivs(shape, key_bytes, iv_bytes):
     lens, alens = SHAPES[shape]

@@ -29,10 +29,10 @@ def kernels_of(tmp_path_factory):
     assert build.returncode == 0, build.stdout
 
     def run(batches):
-        """batches: (lengths, AAD lengths, forced unit bytes, one launch[, fixed buffers])"""
+        """batches: (lengths, AAD lengths, forced unit bytes, one launch[, 1: fixed buffers, 2: captured])"""
         lines = []
         for lens, alens, unit_bytes, one_launch, *fixed in batches:
-            lines.append("256 %d 0 %d %d " % (one_launch, unit_bytes, bool(fixed)) +
+            lines.append("256 %d 0 %d %d " % (one_launch, unit_bytes, fixed[0] if fixed else 0) +
                          " ".join("%d %d" % (n, a) for n, a in zip(lens, alens)))
         out = subprocess.run([exe], input="\n".join(lines) + "\n", stdout=subprocess.PIPE,
                              stderr=subprocess.PIPE, text=True, env=ENV)
@@ -76,6 +76,10 @@ def test_bursts(kernels_of):
         else:
             assert kind in ("words", "fold", "shared"), (name, kernel)
     assert {k for n, k in got.items() if n.startswith("apart_") or n == "passes_1"} == {"words"}
+    assert {k for n, k in got.items() if n.startswith("spread_")} == {"words"} and got["whole"] == "fold 4"
+    # short chunks have one workgroup each, as ever, where they are captured, in fixed buffers or go in units
+    short = [shapes["spread_64_most"][0], [0] * 32]
+    assert kernels_of([(*short, 0, 1, 2), (*short, 0, 1, 1), (*short, 0, 0)]) == ["fold 4"] * 3
     assert {got[n] for n in ("many_even", "many_long")} == {"shared"} and got["many_mixed"] == "words"
     assert {got[n] for n in ("many_apart", "many_apart_512")} == {"shared apart"} and got["many_apart_513"] == "shared"
 
@@ -108,7 +112,7 @@ def test_captured_and_reserved_batches(kernels_of):
                 "spans_uploaded": "span", "one_row": "small", "units": "bulk", "one_launch_units": "swap"}
     for name, (lens, unit_bytes) in test_gpu_graphs.SHAPES.items():
         lens = lens(np.random.default_rng([workloads.BASE_SEED, 5040, len(name)]))
-        got, = kernels_of([(lens, [20] * len(lens), unit_bytes, 1)])
+        got, = kernels_of([(lens, [20] * len(lens), unit_bytes, 1, 2)])
         assert got.split()[0] == expected[name], (name, got)
     expected = {"one_launch": "sweep", "spans_few": "span", "spans_host": "span", "spans_uploaded": "span",
                 "one_row": "small"}
