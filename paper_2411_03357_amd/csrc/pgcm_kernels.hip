@@ -399,7 +399,7 @@ __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict_
         GfWords p = h_power[kDotBlocks + 1 - l];
         for (uint32_t i = 0; i < t; ++i) gfw_mul_x8(p);
         for (uint32_t i = t; i < t + kDotSlices / 4; ++i) {
-            kt->dot[i][l] = p;
+            kt->dot[l / kRowBlocks][i % 4][i / 4][l % kRowBlocks] = p;
             gfw_mul_x8(p);
         }
     }
@@ -2122,7 +2122,7 @@ __device__ __attribute__((noinline)) Block long_hash(const KeyTables* __restrict
         GfWords row{{0, 0, 0, 0}};
 #pragma unroll 1
         for (uint32_t t = 0; t < kDotSlices; ++t) {
-            GfWords q = kt->dot[t][kDotBlocks - kRowBlocks + lane];
+            GfWords q = kt->dot[kRowDot][t % 4][t / 4][lane];
             uint32_t v = b.w[0], bits = 8;
             // (the power times the bits of the byte, the first coefficient at its top)
             v <<= 24;
@@ -2236,8 +2236,17 @@ __device__ __forceinline__ Block length_block_entry(const Block* __restrict__ h_
 __device__ __forceinline__ GfWords lanes_summed(const KeyTables* __restrict__ kt, uint32_t lane,
                                                 const uint32_t y[4]) {
     GfWords q[kDotSlices];
+    // (an instruction's offset reaches four slices: a scalar base for every four, and one offset in a register)
 #pragma unroll
-    for (uint32_t t = 0; t < kDotSlices; ++t) q[t] = kt->dot[t][kDotBlocks - kRowBlocks + lane];
+    for (uint32_t b = 0; b < 4; ++b) {
+        uint64_t base = reinterpret_cast<uint64_t>(kt->dot[kRowDot][b]);
+        asm("" : "+s"(base));
+#pragma unroll
+        for (uint32_t w = 0; w < 4; ++w) {
+            const u32x4 v = reinterpret_cast<global_u128_cptr>(base)[w * kRowBlocks + lane];
+            q[4 * w + b] = GfWords{{v[0], v[1], v[2], v[3]}};
+        }
+    }
     GfWords acc{{0, 0, 0, 0}};
     uint32_t v[4] = {y[0], y[1], y[2], y[3]};
     // (a loop: unrolled, its masks are made ahead of their use and take the registers of the powers)
@@ -2425,7 +2434,8 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
                 if (k < per_thread) tree[k] = from[(k << (6 + wave_power)) + tid];
 #pragma unroll
             for (uint32_t s = 0; s < 4; ++s)
-                if (s < slices) q[s] = kt->dot[slices * wave + s][kDotBlocks - kRowBlocks + lane];
+                if (s < slices)
+                    q[s] = kt->dot[kRowDot][(slices * wave + s) % 4][(slices * wave + s) / 4][lane];
         }
         if (finisher) {
             if (ngroups - 1 != g) hop = kt->hop[p + wave_power - kHopMinPower][ngroups - 1 - g];
@@ -3048,12 +3058,12 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     // a word's four bytes: of the lane's own, or of a column of the pass when its rows are folded
     GfWords powers[4];
     auto fetch_powers = [&]() __attribute__((always_inline)) {
-        const GfWords* const from =
-            kFold ? &kt->dot[4 * (wave & 3)][kDotBlocks - kRowBlocks + lane]
-                  : &kt->dot[4 * column][kDotBlocks - pass_blocks + 16 * wave + (lane >> 2)];
+        const uint32_t first = kDotBlocks - pass_blocks + 16 * wave;  // of the wavefront, where a quad has a block
+        const GfWords* const from = kFold ? &kt->dot[kRowDot][0][wave & 3][lane]
+                                          : &kt->dot[first / kRowBlocks][0][column][first % kRowBlocks + (lane >> 2)];
         if (!kFold || wave < 4 * folded)
 #pragma unroll
-            for (uint32_t s = 0; s < 4; ++s) powers[s] = from[s * kDotBlocks];
+            for (uint32_t s = 0; s < 4; ++s) powers[s] = from[s * 4 * kRowBlocks];
     };
     if constexpr (kKind != BurstKind::kFoldShared) fetch_powers();
     u32x4 fold[2];  // the latter only of the first half of the threads, or in the other half for sweeps
@@ -3458,12 +3468,11 @@ __global__ __launch_bounds__(kGroupThreads) void span_kernel(
         te.fetch(kt, tid);
         // the threads without an entry of the row hash bring what the end needs into the caches: a
         // line each of the powers and of H's table
-        constexpr uint32_t kLines = kRowBlocks * sizeof(GfWords) / 128;
         const uint32_t t = tid - kNibbleTableEntries;
         const uint8_t* const from =
             tid < kNibbleTableEntries ? reinterpret_cast<const uint8_t*>(&kt->ghash[kRowPower][tid])
-            : t < kDotSlices * kLines
-                ? reinterpret_cast<const uint8_t*>(&kt->dot[t / kLines][kDotBlocks - kRowBlocks]) + t % kLines * 128
+            : t < sizeof(kt->dot[kRowDot]) / 128
+                ? reinterpret_cast<const uint8_t*>(kt->dot[kRowDot]) + t * 128
                                         : reinterpret_cast<const uint8_t*>(kt->ghash[0]) + t % 64 * 128;
         gh = global_read128(from);
         key_word = lane < 60 ? kt->rk[lane] : lane == 60 ? kt->rounds : 0u;

@@ -58,13 +58,20 @@ constexpr uint32_t kNumLanePowers = 3;
 // The latency path sums a set's 64 lanes as 64 products of a sum with a known power of H, all
 // at once and bit by bit, and moves a workgroup's result to its place with one more such product:
 // it needs powers of H as plain values, held as four words with coefficient x^0 in the top bit of
-// the first (GfWords).  dot[t][i] = H^(257 - i) * x^(8 t), the multiplication by H that follows
-// the length block included (a row of 64 blocks takes the last 64 of them);  hop[d][k] = H^(k 2^(8 + d)).
+// the first (GfWords).  dot[g][b][w][i] = H^(257 - (64 g + i)) * x^(8 (4 w + b)), the slice of
+// byte b of word w, the multiplication by H that follows the length block included (a row of 64 blocks takes
+// the last 64 of them, dot[kRowDot]);  hop[d][k] = H^(k 2^(8 + d)).
 // A power's slices lie apart and neighbouring powers together: a lane takes a power each, so that a
 // wavefront's load of a slice is 1 KiB in one piece (with a power's sixteen slices together it touched 64
 // lines: 2 MiB decrypted 9.39 -> 9.14 us, 8 MiB both ways 40.5 -> 38.7, 64 chunks of 4 KiB 13.7 -> 13.3).
+// The slices of 64 powers are 16 KiB in one piece, from a cache line's beginning, so that one address reaches four
+// of them: with all slices 4 KiB apart sixteen loads held an address each, and swap_kernel and the long-IV kinds
+// of span_kernel spilled (28 MB in one chunk 48.0 -> 47.3 us, 90 chunks of 4 to 500 KB with 40-byte IVs decrypted
+// 41.8 -> 39.5, 300 of 3 KiB with such 18.0 -> 16.0).  A word's four are 4 KiB apart, as bursts read them: in one
+// piece, 64 chunks of 4 KiB both ways take 13.0 us instead of 12.9, 2 MiB decrypted 8.70 instead of 8.77.
 constexpr uint32_t kDotSlices = 16;
 constexpr uint32_t kDotBlocks = 256;
+constexpr uint32_t kRowDot = kDotBlocks / kRowBlocks - 1;  // what a row takes
 constexpr uint32_t kHopMinPower = 8;    // the shortest stretch of a workgroup: 4 units of 64 blocks
 constexpr uint32_t kHopPowers = 7;      // ... and the longest: 16 units of 1024 blocks
 constexpr uint32_t kHopEntries = 256;   // workgroups of a chunk
@@ -82,7 +89,7 @@ struct alignas(16) Block {
     uint32_t w[4];  // bytes 4i..4i+3 of the block, loaded little-endian into w[i]
 };
 
-struct alignas(16) KeyTables {
+struct alignas(128) KeyTables {
     uint32_t rk[60];       // round key words 0 .. 4 (rounds + 1) - 1, little-endian loads of the
                            // FIPS-197 bytes; the rest zero
     uint32_t rounds;       // Nr: 10, 12 or 14 for 128-, 192-, 256-bit keys (the paper's: 14)
@@ -98,7 +105,7 @@ struct alignas(16) KeyTables {
     Block ghash_rows3[kNibbleTableEntries];  // nibble table of H^192
     // round key words by columns: [c][r] = rk[4 r + c], r < 14, and of the last round key [c][15]
     uint32_t column_keys[4][16];
-    GfWords dot[kDotSlices][kDotBlocks];
+    alignas(128) GfWords dot[kDotBlocks / kRowBlocks][4][kDotSlices / 4][kRowBlocks];
     GfWords hop[kHopPowers][kHopEntries];
     GfWords row_hop[kRowHopEntries];
     GfWords far_hop[kFarHopEntries];
