@@ -22,10 +22,11 @@
  *     the call returns without synchronising.  Device outputs are valid once the stream has
  *     reached the end of the batch; device inputs must stay alive and unchanged until then.
  *   - One key object serves any number of streams and host threads at once (the paper's
- *     transport uses one session key for both directions, section 2.2): every batch call takes a
+ *     transport uses one session key for both directions, section 2.2): a batch call takes a
  *     context of the key (descriptor staging and device workspace), bound to the call's stream,
- *     and batches that share a stream are ordered by it.  Not thread-safe: pgcm_free_key and the
- *     test and measurement aids (pgcm_set_unit_bytes, pgcm_set_timing and its readers).
+ *     and batches that share a stream are ordered by it.  (A call of at most 64 chunks of up to
+ *     8 KiB takes none.)  Not thread-safe: pgcm_free_key and the test and measurement aids
+ *     (pgcm_set_unit_bytes, pgcm_set_timing and its readers).
  *   - Errors are return codes.  A call that fails its argument checks (every status but
  *     PGCM_ERR_NOMEM and PGCM_ERR_HIP) has enqueued nothing; after PGCM_ERR_NOMEM or PGCM_ERR_HIP
  *     part of the batch may be on the stream, and its outputs are undefined.  Authentication

@@ -161,6 +161,8 @@ struct pgcm_key {
     std::mutex mu;                 // guards `contexts` and the binding fields of each context
     std::vector<Context*> contexts;
     uint64_t use_tick = 0;
+    ShortStreams short_streams;  // by `mu` as well
+    ArriveSlot (*short_slots)[kSwapChunkGroups] = nullptr;  // device: their areas, behind the tables
     // the context of the entry point that allocates nothing: fixed staging buffers, and the
     // device's static scratch array as workspace
     Context fixed;
@@ -681,6 +683,21 @@ int run_small_batch(pgcm_key* key, Context* ctx, const BatchArgs& a) {
     return rc_end;
 }
 
+// A key's device memory.
+struct KeyMemory {
+    KeyTables tables;
+    ArriveSlot short_slots[kShortStreams][kSwapChunkGroups];
+};
+
+// The slots for short chunks in so many workgroups on this stream, or null.  (hipStreamPerThread names a
+// stream of every thread.)
+ArriveSlot* short_slots(pgcm_key* key, hipStream_t stream, uint32_t groups) {
+    if (stream == hipStreamPerThread || groups > kSwapChunkGroups) return nullptr;
+    std::lock_guard<std::mutex> lock(key->mu);
+    const size_t area = key->short_streams.area_of(stream);
+    return area < kShortStreams ? key->short_slots[area] : nullptr;
+}
+
 // Workspace of the one-launch path: a slot per workgroup.
 constexpr size_t kSwapWorkBytes = sizeof(ArriveSlot) * kSwapMaxGroups;
 
@@ -732,8 +749,8 @@ void launch_swap_batch(const pgcm_key* key, const BatchArgs& a, const SwapShape&
 
 // A batch of few chunks that does not fill the chip: one kernel.  Up to kArgChunks chunks travel as
 // its arguments, nothing staged; when moreover every chunk has one workgroup, which needs no
-// workspace, the call needs no context at all (ctx is null).
-int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapShape& shape) {
+// slots, or `slots` are given, the call needs no context at all (ctx is null).
+int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapShape& shape, ArriveSlot* slots) {
     ArgBatch batch;
     const bool in_args = a.n <= kArgChunks;
     GroupDesc* h_groups = nullptr;
@@ -770,8 +787,7 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapSh
         groups += of_chunk;
     }
     if (in_args) batch.group_base[a.n] = groups;
-    ArriveSlot* slots = nullptr;
-    if (!shape.alone) {
+    if (!shape.alone && slots == nullptr) {
         const int rc = ensure_work(ctx, kSwapWorkBytes, a.stream);
         if (rc != PGCM_OK) return rc;
         use_slots(ctx, shape.groups, a.stream, a.capturing);
@@ -987,9 +1003,9 @@ int note_capture(BatchArgs& a) {
     return PGCM_OK;
 }
 
-RouteOptions route_options(const pgcm_key* key, bool fixed, bool capturing) {
+RouteOptions route_options(const pgcm_key* key, bool fixed) {
     return RouteOptions{(uint32_t)key->num_cu, key->one_launch, key->matrix_hash, key->forced_unit_power, fixed,
-                        capturing};
+                        false, false};
 }
 
 // One batch under one key: validate everything, choose the way it goes, pick a context unless it
@@ -1003,7 +1019,8 @@ int run_batch(pgcm_key* key, BatchArgs a) {
     if (rc != PGCM_OK) return rc;
     // the units, unless they are not wanted anyway; nothing touched so far
     BatchPlan p{};
-    if (!may_go_in_spans(route_options(key, a.fixed, false), v))
+    RouteOptions options = route_options(key, a.fixed);
+    if (!may_go_in_spans(options, v))
         rc = plan_batch(key->forced_unit_power, key->wave_slots, a, &p);
     if (rc != PGCM_OK) return rc;
     int cur_device = -1;
@@ -1011,12 +1028,25 @@ int run_batch(pgcm_key* key, BatchArgs a) {
     if (cur_device != key->device) return PGCM_ERR_ARG;  // the key lives on another GPU
     rc = note_capture(a);
     if (rc != PGCM_OK) return rc;
+    const ShapeBatch lens{a.n, a.order, a.aad_len, a.len};
     SwapShape shape{};
-    const Route route = route_batch(ShapeBatch{a.n, a.order, a.aad_len, a.len},
-                                    route_options(key, a.fixed, a.capturing), v, &shape);
+    const bool short_args = v.all_small() && a.n <= kArgChunks;
+    options.spread = short_args && !a.fixed && !a.capturing;
+    if (v.all_small() && !short_args && !a.capturing) {
+        std::lock_guard<std::mutex> lock(key->mu);
+        options.clears_slots = a.fixed || clears_slots(key->contexts, a.stream);
+    }
+    Route route = route_batch(lens, options, v, &shape);
+    ArriveSlot* slots = nullptr;
+    if (short_args && route == Route::kOneLaunch && !shape.alone) {
+        slots = short_slots(key, a.stream, shape.groups);
+        options.spread = slots != nullptr;
+        if (slots == nullptr) route = route_batch(lens, options, v, &shape);
+    }
     if (a.fixed && a.n > kFixedMaxChunks) return PGCM_ERR_CAPACITY;
     const bool one_launch = route == Route::kOneLaunch;
-    if (one_launch && shape.alone && a.n <= kArgChunks) return run_one_launch(key, nullptr, a, shape);
+    if (one_launch && (shape.alone || slots != nullptr) && a.n <= kArgChunks)
+        return run_one_launch(key, nullptr, a, shape, slots);
     Context* ctx = nullptr;
     if (a.fixed) {
         ctx = &key->fixed;
@@ -1026,7 +1056,7 @@ int run_batch(pgcm_key* key, BatchArgs a) {
         if (rc != PGCM_OK) return rc;
     }
     if (one_launch) {
-        rc = run_one_launch(key, ctx, a, shape);
+        rc = run_one_launch(key, ctx, a, shape, nullptr);
     } else if (route == Route::kOneRow) {
         rc = run_small_batch(key, ctx, a);
     } else if (route == Route::kSpans) {
@@ -1088,7 +1118,7 @@ int run_batch_keys(pgcm_key* const* keys, size_t nkeys, const uint32_t* key_inde
         for (size_t k = 0; k < nkeys; ++k) {
             const KeyPart& part = parts[k];
             if (part.n == 0) continue;
-            if (!takes_spans(route_options(keys[k], false, false), part.rows, part.longest) ||
+            if (!takes_spans(route_options(keys[k], false), part.rows, part.longest) ||
                 !share_launch(1, part.n, part.rows, num_cu)) {
                 alone.push_back(k);
                 continue;
@@ -1168,7 +1198,10 @@ int pgcm_expand_key_bytes(const uint8_t* key, uint32_t key_bytes, void* hip_stre
         if (hip_failed(hipDeviceGetAttribute(&k->num_cu, hipDeviceAttributeMultiprocessorCount,
                                              k->device))) { rc = PGCM_ERR_HIP; break; }
         if (k->num_cu < 1) k->num_cu = 1;
-        if (hip_failed(hipMalloc((void**)&k->tables, sizeof(KeyTables)))) { rc = PGCM_ERR_NOMEM; break; }
+        KeyMemory* memory = nullptr;
+        if (hip_failed(hipMalloc((void**)&memory, sizeof(KeyMemory)))) { rc = PGCM_ERR_NOMEM; break; }
+        k->tables = &memory->tables;
+        k->short_slots = memory->short_slots;
         if (hip_failed(hipMalloc((void**)&d_key, 32))) { rc = PGCM_ERR_NOMEM; break; }
         k->wave_slots = (uint32_t)k->num_cu * kWavesPerGroup;
         // the fixed context: one pinned block cut into the staging buffers, the device's static
@@ -1192,7 +1225,8 @@ int pgcm_expand_key_bytes(const uint8_t* key, uint32_t key_bytes, void* hip_stre
         if (hip_failed(hipMemcpyAsync(d_key, key, key_bytes, hipMemcpyHostToDevice, stream))) { rc = PGCM_ERR_HIP; break; }
         k->rounds = (int)(key_bytes / 4 + 6);
         hipLaunchKernelGGL(expand_key_kernel, dim3(1), dim3(1024), 0, stream, k->tables, d_key,
-                           key_bytes / 4);
+                           key_bytes / 4, reinterpret_cast<uint4*>(k->short_slots),
+                           (uint32_t)(sizeof(KeyMemory::short_slots) / 16));
         if (hip_failed(hipGetLastError())) { rc = PGCM_ERR_HIP; break; }
         if (hip_failed(hipMemsetAsync(d_key, 0, 32, stream))) { rc = PGCM_ERR_HIP; break; }
         if (hip_failed(hipStreamSynchronize(stream))) { rc = PGCM_ERR_HIP; break; }
@@ -1209,7 +1243,7 @@ int pgcm_expand_key_bytes(const uint8_t* key, uint32_t key_bytes, void* hip_stre
 void pgcm_free_key(pgcm_key_t* k) {
     if (k == nullptr) return;
     if (k->tables) {
-        (void)hipMemset(k->tables, 0, sizeof(KeyTables));
+        (void)hipMemset(k->tables, 0, sizeof(KeyMemory));
         (void)hipFree(k->tables);
     }
     for (Context* c : k->contexts) {

@@ -6,7 +6,9 @@
 
 namespace pgcm {
 
-__global__ void expand_key_kernel(KeyTables* kt, const uint32_t* key_words, uint32_t nk);
+// clear: n_clear elements that are made zero besides
+__global__ void expand_key_kernel(KeyTables* kt, const uint32_t* key_words, uint32_t nk, uint4* clear,
+                                  uint32_t n_clear);
 
 __global__ void j0_kernel(const KeyTables* kt, const ChunkDesc* chunks, const uint8_t* ivs,
                           uint32_t iv_len, uint32_t nchunks, Block* j0);

@@ -235,7 +235,8 @@ __device__ GfWords gfw_square(const GfWords& x) {
 // made, by shifting, and its 512 entries are sums of up to four of them.
 __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict__ kt,
                                                           const uint32_t* __restrict__ key_words,
-                                                          uint32_t nk) {
+                                                          uint32_t nk, uint4* __restrict__ clear,
+                                                          uint32_t n_clear) {
     // H^(2^k), then H^3, H^12, H^48, H^96 and H^192; all but H^96 get a nibble table
     constexpr uint32_t kConstants = kNumPowers + kNumLanePowers + 2, kAt96 = kConstants - 2,
                        kAt192 = kConstants - 1;
@@ -248,6 +249,7 @@ __global__ __launch_bounds__(1024) void expand_key_kernel(KeyTables* __restrict_
     __shared__ uint8_t sbox[256];
     const uint32_t tid = threadIdx.x;
 
+    for (uint32_t i = tid; i < n_clear; i += blockDim.x) clear[i] = make_uint4(0, 0, 0, 0);
     // round tables: te[0][x] = (2s, s, s, 3s) in bytes 0..3, te[r] = te[0] rotated left by 8r bits
     for (uint32_t x = tid; x < 256; x += blockDim.x) {
         uint32_t s = kSbox.v[x];

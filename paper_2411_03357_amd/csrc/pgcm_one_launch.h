@@ -126,16 +126,19 @@ inline bool one_pass_each(const ShapeBatch& a, uint32_t most, SwapShape* shape) 
 // Batches of short chunks, and others of at most sixteen passes for every compute unit, go to burst_kernel.
 // As long as there is a compute unit for every short chunk, a workgroup takes a whole one, with no
 // more wavefronts than it has blocks for.  Up to kArgChunks of them, one longer than a pass of 256 blocks, go in
-// workgroups of one pass instead (one_pass_each), if `spread` lets them: back to back and waited for, one of 8 KiB
-// 7.6 -> 5.8 and 19.6 -> 18.1 us, with AAD 9.1 -> 5.7 and 21.1 -> 18.1, 32 of 8 KiB decrypted 8.2 -> 6.5 and 20.3 ->
-// 18.9, 60 of up to 8 KiB with AAD 7.9 -> 6.8 and 20.5 -> 19.2.  Shorter ones are no better off (16 of 4 KiB 6.6 ->
-// 6.3 and 18.5 -> 18.8, 64 of them decrypted 6.7 -> 7.0), nor are more (120 of up to 8 KiB 9.0 -> 9.7).
-// Of more chunks than compute units, two workgroups share one: of at most
+// workgroups of one pass instead (one_pass_each), if `spread` lets them, which it does where the stream has slots for
+// them at hand (ShortStreams): back to back and waited for, one of 8 KiB 8.1 -> 5.8 and 18.5 -> 17.0 us, with AAD
+// 10.1 -> 5.8 and 21.3 -> 17.0, 32 of 8 KiB 8.4 -> 6.5 and 19.7 -> 17.9, 64 of 4 KiB with AAD 8.4 -> 6.9 and 20.0 -> 18.5,
+// on any stream that has them.  Shorter ones are no better off (16 of 4 KiB 6.6 -> 6.3 and 18.5 -> 18.8, 64 of them
+// decrypted 6.7 -> 7.0), nor are more (120 of up to 8 KiB 9.0 -> 9.7).
+// Of more chunks than compute units, two workgroups share one: if `spread`, of at most
 // eight wavefronts and one pass, of which the longer chunks take several, if 512 of them do; otherwise of
 // sixteen and one pass, if 512 of these do (346 chunks of 1.6 to 8.1 KB 13.4 us, a workgroup each 16.2; 450 of up
-// to 8 KB 12.9, 14.7); otherwise of sixteen and a whole chunk.  Longer chunks are spread over workgroups of
-// four or eight that make one pass (one_pass_each), or over as many of sixteen as there are compute units, with the fewest passes that go: first with none spare,
-// then with one for the first workgroup of each chunk, which is what a few blocks too many take (2 MiB
+// to 8 KB 12.9, 14.7); otherwise of sixteen and a whole chunk, as also where a launch has to clear the slots (300 of up
+// to 8 KB on a stream with a captured batch 17.4 us with several workgroups a chunk, 13.9 with one each; in a graph,
+// where that launch costs less, 15.4 and 15.6: there they have several).  Longer chunks are spread over workgroups of
+// four or eight that make one pass (one_pass_each), or over as many of sixteen as there are compute units, with the
+// fewest passes that go: first with none spare, then with one for the first workgroup of each chunk, which is what a few blocks too many take (2 MiB
 // with AAD in 257 workgroups of two passes: 256 take 11.8 us, four passes in 129 took 14.8; 8 of
 // 256 KiB with AAD 12.3, were 14.7), then with one more (2.3 to 3 MB in three 12.1, in four 14.2).
 // What is left has more than four rows for each wavefront of the device, and takes units of eight rows or
@@ -145,7 +148,7 @@ inline bool one_pass_each(const ShapeBatch& a, uint32_t most, SwapShape* shape) 
 // ("block -1") too long for sixteen with units of eight, as these have no further wavefront for it.
 constexpr uint32_t kLongUnitPower = kRowPower + 3;
 // forced: log2 of the blocks of a unit, or 0; all_small: no chunk is longer than kSmallChunkBytes; spread: of
-// these a chunk may have several workgroups, for which the batch needs a workspace.
+// these a chunk may have several workgroups, for which the batch needs slots.
 inline bool swap_shape(const ShapeBatch& a, uint32_t num_cu, bool one_launch, uint32_t forced, bool all_small,
                        bool spread, SwapShape* shape) {
     if (a.n > kSmallMaxChunks || (!all_small && !one_launch)) return false;
@@ -165,8 +168,9 @@ inline bool swap_shape(const ShapeBatch& a, uint32_t num_cu, bool one_launch, ui
             one_pass_each(a, most, shape))
             return true;
         total = a.n;
-        if (a.n > num_cu && wp > 2 && of_eight <= kSwapMaxGroups) wp = 3, passes = 1, total = of_eight;
-        else if (a.n > num_cu && wp == 4 && of_sixteen <= kSwapMaxGroups) passes = 1, total = of_sixteen;
+        const bool apart = spread && a.n > num_cu;
+        if (apart && wp > 2 && of_eight <= kSwapMaxGroups) wp = 3, passes = 1, total = of_eight;
+        else if (apart && wp == 4 && of_sixteen <= kSwapMaxGroups) passes = 1, total = of_sixteen;
         *shape = SwapShape{true, total == a.n, passes, wp, (uint32_t)total, 0};
         return true;
     }

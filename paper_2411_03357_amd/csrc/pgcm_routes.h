@@ -15,7 +15,8 @@ struct RouteOptions {
     bool one_launch, matrix_hash;
     uint32_t forced_unit_power;  // 0: chosen for the batch
     bool fixed;                  // the entry point that allocates nothing
-    bool capturing;              // into a graph
+    bool spread;                 // short chunks, at most kArgChunks of them, may have several workgroups
+    bool clears_slots;           // the slots that chunks of several workgroups need take a launch that clears them
 };
 
 // What decides of the chunks.
@@ -52,9 +53,8 @@ enum class Route {
 // `shape` is filled in for kOneLaunch.
 inline Route route_batch(const ShapeBatch& a, const RouteOptions& o, const BatchSurvey& v, SwapShape* shape) {
     const bool spans = may_go_in_spans(o, v);
-    // Short chunks of which each has one workgroup need no workspace: so they can be captured on a stream that
-    // nothing is reserved for, and calls in fixed buffers leave these alone.
-    const bool spread = o.one_launch && !o.fixed && !o.capturing;
+    // What short chunks in several workgroups need, and those with a workgroup each do not, is slots.
+    const bool spread = a.n <= kArgChunks ? o.one_launch && o.spread : !o.clears_slots;
     if (swap_shape(a, o.num_cu, o.one_launch, o.forced_unit_power, v.all_small(), spread, shape) &&
         (!spans || shape->burst ||
          units_before_spans(*shape, v.rows, (uint64_t)o.num_cu * kWavesPerGroup)))

@@ -1,6 +1,7 @@
 // Threads that make batches with the contexts of one key, on streams of their own and on shared ones, as the
 // library's host code does: the choice under a mutex, the call outside it.  Run under ThreadSanitizer: what a
-// call writes without the mutex nobody else may read.  Prints how many contexts there were at the end.
+// call writes without the mutex nobody else may read.  Then the streams that get areas of slots for short chunks.
+// Prints how many contexts there were at the end.
 // Test infrastructure.
 #include <cstdint>
 #include <cstdio>
@@ -36,9 +37,23 @@ static void batch(void* stream, uint64_t random) {
     {
         std::lock_guard<std::mutex> lock(mu);
         bool must_wait;
-        c = pick_context(contexts, stream, [&](const Context* o) { return !o->in_call && (random & 4); }, &must_wait);
+        const bool own = clears_slots(contexts, stream);
+        auto ended = [&](const Context* o) { return !o->in_call && (random & 4); };
+        c = pick_context(contexts, stream, ended, &must_wait);
+        // a new one while there are few, or where the others cannot be re-bound
+        size_t free = 0, kept = 0;
+        for (const Context* o : contexts)
+            if (!o->replayed && !o->unmarked) ++kept, free += !o->in_call;
+        CHECK(c != nullptr || free == 0 || kept < kMaxContexts);
         if (c == nullptr) contexts.push_back(c = new Context());
         CHECK(!c->in_call && (!c->bound || c->stream == stream || !(c->replayed || c->unmarked)));
+        // of another stream: its last batch has ended, or is waited for where no more are made, the oldest
+        CHECK(!c->bound || c->stream == stream || must_wait || ended(c));
+        CHECK(!must_wait || kept >= kMaxContexts);
+        if (must_wait)
+            for (const Context* o : contexts)
+                CHECK(o->replayed || o->unmarked || o->in_call || o->last_use >= c->last_use);
+        CHECK(own == (c->replayed && c->stream == stream));
         enter_call(contexts, c, stream, ++tick);
     }
     c->stream = stream;
@@ -86,8 +101,20 @@ static void settle_late() {
     CHECK(!all[0].quiet);
 }
 
+// Areas of slots: the same one for a stream whenever it asks, of no other stream's, kShortStreams of them
+static void short_streams() {
+    static char streams[2 * kShortStreams];
+    ShortStreams s;
+    for (int turn = 0; turn < 3; ++turn) {
+        CHECK(s.area_of(nullptr) == 0);  // the null stream is one of them
+        for (size_t i = 0; i < 2 * kShortStreams; ++i)
+            CHECK(s.area_of(&streams[i]) == (i + 1 < kShortStreams ? i + 1 : kShortStreams));
+    }
+}
+
 int main() {
     settle_late();
+    short_streams();
     static char streams[64];
     std::vector<std::thread> threads;
     for (int t = 0; t < 6; ++t)

@@ -1,5 +1,6 @@
 // Reads batches, a line each: compute units, one launch (0, 1), matrix hash, forced unit bytes, 1 for
-// fixed buffers or 2 if captured, then for every chunk its length and its AAD's.  Prints which kernel takes each.
+// fixed buffers, 2 if captured or 3 where the stream's context was and the stream has no slots for short chunks, then
+// for every chunk its length and its AAD's.  Prints which kernel takes each.
 // Test infrastructure.
 #include <cstdint>
 #include <iostream>
@@ -25,7 +26,7 @@ int main() {
         for (uint64_t l, a; in >> l >> a;) len.push_back(l), aad_len.push_back((uint32_t)a);
         BatchSurvey v;
         for (size_t i = 0; i < len.size(); ++i) v.add(len[i], aad_len[i]);
-        const RouteOptions o{num_cu, one_launch != 0, matrix_hash != 0, forced, fixed == 1, fixed == 2};
+        const RouteOptions o{num_cu, one_launch != 0, matrix_hash != 0, forced, fixed == 1, fixed == 0, fixed == 1 || fixed == 3};
         SwapShape s{};
         switch (route_batch(ShapeBatch{len.size(), nullptr, aad_len.data(), len.data()}, o, v, &s)) {
             case Route::kOneRow: std::cout << "small\n"; break;

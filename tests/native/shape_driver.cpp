@@ -98,7 +98,7 @@ static void check(const ShapeBatch& a, uint32_t num_cu, uint32_t forced) {
             return;
         }
         if (s.alone) CHECK(groups_of(a, (uint64_t)16 << s.wave_power, s.unit_power, 0) == a.n || a.n > num_cu);
-        if (a.n > num_cu && s.wave_power > 2) {
+        if (spread && a.n > num_cu && s.wave_power > 2) {
             const uint64_t of_eight = groups_of(a, 128, 1, 0), of_sixteen = groups_of(a, 256, 1, 0);
             CHECK(s.groups == (of_eight <= kSwapMaxGroups     ? of_eight
                                : of_sixteen <= kSwapMaxGroups ? of_sixteen

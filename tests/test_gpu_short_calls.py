@@ -1,0 +1,159 @@
+"""Calls of at most 64 chunks of up to 8 KiB, one of them longer than 256 blocks, on more streams than the key has
+areas of slots for, from several threads, between replays of a graph and while another thread captures one: they
+get no context and no memory, and their results are the CPU oracle's, bit for bit."""
+import threading
+
+import numpy as np
+import pytest
+import torch
+
+import workloads
+from test_gpu_graphs import _Checked
+
+import paper_2411_03357_amd as pgcm
+
+pytestmark = pytest.mark.gpu
+
+KIB, MIB = 1024, 1 << 20
+# in two to nine workgroups a chunk, of 64 blocks or of 128
+SHORT = [[8 * KIB], [8 * KIB] * 32, [4 * KIB] * 64, [1, 8191, 300, 4097, 8176]]
+
+
+def _batches(rng, raw_key):
+    return [_Checked("short_%d" % i, rng, lens, raw_key) for i, lens in enumerate(SHORT)]
+
+
+def _rng_and_key(number):
+    rng = np.random.default_rng([workloads.BASE_SEED, 6060, number])
+    return rng, rng.integers(0, 256, 32, dtype=np.uint8)
+
+
+def _no_context(key, stream):
+    with pytest.raises(pgcm.PgcmError):
+        pgcm.describe_context(key, stream)
+
+
+def test_on_many_streams():
+    rng, raw_key = _rng_and_key(1)
+    key = pgcm.expand_key(raw_key)
+    batches = _batches(rng, raw_key)
+    streams = [None] + [torch.cuda.Stream() for _ in range(24)]
+    for turn in range(2):
+        for k, stream in enumerate(streams):
+            for b in batches:
+                b.clear()
+            torch.cuda.synchronize()
+            for b in batches:
+                b.b.encrypt(key, stream=stream)
+                b.b.decrypt(key, stream=stream)
+            for b in batches:
+                b.check((turn, k))
+    for stream in streams:
+        _no_context(key, stream)
+    key.free()
+
+
+def test_from_several_threads():
+    """every thread on a stream of its own and, for every other batch, on one that all share"""
+    rng, raw_key = _rng_and_key(2)
+    key = pgcm.expand_key(raw_key)
+    shared = torch.cuda.Stream()
+    own = [(torch.cuda.Stream(), _batches(rng, raw_key)) for _ in range(4)]
+    failed = []
+    torch.cuda.synchronize()
+
+    def work(stream, batches):
+        try:
+            torch.cuda.set_device(0)
+            for _ in range(20):
+                for k, b in enumerate(batches):
+                    on = shared if k % 2 else stream
+                    b.b.encrypt(key, stream=on)
+                    b.b.decrypt(key, stream=on)
+        except Exception as e:  # pylint: disable=broad-except
+            failed.append(e)
+
+    threads = [threading.Thread(target=work, args=a) for a in own]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed, failed
+    for _, batches in own:
+        for b in batches:
+            b.check("threads")
+    key.free()
+
+
+def test_between_replays():
+    rng, raw_key = _rng_and_key(3)
+    key = pgcm.expand_key(raw_key)
+    graphed = [_Checked("captured", rng, [2 * MIB, 300 * KIB + 1], raw_key),
+               _Checked("captured_short", rng, [8 * KIB] * 20, raw_key)]
+    many = _Checked("many", rng, [int(v) for v in rng.integers(1, 8 * KIB, 300)], raw_key)
+    batches = _batches(rng, raw_key) + [many]
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    pgcm.reserve(key, 300, 4 * MIB, stream)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        for g in graphed:
+            g.b.encrypt(key)
+            g.b.decrypt(key)
+    for r in range(4):
+        for b in graphed + batches:
+            b.clear()
+        torch.cuda.synchronize()
+        for b in batches:
+            b.b.encrypt(key, stream=stream)
+        with torch.cuda.stream(stream):
+            graph.replay()
+        for b in batches:
+            b.b.decrypt(key, stream=stream)
+        for b in graphed + batches:
+            b.check(r)
+    torch.cuda.synchronize()
+    key.free()
+
+
+def test_while_another_thread_captures():
+    """the calls allocate nothing, so that a capture in the global mode, under which no thread may, goes on"""
+    rng, raw_key = _rng_and_key(4)
+    key = pgcm.expand_key(raw_key)
+    graphed = _Checked("captured", rng, [2 * MIB, 300 * KIB + 1], raw_key)
+    batches = _batches(rng, raw_key)
+    stream, other = torch.cuda.Stream(), torch.cuda.Stream()
+    for b in batches:
+        b.clear()
+    pgcm.reserve(key, 2, 3 * MIB, stream)
+    torch.cuda.synchronize()
+    failed = []
+
+    def work():
+        try:
+            torch.cuda.set_device(0)
+            for b in batches:
+                b.b.encrypt(key, stream=other)
+                b.b.decrypt(key, stream=other)
+        except Exception as e:  # pylint: disable=broad-except
+            failed.append(e)
+
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream, capture_error_mode="global"):
+        graphed.b.encrypt(key)
+        thread = threading.Thread(target=work)
+        thread.start()
+        thread.join()
+        graphed.b.decrypt(key)
+    assert not failed, failed
+    for b in batches:
+        b.check("while capturing")
+    for r in range(2):
+        graphed.clear()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            graph.replay()
+        graphed.check(r)
+    _no_context(key, other)
+    torch.cuda.synchronize()
+    key.free()

@@ -29,7 +29,8 @@ def kernels_of(tmp_path_factory):
     assert build.returncode == 0, build.stdout
 
     def run(batches):
-        """batches: (lengths, AAD lengths, forced unit bytes, one launch[, 1: fixed buffers, 2: captured])"""
+        """batches: (lengths, AAD lengths, forced unit bytes, one launch[, 1: fixed buffers, 2: captured, 3: on a
+        stream that has no slots for short chunks, and whose context was captured])"""
         lines = []
         for lens, alens, unit_bytes, one_launch, *fixed in batches:
             lines.append("256 %d 0 %d %d " % (one_launch, unit_bytes, fixed[0] if fixed else 0) +
@@ -79,7 +80,10 @@ def test_bursts(kernels_of):
     assert {k for n, k in got.items() if n.startswith("spread_")} == {"words"} and got["whole"] == "fold 4"
     # short chunks have one workgroup each, as ever, where they are captured, in fixed buffers or go in units
     short = [shapes["spread_64_most"][0], [0] * 32]
-    assert kernels_of([(*short, 0, 1, 2), (*short, 0, 1, 1), (*short, 0, 0)]) == ["fold 4"] * 3
+    assert kernels_of([(*short, 0, 1, 3), (*short, 0, 1, 2), (*short, 0, 1, 1), (*short, 0, 0)]) == ["fold 4"] * 4
+    # ... and more than 256 of them where their slots would be cleared by a launch of its own
+    apart = [shapes["many_apart_512"][0], [0] * 406]
+    assert kernels_of([(*apart, 0, 1, 2), (*apart, 0, 1, 3), (*apart, 0, 1, 1)]) == ["shared apart"] + ["shared"] * 2
     assert {got[n] for n in ("many_even", "many_long")} == {"shared"} and got["many_mixed"] == "words"
     assert {got[n] for n in ("many_apart", "many_apart_512")} == {"shared apart"} and got["many_apart_513"] == "shared"
 
