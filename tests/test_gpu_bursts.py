@@ -61,6 +61,18 @@ SHAPES = {
     "spread_64_edges": ([0, 1, 8192] + _EDGES[12:], [1008, 0, 16, 1025, 3000, 33]),
     "spread_128_most": ([8192 - 16 * (i % 3) for i in range(56)] + [4096] * 8, [0]),
     "whole": ([8192] * 65 + _EDGES, [0]),
+    # ... with AAD of every kind: a workgroup of one to three passes for each of more than 64 chunks
+    "whole_aad": ([0, 1] + _EDGES + [8192, 4096] + [16 * b + d for b in (257, 448, 500) for d in (-1, 0, 1)] + [20] * 34,
+                  [16, 0, 5, 64, 17, 1, 48]),
+    "whole_long_aad": ([0, 5, 1024, 4096, 4097, 8192, 8177] * 10, [1008, 1024, 1025, 16, 3000]),
+    # workgroups of sixteen wavefronts and one pass, the first ones of chunks short: AAD in lanes, at the edges of a
+    # row and longer, "block -1" in the first workgroup and in the second
+    "fold_1": ([v + 16 * 4096 for v in _MORE], [0, 16, 33, 1008, 1024, 1025, 3000]),
+    "fold_1_most": ([1 << 20], [0]),
+    "fold_1_aad_most": ([(1 << 20) - 64 * 16], [1024]),
+    "fold_1_aad_before": ([(150 * 256 - 1) * 16 - 12], [33]),
+    "fold_1_aad_with_last": ([150 * 4096], [33]),
+    "fold_1_long_aad": ([513 * KIB], [3000]),
     # workgroups of one to four passes, some of them short; in 2 and 4 a chunk's first may make one more
     "two": ([300 * KIB, 8 * KIB + 16, 9000, 1], [0, 16, 70]),
     "passes_1": (_MORE + [200 * KIB], [0, 16]),
@@ -108,8 +120,9 @@ def test_shapes(shape):
 
 
 @pytest.mark.parametrize("key_bytes,iv_bytes", [(16, 12), (24, 16), (32, 8), (16, 40), (32, 1040)])
-@pytest.mark.parametrize("shape", ["short_aad", "passes_1", "apart_64_edges", "apart_128_edges", "spread_64_edges", "passes_4", "sweeps_2_missing", "many_even",
-                                   "many_mixed", "many_apart"])
+@pytest.mark.parametrize("shape", ["short_aad", "passes_1", "apart_64_edges", "apart_128_edges", "spread_64_edges",
+                                   "whole_aad", "whole_long_aad", "fold_1", "passes_4", "sweeps_2_missing",
+                                   "many_even", "many_mixed", "many_apart"])
 def test_other_keys_and_ivs(shape, key_bytes, iv_bytes):
     lens, alens = SHAPES[shape]
     _full_parity(_workload(shape, lens[:40] if shape == "short_aad" else lens, alens, key_bytes, iv_bytes))

@@ -23,6 +23,8 @@ def _lens(passes, n):
 SHAPES = {
     "words": ([1, 16, 40, 1000, 2031, 0, 2032, 300, 17, 5, 64, 100], 0, True, "words"),
     "one": (_lens(3, 12), 0, True, "words"),
+    "one of sixteen": (_lens(19, 12), 0, True, "fold 1"),
+    "whole": (_lens(2, 72), 0, True, "fold 4"),
     "two": (_lens(3, 150), 0, True, "fold 3"),
     "four": (_lens(16, 48), 0, True, "fold 4"),
     "sweeps": (_lens(9, 130) + _lens(6, 100), 0, True, "sweep 9"),

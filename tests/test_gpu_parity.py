@@ -260,6 +260,7 @@ def test_two_keys_on_two_streams_at_once():
 
 # lengths, forced unit size, one launch, and the kernel (tests/test_routes.py)
 LONG_AAD = [([0, 40, 1000], 0, True, "words"), ([0, 3000, 8192], 0, True, "words"),
+            ([0, 3000, 8192] * 22, 0, True, "fold"),
             ([0, 5, 70000, 1 << 20], 0, True, "fold"), ([0, 5, 70000, 1 << 20], 4096, True, "swap"),
             ([0, 5, 70000, 1 << 20], 0, False, "bulk"), ([0, 40, 900] * 180, 0, True, "small"),
             ([0, 40, 9000] * 90, 0, True, "span")]

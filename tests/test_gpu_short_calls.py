@@ -8,7 +8,10 @@ import pytest
 import torch
 
 import workloads
+from device_batch import DeviceBatch
+from test_gpu_bursts import _workload
 from test_gpu_graphs import _Checked
+from test_gpu_reservations import expected
 
 import paper_2411_03357_amd as pgcm
 
@@ -31,6 +34,42 @@ def _rng_and_key(number):
 def _no_context(key, stream):
     with pytest.raises(pgcm.PgcmError):
         pgcm.describe_context(key, stream)
+
+
+def test_long_aad_captured_and_in_fixed_buffers():
+    """a workgroup of sixteen wavefronts a chunk, whose AAD fills a row, or more"""
+    w = _workload("captured_long_aad", [0, 5, 1024, 4096, 4097, 8192], [1008, 1024, 1025, 16, 3000])
+    host = w.payload_host()
+    cipher, tags = expected(w, host)
+    b = DeviceBatch(w, torch.from_numpy(host).cuda())
+    key = pgcm.expand_key(w.key)
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+
+    def check(what):
+        torch.cuda.synchronize()
+        assert np.array_equal(b.cipher.cpu().numpy(), cipher), what
+        assert np.array_equal(b.tags.cpu().numpy().reshape(-1, 16), tags), what
+        b.cipher.zero_()
+        b.tags.zero_()
+        torch.cuda.synchronize()
+
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        b.encrypt(key)
+        b.decrypt(key)
+    for r in range(3):
+        b.back.zero_()
+        b.ok.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            graph.replay()
+        torch.cuda.synchronize()
+        assert bool((b.ok == 1).all()) and torch.equal(b.back, b.plain), r
+        check(r)
+    pgcm.encrypt_batch_static(key, b.ivs, b.aad_ptrs, b.aad_lens, b.ptrs(b.plain), b.lens, b.ptrs(b.cipher), b.tags)
+    check("static")
+    key.free()
 
 
 def test_on_many_streams():

@@ -65,7 +65,10 @@ def test_bursts(kernels_of):
     # the most passes of a workgroup, a chunk's first
     most = {"passes_2": 3, "passes_3": 3, "passes_4": 3, "even_2": 2, "even_4": 4, "even_4_some": 4,
             "spare_1": 2, "spare_1_payload": 2, "spare_1_long_aad": 2, "spare_2": 3, "spare_3": 4,
-            "spare_of_some": 3}
+            "spare_of_some": 3, "whole": 4, "whole_aad": 4, "whole_long_aad": 4,
+            "one_4096": 4, "one_aad_2048": 4, "one_aad_4080": 4,
+            **{n: 1 for n in shapes if n.startswith("fold_1")}}
+    words = {"short", "short_aad", "long_aad", "aad_before", "aad_with_last", "two", "passes_1", "many_mixed"}
     sweeps = {"sweeps_2": 2, "sweeps_2_whole": 2, "sweeps_2_spare": 3, "sweeps_2_missing": 2,
               "sweeps_2_missing_2": 2, "sweeps_3": 3, "sweeps_4": 4, "sweeps_of_each": 4}
     for name, kernel in got.items():
@@ -74,17 +77,19 @@ def test_bursts(kernels_of):
             assert kernel == "fold %d" % most[name], (name, kernel)
         elif name in sweeps:
             assert kind == "sweep" and -(-int(passes) // 4) == sweeps[name], (name, kernel)
+        elif name in words or name.startswith(("one_", "apart_", "spread_")):
+            assert kernel == "words", (name, kernel)
         else:
-            assert kind in ("words", "fold", "shared"), (name, kernel)
-    assert {k for n, k in got.items() if n.startswith("apart_") or n == "passes_1"} == {"words"}
-    assert {k for n, k in got.items() if n.startswith("spread_")} == {"words"} and got["whole"] == "fold 4"
+            assert kind == "shared", (name, kernel)
     # short chunks have one workgroup each, as ever, where they are captured, in fixed buffers or go in units
     short = [shapes["spread_64_most"][0], [0] * 32]
     assert kernels_of([(*short, 0, 1, 3), (*short, 0, 1, 2), (*short, 0, 1, 1), (*short, 0, 0)]) == ["fold 4"] * 4
+    aad = [0, 5, 1024, 4096, 4097, 8192], [1008, 1024, 1025, 16, 3000, 1008]
+    assert kernels_of([(*aad, 0, 1, 2), (*aad, 0, 1, 1)]) == ["fold 4"] * 2
     # ... and more than 256 of them where their slots would be cleared by a launch of its own
     apart = [shapes["many_apart_512"][0], [0] * 406]
     assert kernels_of([(*apart, 0, 1, 2), (*apart, 0, 1, 3), (*apart, 0, 1, 1)]) == ["shared apart"] + ["shared"] * 2
-    assert {got[n] for n in ("many_even", "many_long")} == {"shared"} and got["many_mixed"] == "words"
+    assert {got[n] for n in ("many_even", "many_long")} == {"shared"}
     assert {got[n] for n in ("many_apart", "many_apart_512")} == {"shared apart"} and got["many_apart_513"] == "shared"
 
 
