@@ -751,7 +751,7 @@ void launch_swap_batch(const pgcm_key* key, const BatchArgs& a, const SwapShape&
 // its arguments, nothing staged; when moreover every chunk has one workgroup, which needs no
 // slots, or `slots` are given, the call needs no context at all (ctx is null).
 int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapShape& shape, ArriveSlot* slots) {
-    ArgBatch batch;
+    ArgBatch batch{};  // (it goes out whole)
     const bool in_args = a.n <= kArgChunks;
     GroupDesc* h_groups = nullptr;
     int s = 0;

@@ -338,11 +338,13 @@ inline SpanPlan plan_spans(const SpanBatch& a, const KeyPart* keys, size_t nkeys
 
 // Fills in a launch's map as far as it goes: the keys, if there are several and they have a place each, and
 // the workgroups' packets one behind the other, if no list is longer than what is held of one and all of them
-// together are read from host memory.  Returns what is filled in; *bytes: the packets'.
+// together are read from host memory.  What is not is zero: a map goes out whole, as a kernel argument.  Returns
+// what is filled in; *bytes: the packets'.
 inline uint32_t map_spans(const KeyPart* keys, size_t nkeys, const SpanGroup* groups, const SpanPlan& plan,
                           SpanMap* map, size_t* bytes) {
     uint32_t filled = nkeys > 1 && nkeys <= kSpanMapKeys ? kSpanKeysMapped : 0, g = 0;
     size_t at = 0;
+    *map = SpanMap{};
     for (size_t q = 0; q < nkeys; ++q) {
         if (g + keys[q].groups > kSpanMapGroups) return 0;
         if (filled) map->key[q] = keys[q].tables;

@@ -5,6 +5,7 @@
 // that they share the longest list and what is filled in of the map.  Test infrastructure.
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <iostream>
 #include <sstream>
 #include <string>
@@ -48,7 +49,7 @@ static void describe(const std::string& line) {
     std::vector<SpanPart> parts(n + ngroups);
     SpanScratch scratch;
     const SpanPlan plan = plan_spans(b, keys.data(), nkeys, scratch, groups.data(), parts.data());
-    SpanMap map{};
+    SpanMap map;
     size_t bytes = 0;
     const uint32_t filled = map_spans(keys.data(), nkeys, groups.data(), plan, &map, &bytes);
     printf("%u%s%s\n", plan.longest, filled & kSpanPlaced ? " placed" : "", filled & kSpanKeysMapped ? " keys" : "");
@@ -82,6 +83,7 @@ int main(int argc, char**) {
                 SpanScratch scratch;
                 const SpanPlan plan = plan_spans(b, keys.data(), nkeys, scratch, groups.data(), parts.data());
                 SpanMap map;
+                memset(&map, 0xA5, sizeof(map));
                 size_t bytes = 0;
                 const uint32_t filled = map_spans(keys.data(), nkeys, groups.data(), plan, &map, &bytes);
                 CHECK(ngroups <= kSpanMapGroups);
@@ -98,6 +100,8 @@ int main(int argc, char**) {
                     if (filled & kSpanKeysMapped) CHECK(map.key[place >> SpanMap::kKeyShift] == groups[g].kt);
                 }
                 if (filled & kSpanPlaced) CHECK(at == bytes && at <= kSpanHostBytes);
+                for (uint32_t g = ngroups; g < kSpanMapGroups; ++g) CHECK(map.place[g] == 0);
+                for (size_t q = filled & kSpanKeysMapped ? nkeys : 0; q < kSpanMapKeys; ++q) CHECK(map.key[q] == nullptr);
                 ++all, placed += (filled & kSpanPlaced) != 0, mapped += (filled & kSpanKeysMapped) != 0;
             }
     printf("maps %u, with packets %u, with keys %u\n", all, placed, mapped);
