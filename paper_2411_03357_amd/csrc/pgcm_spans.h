@@ -88,7 +88,8 @@ struct SpanScratch {
 };
 
 // What one more piece costs a workgroup of sixteen wavefronts, in rows (300 adapters both ways with 8, 6, 5:
-// 159.9, 158.0, 157.9 us; 240 chunks of three keys 158.6 with each); and a wavefront among them, in half
+// 159.9, 158.0, 157.9 us; 150 of 0.1 to 1 MB 139.3, 136.2, 136.0; 60 of 1 to 4 MB 294, 290, 287; 240 chunks of 4 KB to
+// 2 MB, 400 of 320 KiB, 500 of 50 to 300 KB, 700 of 16 to 256 and 1000 of 50 to 250 within 1 %); and a wavefront among them, in half
 // rows, which are 2.2 us (300 adapters with 3, 4, 6: 160.1, 160.1, 159.5; 600 of 16 to 128 KB 101.1, 103.2,
 // 101.5; 100 of 0.1 to 1 MB 108.7, 108.8, 106.7).
 constexpr uint32_t kPieceRows = 6;
@@ -98,14 +99,17 @@ constexpr uint32_t kPieceHalfRows = 6;
 // out to the workgroups by weight: with the line at 9, 100 of 0.1 to 1 MB take 104.0 instead of 106.9 us, 120
 // of 320 KiB 106.5 instead of 105.0, 400 of 64 to 128 KB and 50 of 0.2 to 2 MB the same.
 constexpr uint32_t kFineRows = 12;
-// Of these, up to so many rows and four chunks a workgroup, a workgroup's wavefronts get shares with regard
+// Of these, up to so many rows and five chunks for four workgroups, a workgroup's wavefronts get shares with regard
 // to its own pieces: cut equal, the wavefront with a chunk's end and the next one's beginning is the last by
 // 6 half rows (300 adapters both ways, 17 rows a share, 162.0 -> 159.5 us; 240 chunks of three keys 161.9 ->
-// 158.6; 500 of 320 KiB encrypted 171.9 -> 171.0; with up to 256 rows the same).  With more chunks the
-// workgroup has as many such wavefronts as others, and finding the shares takes the host longer (2000 of
-// 64 KiB 142.5 -> 144.6 us, waited for 174 -> 195).
+// 158.6; with up to 256 rows the same).  With more chunks the workgroup has as many such wavefronts as others, and
+// finding the shares takes the host longer.  On 256 compute units, both ways back to back and encrypted and waited
+// for: 256 of 16 KB to 1 MB 162.0 -> 156.7 and 104.5 -> 103.1 us, 300 of 80 to 400 KB 150.1 -> 145.6 and 98.3 -> 96.0, of
+// 256 KiB 178.6 -> 179.3 and 112.5 -> 114.8; but 350 of 80 to 400 KB 164.1 -> 164.6 and 106.3 -> 108.0, 400 of 16 KB to
+// 1 MB 222.7 -> 220.8 and 133.3 -> 135.5, 512 of 80 to 400 KB 229.8 -> 228.5 and 137.8 -> 140.6, 800 of 160 KiB 278.3 ->
+// 278.6 and 160.9 -> 166.1, 1024 of 128 KiB 284.4 -> 285.1 and 162.4 -> 169.0.
 constexpr uint32_t kEvenRows = 64;
-constexpr uint32_t kEvenChunks = 4;
+constexpr uint32_t kEvenChunks = 5, kEvenGroups = 4;
 
 // One key's chunks of a batch: n of them from the batch's chunk `first` on.
 struct KeyPart {
@@ -209,7 +213,8 @@ inline void cut_key(const KeyPart& key, uint32_t row, const uint32_t* rows, std:
     // to its pieces.
     uint64_t weight = 0, next = 0;
     uint32_t group = 0, begin = row;
-    const bool even = key.rows <= (uint64_t)most * kEvenRows && key.n <= kEvenChunks * (size_t)key.groups;
+    const bool even =
+        key.rows <= (uint64_t)most * kEvenRows && kEvenGroups * key.n <= kEvenChunks * (size_t)key.groups;
     size_t first = 0;          // the chunk with row `begin`
     uint32_t first_end = row + rows[0];  // ... and its end
     auto deal = [&](uint32_t end) {

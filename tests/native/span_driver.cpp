@@ -90,7 +90,7 @@ static void check(const std::vector<uint64_t>& len, const std::vector<uint32_t>&
             // are begun than there are wavefronts; the limit is the first tried that will do.
             const uint64_t most = (uint64_t)key.groups * kWavesPerGroup;
             if ((key.rows > most * kFineRows || key.n > 2 * most) && key.rows <= most * kEvenRows &&
-                key.n <= (uint64_t)kEvenChunks * key.groups && d.nparts > 1) {
+                kEvenGroups * key.n <= (uint64_t)kEvenChunks * key.groups && d.nparts > 1) {
                 const uint32_t rows = d.cut[d.waves], w = rows < kWavesPerGroup ? rows : kWavesPerGroup;
                 uint32_t enough = (2 * rows + kPieceHalfRows * (d.nparts + w)) / w + kPieceHalfRows + 3;
                 enough += 1 + enough / 64;
@@ -188,6 +188,20 @@ int main() {
             if (key.n) keys.push_back(key);
         }
         check(len, aad_len, order, keys, num_cu);
+    }
+    // about a chunk a workgroup, of mixed lengths: shares cut with regard to the workgroup's pieces
+    for (int trial = 0; trial < 120; ++trial) {
+        const uint32_t num_cu = trial % 2 ? 256 : cus[below(7)];
+        const size_t n = 1 + below(3 * num_cu / 2);
+        const double rows = (double)num_cu * kWavesPerGroup * (double)(kFineRows + below(kEvenRows)) / n;
+        std::vector<uint64_t> len(n);
+        std::vector<uint32_t> order(n);
+        for (size_t i = 0; i < n; ++i) {
+            len[i] = trial % 3 ? log_between(rows * 256, rows * 4096) : (uint64_t)(rows * 1024);
+            order[i] = (uint32_t)i;
+        }
+        std::vector<KeyPart> keys{KeyPart{nullptr, tables, 14, 0, n, 0, 0, 0}};
+        check(len, {}, order, keys, num_cu);
     }
     // the longest chunk that goes in spans: as many rows as there are powers of H for
     {
