@@ -99,8 +99,9 @@ void pgcm_free_key(pgcm_key_t *key);
  *   aad      HOST array of n DEVICE pointers (any alignment); entries with aad_len[i] == 0 are
  *            not read.  Must be NULL exactly when aad_len is NULL.
  *   aad_len  HOST array of n byte counts, or NULL for "no chunk has AAD".  Meant for headers: up to
- *            1 KiB of a chunk's AAD is hashed along with its payload, more than that block after
- *            block by one wavefront, some 2 us each (any length is correct).
+ *            1 KiB of a chunk's AAD is hashed along with its payload, more than that by one
+ *            wavefront ahead of it, some 6 us a KiB; of more than 512 chunks of at most 1008 bytes
+ *            all of it block after block, some 1 us each (any length is correct).
  *   src      HOST array of n DEVICE pointers, each 16-byte aligned (unused when len[i] == 0).
  *   len      HOST array of n byte counts, 0 <= len[i] <= PGCM_MAX_CHUNK_BYTES; need not be a
  *            multiple of 16.  Exactly len[i] bytes are read and written, never more.

@@ -914,8 +914,8 @@ int run_span_batch(Context* ctx, const BatchArgs& a, KeyPart* keys, size_t nkeys
     const int s = ctx->next_stage;
     int rc = ensure_stage(ctx, s, most > kSpanHostBytes ? most : kSpanHostBytes);
     if (rc != PGCM_OK) return rc;
-    // Each workgroup's list right behind its descriptor, to be read from host memory, if they are few
-    // and of much the same length; otherwise uploaded, one list after the other.
+    // Each workgroup's list right behind its descriptor, to be read from host memory, if they are few and
+    // none is longer than what is held of it (map_spans); otherwise uploaded, one list after the other.
     uint8_t* const stage = ctx->stage[s];
     uint8_t* image = stage;
     SpanPlan plan;

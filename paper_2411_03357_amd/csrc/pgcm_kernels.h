@@ -25,7 +25,7 @@ __global__ void bulk_kernel(const KeyTables* kt, const ChunkDesc* chunks,
 // least four) and, below sixteen, one more.  The chunks come as arguments, or, when `staged` is not
 // null, with a descriptor per workgroup there (batch is not looked at then).
 // slots: one per workgroup; not touched if no chunk has more than one workgroup.  Units
-// of two to sixteen rows.
+// of two to sixteen rows, of eight or sixteen unless their size is forced.
 // The arguments before `batch` come in registers (compiled for that, they are the first fourteen
 // words), so that the tables are fetched while the rest of the arguments is.
 template <bool kDecrypt, int kRounds>
@@ -43,10 +43,11 @@ __global__ void burst_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t i
                              ArriveSlot* slots, uint8_t* tags, uint8_t* ok, const GroupDesc* staged,
                              ArgBatch batch);
 
-// Spans of rows, one per wavefront, of chunks of one key (`key`) or of several (null; every
-// workgroup has its own).  packets: stride 0: the workgroups' SpanGroup, and their parts in `parts`;
-// otherwise a workgroup's SpanGroup and its parts, at most kSpanLdsParts, every `stride` bytes,
-// and these may lie in host memory.  slots: one per part.  kLongIv: iv_len exceeds kShortIvBytes.
+// Spans of rows, one per wavefront, of chunks of one key (`key`) or of several (null).  mapped: what of `map`
+// is filled in.  With kSpanKeysMapped the workgroups' keys, which are in their SpanGroup otherwise; with
+// kSpanPlaced where in `packets`, which may be host memory then, a workgroup's SpanGroup and its parts lie, at
+// most kSpanLdsParts; otherwise `packets` is the SpanGroup of all, and their parts are in `parts`.  slots: one per
+// part.  kLongIv: iv_len exceeds kShortIvBytes.
 template <bool kDecrypt, bool kLongIv>
 __global__ void span_kernel(const KeyTables* key, const uint8_t* packets, const SpanPart* parts,
                             uint32_t iv_len, uint32_t mapped, const uint8_t* ivs, ArriveSlot* slots,

@@ -2101,7 +2101,7 @@ __device__ __forceinline__ GfWords times_spread(const GfWords& v, const GfWords&
 
 // The GHASH state after `blocks` whole blocks, two at least, from p, by a wavefront, in all lanes.  All but the last
 // in rows counted back from the one before it, lane l's block times H^(65 - l); the last one times H, a nibble a lane.
-// (Some 7 us for a row; block after block from the table in memory it takes 0.5 to 0.75 us a block: 20 chunks of 8 KB
+// (6 to 7 us for a row; block after block from the table in memory it takes 0.5 to 0.75 us a block: 20 chunks of 8 KB
 // with AAD of 3000 bytes 142 -> 28 us, one of 320 KiB 114 -> 20.5, 300 of 400 KB in spans 358 -> 78.)
 // The powers one at a time: the registers are needed by what is usual.
 // A function of its own: in the middle of the span kernels' code it cost every launch of few rows 0.1 to 0.4 us (60

@@ -20,6 +20,7 @@ pytestmark = pytest.mark.gpu
 KIB, MIB = 1024, 1 << 20
 # in two to nine workgroups a chunk, of 64 blocks or of 128
 SHORT = [[8 * KIB], [8 * KIB] * 32, [4 * KIB] * 64, [1, 8191, 300, 4097, 8176]]
+MANY = [1 + (97 * i * i) % 8192 for i in range(300)]
 
 
 def _batches(rng, raw_key):
@@ -69,6 +70,17 @@ def test_long_aad_captured_and_in_fixed_buffers():
         check(r)
     pgcm.encrypt_batch_static(key, b.ivs, b.aad_ptrs, b.aad_lens, b.ptrs(b.plain), b.lens, b.ptrs(b.cipher), b.tags)
     check("static")
+    # more chunks than compute units, that have several workgroups where no launch is needed to clear their slots
+    rng, raw_key = _rng_and_key(5)
+    m = _Checked("static_many", rng, MANY, raw_key)
+    other = pgcm.expand_key(raw_key)
+    for turn in range(2):
+        pgcm.encrypt_batch_static(other, m.b.ivs, m.b.aad_ptrs, m.b.aad_lens, m.b.ptrs(m.b.plain), m.b.lens,
+                                  m.b.ptrs(m.b.cipher), m.b.tags)
+        m.b.decrypt(other)
+        m.check(turn)
+        m.clear()
+    other.free()
     key.free()
 
 
@@ -129,7 +141,7 @@ def test_between_replays():
     key = pgcm.expand_key(raw_key)
     graphed = [_Checked("captured", rng, [2 * MIB, 300 * KIB + 1], raw_key),
                _Checked("captured_short", rng, [8 * KIB] * 20, raw_key)]
-    many = _Checked("many", rng, [int(v) for v in rng.integers(1, 8 * KIB, 300)], raw_key)
+    many = _Checked("many", rng, MANY, raw_key)
     batches = _batches(rng, raw_key) + [many]
     stream = torch.cuda.Stream()
     torch.cuda.synchronize()

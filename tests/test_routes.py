@@ -14,6 +14,7 @@ import test_gpu_parity
 import test_gpu_ragged_ends
 import test_gpu_random_batches
 import test_gpu_reservations
+import test_gpu_short_calls
 import test_gpu_units_in_one_launch
 import test_zz_no_alloc
 import workloads
@@ -129,6 +130,13 @@ def test_captured_and_reserved_batches(kernels_of):
         lens = lens(np.random.default_rng([workloads.BASE_SEED, 8128, len(name)]))
         got, = kernels_of([(lens, [20] * len(lens), 0, 1)])
         assert got.split()[0] == expected[name], (name, got)
+
+
+def test_short_calls(kernels_of):
+    got = [kernels_of([(lens, [20] * len(lens), 0, 1, where)
+                       for lens in test_gpu_short_calls.SHORT + [test_gpu_short_calls.MANY]]) for where in range(4)]
+    whole = ["fold 4"] * 4 + ["shared"]
+    assert got == [["words"] * 4 + ["shared apart"], whole, ["fold 4"] * 4 + ["shared apart"], whole], got
 
 
 def test_batches_in_fixed_buffers(kernels_of):
