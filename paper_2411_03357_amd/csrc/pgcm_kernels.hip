@@ -3060,9 +3060,12 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     // a word's four bytes: of the lane's own, or of a column of the pass when its rows are folded
     GfWords powers[4];
     auto fetch_powers = [&]() __attribute__((always_inline)) {
-        const uint32_t first = kDotBlocks - pass_blocks + 16 * wave;  // of the wavefront, where a quad has a block
-        const GfWords* const from = kFold ? &kt->dot[kRowDot][0][wave & 3][lane]
-                                          : &kt->dot[first / kRowBlocks][0][column][first % kRowBlocks + (lane >> 2)];
+        // Where a quad has a block: its number, by lanes, though its row is the wavefront's.  (The row made by scalar
+        // instructions, one after the other ahead of the loads: 64 chunks of 1 KiB 5.24 us instead of 5.19.)
+        const uint32_t block = kDotBlocks - pass_blocks + 16 * wave + (lane >> 2);
+        const GfWords* const from =
+            kFold ? &kt->dot[kRowDot][0][wave & 3][lane]
+                  : &kt->dot[0][0][0][0] + ((block / kRowBlocks * kDotSlices + column) * kRowBlocks + block % kRowBlocks);
         if (!kFold || wave < 4 * folded)
 #pragma unroll
             for (uint32_t s = 0; s < 4; ++s) powers[s] = from[s * 4 * kRowBlocks];
