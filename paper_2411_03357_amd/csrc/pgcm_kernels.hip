@@ -2102,7 +2102,8 @@ __device__ __forceinline__ GfWords times_spread(const GfWords& v, const GfWords&
 // The GHASH state after `blocks` whole blocks, two at least, from p, by a wavefront, in all lanes.  All but the last
 // in rows counted back from the one before it, lane l's block times H^(65 - l); the last one times H, a nibble a lane.
 // (6 to 7 us for a row; block after block from the table in memory it takes 0.5 to 0.75 us a block: 20 chunks of 8 KB
-// with AAD of 3000 bytes 142 -> 28 us, one of 320 KiB 114 -> 20.5, 300 of 400 KB in spans 358 -> 78.)
+// with AAD of 3000 bytes 142 -> 26 us, one of 320 KiB 114 -> 26.  Without AAD they take 6.4 and 7.0, and 300 of
+// 400 KB in spans, where others have work meanwhile, 123, with it 140.)
 // The powers one at a time: the registers are needed by what is usual.
 // A function of its own: in the middle of the span kernels' code it cost every launch of few rows 0.1 to 0.4 us (60
 // chunks of up to 8 KB of three keys both ways 32.0 us without, 32.2 so, 31.7 now; three of 0.1 to 2 MB 41.9, 42.6, 42.4).
@@ -2123,8 +2124,8 @@ __device__ __attribute__((noinline)) Block long_hash(const KeyTables* __restrict
         if (end + lane >= kRowBlocks) b = global_read_block_any(p + 16 * (uint64_t)(end + lane - kRowBlocks));
         GfWords row{{0, 0, 0, 0}};
 #pragma unroll 1
-        for (uint32_t t = 0; t < kDotSlices; ++t) {
-            GfWords q = kt->dot[kRowDot][t % 4][t / 4][lane];
+        for (uint32_t t = 0; t < kDotSlices; ++t) {  // in the order they lie in: the words' first bytes, their second, ..
+            GfWords q = (&kt->dot[kRowDot][0][0][lane])[t * kRowBlocks];
             uint32_t v = b.w[0], bits = 8;
             // (the power times the bits of the byte, the first coefficient at its top)
             v <<= 24;
@@ -2135,10 +2136,8 @@ __device__ __attribute__((noinline)) Block long_hash(const KeyTables* __restrict
                 for (int k = 0; k < 4; ++k) row.a[k] = xor_and(row.a[k], q.a[k], m);
                 gfw_mul_x(q);
             }
-            b.w[0] = __builtin_amdgcn_alignbit(b.w[1], b.w[0], 8);
-            b.w[1] = __builtin_amdgcn_alignbit(b.w[2], b.w[1], 8);
-            b.w[2] = __builtin_amdgcn_alignbit(b.w[3], b.w[2], 8);
-            b.w[3] >>= 8;
+            const uint32_t rest = b.w[0] >> 8;
+            b.w[0] = b.w[1], b.w[1] = b.w[2], b.w[2] = b.w[3], b.w[3] = rest;
         }
         sum_over_lanes(row.a);
 #pragma unroll
