@@ -718,10 +718,36 @@ void use_slots(Context* ctx, size_t n, hipStream_t stream, bool capturing) {
     ctx->counter_at = nullptr;  // the unit counter of other batches may lie under them
 }
 
-void launch_swap_batch(const pgcm_key* key, const BatchArgs& a, const SwapShape& shape,
-                       hipEvent_t done, const ArgBatch& batch, const GroupDesc* staged,
-                       ArriveSlot* slots) {
-    const uint32_t more = !shape.burst && shape.wave_power < 4;  // a wavefront beyond those with units
+// A batch in one launch, its chunks described by `args` or, in swap_kernel and if that is not null, by `staged`.
+template <class Args>
+void launch_burst(const pgcm_key* key, const BatchArgs& a, const SwapShape& shape, hipEvent_t done, uint32_t nchunks,
+                  const Args& args, ArriveSlot* slots) {
+    const dim3 grid(shape.groups), block(64u << shape.wave_power);
+    const SwapMeta meta = swap_meta(nchunks, shape.unit_power, shape.wave_power, shape.alone, a.order == nullptr,
+                                    shape.groups, (uint32_t)key->rounds);
+    auto burst = [&](auto of) {
+        constexpr BurstKind kKind = decltype(of)::value;
+        const bool long_iv = a.iv_len > kShortIvBytes;
+        return a.decrypt ? (long_iv ? burst_kernel<true, true, kKind, Args> : burst_kernel<true, false, kKind, Args>)
+                         : (long_iv ? burst_kernel<false, true, kKind, Args> : burst_kernel<false, false, kKind, Args>);
+    };
+    const BurstKind kind = burst_kind(shape, (uint32_t)key->num_cu);
+    auto* kernel = kind == BurstKind::kWords  ? burst(std::integral_constant<BurstKind, BurstKind::kWords>{})
+                   : kind == BurstKind::kFold ? burst(std::integral_constant<BurstKind, BurstKind::kFold>{})
+                                              : burst(std::integral_constant<BurstKind, BurstKind::kSweep>{});
+    // (one chunk never has more workgroups than there are compute units)
+    if constexpr (!std::is_same_v<Args, ArgOne>)
+        if (kind == BurstKind::kFoldShared)
+            kernel = burst(std::integral_constant<BurstKind, BurstKind::kFoldShared>{});
+    // one chunk: its place in the caller's arrays is in the pointers
+    const size_t first = std::is_same_v<Args, ArgOne> ? a.at(0) : 0;
+    launch_last(kernel, grid, block, a.stream, a.capturing, done, (const KeyTables*)key->tables,
+                a.ivs + first * a.iv_len, a.iv_len, meta, slots, a.tags + 16 * first,
+                a.ok != nullptr ? a.ok + first : nullptr, args);
+}
+void launch_swap(const pgcm_key* key, const BatchArgs& a, const SwapShape& shape, hipEvent_t done,
+                 const ArgBatch& batch, const GroupDesc* staged, ArriveSlot* slots) {
+    const uint32_t more = shape.wave_power < 4;  // a wavefront beyond those with units
     const dim3 grid(shape.groups), block(64u * ((1u << shape.wave_power) + more));
     const KeyTables* kt = key->tables;
     const SwapMeta meta = swap_meta(staged ? 0 : (uint32_t)a.n, shape.unit_power, shape.wave_power,
@@ -730,29 +756,17 @@ void launch_swap_batch(const pgcm_key* key, const BatchArgs& a, const SwapShape&
     auto* const swap = key->rounds == 10   ? (a.decrypt ? swap_kernel<true, 10> : swap_kernel<false, 10>)
                        : key->rounds == 12 ? (a.decrypt ? swap_kernel<true, 12> : swap_kernel<false, 12>)
                                            : (a.decrypt ? swap_kernel<true, 14> : swap_kernel<false, 14>);
-    auto burst = [&](auto of) {
-        constexpr BurstKind kKind = decltype(of)::value;
-        const bool long_iv = a.iv_len > kShortIvBytes;
-        return a.decrypt ? (long_iv ? burst_kernel<true, true, kKind> : burst_kernel<true, false, kKind>)
-                         : (long_iv ? burst_kernel<false, true, kKind> : burst_kernel<false, false, kKind>);
-    };
-    const BurstKind kind = burst_kind(shape, (uint32_t)key->num_cu);
-    auto* const kernel =
-        !shape.burst ? swap
-        : kind == BurstKind::kWords ? burst(std::integral_constant<BurstKind, BurstKind::kWords>{})
-        : kind == BurstKind::kFold  ? burst(std::integral_constant<BurstKind, BurstKind::kFold>{})
-        : kind == BurstKind::kSweep ? burst(std::integral_constant<BurstKind, BurstKind::kSweep>{})
-                                    : burst(std::integral_constant<BurstKind, BurstKind::kFoldShared>{});
-    launch_last(kernel, grid, block, a.stream, a.capturing || done == nullptr, done, kt, a.ivs,
-                a.iv_len, meta, slots, a.tags, a.ok, staged, batch);
+    launch_last(swap, grid, block, a.stream, a.capturing, done, kt, a.ivs, a.iv_len, meta, slots, a.tags, a.ok,
+                staged, batch);
 }
 
 // A batch of few chunks that does not fill the chip: one kernel.  Up to kArgChunks chunks travel as
 // its arguments, nothing staged; when moreover every chunk has one workgroup, which needs no
 // slots, or `slots` are given, the call needs no context at all (ctx is null).
 int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapShape& shape, ArriveSlot* slots) {
-    ArgBatch batch{};  // (it goes out whole)
-    const bool in_args = a.n <= kArgChunks;
+    const bool one = shape.burst && a.n == 1, in_args = a.n <= kArgChunks;
+    ArgOne only;
+    ArgBatch batch;
     GroupDesc* h_groups = nullptr;
     int s = 0;
     if (ctx != nullptr) s = ctx->next_stage;
@@ -761,10 +775,7 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapSh
         if (rc != PGCM_OK) return rc;
         h_groups = reinterpret_cast<GroupDesc*>(ctx->stage[s]);
     }
-    const ShapeBatch lens{a.n, a.order, a.aad_len, a.len};
-    uint32_t groups = 0;
-    for (size_t k = 0; k < a.n; ++k) {
-        const size_t i = a.at(k);
+    auto describe = [&](size_t i) {
         ArgChunk c;
         c.src = (const uint8_t*)a.src[i];
         c.dst = (uint8_t*)a.dst[i];
@@ -772,21 +783,33 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapSh
         c.aad_len = a.aad_len ? a.aad_len[i] : 0;
         c.aad = c.aad_len ? (const uint8_t*)a.aad[i] : nullptr;
         c.index = (uint32_t)i;
-        const uint32_t of_chunk =
-            !shape.burst  ? swap_groups(lens, i, shape.unit_power, shape.wave_power)
-            : shape.alone ? 1
-                          : (uint32_t)burst_groups(burst_passes(burst_blocks(lens, i), shape.wave_power),
-                                                   shape.unit_power, shape.spare);
-        if (in_args) {
-            batch.c[k] = c;
-            batch.group_base[k] = groups;
-        } else {
-            for (uint32_t g = 0; g < of_chunk; ++g)
-                h_groups[groups + g] = GroupDesc{c, groups, of_chunk};
+        return c;
+    };
+    if (one) {
+        only.c = describe(a.at(0));
+    } else {
+        if (in_args || !shape.burst) batch = ArgBatch{};  // (it goes out whole)
+        const ShapeBatch lens{a.n, a.order, a.aad_len, a.len};
+        uint32_t groups = 0;
+        for (size_t k = 0; k < a.n; ++k) {
+            const size_t i = a.at(k);
+            const ArgChunk c = describe(i);
+            const uint32_t of_chunk =
+                !shape.burst  ? swap_groups(lens, i, shape.unit_power, shape.wave_power)
+                : shape.alone ? 1
+                              : (uint32_t)burst_groups(burst_passes(burst_blocks(lens, i), shape.wave_power),
+                                                       shape.unit_power, shape.spare);
+            if (in_args) {
+                batch.c[k] = c;
+                batch.group_base[k] = groups;
+            } else {
+                for (uint32_t g = 0; g < of_chunk; ++g)
+                    h_groups[groups + g] = GroupDesc{c, groups, of_chunk};
+            }
+            groups += of_chunk;
         }
-        groups += of_chunk;
+        if (in_args) batch.group_base[a.n] = groups;
     }
-    if (in_args) batch.group_base[a.n] = groups;
     if (!shape.alone && slots == nullptr) {
         const int rc = ensure_work(ctx, kSwapWorkBytes, a.stream);
         if (rc != PGCM_OK) return rc;
@@ -800,7 +823,14 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapSh
     // using it again only moves the guard later.)
     const bool marked = ctx != nullptr && !(in_args && ctx->quiet);
     const hipEvent_t done = marked ? ctx->stage_done[s] : nullptr;
-    launch_swap_batch(key, a, shape, done, batch, h_groups, slots);
+    if (!shape.burst)
+        launch_swap(key, a, shape, done, batch, h_groups, slots);
+    else if (one)
+        launch_burst(key, a, shape, done, 1, only, slots);
+    else if (in_args)
+        launch_burst(key, a, shape, done, (uint32_t)a.n, batch, slots);
+    else
+        launch_burst(key, a, shape, done, 0, ArgStaged{h_groups}, slots);
     if (rc_timing == PGCM_OK) rc_timing = record_timing_stop(key, a.stream);
     int rc_end = PGCM_OK;
     if (!in_args) {

@@ -37,11 +37,11 @@ __global__ void swap_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t iv
 // a workgroup, which makes meta.unit_power() passes, or, if it is a chunk's first, as many as are left,
 // or, if it has a chunk to itself, as many as that takes.  It serves any key.  kLongIv: iv_len exceeds
 // kShortIvBytes.  kWords: at most eight wavefronts, and one pass.  kFold: sixteen, and at most kFoldPasses;
-// kSweep: kSweptPasses; kFoldShared: kFoldPasses - 1, and two workgroups fit a compute unit.
-template <bool kDecrypt, bool kLongIv, BurstKind kKind>
+// kSweep: kSweptPasses; kFoldShared: kFoldPasses - 1, and two workgroups fit a compute unit.  Args: ArgOne,
+// ArgBatch or ArgStaged.
+template <bool kDecrypt, bool kLongIv, BurstKind kKind, class Args>
 __global__ void burst_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t iv_len, SwapMeta meta,
-                             ArriveSlot* slots, uint8_t* tags, uint8_t* ok, const GroupDesc* staged,
-                             ArgBatch batch);
+                             ArriveSlot* slots, uint8_t* tags, uint8_t* ok, Args args);
 
 // Spans of rows, one per wavefront, of chunks of one key (`key`) or of several (null).  mapped: what of `map`
 // is filled in.  With kSpanKeysMapped the workgroups' keys, which are in their SpanGroup otherwise; with

@@ -2882,12 +2882,13 @@ __device__ __forceinline__ uint32_t word_bytes(uint64_t at, uint64_t end) {
 
 }  // namespace
 
-template <bool kDecrypt, bool kLongIv, BurstKind kKind>
+template <bool kDecrypt, bool kLongIv, BurstKind kKind, class Args>
 __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kGroupThreads,
                              kKind == BurstKind::kFoldShared ? 8 : 4) void burst_kernel(
     const KeyTables* __restrict__ kt, const uint8_t* __restrict__ ivs, uint32_t iv_len,
     SwapMeta meta, ArriveSlot* __restrict__ slots, uint8_t* __restrict__ tags,
-    uint8_t* __restrict__ ok, const GroupDesc* __restrict__ staged, const ArgBatch batch) {
+    uint8_t* __restrict__ ok, const Args args) {
+    constexpr bool kOne = std::is_same_v<Args, ArgOne>, kStaged = std::is_same_v<Args, ArgStaged>;
     constexpr bool kFold = kKind != BurstKind::kWords, kSweep = kKind == BurstKind::kSweep;
     constexpr bool kRows = kKind == BurstKind::kFold || kSweep;  // a compute unit to itself
     __shared__ QuadLds<kKind> lds;
@@ -2911,31 +2912,31 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     if (tid < 16) column_keys = reinterpret_cast<const u32x4*>(kt->column_keys)[tid];
     const uint32_t key_word = lane < 60 ? kt->rk[lane] : 0u;  // lane i: round key word i
 
-    // this workgroup's chunk (see swap_kernel)
-    const bool alone = meta.nchunks() == 1, each = meta.one_group_each();
-    const bool iv_known = !kLongIv && staged == nullptr && meta.in_order() && (alone || each);
+    // this workgroup's chunk (as in swap_kernel)
+    const bool each = !kOne && !kStaged && meta.one_group_each();
+    const bool iv_known = !kLongIv && (kOne || (meta.in_order() && each));
     Block j{{0, 0, 0, 0}};
-    if (iv_known)
-        j = wave_j0<false>(kt, ivs + (uint64_t)(alone ? 0 : blockIdx.x) * iv_len, iv_len, lane);
+    if (iv_known) j = wave_j0<false>(kt, ivs + (uint64_t)(kOne ? 0 : blockIdx.x) * iv_len, iv_len, lane);
     ArgChunk cd;
-    uint32_t group_base, ngroups;
-    if (staged != nullptr) {
-        const GroupDesc d = staged[blockIdx.x];
+    uint32_t group_base = 0, ngroups = meta.groups();
+    if constexpr (kOne) {
+        cd = args.c;
+        cd.index = 0;
+    } else if constexpr (kStaged) {
+        const GroupDesc d = args.groups[blockIdx.x];
         cd = d.c, group_base = d.group_base, ngroups = d.ngroups;
     } else {
         uint32_t chunk = 0;
-        if (alone) {
-            group_base = 0, ngroups = meta.groups();
-        } else if (each) {
+        if (each) {
             chunk = group_base = blockIdx.x, ngroups = 1;
         } else {
-            const uint32_t first = lane < meta.nchunks() ? batch.group_base[lane] : ~0u;
+            const uint32_t first = lane < meta.nchunks() ? args.group_base[lane] : ~0u;
             chunk = __builtin_amdgcn_readfirstlane(
                 (uint32_t)__popcll(__ballot(first <= blockIdx.x)) - 1u);
-            group_base = batch.group_base[chunk];
-            ngroups = batch.group_base[chunk + 1] - group_base;
+            group_base = args.group_base[chunk];
+            ngroups = args.group_base[chunk + 1] - group_base;
         }
-        cd = batch.c[chunk];
+        cd = args.c[chunk];
     }
     if constexpr (kFold) te4.store(lds.te, tid);
     else if (wave_power == 3) te3.store(lds.te, tid);
@@ -3257,26 +3258,25 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     write_or_compare_tag<kDecrypt>(tag, tag_at, received, ok + cd.index, cd.dst, cd.len, lane);
 }
 
-#define PGCM_INSTANTIATE_BURST(D, L, K)                                                              \
-    template __global__ void burst_kernel<D, L, BurstKind::K>(                                        \
-        const KeyTables*, const uint8_t*, uint32_t, SwapMeta, ArriveSlot*, uint8_t*, uint8_t*,        \
-        const GroupDesc*, ArgBatch)
-PGCM_INSTANTIATE_BURST(false, false, kWords);
-PGCM_INSTANTIATE_BURST(true, false, kWords);
-PGCM_INSTANTIATE_BURST(false, true, kWords);
-PGCM_INSTANTIATE_BURST(true, true, kWords);
-PGCM_INSTANTIATE_BURST(false, false, kFold);
-PGCM_INSTANTIATE_BURST(true, false, kFold);
-PGCM_INSTANTIATE_BURST(false, true, kFold);
-PGCM_INSTANTIATE_BURST(true, true, kFold);
-PGCM_INSTANTIATE_BURST(false, false, kSweep);
-PGCM_INSTANTIATE_BURST(true, false, kSweep);
-PGCM_INSTANTIATE_BURST(false, true, kSweep);
-PGCM_INSTANTIATE_BURST(true, true, kSweep);
-PGCM_INSTANTIATE_BURST(false, false, kFoldShared);
-PGCM_INSTANTIATE_BURST(true, false, kFoldShared);
-PGCM_INSTANTIATE_BURST(false, true, kFoldShared);
-PGCM_INSTANTIATE_BURST(true, true, kFoldShared);
+#define PGCM_INSTANTIATE_BURST(K, A)                                                              \
+    template __global__ void burst_kernel<false, false, BurstKind::K, A> PGCM_BURST_SIGNATURE(A); \
+    template __global__ void burst_kernel<true, false, BurstKind::K, A> PGCM_BURST_SIGNATURE(A);  \
+    template __global__ void burst_kernel<false, true, BurstKind::K, A> PGCM_BURST_SIGNATURE(A);  \
+    template __global__ void burst_kernel<true, true, BurstKind::K, A> PGCM_BURST_SIGNATURE(A)
+#define PGCM_BURST_SIGNATURE(A) \
+    (const KeyTables*, const uint8_t*, uint32_t, SwapMeta, ArriveSlot*, uint8_t*, uint8_t*, A)
+PGCM_INSTANTIATE_BURST(kWords, ArgOne);
+PGCM_INSTANTIATE_BURST(kWords, ArgBatch);
+PGCM_INSTANTIATE_BURST(kWords, ArgStaged);
+PGCM_INSTANTIATE_BURST(kFold, ArgOne);
+PGCM_INSTANTIATE_BURST(kFold, ArgBatch);
+PGCM_INSTANTIATE_BURST(kFold, ArgStaged);
+PGCM_INSTANTIATE_BURST(kSweep, ArgOne);
+PGCM_INSTANTIATE_BURST(kSweep, ArgBatch);
+PGCM_INSTANTIATE_BURST(kSweep, ArgStaged);
+PGCM_INSTANTIATE_BURST(kFoldShared, ArgBatch);
+PGCM_INSTANTIATE_BURST(kFoldShared, ArgStaged);
+#undef PGCM_BURST_SIGNATURE
 #undef PGCM_INSTANTIATE_BURST
 
 // ------------------------------------------------------------------------------------------

@@ -174,6 +174,17 @@ struct ArgBatch {
     uint32_t group_base[kArgChunks + 1];  // first workgroup of every chunk; their number
     ArgChunk c[kArgChunks];
 };
+// burst_kernel has its chunks' descriptors in one of three forms.  What a launch costs the host goes by the bytes
+// of its arguments: of up to 96 2.6 to 2.8 us, of 128 and more 3.4 to 4.1; if its end is marked with an event, of
+// 48 4.5, of 64 to 96 5.1 to 6.2, of more 7.0 to 8.1.  So one chunk does not come with room for kArgChunks, nor do
+// descriptors that are in pinned memory, one for each workgroup (1 byte 4.96 -> 4.59 us, 320 KiB 6.62 -> 6.40, 2 MiB
+// decrypted 8.76 -> 8.45, 300 of up to 8 KiB decrypted 11.2 -> 9.3).
+struct ArgOne {
+    ArgChunk c;  // its place in the caller's arrays is in the pointers already
+};
+struct ArgStaged {
+    const struct GroupDesc* groups;
+};
 // Passes a workgroup of sixteen wavefronts of the kernel for short bursts makes at most, at a time and in
 // all (of fewer wavefronts: one).
 constexpr uint32_t kFoldPasses = 4, kSweptPasses = 16;
@@ -210,7 +221,7 @@ struct SwapMeta {
 #else
 #define PGCM_BOTH
 #endif
-    PGCM_BOTH uint32_t nchunks() const { return w & 0x7Fu; }          // in the arguments: 0 .. 64
+    PGCM_BOTH uint32_t nchunks() const { return w & 0x7Fu; }          // in an ArgBatch: 0 .. 64
     PGCM_BOTH uint32_t unit_power() const { return (w >> 7) & 0x1Fu; }  // burst_kernel: the passes
     PGCM_BOTH uint32_t wave_power() const { return (w >> 12) & 7u; }  // log2 of the wavefronts per
                                                                       // workgroup: 2, 3, 4

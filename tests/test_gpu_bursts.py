@@ -5,9 +5,14 @@ every kind and IVs of other lengths — against the CPU oracle, bit for bit.  (W
 and how many passes a shape takes: tests/test_routes.py.)"""
 import numpy as np
 import pytest
+import torch
 
+import oracle
 import workloads
+from device_batch import DeviceBatch
 from test_gpu_parity import _full_parity
+
+import paper_2411_03357_amd as pgcm
 
 pytestmark = pytest.mark.gpu
 
@@ -126,3 +131,33 @@ def test_shapes(shape):
 def test_other_keys_and_ivs(shape, key_bytes, iv_bytes):
     lens, alens = SHAPES[shape]
     _full_parity(_workload(shape, lens[:40] if shape == "short_aad" else lens, alens, key_bytes, iv_bytes))
+
+
+@pytest.mark.parametrize("iv_bytes", (12, 16, 40))
+@pytest.mark.parametrize("length", (1, 1024, 8192))
+def test_one_chunk_somewhere_in_the_callers_arrays(length, iv_bytes):
+    """a key that shares no launch has one chunk of several: IV, tag and verdict are at its place, and what other
+    chunks have there stays as it is"""
+    w = _workload("one_of_three", [5000, 100, length], [16], iv_bytes=iv_bytes)
+    host = w.payload_host()
+    other = np.arange(16, dtype=np.uint8)
+    raw = [w.key, w.key, other]
+    keys = [pgcm.expand_key_bytes(w.key.tobytes()), pgcm.expand_key_bytes(other.tobytes())]
+    pgcm.set_one_launch(keys[1], False)
+    b = DeviceBatch(w, torch.from_numpy(host).cuda())
+    index = np.array([0, 0, 1], np.uint32)
+    pgcm.encrypt_batch_keys(keys, index, b.ivs, iv_bytes, b.aad_ptrs, b.aad_lens, b.ptrs(b.plain), b.lens,
+                            b.ptrs(b.cipher), b.tags)
+    b.tags.view(-1, 16)[1, 3] ^= 4
+    pgcm.decrypt_verify_batch_keys(keys, index, b.ivs, iv_bytes, b.aad_ptrs, b.aad_lens, b.ptrs(b.cipher), b.lens,
+                                   b.ptrs(b.back), b.tags, b.ok)
+    b.tags.view(-1, 16)[1, 3] ^= 4
+    torch.cuda.synchronize()
+    cipher, tags = b.cipher.cpu().numpy(), b.tags.cpu().numpy().reshape(-1, 16)
+    for i in range(w.n):
+        ct, tag = oracle.encrypt(raw[i], w.ivs[i], np.frombuffer(w.aad_of(i), np.uint8), w.chunk(host, i))
+        assert w.chunk(cipher, i).tobytes() == ct and tags[i].tobytes() == tag, i
+    assert b.ok.cpu().tolist() == [1, 0, 1]
+    assert np.array_equal(w.chunk(b.back.cpu().numpy(), 2), w.chunk(host, 2))
+    for key in keys:
+        key.free()
