@@ -12,7 +12,7 @@ MARSHAL = os.path.join(HERE, "_marshal.so")
 SOURCES = ["pgcm_kernels.hip", "pgcm_bitsliced.hip", "pgcm_host.hip", "pgcm_bounce.hip", "pgcm_pipe.hip",
            "pgcm_seq.cpp"]
 HEADERS = ["pgcm_kernels.h", "pgcm_types.h", "pgcm_arrive.h", "pgcm_contexts.h", "pgcm_one_launch.h",
-           "pgcm_spans.h", "pgcm_routes.h", "pgcm_bitsliced_gen.h",
+           "pgcm_spans.h", "pgcm_routes.h", "pgcm_host_ivs.h", "pgcm_bitsliced_gen.h",
            os.path.join("..", "..", "include", "pgcm.h"),
            os.path.join("..", "..", "include", "pgcm_seq.h"),
            os.path.join("..", "..", "include", "pgcm_bounce.h"),

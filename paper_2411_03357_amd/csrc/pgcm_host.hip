@@ -15,6 +15,7 @@
 
 #include "../../include/pgcm.h"
 #include "pgcm_contexts.h"
+#include "pgcm_host_ivs.h"
 #include "pgcm_kernels.h"
 #include "pgcm_one_launch.h"
 #include "pgcm_routes.h"
@@ -434,6 +435,7 @@ struct BatchArgs {
     bool capturing = false;  // the stream is being captured into a graph
     unsigned long long capture = 0;  // ... which capture that is
     bool fixed = false;  // run in the key's fixed context: allocate nothing, refuse what does not fit
+    bool host_ivs = false;  // `ivs`, 96 bits each, is pinned memory whose contents stay as they are
 
     size_t at(size_t k) const { return order ? order[k] : k; }
 };
@@ -741,9 +743,16 @@ void launch_burst(const pgcm_key* key, const BatchArgs& a, const SwapShape& shap
             kernel = burst(std::integral_constant<BurstKind, BurstKind::kFoldShared>{});
     // one chunk: its place in the caller's arrays is in the pointers
     const size_t first = std::is_same_v<Args, ArgOne> ? a.at(0) : 0;
-    launch_last(kernel, grid, block, a.stream, a.capturing, done, (const KeyTables*)key->tables,
-                a.ivs + first * a.iv_len, a.iv_len, meta, slots, a.tags + 16 * first,
-                a.ok != nullptr ? a.ok + first : nullptr, args);
+    const uint8_t* ivs = a.ivs + first * a.iv_len;
+    uint32_t iv_len = a.iv_len;
+    if (meta.iv_in_place() && std::is_same_v<Args, ArgOne>) {
+        uint64_t words;
+        memcpy(&iv_len, ivs + 8, 4);
+        memcpy(&words, ivs, 8);
+        ivs = reinterpret_cast<const uint8_t*>(words);
+    }
+    launch_last(kernel, grid, block, a.stream, a.capturing, done, (const KeyTables*)key->tables, ivs, iv_len, meta,
+                slots, a.tags + 16 * first, a.ok != nullptr ? a.ok + first : nullptr, args);
 }
 void launch_swap(const pgcm_key* key, const BatchArgs& a, const SwapShape& shape, hipEvent_t done,
                  const ArgBatch& batch, const GroupDesc* staged, ArriveSlot* slots) {
@@ -826,7 +835,7 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapSh
     if (!shape.burst)
         launch_swap(key, a, shape, done, batch, h_groups, slots);
     else if (one)
-        launch_burst(key, a, shape, done, 1, only, slots);
+        launch_burst(key, a, shape, done, a.host_ivs ? 0 : 1, only, slots);  // (SwapMeta::iv_in_place)
     else if (in_args)
         launch_burst(key, a, shape, done, (uint32_t)a.n, batch, slots);
     else
@@ -1205,6 +1214,24 @@ int run_batch_keys(pgcm_key* const* keys, size_t nkeys, const uint32_t* key_inde
 }
 
 }  // namespace
+
+namespace pgcm {
+
+int encrypt_with_host_ivs(pgcm_key_t* key, size_t n, const uint8_t* ivs, const void* const* src, const uint64_t* len,
+                          void* const* dst, uint8_t* tags, hipStream_t stream) {
+    BatchArgs a{false, n, nullptr, ivs, 12, nullptr, nullptr, src, len, dst, tags, nullptr, stream};
+    a.host_ivs = true;
+    return run_batch(key, a);
+}
+
+int decrypt_with_host_ivs(pgcm_key_t* key, size_t n, const uint8_t* ivs, const void* const* src, const uint64_t* len,
+                          void* const* dst, const uint8_t* tags, uint8_t* ok, hipStream_t stream) {
+    BatchArgs a{true, n, nullptr, ivs, 12, nullptr, nullptr, src, len, dst, const_cast<uint8_t*>(tags), ok, stream};
+    a.host_ivs = true;
+    return run_batch(key, a);
+}
+
+}  // namespace pgcm
 
 extern "C" {
 #pragma GCC visibility push(default)

@@ -2916,7 +2916,12 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     const bool each = !kOne && !kStaged && meta.one_group_each();
     const bool iv_known = !kLongIv && (kOne || (meta.in_order() && each));
     Block j{{0, 0, 0, 0}};
-    if (iv_known) j = wave_j0<false>(kt, ivs + (uint64_t)(kOne ? 0 : blockIdx.x) * iv_len, iv_len, lane);
+    if (kOne && !kLongIv && meta.iv_in_place()) {
+        const uint64_t iv = reinterpret_cast<uint64_t>(ivs);
+        j = Block{{(uint32_t)iv, (uint32_t)(iv >> 32), iv_len, 0x01000000u}};  // IV || be32(1)
+    } else if (iv_known) {
+        j = wave_j0<false>(kt, ivs + (uint64_t)(kOne ? 0 : blockIdx.x) * iv_len, iv_len, lane);
+    }
     ArgChunk cd;
     uint32_t group_base = 0, ngroups = meta.groups();
     if constexpr (kOne) {

@@ -9,6 +9,7 @@
 
 #include "../../include/pgcm_pipe.h"
 #include "../../include/pgcm_seq.h"
+#include "pgcm_host_ivs.h"
 
 namespace {
 
@@ -87,7 +88,7 @@ int encrypt_one(pgcm_pipe* p, const void* src, uint64_t len, uint64_t iv, uint8_
     const void* srcs[1] = {src};
     void* dsts[1] = {dst};
     const uint64_t lens[1] = {len};
-    return pgcm_encrypt_batch(p->key, 1, ivs, nullptr, nullptr, srcs, lens, dsts, tag, stream);
+    return pgcm::encrypt_with_host_ivs(p->key, 1, ivs, srcs, lens, dsts, tag, stream);
 }
 
 // the PRE actions gathered so far, as few batch calls as their slots allow (tags of one call must
@@ -112,8 +113,7 @@ int flush_pre(pgcm_pipe* p, hipStream_t stream) {
         uint8_t* ivs = nullptr;
         int rc = stage_ivs(p, ivn, (uint32_t)run, stream, &ivs);
         if (rc != PGCM_OK) return rc;
-        rc = pgcm_encrypt_batch(p->key, run, ivs, nullptr, nullptr, srcs, lens, dsts,
-                                p->slot_tag(p->pending_pre[at]), stream);
+        rc = pgcm::encrypt_with_host_ivs(p->key, run, ivs, srcs, lens, dsts, p->slot_tag(p->pending_pre[at]), stream);
         if (rc != PGCM_OK) return rc;
         at += run;
     }
@@ -345,8 +345,7 @@ int pgcm_recv_accept(pgcm_recv_t* r, const void* ciphertext, uint64_t len, const
     const void* srcs[1] = {ciphertext};
     void* dsts[1] = {dst};
     const uint64_t lens[1] = {len};
-    const int rc = pgcm_decrypt_verify_batch(r->key, 1, iv, nullptr, nullptr, srcs, lens, dsts,
-                                             tag, ok, stream);
+    const int rc = pgcm::decrypt_with_host_ivs(r->key, 1, iv, srcs, lens, dsts, tag, ok, stream);
     if (rc != PGCM_OK) return rc;  // nothing was enqueued: the transfer does not count
     ++r->iv_pos;
     ++r->next_iv;

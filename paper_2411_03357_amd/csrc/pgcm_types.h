@@ -222,6 +222,8 @@ struct SwapMeta {
 #define PGCM_BOTH
 #endif
     PGCM_BOTH uint32_t nchunks() const { return w & 0x7Fu; }          // in an ArgBatch: 0 .. 64
+    PGCM_BOTH bool iv_in_place() const { return nchunks() == 0; }     // with an ArgOne: `ivs` and `iv_len` are no
+                                                                      // pointer and length but the IV's 96 bits
     PGCM_BOTH uint32_t unit_power() const { return (w >> 7) & 0x1Fu; }  // burst_kernel: the passes
     PGCM_BOTH uint32_t wave_power() const { return (w >> 12) & 7u; }  // log2 of the wavefronts per
                                                                       // workgroup: 2, 3, 4
