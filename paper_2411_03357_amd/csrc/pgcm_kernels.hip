@@ -733,12 +733,35 @@ __device__ __forceinline__ void key_xor_into_addr(uint32_t& a, uint32_t rk, uint
 // Sixteen lookup-address registers, one per state byte: a[j][k] serves byte k (row k) of column
 // j and always reads table k.  Bytes 0 and 2 hold the lane's constants for the whole kernel;
 // byte 1 is rewritten every round.
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+__device__ uint32_t struct_buffer_load32(i32x4 rsrc, int vindex, int voffset, int soffset,
+                                         int aux) __asm("llvm.amdgcn.struct.buffer.load.i32");
+template <int K>
+__device__ __forceinline__ uint32_t key_xor_byte(uint32_t rk, uint32_t v) {
+    uint32_t a;
+    if constexpr (K == 0)
+        asm("v_xor_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:BYTE_0" : "=v"(a) : "s"(rk), "v"(v));
+    else if constexpr (K == 1)
+        asm("v_xor_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1 src1_sel:BYTE_1" : "=v"(a) : "s"(rk), "v"(v));
+    else if constexpr (K == 2)
+        asm("v_xor_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_2 src1_sel:BYTE_2" : "=v"(a) : "s"(rk), "v"(v));
+    else
+        asm("v_xor_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:BYTE_3" : "=v"(a) : "s"(rk), "v"(v));
+    return a;
+}
+#ifndef PROBE_FROM
+#define PROBE_FROM 9
+#endif
+#ifndef PROBE_N
+#define PROBE_N 1
+#endif
 struct AesAddr {
     uint32_t a[4][4];
     // the last round key, in vector registers: the sixty key words and everything else a kernel
     // keeps in scalar registers do not fit them all, and one that is spilled costs a vector
     // instruction per use
     uint32_t last_key[4];
+    i32x4 te0;
 };
 
 // last_round_key: the four words of round key Nr
@@ -1065,7 +1088,7 @@ struct GhashRowMatrix {
 // issued in rounds 4 c + 3 .. 4 c + 6 (two matrix pieces fetched ahead of each round's lookups,
 // two instructions, one before and one after the round's sums) and its result packed in the
 // middle of the round after, so that neither the fetch nor the matrix pipeline is waited for.
-template <class Te, int kFirst, int kRounds, class Hash>
+template <class Te, int kFirst, int kRounds, bool kGather, class Hash>
 __device__ __forceinline__ void aes_rounds_lds(const uint32_t* __restrict__ rk, AesAddr& A,
                                                uint32_t u0, uint32_t u1, uint32_t u2, uint32_t u3,
                                                Hash& G, uint32_t base, uint32_t& o0, uint32_t& o1,
@@ -1082,11 +1105,15 @@ __device__ __forceinline__ void aes_rounds_lds(const uint32_t* __restrict__ rk, 
             if constexpr (r <= 10) G.template load<r - 3>();
             __builtin_amdgcn_sched_barrier(0);
         }
-        key_xor_into_addr<0, 0>(A.a[0][0], k[0], u0);
+        constexpr bool kG = kGather && r >= PROBE_FROM, kG2 = kG && PROBE_N > 1;
+        uint32_t t00, t10;
+        if constexpr (kG) t00 = struct_buffer_load32(A.te0, key_xor_byte<0>(k[0], u0), 0, 0, 0);
+        if constexpr (kG2) t10 = struct_buffer_load32(A.te0, key_xor_byte<0>(k[1], u1), 0, 0, 0);
+        if constexpr (!kG) key_xor_into_addr<0, 0>(A.a[0][0], k[0], u0);
         key_xor_into_addr<1, 1>(A.a[0][1], k[0], u0);
         key_xor_into_addr<2, 2>(A.a[0][2], k[0], u0);
         key_xor_into_addr<3, 3>(A.a[0][3], k[0], u0);
-        key_xor_into_addr<0, 0>(A.a[1][0], k[1], u1);
+        if constexpr (!kG2) key_xor_into_addr<0, 0>(A.a[1][0], k[1], u1);
         key_xor_into_addr<1, 1>(A.a[1][1], k[1], u1);
         key_xor_into_addr<2, 2>(A.a[1][2], k[1], u1);
         key_xor_into_addr<3, 3>(A.a[1][3], k[1], u1);
@@ -1098,9 +1125,11 @@ __device__ __forceinline__ void aes_rounds_lds(const uint32_t* __restrict__ rk, 
         key_xor_into_addr<1, 1>(A.a[3][1], k[3], u3);
         key_xor_into_addr<2, 2>(A.a[3][2], k[3], u3);
         key_xor_into_addr<3, 3>(A.a[3][3], k[3], u3);
-        uint32_t t00 = te_read<Te, 0>(A.a[0][0], base), t11 = te_read<Te, 1>(A.a[1][1], base),
+        if constexpr (!kG) t00 = te_read<Te, 0>(A.a[0][0], base);
+        if constexpr (!kG2) t10 = te_read<Te, 0>(A.a[1][0], base);
+        uint32_t t11 = te_read<Te, 1>(A.a[1][1], base),
                  t22 = te_read<Te, 2>(A.a[2][2], base), t33 = te_read<Te, 3>(A.a[3][3], base);
-        uint32_t t10 = te_read<Te, 0>(A.a[1][0], base), t21 = te_read<Te, 1>(A.a[2][1], base),
+        uint32_t t21 = te_read<Te, 1>(A.a[2][1], base),
                  t32 = te_read<Te, 2>(A.a[3][2], base), t03 = te_read<Te, 3>(A.a[0][3], base);
         uint32_t t20 = te_read<Te, 0>(A.a[2][0], base), t31 = te_read<Te, 1>(A.a[3][1], base),
                  t02 = te_read<Te, 2>(A.a[0][2], base), t13 = te_read<Te, 3>(A.a[1][3], base);
@@ -1178,7 +1207,7 @@ __device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, Aes
         G.template step<3>();
     }
     __builtin_amdgcn_sched_barrier(0);
-    aes_rounds_lds<Te, 3, kRounds>(rk, A, u0, u1, u2, u3, G, base, o0, o1, o2, o3);
+    aes_rounds_lds<Te, 3, kRounds, false>(rk, A, u0, u1, u2, u3, G, base, o0, o1, o2, o3);
 }
 
 // round 2's lookups of the lowest counter byte of the row `row` behind the one at hand
@@ -1214,7 +1243,7 @@ __device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, Aes
         G.template step<3>();
     }
     __builtin_amdgcn_sched_barrier(0);
-    aes_rounds_lds<TeWide, 3, kRounds>(rk, A, u0, u1, u2, u3, G, base, o0, o1, o2, o3);
+    aes_rounds_lds<TeWide, 3, kRounds, true>(rk, A, u0, u1, u2, u3, G, base, o0, o1, o2, o3);
 }
 
 // One block, the same in every lane, by a wavefront that has nothing else to do; lane i of key_word has
@@ -2575,10 +2604,14 @@ PGCM_INSTANTIATE_SWAP(true);
 //     quads, 11.9 in rows).  Where such a workgroup makes a single pass there is nothing in it (us, rows
 //     and quads: 64 KiB 7.1 and 7.0, 320 KiB 7.6 and 7.7, decrypted 7.6 and 7.5, 1 MiB 7.8 and 7.8, 20 of
 //     40 KiB decrypted 7.8 and 7.9), so the number of passes is not asked for.
-//   * The round tables are te[0] and te[1] alone, 32 times each, 64 KiB: te[2] and te[3] are these turned
-//     by two bytes.  Half the room to fill (0.8 us of 3.5), no lookups that collide (te[0..3] sixteen
-//     times each, as short transfers once had them, took twice the cycles), and two workgroups fit a
-//     compute unit.
+//   * The round tables are te[0] and, of sixteen wavefronts, te[1], 32 times each: the others are these turned
+//     by one byte or two.  A workgroup fills 64 bytes of LDS a clock, so that what a table less saves is as
+//     long as the wavefronts are few (one byte: tables in place 1.6 us after the start with both, 1.2
+//     with te[0] alone, a call 4.6 -> 4.4; one block of 320 KiB 6.33 -> 6.29).  Sixteen wavefronts keep the
+//     vector units busy and pay more for the two turns a round (64 chunks of 4 KiB both ways 12.4 with te[1],
+//     12.9 without); they store te[1] behind te[0], as they go on (2 MiB decrypted 8.46 -> 8.27, both in one go
+//     8.32).  No lookups collide (te[0..3] sixteen times each, as short transfers once had them, took twice the
+//     cycles), and two workgroups fit a compute unit.
 //   * What the tables are not needed for is asked for after they are in place: sixteen wavefronts' loads
 //     of keys and powers ahead of the last one's of the tables made that wait 1.2 us longer.
 //   * Sixteen wavefronts: the first three rows of a pass are multiplied by H^192, H^128, H^64 and added to
@@ -2602,7 +2635,7 @@ PGCM_INSTANTIATE_SWAP(true);
 namespace {
 
 struct QuadTables {
-    uint32_t te[256 * 64];  // 256 bytes a value: te[0] 32 times, te[1] 32 times
+    uint32_t te[256 * 64];  // 256 bytes a value: te[0] 32 times, te[1] 32 times or nothing
     u32x4 keys[4][4];       // KeyTables::column_keys
     Block long_aad[kWavesPerGroup];
     GfWords shares[kFoldPasses][kWavesPerGroup];
@@ -2627,32 +2660,26 @@ struct QuadLds<BurstKind::kFoldShared> : QuadTables {  // (its tables take the p
 static_assert(2 * sizeof(QuadLds<BurstKind::kFoldShared>) <= 160 << 10 &&
                   2 * sizeof(QuadLds<BurstKind::kWords>) <= 160 << 10,
               "two workgroups on a compute unit");
-// The round tables, by 64 << kWavePower threads: an entry a thread and eight pieces of sixteen bytes, or,
-// of fewer threads, two entries each, of more, half the pieces.  Neighbours have different tables and
-// begin with different pieces, so that a wavefront's store covers all banks evenly.
+// The first round table, by 64 << kWavePower threads: an entry a thread and eight pieces of sixteen bytes,
+// or, of more threads, a half or a quarter of them.  Eight neighbours have all eight pieces between them,
+// so that a wavefront's store covers the table's banks evenly.
 template <int kWavePower>
 struct QuadFill {
-    static constexpr uint32_t kEntries = kWavePower == 2 ? 2 : 1, kPieces = kWavePower == 4 ? 4 : 8;
-    uint32_t v[kEntries];
+    static constexpr uint32_t kShare = kWavePower - 2, kPieces = 8 >> kShare;
+    uint32_t v;
 
-    static __device__ __forceinline__ uint32_t entry(uint32_t tid) {
-        return kWavePower == 4 ? tid >> 2 : (tid >> 1) * kEntries;
-    }
     __device__ __forceinline__ void fetch(const KeyTables* __restrict__ kt, uint32_t tid) {
-        const uint32_t* from = kt->te[tid & 1] + entry(tid);
-#pragma unroll
-        for (uint32_t e = 0; e < kEntries; ++e) v[e] = from[e];
+        v = kt->te[0][tid >> kShare];
     }
+    // kTable: te[0], or te[1], which is te[0] turned by a byte
+    template <int kTable>
     __device__ __forceinline__ void store(uint32_t* te, uint32_t tid) const {
-        const uint32_t i = entry(tid), first = kWavePower == 4 ? (tid & 2) * 2 : 0;
-        u32x4* const te4 = reinterpret_cast<u32x4*>(te) + (tid & 1) * 8;
+        const uint32_t i = tid >> kShare;
+        u32x4* const te4 = reinterpret_cast<u32x4*>(te) + kTable * 8 + i * 16;
+        const uint32_t e = kTable == 0 ? v : __builtin_amdgcn_alignbit(v, v, 24);
+        const u32x4 q = {e, e, e, e};
 #pragma unroll
-        for (uint32_t e = 0; e < kEntries; ++e) {
-            const u32x4 q = {v[e], v[e], v[e], v[e]};
-#pragma unroll
-            for (uint32_t k = 0; k < kPieces; ++k)
-                te4[(i + e) * 16 + ((first + k + i) & 7)] = q;
-        }
+        for (uint32_t k = 0; k < kPieces; ++k) te4[(tid + (k << kShare)) & 7] = q;
     }
 };
 
@@ -2671,10 +2698,12 @@ template <int K>
 __device__ __forceinline__ uint32_t quad_addr(uint32_t v, uint32_t lane_bytes) {
     return __builtin_amdgcn_perm(v, lane_bytes, 0x0c0c0000u | (4u + K) << 8);
 }
+// kTables: te[0] and te[1], or te[0] alone; of a round's lookups that of the lane's own column is the last,
+// and all turning is done when it comes.
 // x: a column of the counter block in every lane, and of the keystream block on return.  (With every lane
 // looking up its own column's bytes, and the results turned instead of the bytes, a round takes eight
 // vector instructions and not eleven, but 64 chunks of 4 KiB both ways 14.2 us and not 13.8.)
-template <int kBlocks>
+template <int kTables, int kBlocks>
 __device__ __forceinline__ void quad_encrypt(const QuadKeys& keys, uint32_t lane, uint32_t base,
                                              uint32_t (&x)[kBlocks]) {
     const uint32_t lane_bytes = (lane & 31) * 4;
@@ -2686,18 +2715,31 @@ __device__ __forceinline__ void quad_encrypt(const QuadKeys& keys, uint32_t lane
                            a1 = quad_addr<1>(quad_turned<1>(x[i]), lane_bytes),
                            a2 = quad_addr<2>(quad_turned<2>(x[i]), lane_bytes),
                            a3 = quad_addr<3>(quad_turned<3>(x[i]), lane_bytes);
-            t[i][2] = lds_read32(a2 + base);
-            t[i][3] = lds_read32(a3 + base + 128);
-            t[i][0] = lds_read32(a0 + base);
-            t[i][1] = lds_read32(a1 + base + 128);
+            if constexpr (kTables == 2) {
+                t[i][2] = lds_read32(a2 + base);
+                t[i][3] = lds_read32(a3 + base + 128);
+                t[i][0] = lds_read32(a0 + base);
+                t[i][1] = lds_read32(a1 + base + 128);
+            } else {
+                t[i][3] = lds_read32(a3 + base);
+                t[i][1] = lds_read32(a1 + base);
+                t[i][2] = lds_read32(a2 + base);
+                t[i][0] = lds_read32(a0 + base);
+            }
         }
     };
     auto round = [&](uint32_t key) __attribute__((always_inline)) {
         lookups();
 #pragma unroll
         for (int i = 0; i < kBlocks; ++i) {
-            const uint32_t turned = t[i][2] ^ t[i][3];
-            x[i] = xor3(t[i][0], t[i][1], key) ^ __builtin_amdgcn_alignbit(turned, turned, 16);
+            if constexpr (kTables == 2) {
+                const uint32_t turned = t[i][2] ^ t[i][3];
+                x[i] = xor3(t[i][0], t[i][1], key) ^ __builtin_amdgcn_alignbit(turned, turned, 16);
+                continue;
+            }
+            const uint32_t odd = t[i][1] ^ __builtin_amdgcn_alignbit(t[i][3], t[i][3], 16);
+            x[i] = xor3(__builtin_amdgcn_alignbit(odd, odd, 24) ^ key,
+                        __builtin_amdgcn_alignbit(t[i][2], t[i][2], 16), t[i][0]);
         }
     };
 #pragma unroll
@@ -2709,11 +2751,11 @@ __device__ __forceinline__ void quad_encrypt(const QuadKeys& keys, uint32_t lane
         if (keys.rounds > 12) round(keys.k[12]), round(keys.k[13]);
     }
     lookups();
-    // no MixColumns: S(x) is bytes 1 and 2 of te[0], 2 and 3 of te[1]
+    // no MixColumns: S(x) is bytes 1 and 2 of te[0]
 #pragma unroll
     for (int i = 0; i < kBlocks; ++i) {
         const uint32_t lo = __builtin_amdgcn_perm(t[i][0], t[i][1], 0x0c0c0205u);
-        const uint32_t hi = __builtin_amdgcn_perm(t[i][2], t[i][3], 0x03060c0cu);
+        const uint32_t hi = __builtin_amdgcn_perm(t[i][2], t[i][3], kTables == 2 ? 0x03060c0cu : 0x02060c0cu);
         x[i] = xor3(lo, hi, keys.last);
     }
 }
@@ -2943,9 +2985,9 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
         }
         cd = args.c[chunk];
     }
-    if constexpr (kFold) te4.store(lds.te, tid);
-    else if (wave_power == 3) te3.store(lds.te, tid);
-    else te2.store(lds.te, tid);
+    if constexpr (kFold) te4.template store<0>(lds.te, tid);
+    else if (wave_power == 3) te3.template store<0>(lds.te, tid);
+    else te2.template store<0>(lds.te, tid);
     if (tid < 16) lds.keys[tid / 4][tid % 4] = column_keys;
     // What comes next is asked for only now: sixteen wavefronts' loads of it ahead of the last one's of the
     // tables made that wait 1.2 us longer, and so did a descriptor or ragged payload waited for before.
@@ -2983,6 +3025,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     // Behind a chunk's first pass of payload: a row a wavefront, a lane a block, which takes fewer instructions
     // a block (see above)
     const bool by_rows = kRows && nblk - ((int64_t)behind << pass_power) > pass_blocks;
+    if constexpr (kFold) te4.template store<1>(lds.te, tid);
     // E_K(J0) is the keystream of "block -1", if that is in a pass of this workgroup (the AAD before it may
     // have one of its own) with payload; otherwise it is made beside the first pass
     const bool mask_apart =
@@ -3145,7 +3188,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
             if (mask_apart && wave == (folded < kFoldPasses ? kWavesPerGroup - 1 : 0)) {
                 uint32_t y[1] = {j.w[0]};
                 y[0] = column == 3 ? j.w[3] : iv_word;
-                quad_encrypt<1>(keys, lane, lds_base, y);
+                quad_encrypt<kFold ? 2 : 1, 1>(keys, lane, lds_base, y);
                 if (lane < 4) lds.mask.w[lane] = y[0];
             }
         }
@@ -3156,10 +3199,10 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
         const bool mask_here = q == 0 && mask_apart && wave == 0;
         const bool mine = __ballot(blk >= (has_mask && !mask_apart ? -1 : 0)) != 0;
         if (mask_here && mine) {
-            quad_encrypt<2>(keys, lane, lds_base, x);
+            quad_encrypt<kFold ? 2 : 1, 2>(keys, lane, lds_base, x);
         } else if (mask_here || mine) {
             uint32_t y[1] = {mine ? x[0] : x[1]};
-            quad_encrypt<1>(keys, lane, lds_base, y);
+            quad_encrypt<kFold ? 2 : 1, 1>(keys, lane, lds_base, y);
             x[0] = x[1] = y[0];
         }
         if (mask_here && lane < 4) lds.mask.w[lane] = x[1];
@@ -3365,6 +3408,10 @@ __device__ __forceinline__ void walk_span(const KeyTables* __restrict__ kt, uint
         asm volatile("" : "+v"(lane));  // what depends on it is not to take registers between pieces
         AesAddr A;
         aes_addr_init<TeWide>(A, lane, rk + 4 * kRounds);
+        {
+            const uint64_t p = (uint64_t)kt->te[0];
+            A.te0 = i32x4{(int)p, (int)((p >> 32) & 0xFFFF) | (4 << 16), 256, 0x00020000};
+        }
         const PartWords cd(lds, args.parts, part, lane);
 #define PGCM_WORD(f) cd.word<offsetof(SpanPart, f)>()
 #define PGCM_PAIR(f) cd.pair<offsetof(SpanPart, f)>()
