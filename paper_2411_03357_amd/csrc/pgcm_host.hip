@@ -724,7 +724,10 @@ void use_slots(Context* ctx, size_t n, hipStream_t stream, bool capturing) {
 template <class Args>
 void launch_burst(const pgcm_key* key, const BatchArgs& a, const SwapShape& shape, hipEvent_t done, uint32_t nchunks,
                   const Args& args, ArriveSlot* slots) {
-    const dim3 grid(shape.groups), block(64u << shape.wave_power);
+    const BurstKind kind = burst_kind(shape, (uint32_t)key->num_cu);
+    const bool each_a_unit = shape.groups <= (uint32_t)key->num_cu;
+    const uint32_t more = kind == BurstKind::kWords && each_a_unit;  // a wavefront beyond those with blocks
+    const dim3 grid(shape.groups), block(64u * ((1u << shape.wave_power) + more));
     const SwapMeta meta = swap_meta(nchunks, shape.unit_power, shape.wave_power, shape.alone, a.order == nullptr,
                                     shape.groups, (uint32_t)key->rounds);
     auto burst = [&](auto of) {
@@ -733,14 +736,16 @@ void launch_burst(const pgcm_key* key, const BatchArgs& a, const SwapShape& shap
         return a.decrypt ? (long_iv ? burst_kernel<true, true, kKind, Args> : burst_kernel<true, false, kKind, Args>)
                          : (long_iv ? burst_kernel<false, true, kKind, Args> : burst_kernel<false, false, kKind, Args>);
     };
-    const BurstKind kind = burst_kind(shape, (uint32_t)key->num_cu);
     auto* kernel = kind == BurstKind::kWords  ? burst(std::integral_constant<BurstKind, BurstKind::kWords>{})
                    : kind == BurstKind::kFold ? burst(std::integral_constant<BurstKind, BurstKind::kFold>{})
                                               : burst(std::integral_constant<BurstKind, BurstKind::kSweep>{});
     // (one chunk never has more workgroups than there are compute units)
-    if constexpr (!std::is_same_v<Args, ArgOne>)
+    if constexpr (!std::is_same_v<Args, ArgOne>) {
         if (kind == BurstKind::kFoldShared)
             kernel = burst(std::integral_constant<BurstKind, BurstKind::kFoldShared>{});
+        if (kind == BurstKind::kWords && !each_a_unit)
+            kernel = burst(std::integral_constant<BurstKind, BurstKind::kWordsShared>{});
+    }
     // one chunk: its place in the caller's arrays is in the pointers
     const size_t first = std::is_same_v<Args, ArgOne> ? a.at(0) : 0;
     const uint8_t* ivs = a.ivs + first * a.iv_len;

@@ -2623,8 +2623,14 @@ PGCM_INSTANTIATE_SWAP(true);
 //     Without a fold and with fewer wavefronts to bring the tables in a pass is over sooner, so that batches
 //     of up to a pass of 64 or 128 blocks a compute unit are made so (one_pass_each: 250 KiB 7.5 -> 6.4 us,
 //     320 KiB 7.5 -> 6.9).  Passes of 256 blocks in that way are no gain: 700 KiB 7.6 -> 8.3.
-//   * E_K(J0) is the keystream of "block -1" where there is a lane for it, otherwise a second block in
-//     every quad of one wavefront, its steps between the first one's.
+//   * What the end of a workgroup needs besides its sum, the power of H that takes it to the chunk's end with x^8,
+//     x^16, .. of it, the length block's product, E_K(J0), is made by a wavefront that has no blocks, while the others
+//     are at theirs: one more than they are where at most eight have blocks and a compute unit has one workgroup (one
+//     block of 320 KiB 6.42 -> 5.94 us; where two share one, 413 workgroups of nine wavefronts were no longer all
+//     resident: 300 of up to 8 KiB decrypted 9.7 -> 11.6), or the last where rows are taken and it has none, at lower
+//     priority than theirs (2 MiB decrypted 8.34 -> 8.24, at the same priority 8.38).
+//   * Elsewhere E_K(J0) is the keystream of "block -1" where there is a lane for it, otherwise a second block
+//     in every quad of one wavefront, its steps between the first one's.
 // A pass's sum is taken to the chunk's end with one more product (KeyTables::row_hop; past 4 MiB, one
 // with far_hop as well), four passes at once.  Results of several workgroups are added up as in the kernel for units, see there.
 // Against that kernel, with units of a row and the round tables 64 or 128 KiB, per call back to back:
@@ -2658,7 +2664,7 @@ struct QuadLds<BurstKind::kFoldShared> : QuadTables {  // (its tables take the p
     Block rows[kFoldPasses - 1][4 * kRowBlocks];
 };
 static_assert(2 * sizeof(QuadLds<BurstKind::kFoldShared>) <= 160 << 10 &&
-                  2 * sizeof(QuadLds<BurstKind::kWords>) <= 160 << 10,
+                  2 * sizeof(QuadLds<BurstKind::kWordsShared>) <= 160 << 10,
               "two workgroups on a compute unit");
 // The first round table, by 64 << kWavePower threads: an entry a thread and eight pieces of sixteen bytes,
 // or, of more threads, a half or a quarter of them.  Eight neighbours have all eight pieces between them,
@@ -2925,13 +2931,16 @@ __device__ __forceinline__ uint32_t word_bytes(uint64_t at, uint64_t end) {
 }  // namespace
 
 template <bool kDecrypt, bool kLongIv, BurstKind kKind, class Args>
-__global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kGroupThreads,
+__global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads / 2 + 64
+                             : kKind == BurstKind::kWordsShared ? kGroupThreads / 2
+                                                                : kGroupThreads,
                              kKind == BurstKind::kFoldShared ? 8 : 4) void burst_kernel(
     const KeyTables* __restrict__ kt, const uint8_t* __restrict__ ivs, uint32_t iv_len,
     SwapMeta meta, ArriveSlot* __restrict__ slots, uint8_t* __restrict__ tags,
     uint8_t* __restrict__ ok, const Args args) {
     constexpr bool kOne = std::is_same_v<Args, ArgOne>, kStaged = std::is_same_v<Args, ArgStaged>;
-    constexpr bool kFold = kKind != BurstKind::kWords, kSweep = kKind == BurstKind::kSweep;
+    constexpr bool kMore = kKind == BurstKind::kWords;  // a wavefront more
+    constexpr bool kFold = !kMore && kKind != BurstKind::kWordsShared, kSweep = kKind == BurstKind::kSweep;
     constexpr bool kRows = kKind == BurstKind::kFold || kSweep;  // a compute unit to itself
     __shared__ QuadLds<kKind> lds;
     __shared__ Block long_j0;  // J0, of a long IV
@@ -2940,7 +2949,9 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t wave_power = kFold ? 4 : meta.wave_power(), nwaves = 1u << wave_power;
     const uint32_t pass_power = 4 + wave_power, pass_blocks = 1u << pass_power;
-    const bool finisher = wave == nwaves - 1;
+    // In kWords the finisher has no blocks: it makes E_K(J0) and prepares the end while the others are at theirs.
+    const bool finisher = wave == (kMore ? nwaves : nwaves - 1);
+    const bool has_blocks = !kMore || wave < nwaves;
 
     // Everything the workgroup needs from memory is asked for as early as it can be: a launch starts
     // with cold caches, and every further round of dependent loads costs it a microsecond.
@@ -2948,6 +2959,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     QuadFill<3> te3;
     QuadFill<4> te4;
     if constexpr (kFold) te4.fetch(kt, tid);
+    else if (!has_blocks) ;
     else if (wave_power == 3) te3.fetch(kt, tid);
     else te2.fetch(kt, tid);
     u32x4 column_keys{};
@@ -2986,6 +2998,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
         cd = args.c[chunk];
     }
     if constexpr (kFold) te4.template store<0>(lds.te, tid);
+    else if (!has_blocks) ;
     else if (wave_power == 3) te3.template store<0>(lds.te, tid);
     else te2.template store<0>(lds.te, tid);
     if (tid < 16) lds.keys[tid / 4][tid % 4] = column_keys;
@@ -2993,9 +3006,9 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     // tables made that wait 1.2 us longer, and so did a descriptor or ragged payload waited for before.
     asm volatile("" ::: "memory");
     if constexpr (kLongIv) {
-        // by one wavefront for all, the last but one, which mostly has no row: all sixteen at it are in each
+        // by one wavefront for all, which mostly has no row: all sixteen at it are in each
         // other's way (320 KiB with IVs of 60 bytes 17.7 us, 11.1 now; 20 of 8 KB 18.2, 11.9; 8 of 2 MiB 39.6, 34.5)
-        if (wave == nwaves - 2) {
+        if (wave == (kMore ? nwaves : nwaves - 2)) {
             j = wave_j0<true>(kt, ivs + (uint64_t)cd.index * iv_len, iv_len, lane);
             if (lane == 0) long_j0 = j;
         }
@@ -3029,7 +3042,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
     // E_K(J0) is the keystream of "block -1", if that is in a pass of this workgroup (the AAD before it may
     // have one of its own) with payload; otherwise it is made beside the first pass
     const bool mask_apart =
-        has_mask && (nblk >= (int64_t)(behind + have) << pass_power ||
+        !kMore && has_mask && (nblk >= (int64_t)(behind + have) << pass_power ||
                      nblk < (int64_t)behind << pass_power ||
                      (!by_rows && have > 1 && nblk <= (int64_t)(behind + have - 1) << pass_power));
 
@@ -3059,13 +3072,13 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
         // with 3000 bytes 700 us, 48 now)
         bool mine = by_rows && wave == wave_of_lead((uint32_t)nblk, behind, folded);
         for (uint32_t q = 0; !by_rows && q < have; ++q)
-            mine |= __ballot(block_of(behind + q) == -1) != 0;
+            mine |= has_blocks && __ballot(block_of(behind + q) == -1) != 0;
         if (mine && g == 0) {
             AadBlocks a = aad;
             a.prepare(kt, lane);
         }
     }
-    int64_t blk = have != 0 ? block_of(behind + have - 1) : -lead - 1;
+    int64_t blk = have != 0 && has_blocks ? block_of(behind + have - 1) : -lead - 1;
     WordPieces loaded;
     RowPayload row{0, 0, 0, 0, 0, false};
     bool row_edge = true;
@@ -3114,7 +3127,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
         const GfWords* const from =
             kFold ? &kt->dot[kRowDot][0][wave & 3][lane]
                   : &kt->dot[0][0][0][0] + ((block / kRowBlocks * kDotSlices + column) * kRowBlocks + block % kRowBlocks);
-        if (!kFold || wave < 4 * folded)
+        if (kFold ? wave < 4 * folded : has_blocks)
 #pragma unroll
             for (uint32_t s = 0; s < 4; ++s) powers[s] = from[s * 4 * kRowBlocks];
     };
@@ -3154,6 +3167,28 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
 
     const uint32_t first_ctr = __builtin_amdgcn_readfirstlane(bswap32(j.w[3])) + 1u;
     const uint32_t iv_word = column == 0 ? j.w[0] : column == 1 ? j.w[1] : j.w[2];
+    // What the end needs besides the passes' sums, ahead of them where the finisher has no blocks (see above).
+    GfWords far_hop{{0, 0, 0, 0}};
+    auto prepare = [&]() __attribute__((always_inline)) {
+        if (far) {
+            const uint32_t m = lane >> 4 < folded ? behind + folded - 1 - (lane >> 4) : 0;
+            far_hop = kt->far_hop[(m << pass_power) / kRowBlocks / kRowHopEntries];
+        }
+        if (has_mask) {
+            sum_over_lanes(extra.w);
+        }
+        if (hops) spread_over_row(hop, lane);
+        if (far) spread_over_row(far_hop, lane);
+    };
+    const bool ahead = kMore || (by_rows && folded < kFoldPasses);  // (it has none)
+    if (finisher && ahead) {
+        if (kMore && has_mask) {
+            uint32_t y[1] = {column == 3 ? j.w[3] : iv_word};
+            quad_encrypt<1, 1>(keys, lane, lds_base, y);
+            if (lane < 4) lds.mask.w[lane] = y[0];
+        }
+        prepare();
+    }
     if constexpr (kRows) {
         if (by_rows) {
             auto keep_mask = [&](uint32_t s0, uint32_t s1, uint32_t s2, uint32_t s3)
@@ -3162,6 +3197,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
                 };
             AesAddr A;
             aes_addr_init<TeHalf>(A, lane);
+            if (wave < 4 * folded) __builtin_amdgcn_s_setprio(2);  // ahead of a finisher without a row
             uint32_t y[4] = {0, 0, 0, 0};
             auto make_row = [&](uint32_t sweep) __attribute__((always_inline)) {
                 if (!has_row(sweep)) return;
@@ -3183,6 +3219,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
                 }
             }
             make_row(sweeps - 1);
+            __builtin_amdgcn_s_setprio(0);
             if (wave < 4 * folded)
                 lds.rows[wave / 4][(wave & 3) * kRowBlocks + lane] = Block{{y[0], y[1], y[2], y[3]}};
             if (mask_apart && wave == (folded < kFoldPasses ? kWavesPerGroup - 1 : 0)) {
@@ -3193,11 +3230,11 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
             }
         }
     }
-    for (uint32_t q = 0; !by_rows && (q < have || (q == 0 && mask_apart)); ++q) {
+    for (uint32_t q = 0; !by_rows && has_blocks && (q < have || (q == 0 && mask_apart)); ++q) {
         uint32_t x[2] = {column == 3 ? bswap32((uint32_t)blk + first_ctr) : iv_word,
                          column == 3 ? j.w[3] : iv_word};
         const bool mask_here = q == 0 && mask_apart && wave == 0;
-        const bool mine = __ballot(blk >= (has_mask && !mask_apart ? -1 : 0)) != 0;
+        const bool mine = __ballot(blk >= (!kMore && has_mask && !mask_apart ? -1 : 0)) != 0;
         if (mask_here && mine) {
             quad_encrypt<kFold ? 2 : 1, 2>(keys, lane, lds_base, x);
         } else if (mask_here || mine) {
@@ -3206,7 +3243,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
             x[0] = x[1] = y[0];
         }
         if (mask_here && lane < 4) lds.mask.w[lane] = x[1];
-        if (has_mask && !mask_apart && blk == -1) lds.mask.w[column] = x[0];
+        if (!kMore && has_mask && !mask_apart && blk == -1) lds.mask.w[column] = x[0];
         const uint32_t word = loaded.word();
         uint32_t hashed = word;  // the ciphertext, or the AAD
         if (blk >= 0) {
@@ -3256,18 +3293,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords ? kGroupThreads / 2 : kG
             lds.shares[wave / 4][wave % 4] =
                 bytes_dot(lds.rows[wave / 4][3 * kRowBlocks + lane].w[wave % 4], powers);
     }
-    GfWords far_hop{{0, 0, 0, 0}};
-    if (finisher) {
-        if (far) {
-            const uint32_t m = lane >> 4 < folded ? behind + folded - 1 - (lane >> 4) : 0;
-            far_hop = kt->far_hop[(m << pass_power) / kRowBlocks / kRowHopEntries];
-        }
-        if (has_mask) {
-            sum_over_lanes(extra.w);
-        }
-        if (hops) spread_over_row(hop, lane);
-        if (far) spread_over_row(far_hop, lane);
-    }
+    if (finisher && !ahead) prepare();
     // When decrypting, the wavefront that finishes the chunk may have to wipe plaintext that
     // others (on other XCDs) wrote: their stores go through to memory, and must be there before
     // the arrival is counted.
@@ -3324,6 +3350,8 @@ PGCM_INSTANTIATE_BURST(kSweep, ArgBatch);
 PGCM_INSTANTIATE_BURST(kSweep, ArgStaged);
 PGCM_INSTANTIATE_BURST(kFoldShared, ArgBatch);
 PGCM_INSTANTIATE_BURST(kFoldShared, ArgStaged);
+PGCM_INSTANTIATE_BURST(kWordsShared, ArgBatch);
+PGCM_INSTANTIATE_BURST(kWordsShared, ArgStaged);
 #undef PGCM_BURST_SIGNATURE
 #undef PGCM_INSTANTIATE_BURST
 

@@ -133,6 +133,17 @@ def test_other_keys_and_ivs(shape, key_bytes, iv_bytes):
     _full_parity(_workload(shape, lens[:40] if shape == "short_aad" else lens, alens, key_bytes, iv_bytes))
 
 
+@pytest.mark.parametrize("iv_bytes", (12, 40))
+@pytest.mark.parametrize("longest", (1024, 2048))
+@pytest.mark.parametrize("n", (255, 256, 257, 512))
+def test_workgroups_with_and_without_a_wavefront_more(n, longest, iv_bytes):
+    """up to a workgroup of four or of eight wavefronts for each compute unit has one more, beyond that none: chunks
+    that are empty, of AAD alone and of a whole pass, some rejected"""
+    lens = [0, longest, 1, longest - 16, 777] * 103
+    w = _workload("more_%d" % longest, lens[:n], [0, 0, 16, 5, 1025, 33, 1024], iv_bytes=iv_bytes)
+    _full_parity(w, flip=[(0, 3, 1, "tag"), (1, 0, 5, "tag"), (n - 1, 9, 2, "tag")])
+
+
 @pytest.mark.parametrize("iv_bytes", (12, 16, 40))
 @pytest.mark.parametrize("length", (1, 1024, 8192))
 def test_one_chunk_somewhere_in_the_callers_arrays(length, iv_bytes):
