@@ -733,35 +733,12 @@ __device__ __forceinline__ void key_xor_into_addr(uint32_t& a, uint32_t rk, uint
 // Sixteen lookup-address registers, one per state byte: a[j][k] serves byte k (row k) of column
 // j and always reads table k.  Bytes 0 and 2 hold the lane's constants for the whole kernel;
 // byte 1 is rewritten every round.
-typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-__device__ uint32_t struct_buffer_load32(i32x4 rsrc, int vindex, int voffset, int soffset,
-                                         int aux) __asm("llvm.amdgcn.struct.buffer.load.i32");
-template <int K>
-__device__ __forceinline__ uint32_t key_xor_byte(uint32_t rk, uint32_t v) {
-    uint32_t a;
-    if constexpr (K == 0)
-        asm("v_xor_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:BYTE_0" : "=v"(a) : "s"(rk), "v"(v));
-    else if constexpr (K == 1)
-        asm("v_xor_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1 src1_sel:BYTE_1" : "=v"(a) : "s"(rk), "v"(v));
-    else if constexpr (K == 2)
-        asm("v_xor_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_2 src1_sel:BYTE_2" : "=v"(a) : "s"(rk), "v"(v));
-    else
-        asm("v_xor_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:BYTE_3" : "=v"(a) : "s"(rk), "v"(v));
-    return a;
-}
-#ifndef PROBE_FROM
-#define PROBE_FROM 9
-#endif
-#ifndef PROBE_N
-#define PROBE_N 1
-#endif
 struct AesAddr {
     uint32_t a[4][4];
     // the last round key, in vector registers: the sixty key words and everything else a kernel
     // keeps in scalar registers do not fit them all, and one that is spilled costs a vector
     // instruction per use
     uint32_t last_key[4];
-    i32x4 te0;
 };
 
 // last_round_key: the four words of round key Nr
@@ -1088,7 +1065,7 @@ struct GhashRowMatrix {
 // issued in rounds 4 c + 3 .. 4 c + 6 (two matrix pieces fetched ahead of each round's lookups,
 // two instructions, one before and one after the round's sums) and its result packed in the
 // middle of the round after, so that neither the fetch nor the matrix pipeline is waited for.
-template <class Te, int kFirst, int kRounds, bool kGather, class Hash>
+template <class Te, int kFirst, int kRounds, class Hash>
 __device__ __forceinline__ void aes_rounds_lds(const uint32_t* __restrict__ rk, AesAddr& A,
                                                uint32_t u0, uint32_t u1, uint32_t u2, uint32_t u3,
                                                Hash& G, uint32_t base, uint32_t& o0, uint32_t& o1,
@@ -1105,15 +1082,11 @@ __device__ __forceinline__ void aes_rounds_lds(const uint32_t* __restrict__ rk, 
             if constexpr (r <= 10) G.template load<r - 3>();
             __builtin_amdgcn_sched_barrier(0);
         }
-        constexpr bool kG = kGather && r >= PROBE_FROM, kG2 = kG && PROBE_N > 1;
-        uint32_t t00, t10;
-        if constexpr (kG) t00 = struct_buffer_load32(A.te0, key_xor_byte<0>(k[0], u0), 0, 0, 0);
-        if constexpr (kG2) t10 = struct_buffer_load32(A.te0, key_xor_byte<0>(k[1], u1), 0, 0, 0);
-        if constexpr (!kG) key_xor_into_addr<0, 0>(A.a[0][0], k[0], u0);
+        key_xor_into_addr<0, 0>(A.a[0][0], k[0], u0);
         key_xor_into_addr<1, 1>(A.a[0][1], k[0], u0);
         key_xor_into_addr<2, 2>(A.a[0][2], k[0], u0);
         key_xor_into_addr<3, 3>(A.a[0][3], k[0], u0);
-        if constexpr (!kG2) key_xor_into_addr<0, 0>(A.a[1][0], k[1], u1);
+        key_xor_into_addr<0, 0>(A.a[1][0], k[1], u1);
         key_xor_into_addr<1, 1>(A.a[1][1], k[1], u1);
         key_xor_into_addr<2, 2>(A.a[1][2], k[1], u1);
         key_xor_into_addr<3, 3>(A.a[1][3], k[1], u1);
@@ -1125,11 +1098,9 @@ __device__ __forceinline__ void aes_rounds_lds(const uint32_t* __restrict__ rk, 
         key_xor_into_addr<1, 1>(A.a[3][1], k[3], u3);
         key_xor_into_addr<2, 2>(A.a[3][2], k[3], u3);
         key_xor_into_addr<3, 3>(A.a[3][3], k[3], u3);
-        if constexpr (!kG) t00 = te_read<Te, 0>(A.a[0][0], base);
-        if constexpr (!kG2) t10 = te_read<Te, 0>(A.a[1][0], base);
-        uint32_t t11 = te_read<Te, 1>(A.a[1][1], base),
+        uint32_t t00 = te_read<Te, 0>(A.a[0][0], base), t11 = te_read<Te, 1>(A.a[1][1], base),
                  t22 = te_read<Te, 2>(A.a[2][2], base), t33 = te_read<Te, 3>(A.a[3][3], base);
-        uint32_t t21 = te_read<Te, 1>(A.a[2][1], base),
+        uint32_t t10 = te_read<Te, 0>(A.a[1][0], base), t21 = te_read<Te, 1>(A.a[2][1], base),
                  t32 = te_read<Te, 2>(A.a[3][2], base), t03 = te_read<Te, 3>(A.a[0][3], base);
         uint32_t t20 = te_read<Te, 0>(A.a[2][0], base), t31 = te_read<Te, 1>(A.a[3][1], base),
                  t02 = te_read<Te, 2>(A.a[0][2], base), t13 = te_read<Te, 3>(A.a[1][3], base);
@@ -1207,7 +1178,7 @@ __device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, Aes
         G.template step<3>();
     }
     __builtin_amdgcn_sched_barrier(0);
-    aes_rounds_lds<Te, 3, kRounds, false>(rk, A, u0, u1, u2, u3, G, base, o0, o1, o2, o3);
+    aes_rounds_lds<Te, 3, kRounds>(rk, A, u0, u1, u2, u3, G, base, o0, o1, o2, o3);
 }
 
 // round 2's lookups of the lowest counter byte of the row `row` behind the one at hand
@@ -1243,7 +1214,7 @@ __device__ __forceinline__ void aes_ctr_lds(const uint32_t* __restrict__ rk, Aes
         G.template step<3>();
     }
     __builtin_amdgcn_sched_barrier(0);
-    aes_rounds_lds<TeWide, 3, kRounds, true>(rk, A, u0, u1, u2, u3, G, base, o0, o1, o2, o3);
+    aes_rounds_lds<TeWide, 3, kRounds>(rk, A, u0, u1, u2, u3, G, base, o0, o1, o2, o3);
 }
 
 // One block, the same in every lane, by a wavefront that has nothing else to do; lane i of key_word has
@@ -3436,10 +3407,6 @@ __device__ __forceinline__ void walk_span(const KeyTables* __restrict__ kt, uint
         asm volatile("" : "+v"(lane));  // what depends on it is not to take registers between pieces
         AesAddr A;
         aes_addr_init<TeWide>(A, lane, rk + 4 * kRounds);
-        {
-            const uint64_t p = (uint64_t)kt->te[0];
-            A.te0 = i32x4{(int)p, (int)((p >> 32) & 0xFFFF) | (4 << 16), 256, 0x00020000};
-        }
         const PartWords cd(lds, args.parts, part, lane);
 #define PGCM_WORD(f) cd.word<offsetof(SpanPart, f)>()
 #define PGCM_PAIR(f) cd.pair<offsetof(SpanPart, f)>()
