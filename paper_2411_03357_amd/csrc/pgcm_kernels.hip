@@ -2604,6 +2604,13 @@ PGCM_INSTANTIATE_SWAP(true);
 //     block of 320 KiB 6.42 -> 5.94 us; where two share one, 413 workgroups of nine wavefronts were no longer all
 //     resident: 300 of up to 8 KiB decrypted 9.7 -> 11.6), or the last where rows are taken and it has none, at lower
 //     priority than theirs (2 MiB decrypted 8.34 -> 8.24, at the same priority 8.38).
+//   * Decrypting, what is hashed is there before it is deciphered.  Of one or two passes in rows half the wavefronts
+//     have no row, and hash those of the others while these decipher: nothing is left to fold and to add up behind
+//     the cipher, which takes 2.9 us instead of 2.7 beside it (2 MiB 8.23 -> 7.61 us, 1 MiB 6.95 -> 6.87; eight layers of
+//     2 MiB through the pipe and its receiver 135.7 -> 130.6).  They wait for each other by counters in LDS, as a barrier
+//     would hold the cipher up.  Neither half goes first: with the cipher ahead the hash ends 1.2 us behind it, with the
+//     hash ahead the cipher ends 1.0 us later.  (Each row from the powers alone, with no tables and nobody to wait for,
+//     is three times the instructions: 8.12.)
 //   * Elsewhere E_K(J0) is the keystream of "block -1" where there is a lane for it, otherwise a second block
 //     in every quad of one wavefront, its steps between the first one's.
 // A pass's sum is taken to the chunk's end with one more product (KeyTables::row_hop; past 4 MiB, one
@@ -2629,6 +2636,7 @@ template <>
 struct QuadLds<BurstKind::kFold> : QuadTables {
     FoldTables fold;
     Block rows[kFoldPasses][4 * kRowBlocks];  // what a pass's blocks add to the hash
+    uint32_t stored, added[kFoldPasses / 2];  // wavefronts that have got so far: see `apart`
 };
 template <>
 struct QuadLds<BurstKind::kSweep> : QuadLds<BurstKind::kFold> {
@@ -3022,6 +3030,12 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
                      (!by_rows && have > 1 && nblk <= (int64_t)(behind + have - 1) << pass_power));
 
     const AadBlocks aad = aad_blocks(cd.aad, cd.aad_len, lds.long_aad + wave);
+    // Decrypting, what is hashed is there before it is deciphered, and of up to two passes in rows half the wavefronts
+    // have none to decipher: those hash the rows meanwhile, a row each.
+    const bool apart = kKind == BurstKind::kFold && kDecrypt && by_rows && folded <= kFoldPasses / 2 &&
+                       aad.blocks <= kAadLaneBlocks;
+    const bool hashes = apart && wave >= kWavesPerGroup / 2;
+    const uint32_t row_wave = apart ? wave % (kWavesPerGroup / 2) : wave;  // the wavefront's row
     // this lane's block in the pass number m from the end
     auto block_of = [&](uint32_t m) __attribute__((always_inline)) {
         return nblk - ((int64_t)(m + 1) << pass_power) + (int64_t)(16 * wave + (lane >> 2));
@@ -3059,12 +3073,12 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
     bool row_edge = true;
     // this wavefront's row of a sweep, if it has one: of the first sweep's passes some may be missing
     auto has_row = [&](uint32_t sweep) __attribute__((always_inline)) {
-        return wave < 4 * folded && (sweep > 0 || wave / 4 >= sweeps * folded - have);
+        return row_wave < 4 * folded && (sweep > 0 || row_wave / 4 >= sweeps * folded - have);
     };
     auto fetch_row = [&](uint32_t sweep) __attribute__((always_inline)) {
         if (has_row(sweep)) {
-            const uint32_t m1 = behind + folded - wave / 4 + kFoldPasses * (sweeps - 1 - sweep);
-            blk = nblk - ((int64_t)m1 << pass_power) + (wave & 3) * kRowBlocks + lane;
+            const uint32_t m1 = behind + folded - row_wave / 4 + kFoldPasses * (sweeps - 1 - sweep);
+            blk = nblk - ((int64_t)m1 << pass_power) + (row_wave & 3) * kRowBlocks + lane;
             const int64_t first = same_in_all_lanes((uint64_t)(blk - lane));
             row_edge = first < 0 || first + kRowBlocks == nblk;
             row = load_row(cd.src, cd.len, blk, row_edge, aad);
@@ -3102,11 +3116,11 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
         const GfWords* const from =
             kFold ? &kt->dot[kRowDot][0][wave & 3][lane]
                   : &kt->dot[0][0][0][0] + ((block / kRowBlocks * kDotSlices + column) * kRowBlocks + block % kRowBlocks);
-        if (kFold ? wave < 4 * folded : has_blocks)
+        if (kFold ? row_wave < 4 * folded : has_blocks)
 #pragma unroll
             for (uint32_t s = 0; s < 4; ++s) powers[s] = from[s * 4 * kRowBlocks];
     };
-    if constexpr (kKind != BurstKind::kFoldShared) fetch_powers();
+    if (kKind != BurstKind::kFoldShared && !apart) fetch_powers();
     u32x4 fold[2];  // the latter only of the first half of the threads, or in the other half for sweeps
     auto fetch_fold = [&]() __attribute__((always_inline)) {
         fold[0] = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower])[tid];  // and the next power's
@@ -3114,7 +3128,17 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
         else if (kSweep && sweeps > 1)
             fold[1] = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower + 4])[tid - kNibbleTableEntries];
     };
-    if constexpr (kRows) fetch_fold();
+    if constexpr (kRows) {
+        if (!apart) fetch_fold();
+    }
+    if constexpr (kKind == BurstKind::kFold) {
+        if (hashes) {
+            if (row_wave % 4 == 3) lds.rows[row_wave / 4][3 * kRowBlocks + lane] = Block{{0, 0, 0, 0}};
+            if (tid == kGroupThreads / 2) lds.stored = lds.added[0] = lds.added[1] = 0;
+        }
+    }
+    // (in place, the other half overwrites what is hashed)
+    if (hashes && cd.src == cd.dst) wait_for_own_global_accesses();
     __syncthreads();  // the tables are in place
     if constexpr (kLongIv) j = long_j0;
     QuadKeys keys;
@@ -3138,7 +3162,8 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
             if (tid >= kNibbleTableEntries && sweeps > 1)
                 reinterpret_cast<u32x4*>(lds.sweep)[tid - kNibbleTableEntries] = fold[1];
     };
-    if constexpr (kRows) store_fold();
+    if constexpr (kRows)
+        if (!apart) store_fold();
 
     const uint32_t first_ctr = __builtin_amdgcn_readfirstlane(bswap32(j.w[3])) + 1u;
     const uint32_t iv_word = column == 0 ? j.w[0] : column == 1 ? j.w[1] : j.w[2];
@@ -3156,7 +3181,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
         if (far) spread_over_row(far_hop, lane);
     };
     const bool ahead = kMore || (by_rows && folded < kFoldPasses);  // (it has none)
-    if (finisher && ahead) {
+    if (finisher && ahead && !apart) {
         if (kMore && has_mask) {
             uint32_t y[1] = {column == 3 ? j.w[3] : iv_word};
             quad_encrypt<1, 1>(keys, lane, lds_base, y);
@@ -3172,10 +3197,10 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
                 };
             AesAddr A;
             aes_addr_init<TeHalf>(A, lane);
-            if (wave < 4 * folded) __builtin_amdgcn_s_setprio(2);  // ahead of a finisher without a row
+            if (wave < 4 * folded && !apart) __builtin_amdgcn_s_setprio(2);  // ahead of a finisher without a row
             uint32_t y[4] = {0, 0, 0, 0};
             auto make_row = [&](uint32_t sweep) __attribute__((always_inline)) {
-                if (!has_row(sweep)) return;
+                if (!has_row(sweep) || hashes) return;
                 GhashNone G;
                 const CtrBlock C{j.w[0], j.w[1], j.w[2], (uint32_t)blk + first_ctr};
                 bulk_row<kDecrypt, 0, true>(LaneKeys{key_word, meta.rounds()}, A, C, row, cd.dst, blk,
@@ -3195,13 +3220,63 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
             }
             make_row(sweeps - 1);
             __builtin_amdgcn_s_setprio(0);
-            if (wave < 4 * folded)
+            if (wave < 4 * folded && !apart)
                 lds.rows[wave / 4][(wave & 3) * kRowBlocks + lane] = Block{{y[0], y[1], y[2], y[3]}};
-            if (mask_apart && wave == (folded < kFoldPasses ? kWavesPerGroup - 1 : 0)) {
+            if (mask_apart && !apart && wave == (folded < kFoldPasses ? kWavesPerGroup - 1 : 0)) {
                 uint32_t y[1] = {j.w[0]};
                 y[0] = column == 3 ? j.w[3] : iv_word;
                 quad_encrypt<kFold ? 2 : 1, 1>(keys, lane, lds_base, y);
                 if (lane < 4) lds.mask.w[lane] = y[0];
+            }
+        }
+    }
+    if constexpr (kKind == BurstKind::kFold && kDecrypt) {
+        if (hashes) {
+            // (the eight are resident together, and each counts itself in before it waits: no wait is for long)
+            auto counted = [&](uint32_t* at) __attribute__((always_inline)) {
+                asm volatile("" ::: "memory");  // (LDS serves a wavefront's accesses in order)
+                if (lane == 0) __hip_atomic_fetch_add(at, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            };
+            auto wait_for = [&](uint32_t* at, uint32_t n) __attribute__((always_inline)) {
+                while ((uint32_t)__builtin_amdgcn_readfirstlane(
+                           __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) < n)
+                    __builtin_amdgcn_s_sleep(1);
+                asm volatile("" ::: "memory");
+            };
+            const uint32_t i = tid % kNibbleTableEntries, q = row_wave / 4, r = row_wave % 4;
+            {
+                const u32x4 f0 = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower])[i],
+                            f1 = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower + 1])[i],
+                            f2 = reinterpret_cast<const u32x4*>(kt->ghash_rows3)[i];
+                reinterpret_cast<u32x4*>(lds.fold[0])[i] = f0;
+                reinterpret_cast<u32x4*>(lds.fold[1])[i] = f1;
+                reinterpret_cast<u32x4*>(lds.fold[2])[i] = f2;
+            }
+            counted(&lds.stored);
+            fetch_powers();
+            if (has_row(0)) {
+                uint32_t c[4] = {row.x0, row.x1, row.x2, row.x3};
+                if (r != 3) {
+                    wait_for(&lds.stored, kWavesPerGroup / 2);
+                    ghash_mul_lds(lds_offset(lds.fold[2 - r]), c);
+                }
+                uint64_t* const to = reinterpret_cast<uint64_t*>(&lds.rows[q][3 * kRowBlocks + lane]);
+                __hip_atomic_fetch_xor(to, (uint64_t)c[0] | (uint64_t)c[1] << 32, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                __hip_atomic_fetch_xor(to + 1, (uint64_t)c[2] | (uint64_t)c[3] << 32, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                counted(&lds.added[q]);
+            }
+            // (the last rows' wavefronts, which have nothing to multiply, have this as well)
+            if (finisher) prepare();
+            if (mask_apart && wave == kWavesPerGroup / 2 + 3) {
+                uint32_t y[1] = {column == 3 ? j.w[3] : iv_word};
+                quad_encrypt<2, 1>(keys, lane, lds_base, y);
+                if (lane < 4) lds.mask.w[lane] = y[0];
+            }
+            if (has_row(0)) {
+                wait_for(&lds.added[q], 4);
+                lds.shares[q][r] = bytes_dot(lds.rows[q][3 * kRowBlocks + lane].w[r], powers);
             }
         }
     }
@@ -3240,7 +3315,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
                 lds.shares[q][wave] = bytes_dot(hashed, powers);
         }
     }
-    if constexpr (kFold) {
+    if constexpr (kFold) if (!apart) {
         // the first three rows of every pass, a word a wavefront, times H^192, H^128, H^64, and added to
         // the fourth
         if constexpr (kKind == BurstKind::kFoldShared) {

@@ -144,6 +144,47 @@ def test_workgroups_with_and_without_a_wavefront_more(n, longest, iv_bytes):
     _full_parity(w, flip=[(0, 3, 1, "tag"), (1, 0, 5, "tag"), (n - 1, 9, 2, "tag")])
 
 
+# one and two passes of 256 blocks a workgroup, whose rows are hashed by wavefronts of their own when decrypting: whole,
+# short, ragged, with AAD in lanes of the first row, of a pass of its own, and too long for lanes
+_HASHED_APART = {
+    "one": ([1 << 20], [0]), "one_short": ([(1 << 20) - 65 * 16 - 3], [33]),
+    "two": ([2 << 20], [0]), "two_ragged": ([(2 << 20) - 5], [0]), "two_aad": ([(2 << 20) - 64 * 16], [1008]),
+    "two_long_aad": ([(2 << 20) - 48 * 16], [3000]), "two_half": ([400 * 4096 + 17], [16]),
+    "some": ([700 * KIB, 300 * KIB + 1, 64 * KIB - 16, 5000, 1, 0], [0, 16, 1024, 5]),
+}
+
+
+@pytest.mark.parametrize("in_place", (False, True))
+@pytest.mark.parametrize("key_bytes,iv_bytes", [(32, 12), (16, 40)])
+@pytest.mark.parametrize("shape", _HASHED_APART)
+def test_rows_hashed_apart(shape, key_bytes, iv_bytes, in_place):
+    lens, alens = _HASHED_APART[shape]
+    w = _workload("apart_%s" % shape, lens, alens, key_bytes, iv_bytes)
+    host = w.payload_host()
+    srcs = [w.chunk(host, i) for i in range(w.n)]
+    aads = [np.frombuffer(w.aad_of(i), np.uint8) for i in range(w.n)]
+    cts, tags, _ = oracle.encrypt_batch(w.key, w.ivs, aads, srcs, nthreads=8)
+    key = pgcm.expand_key_bytes(w.key.tobytes())
+    for flipped in (None, 0, w.n // 2):
+        b = DeviceBatch(w, torch.from_numpy(host).cuda())
+        wire = np.zeros_like(host)
+        for i in range(w.n):
+            w.chunk(wire, i)[:] = cts[i]
+        if flipped is not None and lens[flipped]:
+            w.chunk(wire, flipped)[lens[flipped] * 2 // 3] ^= 16
+        b.cipher.copy_(torch.from_numpy(wire))
+        b.tags.copy_(torch.from_numpy(np.ascontiguousarray(tags).reshape(-1)))
+        out = b.cipher if in_place else b.back
+        b.decrypt(key, dst=out)
+        torch.cuda.synchronize()
+        got, ok = out.cpu().numpy(), b.ok.cpu().tolist()
+        for i in range(w.n):
+            rejected = i == flipped and lens[i] != 0
+            assert ok[i] == (0 if rejected else 1), (flipped, i)
+            assert np.array_equal(w.chunk(got, i), np.zeros_like(srcs[i]) if rejected else srcs[i]), (flipped, i)
+    key.free()
+
+
 @pytest.mark.parametrize("iv_bytes", (12, 16, 40))
 @pytest.mark.parametrize("length", (1, 1024, 8192))
 def test_one_chunk_somewhere_in_the_callers_arrays(length, iv_bytes):
