@@ -733,12 +733,17 @@ void launch_burst(const pgcm_key* key, const BatchArgs& a, const SwapShape& shap
     auto burst = [&](auto of) {
         constexpr BurstKind kKind = decltype(of)::value;
         const bool long_iv = a.iv_len > kShortIvBytes;
-        return a.decrypt ? (long_iv ? burst_kernel<true, true, kKind, Args> : burst_kernel<true, false, kKind, Args>)
-                         : (long_iv ? burst_kernel<false, true, kKind, Args> : burst_kernel<false, false, kKind, Args>);
+        auto* kernel = long_iv ? burst_kernel<true, true, kKind, Args> : burst_kernel<true, false, kKind, Args>;
+        if constexpr (kKind != BurstKind::kFoldApart)
+            if (!a.decrypt)
+                kernel = long_iv ? burst_kernel<false, true, kKind, Args> : burst_kernel<false, false, kKind, Args>;
+        return kernel;
     };
     auto* kernel = kind == BurstKind::kWords  ? burst(std::integral_constant<BurstKind, BurstKind::kWords>{})
                    : kind == BurstKind::kFold ? burst(std::integral_constant<BurstKind, BurstKind::kFold>{})
                                               : burst(std::integral_constant<BurstKind, BurstKind::kSweep>{});
+    if (kind == BurstKind::kFold && a.decrypt && shape.unit_power == 2)  // (see there)
+        kernel = burst(std::integral_constant<BurstKind, BurstKind::kFoldApart>{});
     // (one chunk never has more workgroups than there are compute units)
     if constexpr (!std::is_same_v<Args, ArgOne>) {
         if (kind == BurstKind::kFoldShared)

@@ -36,11 +36,10 @@ __global__ void swap_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t iv
 // The same for batches whose time is that of one chain of steps: 2^wave_power wavefronts of sixteen blocks
 // a workgroup, which makes meta.unit_power() passes, or, if it is a chunk's first, as many as are left,
 // or, if it has a chunk to itself, as many as that takes.  It serves any key.  kLongIv: iv_len exceeds
-// kShortIvBytes.  kWords: at most eight wavefronts, one pass, and a wavefront
-// more (which it counts on: a workgroup has 2^wave_power + 1); kWordsShared: none more, and two workgroups fit a
-// compute unit.  kFold: sixteen, and at most kFoldPasses;
-// kSweep: kSweptPasses; kFoldShared: kFoldPasses - 1, and two workgroups fit a compute unit.  Args: ArgOne
-// (not of the shared kinds), ArgBatch or ArgStaged.
+// kShortIvBytes.  kWords: at most eight wavefronts, one pass, and a wavefront more (which it counts on: a workgroup
+// has 2^wave_power + 1); kWordsShared: none more, and two workgroups fit a compute unit.  kFold: sixteen, and at most
+// kFoldPasses; kFoldApart: the same, decrypting, and faster where they are two; kSweep: kSweptPasses; kFoldShared:
+// kFoldPasses - 1, and two workgroups fit a compute unit.  Args: ArgOne (not of the shared kinds), ArgBatch or ArgStaged.
 template <bool kDecrypt, bool kLongIv, BurstKind kKind, class Args>
 __global__ void burst_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t iv_len, SwapMeta meta,
                              ArriveSlot* slots, uint8_t* tags, uint8_t* ok, Args args);

@@ -2604,13 +2604,14 @@ PGCM_INSTANTIATE_SWAP(true);
 //     block of 320 KiB 6.42 -> 5.94 us; where two share one, 413 workgroups of nine wavefronts were no longer all
 //     resident: 300 of up to 8 KiB decrypted 9.7 -> 11.6), or the last where rows are taken and it has none, at lower
 //     priority than theirs (2 MiB decrypted 8.34 -> 8.24, at the same priority 8.38).
-//   * Decrypting, what is hashed is there before it is deciphered.  Of one or two passes in rows half the wavefronts
-//     have no row, and hash those of the others while these decipher: nothing is left to fold and to add up behind
-//     the cipher, which takes 2.9 us instead of 2.7 beside it (2 MiB 8.23 -> 7.61 us, 1 MiB 6.95 -> 6.87; eight layers of
-//     2 MiB through the pipe and its receiver 135.7 -> 130.6).  They wait for each other by counters in LDS, as a barrier
-//     would hold the cipher up.  Neither half goes first: with the cipher ahead the hash ends 1.2 us behind it, with the
-//     hash ahead the cipher ends 1.0 us later.  (Each row from the powers alone, with no tables and nobody to wait for,
-//     is three times the instructions: 8.12.)
+//   * Decrypting, what is hashed is there before it is deciphered.  Of two passes in rows half the wavefronts have
+//     no row, and hash those of the others while these decipher: nothing is left to fold and to add up behind the
+//     cipher, which takes 2.9 us instead of 2.7 beside it (2 MiB 8.35 -> 7.77 us; eight layers of 2 MiB through the pipe
+//     and its receiver 136.0 -> 130.7).  They wait for each other by counters in LDS, as a barrier would hold the cipher
+//     up.  Neither half goes first: with the cipher ahead the hash ends 1.2 us behind it, with the hash ahead the cipher
+//     ends 1.0 us later.  (Each row from the powers alone, with no tables and nobody to wait for, is three times the
+//     instructions: 8.12.)  Of one pass there is nothing in it, 1 MiB 7.06 and 7.11, and beside other shapes' code it
+//     costs them 0.1 us, so that two passes have a kernel of their own.
 //   * Elsewhere E_K(J0) is the keystream of "block -1" where there is a lane for it, otherwise a second block
 //     in every quad of one wavefront, its steps between the first one's.
 // A pass's sum is taken to the chunk's end with one more product (KeyTables::row_hop; past 4 MiB, one
@@ -2636,7 +2637,10 @@ template <>
 struct QuadLds<BurstKind::kFold> : QuadTables {
     FoldTables fold;
     Block rows[kFoldPasses][4 * kRowBlocks];  // what a pass's blocks add to the hash
-    uint32_t stored, added[kFoldPasses / 2];  // wavefronts that have got so far: see `apart`
+};
+template <>
+struct QuadLds<BurstKind::kFoldApart> : QuadLds<BurstKind::kFold> {
+    uint32_t stored, added[kFoldPasses / 2];  // wavefronts that have got so far
 };
 template <>
 struct QuadLds<BurstKind::kSweep> : QuadLds<BurstKind::kFold> {
@@ -2924,7 +2928,9 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
     constexpr bool kOne = std::is_same_v<Args, ArgOne>, kStaged = std::is_same_v<Args, ArgStaged>;
     constexpr bool kMore = kKind == BurstKind::kWords;  // a wavefront more
     constexpr bool kFold = !kMore && kKind != BurstKind::kWordsShared, kSweep = kKind == BurstKind::kSweep;
-    constexpr bool kRows = kKind == BurstKind::kFold || kSweep;  // a compute unit to itself
+    constexpr bool kApart = kKind == BurstKind::kFoldApart;
+    static_assert(!kApart || kDecrypt, "what is hashed is there");
+    constexpr bool kRows = kKind == BurstKind::kFold || kApart || kSweep;  // a compute unit to itself
     __shared__ QuadLds<kKind> lds;
     __shared__ Block long_j0;  // J0, of a long IV
     const uint32_t lds_base = lds_offset(&lds);
@@ -3032,8 +3038,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
     const AadBlocks aad = aad_blocks(cd.aad, cd.aad_len, lds.long_aad + wave);
     // Decrypting, what is hashed is there before it is deciphered, and of up to two passes in rows half the wavefronts
     // have none to decipher: those hash the rows meanwhile, a row each.
-    const bool apart = kKind == BurstKind::kFold && kDecrypt && by_rows && folded <= kFoldPasses / 2 &&
-                       aad.blocks <= kAadLaneBlocks;
+    const bool apart = kApart && by_rows && folded <= kFoldPasses / 2 && aad.blocks <= kAadLaneBlocks;
     const bool hashes = apart && wave >= kWavesPerGroup / 2;
     const uint32_t row_wave = apart ? wave % (kWavesPerGroup / 2) : wave;  // the wavefront's row
     // this lane's block in the pass number m from the end
@@ -3120,7 +3125,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
 #pragma unroll
             for (uint32_t s = 0; s < 4; ++s) powers[s] = from[s * 4 * kRowBlocks];
     };
-    if (kKind != BurstKind::kFoldShared && !apart) fetch_powers();
+    if (kKind != BurstKind::kFoldShared && !kRows) fetch_powers();
     u32x4 fold[2];  // the latter only of the first half of the threads, or in the other half for sweeps
     auto fetch_fold = [&]() __attribute__((always_inline)) {
         fold[0] = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower])[tid];  // and the next power's
@@ -3129,9 +3134,9 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
             fold[1] = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower + 4])[tid - kNibbleTableEntries];
     };
     if constexpr (kRows) {
-        if (!apart) fetch_fold();
+        if (!apart) fetch_powers(), fetch_fold();
     }
-    if constexpr (kKind == BurstKind::kFold) {
+    if constexpr (kApart) {
         if (hashes) {
             if (row_wave % 4 == 3) lds.rows[row_wave / 4][3 * kRowBlocks + lane] = Block{{0, 0, 0, 0}};
             if (tid == kGroupThreads / 2) lds.stored = lds.added[0] = lds.added[1] = 0;
@@ -3230,7 +3235,7 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
             }
         }
     }
-    if constexpr (kKind == BurstKind::kFold && kDecrypt) {
+    if constexpr (kApart) {
         if (hashes) {
             // (the eight are resident together, and each counts itself in before it waits: no wait is for long)
             auto counted = [&](uint32_t* at) __attribute__((always_inline)) {
@@ -3387,6 +3392,9 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
     template __global__ void burst_kernel<true, false, BurstKind::K, A> PGCM_BURST_SIGNATURE(A);  \
     template __global__ void burst_kernel<false, true, BurstKind::K, A> PGCM_BURST_SIGNATURE(A);  \
     template __global__ void burst_kernel<true, true, BurstKind::K, A> PGCM_BURST_SIGNATURE(A)
+#define PGCM_INSTANTIATE_APART(A)                                                                       \
+    template __global__ void burst_kernel<true, false, BurstKind::kFoldApart, A> PGCM_BURST_SIGNATURE(A); \
+    template __global__ void burst_kernel<true, true, BurstKind::kFoldApart, A> PGCM_BURST_SIGNATURE(A)
 #define PGCM_BURST_SIGNATURE(A) \
     (const KeyTables*, const uint8_t*, uint32_t, SwapMeta, ArriveSlot*, uint8_t*, uint8_t*, A)
 PGCM_INSTANTIATE_BURST(kWords, ArgOne);
@@ -3402,7 +3410,11 @@ PGCM_INSTANTIATE_BURST(kFoldShared, ArgBatch);
 PGCM_INSTANTIATE_BURST(kFoldShared, ArgStaged);
 PGCM_INSTANTIATE_BURST(kWordsShared, ArgBatch);
 PGCM_INSTANTIATE_BURST(kWordsShared, ArgStaged);
+PGCM_INSTANTIATE_APART(ArgOne);
+PGCM_INSTANTIATE_APART(ArgBatch);
+PGCM_INSTANTIATE_APART(ArgStaged);
 #undef PGCM_BURST_SIGNATURE
+#undef PGCM_INSTANTIATE_APART
 #undef PGCM_INSTANTIATE_BURST
 
 // ------------------------------------------------------------------------------------------

@@ -198,7 +198,7 @@ constexpr uint32_t wave_of_lead(uint32_t nblk, uint32_t behind, uint32_t folded)
     const uint32_t pass = nblk / 256, at = 255 - nblk % 256;  // number from the end, and the block's place in it
     return 4 * ((behind + folded - 1 - pass) % kFoldPasses) + at / 64;
 }
-enum class BurstKind { kWords, kFold, kSweep, kFoldShared, kWordsShared };
+enum class BurstKind { kWords, kFold, kSweep, kFoldShared, kWordsShared, kFoldApart };
 // Workgroups of a chunk (KeyTables::hop has their distances) and of a launch.
 constexpr uint32_t kSwapChunkGroups = kHopEntries;
 constexpr uint32_t kSwapMaxGroups = 512;
