@@ -725,8 +725,9 @@ template <class Args>
 void launch_burst(const pgcm_key* key, const BatchArgs& a, const SwapShape& shape, hipEvent_t done, uint32_t nchunks,
                   const Args& args, ArriveSlot* slots) {
     const BurstKind kind = burst_kind(shape, (uint32_t)key->num_cu);
-    const bool each_a_unit = shape.groups <= (uint32_t)key->num_cu;
-    const uint32_t more = kind == BurstKind::kWords && each_a_unit;  // a wavefront beyond those with blocks
+    // a wavefront beyond those with blocks, where every workgroup has a compute unit (one chunk's always have)
+    const bool more = kind == BurstKind::kWords &&
+                      (std::is_same_v<Args, ArgOne> || shape.groups <= (uint32_t)key->num_cu);
     const dim3 grid(shape.groups), block(64u * ((1u << shape.wave_power) + more));
     const SwapMeta meta = swap_meta(nchunks, shape.unit_power, shape.wave_power, shape.alone, a.order == nullptr,
                                     shape.groups, (uint32_t)key->rounds);
@@ -744,11 +745,10 @@ void launch_burst(const pgcm_key* key, const BatchArgs& a, const SwapShape& shap
                                               : burst(std::integral_constant<BurstKind, BurstKind::kSweep>{});
     if (kind == BurstKind::kFold && a.decrypt && shape.unit_power == 2)  // (see there)
         kernel = burst(std::integral_constant<BurstKind, BurstKind::kFoldApart>{});
-    // (one chunk never has more workgroups than there are compute units)
     if constexpr (!std::is_same_v<Args, ArgOne>) {
         if (kind == BurstKind::kFoldShared)
             kernel = burst(std::integral_constant<BurstKind, BurstKind::kFoldShared>{});
-        if (kind == BurstKind::kWords && !each_a_unit)
+        if (kind == BurstKind::kWords && !more)
             kernel = burst(std::integral_constant<BurstKind, BurstKind::kWordsShared>{});
     }
     // one chunk: its place in the caller's arrays is in the pointers

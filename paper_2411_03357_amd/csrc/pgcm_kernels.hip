@@ -470,7 +470,8 @@ __device__ __forceinline__ void global_write_block_any(uint8_t* p, const Block& 
 // for output that a wavefront on another XCD may overwrite later in the same kernel (the wipe of
 // a rejected chunk), where two L2s holding different dirty versions of a line would leave it to
 // chance which one memory keeps.
-// In launches of a few rows a wavefront, encrypting ones write their rows like this as well: what is left in the L2s
+// In launches of a few rows a wavefront, encrypting ones write rows of whole lines like this as well (others, whose
+// neighbours' parts of a line an L2 puts together, come to host memory 3 % later, 2 of 3 to 4 MB 144.7 us -> 149.0): what is left in the L2s
 // is written back when a kernel ends, with nothing else going on (2 MiB 8.47 -> 8.23 us, 8 x 512 KiB both ways 24.1 ->
 // 23.8, 12 MiB 23.8 -> 22.7, 28 MB in units 47.3 -> 46.3, sixteen blocks of 320 KiB into host memory 108.6 -> 106.8;
 // but 64 x 4 KiB, in quads, 12.4 -> 12.5, and 2000 chunks of 16 KiB to 8 MiB in spans 2815 -> 2833).
@@ -482,6 +483,11 @@ __device__ __forceinline__ void global_write128_through(uint8_t* p, u32x4 v) {
 __device__ __forceinline__ void global_write128_through(uint8_t* base, uint32_t offset, u32x4 v) {
     asm volatile("global_store_dwordx4 %0, %1, %2 sc0 sc1\n\ts_nop 1"
                  : : "v"(offset), "v"(v), "s"(base) : "memory");
+}
+
+// Rows, which are counted back from the end of a chunk's nblk blocks, begin and end with lines of 128 bytes.
+__device__ __forceinline__ bool rows_of_whole_lines(const uint8_t* dst, int64_t nblk) {
+    return ((reinterpret_cast<uint64_t>(dst) + 16 * (uint64_t)nblk) & 127) == 0;
 }
 
 // n < 16 bytes at any alignment, zero-padded, and nothing behind them: pieces of 8, 4, 2 and 1 bytes as
@@ -1297,6 +1303,8 @@ struct RowPayload {
     uint32_t x0, x1, x2, x3;
     uint32_t tail;  // bytes in a ragged block, 0 = whole block or none
     bool whole;
+
+    __device__ __forceinline__ void arrive() {}  // (asked for by load_row, waited for where it is used)
 };
 
 // Lanes before the chunk's start get the AAD's blocks, or zero blocks.
@@ -1335,21 +1343,24 @@ __device__ __forceinline__ RowPayload load_row(const uint8_t* src, uint64_t len,
 // G: the row hash engine, on the matrix cores or from a table.
 // `edge` is the same in every lane and held in a scalar register (walk_unit sees to that), so
 // the rows that are no edge rows branch past all of the checks.
-template <bool kDecrypt, int kRounds, bool kThrough, class Keys, class Ctr, class Hash, class StoreMask>
+// through: whole blocks are, too, if that is not known when compiled.
+template <bool kDecrypt, int kRounds, bool kThrough, class Keys, class Ctr, class Row, class Hash, class StoreMask>
 __device__ __forceinline__ void bulk_row(const Keys& rk, AesAddr& A,
-                                         const Ctr& C, const RowPayload& r, uint8_t* dst,
-                                         int64_t blk, bool edge, StoreMask&& store_mask, uint32_t lds_base, Hash& G) {
+                                         const Ctr& C, Row r, uint8_t* dst,
+                                         int64_t blk, bool edge, StoreMask&& store_mask, uint32_t lds_base, Hash& G,
+                                         bool through = kThrough) {
     uint8_t* dp = dst + blk * 16;
-    const uint32_t x0 = r.x0, x1 = r.x1, x2 = r.x2, x3 = r.x3, tail = r.tail;
     // the keystream block ... while the hash state moves one row along
     G.begin();
     uint32_t s0, s1, s2, s3;
     aes_ctr_lds<kRounds>(rk, A, C, G, lds_base, s0, s1, s2, s3);
+    r.arrive();
+    const uint32_t x0 = r.x0, x1 = r.x1, x2 = r.x2, x3 = r.x3, tail = r.tail;
     uint32_t o0 = x0 ^ s0, o1 = x1 ^ s1, o2 = x2 ^ s2, o3 = x3 ^ s3;
 
     auto store_block = [&]() __attribute__((always_inline)) {
         u32x4 o = {o0, o1, o2, o3};
-        if constexpr (kThrough)
+        if (through)
             global_write128_through(dp, o);
         else
             global_write128(dp, o);
@@ -1482,7 +1493,8 @@ __device__ __forceinline__ void walk_unit(const uint32_t* __restrict__ rk, AesAd
                                           uint32_t lane, uint32_t wave, uint32_t lds_base,
                                           const uint8_t* src, uint8_t* dst, uint64_t len,
                                           int64_t b0, int64_t b1, bool last, const AadBlocks& aad,
-                                          const Block& j, Pace& pace, StoreMask&& store_mask, uint32_t y[4]) {
+                                          const Block& j, Pace& pace, StoreMask&& store_mask, uint32_t y[4],
+                                          bool through = kThrough) {
     const uint32_t nrows = (uint32_t)((b1 - b0 + kRowBlocks - 1) / kRowBlocks);
     // a row's counter blocks: inc32^(blk + 1)(J0), the first 96 bits of J0, then its counter field
     // plus blk + 1 modulo 2^32 (SP 800-38D 6.2, 7.1 step 3; ctr1 is that field plus 1, 2 for a
@@ -1527,7 +1539,7 @@ __device__ __forceinline__ void walk_unit(const uint32_t* __restrict__ rk, AesAd
             pace.start_row(lane);
             const RowPayload p = load_row(src, len, row_blk + lane, edge, aad);
             bulk_row<kDecrypt, kRounds, kThrough>(rk, A, C, p, dst, row_blk + lane, edge,
-                                                  store_mask, lds_base, G);
+                                                  store_mask, lds_base, G, through);
         }
     }
     G.home(y);
@@ -2484,9 +2496,9 @@ __global__ __launch_bounds__(kGroupThreads) void swap_kernel(
             AesAddr A;
             aes_addr_init<Te>(A, lane, rk + 4 * kRounds);
             NoPace pace;
-            walk_unit<kDecrypt, kRounds, true, false, false>(
+            walk_unit<kDecrypt, kRounds, kDecrypt, false, false>(
                 rk, A, lane, wave, lds_base, cd.src, cd.dst, cd.len, b0, b1, b1 == nblk, aad, j,
-                pace, keep_mask, y);
+                pace, keep_mask, y, kDecrypt || rows_of_whole_lines(cd.dst, nblk));
         }
         fetch_ahead();
     }
@@ -2606,12 +2618,12 @@ PGCM_INSTANTIATE_SWAP(true);
 //     priority than theirs (2 MiB decrypted 8.34 -> 8.24, at the same priority 8.38).
 //   * Decrypting, what is hashed is there before it is deciphered.  Of two passes in rows half the wavefronts have
 //     no row, and hash those of the others while these decipher: nothing is left to fold and to add up behind the
-//     cipher, which takes 2.9 us instead of 2.7 beside it (2 MiB 8.35 -> 7.77 us; eight layers of 2 MiB through the pipe
-//     and its receiver 136.0 -> 130.7).  They wait for each other by counters in LDS, as a barrier would hold the cipher
-//     up.  Neither half goes first: with the cipher ahead the hash ends 1.2 us behind it, with the hash ahead the cipher
-//     ends 1.0 us later.  (Each row from the powers alone, with no tables and nobody to wait for, is three times the
-//     instructions: 8.12.)  Of one pass there is nothing in it, 1 MiB 7.06 and 7.11, and beside other shapes' code it
-//     costs them 0.1 us, so that two passes have a kernel of their own.
+//     cipher (2 MiB 8.35 -> 7.8 us; eight layers of 2 MiB through the pipe and its receiver 136.0 -> 131.3; out of host
+//     memory, whose payload comes too late for it, 51.3 -> 52.2).  They wait for each other by counters in LDS, as a
+//     barrier would hold the cipher up.  Neither half goes first: with the cipher ahead the hash ends 1.2 us behind it,
+//     with the hash ahead the cipher ends 1.0 us later.  (Each row from the powers alone, with no tables and nobody to
+//     wait for, is three times the instructions: 8.12.)  Of one pass there is nothing in it, 1 MiB 7.06 and 7.11, and
+//     beside other shapes' code it costs them 0.1 us, so that two passes have a kernel of their own.
 //   * Elsewhere E_K(J0) is the keystream of "block -1" where there is a lane for it, otherwise a second block
 //     in every quad of one wavefront, its steps between the first one's.
 // A pass's sum is taken to the chunk's end with one more product (KeyTables::row_hop; past 4 MiB, one
@@ -2910,6 +2922,13 @@ __device__ __forceinline__ u32x4 word_times(uint32_t table, uint32_t v) {
     for (int k = 1; k < 8; ++k) z ^= e[k];
     return z;
 }
+// Until n wavefronts of the workgroup, all resident and on their way there, have counted themselves in.
+__device__ __forceinline__ void wait_for_count(uint32_t* at, uint32_t n) {
+    while ((uint32_t)__builtin_amdgcn_readfirstlane(
+               __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) < n)
+        __builtin_amdgcn_s_sleep(1);
+    asm volatile("" ::: "memory");
+}
 // how many of the four bytes from `at` on lie before `end`
 __device__ __forceinline__ uint32_t word_bytes(uint64_t at, uint64_t end) {
     return at + 4 <= end ? 4u : at < end ? (uint32_t)(end - at) : 0u;
@@ -3074,7 +3093,19 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
     }
     int64_t blk = have != 0 && has_blocks ? block_of(behind + have - 1) : -lead - 1;
     WordPieces loaded;
-    RowPayload row{0, 0, 0, 0, 0, false};
+    // (where others hash the row they alone read it, and it is taken from LDS when the keystream is there: a second read
+    // may be one of host memory, 2 MiB out of it 55.1 us, so 52.2; in place, nothing is overwritten before it is hashed)
+    struct SharedRow : RowPayload {
+        const Block* at = nullptr;
+        uint32_t* stored = nullptr;
+        __device__ __forceinline__ void arrive() {
+            if (at == nullptr) return;
+            wait_for_count(stored, kWavesPerGroup / 2);
+            const Block b = *at;
+            x0 = b.w[0], x1 = b.w[1], x2 = b.w[2], x3 = b.w[3];
+        }
+    };
+    std::conditional_t<kApart, SharedRow, RowPayload> row{};
     bool row_edge = true;
     // this wavefront's row of a sweep, if it has one: of the first sweep's passes some may be missing
     auto has_row = [&](uint32_t sweep) __attribute__((always_inline)) {
@@ -3086,11 +3117,21 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
             blk = nblk - ((int64_t)m1 << pass_power) + (row_wave & 3) * kRowBlocks + lane;
             const int64_t first = same_in_all_lanes((uint64_t)(blk - lane));
             row_edge = first < 0 || first + kRowBlocks == nblk;
-            row = load_row(cd.src, cd.len, blk, row_edge, aad);
+            if constexpr (kApart) {
+                if (apart && !hashes) {
+                    const bool tail = row_edge && blk >= 0 && (uint64_t)blk * 16 + 16 > cd.len;
+                    row.tail = tail ? (uint32_t)(cd.len & 15) : 0;
+                    row.whole = blk >= 0 && row.tail == 0;
+                    row.at = &lds.rows[row_wave / 4][(row_wave & 3) * kRowBlocks + lane];
+                    row.stored = &lds.stored;
+                    return;
+                }
+            }
+            static_cast<RowPayload&>(row) = load_row(cd.src, cd.len, blk, row_edge, aad);
         }
     };
     if (by_rows) {
-        fetch_row(0);
+        if (!hashes) fetch_row(0);  // (those that hash ask for tables first)
     } else {
         loaded = load_word(blk);
     }
@@ -3138,12 +3179,10 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
     }
     if constexpr (kApart) {
         if (hashes) {
-            if (row_wave % 4 == 3) lds.rows[row_wave / 4][3 * kRowBlocks + lane] = Block{{0, 0, 0, 0}};
+            if (row_wave % 4 == 3) lds.rows[2 + row_wave / 4][lane] = Block{{0, 0, 0, 0}};  // the sum of pass q: rows[2 + q]
             if (tid == kGroupThreads / 2) lds.stored = lds.added[0] = lds.added[1] = 0;
         }
     }
-    // (in place, the other half overwrites what is hashed)
-    if (hashes && cd.src == cd.dst) wait_for_own_global_accesses();
     __syncthreads();  // the tables are in place
     if constexpr (kLongIv) j = long_j0;
     QuadKeys keys;
@@ -3204,12 +3243,13 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
             aes_addr_init<TeHalf>(A, lane);
             if (wave < 4 * folded && !apart) __builtin_amdgcn_s_setprio(2);  // ahead of a finisher without a row
             uint32_t y[4] = {0, 0, 0, 0};
+            const bool through = kDecrypt || rows_of_whole_lines(cd.dst, nblk);
             auto make_row = [&](uint32_t sweep) __attribute__((always_inline)) {
                 if (!has_row(sweep) || hashes) return;
                 GhashNone G;
                 const CtrBlock C{j.w[0], j.w[1], j.w[2], (uint32_t)blk + first_ctr};
-                bulk_row<kDecrypt, 0, true>(LaneKeys{key_word, meta.rounds()}, A, C, row, cd.dst, blk,
-                                                row_edge, keep_mask, lds_base, G);
+                bulk_row<kDecrypt, 0, kDecrypt>(LaneKeys{key_word, meta.rounds()}, A, C, row, cd.dst, blk,
+                                                row_edge, keep_mask, lds_base, G, through);
 #pragma unroll
                 for (int k = 0; k < 4; ++k) y[k] ^= G.w[k];
             };
@@ -3242,30 +3282,28 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
                 asm volatile("" ::: "memory");  // (LDS serves a wavefront's accesses in order)
                 if (lane == 0) __hip_atomic_fetch_add(at, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             };
-            auto wait_for = [&](uint32_t* at, uint32_t n) __attribute__((always_inline)) {
-                while ((uint32_t)__builtin_amdgcn_readfirstlane(
-                           __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) < n)
-                    __builtin_amdgcn_s_sleep(1);
-                asm volatile("" ::: "memory");
-            };
             const uint32_t i = tid % kNibbleTableEntries, q = row_wave / 4, r = row_wave % 4;
             {
                 const u32x4 f0 = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower])[i],
                             f1 = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower + 1])[i],
                             f2 = reinterpret_cast<const u32x4*>(kt->ghash_rows3)[i];
+                __builtin_amdgcn_sched_barrier(0);
+                fetch_row(0);  // behind them: it may come from host memory
+                __builtin_amdgcn_sched_barrier(0);
                 reinterpret_cast<u32x4*>(lds.fold[0])[i] = f0;
                 reinterpret_cast<u32x4*>(lds.fold[1])[i] = f1;
                 reinterpret_cast<u32x4*>(lds.fold[2])[i] = f2;
             }
-            counted(&lds.stored);
+            if (has_row(0)) lds.rows[q][r * kRowBlocks + lane] = Block{{row.x0, row.x1, row.x2, row.x3}};
+            counted(&lds.stored);  // the wavefronts that decipher wait for it as well
             fetch_powers();
             if (has_row(0)) {
                 uint32_t c[4] = {row.x0, row.x1, row.x2, row.x3};
                 if (r != 3) {
-                    wait_for(&lds.stored, kWavesPerGroup / 2);
+                    wait_for_count(&lds.stored, kWavesPerGroup / 2);
                     ghash_mul_lds(lds_offset(lds.fold[2 - r]), c);
                 }
-                uint64_t* const to = reinterpret_cast<uint64_t*>(&lds.rows[q][3 * kRowBlocks + lane]);
+                uint64_t* const to = reinterpret_cast<uint64_t*>(&lds.rows[2 + q][lane]);
                 __hip_atomic_fetch_xor(to, (uint64_t)c[0] | (uint64_t)c[1] << 32, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_WORKGROUP);
                 __hip_atomic_fetch_xor(to + 1, (uint64_t)c[2] | (uint64_t)c[3] << 32, __ATOMIC_RELAXED,
@@ -3280,8 +3318,8 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
                 if (lane < 4) lds.mask.w[lane] = y[0];
             }
             if (has_row(0)) {
-                wait_for(&lds.added[q], 4);
-                lds.shares[q][r] = bytes_dot(lds.rows[q][3 * kRowBlocks + lane].w[r], powers);
+                wait_for_count(&lds.added[q], 4);
+                lds.shares[q][r] = bytes_dot(lds.rows[2 + q][lane].w[r], powers);
             }
         }
     }
