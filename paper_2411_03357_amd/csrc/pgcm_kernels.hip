@@ -3055,9 +3055,10 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
                      (!by_rows && have > 1 && nblk <= (int64_t)(behind + have - 1) << pass_power));
 
     const AadBlocks aad = aad_blocks(cd.aad, cd.aad_len, lds.long_aad + wave);
-    // Decrypting, what is hashed is there before it is deciphered, and of up to two passes in rows half the wavefronts
-    // have none to decipher: those hash the rows meanwhile, a row each.
-    const bool apart = kApart && by_rows && folded <= kFoldPasses / 2 && aad.blocks <= kAadLaneBlocks;
+    // Decrypting, what is hashed is there before it is deciphered, and of two passes in rows half the wavefronts
+    // have none to decipher: those hash the rows meanwhile, a row each.  (A first workgroup has one pass, and no rows, or
+    // a third to spare, and hashes behind the cipher; all others have the launch's two.)
+    const bool apart = kApart && by_rows && folded == kFoldPasses / 2 && aad.blocks <= kAadLaneBlocks;
     const bool hashes = apart && wave >= kWavesPerGroup / 2;
     const uint32_t row_wave = apart ? wave % (kWavesPerGroup / 2) : wave;  // the wavefront's row
     // this lane's block in the pass number m from the end
@@ -3277,7 +3278,8 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
     }
     if constexpr (kApart) {
         if (hashes) {
-            // (the eight are resident together, and each counts itself in before it waits: no wait is for long)
+            // (the eight are resident together, each has a row of the two passes' eight, and each counts itself in before
+            // it waits: no wait is for long)
             auto counted = [&](uint32_t* at) __attribute__((always_inline)) {
                 asm volatile("" ::: "memory");  // (LDS serves a wavefront's accesses in order)
                 if (lane == 0) __hip_atomic_fetch_add(at, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -3294,22 +3296,20 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
                 reinterpret_cast<u32x4*>(lds.fold[1])[i] = f1;
                 reinterpret_cast<u32x4*>(lds.fold[2])[i] = f2;
             }
-            if (has_row(0)) lds.rows[q][r * kRowBlocks + lane] = Block{{row.x0, row.x1, row.x2, row.x3}};
+            lds.rows[q][r * kRowBlocks + lane] = Block{{row.x0, row.x1, row.x2, row.x3}};
             counted(&lds.stored);  // the wavefronts that decipher wait for it as well
             fetch_powers();
-            if (has_row(0)) {
-                uint32_t c[4] = {row.x0, row.x1, row.x2, row.x3};
-                if (r != 3) {
-                    wait_for_count(&lds.stored, kWavesPerGroup / 2);
-                    ghash_mul_lds(lds_offset(lds.fold[2 - r]), c);
-                }
-                uint64_t* const to = reinterpret_cast<uint64_t*>(&lds.rows[2 + q][lane]);
-                __hip_atomic_fetch_xor(to, (uint64_t)c[0] | (uint64_t)c[1] << 32, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_WORKGROUP);
-                __hip_atomic_fetch_xor(to + 1, (uint64_t)c[2] | (uint64_t)c[3] << 32, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_WORKGROUP);
-                counted(&lds.added[q]);
+            uint32_t c[4] = {row.x0, row.x1, row.x2, row.x3};
+            if (r != 3) {
+                wait_for_count(&lds.stored, kWavesPerGroup / 2);
+                ghash_mul_lds(lds_offset(lds.fold[2 - r]), c);
             }
+            uint64_t* const to = reinterpret_cast<uint64_t*>(&lds.rows[2 + q][lane]);
+            __hip_atomic_fetch_xor(to, (uint64_t)c[0] | (uint64_t)c[1] << 32, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+            __hip_atomic_fetch_xor(to + 1, (uint64_t)c[2] | (uint64_t)c[3] << 32, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+            counted(&lds.added[q]);
             // (the last rows' wavefronts, which have nothing to multiply, have this as well)
             if (finisher) prepare();
             if (mask_apart && wave == kWavesPerGroup / 2 + 3) {
@@ -3317,10 +3317,8 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
                 quad_encrypt<2, 1>(keys, lane, lds_base, y);
                 if (lane < 4) lds.mask.w[lane] = y[0];
             }
-            if (has_row(0)) {
-                wait_for_count(&lds.added[q], 4);
-                lds.shares[q][r] = bytes_dot(lds.rows[2 + q][lane].w[r], powers);
-            }
+            wait_for_count(&lds.added[q], 4);
+            lds.shares[q][r] = bytes_dot(lds.rows[2 + q][lane].w[r], powers);
         }
     }
     for (uint32_t q = 0; !by_rows && has_blocks && (q < have || (q == 0 && mask_apart)); ++q) {
