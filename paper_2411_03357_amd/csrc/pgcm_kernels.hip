@@ -2618,8 +2618,7 @@ PGCM_INSTANTIATE_SWAP(true);
 //     priority than theirs (2 MiB decrypted 8.34 -> 8.24, at the same priority 8.38).
 //   * Decrypting, what is hashed is there before it is deciphered.  Of two passes in rows half the wavefronts have
 //     no row, and hash those of the others while these decipher: nothing is left to fold and to add up behind the
-//     cipher (2 MiB 8.35 -> 7.8 us; eight layers of 2 MiB through the pipe and its receiver 136.0 -> 131.3; out of host
-//     memory, whose payload comes too late for it, 51.3 -> 52.2).  They wait for each other by counters in LDS, as a
+//     cipher (2 MiB 8.35 -> 7.8 us; eight layers of 2 MiB through the pipe and its receiver 136.0 -> 131.3).  They wait for each other by counters in LDS, as a
 //     barrier would hold the cipher up.  Neither half goes first: with the cipher ahead the hash ends 1.2 us behind it,
 //     with the hash ahead the cipher ends 1.0 us later.  (Each row from the powers alone, with no tables and nobody to
 //     wait for, is three times the instructions: 8.12.)  Of one pass there is nothing in it, 1 MiB 7.06 and 7.11, and
@@ -2929,6 +2928,28 @@ __device__ __forceinline__ void wait_for_count(uint32_t* at, uint32_t n) {
         __builtin_amdgcn_s_sleep(1);
     asm volatile("" ::: "memory");
 }
+// A row whose blocks come with one load in every lane (of anything, where a lane has no whole block), which is waited for
+// when they are used.
+struct LateRow : RowPayload {
+    u32x4 block;
+
+    __device__ __forceinline__ void arrive() {
+        if (whole) x0 = block.x, x1 = block.y, x2 = block.z, x3 = block.w;
+    }
+};
+// ... or that is taken from LDS, where others have stored it.  (A second read may be one of host memory, 2 MiB out of it
+// 52.2 -> 55.1 us; in place, nothing is overwritten before it is hashed.)
+struct SharedRow : LateRow {
+    const Block* at = nullptr;
+    uint32_t* stored = nullptr;  // wavefronts that have
+
+    __device__ __forceinline__ void arrive() {
+        if (at == nullptr) return LateRow::arrive();
+        wait_for_count(stored, kWavesPerGroup / 2);
+        const Block b = *at;
+        x0 = b.w[0], x1 = b.w[1], x2 = b.w[2], x3 = b.w[3];
+    }
+};
 // how many of the four bytes from `at` on lie before `end`
 __device__ __forceinline__ uint32_t word_bytes(uint64_t at, uint64_t end) {
     return at + 4 <= end ? 4u : at < end ? (uint32_t)(end - at) : 0u;
@@ -3094,45 +3115,63 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
     }
     int64_t blk = have != 0 && has_blocks ? block_of(behind + have - 1) : -lead - 1;
     WordPieces loaded;
-    // (where others hash the row they alone read it, and it is taken from LDS when the keystream is there: a second read
-    // may be one of host memory, 2 MiB out of it 55.1 us, so 52.2; in place, nothing is overwritten before it is hashed)
-    struct SharedRow : RowPayload {
-        const Block* at = nullptr;
-        uint32_t* stored = nullptr;
-        __device__ __forceinline__ void arrive() {
-            if (at == nullptr) return;
-            wait_for_count(stored, kWavesPerGroup / 2);
-            const Block b = *at;
-            x0 = b.w[0], x1 = b.w[1], x2 = b.w[2], x3 = b.w[3];
-        }
-    };
-    std::conditional_t<kApart, SharedRow, RowPayload> row{};
+    // Decrypting, the payload may be in host memory and take longer than all else: it is asked for last, ahead of the
+    // barrier, and nothing else waits for it.  (Its load stands in no branch: behind one, the compiler waits for all loads
+    // where the fold tables are stored, that is for the payload, before the keystream is begun.)  Out of host memory,
+    // asked for first and waited for there, and now: 2 MiB 52.5 -> 48.7 us, 4 of 512 KiB 53.5 -> 50.4, 100 of 20 KiB 50.7 ->
+    // 44.6, 3 MiB 70.3 -> 68.0, 1 MiB 28.4 -> 27.6; in device memory 2 MiB 7.83 -> 7.78, 4 of 512 KiB 8.43 -> 8.50, 3 MiB
+    // 9.88 -> 9.93.  Of those that hash apart, asked for behind the barrier: 7.75 and 8.49, out of host memory 51.3 and
+    // 52.4.  Encrypting, and in sweeps, it is asked for first.
+    constexpr bool kRowLast = kDecrypt && kRows && !kSweep;
+    std::conditional_t<kApart, SharedRow, std::conditional_t<kRowLast, LateRow, RowPayload>> row{};
     bool row_edge = true;
     // this wavefront's row of a sweep, if it has one: of the first sweep's passes some may be missing
     auto has_row = [&](uint32_t sweep) __attribute__((always_inline)) {
         return row_wave < 4 * folded && (sweep > 0 || row_wave / 4 >= sweeps * folded - have);
     };
+    auto place_row = [&](uint32_t sweep) __attribute__((always_inline)) {
+        const uint32_t m1 = behind + folded - row_wave / 4 + kFoldPasses * (sweeps - 1 - sweep);
+        blk = nblk - ((int64_t)m1 << pass_power) + (row_wave & 3) * kRowBlocks + lane;
+        const int64_t first = same_in_all_lanes((uint64_t)(blk - lane));
+        row_edge = first < 0 || first + kRowBlocks == nblk;
+    };
     auto fetch_row = [&](uint32_t sweep) __attribute__((always_inline)) {
-        if (has_row(sweep)) {
-            const uint32_t m1 = behind + folded - row_wave / 4 + kFoldPasses * (sweeps - 1 - sweep);
-            blk = nblk - ((int64_t)m1 << pass_power) + (row_wave & 3) * kRowBlocks + lane;
-            const int64_t first = same_in_all_lanes((uint64_t)(blk - lane));
-            row_edge = first < 0 || first + kRowBlocks == nblk;
-            if constexpr (kApart) {
-                if (apart && !hashes) {
-                    const bool tail = row_edge && blk >= 0 && (uint64_t)blk * 16 + 16 > cd.len;
-                    row.tail = tail ? (uint32_t)(cd.len & 15) : 0;
-                    row.whole = blk >= 0 && row.tail == 0;
-                    row.at = &lds.rows[row_wave / 4][(row_wave & 3) * kRowBlocks + lane];
-                    row.stored = &lds.stored;
-                    return;
+        if constexpr (!kRowLast) {
+            if (!has_row(sweep)) return;
+            place_row(sweep);
+            row = load_row(cd.src, cd.len, blk, row_edge, aad);
+        }
+    };
+    // ... as load_row has it, for kRowLast
+    auto fetch_row_last = [&]() __attribute__((always_inline)) {
+        if constexpr (kRowLast) {
+            const uint8_t* at = reinterpret_cast<const uint8_t*>(kt);
+            if (by_rows && has_row(0)) {
+                place_row(0);
+                row.tail = row_edge && blk >= 0 && (uint64_t)blk * 16 + 16 > cd.len ? (uint32_t)(cd.len & 15) : 0;
+                row.whole = blk >= 0 && row.tail == 0;
+                bool here = true;
+                if constexpr (kApart) {
+                    if (apart && !hashes) {
+                        here = false;
+                        row.at = &lds.rows[row_wave / 4][(row_wave & 3) * kRowBlocks + lane];
+                        row.stored = &lds.stored;
+                    }
+                }
+                if (here && row.whole) {
+                    at = cd.src + blk * 16;
+                } else if (here) {
+                    const Block b = blk < 0 ? aad.at(blk) : read_bytes(cd.src + blk * 16, row.tail);
+                    row.x0 = b.w[0], row.x1 = b.w[1], row.x2 = b.w[2], row.x3 = b.w[3];
                 }
             }
-            static_cast<RowPayload&>(row) = load_row(cd.src, cd.len, blk, row_edge, aad);
+            __builtin_amdgcn_sched_barrier(0);
+            row.block = global_read128(at);
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
     if (by_rows) {
-        if (!hashes) fetch_row(0);  // (those that hash ask for tables first)
+        fetch_row(0);
     } else {
         loaded = load_word(blk);
     }
@@ -3178,12 +3217,18 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
     if constexpr (kRows) {
         if (!apart) fetch_powers(), fetch_fold();
     }
+    u32x4 fold_apart[3];  // an entry of each table
     if constexpr (kApart) {
         if (hashes) {
+            const uint32_t i = tid % kNibbleTableEntries;
+            fold_apart[0] = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower])[i];
+            fold_apart[1] = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower + 1])[i];
+            fold_apart[2] = reinterpret_cast<const u32x4*>(kt->ghash_rows3)[i];
             if (row_wave % 4 == 3) lds.rows[2 + row_wave / 4][lane] = Block{{0, 0, 0, 0}};  // the sum of pass q: rows[2 + q]
             if (tid == kGroupThreads / 2) lds.stored = lds.added[0] = lds.added[1] = 0;
         }
     }
+    fetch_row_last();
     __syncthreads();  // the tables are in place
     if constexpr (kLongIv) j = long_j0;
     QuadKeys keys;
@@ -3285,17 +3330,9 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
                 if (lane == 0) __hip_atomic_fetch_add(at, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             };
             const uint32_t i = tid % kNibbleTableEntries, q = row_wave / 4, r = row_wave % 4;
-            {
-                const u32x4 f0 = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower])[i],
-                            f1 = reinterpret_cast<const u32x4*>(kt->ghash[kRowPower + 1])[i],
-                            f2 = reinterpret_cast<const u32x4*>(kt->ghash_rows3)[i];
-                __builtin_amdgcn_sched_barrier(0);
-                fetch_row(0);  // behind them: it may come from host memory
-                __builtin_amdgcn_sched_barrier(0);
-                reinterpret_cast<u32x4*>(lds.fold[0])[i] = f0;
-                reinterpret_cast<u32x4*>(lds.fold[1])[i] = f1;
-                reinterpret_cast<u32x4*>(lds.fold[2])[i] = f2;
-            }
+#pragma unroll
+            for (int t = 0; t < 3; ++t) reinterpret_cast<u32x4*>(lds.fold[t])[i] = fold_apart[t];
+            row.arrive();
             lds.rows[q][r * kRowBlocks + lane] = Block{{row.x0, row.x1, row.x2, row.x3}};
             counted(&lds.stored);  // the wavefronts that decipher wait for it as well
             fetch_powers();
