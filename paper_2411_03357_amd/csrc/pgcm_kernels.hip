@@ -471,10 +471,10 @@ __device__ __forceinline__ void global_write_block_any(uint8_t* p, const Block& 
 // a rejected chunk), where two L2s holding different dirty versions of a line would leave it to
 // chance which one memory keeps.
 // In launches of a few rows a wavefront, encrypting ones write rows of whole lines like this as well (others, whose
-// neighbours' parts of a line an L2 puts together, come to host memory 3 % later, 2 of 3 to 4 MB 144.7 us -> 149.0): what is left in the L2s
-// is written back when a kernel ends, with nothing else going on (2 MiB 8.47 -> 8.23 us, 8 x 512 KiB both ways 24.1 ->
-// 23.8, 12 MiB 23.8 -> 22.7, 28 MB in units 47.3 -> 46.3, sixteen blocks of 320 KiB into host memory 108.6 -> 106.8;
-// but 64 x 4 KiB, in quads, 12.4 -> 12.5, and 2000 chunks of 16 KiB to 8 MiB in spans 2815 -> 2833).
+// neighbours' parts of a line an L2 puts together, come to host memory 3 % later, 2 of 3 to 4 MB 144.7 us -> 149.0; of sweeps
+// see sweep_through): what is left in the L2s is written back when a kernel ends, with nothing else going on (2 MiB 8.47 ->
+// 8.23 us, 8 x 512 KiB both ways 24.1 -> 23.8, 28 MB in units 47.3 -> 46.3; but 64 x 4 KiB, in quads, 12.4 -> 12.5, and 2000
+// chunks of 16 KiB to 8 MiB in spans 2815 -> 2833).
 // (A store of more than 64 bits still reads its registers when the next instruction issues: the next
 // two must not write them, and only in code of its own does the compiler see to that.)
 __device__ __forceinline__ void global_write128_through(uint8_t* p, u32x4 v) {
@@ -3295,7 +3295,9 @@ __global__ __launch_bounds__(kKind == BurstKind::kWords         ? kGroupThreads 
                 GhashNone G;
                 const CtrBlock C{j.w[0], j.w[1], j.w[2], (uint32_t)blk + first_ctr};
                 bulk_row<kDecrypt, 0, kDecrypt>(LaneKeys{key_word, meta.rounds()}, A, C, row, cd.dst, blk,
-                                                row_edge, keep_mask, lds_base, G, through);
+                                                row_edge, keep_mask, lds_base, G,
+                                                through && (!kSweep || kDecrypt ||
+                                                            sweep_through(meta.unit_power(), sweep, sweeps)));
 #pragma unroll
                 for (int k = 0; k < 4; ++k) y[k] ^= G.w[k];
             };

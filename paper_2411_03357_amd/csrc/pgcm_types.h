@@ -198,6 +198,16 @@ constexpr uint32_t wave_of_lead(uint32_t nblk, uint32_t behind, uint32_t folded)
     const uint32_t pass = nblk / 256, at = 255 - nblk % 256;  // number from the end, and the block's place in it
     return 4 * ((behind + folded - 1 - pass) % kFoldPasses) + at / 64;
 }
+// Encrypting in sweeps, are the rows of this one written through to memory?  A sweep's payload is asked for behind the
+// stores of the one before, and waits for them, which takes long if they go out to host memory: only the last sweep's
+// are, and none where each workgroup makes one sweep but for the passes that a chunk's first has to spare.  Into host
+// memory, none written through, all, and so: 12 MiB 236.2, 242.0, 234.4 us, 7 MiB 147, 148, 138, 8 MiB 167.9, 166.4, 157.7,
+// sixteen of 320 KiB 108.9, 106.6, 103.7, five of 1 to 3 MB 161, 149.6, 153.3, 4 MiB with AAD 86.8, 88.7, 86.6 (the last
+// sweep's there 87.7).  In device memory 12 MiB 23.9, 22.8, 23.3, 8 MiB 18.9, 17.9, 18.1, four of 2 MiB 19.0, 17.9, 18.4,
+// 4 MiB with AAD 16.0, 15.4, 15.8.
+constexpr bool sweep_through(uint32_t passes_each, uint32_t sweep, uint32_t sweeps) {
+    return passes_each > kFoldPasses && sweep + 1 == sweeps;
+}
 enum class BurstKind { kWords, kFold, kSweep, kFoldShared, kWordsShared, kFoldApart };
 // Workgroups of a chunk (KeyTables::hop has their distances) and of a launch.
 constexpr uint32_t kSwapChunkGroups = kHopEntries;
