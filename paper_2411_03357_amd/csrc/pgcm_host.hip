@@ -729,8 +729,9 @@ void launch_burst(const pgcm_key* key, const BatchArgs& a, const SwapShape& shap
     const bool more = kind == BurstKind::kWords &&
                       (std::is_same_v<Args, ArgOne> || shape.groups <= (uint32_t)key->num_cu);
     const dim3 grid(shape.groups), block(64u * ((1u << shape.wave_power) + more));
+    const bool in_place = a.host_ivs && std::is_same_v<Args, ArgOne>;
     const SwapMeta meta = swap_meta(nchunks, shape.unit_power, shape.wave_power, shape.alone, a.order == nullptr,
-                                    shape.groups, (uint32_t)key->rounds);
+                                    shape.groups, (uint32_t)key->rounds, in_place);
     auto burst = [&](auto of) {
         constexpr BurstKind kKind = decltype(of)::value;
         const bool long_iv = a.iv_len > kShortIvBytes;
@@ -755,7 +756,7 @@ void launch_burst(const pgcm_key* key, const BatchArgs& a, const SwapShape& shap
     const size_t first = std::is_same_v<Args, ArgOne> ? a.at(0) : 0;
     const uint8_t* ivs = a.ivs + first * a.iv_len;
     uint32_t iv_len = a.iv_len;
-    if (meta.iv_in_place() && std::is_same_v<Args, ArgOne>) {
+    if (in_place) {
         uint64_t words;
         memcpy(&iv_len, ivs + 8, 4);
         memcpy(&words, ivs, 8);
@@ -845,7 +846,7 @@ int run_one_launch(pgcm_key* key, Context* ctx, const BatchArgs& a, const SwapSh
     if (!shape.burst)
         launch_swap(key, a, shape, done, batch, h_groups, slots);
     else if (one)
-        launch_burst(key, a, shape, done, a.host_ivs ? 0 : 1, only, slots);  // (SwapMeta::iv_in_place)
+        launch_burst(key, a, shape, done, 1, only, slots);
     else if (in_args)
         launch_burst(key, a, shape, done, (uint32_t)a.n, batch, slots);
     else

@@ -232,22 +232,22 @@ struct SwapMeta {
 #define PGCM_BOTH
 #endif
     PGCM_BOTH uint32_t nchunks() const { return w & 0x7Fu; }          // in an ArgBatch: 0 .. 64
-    PGCM_BOTH bool iv_in_place() const { return nchunks() == 0; }     // with an ArgOne: `ivs` and `iv_len` are no
-                                                                      // pointer and length but the IV's 96 bits
     PGCM_BOTH uint32_t unit_power() const { return (w >> 7) & 0x1Fu; }  // burst_kernel: the passes
     PGCM_BOTH uint32_t wave_power() const { return (w >> 12) & 7u; }  // log2 of the wavefronts per
                                                                       // workgroup: 2, 3, 4
     PGCM_BOTH bool one_group_each() const { return (w >> 15) & 1u; }  // every chunk has a workgroup
     PGCM_BOTH bool in_order() const { return (w >> 16) & 1u; }        // chunk k is the caller's k
     PGCM_BOTH uint32_t groups() const { return (w >> 17) & 0x3FFu; }  // workgroups of the launch
-    PGCM_BOTH uint32_t rounds() const { return w >> 27; }
+    PGCM_BOTH uint32_t rounds() const { return (w >> 27) & 0xFu; }
+    PGCM_BOTH bool iv_in_place() const { return w >> 31; }  // `ivs` and `iv_len` are no pointer and length but
+                                                            // the 96 bits of the IV of an ArgOne
 #undef PGCM_BOTH
 };
 constexpr SwapMeta swap_meta(uint32_t nchunks, uint32_t unit_power, uint32_t wave_power,
                              bool one_group_each, bool in_order, uint32_t groups,
-                             uint32_t rounds) {
+                             uint32_t rounds, bool iv_in_place = false) {
     return SwapMeta{nchunks | unit_power << 7 | wave_power << 12 | (uint32_t)one_group_each << 15 |
-                    (uint32_t)in_order << 16 | groups << 17 | rounds << 27};
+                    (uint32_t)in_order << 16 | groups << 17 | rounds << 27 | (uint32_t)iv_in_place << 31};
 }
 // Batches of more chunks than fit the arguments have a descriptor per workgroup in pinned memory.
 struct alignas(64) GroupDesc {   // one line of host memory

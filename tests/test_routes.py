@@ -3,6 +3,7 @@
 the passes of a chunk's first workgroup are told apart, of swap_kernel the bytes of a unit."""
 import os
 import subprocess
+import tempfile
 
 import numpy as np
 import pytest
@@ -155,3 +156,37 @@ def test_long_aad_in_every_place(kernels_of):
     got = kernels_of([(lens, np.resize(test_gpu_long_aad.AADS, len(lens)), unit_bytes, one_launch)
                       for lens, unit_bytes, one_launch, _ in shapes.values()])
     assert dict(zip(shapes, got)) == {name: s[3] for name, s in shapes.items()}
+
+
+def test_what_a_launch_says_of_itself():
+    """every field of the word is what was put in, whatever the others are: above all, only a launch that has its IV in
+    place says so, and none whose descriptors are staged, which has no chunks in its arguments either"""
+    code = """
+#include <initializer_list>
+#include "pgcm_types.h"
+using namespace pgcm;
+bool all() {
+    for (uint32_t chunks : {0u, 1u, 64u})
+        for (uint32_t power : {1u, 16u})
+            for (uint32_t waves : {2u, 4u})
+                for (uint32_t groups : {1u, 512u})
+                    for (uint32_t rounds : {10u, 12u, 14u})
+                        for (uint32_t bits = 0; bits < 8; ++bits) {
+                            const bool each = bits & 1, order = bits & 2, iv = bits & 4;
+                            const SwapMeta m = swap_meta(chunks, power, waves, each, order, groups, rounds, iv);
+                            if (m.nchunks() != chunks || m.unit_power() != power || m.wave_power() != waves ||
+                                m.groups() != groups || m.rounds() != rounds || m.one_group_each() != each ||
+                                m.in_order() != order || m.iv_in_place() != iv)
+                                return false;
+                        }
+    return true;
+}
+int main() { return all() && !swap_meta(0, 1, 2, true, true, 65, 14).iv_in_place() ? 0 : 1; }
+"""
+    with tempfile.TemporaryDirectory() as d:
+        exe = os.path.join(d, "meta")
+        out = subprocess.run(["g++"] + SAN + ["-std=c++17", "-x", "c++", "-", "-o", exe,
+                                              "-I" + os.path.join(ROOT, "paper_2411_03357_amd", "csrc")], input=code,
+                             stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        assert out.returncode == 0, out.stdout
+        assert subprocess.run([exe], env=ENV).returncode == 0
