@@ -238,3 +238,99 @@ def test_pipe_object_drives_the_batch_calls(kind, noise):
     rx.rx.destroy()
     rx.key.free()
     key.free()
+
+
+# single chunks whose IV travels in the kernel's arguments, one of each kind of launch that takes one
+IN_ARGUMENTS = (1, 320 * 1024, 1 << 20, 2 << 20, (12 << 20) - 5)
+
+
+def _number_0(carry, iv_start, seed):
+    """IV_0, no byte of it zero or like another's by rule, with which the IV's low `carry` bits are all ones two transfers
+    after iv_start"""
+    rng = np.random.default_rng(seed)
+    high = int.from_bytes(rng.integers(1, 256, 12, dtype=np.uint8).tobytes(), "big") >> carry << carry
+    return ((high | ((1 << carry) - 1)) - 2 - iv_start) % (1 << 96)
+
+
+class _At:
+    """device memory as an array"""
+
+    def __init__(self, at, length):
+        self.__cuda_array_interface__ = {"shape": (length,), "typestr": "|u1", "data": (at, False), "version": 2}
+
+
+@pytest.mark.parametrize("carry,key_bytes", [(32, 32), (64, 16)])
+def test_the_pipe_encrypts_under_the_iv_of_the_transfer(carry, key_bytes):
+    """whatever is delivered, made ahead of demand or just now, is the oracle's ciphertext and tag under IV_0 + its number,
+    across the carry into the next words"""
+    start = (1 << 40) + 77
+    iv0 = _number_0(carry, start, 31 + carry)
+    rng = np.random.default_rng(32 + carry)
+    keyb = rng.integers(0, 256, key_bytes, dtype=np.uint8)
+    key = pgcm.expand_key_bytes(keyb.tobytes())
+    mem = [torch.from_numpy(rng.integers(0, 256, n, dtype=np.uint8)).cuda() for n in IN_ARGUMENTS]
+    got = []
+
+    def deliver(kind, addr, length, iv, ct, tag, stream):
+        torch.cuda.synchronize()
+        got.append((kind, addr, iv, torch.as_tensor(_At(ct, length), device="cuda").cpu().numpy().tobytes(),
+                    torch.as_tensor(_At(tag, 16), device="cuda").cpu().numpy().tobytes()))
+
+    pipe = pgcm.Pipe(key, iv0.to_bytes(12, "big"), deliver, depth=1, iv_start=start, max_chunk_bytes=max(IN_ARGUMENTS))
+    for _ in range(3):
+        for t in mem:
+            pipe.request(t.data_ptr(), t.numel())
+            pipe.sync()
+    pipe.destroy()
+    payload = {t.data_ptr(): t.cpu().numpy() for t in mem}
+    for k, (kind, addr, iv, ct, tag) in enumerate(got):
+        assert iv == start + k
+        want = oracle.encrypt(keyb, ((iv0 + iv) % (1 << 96)).to_bytes(12, "big"), b"",
+                              np.zeros(1, np.uint8) if kind == "nop" else payload[addr])
+        assert (ct, tag) == want, (k, kind, len(ct))
+    assert [g[1] for g in got if g[0] != "nop"] == [t.data_ptr() for t in mem] * 3
+    assert {g[0] for g in got} >= {"send", "now"}
+    key.free()
+
+
+@pytest.mark.parametrize("carry,key_bytes", [(32, 16), (64, 32)])
+def test_the_receiver_decrypts_under_the_iv_it_counts_to(carry, key_bytes):
+    """the oracle's ciphertexts are accepted in their order and recovered; delivered a second time, or made under an IV
+    that differs in one bit of any byte, they are rejected"""
+    start = 5
+    iv0 = _number_0(carry, start, 41 + carry)
+    rng = np.random.default_rng(42 + carry)
+    keyb = rng.integers(0, 256, key_bytes, dtype=np.uint8)
+    key = pgcm.expand_key_bytes(keyb.tobytes())
+    rx = pgcm.Receiver(key, iv0.to_bytes(12, "big"), start)
+
+    def accept(plain, iv):
+        ct, tag = oracle.encrypt(keyb, iv, b"", plain)
+        src = torch.from_numpy(np.frombuffer(ct, np.uint8).copy()).cuda()
+        out = torch.full((plain.size,), 0xDD, dtype=torch.uint8, device="cuda")
+        ok = torch.full((1,), 9, dtype=torch.uint8, device="cuda")
+        tag = torch.from_numpy(np.frombuffer(tag, np.uint8).copy()).cuda()
+        rx.accept(src, plain.size, tag, out, ok)
+        torch.cuda.synchronize()
+        return int(ok.item()), out.cpu().numpy()
+
+    def expected():
+        return ((iv0 + rx.next_iv) % (1 << 96)).to_bytes(12, "big")
+
+    for n in IN_ARGUMENTS:
+        plain = rng.integers(1, 256, n, dtype=np.uint8)
+        iv = expected()
+        ok, out = accept(plain, iv)
+        assert ok == 1 and np.array_equal(out, plain), n
+        ok, out = accept(plain, iv)             # the same ciphertext and tag again
+        assert ok == 0 and not out.any(), n
+    plain = rng.integers(1, 256, 320, dtype=np.uint8)
+    for byte in range(12):
+        iv = bytearray(expected())
+        iv[byte] ^= 1 << byte % 8
+        ok, out = accept(plain, bytes(iv))
+        assert ok == 0 and not out.any(), byte
+    assert accept(plain, expected())[0] == 1
+    assert rx.next_iv == start + 2 * len(IN_ARGUMENTS) + 13
+    rx.destroy()
+    key.free()
