@@ -144,7 +144,77 @@ def test_workgroups_with_and_without_a_wavefront_more(n, longest, iv_bytes):
     _full_parity(w, flip=[(0, 3, 1, "tag"), (1, 0, 5, "tag"), (n - 1, 9, 2, "tag")])
 
 
-# one and two passes of 256 blocks a workgroup, whose rows are hashed by wavefronts of their own when decrypting: whole,
+# chunks of at most 64 blocks, AAD included, and of at most 128: (longest, AAD lengths, wavefronts with blocks)
+MORE = {"four": (1024 - 48, [0, 16, 5, 33], 4), "four_aad": (0, [1008], 4), "eight": (2048 - 48, [0, 16, 5, 33], 8),
+        "eight_aad": (1040, [1008, 0, 1000], 8)}
+
+
+def more(n, shape):
+    """n such chunks, each in one workgroup: the longest among them, if there is payload at all"""
+    longest, alens, waves = MORE[shape]
+    lens = [longest, 0, min(longest, 1), max(longest - 16, 0), longest // 2 + 5 if longest else 0]
+    return np.resize(lens, n), np.resize(alens, n), waves
+
+
+@pytest.mark.parametrize("iv_bytes", (12, 40))
+@pytest.mark.parametrize("shape", MORE)
+@pytest.mark.parametrize("n", (65, 255, 256, 257, 512))
+def test_workgroups_of_four_and_of_eight(n, shape, iv_bytes):
+    """up to a workgroup for each compute unit has a wavefront more than its blocks need, beyond that none, whose blocks
+    make E_K(J0) as well"""
+    lens, alens, _ = more(n, shape)
+    _full_parity(_workload("of_%s" % shape, lens, alens, iv_bytes=iv_bytes),
+                 flip=[(0, 3, 1, "tag"), (2, 0, 5, "tag"), (n - 1, 9, 2, "tag")])
+
+
+# workgroups of sixteen wavefronts, some of two passes in rows, which others hash meanwhile when decrypting, and some of one,
+# in quads; "spare": chunks' first workgroups make up to three and hash behind the cipher.  65 chunks and more have their
+# descriptors in pinned memory.
+APART = {
+    "halves": ([400 * 4096 + 17, 4096, 100 * 4096 - 15, 1], [16, 0, 33]),
+    "halves_long_aad": ([400 * 4096 - 50 * 16], [3000]),
+    "spare": ([512 * 4096 - 48 * 16], [1008]),
+    "spare_some": ([100 * 4096 + 1, 103 * 4096 - 16, 150 * 4096, 155 * 4096 - 5, 4096], [0, 16, 1008]),
+    "staged": ([6 * 4096 - 16 * (i % 3) - i % 2 for i in range(80)], [0, 16, 5]),
+    "staged_spare": ([5 * 4096 - 16 * (i % 3) - i % 2 for i in range(100)], [0, 16, 5]),
+}
+
+
+@pytest.mark.parametrize("in_place", (False, True))
+@pytest.mark.parametrize("key_bytes,iv_bytes", [(32, 12), (24, 40)])
+@pytest.mark.parametrize("shape", APART)
+def test_some_rows_hashed_apart(shape, key_bytes, iv_bytes, in_place):
+    """with nothing changed, and with a bit of the first, a middle and the last chunk: in the first workgroup, which may
+    be the one of fewer or more passes, half way and in the last block"""
+    lens, alens = APART[shape]
+    w = _workload("some_%s" % shape, lens, alens, key_bytes, iv_bytes)
+    host = w.payload_host()
+    srcs = [w.chunk(host, i) for i in range(w.n)]
+    aads = [np.frombuffer(w.aad_of(i), np.uint8) for i in range(w.n)]
+    cts, tags, _ = oracle.encrypt_batch(w.key, w.ivs, aads, srcs, nthreads=8)
+    wire = np.zeros_like(host)
+    for i in range(w.n):
+        w.chunk(wire, i)[:] = cts[i]
+    key = pgcm.expand_key_bytes(w.key.tobytes())
+    b = DeviceBatch(w, torch.from_numpy(host).cuda())
+    b.tags.copy_(torch.from_numpy(np.ascontiguousarray(tags).reshape(-1)))
+    for at in (None, 0.0, 0.5, 1.0):
+        flipped = set() if at is None else {0, w.n // 2, w.n - 1}
+        sent = wire.copy()
+        for i in flipped:
+            w.chunk(sent, i)[int(at * (lens[i] - 1))] ^= 32
+        b.cipher.copy_(torch.from_numpy(sent))
+        out = b.cipher if in_place else b.back
+        b.decrypt(key, dst=out)
+        torch.cuda.synchronize()
+        got, ok = out.cpu().numpy(), b.ok.cpu().tolist()
+        for i in range(w.n):
+            assert ok[i] == (i not in flipped), (at, i)
+            assert np.array_equal(w.chunk(got, i), np.zeros_like(srcs[i]) if i in flipped else srcs[i]), (at, i)
+    key.free()
+
+
+# one pass of 256 blocks a workgroup, and two, whose rows are hashed by wavefronts of their own when decrypting: whole,
 # short, ragged, with AAD in lanes of the first row, of a pass of its own, and too long for lanes
 _HASHED_APART = {
     "one": ([1 << 20], [0]), "one_short": ([(1 << 20) - 65 * 16 - 3], [33]),
