@@ -724,10 +724,8 @@ void use_slots(Context* ctx, size_t n, hipStream_t stream, bool capturing) {
 template <class Args>
 void launch_burst(const pgcm_key* key, const BatchArgs& a, const SwapShape& shape, hipEvent_t done, uint32_t nchunks,
                   const Args& args, ArriveSlot* slots) {
-    const BurstKind kind = burst_kind(shape, (uint32_t)key->num_cu);
-    // a wavefront beyond those with blocks, where every workgroup has a compute unit (one chunk's always have)
-    const bool more = kind == BurstKind::kWords &&
-                      (std::is_same_v<Args, ArgOne> || shape.groups <= (uint32_t)key->num_cu);
+    const BurstKind kind = burst_kind(shape, (uint32_t)key->num_cu, a.decrypt);
+    const bool more = kind == BurstKind::kWords;
     const dim3 grid(shape.groups), block(64u * ((1u << shape.wave_power) + more));
     const bool in_place = a.host_ivs && std::is_same_v<Args, ArgOne>;
     const SwapMeta meta = swap_meta(nchunks, shape.unit_power, shape.wave_power, shape.alone, a.order == nullptr,
@@ -741,16 +739,19 @@ void launch_burst(const pgcm_key* key, const BatchArgs& a, const SwapShape& shap
                 kernel = long_iv ? burst_kernel<false, true, kKind, Args> : burst_kernel<false, false, kKind, Args>;
         return kernel;
     };
-    auto* kernel = kind == BurstKind::kWords  ? burst(std::integral_constant<BurstKind, BurstKind::kWords>{})
-                   : kind == BurstKind::kFold ? burst(std::integral_constant<BurstKind, BurstKind::kFold>{})
-                                              : burst(std::integral_constant<BurstKind, BurstKind::kSweep>{});
-    if (kind == BurstKind::kFold && a.decrypt && shape.unit_power == 2)  // (see there)
-        kernel = burst(std::integral_constant<BurstKind, BurstKind::kFoldApart>{});
-    if constexpr (!std::is_same_v<Args, ArgOne>) {
-        if (kind == BurstKind::kFoldShared)
-            kernel = burst(std::integral_constant<BurstKind, BurstKind::kFoldShared>{});
-        if (kind == BurstKind::kWords && !more)
-            kernel = burst(std::integral_constant<BurstKind, BurstKind::kWordsShared>{});
+    decltype(burst(std::integral_constant<BurstKind, BurstKind::kWords>{})) kernel = nullptr;
+    switch (kind) {
+        case BurstKind::kWords: kernel = burst(std::integral_constant<BurstKind, BurstKind::kWords>{}); break;
+        case BurstKind::kFold: kernel = burst(std::integral_constant<BurstKind, BurstKind::kFold>{}); break;
+        case BurstKind::kFoldApart: kernel = burst(std::integral_constant<BurstKind, BurstKind::kFoldApart>{}); break;
+        case BurstKind::kSweep: kernel = burst(std::integral_constant<BurstKind, BurstKind::kSweep>{}); break;
+        case BurstKind::kFoldShared:
+        case BurstKind::kWordsShared:
+            if constexpr (!std::is_same_v<Args, ArgOne>)
+                kernel = kind == BurstKind::kFoldShared
+                             ? burst(std::integral_constant<BurstKind, BurstKind::kFoldShared>{})
+                             : burst(std::integral_constant<BurstKind, BurstKind::kWordsShared>{});
+            break;
     }
     // one chunk: its place in the caller's arrays is in the pointers
     const size_t first = std::is_same_v<Args, ArgOne> ? a.at(0) : 0;

@@ -62,11 +62,15 @@ inline Route route_batch(const ShapeBatch& a, const RouteOptions& o, const Batch
     return v.all_one_row() ? Route::kOneRow : spans ? Route::kSpans : Route::kUnits;
 }
 
-inline BurstKind burst_kind(const SwapShape& s, uint32_t num_cu) {
-    return s.wave_power < 4                       ? BurstKind::kWords
-           : s.groups > num_cu                    ? BurstKind::kFoldShared
-           : s.unit_power + s.spare > kFoldPasses ? BurstKind::kSweep
-                                                  : BurstKind::kFold;
+// Up to eight wavefronts with blocks have one more that has none, where no two workgroups share a compute unit; what
+// decrypts in two passes of sixteen hashes them beside the cipher (see burst_kernel).  One chunk, whose workgroups have
+// a compute unit each, never takes a shared kind.
+inline BurstKind burst_kind(const SwapShape& s, uint32_t num_cu, bool decrypt) {
+    const bool shared = s.groups > num_cu;
+    if (s.wave_power < 4) return shared ? BurstKind::kWordsShared : BurstKind::kWords;
+    if (shared) return BurstKind::kFoldShared;
+    if (s.unit_power + s.spare > kFoldPasses) return BurstKind::kSweep;
+    return decrypt && s.unit_power == 2 ? BurstKind::kFoldApart : BurstKind::kFold;
 }
 
 }  // namespace pgcm

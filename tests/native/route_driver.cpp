@@ -1,6 +1,7 @@
 // Reads batches, a line each: compute units, one launch (0, 1), matrix hash, forced unit bytes, 1 for
 // fixed buffers, 2 if captured or 3 where the stream's context was and the stream has no slots for short chunks, then
-// for every chunk its length and its AAD's.  Prints which kernel takes each.
+// for every chunk its length and its AAD's.  Prints which kernel takes each; called with "enc" or "dec", of those that
+// burst_kernel takes the instance that this direction has, and the wavefronts of its workgroups that have blocks.
 // Test infrastructure.
 #include <cstdint>
 #include <iostream>
@@ -12,7 +13,20 @@
 
 using namespace pgcm;
 
-int main() {
+const char* instance(BurstKind k) {
+    switch (k) {
+        case BurstKind::kWords: return "words";
+        case BurstKind::kWordsShared: return "words_shared";
+        case BurstKind::kFold: return "fold";
+        case BurstKind::kFoldApart: return "fold_apart";
+        case BurstKind::kFoldShared: return "fold_shared";
+        case BurstKind::kSweep: return "sweep";
+    }
+    return "none";
+}
+
+int main(int argc, char** argv) {
+    const std::string direction = argc > 1 ? argv[1] : "";
     std::string line;
     while (std::getline(std::cin, line)) {
         std::istringstream in(line);
@@ -37,8 +51,14 @@ int main() {
                     std::cout << "swap " << (16u << s.unit_power) << "\n";
                     break;
                 }
-                switch (burst_kind(s, num_cu)) {
-                    case BurstKind::kWords: std::cout << "words\n"; break;
+                if (!direction.empty()) {
+                    std::cout << instance(burst_kind(s, num_cu, direction == "dec")) << " " << (1u << s.wave_power) << "\n";
+                    break;
+                }
+                switch (burst_kind(s, num_cu, false)) {
+                    case BurstKind::kWords:
+                    case BurstKind::kWordsShared: std::cout << "words\n"; break;
+                    case BurstKind::kFoldApart:
                     case BurstKind::kFold: std::cout << "fold " << s.unit_power + s.spare << "\n"; break;
                     case BurstKind::kSweep: std::cout << "sweep " << s.unit_power + s.spare << "\n"; break;
                     case BurstKind::kFoldShared: std::cout << (s.alone ? "shared\n" : "shared apart\n"); break;

@@ -12,6 +12,7 @@ import test_gpu_bursts
 import test_gpu_graphs
 import test_gpu_long_aad
 import test_gpu_parity
+import test_gpu_pipeline
 import test_gpu_ragged_ends
 import test_gpu_random_batches
 import test_gpu_reservations
@@ -30,14 +31,15 @@ def kernels_of(tmp_path_factory):
                            stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert build.returncode == 0, build.stdout
 
-    def run(batches):
+    def run(batches, direction=None):
         """batches: (lengths, AAD lengths, forced unit bytes, one launch[, 1: fixed buffers, 2: captured, 3: on a
-        stream that has no slots for short chunks, and whose context was captured])"""
+        stream that has no slots for short chunks, and whose context was captured]); direction "enc" or "dec": of what
+        burst_kernel takes, its instance and the wavefronts of a workgroup that have blocks"""
         lines = []
         for lens, alens, unit_bytes, one_launch, *fixed in batches:
             lines.append("256 %d 0 %d %d " % (one_launch, unit_bytes, fixed[0] if fixed else 0) +
                          " ".join("%d %d" % (n, a) for n, a in zip(lens, alens)))
-        out = subprocess.run([exe], input="\n".join(lines) + "\n", stdout=subprocess.PIPE,
+        out = subprocess.run([exe] + ([direction] if direction else []), input="\n".join(lines) + "\n", stdout=subprocess.PIPE,
                              stderr=subprocess.PIPE, text=True, env=ENV)
         assert out.returncode == 0, out.stderr
         return out.stdout.split("\n")[:-1]
@@ -93,6 +95,26 @@ def test_bursts(kernels_of):
     assert kernels_of([(*apart, 0, 1, 2), (*apart, 0, 1, 3), (*apart, 0, 1, 1)]) == ["shared apart"] + ["shared"] * 2
     assert {got[n] for n in ("many_even", "many_long")} == {"shared"}
     assert {got[n] for n in ("many_apart", "many_apart_512")} == {"shared apart"} and got["many_apart_513"] == "shared"
+
+
+def test_burst_instances(kernels_of):
+    """which instance of burst_kernel takes a batch, where that goes by the workgroups of a compute unit or by the direction"""
+    for n, shape in ((n, s) for n in (1, 64, 65, 255, 256, 257, 512) for s in test_gpu_bursts.MORE):
+        lens, alens, waves = test_gpu_bursts.more(n, shape)
+        for direction in ("enc", "dec"):
+            got, = kernels_of([(lens, alens, 0, 1)], direction)
+            assert got == "%s %d" % ("words" if n <= 256 else "words_shared", waves), (n, shape, got)
+    for name, (lens, alens) in test_gpu_bursts.APART.items():
+        batch = [(lens, np.resize(alens, len(lens)), 0, 1)]
+        assert kernels_of(batch, "dec") == ["fold_apart 16"] and kernels_of(batch, "enc") == ["fold 16"], name
+        spare = "spare" in name
+        assert kernels_of(batch) == ["fold %d" % (3 if spare else 2)], name
+    passes = {name: kernels_of([(*test_gpu_bursts.SHAPES[name], 0, 1)], "dec") for name in ("fold_1_most", "passes_3")}
+    assert passes == {"fold_1_most": ["fold 16"], "passes_3": ["fold 16"]}
+    # what goes through the pipe and its receiver with the IV in the arguments: one chunk of each kind that there is
+    sizes = [([n], [0], 0, 1) for n in test_gpu_pipeline.IN_ARGUMENTS]
+    assert kernels_of(sizes, "enc") == ["words 4", "words 8", "fold 16", "fold 16", "sweep 16"]
+    assert kernels_of(sizes, "dec") == ["words 4", "words 8", "fold 16", "fold_apart 16", "sweep 16"]
 
 
 def test_units_in_one_launch(kernels_of):
