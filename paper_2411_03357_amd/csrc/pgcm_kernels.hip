@@ -2613,9 +2613,13 @@ PGCM_INSTANTIATE_SWAP(true);
 //   * What the end of a workgroup needs besides its sum, the power of H that takes it to the chunk's end with x^8,
 //     x^16, .. of it, the length block's product, E_K(J0), is made by a wavefront that has no blocks, while the others
 //     are at theirs: one more than they are where at most eight have blocks and a compute unit has one workgroup (one
-//     block of 320 KiB 6.42 -> 5.94 us; where two share one, 413 workgroups of nine wavefronts were no longer all
-//     resident: 300 of up to 8 KiB decrypted 9.7 -> 11.6), or the last where rows are taken and it has none, at lower
+//     block of 320 KiB 6.42 -> 5.94 us), or the last where rows are taken and it has none, at lower
 //     priority than theirs (2 MiB decrypted 8.34 -> 8.24, at the same priority 8.38).
+//     Where two share a compute unit there is none more (kWordsShared): with nine wavefronts the second begins when the
+//     first has ended, 5.2 us on (300 of up to 8 KiB decrypted 8.9 -> 11.9, 512 of 1900 bytes 8.5 -> 11.9, 257 of them 7.2 ->
+//     10.7).  They use 62 to 64 registers and are given 88 (with long IVs 91 and 96), as the compiler sees that LDS leaves a
+//     SIMD five wavefronts and has no use for less; of nine, three are on one SIMD, and six would need 528 of its 512.  With
+//     five wavefronts instead of four they do fit, and 300 to 512 chunks of 976 bytes gain nothing by it (7.0 and 7.1).
 //   * Decrypting, what is hashed is there before it is deciphered.  Of two passes in rows half the wavefronts have
 //     no row, and hash those of the others while these decipher: nothing is left to fold and to add up behind the
 //     cipher (2 MiB 8.35 -> 7.8 us; eight layers of 2 MiB through the pipe and its receiver 136.0 -> 131.3).  They wait for each other by counters in LDS, as a

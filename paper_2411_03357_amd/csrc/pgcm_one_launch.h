@@ -101,11 +101,12 @@ inline bool first_burst_choice(uint64_t passes, size_t n, uint64_t most, Groups 
 // Passes of 64 blocks, or of 128, if no workgroup has to make more than one.  Their workgroups multiply every
 // word by its own power and have no rows to fold, and four or eight wavefronts bring the tables in and make
 // their blocks sooner than sixteen do.  Of 64 where there are compute units for them, unless only of 128 a
-// chunk's shares are added up in one set (kArriveSet; 40 KiB in 20 workgroups 6.25 us, in 40 6.46).  Per call,
-// passes of 256, 128 and 64 blocks: 16 KiB 6.8, 6.3, 5.9; 96 KiB 7.0, 6.9, 6.4; 250 KiB 7.5, 6.9, 6.4; 16 of
-// 12 KiB 7.5, 6.9, 6.3; 320 KiB 7.5, 6.9; 20 of 20 KiB 7.5, 7.0; three of 100 KiB, which 256 blocks have in one
-// set each, 7.5, 7.3.  A first workgroup with a pass more, two passes of 128 blocks (320 KiB 8.4, 700 KiB 8.8
-// instead of 7.6) and two workgroups on a compute unit (10 of 90 KiB 10.2 instead of 7.6) are all longer.
+// chunk's shares are added up in one set (kArriveSet; 40 KiB in 20 workgroups 5.52 us, in 40 5.66).  Per call,
+// passes of 256, 128 and 64 blocks: 16 KiB 6.4, 5.5, 5.1; 96 KiB 6.6, 5.9, 5.6; 250 KiB 7.0, 5.9, 5.6; 16 of
+// 12 KiB 7.4, 6.9, 6.2; 320 KiB 7.1, 6.0; 20 of 20 KiB 7.4, 6.9; three of 100 KiB, which 256 blocks have in one
+// set each, 7.2, 7.1.  Two workgroups on a compute unit are longer (10 of 90 KiB 8.8 instead of 7.2, three of 256 KiB 8.8
+// instead of 7.8, two of 450 KiB 8.6 instead of 7.5), and were so, as a first workgroup with a pass more and two passes of
+// 128 blocks (320 KiB 8.4, 700 KiB 8.8 instead of 7.6), when up to eight wavefronts had two round tables to bring in.
 inline bool one_pass_each(const ShapeBatch& a, uint32_t most, SwapShape* shape) {
     uint64_t total[2] = {0, 0}, longest[2] = {0, 0};
     for (size_t k = 0; k < a.n; ++k) {
@@ -127,20 +128,24 @@ inline bool one_pass_each(const ShapeBatch& a, uint32_t most, SwapShape* shape) 
 // As long as there is a compute unit for every short chunk, a workgroup takes a whole one, with no
 // more wavefronts than it has blocks for.  Up to kArgChunks of them, one longer than a pass of 256 blocks, go in
 // workgroups of one pass instead (one_pass_each), if `spread` lets them, which it does where the stream has slots for
-// them at hand (ShortStreams): back to back and waited for, one of 8 KiB 8.1 -> 5.8 and 18.5 -> 17.0 us, with AAD
-// 10.1 -> 5.8 and 21.3 -> 17.0, 32 of 8 KiB 8.4 -> 6.5 and 19.7 -> 17.9, 64 of 4 KiB with AAD 8.4 -> 6.9 and 20.0 -> 18.5,
-// on any stream that has them.  Shorter ones are no better off (16 of 4 KiB 6.6 -> 6.3 and 18.5 -> 18.8, 64 of them
-// decrypted 6.7 -> 7.0), nor are more (120 of up to 8 KiB 9.0 -> 9.7).
+// them at hand (ShortStreams): back to back and waited for, one of 8 KiB 7.0 -> 5.1 and 17.5 -> 15.5 us, with AAD
+// 8.8 -> 5.0 and 19.2 -> 15.5, 32 of 8 KiB 7.6 -> 6.1 and 18.5 -> 16.7, 64 of 4 KiB with AAD 7.5 -> 6.5 and 18.6 -> 17.7,
+// on any stream that has them.  More of them are no better off (120 of up to 8 KiB 9.1 -> 9.2, decrypted 8.7 -> 9.1).  Chunks
+// of 129 to 256 blocks alone have a workgroup each, which dates from when up to eight wavefronts had two round tables to bring
+// in (16 of 4 KiB 6.6 -> 6.3 and 18.5 -> 18.8, 64 of them decrypted 6.7 -> 7.0); passes of 64 blocks would be better now (one
+// of 4 KiB 5.7 -> 4.7 and 15.9 -> 15.1, 16 of them 6.0 -> 5.8 and 17.0 -> 16.7, 64 of them 6.0 -> 5.9 and 17.3 -> 17.2,
+// decrypted 6.1 -> 6.0 and 17.3 either way), of 128 not (5.5, 6.8, 6.7 and 6.7).
 // Of more chunks than compute units, two workgroups share one: if `spread`, of at most
 // eight wavefronts and one pass, of which the longer chunks take several, if 512 of them do; otherwise of
-// sixteen and one pass, if 512 of these do (346 chunks of 1.6 to 8.1 KB 13.4 us, a workgroup each 16.2; 450 of up
-// to 8 KB 12.9, 14.7); otherwise of sixteen and a whole chunk, as also where a launch has to clear the slots (300 of up
-// to 8 KB on a stream with a captured batch 17.4 us with several workgroups a chunk, 13.9 with one each; in a graph,
-// where that launch costs less, 15.4 and 15.6: there they have several).  Longer chunks are spread over workgroups of
-// four or eight that make one pass (one_pass_each), or over as many of sixteen as there are compute units, with the
-// fewest passes that go: first with none spare, then with one for the first workgroup of each chunk, which is what a few blocks too many take (2 MiB
-// with AAD in 257 workgroups of two passes: 256 take 11.8 us, four passes in 129 took 14.8; 8 of
-// 256 KiB with AAD 12.3, were 14.7), then with one more (2.3 to 3 MB in three 12.1, in four 14.2).
+// sixteen and one pass, if 512 of these do (346 chunks of 1.6 to 8.1 KB 10.9 us, a workgroup each 13.6; 450 of up
+// to 8 KB 10.6, 13.2); otherwise of sixteen and a whole chunk, as also where a launch has to clear the slots (300 of up
+// to 8 KB on a stream with a captured batch, when each call passed 2.8 KB of arguments, 17.4 us with several workgroups a
+// chunk, 13.9 with one each; in a graph, where that launch costs less, 15.4 and 15.6: there they have several).  Longer
+// chunks are spread over workgroups of four or eight that make one pass (one_pass_each), or over as many of sixteen as there
+// are compute units, with the fewest passes that go: first with none spare, then with one for the first workgroup of each
+// chunk, which is what a few blocks too many take (back to back and waited for, 2 MiB with AAD, 257 workgroups of two passes if none had one to spare,
+// 9.9 and 20.2, in three passes 9.9 and 20.5; 8 of 256 KiB with AAD 9.9 and 20.2, in three 9.9 and 20.8), then with one more
+// (2.3 to 3 MB in three 10.0, 4 MiB in four 11.7).
 // What is left has more than four rows for each wavefront of the device, and takes units of eight rows or
 // sixteen, a wavefront each, with a workgroup of sixteen a compute unit.  Units of sixteen rows, and those of a
 // forced size, take the fewest wavefronts a workgroup, four at least, with which they still fit: chunks
@@ -222,13 +227,14 @@ inline bool swap_shape(const ShapeBatch& a, uint32_t num_cu, bool one_launch, ui
 
 // Where units of swap_kernel and spans could both take a batch of so many rows: are units no longer?  Spans
 // have fewer rows for a wavefront, as units are a power of two, but their descriptors are planned on the
-// host.  Units of eight rows take 46 us decrypting and 47.5 encrypting, whatever part of them is filled;
-// spans 21.5 and 3.75 a row of a wavefront, and 4 more on the host, which shows where a call is waited for
-// (back to back / waited for, units and spans: 12 of 2 MiB 47.4 / 60.4, 44.8 / 63.6; one of 28 MB
-// 47.5 / 60.1, 47.4 / 66.1; 14 of 2 MiB decrypted 46.3 / 59.1, 45.9 / 64.9; one of 31 MB decrypted
-// 46.4 / 59.1, 49.1 / 67.8).  Units of sixteen rows take 50 with eight wavefronts a workgroup (one of 32 MiB
-// 50.0 / 62.8, 52.0 / 71.0, decrypted 48.8 / 62.0, 51.0 / 70.2; 256 of 128 KiB 50.2 / 68.1, 51.2 / 73.0; 228 of
-// them, 7.1 rows a wavefront, back to back 50.1, 49.1) and 81 with sixteen, and spans no longer than that.
+// host.  Units of eight rows take 46 us, whatever part of them is filled; spans, at the clock of the machine that both
+// were timed on, 18 and 3.75 a row of a wavefront, and 5 to 8 more on the host, which shows where a call is waited for
+// (back to back / waited for, units and spans: 12 of 2 MiB 46.3 / 57.0, 42.3 / 58.9; one of 28 MB
+// 46.6 / 57.1, 45.9 / 62.4; 14 of 2 MiB decrypted 46.1 / 57.1, 42.7 / 61.6; one of 31 MB decrypted
+// 46.2 / 56.9, 45.3 / 63.8).  Units of sixteen rows take 49 with eight wavefronts a workgroup (one of 32 MiB
+// 49.2 / 59.6, 51.2 / 67.8, decrypted 48.6 / 59.3, 48.0 / 66.6; 256 of 128 KiB 49.3 / 64.0, 49.7 / 68.7, decrypted
+// 48.7 / 63.7, 46.3 / 67.8; 228 of them, 7.1 rows a wavefront, 49.0 / 64.0, 47.3 / 67.7) and 81 with sixteen, and spans no
+// longer than that.
 inline bool units_before_spans(const SwapShape& s, uint64_t rows, uint64_t wave_slots) {
     if (s.unit_power == kLongUnitPower) return 2 * rows >= 13 * wave_slots;
     return s.wave_power == 3 && 2 * rows >= 15 * wave_slots;
