@@ -38,8 +38,9 @@ __global__ void swap_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t iv
 // or, if it has a chunk to itself, as many as that takes.  It serves any key.  kLongIv: iv_len exceeds
 // kShortIvBytes.  kWords: at most eight wavefronts, one pass, and a wavefront more (which it counts on: a workgroup
 // has 2^wave_power + 1); kWordsShared: none more, and two workgroups fit a compute unit.  kFold: sixteen, and at most
-// kFoldPasses; kFoldApart: the same, decrypting, and faster where they are two; kSweep: kSweptPasses; kFoldShared:
-// kFoldPasses - 1, and two workgroups fit a compute unit.  Args: ArgOne (not of the shared kinds), ArgBatch or ArgStaged.
+// kFoldPasses; kFoldApart: the same, decrypting two, but for chunks' first workgroups of fewer or of one more; kSweep:
+// kSweptPasses; kFoldShared: kFoldPasses - 1, and two workgroups fit a compute unit.  Args: ArgOne (not of the shared
+// kinds), ArgBatch or ArgStaged.
 template <bool kDecrypt, bool kLongIv, BurstKind kKind, class Args>
 __global__ void burst_kernel(const KeyTables* kt, const uint8_t* ivs, uint32_t iv_len, SwapMeta meta,
                              ArriveSlot* slots, uint8_t* tags, uint8_t* ok, Args args);
